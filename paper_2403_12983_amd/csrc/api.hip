@@ -15,13 +15,19 @@ using namespace osscar;
 
 namespace {
 
-constexpr int64_t XT_ROWS = 4096;   // calibration rows per sub-step of the generic (non-MFMA-bf16) Gram path
+// calibration rows per launch of the generic (non-MFMA-bf16) Gram path: a bound on the kernel's 32-bit row index only
+constexpr int64_t GEN_ROWS = 1 << 20;
 constexpr int64_t PACK_ROWS = 16384;   // calibration rows repacked at a time on the bf16 MFMA path
-// staging buffer of the Gram phase: float32 X^T sub-step (generic path) or repacked bf16 rows (MFMA path)
+// Workspace of the 64 x 64 float64 products (partial tiles of a cut contraction): 1024 tiles, four workgroups per compute
+// unit, is as far as cutting pays; a layer that never reaches that many takes what its contractions can be cut into.
+size_t gemm_ws_bytes(int64_t d1, int64_t m) {
+  const int64_t t = ((d1 + 63) / 64) * ((std::max(d1, m) + 63) / 64);
+  return (size_t)std::min<int64_t>(1024, t * 64) * GEMM64_TILE_BYTES;
+}
+// staging buffer of the Gram phase: repacked bf16 rows (MFMA path)
 size_t rect_tile_entries(int64_t d1, int64_t m) { return (size_t)(((d1 + 127) / 128 + 3) / 4 * (((m + 127) / 128 + 7) / 8) + 8) * 32; }
-// staging of a target chunk: repacked bf16 rows (MFMA path) or a float32 sub-step (generic path)
-size_t target_stage_bytes(int64_t m) { return (size_t)std::max<int64_t>(XT_ROWS * m * 4, PACK_ROWS * ((m + 127) / 128 * 128) * 2); }
-size_t gram_stage_bytes(int64_t d1) { return (size_t)std::max<int64_t>(d1 * XT_ROWS * 4, PACK_ROWS * ((d1 + 127) / 128 * 128) * 2); }
+size_t target_stage_bytes(int64_t m) { return (size_t)(PACK_ROWS * ((m + 127) / 128 * 128) * 2); }
+size_t gram_stage_bytes(int64_t d1) { return (size_t)(PACK_ROWS * ((d1 + 127) / 128 * 128) * 2); }
 constexpr int EV_SAMPLES = 64;
 
 size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
@@ -105,6 +111,7 @@ struct osscar_ctx {
   int32_t *g_pick, *g_removed; float* g_gap;   // nested schedule from the dense layer
   int2 *tiles_sym, *tiles_rect;                // tile schedules of the bf16 matrix-core products (uploaded once at create)
   size_t n_tiles_sym = 0, n_tiles_rect = 0;
+  double* gemm_ws; size_t gemm_ws_size;        // partial tiles of the 64 x 64 float64 products (this stream only)
   int2* tiles_state;                           // two schedules of the corrections' products (shapes follow the kept count)
   std::vector<int2> tl_host[2];                // their host copies stay alive while the copies to the device are in flight
   int64_t counters[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -177,6 +184,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
   int2* tiles_sym = cv.take<int2>(gram_tile_entries(d1));
   int2* tiles_rect = cv.take<int2>(rect_tile_entries(d1, m));
   int2* tiles_state = cv.take<int2>(2 * state_tile_entries(d1, m));
+  double* gemm_ws = reinterpret_cast<double*>(cv.take<char>(gemm_ws_bytes(d1, m)));
   LazyPtrs L{};
   if (q == 1) {
     const int64_t TM = LAZY_TM;
@@ -222,6 +230,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
     c->trace_out = trace_out; c->trace_in = trace_in; c->trace_gap = trace_gap; c->trace_obj = trace_obj;
     c->g_pick = g_pick; c->g_removed = g_removed; c->g_gap = g_gap; c->Wdense = Wdense;
     c->tiles_sym = tiles_sym; c->tiles_rect = tiles_rect; c->tiles_state = tiles_state;
+    c->gemm_ws = gemm_ws; c->gemm_ws_size = gemm_ws_bytes(d1, m); L.gemm_ws = gemm_ws; L.gemm_ws_bytes = c->gemm_ws_size;
     c->scratch = scratch; c->scratch_bytes = scratch_bytes; c->lazy = L;
   }
   Layout lay; lay.total = cv.off; lay.scratch_bytes = scratch_bytes;
@@ -263,14 +272,14 @@ TabPtrs ptrs(const osscar_ctx* c) {
   return t;
 }
 
-hipError_t gemm(hipStream_t s, int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, const float* Cin,
+hipError_t gemm(const osscar_ctx* c, int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb, const float* Cin,
                 int64_t ldcin, float* C, int64_t ldc, double alpha, double beta, double diag_add = 0.0, int lower_only = 0,
                 int trans_b = 0, int acc_f32 = 0) {
   GemmArgs g{};
   g.M = M; g.N = N; g.K = K; g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.Cin = Cin; g.ldcin = ldcin; g.C = C; g.ldc = ldc;
   g.alpha = alpha; g.beta = beta; g.diag_add = diag_add; g.c_is_f64 = 0; g.lower_only = lower_only; g.trans_b = trans_b;
-  g.acc_f32 = acc_f32;
-  return launch_gemm_f64acc(g, s);
+  g.acc_f32 = acc_f32; g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
+  return launch_gemm_f64acc(g, c->stream);
 }
 
 // The large products that define the state (B = P G_K, V, S, R): on the int8 matrix cores (i8gemm.hip) when every dimension
@@ -283,7 +292,7 @@ struct I8Bufs {
 };
 constexpr int I8_MIN_DIM = 1024;
 bool g_i8_products = true;
-hipError_t big_gemm(hipStream_t s, const I8Bufs* ib, int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb,
+hipError_t big_gemm(const osscar_ctx* c, const I8Bufs* ib, int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb,
                     const float* Cin, int64_t ldcin, float* C, int64_t ldc, double alpha, double beta, double diag_add = 0.0,
                     int lower_only = 0, int diag_a = 0, int diag_b = 0, int ksign = 0) {
   GemmArgs g{};
@@ -293,8 +302,9 @@ hipError_t big_gemm(hipStream_t s, const I8Bufs* ib, int M, int N, int K, const 
   g.alpha = alpha; g.beta = beta; g.diag_add = diag_add; g.lower_only = lower_only;
   if (g_i8_products && ib && ib->packA && M >= I8_MIN_DIM && N >= I8_MIN_DIM && K >= I8_MIN_DIM && i8_gemm_fits(g) &&
       i8_pack_bytes(M, K) <= ib->capA && i8_pack_bytes(N, K) <= ib->capB && (size_t)M + (size_t)N <= ib->mx_entries)
-    return launch_i8_gemm(g, ib->packA, ib->capA, ib->packB, ib->capB, ib->mx, ib->mx_entries, s);
-  return launch_gemm_f64acc(g, s);
+    return launch_i8_gemm(g, ib->packA, ib->capA, ib->packB, ib->capB, ib->mx, ib->mx_entries, c->stream);
+  g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
+  return launch_gemm_f64acc(g, c->stream);
 }
 
 // Host copy of the membership flags -> sorted row lists on the device.
@@ -431,7 +441,7 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
     // few dominant directions of H (where P is 1e-4 and less of its norm), and five 7-bit digits per operand do not carry that:
     // with this one product on the int8 path the addition gains of the 28672-row benchmark layer came out 4 times further
     // from the float64 state (8e-5 against 2e-5), with all the others there they are unchanged.
-    HIPCHK(c, gemm(s, kr, kr, kr, b.HKK, kr, b.P, kr, nullptr, 0, b.T1, kr, -1.0, 0.0, 1.0));
+    HIPCHK(c, gemm(c, kr, kr, kr, b.HKK, kr, b.P, kr, nullptr, 0, b.T1, kr, -1.0, 0.0, 1.0));
     HIPCHK(c, hipEventRecord(c->ev_s[2][1], s));
     HIPCHK(c, launch_absmax(b.T1, (int64_t)kr * kr, c->partial, s));
     // P + P (I - H P) is symmetric up to rounding: compute its lower triangle and mirror it.  The correction P (I - H P) is
@@ -443,7 +453,7 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
       if ((st = pack_into(c, *sp, sp->packX, b.T1, kr, kr, kr)) != OSSCAR_OK) return st;
       if ((st = split_gemm(c, *sp, sp->packP, kr, sp->packX, kr, kr, 3, t_low, b.P, kr, b.T2, kr, 1.0, 1.0)) != OSSCAR_OK) return st;
     } else {
-      HIPCHK(c, gemm(s, kr, kr, kr, b.P, kr, b.T1, kr, b.P, kr, b.T2, kr, 1.0, 1.0, 0.0, 1, 0, 1));
+      HIPCHK(c, gemm(c, kr, kr, kr, b.P, kr, b.T1, kr, b.P, kr, b.T2, kr, 1.0, 1.0, 0.0, 1, 0, 1));
     }
     HIPCHK(c, hipEventRecord(c->ev_s[1][1], s));
     hipLaunchKernelGGL(mirror_from_lower_kernel, dim3(grid_for((int64_t)kr * kr)), dim3(256), 0, s, b.T2, b.P, kr);
@@ -476,15 +486,15 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
     return OSSCAR_OK;
   }
   float* B0 = correct ? b.T3 : b.B;
-  HIPCHK(c, big_gemm(s, b.i8, kr, m, kr, b.P, kr, b.GK, m, nullptr, 0, B0, m, 1.0, 0.0, 0.0, 0, 1, 0, 1));
+  HIPCHK(c, big_gemm(c, b.i8, kr, m, kr, b.P, kr, b.GK, m, nullptr, 0, B0, m, 1.0, 0.0, 0.0, 0, 1, 0, 1));
   if (!correct) return OSSCAR_OK;
-  HIPCHK(c, gemm(s, kr, m, kr, b.HKK, kr, b.T3, m, b.GK, m, b.T4, m, -1.0, 1.0));      // the residual: float64 accumulation
+  HIPCHK(c, gemm(c, kr, m, kr, b.HKK, kr, b.T3, m, b.GK, m, b.T4, m, -1.0, 1.0));      // the residual: float64 accumulation
   if (sp) {
     if ((st = pack_into(c, *sp, sp->packP, b.P, kr, kr, kr)) != OSSCAR_OK) return st;      // the refined inverse
     if ((st = pack_into(c, *sp, sp->packX, b.T4, m, kr, m)) != OSSCAR_OK) return st;
     if ((st = split_gemm(c, *sp, sp->packP, kr, sp->packX, m, kr, 3, t_b, b.T3, m, b.B, m, 1.0, 1.0)) != OSSCAR_OK) return st;
   } else {
-    HIPCHK(c, gemm(s, kr, m, kr, b.P, kr, b.T4, m, b.T3, m, b.B, m, 1.0, 1.0));
+    HIPCHK(c, gemm(c, kr, m, kr, b.P, kr, b.T4, m, b.T3, m, b.B, m, 1.0, 1.0));
   }
   return OSSCAR_OK;
 }
@@ -560,9 +570,9 @@ osscar_status build_state(osscar_ctx* c, double* obj_out, const float* B_known =
     HIPCHK(c, launch_gather(c->G, m, c->rowsC, cr, nullptr, m, R, m, s));
     HIPCHK(c, hipEventRecord(c->ev_s[0][0], s));
     HIPCHK(c, launch_gather(c->H, d1, c->rowsC, cr, c->rowsK, kr, HCK, kr, s));
-    HIPCHK(c, big_gemm(s, b.i8, kr, cr, kr, b.P, kr, HKC, cr, nullptr, 0, V, cr, 1.0, 0.0, 0.0, 0, 1, 0, 1));   // V = P H_{K,Kc}
-    HIPCHK(c, big_gemm(s, b.i8, cr, cr, kr, HCK, kr, V, cr, S, cr, S, cr, -1.0, 1.0, 0.0, 1, 0, 0, -1));   // S = H_cc - H_cK V (lower)
-    HIPCHK(c, big_gemm(s, b.i8, cr, m, kr, HCK, kr, b.B, m, R, m, R, m, -1.0, 1.0, 0.0, 0, 0, 0, -1));     // R = G_c - H_cK B
+    HIPCHK(c, big_gemm(c, b.i8, kr, cr, kr, b.P, kr, HKC, cr, nullptr, 0, V, cr, 1.0, 0.0, 0.0, 0, 1, 0, 1));   // V = P H_{K,Kc}
+    HIPCHK(c, big_gemm(c, b.i8, cr, cr, kr, HCK, kr, V, cr, S, cr, S, cr, -1.0, 1.0, 0.0, 1, 0, 0, -1));   // S = H_cc - H_cK V (lower)
+    HIPCHK(c, big_gemm(c, b.i8, cr, m, kr, HCK, kr, b.B, m, R, m, R, m, -1.0, 1.0, 0.0, 0, 0, 0, -1));     // R = G_c - H_cK B
     HIPCHK(c, hipEventRecord(c->ev_s[0][1], s));
     HIPCHK(c, launch_scatter(V, cr, c->rowsK, kr, c->rowsC, cr, c->N, d1, 1.f, 0, s));
     HIPCHK(c, launch_scatter(S, cr, c->rowsC, cr, c->rowsC, cr, c->N, d1, 1.f, 1, s));
@@ -691,11 +701,11 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   Carve cv(c->scratch);
   double* H64 = cv.take<double>((int64_t)d1 * d1);
   float* Wf = cv.take<float>((int64_t)d1 * m);
-  float* Xt = reinterpret_cast<float*>(cv.take<char>(gram_stage_bytes(d1)));
-  double* G64 = nullptr; float* Ys = nullptr;
+  void* Xt = cv.take<char>(gram_stage_bytes(d1));
+  double* G64 = nullptr; void* Ys = nullptr;
   if (c->desc.target_output) {
     G64 = cv.take<double>((int64_t)d1 * m);
-    Ys = reinterpret_cast<float*>(cv.take<char>(target_stage_bytes(m)));
+    Ys = cv.take<char>(target_stage_bytes(m));
   }
   if (c->phase != osscar_ctx::ACCUM) {   // first chunk of a layer
     hipLaunchKernelGGL(fill_f64_kernel, dim3(grid_for((int64_t)d1 * d1)), dim3(256), 0, s, H64, (int64_t)d1 * d1, 0.0);
@@ -722,24 +732,24 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
         c->ev_g_rows = n_c;
       }
     } else {
+      // any alignment and float32: float64 sums straight from the caller's rows; patches are written out as rows first, as
+      // many at a time as the staging buffer holds
       const size_t esz = bf16 ? 2 : 4;
-      for (int64_t r0 = 0; r0 < n_c; r0 += XT_ROWS) {
-        int64_t nr = std::min<int64_t>(XT_ROWS, n_c - r0);
-        const char* src = reinterpret_cast<const char*>(Xc) + (size_t)r0 * ldx * esz;
-        if (conv) HIPCHK(c, launch_im2col_transpose(Xc, bf16, *conv, r0, nr, d1, Xt, XT_ROWS, s));
-        else HIPCHK(c, launch_transpose_to_f32(src, bf16, nr, d1, ldx, Xt, XT_ROWS, s));
-        GemmArgs g{};
-        g.M = d1; g.N = d1; g.K = (int)nr; g.A = Xt; g.lda = XT_ROWS; g.B = Xt; g.ldb = XT_ROWS; g.trans_b = 1;
-        g.Cin = reinterpret_cast<const float*>(H64); g.ldcin = d1; g.C = H64; g.ldc = d1; g.alpha = 1.0; g.beta = 1.0;
-        g.c_is_f64 = 1; g.lower_only = 1;
-        HIPCHK(c, launch_gemm_f64acc(g, s));
-        if (target) {   // G64 += Xt (d1 x nr) * Yc (nr x m)
-          const char* srcy = reinterpret_cast<const char*>(Yc) + (size_t)r0 * ldy * esz;
-          HIPCHK(c, launch_convert_to_f32(srcy, bf16, nr, m, ldy, Ys, s));
-          GemmArgs y{};
-          y.M = d1; y.N = m; y.K = (int)nr; y.A = Xt; y.lda = XT_ROWS; y.B = Ys; y.ldb = m;
-          y.Cin = reinterpret_cast<const float*>(G64); y.ldcin = m; y.C = G64; y.ldc = m; y.alpha = 1.0; y.beta = 1.0; y.c_is_f64 = 1;
-          HIPCHK(c, launch_gemm_f64acc(y, s));
+      const int64_t most = conv ? (int64_t)(gram_stage_bytes(d1) / ((size_t)d1 * 4)) : GEN_ROWS;
+      for (int64_t r0 = 0; r0 < n_c; r0 += most) {
+        const int64_t nr = std::min<int64_t>(most, n_c - r0);
+        if (conv) HIPCHK(c, launch_im2col_rows(Xc, bf16, *conv, r0, nr, d1, reinterpret_cast<float*>(Xt), s));
+        const void* src = conv ? Xt : reinterpret_cast<const char*>(Xc) + (size_t)r0 * ldx * esz;
+        Gemm64 g{};      // H64 += Xc^T Xc
+        g.M = d1; g.N = d1; g.K = (int)nr; g.lower = 1; g.A = g.B = src; g.lda = g.ldb = conv ? d1 : ldx;
+        g.a_kind = g.b_kind = (bf16 && !conv) ? OPK_K_BF16 : OPK_K_F32;
+        g.Cin = H64; g.ldcin = d1; g.C = H64; g.ldc = d1; g.c_is_f64 = 1; g.alpha = 1.0; g.beta = 1.0; g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
+        HIPCHK(c, launch_gemm64(g, s));
+        if (target) {      // G64 += Xc^T Yc
+          Gemm64 y = g;
+          y.N = m; y.lower = 0; y.B = reinterpret_cast<const char*>(Yc) + (size_t)r0 * ldy * esz; y.ldb = ldy;
+          y.Cin = G64; y.ldcin = m; y.C = G64; y.ldc = m;
+          HIPCHK(c, launch_gemm64(y, s));
         }
       }
     }
@@ -783,7 +793,14 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
       HIPCHK(c, launch_hw_split(c->H, d1, W, ldw, m, Gacc, c->tiles_rect, c->n_tiles_rect, pack_h, pack_w, prow, s));
       HIPCHK(c, launch_finalize_G(Gacc, Wf, c->scal + 13, c->G, (int64_t)d1 * m, s));
     } else {
-      HIPCHK(c, gemm(s, d1, m, d1, c->H, d1, Wf, m, nullptr, 0, c->G, m, 1.0, 0.0));
+      if (d1 % 4 == 0 && m % 4 == 0 && (int64_t)((d1 + 127) / 128) * ((m + 127) / 128) >= 768) {
+        HIPCHK(c, gemm(c, d1, m, d1, c->H, d1, Wf, m, nullptr, 0, c->G, m, 1.0, 0.0));      // the size of the 128 x 128 tiles
+      } else {
+      Gemm64 g{};      // H is symmetric: its rows serve as the columns that the product contracts
+      g.M = d1; g.N = m; g.K = d1; g.a_kind = OPK_K_F32; g.A = c->H; g.lda = d1; g.b_kind = OPK_K_F32; g.B = Wf; g.ldb = m;
+      g.C = c->G; g.ldc = m; g.alpha = 1.0; g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
+      HIPCHK(c, launch_gemm64(g, s));
+      }
     }
     HIPCHK(c, hipEventRecord(c->ev_s[0][1], s));
     HIPCHK(c, launch_dot64(Wf, c->G, (int64_t)d1 * m, c->scal + 2, c->partial, s));
@@ -1327,14 +1344,14 @@ osscar_status osscar_backsolve(osscar_ctx* c, void* What, int64_t ldw_hat, int32
     for (int step = 0; step < 3 && !ok; step++) {
       // residual, sums exact: H_KK levelled along k and the weights B have no entries far below their row / column maxima,
       // so the int8 digits carry both operands whole (unlike a residual that involves P)
-      HIPCHK(c, big_gemm(s, b.i8, kr, m, kr, b.HKK, kr, b.B, m, b.GK, m, b.T4, m, -1.0, 1.0, 0.0, 0, 0, 0, -1));
+      HIPCHK(c, big_gemm(c, b.i8, kr, m, kr, b.HKK, kr, b.B, m, b.GK, m, b.T4, m, -1.0, 1.0, 0.0, 0, 0, 0, -1));
       // the correction is small, a few digits of it are enough: float32 accumulation, or the three leading products of
       // the bf16 pieces
       if (split) {
         if ((st = pack_into(c, sp, sp.packX, b.T4, m, kr, m)) != OSSCAR_OK) return st;
         if ((st = split_gemm(c, sp, sp.packP, kr, sp.packX, m, kr, 3, t_b, nullptr, 0, b.T3, m, 1.0, 0.0)) != OSSCAR_OK) return st;
       } else {
-        HIPCHK(c, gemm(s, kr, m, kr, b.P, kr, b.T4, m, nullptr, 0, b.T3, m, 1.0, 0.0, 0.0, 0, 0, 1));
+        HIPCHK(c, gemm(c, kr, m, kr, b.P, kr, b.T4, m, nullptr, 0, b.T3, m, 1.0, 0.0, 0.0, 0, 0, 1));
       }
       HIPCHK(c, launch_dot64(b.T3, b.T3, (int64_t)kr * m, c->scal + 9, c->partial, s));
       HIPCHK(c, launch_dot64(b.B, b.B, (int64_t)kr * m, c->scal + 10, c->partial + 1024, s));

@@ -423,6 +423,15 @@ hipError_t launch_gemm_f64acc(const GemmArgs& a, hipStream_t s) {
   return r;
 }
 
+// Which of the two float64-accumulating kernels.  The 128 x 128 one needs about four rounds of two workgroups per compute
+// unit to show its rate and 16-byte loads of both operands: 4096^3 2.26 ms against 2.70 ms of the 64 x 64 one, 8192 x 2048 x
+// 8192 4.38 against 5.39 ms (1024 tiles each), but 1536 x 2048 x 1536 (192 tiles) 0.43 against 0.23 ms, 5461 x 1365 x 5461 (473
+// tiles, unaligned rows) 3.55 against 1.98 ms, and a lower triangle of 7000 (1540 tiles, padding tiles among them) 7.6 against 7.2 ms.
+static bool big_tiles_pay(const GemmArgs& a, bool vec) {
+  const int64_t tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
+  return vec && (a.lower_only ? tm * (tm + 1) / 2 >= 3072 : tm * tn >= 768);
+}
+
 static hipError_t launch_gemm_impl(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   const int blocks = grid_blocks(a);
@@ -431,6 +440,14 @@ static hipError_t launch_gemm_impl(const GemmArgs& a, hipStream_t s) {
   int vecC = (!a.c_is_f64) && (a.ldc % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.C) & 15) == 0) &&
              (a.Cin == nullptr || ((a.ldcin % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.Cin) & 15) == 0)));
   if (a.acc_f32 && a.c_is_f64) return hipErrorInvalidValue;      // float32 accumulation has float32 output only
+  // (a product that may accumulate in float32 takes it too: 1499 x 1003 x 1499 in 0.13 ms against 0.37 ms of 96 large tiles)
+  if (!big_tiles_pay(a, vecA && vecB)) {
+    Gemm64 q{};
+    q.M = a.M; q.N = a.N; q.K = a.K; q.a_kind = OPK_ROW_F32; q.b_kind = a.trans_b ? OPK_ROW_F32 : OPK_K_F32; q.lower = a.lower_only;
+    q.A = a.A; q.lda = a.lda; q.B = a.B; q.ldb = a.ldb; q.Cin = a.Cin; q.ldcin = a.ldcin; q.C = a.C; q.ldc = a.ldc; q.c_is_f64 = a.c_is_f64;
+    q.alpha = a.alpha; q.beta = a.beta; q.diag_add = a.diag_add; q.ws = a.ws; q.ws_bytes = a.ws_bytes;
+    return launch_gemm64(q, s);
+  }
   if (a.acc_f32)
     hipLaunchKernelGGL(gemm_f32acc_kernel, dim3(blocks), dim3(256), 0, s, a, vecA, vecB, vecC);
   else if (a.c_is_f64)

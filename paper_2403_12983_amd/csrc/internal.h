@@ -30,6 +30,8 @@ struct GemmArgs {
   int i8_diag_a, i8_diag_b;
   // and a levelling of the contraction index: A is used as A 2^(ksign kexp[k]), B as 2^(-ksign kexp[k]) B (nullptr: none)
   const int* i8_kexp; int i8_ksign;
+  // workspace of the 64 x 64 kernel (gemm64.hip) for the partial tiles of a cut contraction (nullptr: it never cuts)
+  double* ws; size_t ws_bytes;
 };
 hipError_t launch_gemm_f64acc(const GemmArgs& a, hipStream_t s);
 // diagnostic log of the launches above: enable (1) / disable and clear (0); read = rows of {M, N, K, kind, ms} with
@@ -39,6 +41,22 @@ void gemm_log_enable(int on);
 int gemm_log_read(double* out, int capacity);
 void gemm_log_open(int M, int N, int K, int kind, hipStream_t s, int* slot);
 void gemm_log_close(int slot, hipStream_t s);
+
+// ----------------------------------------------------------------------------------------------
+// gemm64.hip : the same product in 64 x 64 tiles, the contraction cut into ranges where the tiles alone do not fill the chip,
+// and from operands as the caller holds them
+// ----------------------------------------------------------------------------------------------
+// ROW: result rows x K, float32.  K_*: K x result rows, contraction along the rows.
+enum Opk64 { OPK_ROW_F32 = 0, OPK_K_F32 = 1, OPK_K_BF16 = 2 };
+struct Gemm64 {
+  int M, N, K, a_kind, b_kind, lower;
+  const void* A; int64_t lda; const void* B; int64_t ldb;
+  const void* Cin; int64_t ldcin; void* C; int64_t ldc; int c_is_f64;
+  double alpha, beta, diag_add;
+  double* ws; size_t ws_bytes;                // partial tiles of a cut contraction (none: never cut)
+};
+constexpr size_t GEMM64_TILE_BYTES = 64 * 64 * 8;
+hipError_t launch_gemm64(const Gemm64& q, hipStream_t s);
 
 // ----------------------------------------------------------------------------------------------
 // i8gemm.hip : the same product C = alpha A B + beta Cin (+ diag_add on the diagonal; lower_only) for float32 A, B, Cin, C
@@ -74,9 +92,6 @@ hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, 
 void gram_tile_list_host(int d1, std::vector<int2>& out);
 void rect_tile_list_host(int d1, int m, std::vector<int2>& out);
 // conv (optional): Xc is a feature map (NCHW, bf16) and the rows are its patches
-// Xt[c][r - r0] = patch matrix entry (r, c) as float32 for rows r0 .. r0 + nr (generic path of convolutional layers)
-hipError_t launch_im2col_transpose(const void* F, int is_bf16, const ConvSpec& cs, int64_t r0, int64_t nr, int d1, float* Xt,
-                                   int64_t ldxt, hipStream_t s);
 // Yc (optional, bf16 n_c x m): also G64 (d1 x m, float64) += Xc^T Yc, with its own tile list (>= 8 * (ceil(d1/128) *
 // ceil(m/128) / 8 + 64) entries) and pack buffer (pack_rows * 128*ceil(m/128) * 2 bytes)
 int gram_tile_schedule(int tiles_per_side, int32_t* out, int capacity);   // host only: the tile order of the SYRK kernel
@@ -97,12 +112,12 @@ hipError_t launch_split_epilogue(const double* acc, int M, int N, const float* C
 hipError_t launch_sumsq(const void* A, int is_bf16, int64_t rows, int64_t cols, int64_t ld, double* acc, double* partial,
                         hipStream_t s);   // partial: 1024 doubles
 hipError_t launch_finalize_G(const double* G64, const float* Wf, const double* lambda_dev, float* G, int64_t n, hipStream_t s);
-hipError_t launch_transpose_to_f32(const void* X, int is_bf16, int64_t rows, int64_t cols, int64_t ldx, float* Xt,
-                                   int64_t ldxt, hipStream_t s);
 // H = float(mirror(H64) + lam*I); also usable with lam = 0
 hipError_t launch_finalize_H(const double* H64, float* H, int d1, const double* lam_dev, hipStream_t s);
 // out[0] = sum_i H64[i][i]
 hipError_t launch_trace64(const double* H64, int d1, double* out, hipStream_t s);
+// rows r0 .. r0 + nr of the patch matrix as float32, nr x d1
+hipError_t launch_im2col_rows(const void* F, int is_bf16, const ConvSpec& cs, int64_t r0, int64_t nr, int d1, float* out, hipStream_t s);
 hipError_t launch_convert_to_f32(const void* src, int is_bf16, int64_t rows, int64_t cols, int64_t lds, float* dst,
                                  hipStream_t s);
 // norms2[j] = sum over group j of W^2 (float64); c0 = sum W*G
@@ -220,6 +235,7 @@ struct LazyPtrs {
   // tile schedules of the two updates (the Gram kernel's: lower triangle of d1 x d1, all of d1 x m), uploaded at create
   void* Epk; void* Cpk; void* Zpk;
   const int2* tiles_sym; size_t n_tiles_sym; const int2* tiles_rect; size_t n_tiles_rect;
+  double* gemm_ws; size_t gemm_ws_bytes;      // workspace of the 64 x 64 products (shapes that take the general kernels)
   void* ZcP;        // LAZY_NC x 32*ceil(m/32) x 3 bf16: the candidate rows cut into three bf16 pieces, in matrix-core operand order
   int32_t* cslot;   // d1: slot of a row in GbT or -1
   int32_t* cand;    // LAZY_NC + LAZY_NS: row held by a slot or -1

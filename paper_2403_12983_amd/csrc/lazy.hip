@@ -1065,7 +1065,7 @@ static hipError_t launch_candidate_products(const TabDims& d, const TabPtrs& t, 
   hipLaunchKernelGGL(cand_gather_kernel, dim3(n_k + n_c), dim3(256), 0, s, L, t.Z, d.m);
   GemmArgs g{};                         // GbT[0 .. LAZY_NC) = Zc Z0^T, float64 accumulation and output
   g.M = n_k + n_c; g.N = d.d1; g.K = d.m; g.A = L.Zc; g.lda = d.m; g.B = t.Z; g.ldb = d.m; g.trans_b = 1;
-  g.C = L.GbT; g.ldc = d.d1; g.alpha = 1.0; g.beta = 0.0; g.c_is_f64 = 1;
+  g.C = L.GbT; g.ldc = d.d1; g.alpha = 1.0; g.beta = 0.0; g.c_is_f64 = 1; g.ws = L.gemm_ws; g.ws_bytes = L.gemm_ws_bytes;
   return launch_gemm_f64acc(g, s);
 }
 static hipError_t launch_candidates(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {

@@ -14,10 +14,10 @@ using namespace osscar;
 namespace {
 
 constexpr int64_t ST_MAX = OSSCAR_STATIC_MAX_DIM;      // largest d1 and m
-constexpr int64_t ST_XT_ROWS = 2048;                   // calibration rows per sub-step
-constexpr size_t ST_H64 = (size_t)ST_MAX * ST_MAX * 8, ST_WF = (size_t)ST_MAX * ST_MAX * 4, ST_XT = (size_t)ST_MAX * ST_XT_ROWS * 4;
+constexpr int64_t ST_ROWS = 1 << 20;                     // calibration rows per launch (the kernel's row index is 32 bits wide)
+constexpr size_t ST_H64 = (size_t)ST_MAX * ST_MAX * 8, ST_WF = (size_t)ST_MAX * ST_MAX * 4, ST_PART = (size_t)ST_MAX * 8192;      // accumulator, W, partial tiles
 constexpr size_t ST_SMALL = 64 * 1024;                 // scalars and the partial sums of the reductions
-constexpr size_t ST_BYTES = ST_H64 + ST_WF + ST_XT + ST_SMALL;
+constexpr size_t ST_BYTES = ST_H64 + ST_WF + ST_PART + ST_SMALL;
 static_assert(ST_BYTES == OSSCAR_STATIC_SCRATCH_BYTES, "the header states the size of the array");
 
 // One copy per GPU, at its own address on each, for as long as the process lives.  In host code this name is only a
@@ -76,25 +76,21 @@ extern "C" osscar_status osscar_gram_static(const void* X_dev, int64_t n, int64_
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   double* H64 = reinterpret_cast<double*>(base);
   float* Wf = reinterpret_cast<float*>(base + ST_H64);
-  float* Xt = reinterpret_cast<float*>(base + ST_H64 + ST_WF);
-  double* scal = reinterpret_cast<double*>(base + ST_H64 + ST_WF + ST_XT);      // 64 scalars, then 2048 partial sums
+  double* part = reinterpret_cast<double*>(base + ST_H64 + ST_WF);
+  double* scal = reinterpret_cast<double*>(base + ST_H64 + ST_WF + ST_PART);      // 64 scalars, then 2048 partial sums
   double* partial = scal + 64;
   const int D = (int)d1, M = (int)m;
   const bool xbf = x_dtype == OSSCAR_BF16;
-  // the array keeps the last call's contents: the accumulator starts at zero, everything else is written before it is read
-  hipLaunchKernelGGL(st_fill_f64_kernel, dim3((unsigned)std::min<int64_t>((d1 * d1 + 1023) / 1024, 4096)), dim3(256), 0, s, H64, d1 * d1, 0.0);
-  const size_t esz = xbf ? 2 : 4;
+  // the array keeps the last call's contents; everything in it is written before it is read
   hipError_t e = hipSuccess;
-  for (int64_t r0 = 0; r0 < n && e == hipSuccess; r0 += ST_XT_ROWS) {
-    const int64_t nr = std::min<int64_t>(ST_XT_ROWS, n - r0);
-    const char* src = reinterpret_cast<const char*>(X_dev) + (size_t)r0 * ldx * esz;
-    e = launch_transpose_to_f32(src, xbf, nr, d1, ldx, Xt, ST_XT_ROWS, s);
-    if (e != hipSuccess) break;
-    GemmArgs g{};      // H64 += Xt Xt^T on the lower triangle, float64 accumulation on the matrix cores
-    g.M = D; g.N = D; g.K = (int)nr; g.A = Xt; g.lda = ST_XT_ROWS; g.B = Xt; g.ldb = ST_XT_ROWS; g.trans_b = 1;
-    g.Cin = reinterpret_cast<const float*>(H64); g.ldcin = D; g.C = H64; g.ldc = D; g.alpha = 1.0; g.beta = 1.0;
-    g.c_is_f64 = 1; g.lower_only = 1;
-    e = launch_gemm_f64acc(g, s);
+  const size_t esz = xbf ? 2 : 4;
+  if (n == 0) hipLaunchKernelGGL(st_fill_f64_kernel, dim3((unsigned)std::min<int64_t>((d1 * d1 + 1023) / 1024, 4096)), dim3(256), 0, s, H64, d1 * d1, 0.0);
+  for (int64_t r0 = 0; r0 < n && e == hipSuccess; r0 += ST_ROWS) {
+    Gemm64 g{};      // H64 (+)= X^T X on the lower triangle, float64 sums on the matrix cores
+    g.M = D; g.N = D; g.K = (int)std::min<int64_t>(ST_ROWS, n - r0); g.lower = 1;
+    g.A = g.B = reinterpret_cast<const char*>(X_dev) + (size_t)r0 * ldx * esz; g.lda = g.ldb = ldx; g.a_kind = g.b_kind = xbf ? OPK_K_BF16 : OPK_K_F32;
+    g.Cin = r0 ? H64 : nullptr; g.ldcin = D; g.C = H64; g.ldc = D; g.c_is_f64 = 1; g.alpha = 1.0; g.beta = 1.0; g.ws = part; g.ws_bytes = ST_PART;
+    e = launch_gemm64(g, s);
   }
   if (e == hipSuccess) e = launch_trace64(H64, D, scal, s);
   if (e == hipSuccess) {
@@ -103,9 +99,10 @@ extern "C" osscar_status osscar_gram_static(const void* X_dev, int64_t n, int64_
   }
   if (e == hipSuccess) e = launch_convert_to_f32(W_dev, w_dtype == OSSCAR_BF16, d1, m, ldw, Wf, s);
   if (e == hipSuccess) {
-    GemmArgs g{};      // G = H W
-    g.M = D; g.N = M; g.K = D; g.A = H_dev; g.lda = D; g.B = Wf; g.ldb = M; g.C = G_dev; g.ldc = M; g.alpha = 1.0; g.beta = 0.0;
-    e = launch_gemm_f64acc(g, s);
+    Gemm64 g{};      // G = H W (H is symmetric: its rows serve as the columns that the product contracts)
+    g.M = D; g.N = M; g.K = D; g.A = H_dev; g.lda = D; g.a_kind = OPK_K_F32; g.B = Wf; g.ldb = M; g.b_kind = OPK_K_F32; g.C = G_dev; g.ldc = M;
+    g.alpha = 1.0; g.ws = part; g.ws_bytes = ST_PART;
+    e = launch_gemm64(g, s);
   }
   if (e == hipSuccess) e = launch_dot64(Wf, G_dev, d1 * m, scal + 2, partial, s);      // c0 = Tr(W^T G)
   if (e == hipSuccess) {
