@@ -444,42 +444,157 @@ __global__ __launch_bounds__(256) void narrow_negate_mirror_kernel(const double*
     }
   }
 }
-__global__ __launch_bounds__(256) void extract_panel64_kernel(const double* __restrict__ N, int64_t ld, int n, int t0, int w,
-                                                               double* __restrict__ C) {
-  __shared__ double T[PANEL_ROWS64][129];
-  const int i0 = blockIdx.x * PANEL_ROWS64, tid = threadIdx.x;
+typedef double swd4 __attribute__((ext_vector_type(4)));
+// lane k of each row of 16 lanes, to all 16 of them
+template <int K>
+__device__ __forceinline__ double row16_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + K, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + K, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+// Pivots K.. of the Gauss-Jordan inverse of a 16 x 16 block that one wave holds like a result of v_mfma_f64_16x16x4_f64:
+// x[r] = element (4 r + lane / 16, lane % 16).  The pivot row crosses the rows of lanes by one ds_bpermute (two dwords),
+// the pivot column and the pivot itself by DPP broadcasts.
+template <int K>
+__device__ __forceinline__ void inv16_steps(swd4& x, int lane, bool& flag) {
+  if constexpr (K < 16) {
+    const int from = (((K & 3) << 4) | (lane & 15)) << 2;
+    const double mine = x[K >> 2];
+    const double row = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(mine)),
+                                        __builtin_amdgcn_ds_bpermute(from, __double2loint(mine)));
+    double piv = row16_bcast<K>(row);
+    if (!(piv > 0.0)) { flag = true; piv = 1.0; }
+    const double d = 1.0 / piv, rs = row * d;
+    const bool pcol = (lane & 15) == K, prow = (lane >> 4) == (K & 3);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const double c = row16_bcast<K>(x[r]);
+      const double v = x[r] - c * rs;
+      x[r] = pcol ? -c * d : v;
+    }
+    if (prow) x[K >> 2] = pcol ? d : rs;
+    inv16_steps<K + 1>(x, lane, flag);
+  }
+}
+
+constexpr int IB_T = 768, IB_LD = 17;                  // 12 waves x 3 of the 36 lower 16 x 16 tiles of the pivot block
+struct InvBlockLds { double Pn[2][8][16][IB_LD], Q[8][16][IB_LD], D[2][16][IB_LD]; };
+// D (w x w) = inverse of the pivot block N[t0.., t0..] (lower triangle read, w <= 128), by one workgroup of 768 threads.
+// The symmetric sweep 16 pivots at a time: the tiles of tile column kb go to LDS as P, Q = P D on the matrix cores, every
+// other tile takes -= Q P^T, tile column kb becomes Q and its diagonal tile -D, so that -N is the inverse at the end.  What
+// bounds it is the chain of 128 pivots (one wave, about 0.1 us each), so the wave that owns the next diagonal tile updates that
+// one first and inverts it while the other waves finish their tiles.  Rows and columns past w behave as an identity block.
+__device__ void inv_block128(const double* __restrict__ N, int64_t ld, int t0, int w, double* __restrict__ D, int32_t* notpd, InvBlockLds& L) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  const int nb = (w + 15) / 16;
+  int ti[3], tj[3];
+  swd4 x[3];
+  bool flag = false;
+#pragma unroll
+  for (int s = 0; s < 3; s++) {
+    const int t = wave + 12 * s;
+    int I = 0;
+    while ((I + 1) * (I + 2) / 2 <= t) I++;
+    ti[s] = __builtin_amdgcn_readfirstlane(I); tj[s] = __builtin_amdgcn_readfirstlane(t - I * (I + 1) / 2);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
+      const int hi = i > j ? i : j, lo = i > j ? j : i;
+      x[s][r] = hi < w ? N[(int64_t)(t0 + hi) * ld + t0 + lo] : (i == j ? 1.0 : 0.0);
+    }
+  }
+  auto invert = [&](const swd4& a, int kb) {
+    swd4 y = a;
+    inv16_steps<0>(y, lane, flag);
+#pragma unroll
+    for (int r = 0; r < 4; r++) L.D[kb & 1][4 * r + lr][lc] = y[r];
+  };
+  if (wave == 0) invert(x[0], 0);
+  for (int kb = 0; kb < nb; kb++) {
+    double (*P)[16][IB_LD] = L.Pn[kb & 1];
+    double (*Dk)[IB_LD] = L.D[kb & 1];
+#pragma unroll
+    for (int s = 0; s < 3; s++) {
+      if (tj[s] == kb && ti[s] > kb) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) P[ti[s]][4 * r + lr][lc] = x[s][r];
+      } else if (ti[s] == kb && tj[s] < kb) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) P[tj[s]][lc][4 * r + lr] = x[s][r];
+      }
+    }
+    __syncthreads();
+    if (wave < nb && wave != kb) {
+      swd4 q = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++)
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(P[wave][lc][kk * 4 + lr], Dk[kk * 4 + lr][lc], q, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; r++) L.Q[wave][4 * r + lr][lc] = q[r];
+    }
+    __syncthreads();
+    auto update = [&](int s) {
+      const int I = ti[s], J = tj[s];
+      if (I >= nb) return;
+      if (I != kb && J != kb) {
+#pragma unroll
+        for (int kk = 0; kk < 4; kk++)
+          x[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(-L.Q[I][lc][kk * 4 + lr], P[J][lc][kk * 4 + lr], x[s], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+          x[s][r] = I > kb ? L.Q[I][4 * r + lr][lc] : J < kb ? L.Q[J][lc][4 * r + lr] : -Dk[4 * r + lr][lc];
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < 3; s++)
+      if (ti[s] == kb + 1 && tj[s] == kb + 1 && kb + 1 < nb) { update(s); invert(x[s], kb + 1); }
+#pragma unroll
+    for (int s = 0; s < 3; s++)
+      if (!(ti[s] == kb + 1 && tj[s] == kb + 1)) update(s);
+  }
+  if (__any(flag) && lane == 0) *notpd = 1;
+#pragma unroll
+  for (int s = 0; s < 3; s++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
+      if (i < w && j <= i) { D[i * w + j] = -x[s][r]; D[j * w + i] = -x[s][r]; }
+    }
+}
+
+// C = the pivot columns t0 .. t0 + w of N for every row, and (the first workgroup) D = the inverse of the pivot block,
+// straight from N, so that the copy runs beside the inverse.
+__global__ __launch_bounds__(IB_T) void panel_inverse64_kernel(const double* __restrict__ N, int64_t ld, int n, int t0, int w,
+                                                                double* __restrict__ C, double* __restrict__ D, int32_t* notpd) {
+  __shared__ InvBlockLds L;
+  static_assert(sizeof(InvBlockLds) >= PANEL_ROWS64 * 129 * sizeof(double), "the copy's tile shares the inverse's memory");
+  if (blockIdx.x == 0) { inv_block128(N, ld, t0, w, D, notpd, L); return; }
+  double (*T)[129] = reinterpret_cast<double (*)[129]>(&L);
+  const int i0 = (blockIdx.x - 1) * PANEL_ROWS64, tid = threadIdx.x;
   if (i0 >= t0 + w) {
-    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += IB_T) {
       const int r = idx / w, c = idx % w;
       if (i0 + r < n) C[(int64_t)(i0 + r) * w + c] = N[(int64_t)(i0 + r) * ld + t0 + c];
     }
     return;
   }
   if (i0 + PANEL_ROWS64 <= t0) {
-    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += IB_T) {
       const int c = idx / PANEL_ROWS64, r = idx % PANEL_ROWS64;
       T[r][c] = N[(int64_t)(t0 + c) * ld + i0 + r];
     }
   } else {
-    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += IB_T) {
       const int r = idx / w, c = idx % w;
       T[r][c] = (i0 + r < n) ? nsym64(N, ld, i0 + r, t0 + c) : 0.0;
     }
   }
   __syncthreads();
-  for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+  for (int idx = tid; idx < PANEL_ROWS64 * w; idx += IB_T) {
     const int r = idx / w, c = idx % w;
     if (i0 + r < n) C[(int64_t)(i0 + r) * w + c] = T[r][c];
   }
-}
-__global__ __launch_bounds__(256) void inv_block64_kernel(const double* __restrict__ C, int w, int t0, double* __restrict__ D,
-                                                           int32_t* notpd) {
-  __shared__ double buf[64 * (INV_NB / 16)];
-  for (int idx = threadIdx.x; idx < w * w; idx += 256) {
-    const int r = idx / w, c = idx % w;
-    D[idx] = C[(int64_t)(t0 + r) * w + c];
-  }
-  small_inverse<INV_NB / 16>(D, w, +1, notpd, buf);
 }
 // outz = C D and Cz = C, both with the pivot rows zeroed: the operands of the bulk update; the pivot-row fix reads outz
 // outside the pivot rows only.  8 rows per workgroup, thread (h, c) sums 4 rows of column c, k ascending.
@@ -509,30 +624,30 @@ __global__ __launch_bounds__(256) void panel_times_small64_kernel(const double* 
     Cz[(int64_t)i * w + c] = piv ? 0.0 : Csh[h * 4 + r][c];
   }
 }
-__global__ __launch_bounds__(256) void inv_fix64_kernel(double* __restrict__ N, int64_t ld, int n, int t0, int w,
-                                                         const double* __restrict__ CD, const double* __restrict__ D) {
-  __shared__ double T[PANEL_ROWS64][129];
-  const int i0 = blockIdx.x * PANEL_ROWS64, tid = threadIdx.x;
+// pivot rows after the sweep of rows t0 .. t0 + w, for the 32 rows i0 ..: N(t0 + c, l) = CD[l][c] outside the pivot, -D on it
+__device__ void inv_fix64(double* __restrict__ N, int64_t ld, int n, int t0, int w, const double* __restrict__ CD,
+                          const double* __restrict__ D, int i0, double (*T)[129]) {
+  const int tid = threadIdx.x, nt = blockDim.x;
   if (i0 >= t0 + w) {
-    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += nt) {
       const int r = idx / w, c = idx % w;
       if (i0 + r < n) N[(int64_t)(i0 + r) * ld + t0 + c] = CD[(int64_t)(i0 + r) * w + c];
     }
     return;
   }
-  for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+  for (int idx = tid; idx < PANEL_ROWS64 * w; idx += nt) {
     const int r = idx / w, c = idx % w;
     T[r][c] = (i0 + r < n) ? CD[(int64_t)(i0 + r) * w + c] : 0.0;
   }
   __syncthreads();
   if (i0 + PANEL_ROWS64 <= t0) {
-    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+    for (int idx = tid; idx < PANEL_ROWS64 * w; idx += nt) {
       const int c = idx / PANEL_ROWS64, r = idx % PANEL_ROWS64;
       N[(int64_t)(t0 + c) * ld + i0 + r] = T[r][c];
     }
     return;
   }
-  for (int idx = tid; idx < PANEL_ROWS64 * w; idx += 256) {
+  for (int idx = tid; idx < PANEL_ROWS64 * w; idx += nt) {
     const int r = idx / w, c = idx % w, l = i0 + r;
     if (l >= n) continue;
     if (l < t0) N[(int64_t)(t0 + c) * ld + l] = T[r][c];
@@ -547,16 +662,22 @@ __global__ __launch_bounds__(256) void inv_fix64_kernel(double* __restrict__ N, 
 // different bank groups).  The workgroup's part of N (16 values per thread) is requested while the first products run and is
 // there when the last one ends: with a whole tile per workgroup the registers held a quarter of it at a time, and four
 // round trips to memory followed the products.  Tiles in 8 x 8 super-blocks per XCD, the two halves of a tile on one XCD.
-typedef double swd4 __attribute__((ext_vector_type(4)));
 constexpr int SW_LD = 144, SW_LDB = 80;
 constexpr size_t SW_LDS_BYTES = (size_t)2 * 16 * (SW_LD + SW_LDB) * sizeof(double);
 // part = 0: every tile of the triangle.  The pivot rows of A and B are zero, so the tiles of tile row / column pk (the
 // pivot panel's) receive nothing and are always left alone (the pivot-row fix rewrites them, possibly meanwhile).
 // part = 1: only tile row and tile column pk + 1, what the next panel is made of (two workgroups per tile, blockIdx / 2 =
 // the other tile index); part = 2: everything but those.
+// Workgroups from fix_at on write the pivot rows instead (32 rows each; D = the inverse of the pivot block): they touch
+// tile row and column pk only, and as a launch of their own behind part 1 they cost the next panel 10 - 15 us.
 __global__ __launch_bounds__(512, 2) void sweep_update64_kernel(const double* __restrict__ A, const double* __restrict__ B, int n, int w,
-                                                                 double* __restrict__ N, int part, int pk) {
+                                                                 double* __restrict__ N, int part, int pk, unsigned fix_at,
+                                                                 const double* __restrict__ D) {
   extern __shared__ double sw_lds[];           // 56 KB: above the static limit, so taken dynamically
+  if (blockIdx.x >= fix_at) {
+    inv_fix64(N, n, n, pk * INV_NB, w, A, D, (int)(blockIdx.x - fix_at) * PANEL_ROWS64, reinterpret_cast<double (*)[129]>(sw_lds));
+    return;
+  }
   double (*As)[16][SW_LD] = reinterpret_cast<double (*)[16][SW_LD]>(sw_lds);
   double (*Bs)[16][SW_LDB] = reinterpret_cast<double (*)[16][SW_LDB]>(sw_lds + 2 * 16 * SW_LD);
   int tm, tn, half;
@@ -764,12 +885,10 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
     // operand panels alternate: the bulk update of step k - 1 may still be reading the other pair
     double* panelDz = panels + (int64_t)(1 + 2 * (k & 1)) * n * INV_NB;
     double* panelCz = panelDz + (int64_t)n * INV_NB;
-    hipLaunchKernelGGL(extract_panel64_kernel, dim3(rb), dim3(256), 0, s, A64, (int64_t)n, n, t0, w, panel);
-    hipLaunchKernelGGL(inv_block64_kernel, dim3(1), dim3(256), 0, s, panel, w, t0, small, notpd_flag);
+    hipLaunchKernelGGL(panel_inverse64_kernel, dim3(rb + 1), dim3(IB_T), 0, s, A64, (int64_t)n, n, t0, w, panel, small, notpd_flag);
     hipLaunchKernelGGL(panel_times_small64_kernel, dim3((n + 7) / 8), dim3(256), 0, s, panel, small, n, w, t0, panelDz, panelCz);
     if (!two) {
-      hipLaunchKernelGGL(sweep_update64_kernel, dim3(upd_grid), dim3(512), shmem, s, panelDz, panelCz, n, w, A64, 0, k);
-      hipLaunchKernelGGL(inv_fix64_kernel, dim3(rb), dim3(256), 0, s, A64, (int64_t)n, n, t0, w, panelDz, small);
+      hipLaunchKernelGGL(sweep_update64_kernel, dim3(upd_grid + rb), dim3(512), shmem, s, panelDz, panelCz, n, w, A64, 0, k, upd_grid, small);
       continue;
     }
     // The bulk updates follow one another on the side stream without a gap: step k's needs its operands (ready here) and
@@ -779,13 +898,13 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
     // This stream's next launch changes the next panel's tiles, which the bulk update of step k - 1 also does: it waits for
     // that one (the event's latest record), not for step k's, whose launch leaves those tiles out.
     if (pending && (err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
-    hipLaunchKernelGGL(sweep_update64_kernel, dim3(upd_grid), dim3(512), shmem, side->stream, panelDz, panelCz, n, w, A64, 2, k);
+    hipLaunchKernelGGL(sweep_update64_kernel, dim3(upd_grid), dim3(512), shmem, side->stream, panelDz, panelCz, n, w, A64, 2, k, upd_grid, small);
     if ((err = hipEventRecord(side->join, side->stream)) != hipSuccess) return err;
     pending = true;
-    if (k + 1 < tiles) hipLaunchKernelGGL(sweep_update64_kernel, dim3(2 * tiles), dim3(512), shmem, s, panelDz, panelCz, n, w, A64, 1, k);
-    // tile row and column k only: no launch of this step's update touches them, the next step's bulk update does (it is
-    // enqueued behind an event that this stream records after the fix)
-    hipLaunchKernelGGL(inv_fix64_kernel, dim3(rb), dim3(256), 0, s, A64, (int64_t)n, n, t0, w, panelDz, small);
+    // with the pivot rows of this step: tile row and column k only, which no launch of this step's update touches and the next
+    // step's bulk update does (it is enqueued behind an event that this stream records later)
+    const unsigned next = k + 1 < tiles ? 2u * tiles : 0u;
+    hipLaunchKernelGGL(sweep_update64_kernel, dim3(next + rb), dim3(512), shmem, s, panelDz, panelCz, n, w, A64, 1, k, next, small);
   }
   if (pending && (err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
   const int64_t t32 = (n + 31) / 32;

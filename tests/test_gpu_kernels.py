@@ -62,3 +62,30 @@ def test_patch_rows_in_several_pieces(dtype):
     s.close()
     X = torch.nn.functional.unfold(F.double(), 3, padding=1).permute(0, 2, 1).reshape(-1, C * 9).numpy()
     assert X.shape[0] == 9408 and _gram_err(H, X, 0.5) <= 6.1e-8
+
+
+@pytest.mark.parametrize("side", [True, False])
+@pytest.mark.parametrize("kr", [1, 15, 16, 17, 113, 127, 128, 129, 255, 257, 385, 600])
+def test_sweep_inverse_at_the_edges_of_its_blocks(kr, side):
+    """P = H_KK^-1 where the last pivot block and its last 16 x 16 tile are full, ragged or one row, on one stream and on two.
+    The sweep is float64 (condition number below 20: 1e-14), so P is the float32 rounding of the inverse: 2^-24."""
+    from paper_2403_12983_amd import binding
+    pkg = _pkg()
+    d1 = kr + 5
+    g = torch.Generator().manual_seed(kr)
+    A = torch.randn(2 * d1, d1, generator=g, dtype=torch.float64)
+    H = (A.T @ A / (2 * d1) + 0.2 * torch.eye(d1, dtype=torch.float64)).float()
+    H = torch.tril(H) + torch.tril(H, -1).T
+    s = pkg.Solver(d1, 3, d1, 1, kr, 1, torch.float32, torch.float32, DEV)
+    binding.side_stream(side)
+    try:
+        s.osscar_set_quadratic(H.to(DEV), torch.randn(d1, 3, generator=g).to(DEV), 1.0, np.ones(d1))
+        groups = sorted(np.random.default_rng(kr).choice(d1, kr, replace=False).tolist())
+        s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, groups)
+        P = s.osscar_get_tensor(2).cpu().double().numpy()
+    finally:
+        binding.side_stream(True)
+        s.close()
+    R = np.linalg.inv(H.double().numpy()[np.ix_(groups, groups)])
+    d = np.sqrt(np.diag(R))
+    assert np.array_equal(P, P.T) and np.max(np.abs(P - R) / np.outer(d, d)) <= 6.1e-8
