@@ -48,7 +48,9 @@ size_t split_bytes(size_t a, size_t b, size_t m) {
 }
 size_t gram_tile_entries(int64_t d1) { size_t t = (size_t)(d1 + 127) / 128; return 8 * (t * t / 2 + t + 8); }
 // room for any tile list of the state build: shapes up to d1 x max(d1, m), rectangular or lower triangle
-size_t state_tile_entries(int64_t d1, int64_t m) { return std::max(rect_tile_entries(d1, std::max(d1, m)), gram_tile_entries(d1)); }
+size_t state_tile_entries(int64_t d1, int64_t m) {
+  return std::max(rect_tile_entries(d1, std::max(d1, m)) + wide_tile_entries(d1, std::max(d1, m)), gram_tile_entries(d1));
+}
 
 struct Carve {
   char* base; size_t off;
@@ -109,8 +111,9 @@ struct osscar_ctx {
   SearchCtrl* ctrl;
   int32_t *trace_out, *trace_in; float* trace_gap; double* trace_obj;
   int32_t *g_pick, *g_removed; float* g_gap;   // nested schedule from the dense layer
-  int2 *tiles_sym, *tiles_rect;                // tile schedules of the bf16 matrix-core products (uploaded once at create)
-  size_t n_tiles_sym = 0, n_tiles_rect = 0;
+  int2* tiles;                                 // tile schedules of the bf16 matrix-core products (uploaded once at create)
+  PackedTiles tiles_h, tiles_g;                // of a d1 x d1 result (lower triangle) and of a d1 x m one, in `tiles`
+  int h_copies = 1, g_copies = 1;              // copies of the float64 accumulators that the layer's chunks have used so far
   double* gemm_ws; size_t gemm_ws_size;        // partial tiles of the 64 x 64 float64 products (this stream only)
   int2* tiles_state;                           // two schedules of the corrections' products (shapes follow the kept count)
   std::vector<int2> tl_host[2];                // their host copies stay alive while the copies to the device are in flight
@@ -141,6 +144,15 @@ namespace {
 struct Layout {
   size_t total = 0, scratch_bytes = 0;
 };
+
+// Copies of the float64 accumulators of X^T X and X^T Y: float32 activations take another path, with one.
+int h_copies_of(const osscar_desc& ds) {
+  const int64_t t = (ds.d1 + 127) / 128;
+  return ds.x_dtype == OSSCAR_BF16 ? packed_copies(ds.d1 * ds.d1, t * (t + 1) / 2) : 1;
+}
+int g_copies_of(const osscar_desc& ds) {
+  return ds.x_dtype == OSSCAR_BF16 ? packed_copies(ds.d1 * ds.m, (ds.d1 + 127) / 128 * ((ds.m + 127) / 128)) : 1;
+}
 
 // Carves (or just sizes, when base == nullptr) the workspace for a description.
 Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
@@ -181,8 +193,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
   int32_t* g_removed = cv.take<int32_t>(p);
   float* g_gap = cv.take<float>(p);
   float* Wdense = cv.take<float>(d1 * m);
-  int2* tiles_sym = cv.take<int2>(gram_tile_entries(d1));
-  int2* tiles_rect = cv.take<int2>(rect_tile_entries(d1, m));
+  int2* tiles = cv.take<int2>(gram_tile_entries(d1) + rect_tile_entries(d1, m) + wide_tile_entries(d1, d1) + wide_tile_entries(d1, m));
   int2* tiles_state = cv.take<int2>(2 * state_tile_entries(d1, m));
   double* gemm_ws = reinterpret_cast<double*>(cv.take<char>(gemm_ws_bytes(d1, m)));
   LazyPtrs L{};
@@ -209,8 +220,8 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
     L.bG = cv.take<int32_t>(LAZY_BT);
   }
   // scratch: the larger of the Gram phase and the init / refresh / backsolve phase
-  size_t gram_phase = align_up((size_t)d1 * d1 * 8) + align_up((size_t)d1 * m * 4) + align_up(gram_stage_bytes(d1));
-  if (ds.target_output) gram_phase += align_up((size_t)d1 * m * 8) + align_up(target_stage_bytes(m));
+  size_t gram_phase = align_up((size_t)d1 * d1 * 8 * h_copies_of(ds)) + align_up((size_t)d1 * m * 4) + align_up(gram_stage_bytes(d1));
+  if (ds.target_output) gram_phase += align_up((size_t)d1 * m * 8 * g_copies_of(ds)) + align_up(target_stage_bytes(m));
   auto init_bytes = [&](size_t a, size_t b) {   // kept rows a, candidate rows b
     return 4 * align_up(a * a * 4) + 3 * align_up(a * b * 4) + align_up(b * b * 4) + 4 * align_up(a * m * 4) + align_up(b * m * 4) +
            align_up(10 * a * INV_NB * 4) + split_bytes(a, b, m) + i8_bytes(a, b, m) + 4096;
@@ -229,7 +240,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
     c->notpd = notpd; c->C1 = C1; c->C2 = C2; c->Cblk = Cblk; c->rZ1 = rZ1; c->rZ2 = rZ2; c->ctrl = ctrl;
     c->trace_out = trace_out; c->trace_in = trace_in; c->trace_gap = trace_gap; c->trace_obj = trace_obj;
     c->g_pick = g_pick; c->g_removed = g_removed; c->g_gap = g_gap; c->Wdense = Wdense;
-    c->tiles_sym = tiles_sym; c->tiles_rect = tiles_rect; c->tiles_state = tiles_state;
+    c->tiles = tiles; c->tiles_state = tiles_state;
     c->gemm_ws = gemm_ws; c->gemm_ws_size = gemm_ws_bytes(d1, m); L.gemm_ws = gemm_ws; L.gemm_ws_bytes = c->gemm_ws_size;
     c->scratch = scratch; c->scratch_bytes = scratch_bytes; c->lazy = L;
   }
@@ -334,16 +345,19 @@ bool split_ok(const osscar_ctx* c) { return c->kr % 8 == 0 && c->m % 8 == 0; }
 
 // Tile schedule `slot` of the state build for an M x N result (lower: the lower triangle of a square result): built on the
 // host, copied behind the stream's earlier work.
-struct TileRef { const int2* dev; size_t entries; int ntiles; };
+struct TileRef { PackedTiles tiles; int ntiles = 0; };
 osscar_status stage_tiles(osscar_ctx* c, int slot, int M, int N, bool lower, TileRef* out) {
   std::vector<int2>& v = c->tl_host[slot];
-  if (lower) gram_tile_list_host(M, v); else rect_tile_list_host(M, N, v);
-  const size_t cap = state_tile_entries(c->d1, c->m);
+  std::vector<int2> wide;
+  if (lower) gram_tile_list_host(M, v);
+  else { rect_tile_list_host(M, N, v); wide_tile_list_host(M, N, false, wide); }
+  const size_t n = v.size(), cap = state_tile_entries(c->d1, c->m);
+  v.insert(v.end(), wide.begin(), wide.end());
   if (v.size() > cap) return fail(c, OSSCAR_ENOMEM, "internal: tile schedule of a %d x %d product exceeds its buffer", M, N);
   int2* dev = c->tiles_state + (size_t)slot * cap;
   HIPCHK(c, hipMemcpyAsync(dev, v.data(), v.size() * sizeof(int2), hipMemcpyHostToDevice, c->stream));
   const int tm = (M + 127) / 128, tn = (N + 127) / 128;
-  out->dev = dev; out->entries = v.size(); out->ntiles = lower ? tm * (tm + 1) / 2 : tm * tn;
+  out->tiles = PackedTiles{dev, n, lower ? nullptr : dev + n, wide.size()}; out->ntiles = lower ? tm * (tm + 1) / 2 : tm * tn;
   return OSSCAR_OK;
 }
 
@@ -359,7 +373,7 @@ osscar_status pack_into(osscar_ctx* c, const SplitBufs& sp, void* pack, const fl
 osscar_status split_gemm(osscar_ctx* c, const SplitBufs& sp, const void* packA, int M, const void* packB, int N, int K, int nprod,
                          const TileRef& t, const float* Cin, int64_t ldcin, float* C, int64_t ldc, double alpha, double beta) {
   if ((size_t)M * N > sp.cap_acc) return fail(c, OSSCAR_ENOMEM, "internal: %d x %d product exceeds the accumulator", M, N);
-  HIPCHK(c, launch_split_product(packA, M, packB, N, K, nprod, sp.acc, t.dev, t.entries, t.ntiles, c->stream));
+  HIPCHK(c, launch_split_product(packA, M, packB, N, K, nprod, sp.acc, t.tiles, t.ntiles, c->stream));
   HIPCHK(c, launch_split_epilogue(sp.acc, M, N, Cin, ldcin, C, ldc, alpha, beta, c->stream));
   return OSSCAR_OK;
 }
@@ -644,14 +658,21 @@ osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* wor
   c->kr = desc->k * desc->q; c->cr = c->d1 - c->kr;
   carve_all(*desc, workspace_dev, c);
   {   // tile schedules of the packed matrix-core products: built and uploaded once, so that no chunk call waits for the stream
-    std::vector<int2> ts, tr;
+    std::vector<int2> all, ts, tr, ws, wr;
     gram_tile_list_host(c->d1, ts);
     rect_tile_list_host(c->d1, c->m, tr);
-    if (ts.size() > gram_tile_entries(c->d1) || tr.size() > rect_tile_entries(c->d1, c->m)) { delete c; return OSSCAR_ENOMEM; }
-    if (hipMemcpy(c->tiles_sym, ts.data(), ts.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(c->tiles_rect, tr.data(), tr.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess) { delete c; return OSSCAR_EHIP; }
-    c->n_tiles_sym = ts.size(); c->n_tiles_rect = tr.size();
-    c->lazy.tiles_sym = c->tiles_sym; c->lazy.n_tiles_sym = ts.size(); c->lazy.tiles_rect = c->tiles_rect; c->lazy.n_tiles_rect = tr.size();
+    if (desc->x_dtype == OSSCAR_BF16 || desc->w_dtype == OSSCAR_BF16) {
+      wide_tile_list_host(c->d1, c->d1, true, ws);
+      wide_tile_list_host(c->d1, c->m, false, wr);
+    }
+    if (ts.size() > gram_tile_entries(c->d1) || tr.size() > rect_tile_entries(c->d1, c->m) || ws.size() > wide_tile_entries(c->d1, c->d1) ||
+        wr.size() > wide_tile_entries(c->d1, c->m)) { delete c; return OSSCAR_ENOMEM; }
+    for (const auto* v : {&ts, &tr, &ws, &wr}) all.insert(all.end(), v->begin(), v->end());
+    if (hipMemcpy(c->tiles, all.data(), all.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess) { delete c; return OSSCAR_EHIP; }
+    const int2 *sym = c->tiles, *rect = sym + ts.size(), *wsym = rect + tr.size(), *wrect = wsym + ws.size();
+    c->tiles_h = PackedTiles{sym, ts.size(), ws.empty() ? nullptr : wsym, ws.size()};
+    c->tiles_g = PackedTiles{rect, tr.size(), wr.empty() ? nullptr : wrect, wr.size()};
+    c->lazy.tiles_sym = sym; c->lazy.n_tiles_sym = ts.size(); c->lazy.tiles_rect = rect; c->lazy.n_tiles_rect = tr.size();
   }
   c->ev_ok = (hipEventCreate(&c->ev_a) == hipSuccess) && (hipEventCreate(&c->ev_b) == hipSuccess);
   for (int i = 0; i < EV_SAMPLES && c->ev_ok; i++)
@@ -699,12 +720,12 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   hipStream_t s = c->stream;
   const int d1 = c->d1, m = c->m;
   Carve cv(c->scratch);
-  double* H64 = cv.take<double>((int64_t)d1 * d1);
+  double* H64 = cv.take<double>((int64_t)d1 * d1 * h_copies_of(c->desc));
   float* Wf = cv.take<float>((int64_t)d1 * m);
   void* Xt = cv.take<char>(gram_stage_bytes(d1));
   double* G64 = nullptr; void* Ys = nullptr;
   if (c->desc.target_output) {
-    G64 = cv.take<double>((int64_t)d1 * m);
+    G64 = cv.take<double>((int64_t)d1 * m * g_copies_of(c->desc));
     Ys = cv.take<char>(target_stage_bytes(m));
   }
   if (c->phase != osscar_ctx::ACCUM) {   // first chunk of a layer
@@ -715,6 +736,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     }
     c->phase = osscar_ctx::ACCUM;
     c->accum_target = target;
+    c->h_copies = c->g_copies = 1;
     c->timers[0] = 0;
   }
   if (n_c > 0) {
@@ -724,11 +746,11 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     if (target) fast = fast && (m % 8 == 0) && (ldy % 8 == 0) && ((reinterpret_cast<uintptr_t>(Yc) & 15) == 0);
     if (target) HIPCHK(c, launch_sumsq(Yc, bf16, n_c, m, ldy, c->scal + 12, c->partial, s));
     if (fast) {
-      if (target) HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, H64, c->tiles_sym, c->n_tiles_sym, Xt, PACK_ROWS, s, Yc, ldy, m, G64,
-                                               c->tiles_rect, c->n_tiles_rect, Ys));
+      const PackedAcc acc_h{H64, h_copies_of(c->desc), &c->h_copies}, acc_g{G64, g_copies_of(c->desc), &c->g_copies};
+      if (target) HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, acc_h, c->tiles_h, Xt, PACK_ROWS, s, Yc, ldy, m, acc_g, c->tiles_g, Ys));
       else {
-        HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, H64, c->tiles_sym, c->n_tiles_sym, Xt, PACK_ROWS, s, nullptr, 0, 0, nullptr,
-                                     nullptr, 0, nullptr, conv, c->ev_g, EV_SAMPLES, &c->ev_g_used));
+        HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, acc_h, c->tiles_h, Xt, PACK_ROWS, s, nullptr, 0, 0, PackedAcc(), PackedTiles(), nullptr, conv,
+                                     c->ev_g, EV_SAMPLES, &c->ev_g_used));
         c->ev_g_rows = n_c;
       }
     } else {
@@ -759,6 +781,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   if (!finalize) return OSSCAR_OK;
 
   HIPCHK(c, hipEventRecord(c->ev_a, s));
+  HIPCHK(c, launch_sum_copies(H64, c->h_copies, d1, d1, 1, s));
   HIPCHK(c, launch_trace64(H64, d1, c->scal, s));
   double tr = 0;
   HIPCHK(c, hipMemcpyAsync(&tr, c->scal, 8, hipMemcpyDeviceToHost, s));
@@ -770,6 +793,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   double yy = 0;
   if (target) {
     // G = X^T Y + lambda W, c0 = ||Y||^2 + lambda ||W||^2
+    HIPCHK(c, launch_sum_copies(G64, c->g_copies, d1, m, 0, s));
     HIPCHK(c, launch_finalize_G(G64, Wf, c->scal + 1, c->G, (int64_t)d1 * m, s));
     HIPCHK(c, launch_dot64(Wf, Wf, (int64_t)d1 * m, c->scal + 2, c->partial, s));
     HIPCHK(c, hipMemcpyAsync(&yy, c->scal + 12, 8, hipMemcpyDeviceToHost, s));
@@ -790,7 +814,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
       void* pack_w = base + g64_bytes + ph_bytes;
       hipLaunchKernelGGL(fill_f64_kernel, dim3(grid_for((int64_t)d1 * m)), dim3(256), 0, s, Gacc, (int64_t)d1 * m, 0.0);
       hipLaunchKernelGGL(fill_f64_kernel, dim3(1), dim3(64), 0, s, c->scal + 13, (int64_t)1, 0.0);
-      HIPCHK(c, launch_hw_split(c->H, d1, W, ldw, m, Gacc, c->tiles_rect, c->n_tiles_rect, pack_h, pack_w, prow, s));
+      HIPCHK(c, launch_hw_split(c->H, d1, W, ldw, m, Gacc, c->tiles_g, pack_h, pack_w, prow, s));
       HIPCHK(c, launch_finalize_G(Gacc, Wf, c->scal + 13, c->G, (int64_t)d1 * m, s));
     } else {
       if (d1 % 4 == 0 && m % 4 == 0 && (int64_t)((d1 + 127) / 128) * ((m + 127) / 128) >= 768) {

@@ -7,10 +7,10 @@
 //   rewritten once into that order (8 x 8 register transposes, HBM-bound, a few percent of the product's
 //   time), and the product kernel then only copies contiguous blocks into LDS and issues MFMAs.
 //   Tile order: the host lays the tiles out so that the workgroups that run together on one XCD (block
-//   index modulo 8) form 4 x 8 blocks of tiles sharing their 12 column panels in that XCD's L2, and deals
-//   the strips of tile rows to the XCDs in alternating direction so that all eight get equal work.
+//   index modulo 8) form 4 x 8 blocks of tiles sharing their 12 column panels in that XCD's L2.
 #include "internal.h"
 #include <cstdlib>
+#include <type_traits>
 #include <vector>
 
 namespace osscar {
@@ -20,48 +20,43 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
 constexpr int GBK = 64;            // tokens per LDS stage
 
-// Tile order: strips of 4 tile rows are dealt to the 8 XCDs (block index modulo 8 selects the XCD), largest strip first to
-// the XCD with the least work so far, so that all eight finish together; within a strip the tiles are walked in 4 x 8
-// blocks.  Lists are padded with (-1, -1) to equal length.
-static void build_tile_list(int tm_count, std::vector<int2>& out) {
-  constexpr int NX = 8, RB = 4, CB = 8;
-  std::vector<std::vector<int2>> lists(NX);
-  const int strips = (tm_count + RB - 1) / RB;
-  std::vector<int> owner(strips, 0);
-  std::vector<long> load(NX, 0);
-  for (int sidx = strips - 1; sidx >= 0; sidx--) {            // strips grow with the row index: last = largest
-    const int r0 = sidx * RB, r1 = std::min(tm_count, r0 + RB);
-    long tiles = 0;
-    for (int r = r0; r < r1; r++) tiles += r + 1;
-    int best = 0;
-    for (int x = 1; x < NX; x++) if (load[x] < load[best]) best = x;
-    owner[sidx] = best; load[best] += tiles;
-  }
-  for (int sidx = 0; sidx < strips; sidx++) {
-    std::vector<int2>& L = lists[owner[sidx]];
-    int r0 = sidx * RB, r1 = std::min(tm_count, r0 + RB);
-    for (int c0 = 0; c0 < r1; c0 += CB)
-      for (int r = r0; r < r1; r++)
-        for (int c = c0; c < c0 + CB && c <= r; c++) L.push_back(int2{r, c});
-  }
-  size_t len = 0;
-  for (auto& L : lists) len = std::max(len, L.size());
-  out.assign(len * NX, int2{-1, -1});
-  for (int x = 0; x < NX; x++)
-    for (size_t i = 0; i < lists[x].size(); i++) out[i * NX + x] = lists[x][i];
+// Tile order: the tiles in RB x CB blocks, one block after the other, and the whole sequence cut into eight equal parts, one per
+// XCD (block index modulo 8 selects the XCD); padded with (-1, -1) to equal length.  The tiles that an XCD works on at a time
+// share their panels, and all eight have equal work at every size: with whole strips of 4 tile rows dealt to the XCDs, 2048
+// columns kept four XCDs busy, and 4096 columns gave one of them twice the average.
+template <typename Keep>
+static void deal_tiles(int R, int C, int RB, int CB, Keep keep, std::vector<int2>& out) {
+  std::vector<int2> seq;
+  for (int r0 = 0; r0 < R; r0 += RB)
+    for (int c0 = 0; c0 < C; c0 += CB)
+      for (int r = r0; r < std::min(R, r0 + RB); r++)
+        for (int c = c0; c < std::min(C, c0 + CB); c++)
+          if (keep(r, c)) seq.push_back(int2{r, c});
+  const size_t per = (seq.size() + 7) / 8;
+  out.assign(per * 8, int2{-1, -1});
+  for (size_t i = 0; i < seq.size(); i++) out[(i % per) * 8 + i / per] = seq[i];
+}
+static void build_tile_list(int tiles, std::vector<int2>& out) {
+  deal_tiles(tiles, tiles, 4, 8, [](int r, int c) { return c <= r; }, out);
 }
 
 // ------------------------------------------------------------------------------------------------
-// gram_pack_kernel rewrites a chunk of X once into the operand format of the MFMA: for every stage
-// (64 tokens) and every panel (128 columns) one contiguous 16 KB block of 16-byte packets, packet (kg, c) = the 8
-// tokens kg*8..kg*8+7 of column c, at slot kg*128 + c.  Tokens past the chunk and columns past d1 are zero.
+// gram_pack_kernel rewrites a chunk of X once into the operand format of the MFMA: for every panel (64 columns; always an
+// even number of panels) and every stage (64 tokens) one contiguous 8 KB block of 16-byte packets, packet (kg, c) = the 8
+// tokens kg*8..kg*8+7 of column c, at slot kg*64 + c.  Tokens past the chunk and columns past d1 are zero.  The stages of a
+// panel follow one another: with the panels of a stage side by side every stage of a workgroup lay on other pages (3.7 MB
+// on for 28672 columns), and the wide kernel below took 14.7 instead of 13.6 ms for 16384 rows.
 // gram_packed_kernel then copies whole blocks global -> LDS (linear, no transposes or masks in the hot loop) and
 // reads MFMA operands as single ds_read_b128: 16 neighbouring lanes read 16 neighbouring packets.
 // Accuracy: the MFMA accumulators are added (v_add_f32, round to nearest) to a second float32 register set every
 // `window` stages and restarted from zero, so the accumulation inside the matrix core never spans more than
 // window*64 tokens; the second set is added to the float64 H once per launch.
 // ------------------------------------------------------------------------------------------------
-constexpr int PK_SLOTS = 8 * 128;   // packets per (stage, panel)
+constexpr int PK_SLOTS = 8 * 64;    // packets per (panel, stage)
+// first packet of the 8 x 8 block (kg, columns 8 cg ..) of a pair of panels in a stage
+__device__ __forceinline__ int64_t pack_slot(int pair, int nstages, int stage, int kg, int cg) {
+  return ((int64_t)(pair * 2 + (cg >> 3)) * nstages + stage) * PK_SLOTS + kg * 64 + (cg & 7) * 8;
+}
 
 __global__ __launch_bounds__(256) void gram_pack_kernel(const uint16_t* __restrict__ X, int64_t n_c, int64_t ldx, int d1,
                                                          int npanels, uint4* __restrict__ Xp) {
@@ -83,7 +78,7 @@ __global__ __launch_bounds__(256) void gram_pack_kernel(const uint16_t* __restri
 #pragma unroll
   for (int r = 0; r < 8; r++)
     if (!live || row0 + r >= n_c) st[r] = uint4{0u, 0u, 0u, 0u};
-  uint4* out = Xp + ((int64_t)blockIdx.y * npanels + panel) * PK_SLOTS + kg * 128 + cg * 8;
+  uint4* out = Xp + pack_slot(panel, gridDim.y, blockIdx.y, kg, cg);
 #define OSSCAR_PACK_LO(F) uint4{(st[0].F & 0xFFFFu) | (st[1].F << 16), (st[2].F & 0xFFFFu) | (st[3].F << 16), \
                                 (st[4].F & 0xFFFFu) | (st[5].F << 16), (st[6].F & 0xFFFFu) | (st[7].F << 16)}
 #define OSSCAR_PACK_HI(F) uint4{(st[0].F >> 16) | (st[1].F & 0xFFFF0000u), (st[2].F >> 16) | (st[3].F & 0xFFFF0000u), \
@@ -128,25 +123,68 @@ __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __r
       v[j][r >> 1] |= (r & 1) ? (e << 16) : e;
     }
   }
-  uint4* out = Xp + ((int64_t)blockIdx.y * npanels + panel) * PK_SLOTS + kg * 128 + cg * 8;
+  uint4* out = Xp + pack_slot(panel, gridDim.y, blockIdx.y, kg, cg);
 #pragma unroll
   for (int j = 0; j < 8; j++) out[j] = uint4{v[j][0], v[j][1], v[j][2], v[j][3]};
 }
 
+// H64 += acc + acc2 for a wave's RT x CT MFMA tiles at (row0, col0); symmetric: on and below the diagonal only.  C layout of the
+// 32 x 32 MFMA: register r = rr*4 + r3 holds row rr*8 + (lane/32)*4 + r3, column lane%32.  A workgroup is the only one that
+// touches its tile in a launch, so these are plain loads and stores, a batch of 4 CT loads ahead of the batch that is stored:
+// float64 atomic adds cost 0.12 ms more on 8192 columns (0.305 against 0.251 ms for 2048 rows, 0.19 without reading H64).
+template <int RT, int CT>
+__device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (&acc2)[RT][CT], double* __restrict__ H64, int ldo, int row0,
+                                         int col0, int rows_out, int cols_out, int symmetric, int lane) {
+  int ldv = ldo;      // opaque: keeps the compiler from computing all the addresses ahead of the main loop
+  asm volatile("" : "+s"(ldv));
+  const int rbase = row0 + (lane >> 5) * 4, cbase = col0 + (lane & 31);
+  double* hbase = H64 + (int64_t)rbase * ldv + cbase;
+  double old[2][4][CT];
+  auto inside = [&](int ro, int b) {
+    const int row = rbase + ro, col = cbase + b * 32;
+    return row < rows_out && col < cols_out && (!symmetric || col <= row);
+  };
+  auto load = [&](int batch) {
+#pragma unroll
+    for (int r3 = 0; r3 < 4; r3++)
+#pragma unroll
+      for (int b = 0; b < CT; b++) {
+        const int ro = (batch >> 2) * 32 + (batch & 3) * 8 + r3;
+        old[batch & 1][r3][b] = inside(ro, b) ? hbase[(int64_t)ro * ldv + b * 32] : 0.0;
+      }
+  };
+  load(0);
+#pragma unroll
+  for (int batch = 0; batch < RT * 4; batch++) {
+    if (batch + 1 < RT * 4) load(batch + 1);
+#pragma unroll
+    for (int r3 = 0; r3 < 4; r3++)
+#pragma unroll
+      for (int b = 0; b < CT; b++) {
+        const int a = batch >> 2, r = (batch & 3) * 4 + r3, ro = a * 32 + (batch & 3) * 8 + r3;
+        if (inside(ro, b)) hbase[(int64_t)ro * ldv + b * 32] = old[batch & 1][r3][b] + ((double)acc[a][b][r] + (double)acc2[a][b][r]);
+      }
+    asm volatile("" ::: "memory");
+  }
+}
+
 // Out (+)= A^T B for packed operands Ap (rows of the result) and Bp (columns of the result); symmetric: Ap == Bp and only
-// tiles on or below the diagonal are listed, the diagonal ones loading one panel.
+// tiles on or below the diagonal are listed, the diagonal ones loading one operand.  blockIdx.y: the part of the contraction;
+// part y is added to copy y of Out (copy_stride doubles apart), so that parts that run side by side never meet.  Sums inside
+// the matrix core restart every `window` stages and at every multiple of `range` stages.
 __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_packed_kernel(
-    const uint4* __restrict__ Ap, int64_t a_sstride, const uint4* __restrict__ Bp, int64_t b_sstride, int nstages, int rows_out,
-    int cols_out, int ldo, double* __restrict__ H64, const int2* __restrict__ tile_list, int stages_per_split, int window,
-    int symmetric, int split) {
+    const uint4* __restrict__ Ap, const uint4* __restrict__ Bp, int nstages, int rows_out, int cols_out, int ldo,
+    double* __restrict__ H64, int64_t copy_stride, const int2* __restrict__ tile_list, int stages_per_split, int window,
+    int range, int symmetric) {
   constexpr int WT = 2, TS = 128;
-  extern __shared__ uint4 lds[];             // [2 buffers][2 panels][PK_SLOTS]
+  extern __shared__ uint4 lds[];             // [2 buffers][2 operands][2 panels][PK_SLOTS]
   const int2 tile = tile_list[blockIdx.x];
   if (tile.x < 0) return;
   const int tm = tile.x, tn = tile.y;
   const bool diag = symmetric && (tm == tn);
   const int i0 = tm * TS, j0 = tn * TS;
-  const int s_begin = split * stages_per_split;
+  const int s_begin = (int)blockIdx.y * stages_per_split;
+  H64 += (int64_t)blockIdx.y * copy_stride;
   const int s_end = (s_begin + stages_per_split < nstages) ? s_begin + stages_per_split : nstages;
   if (s_begin >= s_end) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -160,44 +198,45 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #pragma unroll
       for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
 
-  const uint4* ga = Ap + (int64_t)tm * PK_SLOTS + tid;
-  const uint4* gb = Bp + (int64_t)tn * PK_SLOTS + tid;
+  const int64_t pstride = (int64_t)nstages * PK_SLOTS;
+  const uint4* ga = Ap + 2 * tm * pstride + tid;
+  const uint4* gb = Bp + 2 * tn * pstride + tid;
   uint4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
   rb0 = rb1 = rb2 = rb3 = uint4{0u, 0u, 0u, 0u};
 #define OSSCAR_GLOAD(st)                                                                         \
   {                                                                                              \
-    const uint4* pa_ = ga + (st) * a_sstride;                                                    \
-    ra0 = pa_[0]; ra1 = pa_[256]; ra2 = pa_[512]; ra3 = pa_[768];                                \
+    const uint4* pa_ = ga + (int64_t)(st) * PK_SLOTS;                                            \
+    ra0 = pa_[0]; ra1 = pa_[256]; ra2 = pa_[pstride]; ra3 = pa_[pstride + 256];                  \
     if (!diag) {                                                                                 \
-      const uint4* pb_ = gb + (st) * b_sstride;                                                  \
-      rb0 = pb_[0]; rb1 = pb_[256]; rb2 = pb_[512]; rb3 = pb_[768];                              \
+      const uint4* pb_ = gb + (int64_t)(st) * PK_SLOTS;                                          \
+      rb0 = pb_[0]; rb1 = pb_[256]; rb2 = pb_[pstride]; rb3 = pb_[pstride + 256];                \
     }                                                                                            \
   }
 #define OSSCAR_SSTORE(buf)                                                                       \
   {                                                                                              \
-    uint4* la_ = lds + ((buf) * 2 + 0) * PK_SLOTS + tid;                                         \
+    uint4* la_ = lds + ((buf) * 4 + 0) * PK_SLOTS + tid;                                         \
     la_[0] = ra0; la_[256] = ra1; la_[512] = ra2; la_[768] = ra3;                                \
     if (!diag) {                                                                                 \
-      uint4* lb_ = lds + ((buf) * 2 + 1) * PK_SLOTS + tid;                                       \
+      uint4* lb_ = lds + ((buf) * 4 + 2) * PK_SLOTS + tid;                                       \
       lb_[0] = rb0; lb_[256] = rb1; lb_[512] = rb2; lb_[768] = rb3;                              \
     }                                                                                            \
   }
-  const int oa = wm * 64 + (lane & 31), ob = wn * 64 + (lane & 31);
+  const int oa = wm * PK_SLOTS + (lane & 31), ob = wn * PK_SLOTS + (lane & 31);
 
   OSSCAR_GLOAD(s_begin);
   OSSCAR_SSTORE(0);
   __syncthreads();
-  int in_window = 0;
+  int in_window = 0, in_range = 0;
   int buf = 0;
   for (int st = s_begin; st < s_end; st++) {
     const bool more = (st + 1 < s_end);
     if (more) OSSCAR_GLOAD(st + 1);
-    const uint4* pa = lds + (buf * 2 + 0) * PK_SLOTS;
-    const uint4* pb = diag ? pa : lds + (buf * 2 + 1) * PK_SLOTS;
+    const uint4* pa = lds + (buf * 4 + 0) * PK_SLOTS;
+    const uint4* pb = diag ? pa : lds + (buf * 4 + 2) * PK_SLOTS;
     __builtin_amdgcn_s_setprio(1);        // the wave that is multiplying goes first; the other wave of the SIMD issues its loads and stores in between
 #pragma unroll
     for (int ks = 0; ks < GBK / 16; ks++) {
-      const int kgo = (ks * 2 + (lane >> 5)) * 128;
+      const int kgo = (ks * 2 + (lane >> 5)) * 64;
       bf8 fa[WT], fb[WT];
 #pragma unroll
       for (int a = 0; a < WT; a++) {
@@ -216,8 +255,10 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
           acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
     }
     __builtin_amdgcn_s_setprio(0);
-    if (++in_window >= window && more) {
+    ++in_range;
+    if ((++in_window >= window || in_range == range) && more) {
       in_window = 0;
+      if (in_range == range) in_range = 0;
 #pragma unroll
       for (int a = 0; a < WT; a++)
 #pragma unroll
@@ -232,30 +273,147 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #undef OSSCAR_GLOAD
 #undef OSSCAR_SSTORE
 
-  // C layout of the 32 x 32 MFMA: register r = rr*4 + r3 holds row rr*8 + (lane/32)*4 + r3, column lane%32
-  // (the opaque copy of d1 keeps the compiler from computing the 64 output addresses ahead of the main loop)
-  int d1v = ldo;
-  asm volatile("" : "+s"(d1v));
-  const int rbase = i0 + wm * 64 + (lane >> 5) * 4;
-  const int cbase = j0 + wn * 64 + (lane & 31);
-  double* hbase = H64 + (int64_t)rbase * d1v + cbase;
-#pragma unroll
-  for (int a = 0; a < WT; a++)
-#pragma unroll
-    for (int rr = 0; rr < 4; rr++) {
-#pragma unroll
-      for (int r3 = 0; r3 < 4; r3++) {
-        const int ro = a * 32 + rr * 8 + r3;
-        double* hrow = hbase + (int64_t)ro * d1v;
-        const bool rok = (rbase + ro < rows_out);
-#pragma unroll
-        for (int b = 0; b < WT; b++)
-          if (rok && cbase + b * 32 < cols_out)
-            unsafeAtomicAdd(hrow + b * 32, (double)acc[a][b][rr * 4 + r3] + (double)acc2[a][b][rr * 4 + r3]);
-      }
-      asm volatile("" ::: "memory");
-    }
+  add_tile<WT, WT>(acc, acc2, H64, ldo, i0 + wm * 64, j0 + wn * 64, rows_out, cols_out, symmetric, lane);
 }
+
+// ------------------------------------------------------------------------------------------------
+// The same product in 256 x 192 tiles, one workgroup of 8 waves (64 x 96 each) per compute unit.  The 128 x 128 tile moves
+// 64 KB through LDS and 32 KB into it for every 64 MFMAs per SIMD and is bound by that path; here it is 160 KB and 56 KB for
+// 192.  Stages of 32 tokens go global -> LDS directly into four buffers of 28 KB, so that three stages are in flight behind
+// the one that is read; the operands of a half stage are read while the other half multiplies, and one barrier per stage
+// says both that the next stage has landed and that this one's buffer is free.  The buffers are separate arrays and the
+// steady loop has no condition: with one array, or with conditional requests, the compiler cannot tell which requests
+// a read of LDS depends on and waits for all of them.  16384 rows of 28672 columns, evenly distributed values: 21.0 ms
+// that way, 13.6 ms as here, 16.0 ms in 128 x 128 tiles; the layer's own activations: 11.5 against 16.3 ms.  Five buffers
+// were 1 % faster still, but their loop cannot end an accumulation window at 1024 tokens.  What bounds it: the matrix cores
+// are busy 55 % of the cycles, the requests' way into LDS takes most of the rest, and the clock falls to 1.8 GHz under this load.
+// ------------------------------------------------------------------------------------------------
+constexpr int GW_R = 256, GW_C = 192, GW_A = 1024, GW_ST = 1024 + 768;      // packets of a 32-token stage: 4 panels of A, 3 of B
+#define OSSCAR_GW_WAIT(n_) __builtin_amdgcn_s_waitcnt(((n_) & 15) | (7 << 4) | (15 << 8) | (((n_) >> 4) << 14))      // vmcnt <= n_
+#define OSSCAR_GW_BARRIER()                                                                                        \
+  {                                                                                                                \
+    asm volatile("" ::: "memory");                                                                                 \
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14)); /* lgkmcnt = 0: all reads of the current buffer are done */ \
+    __builtin_amdgcn_s_barrier();                                                                                  \
+    asm volatile("" ::: "memory");                                                                                 \
+  }
+__global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_wide_kernel(
+    const uint4* __restrict__ Ap, int a_panels, const uint4* __restrict__ Bp, int b_panels, int nstages, int rows_out, int cols_out,
+    int ldo, double* __restrict__ H64, const int2* __restrict__ tile_list, int window, int symmetric) {
+  __shared__ uint4 lb0[GW_ST], lb1[GW_ST], lb2[GW_ST], lb3[GW_ST];
+  const int2 tile = tile_list[blockIdx.x];
+  if (tile.x < 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int nst = nstages * 2;                       // stages of 32 tokens
+  f16v acc[2][3], acc2[2][3];
+#pragma unroll
+  for (int a = 0; a < 2; a++)
+#pragma unroll
+    for (int b = 0; b < 3; b++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
+  // Requests of 64 packets.  Waves 0 - 3: the four kg of one panel of A; waves 4 - 7: one kg of the three panels of B.
+  // Panels past the last one are read from the last one (their results are not written).
+  const bool ld_a = wave < 4;
+  const uint4* gp[4];
+  int ldst, lstep;
+  if (ld_a) {
+    const int p = min(tile.x * 4 + wave, a_panels - 1);
+#pragma unroll
+    for (int i = 0; i < 4; i++) gp[i] = Ap + (int64_t)p * nstages * PK_SLOTS + i * 64 + lane;
+    ldst = wave * 64; lstep = GW_R;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int p = min(tile.y * 3 + (i < 3 ? i : 2), b_panels - 1);
+      gp[i] = Bp + (int64_t)p * nstages * PK_SLOTS + (wave - 4) * 64 + lane;
+    }
+    ldst = GW_A + (wave - 4) * GW_C; lstep = 64;
+  }
+  // in LDS: A as [kg][256 columns], then B as [kg][192 columns]
+  const int oa = (lane >> 5) * GW_R + wm * 64 + (lane & 31), ob = GW_A + (lane >> 5) * GW_C + wn * 96 + (lane & 31);
+  bf8 fa[2][2], fb[2][3];
+#define OSSCAR_GW_LOAD(st_, buf_)                                                                               \
+  {                                                                                                             \
+    _Pragma("unroll") for (int i = 0; i < 4; i++) if (i < NL)                                                   \
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gp[i] + (int64_t)(st_) * 256), \
+                                       (__attribute__((address_space(3))) void*)(buf_ + ldst + i * lstep), 16, 0, 0); \
+  }
+#define OSSCAR_GW_READ(set_, buf_, ks_)                                                                         \
+  {                                                                                                             \
+    _Pragma("unroll") for (int a = 0; a < 2; a++) { uint4 v = buf_[oa + (ks_) * 2 * GW_R + a * 32]; fa[set_][a] = *reinterpret_cast<bf8*>(&v); } \
+    _Pragma("unroll") for (int b = 0; b < 3; b++) { uint4 v = buf_[ob + (ks_) * 2 * GW_C + b * 32]; fb[set_][b] = *reinterpret_cast<bf8*>(&v); } \
+  }
+#define OSSCAR_GW_MULT(set_)                                                                                    \
+  _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < 3; b++)                   \
+    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set_][a], fb[set_][b], acc[a][b], 0, 0, 0);
+#define OSSCAR_GW_STEADY(st_, cur_, nxt_)                                                                       \
+  {                                                                                                             \
+    OSSCAR_GW_READ(1, cur_, 1);                                                                                 \
+    OSSCAR_GW_MULT(0);                                                                                          \
+    OSSCAR_GW_WAIT(2 * NL);                                                                                     \
+    OSSCAR_GW_BARRIER();                                                                                        \
+    OSSCAR_GW_LOAD((st_) + 4, cur_);                                                                            \
+    OSSCAR_GW_READ(0, nxt_, 0);                                                                                 \
+    OSSCAR_GW_MULT(1);                                                                                          \
+  }
+#define OSSCAR_GW_TAIL(st_, cur_, nxt_)                                                                         \
+  if ((st_) < nst) {                                                                                            \
+    OSSCAR_GW_READ(1, cur_, 1);                                                                                 \
+    OSSCAR_GW_MULT(0);                                                                                          \
+    if ((st_) + 1 < nst) {                                                                                      \
+      OSSCAR_GW_WAIT(0);                                                                                        \
+      OSSCAR_GW_BARRIER();                                                                                      \
+      if ((st_) + 4 < nst) OSSCAR_GW_LOAD((st_) + 4, cur_);                                                     \
+      OSSCAR_GW_READ(0, nxt_, 0);                                                                               \
+    }                                                                                                           \
+    OSSCAR_GW_MULT(1);                                                                                          \
+  }
+#define OSSCAR_GW_FOLD()                                                                                        \
+  if ((in_window += 4) == window) {                                                                             \
+    in_window = 0;                                                                                              \
+    _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < 3; b++)                 \
+      _Pragma("unroll") for (int r = 0; r < 16; r++) { acc2[a][b][r] += acc[a][b][r]; acc[a][b][r] = 0.f; }     \
+  }
+  // two copies of the loop: waves with four requests per stage and waves with three (the count of a wait is a constant)
+  auto run = [&](auto nl) {
+    constexpr int NL = decltype(nl)::value;
+    OSSCAR_GW_LOAD(0, lb0); OSSCAR_GW_LOAD(1, lb1);      // nst is even
+    if (2 < nst) { OSSCAR_GW_LOAD(2, lb2); OSSCAR_GW_LOAD(3, lb3); }
+    if (nst >= 4) OSSCAR_GW_WAIT(3 * NL); else OSSCAR_GW_WAIT(0);
+    OSSCAR_GW_BARRIER();
+    OSSCAR_GW_READ(0, lb0, 0);
+    int in_window = 0, st = 0;
+    if (nst >= 8) {
+      do {
+        OSSCAR_GW_STEADY(st, lb0, lb1); OSSCAR_GW_STEADY(st + 1, lb1, lb2);
+        OSSCAR_GW_STEADY(st + 2, lb2, lb3); OSSCAR_GW_STEADY(st + 3, lb3, lb0);
+        OSSCAR_GW_FOLD();
+        st += 4;
+      } while (st + 8 <= nst);
+    }
+    for (; st < nst; st += 4) {
+      OSSCAR_GW_TAIL(st, lb0, lb1); OSSCAR_GW_TAIL(st + 1, lb1, lb2); OSSCAR_GW_TAIL(st + 2, lb2, lb3); OSSCAR_GW_TAIL(st + 3, lb3, lb0);
+      OSSCAR_GW_FOLD();
+    }
+  };
+  if (ld_a) run(std::integral_constant<int, 4>{}); else run(std::integral_constant<int, 3>{});
+#undef OSSCAR_GW_LOAD
+#undef OSSCAR_GW_READ
+#undef OSSCAR_GW_MULT
+#undef OSSCAR_GW_STEADY
+#undef OSSCAR_GW_TAIL
+#undef OSSCAR_GW_FOLD
+  add_tile<2, 3>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * GW_C + wn * 96, rows_out, cols_out, symmetric, lane);
+}
+
+// Tiles of the wide kernel (blocks of 1024 x 1536).  symmetric: tiles that hold an element on or below the diagonal.
+void wide_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& out) {
+  deal_tiles((rows + GW_R - 1) / GW_R, (cols + GW_C - 1) / GW_C, 4, 8,
+             [&](int r, int c) { return !symmetric || c * GW_C <= std::min(rows, (r + 1) * GW_R) - 1; }, out);
+}
+size_t wide_tile_entries(int64_t rows, int64_t cols) { return (size_t)((rows + GW_R - 1) / GW_R * ((cols + GW_C - 1) / GW_C) + 8); }
 
 // Rows r0 .. r0 + nr of the patch matrix as float32 (float32 maps and bf16 maps of other than a multiple of eight columns).
 // Thread = one column of 16 patches, so that writes run along the rows; bound by writing the rows (115 MB in 0.06 ms).
@@ -294,82 +452,81 @@ int gram_tile_schedule(int tiles_per_side, int32_t* out, int capacity) {
   return (int)t.size();
 }
 
-// all tiles of an R x C grid, in 4 x 8 blocks dealt to the XCDs in turn
-static void build_rect_tile_list(int R, int C, std::vector<int2>& out) {
-  constexpr int NX = 8, RB = 4, CB = 8;
-  std::vector<std::vector<int2>> lists(NX);
-  int blk = 0;
-  for (int r0 = 0; r0 < R; r0 += RB)
-    for (int c0 = 0; c0 < C; c0 += CB, blk++)
-      for (int r = r0; r < std::min(R, r0 + RB); r++)
-        for (int c = c0; c < std::min(C, c0 + CB); c++) lists[blk % NX].push_back(int2{r, c});
-  size_t len = 0;
-  for (auto& L : lists) len = std::max(len, L.size());
-  out.assign(len * NX, int2{-1, -1});
-  for (int x = 0; x < NX; x++)
-    for (size_t i = 0; i < lists[x].size(); i++) out[i * NX + x] = lists[x][i];
-}
-
-static int split_stages(int ntiles, int nstages, int* per_out) {
-  int splits = 1;
-  if (ntiles < 1024) splits = std::min(nstages, (2048 + ntiles - 1) / ntiles);
-  int per = (nstages + splits - 1) / splits;
-  per = std::max(per, std::min(nstages, 8));
-  *per_out = per;
-  return (nstages + per - 1) / per;
+// How many copies of a float64 result of this many elements and 128 x 128 tiles are kept, so that ranges of the contraction
+// can run side by side, each into its own copy: enough for 512 workgroups (two per compute unit), in at most 320 MB.
+int packed_copies(int64_t elems, int64_t ntiles) {
+  return (int)std::max<int64_t>(1, std::min({(int64_t)32, 512 / std::max<int64_t>(ntiles, 1), ((int64_t)320 << 20) / (8 * elems)}));
 }
 
 void gram_tile_list_host(int d1, std::vector<int2>& out) { build_tile_list((d1 + 127) / 128, out); }
-void rect_tile_list_host(int d1, int m, std::vector<int2>& out) { build_rect_tile_list((d1 + 127) / 128, (m + 127) / 128, out); }
-
-// Out += A^T B over all stages.  When the contraction is cut into several ranges (few tiles: small layers), the ranges run
-// as launches one after the other, so that every element of Out receives its additions in one fixed order (each launch
-// adds once per element: the atomic adds never meet).
-static void launch_packed_splits(const uint4* Ap, int64_t a_ss, const uint4* Bp, int64_t b_ss, int nstages, int rows_out, int cols_out,
-                                 int ldo, double* Out, const int2* tiles, size_t tile_entries, int ntiles, int window, int symmetric,
-                                 hipStream_t s) {
-  int per = 0;
-  const int splits = split_stages(ntiles, nstages, &per);
-  const size_t shmem = (size_t)2 * 2 * PK_SLOTS * 16;
-  for (int sp = 0; sp < splits; sp++)
-    hipLaunchKernelGGL(gram_packed_kernel, dim3((unsigned)tile_entries), dim3(256), shmem, s, Ap, a_ss, Bp, b_ss, nstages, rows_out,
-                       cols_out, ldo, Out, tiles, per, window, symmetric, sp);
+void rect_tile_list_host(int d1, int m, std::vector<int2>& out) {
+  deal_tiles((d1 + 127) / 128, (m + 127) / 128, 4, 8, [](int, int) { return true; }, out);
 }
 
-hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, double* H64, const int2* tiles,
-                              size_t tile_entries, void* pack_buf, int64_t pack_rows, hipStream_t s, const void* Yc,
-                              int64_t ldy, int m, double* G64, const int2* tiles_y, size_t tile_y_entries, void* pack_buf_y,
-                              const ConvSpec* conv, hipEvent_t* ev, int ev_pairs, int* ev_used) {
+__global__ void fill_zero_f64_kernel(double* __restrict__ p, int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0.0;
+}
+
+// Out += A^T B over all stages, one launch.  The contraction falls into ranges, as many as bring 2048 tiles together, of at
+// least 8 stages: sums restart at their ends, because the error of a window grows with its length.
+// From GW_MIN_TILES wide tiles and GW_MIN_STAGES stages on: the wide kernel (if its windows of 1024 tokens end with the ranges).
+// Else 128 x 128 tiles, two workgroups per compute unit; when there are too few of them for the chip, the ranges are dealt to
+// up to acc.copies workgroups per tile, each adding to its own copy of Out; the caller adds the copies up in order.
+// Either way every element of every copy receives one addition per launch, so the result does not depend on scheduling.
+constexpr size_t GW_MIN_TILES = 128;
+constexpr int GW_MIN_STAGES = 32;
+static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int nstages, int rows_out, int cols_out, const PackedAcc& acc,
+                                const PackedTiles& t, int ntiles, int window, int symmetric, hipStream_t s) {
+  int ranges = ntiles < 1024 ? std::min(nstages, (2048 + ntiles - 1) / ntiles) : 1;
+  const int range = std::max((nstages + ranges - 1) / ranges, std::min(nstages, 8));
+  ranges = (nstages + range - 1) / range;
+  if (t.wide && t.wide_entries >= GW_MIN_TILES && nstages >= GW_MIN_STAGES && (ranges == 1 || range % window == 0)) {
+    hipLaunchKernelGGL(gram_wide_kernel, dim3((unsigned)t.wide_entries), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
+                       (cols_out + 127) / 128 * 2, nstages, rows_out, cols_out, cols_out, acc.out, t.wide, 2 * window, symmetric);
+    return hipGetLastError();
+  }
+  const int per = (ranges + acc.copies - 1) / acc.copies * range, parts = (nstages + per - 1) / per;
+  const int64_t elems = (int64_t)rows_out * cols_out;
+  if (acc.cleared && *acc.cleared < parts) {      // copies that no earlier call of this result has used
+    hipLaunchKernelGGL(fill_zero_f64_kernel, dim3(2048), dim3(256), 0, s, acc.out + *acc.cleared * elems, (parts - *acc.cleared) * elems);
+    *acc.cleared = parts;
+  }
+  hipLaunchKernelGGL(gram_packed_kernel, dim3((unsigned)t.entries, (unsigned)parts), dim3(256), (size_t)2 * 4 * PK_SLOTS * 16, s, Ap, Bp, nstages,
+                     rows_out, cols_out, cols_out, acc.out, elems, t.list, per, window, range, symmetric);
+  return hipGetLastError();
+}
+
+hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, const PackedAcc& H64, const PackedTiles& tiles,
+                              void* pack_buf, int64_t pack_rows, hipStream_t s, const void* Yc, int64_t ldy, int m, const PackedAcc& G64,
+                              const PackedTiles& tiles_y, void* pack_buf_y, const ConvSpec* conv, hipEvent_t* ev, int ev_pairs, int* ev_used) {
   if (ev_used) *ev_used = 0;
   if (n_c <= 0) return hipSuccess;
-  if (pack_rows < GBK || pack_rows % GBK || !tiles || tile_entries == 0) return hipErrorInvalidValue;
-  if (Yc && (!tiles_y || tile_y_entries == 0)) return hipErrorInvalidValue;
-  const int npanels = (d1 + 127) / 128, npanels_y = Yc ? (m + 127) / 128 : 0;
-  const int ntiles = npanels * (npanels + 1) / 2;
-  const int window = 16;   // 1024 tokens per MFMA accumulation window
+  if (pack_rows < GBK || pack_rows % GBK || !tiles.list || tiles.entries == 0) return hipErrorInvalidValue;
+  if (Yc && (!tiles_y.list || tiles_y.entries == 0)) return hipErrorInvalidValue;
+  const int npairs = (d1 + 127) / 128, npairs_y = Yc ? (m + 127) / 128 : 0;
+  const int ntiles = npairs * (npairs + 1) / 2, window = 16;   // 1024 tokens per MFMA accumulation window
   for (int64_t r0 = 0; r0 < n_c; r0 += pack_rows) {
     const int64_t nr = std::min<int64_t>(pack_rows, n_c - r0);
     const int nstages = (int)((nr + GBK - 1) / GBK);
     const uint16_t* src = reinterpret_cast<const uint16_t*>(Xc) + r0 * ldx;
     const uint4* Xp = reinterpret_cast<const uint4*>(pack_buf);
     if (conv)
-      hipLaunchKernelGGL(gram_pack_conv_kernel, dim3((npanels + 1) / 2, nstages), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(Xc),
-                         *conv, r0, nr, d1, npanels, reinterpret_cast<uint4*>(pack_buf));
+      hipLaunchKernelGGL(gram_pack_conv_kernel, dim3((npairs + 1) / 2, nstages), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(Xc),
+                         *conv, r0, nr, d1, npairs, reinterpret_cast<uint4*>(pack_buf));
     else
-      hipLaunchKernelGGL(gram_pack_kernel, dim3((npanels + 1) / 2, nstages), dim3(256), 0, s, src, nr, ldx, d1, npanels,
+      hipLaunchKernelGGL(gram_pack_kernel, dim3((npairs + 1) / 2, nstages), dim3(256), 0, s, src, nr, ldx, d1, npairs,
                          reinterpret_cast<uint4*>(pack_buf));
-    const int64_t xs = (int64_t)npanels * PK_SLOTS;
     const bool timed = ev && ev_used && *ev_used < ev_pairs;
     if (timed) hipEventRecord(ev[2 * *ev_used], s);
-    launch_packed_splits(Xp, xs, Xp, xs, nstages, d1, d1, d1, H64, tiles, tile_entries, ntiles, window, 1, s);
+    hipError_t e = launch_packed(Xp, Xp, nstages, d1, d1, H64, tiles, ntiles, window, 1, s);
+    if (e != hipSuccess) return e;
     if (timed) { hipEventRecord(ev[2 * *ev_used + 1], s); ++*ev_used; }
     if (Yc) {
       const uint16_t* srcy = reinterpret_cast<const uint16_t*>(Yc) + r0 * ldy;
       const uint4* Yp = reinterpret_cast<const uint4*>(pack_buf_y);
-      hipLaunchKernelGGL(gram_pack_kernel, dim3((npanels_y + 1) / 2, nstages), dim3(256), 0, s, srcy, nr, ldy, m, npanels_y,
+      hipLaunchKernelGGL(gram_pack_kernel, dim3((npairs_y + 1) / 2, nstages), dim3(256), 0, s, srcy, nr, ldy, m, npairs_y,
                          reinterpret_cast<uint4*>(pack_buf_y));
-      launch_packed_splits(Xp, xs, Yp, (int64_t)npanels_y * PK_SLOTS, nstages, d1, m, m, G64, tiles_y, tile_y_entries,
-                           npanels * npanels_y, window, 0, s);
+      if ((e = launch_packed(Xp, Yp, nstages, d1, m, G64, tiles_y, npairs * npairs_y, window, 0, s)) != hipSuccess) return e;
     }
   }
   return hipGetLastError();
@@ -416,7 +573,7 @@ __global__ __launch_bounds__(256) void gram_pack_split_kernel(const float* __res
       h[r][j] = bits;
     }
   }
-  uint4* out = Xp + ((int64_t)blockIdx.y * npanels + panel) * PK_SLOTS + kg * 128 + cg * 8;
+  uint4* out = Xp + pack_slot(panel, gridDim.y, blockIdx.y, kg, cg);
 #pragma unroll
   for (int j = 0; j < 8; j++)
     out[j] = uint4{h[0][j] | (h[1][j] << 16), h[2][j] | (h[3][j] << 16), h[4][j] | (h[5][j] << 16), h[6][j] | (h[7][j] << 16)};
@@ -424,9 +581,9 @@ __global__ __launch_bounds__(256) void gram_pack_split_kernel(const float* __res
 
 // G64 (d1 x m, float64, zeroed by the caller) += H W.  H: d1 x d1 float32 (ld = d1, d1 % 8 == 0, 16-byte aligned), W: d1 x m bf16
 // (m % 8 == 0, ldw % 8 == 0, 16-byte aligned).  pack_h: pack_rows * 128*ceil(d1/128) * 2 bytes, pack_w likewise for m.
-hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, int m, double* G64, const int2* tiles,
-                           size_t tile_entries, void* pack_h, void* pack_w, int64_t pack_rows, hipStream_t s) {
-  if (pack_rows < GBK || pack_rows % GBK || !tiles || tile_entries == 0) return hipErrorInvalidValue;
+hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, int m, double* G64, const PackedTiles& tiles,
+                           void* pack_h, void* pack_w, int64_t pack_rows, hipStream_t s) {
+  if (pack_rows < GBK || pack_rows % GBK || !tiles.list || tiles.entries == 0) return hipErrorInvalidValue;
   const int npanels = (d1 + 127) / 128, npanels_w = (m + 127) / 128;
   const int window = 16;
   for (int64_t r0 = 0; r0 < d1; r0 += pack_rows) {
@@ -437,8 +594,9 @@ hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, i
     for (int piece = 0; piece < 3; piece++) {
       hipLaunchKernelGGL(gram_pack_split_kernel, dim3((npanels + 1) / 2, nstages), dim3(256), 0, s, H + r0 * d1, nr, (int64_t)d1, d1,
                          npanels, piece, reinterpret_cast<uint4*>(pack_h));
-      launch_packed_splits(reinterpret_cast<const uint4*>(pack_h), (int64_t)npanels * PK_SLOTS, reinterpret_cast<const uint4*>(pack_w),
-                           (int64_t)npanels_w * PK_SLOTS, nstages, d1, m, m, G64, tiles, tile_entries, npanels * npanels_w, window, 0, s);
+      const hipError_t e = launch_packed(reinterpret_cast<const uint4*>(pack_h), reinterpret_cast<const uint4*>(pack_w), nstages, d1, m,
+                                         PackedAcc{G64, 1, nullptr}, tiles, npanels * npanels_w, window, 0, s);
+      if (e != hipSuccess) return e;
     }
   }
   return hipGetLastError();
@@ -459,7 +617,7 @@ hipError_t launch_pack_pieces(const float* A, int64_t lda, int64_t K, int cols, 
   if (K <= 0 || cols <= 0) return hipSuccess;
   if (cols % 8 || lda % 4 || (reinterpret_cast<uintptr_t>(A) & 15)) return hipErrorInvalidValue;
   const int npanels = (cols + 127) / 128, nstages = (int)(split_kpad(K) / GBK);
-  const size_t piece = (size_t)nstages * npanels * PK_SLOTS;      // uint4 packets per piece
+  const size_t piece = (size_t)nstages * npanels * 2 * PK_SLOTS;      // uint4 packets per piece
   for (int pc = 0; pc < 3; pc++)
     hipLaunchKernelGGL(gram_pack_split_kernel, dim3((npanels + 1) / 2, nstages), dim3(256), 0, s, A, K, lda, cols, npanels, pc,
                        reinterpret_cast<uint4*>(pack) + pc * piece);
@@ -479,19 +637,18 @@ __global__ void split_epilogue_kernel(const double* __restrict__ acc, int M, int
 
 // acc (M x N float64, dense) = A^T B from packed pieces; nprod = 6 (full float32 accuracy) or 3 (a1 b1 + a1 b2 + a2 b1: 2^-16)
 hipError_t launch_split_product(const void* packA, int M, const void* packB, int N, int64_t K, int nprod, double* acc,
-                                const int2* tiles, size_t tile_entries, int ntiles, hipStream_t s) {
+                                const PackedTiles& tiles, int ntiles, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (!tiles || tile_entries == 0 || (nprod != 6 && nprod != 3)) return hipErrorInvalidValue;
+  if (!tiles.list || tiles.entries == 0 || (nprod != 6 && nprod != 3)) return hipErrorInvalidValue;
   const int npa = (M + 127) / 128, npb = (N + 127) / 128, nstages = (int)(split_kpad(K) / GBK);
-  const size_t pieceA = (size_t)nstages * npa * PK_SLOTS, pieceB = (size_t)nstages * npb * PK_SLOTS;
+  const size_t pieceA = (size_t)nstages * npa * 2 * PK_SLOTS, pieceB = (size_t)nstages * npb * 2 * PK_SLOTS;
   hipError_t e = hipMemsetAsync(acc, 0, (size_t)M * N * 8, s);
   if (e != hipSuccess) return e;
   if (K <= 0) return hipSuccess;
   static const int combo[6][2] = {{0, 0}, {0, 1}, {1, 0}, {1, 1}, {0, 2}, {2, 0}};
   for (int c = 0; c < nprod; c++)
-    launch_packed_splits(reinterpret_cast<const uint4*>(packA) + combo[c][0] * pieceA, (int64_t)npa * PK_SLOTS,
-                         reinterpret_cast<const uint4*>(packB) + combo[c][1] * pieceB, (int64_t)npb * PK_SLOTS, nstages, M, N, N, acc,
-                         tiles, tile_entries, ntiles, 16, 0, s);
+    if ((e = launch_packed(reinterpret_cast<const uint4*>(packA) + combo[c][0] * pieceA, reinterpret_cast<const uint4*>(packB) + combo[c][1] * pieceB,
+                           nstages, M, N, PackedAcc{acc, 1, nullptr}, tiles, ntiles, 16, 0, s)) != hipSuccess) return e;
   return hipGetLastError();
 }
 
@@ -537,6 +694,22 @@ __global__ void finalize_G_kernel(const double* __restrict__ G64, const float* _
 }
 hipError_t launch_finalize_G(const double* G64, const float* Wf, const double* lambda_dev, float* G, int64_t n, hipStream_t s) {
   hipLaunchKernelGGL(finalize_G_kernel, dim3(2048), dim3(256), 0, s, G64, Wf, lambda_dev, G, n);
+  return hipGetLastError();
+}
+
+// A (rows x cols) += its copies 1 .. copies - 1 in order; lower: on and below the diagonal only.  Bound by reading the copies
+// (32 of 576 columns: 43 MB).
+__global__ __launch_bounds__(256) void sum_copies_kernel(double* __restrict__ A, int copies, int rows, int cols, int lower) {
+  const int64_t n = (int64_t)rows * cols, i = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (i >= n || (lower && i % cols > i / cols)) return;
+  double x = A[i];
+#pragma unroll 8
+  for (int cp = 1; cp < copies; cp++) x += A[cp * n + i];
+  A[i] = x;
+}
+hipError_t launch_sum_copies(double* A, int copies, int rows, int cols, int lower, hipStream_t s) {
+  if (copies <= 1) return hipSuccess;
+  hipLaunchKernelGGL(sum_copies_kernel, dim3((unsigned)(((int64_t)rows * cols + 255) / 256)), dim3(256), 0, s, A, copies, rows, cols, lower);
   return hipGetLastError();
 }
 

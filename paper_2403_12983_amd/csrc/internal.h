@@ -74,38 +74,46 @@ hipError_t launch_i8_gemm(const GemmArgs& g, void* packA, size_t capA, void* pac
 // ----------------------------------------------------------------------------------------------
 // gram.hip : H64 (+)= Xc^T Xc on the lower-triangle tiles (bf16 X, d1 % 8 == 0, ldx % 8 == 0, 16-byte aligned)
 // ----------------------------------------------------------------------------------------------
-// Repacks `pack_rows`-token chunks of Xc into MFMA operand order in pack_buf (pack_rows * 128*ceil(d1/128) * 2 bytes)
-// and accumulates them into H64.
-// tiles: the tile schedule on the device (gram_tile_list_host for the symmetric product, rect_tile_list_host for a
-// rectangular one), uploaded once by the caller; no call here waits for the stream.
+// Tile schedules of a packed product on the device, uploaded once by the caller (no call here waits for the stream): 128 x 128
+// tiles (gram_tile_list_host / rect_tile_list_host) and, optionally, 256 x 192 tiles (wide_tile_list_host).
+struct PackedTiles { const int2* list = nullptr; size_t entries = 0; const int2* wide = nullptr; size_t wide_entries = 0; };
+// A float64 result that is accumulated over calls, as the sum of up to `copies` consecutive copies of it; *cleared = how many of
+// them hold something (or zeros) so far, nullptr: the caller has cleared all.
+struct PackedAcc { double* out = nullptr; int copies = 1; int* cleared = nullptr; };
+hipError_t launch_sum_copies(double* A, int copies, int rows, int cols, int lower, hipStream_t s);      // into the first one, in order
+int packed_copies(int64_t elems, int64_t ntiles);      // copies worth keeping for a result of this many elements and 128 x 128 tiles
 // Patch geometry of a convolutional layer: row (b*Hout + oy)*Wout + ox, column (c*kh + dy)*kw + dx of the patch matrix is
 // F[b][c][oy*stride + dy - pad][ox*stride + dx - pad] (zero outside the map).
 struct ConvSpec { int B, C, Hin, Win, kh, kw, stride, pad, Hout, Wout; };
-hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, double* H64, const int2* tiles,
-                              size_t tile_entries, void* pack_buf, int64_t pack_rows, hipStream_t s,
-                              const void* Yc = nullptr, int64_t ldy = 0, int m = 0, double* G64 = nullptr,
-                              const int2* tiles_y = nullptr, size_t tile_y_entries = 0, void* pack_buf_y = nullptr,
+// Repacks `pack_rows`-token chunks of Xc into MFMA operand order in pack_buf (pack_rows * 128*ceil(d1/128) * 2 bytes)
+// and accumulates them into H64.
+hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, const PackedAcc& H64, const PackedTiles& tiles,
+                              void* pack_buf, int64_t pack_rows, hipStream_t s, const void* Yc = nullptr, int64_t ldy = 0, int m = 0,
+                              const PackedAcc& G64 = PackedAcc(), const PackedTiles& tiles_y = PackedTiles(), void* pack_buf_y = nullptr,
                               const ConvSpec* conv = nullptr, hipEvent_t* ev = nullptr, int ev_pairs = 0, int* ev_used = nullptr);
 // ev (optional, 2 * ev_pairs events): recorded before and after each launch of the symmetric product kernel (one per
 // pack_rows chunk), *ev_used = pairs recorded
 // host-side schedules: lower-triangle tiles of a d1 x d1 result / all tiles of a d1 x m result (128 x 128 tiles)
 void gram_tile_list_host(int d1, std::vector<int2>& out);
 void rect_tile_list_host(int d1, int m, std::vector<int2>& out);
+// the same for the 256 x 192 tiles of a rows x cols result (symmetric: of its lower triangle)
+void wide_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& out);
+size_t wide_tile_entries(int64_t rows, int64_t cols);      // an upper bound of that list's length
 // conv (optional): Xc is a feature map (NCHW, bf16) and the rows are its patches
 // Yc (optional, bf16 n_c x m): also G64 (d1 x m, float64) += Xc^T Yc, with its own tile list (>= 8 * (ceil(d1/128) *
 // ceil(m/128) / 8 + 64) entries) and pack buffer (pack_rows * 128*ceil(m/128) * 2 bytes)
 int gram_tile_schedule(int tiles_per_side, int32_t* out, int capacity);   // host only: the tile order of the SYRK kernel
 // G64 (zeroed by the caller) += H W for bf16 W through three bf16 pieces of the float32 H (see gram.hip)
-hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, int m, double* G64, const int2* tiles,
-                           size_t tile_entries, void* pack_h, void* pack_w, int64_t pack_rows, hipStream_t s);
+hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, int m, double* G64, const PackedTiles& tiles,
+                           void* pack_h, void* pack_w, int64_t pack_rows, hipStream_t s);
 // Products of float32 matrices on the bf16 matrix cores through three bf16 pieces per operand (see gram.hip).  Operands are
 // row-major with the contraction along their rows (C = A^T B).  pack: split_pack_bytes(K, cols) bytes, 256-byte aligned.
 size_t split_pack_bytes(int64_t K, int64_t cols);
 hipError_t launch_pack_pieces(const float* A, int64_t lda, int64_t K, int cols, void* pack, hipStream_t s);   // cols % 8 == 0, lda % 4 == 0
 // acc (M x N float64, dense; cleared here) = A^T B.  tiles: rect_tile_list_host(M, N), or gram_tile_list_host(M) for the lower
-// triangle of a square result (ntiles = number of real tiles in the list, for the split of the contraction over workgroups)
+// triangle of a square result (ntiles = number of real tiles in the list)
 hipError_t launch_split_product(const void* packA, int M, const void* packB, int N, int64_t K, int nprod, double* acc,
-                                const int2* tiles, size_t tile_entries, int ntiles, hipStream_t s);
+                                const PackedTiles& tiles, int ntiles, hipStream_t s);
 // C = float(beta * Cin + alpha * acc)
 hipError_t launch_split_epilogue(const double* acc, int M, int N, const float* Cin, int64_t ldcin, float* C, int64_t ldc, double alpha,
                                  double beta, hipStream_t s);

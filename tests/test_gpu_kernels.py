@@ -89,3 +89,39 @@ def test_sweep_inverse_at_the_edges_of_its_blocks(kr, side):
     R = np.linalg.inv(H.double().numpy()[np.ix_(groups, groups)])
     d = np.sqrt(np.diag(R))
     assert np.array_equal(P, P.T) and np.max(np.abs(P - R) / np.outer(d, d)) <= 6.1e-8
+
+
+@pytest.mark.parametrize("d1,m,chunks", [
+    (8, 8, [1, 600]), (136, 72, [5000, 63, 2048]),      # ranges of the contraction into copies, fewer of them later, ragged stages
+    (2048, 8, [2048, 500]), (1000, 1000, [1537]),
+    (3528, 2056, [8200]),                                # wide tiles, ragged in both directions and in the last stage
+    (3592, 2056, [700, 8129, 16384 + 64]),               # both kernels on one layer, a second repacked piece
+])
+def test_packed_gram_in_ranges_and_in_wide_tiles(d1, m, chunks):
+    """H = X^T X and G = X^T Y from bf16 rows, chunk by chunk.  Products are exact; the matrix core adds 16 rows at a time in
+    float32 and may cut off up to one unit in the last place, 2^-23 of the partial sum, each time; sums restart every 1024 rows
+    at most and go on in rounded float32 and float64.  64 such steps on a sum that grows evenly: at most 64 / 2 * 2^-23 = 3.8e-6
+    of sqrt(H_ii H_jj) (measured 3e-7, on the diagonal).  A missing or doubled stage of 64 rows would show as 1e-3."""
+    n = sum(chunks)
+    g = torch.Generator(device=DEV).manual_seed(d1 + n)
+    X = torch.randn(n, d1, generator=g, device=DEV).to(torch.bfloat16)
+    Y = torch.randn(n, m, generator=g, device=DEV).to(torch.bfloat16)
+    W = torch.zeros(d1, m, dtype=torch.bfloat16, device=DEV)
+    s = _pkg().Solver(d1, m, d1, 1, max(1, d1 // 2), 1, torch.bfloat16, torch.bfloat16, DEV, target_output=True)
+    r0 = 0
+    for c in chunks:
+        last = r0 + c == n
+        s.osscar_gram_target(X[r0:r0 + c], Y[r0:r0 + c], *((True, W, 0.0, 1e-2) if last else (False,)))
+        r0 += c
+    H, G = s.osscar_get_tensor(0).cpu().double().numpy(), s.osscar_get_tensor(1).cpu().double().numpy()
+    lam = s.osscar_get_scalars()[0]
+    s.close()
+    Hr, Gr = np.zeros((d1, d1)), np.zeros((d1, m))
+    for r0 in range(0, n, 4096):
+        Xd, Yd = X[r0:r0 + 4096].double(), Y[r0:r0 + 4096].double()
+        Hr += (Xd.T @ Xd).cpu().numpy()
+        Gr += (Xd.T @ Yd).cpu().numpy()
+    Hr += lam * np.eye(d1)
+    dx, dy = np.sqrt(np.diag(Hr)), np.sqrt((Y.double() ** 2).sum(0).cpu().numpy())
+    assert np.array_equal(H, H.T) and np.max(np.abs(H - Hr) / np.outer(dx, dx)) <= 3.8e-6
+    assert np.max(np.abs(G - Gr) / np.outer(dx, dy)) <= 3.8e-6
