@@ -26,8 +26,9 @@
 // The kernel: one workgroup of 8 waves (two per SIMD) per 128 x 128 tile, wave tile 64 x 32 = 2 matrix-core tiles x I8_S
 // accumulator sets (160 registers); operand blocks go from global memory straight into LDS (global_load_lds_dwordx4), three
 // stage buffers, loads three stages ahead; one barrier per stage that waits for LDS traffic only, placed before the last
-// two products of the stage so that the next stage's row-side operands are on their way while those run.  (With 4 waves of
-// 64 x 64, one per SIMD, the 14336^3 product took 51 ms instead of 41 ms: nothing to run while a wave waits.)
+// two products of the stage so that the next stage's row-side operands are on their way while those run.  14336^3: 36.2 ms
+// (0.49 of the int8 peak); 42.0 ms while the compiler's own waits emptied the request queue every stage.  (4 waves of 64 x 64, one
+// per SIMD, took 51 ms where 8 took 41: nothing to run while a wave waits.)
 #include "internal.h"
 
 namespace osscar {
@@ -184,10 +185,21 @@ struct I8Args {
   const float* A; int64_t lda; const float* B; int64_t ldb; int diag_a, diag_b;      // the operands themselves, for the diagonal terms
 };
 
-__device__ __forceinline__ void lds_only_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// vmcnt <= N; lgkmcnt = 0, then the barrier: builtins, which the compiler takes into account where it places waits of its own
+template <int N>
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14)); }
+__device__ __forceinline__ void lds_only_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (3 << 14));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
-  extern __shared__ uint4 lds[];                 // [3 stage buffers][A block | B block]
+  // Stage buffers, each the A block followed by the B block.  Three arrays and a steady loop without conditions: with one
+  // array, or with conditional requests, the compiler cannot tell which requests a read of LDS depends on and waits for all
+  // of them, the one just issued for three stages later included.
+  __shared__ uint4 lb0[2 * BLK], lb1[2 * BLK], lb2[2 * BLK];
   // 8 x 8 super-blocks of tiles, dealt to the XCDs in turn (workgroup index modulo 8): the tiles an XCD works on together
   // share row and column panels in its L2.  lower_only: the super-blocks on or below the diagonal.
   int tm, tn;
@@ -233,61 +245,71 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
       const int p0 = i * 512 + wave * 64;                                                                                        \
       const uint4* src = (p0 < BLK) ? ga + (int64_t)(st_) * BLK + p0 + lane : gb + (int64_t)(st_) * BLK + (p0 - BLK) + lane;     \
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,                                       \
-                                       (__attribute__((address_space(3))) void*)(lds + (buf_) * 2 * BLK + p0), 16, 0, 0);        \
+                                       (__attribute__((address_space(3))) void*)(buf_ + p0), 16, 0, 0);                          \
     }                                                                                                                            \
   }
-  OSSCAR_I8_ISSUE(0, 0);
-  if (nstages > 1) OSSCAR_I8_ISSUE(1, 1);
-  if (nstages > 2) OSSCAR_I8_ISSUE(2, 2);
+#define OSSCAR_I8_READ_A(buf_)                                                                                                   \
+  _Pragma("unroll") for (int t = 0; t < S; t++) _Pragma("unroll") for (int a = 0; a < 2; a++) {                                  \
+    uint4 q = buf_[t * 256 + oa + a * 32];                                                                                       \
+    fa[a][t] = *reinterpret_cast<v4i*>(&q);                                                                                      \
+  }
+  // A stage: column-side digits 0 .. S-2 against every row-side digit they meet (28 of its 30 products).  The last
+  // column-side digit goes to a register; then every wave has taken all it needs from this stage's buffer, which the barrier
+  // establishes, and NEXT refills the buffer with the stage three ahead and requests the next stage's row-side operands
+  // before the last two products.
+#define OSSCAR_I8_STAGE(cur_, NEXT)                                                                                              \
+  {                                                                                                                              \
+    const uint4* pb = cur_ + BLK;                                                                                                \
+    _Pragma("unroll") for (int u = 0; u < S - 1; u++) {                                                                          \
+      v4i fb;                                                                                                                    \
+      { uint4 q = pb[u * 256 + ob]; fb = *reinterpret_cast<v4i*>(&q); }                                                          \
+      _Pragma("unroll") for (int t = 0; t + u < S; t++) _Pragma("unroll") for (int a = 0; a < 2; a++)                            \
+        acc[t + u][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a][t], fb, acc[t + u][a], 0, 0, 0);                             \
+    }                                                                                                                            \
+    v4i fl;                                                                                                                      \
+    { uint4 q = pb[(S - 1) * 256 + ob]; fl = *reinterpret_cast<v4i*>(&q); }                                                      \
+    v4i a0[2];                                                                                                                   \
+    a0[0] = fa[0][0]; a0[1] = fa[1][0];                                                                                          \
+    NEXT                                                                                                                         \
+    _Pragma("unroll") for (int a = 0; a < 2; a++) acc[S - 1][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0[a], fl, acc[S - 1][a], 0, 0, 0); \
+  }
+#define OSSCAR_I8_STEADY(st_, cur_, nxt_)                                                                                        \
+  OSSCAR_I8_STAGE(cur_, wait_loads<NI>(); lds_only_barrier(); OSSCAR_I8_ISSUE((st_) + 3, cur_); OSSCAR_I8_READ_A(nxt_))
+#define OSSCAR_I8_TAIL(st_, cur_, nxt_)                                                                                          \
+  if ((st_) < nstages)                                                                                                           \
+    OSSCAR_I8_STAGE(cur_, if ((st_) + 1 < nstages) {                                                                             \
+      wait_loads<0>(); lds_only_barrier();                                                                                       \
+      if ((st_) + 3 < nstages) OSSCAR_I8_ISSUE((st_) + 3, cur_);                                                                 \
+      OSSCAR_I8_READ_A(nxt_)                                                                                                     \
+    })
   const int oa = (lane >> 5) * 128 + wm * 64 + (lane & 31), ob = (lane >> 5) * 128 + wn * 32 + (lane & 31);
+  OSSCAR_I8_ISSUE(0, lb0);
+  if (nstages > 1) OSSCAR_I8_ISSUE(1, lb1);
+  if (nstages > 2) OSSCAR_I8_ISSUE(2, lb2);
   // stage 0 has landed (each wave waits for its own loads of that stage, then the barrier)
-  if (nstages > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
-  else if (nstages == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (nstages > 2) wait_loads<2 * NI>(); else wait_loads<0>();
   lds_only_barrier();
   v4i fa[2][S];
-#pragma unroll
-  for (int t = 0; t < S; t++)
-#pragma unroll
-    for (int a = 0; a < 2; a++) { uint4 q = lds[t * 256 + oa + a * 32]; fa[a][t] = *reinterpret_cast<v4i*>(&q); }
-  int buf = 0;
-  for (int st = 0; st < nstages; st++) {
-    __builtin_amdgcn_iglp_opt(0);
-    const uint4* pb = lds + buf * 2 * BLK + BLK;
-    // column-side digits 0 .. S-2 against every row-side digit they meet: 28 of the stage's 30 products
-#pragma unroll
-    for (int u = 0; u < S - 1; u++) {
-      v4i fb;
-      { uint4 q = pb[u * 256 + ob]; fb = *reinterpret_cast<v4i*>(&q); }
-#pragma unroll
-      for (int t = 0; t + u < S; t++)
-#pragma unroll
-        for (int a = 0; a < 2; a++)
-          acc[t + u][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a][t], fb, acc[t + u][a], 0, 0, 0);
-    }
-    // The last column-side digit goes to a register; then every wave has taken all it needs from this stage's buffer,
-    // which the barrier establishes, and the buffer is refilled with the stage three ahead.  The next stage's row-side
-    // operands are requested before the last two products of this one.
-    v4i fl;
-    { uint4 q = pb[(S - 1) * 256 + ob]; fl = *reinterpret_cast<v4i*>(&q); }
-    v4i a0[2];
-    a0[0] = fa[0][0]; a0[1] = fa[1][0];
-    if (st + 1 < nstages) {
-      if (st + 2 < nstages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NI) : "memory");      // stage st + 1 has landed, st + 2 may be in flight
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      lds_only_barrier();
-      if (st + 3 < nstages) { const int nb = buf; OSSCAR_I8_ISSUE(st + 3, nb); }
-      const uint4* qa = lds + ((buf + 1) % 3) * 2 * BLK;
-#pragma unroll
-      for (int t = 0; t < S; t++)
-#pragma unroll
-        for (int a = 0; a < 2; a++) { uint4 q = qa[t * 256 + oa + a * 32]; fa[a][t] = *reinterpret_cast<v4i*>(&q); }
-    }
-#pragma unroll
-    for (int a = 0; a < 2; a++) acc[S - 1][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0[a], fl, acc[S - 1][a], 0, 0, 0);
-    buf = (buf + 1) % 3;
+  OSSCAR_I8_READ_A(lb0)
+  int st = 0;
+  if (nstages >= 6) {
+    do {
+      OSSCAR_I8_STEADY(st, lb0, lb1)
+      OSSCAR_I8_STEADY(st + 1, lb1, lb2)
+      OSSCAR_I8_STEADY(st + 2, lb2, lb0)
+      st += 3;
+    } while (st + 6 <= nstages);
+  }
+  for (; st < nstages; st += 3) {
+    OSSCAR_I8_TAIL(st, lb0, lb1)
+    OSSCAR_I8_TAIL(st + 1, lb1, lb2)
+    OSSCAR_I8_TAIL(st + 2, lb2, lb0)
   }
 #undef OSSCAR_I8_ISSUE
+#undef OSSCAR_I8_READ_A
+#undef OSSCAR_I8_STAGE
+#undef OSSCAR_I8_STEADY
+#undef OSSCAR_I8_TAIL
   // C layout of a 32 x 32 tile: register r = rr*4 + r3 holds row rr*8 + (lane/32)*4 + r3, column lane%32
   const int col = tn * 128 + wn * 32 + (lane & 31);
   const int eb = expo_of(g.mxb[col < g.N ? col : 0]);
@@ -350,12 +372,7 @@ hipError_t launch_i8_gemm(const GemmArgs& g, void* packA, size_t capA, void* pac
   int nsb;
   if (g.lower_only) { const int nr = (npa + 7) / 8; nsb = nr * (nr + 1) / 2; }
   else nsb = ((npa + 7) / 8) * ((npb + 7) / 8);
-  const size_t shmem = (size_t)3 * 2 * BLK * 16;
-  {   // 120 KB of dynamic shared memory needs the opt-in (per device; the call is host-side only)
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(i8_gemm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(i8_gemm_kernel, dim3((unsigned)((nsb + 7) / 8 * 8 * 64)), dim3(512), shmem, s, a);
+  hipLaunchKernelGGL(i8_gemm_kernel, dim3((unsigned)((nsb + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
   gemm_log_close(log_slot, s);
   return hipGetLastError();
 }
