@@ -106,6 +106,7 @@ struct osscar_ctx {
   float *H, *G, *N, *Z;
   double *norms2, *score, *gram, *dblk, *small, *scal, *partial, *dpart;
   double *cross, *xgram, *xdblk, *xscore;   // exact entering rule
+  double* gpart;                            // column chunks of the groups' Grams
   int32_t *kept, *rowsK, *rowsC, *notpd;
   float *C1, *C2, *Cblk, *rZ1, *rZ2;
   SearchCtrl* ctrl;
@@ -172,6 +173,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
   double* xgram = cv.take<double>(p * q * q);
   double* xdblk = cv.take<double>(p * q * q);
   double* xscore = cv.take<double>(p);
+  double* gpart = cv.take<double>(group_part_doubles(p, q, m));
   double* scal = cv.take<double>(1024);
   double* partial = cv.take<double>(2048);
   double* dpart = cv.take<double>((m + 15) / 16 + 64);
@@ -235,7 +237,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
   char* scratch = cv.take<char>(scratch_bytes);
   if (c) {
     c->H = H; c->G = G; c->N = N; c->Z = Z; c->norms2 = norms2; c->score = score; c->gram = gram; c->dblk = dblk;
-    c->cross = cross; c->xgram = xgram; c->xdblk = xdblk; c->xscore = xscore;
+    c->cross = cross; c->xgram = xgram; c->xdblk = xdblk; c->xscore = xscore; c->gpart = gpart;
     c->small = small; c->scal = scal; c->partial = partial; c->dpart = dpart; c->kept = kept; c->rowsK = rowsK; c->rowsC = rowsC;
     c->notpd = notpd; c->C1 = C1; c->C2 = C2; c->Cblk = Cblk; c->rZ1 = rZ1; c->rZ2 = rZ2; c->ctrl = ctrl;
     c->trace_out = trace_out; c->trace_in = trace_in; c->trace_gap = trace_gap; c->trace_obj = trace_obj;
@@ -278,7 +280,7 @@ TabPtrs ptrs(const osscar_ctx* c) {
   t.N = c->N; t.Z = c->Z; t.kept = c->kept; t.score = c->score; t.gram = c->gram; t.dblk = c->dblk;
   t.C1 = c->C1; t.C2 = c->C2; t.C1D = c->Cblk; t.C2D = c->Cblk + (int64_t)c->d1 * c->q;
   t.rZ1 = c->rZ1; t.rZ2 = c->rZ2; t.small = c->small; t.dpart = c->dpart; t.ctrl = c->ctrl;
-  t.cross = c->cross; t.xgram = c->xgram; t.xdblk = c->xdblk; t.xscore = c->xscore;
+  t.cross = c->cross; t.xgram = c->xgram; t.xdblk = c->xdblk; t.xscore = c->xscore; t.part = c->gpart;
   t.trace_out = c->trace_out; t.trace_in = c->trace_in; t.trace_gap = c->trace_gap; t.trace_obj = c->trace_obj;
   return t;
 }

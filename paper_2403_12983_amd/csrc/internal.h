@@ -189,12 +189,14 @@ struct TabPtrs {
   float* C1D; float* C2D;          // d1 x q panels times D
   float* rZ1; float* rZ2;          // q x m
   double* small;                   // scratch for q x q algebra (>= 16*q*q doubles)
+  double* part;                    // group_part_doubles(): the column chunks of the groups' Grams (groups of more than one row)
   double* dpart;                   // ceil(m / 16) partial sums of the exact change of a pair (column blocks, fixed order)
   double* cross; double* xgram; double* xdblk; double* xscore;   // exact entering rule: d1*q, p*q*q, p*q*q, p
   SearchCtrl* ctrl;
   int32_t* trace_out; int32_t* trace_in; float* trace_gap; double* trace_obj;
 };
 
+size_t group_part_doubles(int64_t p, int64_t q, int64_t m);
 hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s);
 hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s);        // first half: Gram and diagonal blocks
 hipError_t launch_refresh_from_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s);   // second half: the scores from them   // gram, dblk, score from N, Z

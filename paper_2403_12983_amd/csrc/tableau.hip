@@ -91,6 +91,160 @@ __device__ void small_inverse(double* A, int n, int want_sign, int32_t* bad, dou
   __syncthreads();
 }
 
+typedef double swd4 __attribute__((ext_vector_type(4)));
+// lane k of each row of 16 lanes, to all 16 of them
+template <int K>
+__device__ __forceinline__ double row16_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + K, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + K, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+// Pivots K.. of the Gauss-Jordan inverse of a 16 x 16 block that one wave holds like a result of v_mfma_f64_16x16x4_f64:
+// x[r] = element (4 r + lane / 16, lane % 16).  The pivot row crosses the rows of lanes by one ds_bpermute (two dwords),
+// the pivot column and the pivot itself by DPP broadcasts.
+template <int K>
+__device__ __forceinline__ void inv16_steps(swd4& x, int lane, int n, bool& flag) {
+  if constexpr (K < 16) {
+    if (K >= n) return;                    // uniform: rows and columns from n on behave as an identity block
+    const int from = (((K & 3) << 4) | (lane & 15)) << 2;
+    const double mine = x[K >> 2];
+    const double row = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(mine)),
+                                        __builtin_amdgcn_ds_bpermute(from, __double2loint(mine)));
+    double piv = row16_bcast<K>(row);
+    if (!(piv > 0.0)) { flag = true; piv = 1.0; }
+    const double d = 1.0 / piv, rs = row * d;
+    const bool pcol = (lane & 15) == K, prow = (lane >> 4) == (K & 3);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const double c = row16_bcast<K>(x[r]);
+      const double v = x[r] - c * rs;
+      x[r] = pcol ? -c * d : v;
+    }
+    if (prow) x[K >> 2] = pcol ? d : rs;
+    inv16_steps<K + 1>(x, lane, n, flag);
+  }
+}
+
+constexpr int IB_LD = 17;
+template <int NB> struct InvLds { double Pn[2][NB][16][IB_LD], Q[NB][16][IB_LD], D[2][16][IB_LD]; };
+// Inverse of the symmetric positive definite w x w block that get(i, j), j <= i < w, returns (w <= 16 NB, NB <= W), by one
+// workgroup of W waves that hold T of the lower 16 x 16 tiles each (W T >= NB (NB + 1) / 2); put(i, j, v), j <= i, receives it.
+// The symmetric sweep 16 pivots at a time: the tiles of tile column kb go to LDS as P, Q = P D on the matrix cores, every
+// other tile takes -= Q P^T, tile column kb becomes Q and its diagonal tile -D, so that the negated block is the inverse at
+// the end.  What bounds it is the chain of pivots (one wave, about 0.1 us each; 256 threads with one pivot per barrier took
+// 1.1 us each for 128 rows), so the wave that owns the next diagonal tile updates that one first and inverts it while the
+// other waves finish their tiles.  A pivot that is not positive is taken as 1 and reported (by every lane).
+template <int W, int T, int NB, typename Get, typename Put>
+__device__ __forceinline__ bool inv_sym(int w, InvLds<NB>& L, Get get, Put put) {
+  static_assert(NB <= W && W * T >= NB * (NB + 1) / 2, "tiles per wave");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  const int nb = (w + 15) / 16;
+  int ti[T], tj[T];
+  swd4 x[T];
+  bool flag = false;
+#pragma unroll
+  for (int s = 0; s < T; s++) {
+    const int t = wave + W * s;
+    int I = 0;
+    while ((I + 1) * (I + 2) / 2 <= t) I++;
+    ti[s] = __builtin_amdgcn_readfirstlane(I); tj[s] = __builtin_amdgcn_readfirstlane(t - I * (I + 1) / 2);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
+      const int hi = i > j ? i : j, lo = i > j ? j : i;
+      x[s][r] = hi < w ? get(hi, lo) : (i == j ? 1.0 : 0.0);
+    }
+  }
+  auto invert = [&](const swd4& a, int kb) {
+    swd4 y = a;
+    inv16_steps<0>(y, lane, w - kb * 16, flag);
+#pragma unroll
+    for (int r = 0; r < 4; r++) L.D[kb & 1][4 * r + lr][lc] = y[r];
+  };
+  if (wave == 0) invert(x[0], 0);
+  for (int kb = 0; kb < nb; kb++) {
+    double (*P)[16][IB_LD] = L.Pn[kb & 1];
+    double (*Dk)[IB_LD] = L.D[kb & 1];
+#pragma unroll
+    for (int s = 0; s < T; s++) {
+      if (ti[s] >= nb) continue;
+      if (tj[s] == kb && ti[s] > kb) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) P[ti[s]][4 * r + lr][lc] = x[s][r];
+      } else if (ti[s] == kb && tj[s] < kb) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) P[tj[s]][lc][4 * r + lr] = x[s][r];
+      }
+    }
+    __syncthreads();
+    if (wave < nb && wave != kb) {
+      swd4 q = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 4; kk++)
+        q = __builtin_amdgcn_mfma_f64_16x16x4f64(P[wave][lc][kk * 4 + lr], Dk[kk * 4 + lr][lc], q, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; r++) L.Q[wave][4 * r + lr][lc] = q[r];
+    }
+    __syncthreads();
+    auto update = [&](int s) {
+      const int I = ti[s], J = tj[s];
+      if (I >= nb) return;
+      if (I != kb && J != kb) {
+#pragma unroll
+        for (int kk = 0; kk < 4; kk++)
+          x[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(-L.Q[I][lc][kk * 4 + lr], P[J][lc][kk * 4 + lr], x[s], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+          x[s][r] = I > kb ? L.Q[I][4 * r + lr][lc] : J < kb ? L.Q[J][lc][4 * r + lr] : -Dk[4 * r + lr][lc];
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < T; s++)
+      if (ti[s] == kb + 1 && tj[s] == kb + 1 && kb + 1 < nb) { update(s); invert(x[s], kb + 1); }
+#pragma unroll
+    for (int s = 0; s < T; s++)
+      if (!(ti[s] == kb + 1 && tj[s] == kb + 1)) update(s);
+  }
+#pragma unroll
+  for (int s = 0; s < T; s++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
+      if (i < w && j <= i) put(i, j, -x[s][r]);
+    }
+  return __any(flag);
+}
+
+// out(i, j, sum_k a(i, k) b(k, j)) for i, j, k < q <= 16 RT, by the four waves of a workgroup, 16 x 16 tiles on the float64 matrix
+// cores; a and b return float64 from wherever they lie.
+template <int RT, typename FA, typename FB, typename FO>
+__device__ __forceinline__ void mm_small(int q, FA a, FB b, FO out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane >> 4, lc = lane & 15;
+  for (int t = wave; t < RT * RT; t += 4) {
+    const int i0 = t / RT * 16, j0 = t % RT * 16;
+    if (i0 >= q || j0 >= q) continue;
+    swd4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int k0 = 0; k0 < q; k0 += 4) {
+      const int k = k0 + lr;
+      const double av = (i0 + lc < q && k < q) ? a(i0 + lc, k) : 0.0, bv = (j0 + lc < q && k < q) ? b(k, j0 + lc) : 0.0;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+      if (i0 + 4 * r + lr < q && j0 + lc < q) out(i0 + 4 * r + lr, j0 + lc, acc[r]);
+  }
+}
+// f(integral_constant RT) for the number of 16-row tiles of a group
+#define OSSCAR_BY_TILES(q_, CALL)                                                        \
+  switch (((q_) + 15) / 16) {                                                            \
+    case 1: { constexpr int RT = 1; CALL; } break;                                       \
+    case 2: { constexpr int RT = 2; CALL; } break;                                       \
+    case 3: { constexpr int RT = 3; CALL; } break;                                       \
+    default: { constexpr int RT = 4; CALL; } break;                                      \
+  }
+
 __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   return v;
@@ -444,132 +598,19 @@ __global__ __launch_bounds__(256) void narrow_negate_mirror_kernel(const double*
     }
   }
 }
-typedef double swd4 __attribute__((ext_vector_type(4)));
-// lane k of each row of 16 lanes, to all 16 of them
-template <int K>
-__device__ __forceinline__ double row16_bcast(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + K, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + K, 0xF, 0xF, true);
-  return __hiloint2double(hi, lo);
-}
-// Pivots K.. of the Gauss-Jordan inverse of a 16 x 16 block that one wave holds like a result of v_mfma_f64_16x16x4_f64:
-// x[r] = element (4 r + lane / 16, lane % 16).  The pivot row crosses the rows of lanes by one ds_bpermute (two dwords),
-// the pivot column and the pivot itself by DPP broadcasts.
-template <int K>
-__device__ __forceinline__ void inv16_steps(swd4& x, int lane, bool& flag) {
-  if constexpr (K < 16) {
-    const int from = (((K & 3) << 4) | (lane & 15)) << 2;
-    const double mine = x[K >> 2];
-    const double row = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(mine)),
-                                        __builtin_amdgcn_ds_bpermute(from, __double2loint(mine)));
-    double piv = row16_bcast<K>(row);
-    if (!(piv > 0.0)) { flag = true; piv = 1.0; }
-    const double d = 1.0 / piv, rs = row * d;
-    const bool pcol = (lane & 15) == K, prow = (lane >> 4) == (K & 3);
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const double c = row16_bcast<K>(x[r]);
-      const double v = x[r] - c * rs;
-      x[r] = pcol ? -c * d : v;
-    }
-    if (prow) x[K >> 2] = pcol ? d : rs;
-    inv16_steps<K + 1>(x, lane, flag);
-  }
-}
-
-constexpr int IB_T = 768, IB_LD = 17;                  // 12 waves x 3 of the 36 lower 16 x 16 tiles of the pivot block
-struct InvBlockLds { double Pn[2][8][16][IB_LD], Q[8][16][IB_LD], D[2][16][IB_LD]; };
-// D (w x w) = inverse of the pivot block N[t0.., t0..] (lower triangle read, w <= 128), by one workgroup of 768 threads.
-// The symmetric sweep 16 pivots at a time: the tiles of tile column kb go to LDS as P, Q = P D on the matrix cores, every
-// other tile takes -= Q P^T, tile column kb becomes Q and its diagonal tile -D, so that -N is the inverse at the end.  What
-// bounds it is the chain of 128 pivots (one wave, about 0.1 us each), so the wave that owns the next diagonal tile updates that
-// one first and inverts it while the other waves finish their tiles.  Rows and columns past w behave as an identity block.
-__device__ void inv_block128(const double* __restrict__ N, int64_t ld, int t0, int w, double* __restrict__ D, int32_t* notpd, InvBlockLds& L) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
-  const int nb = (w + 15) / 16;
-  int ti[3], tj[3];
-  swd4 x[3];
-  bool flag = false;
-#pragma unroll
-  for (int s = 0; s < 3; s++) {
-    const int t = wave + 12 * s;
-    int I = 0;
-    while ((I + 1) * (I + 2) / 2 <= t) I++;
-    ti[s] = __builtin_amdgcn_readfirstlane(I); tj[s] = __builtin_amdgcn_readfirstlane(t - I * (I + 1) / 2);
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
-      const int hi = i > j ? i : j, lo = i > j ? j : i;
-      x[s][r] = hi < w ? N[(int64_t)(t0 + hi) * ld + t0 + lo] : (i == j ? 1.0 : 0.0);
-    }
-  }
-  auto invert = [&](const swd4& a, int kb) {
-    swd4 y = a;
-    inv16_steps<0>(y, lane, flag);
-#pragma unroll
-    for (int r = 0; r < 4; r++) L.D[kb & 1][4 * r + lr][lc] = y[r];
-  };
-  if (wave == 0) invert(x[0], 0);
-  for (int kb = 0; kb < nb; kb++) {
-    double (*P)[16][IB_LD] = L.Pn[kb & 1];
-    double (*Dk)[IB_LD] = L.D[kb & 1];
-#pragma unroll
-    for (int s = 0; s < 3; s++) {
-      if (tj[s] == kb && ti[s] > kb) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) P[ti[s]][4 * r + lr][lc] = x[s][r];
-      } else if (ti[s] == kb && tj[s] < kb) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) P[tj[s]][lc][4 * r + lr] = x[s][r];
-      }
-    }
-    __syncthreads();
-    if (wave < nb && wave != kb) {
-      swd4 q = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int kk = 0; kk < 4; kk++)
-        q = __builtin_amdgcn_mfma_f64_16x16x4f64(P[wave][lc][kk * 4 + lr], Dk[kk * 4 + lr][lc], q, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; r++) L.Q[wave][4 * r + lr][lc] = q[r];
-    }
-    __syncthreads();
-    auto update = [&](int s) {
-      const int I = ti[s], J = tj[s];
-      if (I >= nb) return;
-      if (I != kb && J != kb) {
-#pragma unroll
-        for (int kk = 0; kk < 4; kk++)
-          x[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(-L.Q[I][lc][kk * 4 + lr], P[J][lc][kk * 4 + lr], x[s], 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; r++)
-          x[s][r] = I > kb ? L.Q[I][4 * r + lr][lc] : J < kb ? L.Q[J][lc][4 * r + lr] : -Dk[4 * r + lr][lc];
-      }
-    };
-#pragma unroll
-    for (int s = 0; s < 3; s++)
-      if (ti[s] == kb + 1 && tj[s] == kb + 1 && kb + 1 < nb) { update(s); invert(x[s], kb + 1); }
-#pragma unroll
-    for (int s = 0; s < 3; s++)
-      if (!(ti[s] == kb + 1 && tj[s] == kb + 1)) update(s);
-  }
-  if (__any(flag) && lane == 0) *notpd = 1;
-#pragma unroll
-  for (int s = 0; s < 3; s++)
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
-      if (i < w && j <= i) { D[i * w + j] = -x[s][r]; D[j * w + i] = -x[s][r]; }
-    }
-}
-
 // C = the pivot columns t0 .. t0 + w of N for every row, and (the first workgroup) D = the inverse of the pivot block,
 // straight from N, so that the copy runs beside the inverse.
+constexpr int IB_T = 768;                              // 12 waves x 3 of the 36 lower tiles of a pivot block
 __global__ __launch_bounds__(IB_T) void panel_inverse64_kernel(const double* __restrict__ N, int64_t ld, int n, int t0, int w,
                                                                 double* __restrict__ C, double* __restrict__ D, int32_t* notpd) {
-  __shared__ InvBlockLds L;
-  static_assert(sizeof(InvBlockLds) >= PANEL_ROWS64 * 129 * sizeof(double), "the copy's tile shares the inverse's memory");
-  if (blockIdx.x == 0) { inv_block128(N, ld, t0, w, D, notpd, L); return; }
+  __shared__ InvLds<8> L;
+  static_assert(sizeof(InvLds<8>) >= PANEL_ROWS64 * 129 * sizeof(double), "the copy's tile shares the inverse's memory");
+  if (blockIdx.x == 0) {
+    const bool bad = inv_sym<12, 3, 8>(w, L, [&](int i, int j) { return N[(int64_t)(t0 + i) * ld + t0 + j]; },
+                                       [&](int i, int j, double v) { D[i * w + j] = v; D[j * w + i] = v; });
+    if (bad && (threadIdx.x & 63) == 0) *notpd = 1;
+    return;
+  }
   double (*T)[129] = reinterpret_cast<double (*)[129]>(&L);
   const int i0 = (blockIdx.x - 1) * PANEL_ROWS64, tid = threadIdx.x;
   if (i0 >= t0 + w) {
@@ -915,24 +956,6 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
 // ------------------------------------------------------------------------------------------------
 // scores: gram[h] = Z_h Z_h^T, dblk[h] = N_hh (float64), score[h] = Tr(gram_h |N_hh|^-1)
 // ------------------------------------------------------------------------------------------------
-// one workgroup per group; wave w takes the pairs (r, c), c <= r, in a fixed order, lanes over columns
-__device__ void group_gram(const float* __restrict__ Zg, int q, int m, double* __restrict__ gram_h) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int npairs = q * (q + 1) / 2;
-  for (int pr = wave; pr < npairs; pr += nw) {
-    int r = (int)((sqrtf(8.f * (float)pr + 1.f) - 1.f) * 0.5f);
-    while ((r + 1) * (r + 2) / 2 <= pr) r++;
-    while (r * (r + 1) / 2 > pr) r--;
-    int c = pr - r * (r + 1) / 2;
-    const float* zr = Zg + (int64_t)r * m;
-    const float* zc = Zg + (int64_t)c * m;
-    double v = 0;
-    for (int col = lane; col < m; col += 64) v += (double)zr[col] * (double)zc[col];
-    v = wave_sum(v);
-    if (lane == 0) { gram_h[r * q + c] = v; gram_h[c * q + r] = v; }
-  }
-}
-
 // groups of one row: gram[h] = |Z_h|^2 and dblk[h] = N_hh, one wave per row (four rows per workgroup), 16-byte loads
 __global__ __launch_bounds__(256) void gram_dblk_q1_kernel(int d1, int m, const float* __restrict__ N, const float* __restrict__ Z,
                                                             double* __restrict__ gram, double* __restrict__ dblk) {
@@ -953,35 +976,134 @@ __global__ __launch_bounds__(256) void gram_dblk_q1_kernel(int d1, int m, const 
   if (lane == 0) { gram[h] = v; dblk[h] = (double)N[(int64_t)h * d1 + h]; }
 }
 
-// gram[h] = Z_h Z_h^T for every group: 16 x 16 outputs per workgroup (lower blocks only, mirrored), Z tiles of 64 columns in LDS
-__global__ __launch_bounds__(256) void group_gram_kernel(TabDims d, const float* __restrict__ Z, double* __restrict__ gram,
-                                                          const SearchCtrl* __restrict__ ctrl) {
-  __shared__ float zr[16][65], zc[16][65];
+// Groups of more than one row: Z_h -= P1_h rZ1 + P2_h rZ2 (P1 == nullptr: left as it is; single: the first term only) and the
+// columns' share of gram[h] = Z_h Z_h^T, one pass over Z.  Workgroup = (group, chunk of columns); a wave takes 32 columns at
+// a time: the update on v_mfma_f32_16x16x4_f32 (float32 products and sums, as the elements are stored), the new values
+// through LDS into operand order, their products on v_mfma_f64_16x16x4_f64.  The waves' sums are added in order and left in
+// part[h][chunk][lower tile][256]; score_kernel adds the chunks in order.  Bound by the float32 matrix cores and Z's two
+// passes of memory about equally; as a row x 256 columns of scalar products and a second pass for the Grams a swap of two
+// groups of 64 rows, 4096 columns took 0.42 + 0.20 ms.
+constexpr int GU_LD = 36;
+template <int RT> struct GroupUpdLds { float zt[4][16 * RT][GU_LD]; };
+static __host__ __device__ inline int gu_kq(int q) { return (q + 3) / 4 * 4; }
+template <int RT>
+__global__ __launch_bounds__(256) void group_update_kernel(TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
+                                                            const float* __restrict__ P2, const float* __restrict__ rZ1,
+                                                            const float* __restrict__ rZ2, int single, double* __restrict__ part,
+                                                            int chunk_cols, const SearchCtrl* __restrict__ ctrl) {
+  extern __shared__ float gu_lds[];
   if (ctrl && ctrl->done) return;
-  const int q = d.q, m = d.m, h = blockIdx.x, nb = (q + 15) / 16;
-  int br = 0, bc = blockIdx.y;                      // linear index over the lower block triangle
-  while (bc > br) { bc -= br + 1; br++; }
-  if (br >= nb) return;
-  const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;
-  const int r = br * 16 + tr, c = bc * 16 + tc;
-  const float* Zh = Z + (int64_t)h * q * m;
-  double acc = 0;
-  for (int c0 = 0; c0 < m; c0 += 64) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < 16 * 64; idx += 256) {
-      const int rr = idx >> 6, cc = idx & 63;
-      const bool okc = c0 + cc < m;
-      zr[rr][cc] = (okc && br * 16 + rr < q) ? Zh[(int64_t)(br * 16 + rr) * m + c0 + cc] : 0.f;
-      zc[rr][cc] = (okc && bc * 16 + rr < q) ? Zh[(int64_t)(bc * 16 + rr) * m + c0 + cc] : 0.f;
+  constexpr int NT = RT * (RT + 1) / 2;
+  float (*zt)[16 * RT][GU_LD] = reinterpret_cast<float (*)[16 * RT][GU_LD]>(gu_lds);
+  float* Ps = gu_lds + 4 * 16 * RT * GU_LD;               // [16 RT][ks]: the rows' coefficients, both pivots' halves side by side
+  const int q = d.q, m = d.m, h = blockIdx.x, kq = gu_kq(q), K = P1 ? (single ? kq : 2 * kq) : 0, ks = 2 * kq + 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  float* Zh = Z + (int64_t)h * q * m;
+  for (int idx = tid; idx < 16 * RT * K; idx += 256) {
+    const int r = idx / K, kk = idx % K, half = kk >= kq, c = kk - half * kq;
+    Ps[r * ks + kk] = (r < q && c < q) ? (half ? P2 : P1)[((int64_t)h * q + r) * q + c] : 0.f;
+  }
+  __syncthreads();
+  swd4 g[NT];
+#pragma unroll
+  for (int t = 0; t < NT; t++) g[t] = swd4{0.0, 0.0, 0.0, 0.0};
+  const int c_end = min(m, ((int)blockIdx.y + 1) * chunk_cols);
+  for (int c0 = blockIdx.y * chunk_cols + wave * 32; c0 < c_end; c0 += 128) {
+    typedef float f4v __attribute__((ext_vector_type(4)));
+    f4v acc[RT][2];
+    float z[RT][2][4];
+#pragma unroll
+    for (int t = 0; t < RT; t++)
+#pragma unroll
+      for (int j = 0; j < 2; j++) {
+        acc[t][j] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int r = 0; r < 4; r++) {                     // C layout: row 4 (lane / 16) + r, column lane % 16
+          const int row = t * 16 + 4 * lr + r, col = c0 + j * 16 + lc;
+          z[t][j][r] = (row < q && col < m) ? Zh[(int64_t)row * m + col] : 0.f;
+        }
+      }
+#pragma unroll 8
+    for (int kk = 0; kk < K; kk += 4) {
+      const int half = kk >= kq, c = kk + lr - half * kq;
+      const float* rz = half ? rZ2 : rZ1;
+      float b[2];
+#pragma unroll
+      for (int j = 0; j < 2; j++) b[j] = (c < q && c0 + j * 16 + lc < m) ? rz[(int64_t)c * m + c0 + j * 16 + lc] : 0.f;
+#pragma unroll
+      for (int t = 0; t < RT; t++) {
+        const float av = Ps[(t * 16 + lc) * ks + kk + lr];
+#pragma unroll
+        for (int j = 0; j < 2; j++) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[j], acc[t][j], 0, 0, 0);
+      }
     }
+#pragma unroll
+    for (int t = 0; t < RT; t++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int row = t * 16 + 4 * lr + r, col = c0 + j * 16 + lc;
+          const float v = z[t][j][r] - acc[t][j][r];
+          if (K && row < q && col < m) Zh[(int64_t)row * m + col] = v;
+          zt[wave][row][j * 16 + lc] = v;
+        }
+    // the wave's own part of LDS: in order, no barrier
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int s4 = 0; s4 < 8; s4++) {
+      double v[RT];
+#pragma unroll
+      for (int t = 0; t < RT; t++) v[t] = (double)zt[wave][t * 16 + lc][4 * s4 + lr];
+#pragma unroll
+      for (int t = 0, n = 0; t < RT; t++)
+#pragma unroll
+        for (int u = 0; u <= t; u++, n++) g[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t], v[u], g[n], 0, 0, 0);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+  double* red = reinterpret_cast<double*>(gu_lds);        // [NT][256], over zt
+  for (int w = 0; w < 4; w++) {
     __syncthreads();
-#pragma unroll 16
-    for (int k = 0; k < 64; k++) acc += (double)zr[tr][k] * (double)zc[tc][k];
+    if (wave == w) {
+#pragma unroll
+      for (int t = 0; t < NT; t++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          double* p = red + t * 256 + r * 64 + lane;
+          *p = w ? *p + g[t][r] : g[t][r];
+        }
+    }
   }
-  if (r < q && c < q) {
-    gram[(int64_t)h * q * q + r * q + c] = acc;
-    gram[(int64_t)h * q * q + c * q + r] = acc;
-  }
+  __syncthreads();
+  double* out = part + ((int64_t)h * gridDim.y + blockIdx.y) * (NT * 256);
+  for (int idx = tid; idx < NT * 256; idx += 256) out[idx] = red[idx];
+}
+// columns per chunk of the pass over Z: about 1024 workgroups, whole steps of 128 columns
+static int gu_chunk_cols(int p, int m) {
+  const int chunks = std::max(1, std::min(1024 / std::max(p, 1), (m + 127) / 128));
+  return ((m + chunks - 1) / chunks + 127) / 128 * 128;
+}
+size_t group_part_doubles(int64_t p, int64_t q, int64_t m) {
+  if (q <= 1) return 0;
+  const int64_t rt = (q + 15) / 16, cc = gu_chunk_cols((int)p, (int)m);
+  return (size_t)(p * ((m + cc - 1) / cc) * (rt * (rt + 1) / 2) * 256);
+}
+static hipError_t launch_group_update(const TabDims& d, const TabPtrs& t, const float* P1, const float* P2, int single, const SearchCtrl* ctrl,
+                                      hipStream_t s) {
+  const int cc = gu_chunk_cols(d.p, d.m);
+  OSSCAR_BY_TILES(d.q, {
+    const size_t lds = (size_t)(4 * 16 * RT * GU_LD + 16 * RT * (2 * gu_kq(d.q) + 4)) * 4;
+    static_assert(sizeof(GroupUpdLds<RT>) >= RT * (RT + 1) / 2 * 256 * 8, "the reduction shares the tiles' memory");
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(group_update_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(group_update_kernel<RT>, dim3(d.p, (d.m + cc - 1) / cc), dim3(256), lds, s, d, t.Z, P1, P2, t.rZ1, t.rZ2, single, t.part, cc, ctrl);
+  })
+  return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void dblk_copy_kernel(TabDims d, const float* __restrict__ N, double* __restrict__ dblk) {
@@ -992,41 +1114,77 @@ __global__ __launch_bounds__(256) void dblk_copy_kernel(TabDims d, const float* 
   }
 }
 
-// score[h] = Tr(gram_h * (sigma * dblk_h)^-1), sigma = -1 for kept groups (N_hh = -P_hh), +1 otherwise.
-// One workgroup of 64 threads per group; Cholesky in shared memory, then one column solve per thread.
-__global__ __launch_bounds__(256) void score_kernel(TabDims d, const int32_t* __restrict__ kept,
-                                                     const double* __restrict__ gram, const double* __restrict__ dblk,
-                                                     double* __restrict__ score, SearchCtrl* ctrl, int skip_if_done) {
-  extern __shared__ double sh[];   // A: q*q, then 256 doubles for the inverse
-  __shared__ int32_t bad;
+// score[h] = Tr(gram_h (sigma dblk_h)^-1), sigma = -1 for kept groups (N_hh = -P_hh), +1 otherwise; one workgroup per group.
+// Before that, if given: gram_h = the sum of its column chunks (part), and the float64 diagonal block of a group outside the
+// pivots takes -= P1D_h P1_h^T + P2D_h P2_h^T (P1; single: the first term only).
+template <int RT>
+__global__ __launch_bounds__(256) void score_kernel(TabDims d, const int32_t* __restrict__ kept, double* gram, double* dblk,
+                                                     double* __restrict__ score, SearchCtrl* ctrl, int skip_if_done,
+                                                     const double* __restrict__ part, int chunks, const float* __restrict__ P1,
+                                                     const float* __restrict__ P2, const float* __restrict__ P1D,
+                                                     const float* __restrict__ P2D, const int32_t* __restrict__ single) {
+  __shared__ InvLds<RT> L;
   __shared__ double red[4];
   if (skip_if_done && ctrl->done) return;          // a search iteration that changed nothing
-  const int h = blockIdx.x, q = d.q, tid = threadIdx.x;
-  const double sigma = kept[h] ? -1.0 : 1.0;
-  if (q == 1) {
-    if (tid == 0) {
-      double a = sigma * dblk[h];
-      if (!(a > 0.0)) { ctrl->notpd = 1; a = 1.0; }
-      score[h] = gram[h] / a;
+  constexpr int NT = RT * (RT + 1) / 2;
+  const int h = blockIdx.x, q = d.q, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  double* gram_h = gram + (int64_t)h * q * q;
+  double* dblk_h = dblk + (int64_t)h * q * q;
+  if (part) {
+    const double* ph = part + (int64_t)h * chunks * (NT * 256);
+    for (int idx = tid; idx < NT * 256; idx += 256) {
+      double v = 0;
+#pragma unroll 4
+      for (int ch = 0; ch < chunks; ch++) v += ph[(int64_t)ch * (NT * 256) + idx];
+      int t = idx >> 8, br = 0;
+      while (t > br) { t -= br + 1; br++; }
+      const int r = br * 16 + ((idx & 255) >> 4), c = t * 16 + (idx & 15);
+      if (r < q && c < q) {
+        gram_h[r * q + c] = v;
+        if (br != t) gram_h[c * q + r] = v;
+      }
     }
-    return;
   }
-  // Tr(|N_hh|^-1 Z_h Z_h^T): inverse of the q x q block by Gauss-Jordan in registers, then the sum of the products with
-  // the Gram block (both symmetric)
-  double* A = sh;
-  double* buf = sh + q * q;
-  if (tid == 0) bad = 0;
-  for (int idx = tid; idx < q * q; idx += 256) A[idx] = sigma * dblk[(int64_t)h * q * q + idx];
-  small_inverse<4>(A, q, +1, &bad, buf);
-  double contrib = 0;
-  for (int idx = tid; idx < q * q; idx += 256) contrib += A[idx] * gram[(int64_t)h * q * q + idx];
-  contrib = wave_sum(contrib);
-  if ((tid & 63) == 0) red[tid >> 6] = contrib;
+  if (P1) {
+    const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in;
+    if (h != g && h != j) {                       // pivot groups get their blocks in pair_fix_kernel
+      const int64_t base = (int64_t)h * q * q;
+      for (int t = wave; t < NT; t += 4) {
+        int br = 0, bc = t;
+        while (bc > br) { bc -= br + 1; br++; }
+        const int i = br * 16 + lc, l = bc * 16 + lc;
+        swd4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int half = 0; half < (single ? 1 : 2); half++) {
+          const float* A = half ? P2D : P1D;
+          const float* B = half ? P2 : P1;
+#pragma unroll 4
+          for (int k0 = 0; k0 < q; k0 += 4) {
+            const int k = k0 + lr;
+            const double av = (i < q && k < q) ? (double)A[base + i * q + k] : 0.0, bv = (l < q && k < q) ? (double)B[base + l * q + k] : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int a = br * 16 + 4 * r + lr, b = bc * 16 + lc;
+          if (a < q && b <= a) {
+            const double v = dblk_h[a * q + b] - acc[r];
+            dblk_h[a * q + b] = v; dblk_h[b * q + a] = v;
+          }
+        }
+      }
+    }
+  }
   __syncthreads();
-  if (tid == 0) {
-    score[h] = red[0] + red[1] + red[2] + red[3];
-    if (bad) ctrl->notpd = 1;
-  }
+  const double sigma = kept[h] ? -1.0 : 1.0;
+  double contrib = 0;
+  const bool bad = inv_sym<4, (NT + 3) / 4, RT>(q, L, [&](int i, int j) { return sigma * dblk_h[i * q + j]; },
+                                                [&](int i, int j, double v) { contrib += (i == j ? 1.0 : 2.0) * v * gram_h[i * q + j]; });
+  contrib = wave_sum(contrib);
+  if (lane == 0) red[wave] = contrib;
+  if (bad && lane == 0) ctrl->notpd = 1;
+  __syncthreads();
+  if (tid == 0) score[h] = red[0] + red[1] + red[2] + red[3];
 }
 // groups of one row: one thread per group
 __global__ __launch_bounds__(256) void score_q1_kernel(int p, const int32_t* __restrict__ kept, const double* __restrict__ gram,
@@ -1039,13 +1197,16 @@ __global__ __launch_bounds__(256) void score_q1_kernel(int p, const int32_t* __r
   if (!(a > 0.0)) { ctrl->notpd = 1; a = 1.0; }
   score[h] = gram[h] / a;
 }
-static void launch_score(const TabDims& d, const int32_t* kept, const double* gram, const double* dblk, double* score,
-                         SearchCtrl* ctrl, int skip_if_done, hipStream_t s) {
-  if (d.q == 1)
+struct ScoreUpdate { const double* part = nullptr; const float *P1 = nullptr, *P2 = nullptr, *P1D = nullptr, *P2D = nullptr; const int32_t* single = nullptr; };
+static void launch_score(const TabDims& d, const int32_t* kept, double* gram, double* dblk, double* score, SearchCtrl* ctrl, int skip_if_done,
+                         hipStream_t s, const ScoreUpdate& u = ScoreUpdate()) {
+  if (d.q == 1) {
     hipLaunchKernelGGL(score_q1_kernel, dim3((d.p + 255) / 256), dim3(256), 0, s, d.p, kept, gram, dblk, score, ctrl, skip_if_done);
-  else
-    hipLaunchKernelGGL(score_kernel, dim3(d.p), dim3(256), (size_t)(d.q * d.q + 256) * 8, s, d, kept, gram, dblk, score, ctrl,
-                       skip_if_done);
+    return;
+  }
+  const int cc = gu_chunk_cols(d.p, d.m);
+  OSSCAR_BY_TILES(d.q, hipLaunchKernelGGL(score_kernel<RT>, dim3(d.p), dim3(256), 0, s, d, kept, gram, dblk, score, ctrl, skip_if_done, u.part,
+                                          (d.m + cc - 1) / cc, u.P1, u.P2, u.P1D, u.P2D, u.single))
 }
 
 // the two halves of the refresh: the per-group Gram blocks and diagonal blocks (one pass over Z and the diagonal of N),
@@ -1054,14 +1215,16 @@ hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipStream_t
   if (d.q == 1) {
     hipLaunchKernelGGL(gram_dblk_q1_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d.d1, d.m, t.N, t.Z, t.gram, t.dblk);
   } else {
-    const int nb = (d.q + 15) / 16;
-    hipLaunchKernelGGL(group_gram_kernel, dim3(d.p, nb * (nb + 1) / 2), dim3(256), 0, s, d, t.Z, t.gram, (const SearchCtrl*)nullptr);
+    const hipError_t e = launch_group_update(d, t, nullptr, nullptr, 0, nullptr, s);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(dblk_copy_kernel, dim3(d.p), dim3(256), 0, s, d, t.N, t.dblk);
   }
   return hipGetLastError();
 }
 hipError_t launch_refresh_from_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s) {
-  launch_score(d, t.kept, t.gram, t.dblk, t.score, t.ctrl, 0, s);
+  ScoreUpdate u;
+  u.part = t.part;
+  launch_score(d, t.kept, t.gram, t.dblk, t.score, t.ctrl, 0, s, u);
   return hipGetLastError();
 }
 hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s) {
@@ -1258,128 +1421,149 @@ __global__ __launch_bounds__(1024) void select_in_kernel(TabDims d, const int32_
   }
 }
 
-// panels of both pivots and copies of their Z rows
+// panels of both pivots (blockIdx.y = 0, 1: C1, C2; 64 rows per workgroup, through LDS where the pivot rows of N hold them) and
+// copies of their Z rows (blockIdx.y = 2, 3).  single != nullptr: removal of the one group *single, no second pivot.
 __global__ __launch_bounds__(256) void extract_pair_kernel(TabDims d, const float* __restrict__ N, const float* __restrict__ Z,
                                                             const SearchCtrl* __restrict__ ctrl, float* __restrict__ C1,
                                                             float* __restrict__ C2, float* __restrict__ Zg,
                                                             float* __restrict__ Zj, const int32_t* __restrict__ single) {
+  __shared__ float T[64][65];
   if (ctrl->done) return;
-  // single != nullptr: removal of the one group *single (no group enters); the second pivot then aliases the first
-  const int q = d.q, g0 = (single ? *single : ctrl->g_out) * q, j0 = (single ? *single : ctrl->g_in) * q;
-  int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < d.d1) {
-    for (int c = 0; c < q; c++) {
-      C1[(int64_t)i * q + c] = nsym(N, d.d1, i, g0 + c);
-      C2[(int64_t)i * q + c] = nsym(N, d.d1, i, j0 + c);
+  const int q = d.q, second = blockIdx.y & 1, tid = threadIdx.x;
+  const int t0 = (single ? *single : second ? ctrl->g_in : ctrl->g_out) * q;
+  if (blockIdx.y >= 2) {
+    const float* src = Z + (int64_t)t0 * d.m;
+    float* dst = second ? Zj : Zg;
+    for (int64_t idx = blockIdx.x * 256 + tid; idx < (int64_t)q * d.m; idx += (int64_t)gridDim.x * 256) dst[idx] = src[idx];
+    return;
+  }
+  float* C = second ? C2 : C1;
+  const int i0 = blockIdx.x * 64, ni = min(64, d.d1 - i0);
+  if (i0 + ni <= t0) {                                   // above the pivot: the pivot's rows of N, along i
+    for (int idx = tid; idx < 64 * q; idx += 256) {
+      const int c = idx >> 6, r = idx & 63;
+      if (r < ni) T[r][c] = N[(int64_t)(t0 + c) * d.d1 + i0 + r];
     }
+    __syncthreads();
+    for (int idx = tid; idx < ni * q; idx += 256) C[(int64_t)i0 * q + idx] = T[idx / q][idx % q];
+    return;
   }
-  int64_t tot = (int64_t)q * d.m;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < tot; idx += (int64_t)gridDim.x * 256) {
-    Zg[idx] = Z[(int64_t)g0 * d.m + idx];
-    Zj[idx] = Z[(int64_t)j0 * d.m + idx];
-  }
+  for (int idx = tid; idx < ni * q; idx += 256) C[(int64_t)i0 * q + idx] = nsym(N, d.d1, i0 + idx / q, t0 + idx % q);
 }
 
 // q x q algebra of the pair (the exact change of the objective and the acceptance test follow in pair_cols_kernel and
 // pair_accept_kernel).
-// small layout (doubles, each q*q): [0] Dg, [1] Njg, [2] M1 = Dg Ngj, [3] Dj' , [4] W2Dj = -M1 Dj', [5] scratch
+// small layout (doubles, each q*q): [0] Dg, [1] Njg, [2] M1 = Dg Ngj, [3] Dj' , [4] W2Dj = -M1 Dj'; single: Dg only (the
+// others are written as zeros for one-row groups, whose bulk kernels always take both terms).  One workgroup: bound by the
+// two chains of q pivots.
+template <int RT>
 __global__ __launch_bounds__(256) void pair_small_kernel(TabDims d, const float* __restrict__ C1, const float* __restrict__ C2,
                                                           double* __restrict__ small, SearchCtrl* ctrl,
                                                           const int32_t* __restrict__ single) {
-  extern __shared__ double psm[];      // three q x q matrices, then 256 doubles for the inverses
-  __shared__ int32_t bad;
+  extern __shared__ double psm[];      // three q x q matrices with rows of q + 1
+  __shared__ InvLds<RT> L;
   if (ctrl->done) return;
-  const int q = d.q, qq = q * q, tid = threadIdx.x;
+  constexpr int T = (RT * (RT + 1) / 2 + 3) / 4;
+  const int q = d.q, qq = q * q, qs = q + 1, tid = threadIdx.x;
   const int g0 = (single ? *single : ctrl->g_out) * q, j0 = (single ? *single : ctrl->g_in) * q;
   double* Dg = small; double* Njg = small + qq; double* M1 = small + 2 * qq; double* Dj = small + 3 * qq;
   double* W2Dj = small + 4 * qq;
-  double* X0 = psm; double* X1 = psm + qq; double* X2 = psm + 2 * qq; double* buf = psm + 3 * qq;
-  if (tid == 0) bad = 0;
-  for (int idx = tid; idx < qq; idx += 256) {
-    const int r = idx / q, c = idx % q;
-    X0[idx] = (double)C1[(int64_t)(g0 + r) * q + c];          // N_gg
-    const double njg = (double)C1[(int64_t)(j0 + r) * q + c]; // N(j_r, g_c)
-    Njg[idx] = njg;
-    X1[c * q + r] = njg;                                      // N_gj = Njg^T
-  }
-  small_inverse<4>(X0, q, -1, &bad, buf);                    // kept pivot: N_gg = -P_gg is negative definite
-  for (int idx = tid; idx < qq; idx += 256) Dg[idx] = X0[idx];
-  if (single) {
-    // Case 1 alone: with M1 = 0 and Dj' = 0 every term of the second sweep below vanishes
-    for (int idx = tid; idx < qq; idx += 256) { M1[idx] = 0.0; Dj[idx] = 0.0; W2Dj[idx] = 0.0; Njg[idx] = 0.0; }
-  } else {
-    for (int idx = tid; idx < qq; idx += 256) {              // M1 = Dg N_gj
-      const int r = idx / q, c = idx % q;
-      double v = 0;
-      for (int k = 0; k < q; k++) v += X0[r * q + k] * X1[k * q + c];
-      X2[idx] = v; M1[idx] = v;
+  double* X0 = psm; double* X1 = psm + q * qs; double* X2 = psm + 2 * q * qs;
+  if (!single)
+    for (int idx = tid; idx < qq; idx += 256) {
+      const double njg = (double)C1[(int64_t)j0 * q + idx];      // N(j_r, g_c)
+      Njg[idx] = njg;
+      X1[idx / q * qs + idx % q] = njg;
     }
-    __syncthreads();
-    for (int idx = tid; idx < qq; idx += 256) {              // X0 = N_jg
-      const int r = idx / q, c = idx % q;
-      X0[idx] = X1[c * q + r];
-    }
-    __syncthreads();
-    for (int idx = tid; idx < qq; idx += 256) {              // N'_jj = N_jj - N_jg M1  (into X1, N_gj being spent)
-      const int r = idx / q, c = idx % q;
-      double v = 0;
-      for (int k = 0; k < q; k++) v += X0[r * q + k] * X2[k * q + c];
-      Dj[idx] = (double)C2[(int64_t)(j0 + r) * q + c] - v;
-    }
-    __syncthreads();
-    for (int idx = tid; idx < qq; idx += 256) X1[idx] = Dj[idx];
-    small_inverse<4>(X1, q, +1, &bad, buf);                  // entering pivot: Schur complement, positive definite
-    for (int idx = tid; idx < qq; idx += 256) {              // W2Dj = W2 Dj', W2 = N'_gj = -M1
-      const int r = idx / q, c = idx % q;
-      double v = 0;
-      for (int k = 0; k < q; k++) v -= X2[r * q + k] * X1[k * q + c];
-      W2Dj[idx] = v; Dj[idx] = X1[idx];
-    }
-  }
+  // kept pivot: N_gg = -P_gg is negative definite
+  bool bad = inv_sym<4, T, RT>(q, L, [&](int i, int j) { return -(double)C1[(int64_t)(g0 + i) * q + j]; },
+                               [&](int i, int j, double v) { X0[i * qs + j] = X0[j * qs + i] = -v; Dg[i * q + j] = Dg[j * q + i] = -v; });
   __syncthreads();
-  if (tid == 0) { ctrl->delta = 0.0; if (bad) ctrl->notpd = 1; }
+  if (single) {
+    // Case 1 alone: with M1 = 0 and Dj' = 0 every term of the second sweep vanishes
+    if (q == 1 && tid == 0) { M1[0] = 0.0; Dj[0] = 0.0; W2Dj[0] = 0.0; Njg[0] = 0.0; }
+  } else {
+    mm_small<RT>(q, [&](int i, int k) { return X0[i * qs + k]; }, [&](int k, int j) { return X1[j * qs + k]; },      // M1 = Dg Ngj
+                 [&](int i, int j, double v) { X2[i * qs + j] = v; M1[i * q + j] = v; });
+    __syncthreads();
+    mm_small<RT>(q, [&](int i, int k) { return X1[i * qs + k]; }, [&](int k, int j) { return X2[k * qs + j]; },      // N'_jj = N_jj - N_jg M1
+                 [&](int i, int j, double v) { X0[i * qs + j] = (double)C2[(int64_t)(j0 + i) * q + j] - v; });
+    __syncthreads();
+    // entering pivot: Schur complement, positive definite
+    bad |= inv_sym<4, T, RT>(q, L, [&](int i, int j) { return X0[i * qs + j]; },
+                             [&](int i, int j, double v) { X1[i * qs + j] = X1[j * qs + i] = v; Dj[i * q + j] = Dj[j * q + i] = v; });
+    __syncthreads();
+    mm_small<RT>(q, [&](int i, int k) { return -X2[i * qs + k]; }, [&](int k, int j) { return X1[k * qs + j]; },     // W2Dj, W2 = N'_gj = -M1
+                 [&](int i, int j, double v) { W2Dj[i * q + j] = v; });
+  }
+  if (tid == 0) ctrl->delta = 0.0;
+  if (bad && (tid & 63) == 0) ctrl->notpd = 1;
 }
 
 // Column phase of the pair: rZ1 = Dg Zg ; Z'j = Zj - Njg rZ1 ; rZ2 = Dj' Z'j (both written in place of Zg, Zj) and
 // delta = -<Zg, rZ1> - <Z'j, rZ2>, one partial sum per workgroup in dpart (added up in a fixed order by the acceptance
-// kernel, so that the result does not depend on scheduling).  16 columns x 16 row slots per workgroup; the three q x q
-// matrices and the column tiles live in LDS.
+// kernel, so that the result does not depend on scheduling).  16 columns per workgroup, a wave = 16 rows, float64 matrix cores;
+// the q x q matrices come from L2 (a row's 4 k are 32 bytes).
 constexpr int PC_COLS = 16;
+template <int RT>
 __global__ __launch_bounds__(256) void pair_cols_kernel(TabDims d, float* __restrict__ Zg, float* __restrict__ Zj,
-                                                         const double* __restrict__ small, SearchCtrl* ctrl, double* __restrict__ dpart) {
-  extern __shared__ double pcs[];   // Dg, Njg, Dj (q*q each), ta, tb (q*16 each)
+                                                         const double* __restrict__ small, SearchCtrl* ctrl, double* __restrict__ dpart,
+                                                         const int32_t* __restrict__ single) {
+  __shared__ double ta[16 * RT][PC_COLS + 1], tb[16 * RT][PC_COLS + 1];
   __shared__ double red[4];
   if (ctrl->done) return;
-  const int q = d.q, qq = q * q, m = d.m, tid = threadIdx.x;
-  double* Dg = pcs; double* Njg = pcs + qq; double* Dj = pcs + 2 * qq; double* ta = pcs + 3 * qq; double* tb = ta + q * PC_COLS;
-  for (int idx = tid; idx < qq; idx += 256) { Dg[idx] = small[idx]; Njg[idx] = small[qq + idx]; Dj[idx] = small[3 * qq + idx]; }
-  const int c = tid & 15, slot = tid >> 4, col = blockIdx.x * PC_COLS + c;
-  const bool live = col < m;
-  for (int r = slot; r < q; r += 16) ta[r * PC_COLS + c] = live ? (double)Zg[(int64_t)r * m + col] : 0.0;
+  const int q = d.q, qq = q * q, m = d.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  const double* Dg = small; const double* Njg = small + qq; const double* Dj = small + 3 * qq;
+  const int i0 = wave * 16, col = blockIdx.x * PC_COLS + lc;
+  const bool live = col < m, mine = i0 < q;
+  for (int r = tid >> 4; r < q; r += 16) ta[r][tid & 15] = blockIdx.x * PC_COLS + (tid & 15) < m ? (double)Zg[(int64_t)r * m + blockIdx.x * PC_COLS + (tid & 15)] : 0.0;
   __syncthreads();
+  auto product = [&](const double* A, double (*B)[PC_COLS + 1]) {
+    swd4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (mine) {
+#pragma unroll 4
+      for (int k0 = 0; k0 < q; k0 += 4) {
+        const int k = k0 + lr;
+        const double av = (i0 + lc < q && k < q) ? A[(i0 + lc) * q + k] : 0.0, bv = k < q ? B[k][lc] : 0.0;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+      }
+    }
+    return acc;
+  };
   double part = 0;
-  for (int r = slot; r < q; r += 16) {                       // tb = Dg zg
-    double v = 0;
-    for (int k = 0; k < q; k++) v += Dg[r * q + k] * ta[k * PC_COLS + c];
-    tb[r * PC_COLS + c] = v;
-    part -= ta[r * PC_COLS + c] * v;
+  swd4 v = product(Dg, ta);                                  // tb = rZ1 = Dg zg
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int i = i0 + 4 * r + lr;
+    if (mine && i < q) {
+      part -= ta[i][lc] * v[r];
+      tb[i][lc] = v[r];
+      if (live) Zg[(int64_t)i * m + col] = (float)v[r];
+    }
   }
-  __syncthreads();
-  for (int r = slot; r < q; r += 16) {                       // ta = z'j = zj - Njg tb ; rZ1 out
-    double v = live ? (double)Zj[(int64_t)r * m + col] : 0.0;
-    for (int k = 0; k < q; k++) v -= Njg[r * q + k] * tb[k * PC_COLS + c];
-    ta[r * PC_COLS + c] = v;
-    if (live) Zg[(int64_t)r * m + col] = (float)tb[r * PC_COLS + c];
-  }
-  __syncthreads();
-  for (int r = slot; r < q; r += 16) {                       // rZ2 = Dj' z'j
-    double v = 0;
-    for (int k = 0; k < q; k++) v += Dj[r * q + k] * ta[k * PC_COLS + c];
-    part -= ta[r * PC_COLS + c] * v;
-    if (live) Zj[(int64_t)r * m + col] = (float)v;
+  if (!single) {
+    __syncthreads();
+    v = product(Njg, tb);                                    // ta = z'j = zj - Njg tb
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = i0 + 4 * r + lr;
+      if (mine && i < q) ta[i][lc] = (live ? (double)Zj[(int64_t)i * m + col] : 0.0) - v[r];
+    }
+    __syncthreads();
+    v = product(Dj, ta);                                     // rZ2 = Dj' z'j
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = i0 + 4 * r + lr;
+      if (mine && i < q) {
+        part -= ta[i][lc] * v[r];
+        if (live) Zj[(int64_t)i * m + col] = (float)v[r];
+      }
+    }
+  } else if (q == 1 && wave == 0 && lr == 0 && live) {
+    Zj[col] = 0.f;
   }
   part = wave_sum(part);
-  if ((tid & 63) == 0) red[tid >> 6] = part;
+  if (lane == 0) red[wave] = part;
   __syncthreads();
   if (tid == 0) dpart[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
@@ -1410,41 +1594,58 @@ __global__ __launch_bounds__(64) void pair_accept_kernel(SearchCtrl* ctrl, int a
 
 // bulk panels: P1 = C1, P2 = C2 - C1 M1, P1D = P1 Dg, P2D = P2 Dj', with the rows of both pivots zeroed;
 // and the new pivot rows of N and Z, the diagonal blocks (float64) and the membership flags.
-// T1 (d1 x q) = true C1 Dg, T2 (d1 x q) = true (C2 - C1 M1) Dj' for rows outside the pivots.
+// 16 rows per workgroup, a wave = 16 columns, float64 matrix cores; the q x q matrices come from L2.  single: P1 and P1D only.
+template <int RT>
 __global__ __launch_bounds__(256) void pair_panels_kernel(TabDims d, const float* __restrict__ C1, const float* __restrict__ C2,
                                                            const double* __restrict__ small, const SearchCtrl* __restrict__ ctrl,
                                                            float* __restrict__ P1, float* __restrict__ P2,
                                                            float* __restrict__ P1D, float* __restrict__ P2D,
                                                            const int32_t* __restrict__ single) {
-  // one thread per (row, column): 4 rows x 64 columns per workgroup; the q x q matrices are read from global memory
-  // (consecutive threads, consecutive columns), the row's own coefficients go through LDS
-  __shared__ double sc1[4][64], sc2[4][64];
+  __shared__ double sc1[16][16 * RT + 1], sc2[16][16 * RT + 1];
   if (ctrl->done) return;
-  const int q = d.q, qq = q * q;
+  const int q = d.q, qq = q * q, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   const int g0 = (single ? *single : ctrl->g_out) * q, j0 = (single ? *single : ctrl->g_in) * q;
   const double* Dg = small; const double* M1 = small + 2 * qq; const double* Dj = small + 3 * qq;
-  const int lr = threadIdx.x >> 6, c = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + lr;
-  const bool live = (i < d.d1) && (c < q);
-  const bool piv = (i >= g0 && i < g0 + q) || (i >= j0 && i < j0 + q);
-  sc1[lr][c] = live ? (double)C1[(int64_t)i * q + c] : 0.0;
+  const int i0 = blockIdx.x * 16, j = wave * 16 + lc, ni = min(16, d.d1 - i0);
+  for (int idx = tid; idx < 16 * q; idx += 256) sc1[idx / q][idx % q] = idx < ni * q ? (double)C1[(int64_t)i0 * q + idx] : 0.0;
   __syncthreads();
-  double v = 0;
-  if (live) {
-    v = (double)C2[(int64_t)i * q + c];
-    for (int k = 0; k < q; k++) v -= sc1[lr][k] * M1[k * q + c];
+  auto product = [&](const double (*A)[16 * RT + 1], const double* B) {
+    swd4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int k0 = 0; k0 < q; k0 += 4) {
+      const int k = k0 + lr;
+      const double av = k < q ? A[lc][k] : 0.0, bv = (k < q && j < q) ? B[k * q + j] : 0.0;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+    }
+    return acc;
+  };
+  swd4 v1 = {0.0, 0.0, 0.0, 0.0}, v2 = v1;
+  const bool mine = wave < RT;
+  if (mine) v1 = product(sc1, Dg);
+  if (!single) {
+    if (mine) {
+      const swd4 v = product(sc1, M1);
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int i = 4 * r + lr;
+        sc2[i][j] = (i < ni && j < q) ? (double)C2[(int64_t)(i0 + i) * q + j] - v[r] : 0.0;
+      }
+    }
+    __syncthreads();
+    if (mine) v2 = product(sc2, Dj);
   }
-  sc2[lr][c] = v;
-  __syncthreads();
-  if (!live) return;
-  const int64_t o = (int64_t)i * q + c;
-  if (piv) { P1[o] = 0.f; P2[o] = 0.f; P1D[o] = 0.f; P2D[o] = 0.f; return; }
-  double v1 = 0, v2 = 0;
-  for (int k = 0; k < q; k++) { v1 += sc1[lr][k] * Dg[k * q + c]; v2 += sc2[lr][k] * Dj[k * q + c]; }
-  P1[o] = (float)sc1[lr][c];
-  P2[o] = (float)sc2[lr][c];
-  P1D[o] = (float)v1;
-  P2D[o] = (float)v2;
+  if (!mine || j >= q) return;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int l = 4 * r + lr, i = i0 + l;
+    if (l >= ni) continue;
+    const bool piv = (i >= g0 && i < g0 + q) || (i >= j0 && i < j0 + q);
+    const int64_t o = (int64_t)i * q + j;
+    P1[o] = piv ? 0.f : (float)sc1[l][j];
+    P1D[o] = piv ? 0.f : (float)v1[r];
+    if (!single) { P2[o] = piv ? 0.f : (float)sc2[l][j]; P2D[o] = piv ? 0.f : (float)v2[r]; }
+    else if (q == 1) { P2[o] = 0.f; P2D[o] = 0.f; }
+  }
 }
 
 // New pivot rows (after both sweeps), for every l outside the pivots:
@@ -1452,136 +1653,173 @@ __global__ __launch_bounds__(256) void pair_panels_kernel(TabDims d, const float
 //   N''(j_r, l) =  P2D[l][r]
 // pivot-pivot blocks: N''_gg = -Dg - W2 Dj' W2^T, N''_jj = -Dj', N''(g, j) = W2 Dj'.
 // Z''_g = -rZ1 + M1 rZ2, Z''_j = rZ2.  Diagonal blocks of the other groups are updated in float64.
+// Workgroups: 16 rows l of N each (row_blocks of them), then 64 columns of the Z rows each; the first one also writes the
+// pivot-pivot blocks and the flags.
+template <int RT>
 __global__ __launch_bounds__(256) void pair_fix_kernel(TabDims d, float* __restrict__ N, float* __restrict__ Z,
-                                                        const float* __restrict__ P1, const float* __restrict__ P2,
                                                         const float* __restrict__ P1D, const float* __restrict__ P2D,
                                                         const float* __restrict__ rZ1, const float* __restrict__ rZ2,
                                                         const double* __restrict__ small, const SearchCtrl* __restrict__ ctrl,
                                                         double* __restrict__ dblk, int32_t* __restrict__ kept,
-                                                        const int32_t* __restrict__ single) {
+                                                        const int32_t* __restrict__ single, int row_blocks) {
+  __shared__ float tg[16][16 * RT + 1], tj[16][16 * RT + 1];
   if (ctrl->done) return;
-  const int q = d.q, qq = q * q, m = d.m;
+  const int q = d.q, qq = q * q, m = d.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in, g0 = g * q, j0 = j * q;
   const double* Dg = small; const double* M1 = small + 2 * qq; const double* Dj = small + 3 * qq; const double* W2Dj = small + 4 * qq;
   const int64_t ld = d.d1;
-  {
-    // one thread per (row l, pivot row r): 4 rows x 64 pivot rows per workgroup
-    const int l = blockIdx.x * 4 + (threadIdx.x >> 6), r = threadIdx.x & 63;
-    if (l < d.d1 && r < q) {
-      const bool in_g = (l >= g0 && l < g0 + q), in_j = (l >= j0 && l < j0 + q);
-      if (!in_g && !in_j) {
-        double vg = -(double)P1D[(int64_t)l * q + r];
-        for (int c = 0; c < q; c++) vg += M1[r * q + c] * (double)P2D[(int64_t)l * q + c];
-        const float vj = P2D[(int64_t)l * q + r];
-        const int gr = g0 + r, jr = j0 + r;
-        if (l < gr) N[(int64_t)gr * ld + l] = (float)vg; else N[(int64_t)l * ld + gr] = (float)vg;
-        if (!single) { if (l < jr) N[(int64_t)jr * ld + l] = vj; else N[(int64_t)l * ld + jr] = vj; }
+  if ((int)blockIdx.x >= row_blocks) {
+    const int col = ((int)blockIdx.x - row_blocks) * 64 + wave * 16 + lc;
+    for (int i0 = 0; i0 < q; i0 += 16) {
+      swd4 acc = {0.0, 0.0, 0.0, 0.0};
+      if (!single) {
+#pragma unroll 4
+        for (int k0 = 0; k0 < q; k0 += 4) {
+          const int k = k0 + lr;
+          const double av = (i0 + lc < q && k < q) ? M1[(i0 + lc) * q + k] : 0.0, bv = (k < q && col < m) ? (double)rZ2[(int64_t)k * m + col] : 0.0;
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int i = i0 + 4 * r + lr;
+        if (i >= q || col >= m) continue;
+        Z[(int64_t)(g0 + i) * m + col] = (float)(acc[r] - (double)rZ1[(int64_t)i * m + col]);
+        if (!single) Z[(int64_t)(j0 + i) * m + col] = rZ2[(int64_t)i * m + col];
       }
     }
+    return;
   }
-  // pivot-pivot blocks and flags: first workgroup
-  if (blockIdx.x == 0) {
-    for (int idx = threadIdx.x; idx < qq; idx += 256) {
-      int r = idx / q, c = idx % q;
-      double ngg = -Dg[idx];
-      for (int k = 0; k < q; k++) ngg += W2Dj[r * q + k] * M1[c * q + k];     // - W2 Dj' W2^T = + (W2 Dj') M1^T
-      double njj = -Dj[idx];
-      double ngj = W2Dj[idx];                                                  // N''(g_r, j_c)
-      dblk[(int64_t)g * qq + idx] = ngg;
-      if (c <= r) N[(int64_t)(g0 + r) * ld + g0 + c] = (float)ngg;
-      if (single) continue;
+  const int l0 = blockIdx.x * 16, nl = min(16, d.d1 - l0);
+  if (!single) {
+    for (int idx = tid; idx < 16 * q; idx += 256) tj[idx / q][idx % q] = idx < nl * q ? P2D[(int64_t)l0 * q + idx] : 0.f;
+    __syncthreads();
+  }
+  if (wave < RT) {
+    const int r0 = wave * 16 + lc;                 // pivot row
+    swd4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (!single) {
+#pragma unroll 4
+      for (int k0 = 0; k0 < q; k0 += 4) {
+        const int k = k0 + lr;
+        const double av = k < q ? (double)tj[lc][k] : 0.0, bv = (k < q && r0 < q) ? M1[r0 * q + k] : 0.0;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int l = 4 * r + lr;
+      if (l < nl && r0 < q) tg[l][r0] = (float)(acc[r] - (double)P1D[(int64_t)(l0 + l) * q + r0]);
+    }
+  }
+  __syncthreads();
+  auto write = [&](int t0, const float (*T)[16 * RT + 1], int other) {
+    auto outside = [&](int l) { return !(l >= t0 && l < t0 + q) && !(l >= other && l < other + q); };
+    if (l0 + nl <= t0) {                           // the pivot's rows of N, along l
+      for (int idx = tid; idx < 16 * q; idx += 256) {
+        const int l = idx & 15, r = idx >> 4;
+        if (l < nl && outside(l0 + l)) N[(int64_t)(t0 + r) * ld + l0 + l] = T[l][r];
+      }
+    } else {
+      for (int idx = tid; idx < nl * q; idx += 256) {
+        const int l = idx / q, r = idx % q, row = l0 + l, pr = t0 + r;
+        if (!outside(row)) continue;
+        if (row < pr) N[(int64_t)pr * ld + row] = T[l][r]; else N[(int64_t)row * ld + pr] = T[l][r];
+      }
+    }
+  };
+  write(g0, tg, j0);
+  if (!single) write(j0, tj, g0);
+  if (blockIdx.x != 0) return;
+  auto set_gg = [&](int r, int c, double ngg) {    // N''_gg
+    dblk[(int64_t)g * qq + r * q + c] = ngg;
+    if (c <= r) N[(int64_t)(g0 + r) * ld + g0 + c] = (float)ngg;
+  };
+  if (single) {
+    for (int idx = tid; idx < qq; idx += 256) set_gg(idx / q, idx % q, -Dg[idx]);
+  } else {
+    // - W2 Dj' W2^T = + (W2 Dj') M1^T
+    mm_small<RT>(q, [&](int i, int k) { return W2Dj[i * q + k]; }, [&](int k, int c) { return M1[c * q + k]; },
+                 [&](int i, int c, double v) { set_gg(i, c, v - Dg[i * q + c]); });
+    for (int idx = tid; idx < qq; idx += 256) {
+      const int r = idx / q, c = idx % q;
+      const double njj = -Dj[idx], ngj = W2Dj[idx];                            // N''(g_r, j_c)
       dblk[(int64_t)j * qq + idx] = njj;
       if (c <= r) N[(int64_t)(j0 + r) * ld + j0 + c] = (float)njj;
       if (g0 > j0) N[(int64_t)(g0 + r) * ld + j0 + c] = (float)ngj;
       else N[(int64_t)(j0 + c) * ld + g0 + r] = (float)ngj;
     }
-    if (threadIdx.x == 0) { kept[g] = 0; if (!single) kept[j] = 1; }
   }
-  // Z rows of the pivots
-  int64_t tot = (int64_t)q * m;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < tot; idx += (int64_t)gridDim.x * 256) {
-    int r = (int)(idx / m), col = (int)(idx % m);
-    double vg = -(double)rZ1[idx];
-    for (int c = 0; c < q; c++) vg += M1[r * q + c] * (double)rZ2[(int64_t)c * m + col];
-    Z[(int64_t)(g0 + r) * m + col] = (float)vg;
-    if (!single) Z[(int64_t)(j0 + r) * m + col] = rZ2[idx];
-  }
+  if (tid == 0) { kept[g] = 0; if (!single) kept[j] = 1; }
 }
 
-// float64 diagonal blocks of the groups outside the pivots: dblk[h] -= P1D_h P1_h^T + P2D_h P2_h^T.  One workgroup per group.
-__global__ __launch_bounds__(256) void pair_dblk_kernel(TabDims d, const float* __restrict__ P1, const float* __restrict__ P2,
-                                                         const float* __restrict__ P1D, const float* __restrict__ P2D,
-                                                         const SearchCtrl* __restrict__ ctrl, double* __restrict__ dblk,
-                                                         const int32_t* __restrict__ single) {
-  extern __shared__ float pds[];   // the four q x q panels of this group
-  if (ctrl->done) return;
-  const int q = d.q, qq = q * q, h = blockIdx.x;
-  const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in;
-  if (h == g || h == j) return;    // pivot groups get their blocks in pair_fix_kernel
-  // rows of b1, b2 are read by neighbouring threads: stride q + 1 keeps them in different LDS banks
-  const int qs = q + 1;
-  float* a1 = pds; float* a2 = pds + qq; float* b1 = pds + 2 * qq; float* b2 = b1 + q * qs;
-  const int64_t base = (int64_t)h * qq;
-  for (int idx = threadIdx.x; idx < qq; idx += 256) {
-    const int r = idx / q, c = idx % q;
-    a1[idx] = P1D[base + idx]; a2[idx] = P2D[base + idx]; b1[r * qs + c] = P1[base + idx]; b2[r * qs + c] = P2[base + idx];
-  }
-  __syncthreads();
-  for (int idx = threadIdx.x; idx < qq; idx += 256) {
-    const int r = idx / q, c = idx % q;
-    double v = 0;
-    for (int k = 0; k < q; k++) v += (double)a1[r * q + k] * (double)b1[c * qs + k] + (double)a2[r * q + k] * (double)b2[c * qs + k];
-    dblk[base + idx] -= v;
-  }
-}
-
-// bulk update of the lower triangle: N[i][l] -= sum_c P1D[i][c] P1[l][c] + P2D[i][c] P2[l][c]
-// generic in q; 64 x 64 tiles, 16 x 16 threads, 4 x 4 elements per thread, panels staged in LDS 16 columns at a time.
+// bulk update of the lower triangle: N[i][l] -= sum_c P1D[i][c] P1[l][c] + P2D[i][c] P2[l][c] (single: the first term only).
+// 64 x 64 tiles, four waves x (2 x 2) v_mfma_f32_16x16x4_f32, the panels' rows whole in LDS (rows of 2 kq + 4 floats: the 16
+// rows x 4 k of an operand read lie in different banks).  Bound by N's read and write; the requests for N go first.
 __global__ __launch_bounds__(256) void update_N_kernel(TabDims d, float* __restrict__ N, const float* __restrict__ P1,
                                                         const float* __restrict__ P2, const float* __restrict__ P1D,
-                                                        const float* __restrict__ P2D, const SearchCtrl* __restrict__ ctrl) {
+                                                        const float* __restrict__ P2D, const SearchCtrl* __restrict__ ctrl, int single) {
+  extern __shared__ float un_lds[];
   if (ctrl->done) return;
-  const int tr = blockIdx.y, tc = blockIdx.x;
-  if (tc > tr) return;
-  __shared__ float sRD[2][64][17];   // P1D / P2D rows of this tile
-  __shared__ float sC[2][64][17];    // P1 / P2 rows of the column range
-  const int q = d.q, n = d.d1;
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  const int i0 = tr * 64, l0 = tc * 64;
-  float acc[4][4] = {};
-  for (int c0 = 0; c0 < q; c0 += 16) {
-    int cw = (q - c0 < 16) ? q - c0 : 16;
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < 64 * 16; idx += 256) {
-      int r = idx >> 4, c = idx & 15;
-      bool okc = c < cw;
-      int ri = i0 + r, rl = l0 + r;
-      sRD[0][r][c] = (okc && ri < n) ? P1D[(int64_t)ri * q + c0 + c] : 0.f;
-      sRD[1][r][c] = (okc && ri < n) ? P2D[(int64_t)ri * q + c0 + c] : 0.f;
-      sC[0][r][c] = (okc && rl < n) ? P1[(int64_t)rl * q + c0 + c] : 0.f;
-      sC[1][r][c] = (okc && rl < n) ? P2[(int64_t)rl * q + c0 + c] : 0.f;
-    }
-    __syncthreads();
-    for (int c = 0; c < cw; c++) {
-      float a1[4], a2[4], b1[4], b2[4];
+  typedef float f4v __attribute__((ext_vector_type(4)));
+  int tr = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
+  while ((int64_t)(tr + 1) * (tr + 2) / 2 <= (int64_t)blockIdx.x) tr++;
+  while ((int64_t)tr * (tr + 1) / 2 > (int64_t)blockIdx.x) tr--;
+  const int tc = (int)(blockIdx.x - (int64_t)tr * (tr + 1) / 2);
+  const int q = d.q, n = d.d1, kq = gu_kq(q), K = single ? kq : 2 * kq, ks = 2 * kq + 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  const int i0 = tr * 64, l0 = tc * 64, wi = (wave >> 1) * 32, wl = (wave & 1) * 32;
+  float* As = un_lds; float* Bs = un_lds + 64 * ks;
+  float old[2][2][4];
+  auto at = [&](int a, int b, int r) { return (int64_t)(i0 + wi + a * 16 + 4 * lr + r) * n + l0 + wl + b * 16 + lc; };
+  auto inside = [&](int a, int b, int r) {
+    const int i = i0 + wi + a * 16 + 4 * lr + r, l = l0 + wl + b * 16 + lc;
+    return i < n && l <= i;
+  };
 #pragma unroll
-      for (int u = 0; u < 4; u++) { a1[u] = sRD[0][ty * 4 + u][c]; a2[u] = sRD[1][ty * 4 + u][c]; b1[u] = sC[0][tx * 4 + u][c]; b2[u] = sC[1][tx * 4 + u][c]; }
+  for (int a = 0; a < 2; a++)
 #pragma unroll
-      for (int u = 0; u < 4; u++)
+    for (int b = 0; b < 2; b++)
 #pragma unroll
-        for (int v = 0; v < 4; v++) acc[u][v] += a1[u] * b1[v] + a2[u] * b2[v];
-    }
+      for (int r = 0; r < 4; r++) old[a][b][r] = inside(a, b, r) ? N[at(a, b, r)] : 0.f;
+  for (int idx = tid; idx < 64 * K; idx += 256) {
+    const int r = idx / K, kk = idx % K, half = kk >= kq, c = kk - half * kq;
+    As[r * ks + kk] = (c < q && i0 + r < n) ? (half ? P2D : P1D)[(int64_t)(i0 + r) * q + c] : 0.f;
+    Bs[r * ks + kk] = (c < q && l0 + r < n) ? (half ? P2 : P1)[(int64_t)(l0 + r) * q + c] : 0.f;
+  }
+  __syncthreads();
+  f4v acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; a++)
+#pragma unroll
+    for (int b = 0; b < 2; b++) acc[a][b] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int kk = 0; kk < K; kk += 4) {
+    float av[2], bv[2];
+#pragma unroll
+    for (int a = 0; a < 2; a++) { av[a] = As[(wi + a * 16 + lc) * ks + kk + lr]; bv[a] = Bs[(wl + a * 16 + lc) * ks + kk + lr]; }
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc[a][b], 0, 0, 0);
   }
 #pragma unroll
-  for (int u = 0; u < 4; u++) {
-    int i = i0 + ty * 4 + u;
-    if (i >= n) continue;
+  for (int a = 0; a < 2; a++)
 #pragma unroll
-    for (int v = 0; v < 4; v++) {
-      int l = l0 + tx * 4 + v;
-      if (l <= i) N[(int64_t)i * n + l] -= acc[u][v];
-    }
-  }
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+        if (inside(a, b, r)) N[at(a, b, r)] = old[a][b][r] - acc[a][b][r];
+}
+
+// groups of one row: the float64 diagonal of the rows outside the pivots (theirs is written by pair_fix_kernel)
+__global__ __launch_bounds__(256) void pair_dblk_q1_kernel(TabDims d, const float* __restrict__ P1, const float* __restrict__ P2,
+                                                            const float* __restrict__ P1D, const float* __restrict__ P2D,
+                                                            const SearchCtrl* __restrict__ ctrl, double* __restrict__ dblk,
+                                                            const int32_t* __restrict__ single) {
+  if (ctrl->done) return;
+  const int h = blockIdx.x * 256 + threadIdx.x, g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in;
+  if (h < d.p && h != g && h != j) dblk[h] -= (double)P1D[h] * (double)P1[h] + (double)P2D[h] * (double)P2[h];
 }
 
 // q = 1 fast path of the bulk update: N[i][l] -= a1[i]*b1[l] + a2[i]*b2[l] on the lower triangle.
@@ -1620,15 +1858,15 @@ __global__ __launch_bounds__(256) void update_N_q1_kernel(int n, float* __restri
   }
 }
 
-// Z rows of one group: Z[i][:] -= sum_c P1[i][c] rZ1[c][:] + P2[i][c] rZ2[c][:], then gram[h] = Z_h Z_h^T.
+// groups of one row: Z[i][:] -= P1[i] rZ1[:] + P2[i] rZ2[:], then gram[i] = |Z_i|^2
 __global__ __launch_bounds__(256) void update_Z_kernel(TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
                                                         const float* __restrict__ P2, const float* __restrict__ rZ1,
                                                         const float* __restrict__ rZ2, double* __restrict__ gram,
                                                         const SearchCtrl* __restrict__ ctrl) {
   if (ctrl->done) return;
-  const int h = blockIdx.x, q = d.q, m = d.m;
-  float* Zh = Z + (int64_t)h * q * m;
-  if (q == 1) {
+  const int h = blockIdx.x, m = d.m;
+  float* Zh = Z + (int64_t)h * m;
+  {
     const float a1 = P1[h], a2 = P2[h];
     double v = 0;
     if ((m & 3) == 0) {                        // rows are 16-byte aligned: four columns per load
@@ -1654,18 +1892,7 @@ __global__ __launch_bounds__(256) void update_Z_kernel(TabDims d, float* __restr
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     if (threadIdx.x == 0) gram[h] = red[0] + red[1] + red[2] + red[3];
-    return;
   }
-  for (int64_t idx = threadIdx.x; idx < (int64_t)q * m; idx += 256) {
-    int r = (int)(idx / m), col = (int)(idx % m);
-    const float* p1 = P1 + (int64_t)(h * q + r) * q;
-    const float* p2 = P2 + (int64_t)(h * q + r) * q;
-    float acc = 0.f;
-    for (int c = 0; c < q; c++) acc += p1[c] * rZ1[(int64_t)c * m + col] + p2[c] * rZ2[(int64_t)c * m + col];
-    Zh[idx] -= acc;
-  }
-  __syncthreads();
-  group_gram(Zh, q, m, gram + (int64_t)h * q * q);
 }
 
 // The `take` kept groups with the smallest removal cost (ascending cost, lowest index on ties) -> pick[0..take), and
@@ -1779,21 +2006,6 @@ hipError_t launch_greedy_pick(const TabDims& d, const TabPtrs& t, int take, int3
   return hipGetLastError();
 }
 
-// Z[i][:] -= sum_c P1[i][c] rZ1[c][:] + P2[i][c] rZ2[c][:] for groups of more than one row: one row x 256 columns per
-// workgroup (the row's 2q coefficients are uniform loads); the group Grams follow in group_gram_kernel.
-__global__ __launch_bounds__(256) void update_Z_rows_kernel(TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
-                                                             const float* __restrict__ P2, const float* __restrict__ rZ1,
-                                                             const float* __restrict__ rZ2, const SearchCtrl* __restrict__ ctrl) {
-  if (ctrl->done) return;
-  const int q = d.q, m = d.m, i = blockIdx.x, col = blockIdx.y * 256 + threadIdx.x;
-  if (col >= m) return;
-  const float* p1 = P1 + (int64_t)i * q;
-  const float* p2 = P2 + (int64_t)i * q;
-  float acc = 0.f;
-  for (int c = 0; c < q; c++) acc += p1[c] * rZ1[(int64_t)c * m + col] + p2[c] * rZ2[(int64_t)c * m + col];
-  Z[(int64_t)i * m + col] -= acc;
-}
-
 hipError_t launch_select(const TabDims& d, const TabPtrs& t, int forced_out, int forced_in, hipStream_t s) {
   hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, t.ctrl, forced_out, forced_in);
   return hipGetLastError();
@@ -1802,14 +2014,9 @@ hipError_t launch_select(const TabDims& d, const TabPtrs& t, int forced_out, int
 hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int forced_out, int forced_in, int always_accept,
                                    hipStream_t s, hipEvent_t* ev, const int32_t* single, int exact_in) {
   const int q = d.q;
-  const int rb = (d.d1 + 255) / 256;
-  const size_t pc_lds = (size_t)(3 * q * q + 2 * q * PC_COLS) * 8;
-  if (pc_lds > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pair_cols_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pc_lds);
-    if (e != hipSuccess) return e;
-  }
+  const dim3 ex_grid((d.d1 + 63) / 64, 4);
   if (!single) hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, t.ctrl, forced_out, forced_in);
-  hipLaunchKernelGGL(extract_pair_kernel, dim3(rb), dim3(256), 0, s, d, t.N, t.Z, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2, single);
+  hipLaunchKernelGGL(extract_pair_kernel, ex_grid, dim3(256), 0, s, d, t.N, t.Z, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2, single);
   if (exact_in && !single && forced_out < 0) {
     // the leaving group stands; choose the entering one by the exact gain of the pair and extract its panel again
     hipLaunchKernelGGL(exact_cross_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d, t.Z, t.rZ1, t.ctrl, t.cross);
@@ -1827,16 +2034,18 @@ hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int force
       launch_score(d, t.kept, t.xgram, t.xdblk, t.xscore, t.ctrl, 1, s);
     }
     hipLaunchKernelGGL(select_in_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.xscore, t.ctrl);
-    hipLaunchKernelGGL(extract_pair_kernel, dim3(rb), dim3(256), 0, s, d, t.N, t.Z, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2, single);
+    hipLaunchKernelGGL(extract_pair_kernel, ex_grid, dim3(256), 0, s, d, t.N, t.Z, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2, single);
   }
-  const size_t ps_lds = (size_t)(3 * q * q + 256) * 8;
-  if (ps_lds > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pair_small_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ps_lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(pair_small_kernel, dim3(1), dim3(256), ps_lds, s, d, t.C1, t.C2, t.small, t.ctrl, single);
+  const size_t ps_lds = (size_t)3 * q * (q + 1) * 8;
   const int ncb = (d.m + PC_COLS - 1) / PC_COLS;
-  hipLaunchKernelGGL(pair_cols_kernel, dim3(ncb), dim3(256), pc_lds, s, d, t.rZ1, t.rZ2, t.small, t.ctrl, t.dpart);
+  OSSCAR_BY_TILES(q, {
+    if (ps_lds > 32768) {      // beside the inverse's 35 KB
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pair_small_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ps_lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(pair_small_kernel<RT>, dim3(1), dim3(256), ps_lds, s, d, t.C1, t.C2, t.small, t.ctrl, single);
+    hipLaunchKernelGGL(pair_cols_kernel<RT>, dim3(ncb), dim3(256), 0, s, d, t.rZ1, t.rZ2, t.small, t.ctrl, t.dpart, single);
+  })
   hipLaunchKernelGGL(pair_accept_kernel, dim3(1), dim3(64), 0, s, t.ctrl, always_accept, t.trace_out, t.trace_in, t.trace_gap,
                      t.trace_obj, single, t.dpart, ncb);
   // bulk panels go to C1D/C2D (times D) and to two further panels stored behind them
@@ -1844,29 +2053,37 @@ hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int force
   float* P2 = P1 + (int64_t)d.d1 * q;
   float* P1D = t.C1D;
   float* P2D = t.C2D;
-  hipLaunchKernelGGL(pair_panels_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d, t.C1, t.C2, t.small, t.ctrl, P1, P2, P1D, P2D,
-                     single);
-  hipLaunchKernelGGL(pair_fix_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d, t.N, t.Z, P1, P2, P1D, P2D, t.rZ1, t.rZ2, t.small,
-                     t.ctrl, t.dblk, t.kept, single);
-  hipLaunchKernelGGL(pair_dblk_kernel, dim3(d.p), dim3(256), (size_t)(4 * q * q + 2 * q) * 4, s, d, P1, P2, P1D, P2D, t.ctrl, t.dblk, single);
+  const int rows16 = (d.d1 + 15) / 16;
+  OSSCAR_BY_TILES(q, {
+    hipLaunchKernelGGL(pair_panels_kernel<RT>, dim3(rows16), dim3(256), 0, s, d, t.C1, t.C2, t.small, t.ctrl, P1, P2, P1D, P2D, single);
+    hipLaunchKernelGGL(pair_fix_kernel<RT>, dim3(rows16 + (d.m + 63) / 64), dim3(256), 0, s, d, t.N, t.Z, P1D, P2D, t.rZ1, t.rZ2, t.small, t.ctrl,
+                       t.dblk, t.kept, single, rows16);
+  })
   if (ev) hipEventRecord(ev[0], s);
   if (q == 1) {
+    hipLaunchKernelGGL(pair_dblk_q1_kernel, dim3((d.p + 255) / 256), dim3(256), 0, s, d, P1, P2, P1D, P2D, t.ctrl, t.dblk, single);
     dim3 grid((d.d1 + 1023) / 1024, (d.d1 + 31) / 32);
     hipLaunchKernelGGL(update_N_q1_kernel, grid, dim3(256), 0, s, d.d1, t.N, P1, P2, P1D, P2D, t.ctrl);
   } else {
-    int tiles = (d.d1 + 63) / 64;
-    hipLaunchKernelGGL(update_N_kernel, dim3(tiles, tiles), dim3(256), 0, s, d, t.N, P1, P2, P1D, P2D, t.ctrl);
+    const int64_t tiles = (d.d1 + 63) / 64;
+    const size_t lds = (size_t)2 * 64 * (2 * gu_kq(q) + 4) * 4;
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(update_N_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(update_N_kernel, dim3((unsigned)(tiles * (tiles + 1) / 2)), dim3(256), lds, s, d, t.N, P1, P2, P1D, P2D, t.ctrl, single != nullptr);
   }
   if (ev) hipEventRecord(ev[1], s);
+  ScoreUpdate u;
   if (q == 1) {
     hipLaunchKernelGGL(update_Z_kernel, dim3(d.p), dim3(256), 0, s, d, t.Z, P1, P2, t.rZ1, t.rZ2, t.gram, t.ctrl);
   } else {
-    const int nb = (q + 15) / 16;
-    hipLaunchKernelGGL(update_Z_rows_kernel, dim3(d.d1, (d.m + 255) / 256), dim3(256), 0, s, d, t.Z, P1, P2, t.rZ1, t.rZ2, t.ctrl);
-    hipLaunchKernelGGL(group_gram_kernel, dim3(d.p, nb * (nb + 1) / 2), dim3(256), 0, s, d, t.Z, t.gram, t.ctrl);
+    const hipError_t e = launch_group_update(d, t, P1, P2, single != nullptr, t.ctrl, s);
+    if (e != hipSuccess) return e;
+    u = ScoreUpdate{t.part, P1, P2, P1D, P2D, single};
   }
   if (ev) hipEventRecord(ev[2], s);
-  launch_score(d, t.kept, t.gram, t.dblk, t.score, t.ctrl, 1, s);
+  launch_score(d, t.kept, t.gram, t.dblk, t.score, t.ctrl, 1, s, u);
   return hipGetLastError();
 }
 

@@ -125,3 +125,60 @@ def test_packed_gram_in_ranges_and_in_wide_tiles(d1, m, chunks):
     dx, dy = np.sqrt(np.diag(Hr)), np.sqrt((Y.double() ** 2).sum(0).cpu().numpy())
     assert np.array_equal(H, H.T) and np.max(np.abs(H - Hr) / np.outer(dx, dx)) <= 3.8e-6
     assert np.max(np.abs(G - Gr) / np.outer(dx, dy)) <= 3.8e-6
+
+
+@pytest.mark.parametrize("q,p,m", [(2, 40, 3), (9, 15, 64), (15, 6, 130), (16, 7, 128), (17, 5, 33), (33, 5, 257), (48, 4, 1), (63, 4, 40),
+                                   (64, 6, 300)])
+def test_swaps_of_groups_of_every_tile_count(q, p, m):
+    """Groups of 1 - 4 tiles of 16 rows, full and ragged, after three swaps (the middle one towards a higher index, the others
+    towards a lower one) and, from the dense layer, after single removals: the state and every score against float64 inverses
+    of the kept set.  The state is float32 and every swap rounds it again: a few times 2^-24 = 6e-8 times the condition number
+    (below 20) per swap, 1e-5 in all; scores are squares of it."""
+    pkg = _pkg()
+    d1, k = p * q, p // 2 + 1
+    g = torch.Generator().manual_seed(q * 100 + p)
+    A = torch.randn(2 * d1, d1, generator=g, dtype=torch.float64)
+    H = (A.T @ A / (2 * d1) + 0.2 * torch.eye(d1, dtype=torch.float64)).float()
+    H = torch.tril(H) + torch.tril(H, -1).T
+    W = torch.randn(d1, m, generator=g, dtype=torch.float64)
+    G = (H.double() @ W).float()
+    Hd, Gd = H.double().numpy(), G.double().numpy()
+
+    def check(s, kept):
+        rows = lambda gs: np.concatenate([np.arange(x * q, x * q + q) for x in sorted(gs)])
+        out = [x for x in range(p) if x not in kept]
+        K, C = rows(kept), rows(out)
+        P = np.linalg.inv(Hd[np.ix_(K, K)])
+        B = P @ Gd[K]
+        V = P @ Hd[np.ix_(K, C)]
+        R = Gd[C] - V.T @ Gd[K]
+        S = Hd[np.ix_(C, C)] - Hd[np.ix_(C, K)] @ V
+        T = lambda i: s.osscar_get_tensor(i).cpu().double().numpy()
+        assert T(8).astype(int).tolist() == sorted(kept)
+        for got, ref in ((T(2), P), (T(3), B), (T(4), V), (T(5), R)):
+            assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+        rem, add = T(6), T(7)
+        for n, x in enumerate(sorted(kept)):
+            b, pb = B[n * q:n * q + q], P[n * q:n * q + q, n * q:n * q + q]
+            assert abs(rem[x] - np.sum(b * np.linalg.solve(pb, b))) <= 2e-5 * rem[x]
+        for n, x in enumerate(out):
+            r, sb = R[n * q:n * q + q], S[n * q:n * q + q, n * q:n * q + q]
+            assert abs(add[x] - np.sum(r * np.linalg.solve(sb, r))) <= 2e-5 * add[x]
+
+    kept = set(range(0, 2 * k, 2)) if 2 * k <= p else set(range(k))
+    s = pkg.Solver(d1, m, p, q, k, 4, torch.float32, torch.float32, DEV)
+    s.osscar_set_quadratic(H.to(DEV), G.to(DEV), float(np.sum(W.numpy() * Gd)), np.ones(p))
+    s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, sorted(kept))
+    check(s, kept)
+    for go, gi in ((max(kept), min(set(range(p)) - kept)), (None, None), (None, None)):
+        if go is None:
+            go, gi = min(kept), max(set(range(p)) - kept)
+        s.osscar_apply_swap(go, gi)
+        kept = kept - {go} | {gi}
+        check(s, kept)
+    s.close()
+    s = pkg.Solver(d1, m, p, q, k, 4, torch.float32, torch.float32, DEV, from_dense=True)
+    s.osscar_set_quadratic(H.to(DEV), G.to(DEV), float(np.sum(W.numpy() * Gd)), np.ones(p))
+    s.osscar_init_greedy(2)
+    check(s, set(s.osscar_get_tensor(8).cpu().tolist()))
+    s.close()
