@@ -455,7 +455,7 @@ int gram_tile_schedule(int tiles_per_side, int32_t* out, int capacity) {
 // How many copies of a float64 result of this many elements and 128 x 128 tiles are kept, so that ranges of the contraction
 // can run side by side, each into its own copy: enough for 512 workgroups (two per compute unit), in at most 320 MB.
 int packed_copies(int64_t elems, int64_t ntiles) {
-  return (int)std::max<int64_t>(1, std::min({(int64_t)32, 512 / std::max<int64_t>(ntiles, 1), ((int64_t)320 << 20) / (8 * elems)}));
+  return (int)std::max<int64_t>(1, std::min({(int64_t)16, 512 / std::max<int64_t>(ntiles, 1), ((int64_t)320 << 20) / (8 * elems)}));
 }
 
 void gram_tile_list_host(int d1, std::vector<int2>& out) { build_tile_list((d1 + 127) / 128, out); }

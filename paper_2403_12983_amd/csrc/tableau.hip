@@ -110,9 +110,14 @@ __device__ __forceinline__ void inv16_steps(swd4& x, int lane, int n, bool& flag
     const double mine = x[K >> 2];
     const double row = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(mine)),
                                         __builtin_amdgcn_ds_bpermute(from, __double2loint(mine)));
-    double piv = row16_bcast<K>(row);
+    // the pivot goes by v_readlane, ahead of the row; its reciprocal by v_rcp_f64 and two Newton steps (2^-24 -> 2^-48 -> 1 ulp)
+    double piv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), ((K & 3) << 4) | K),
+                                  __builtin_amdgcn_readlane(__double2loint(mine), ((K & 3) << 4) | K));
     if (!(piv > 0.0)) { flag = true; piv = 1.0; }
-    const double d = 1.0 / piv, rs = row * d;
+    double d = __builtin_amdgcn_rcp(piv);
+    d = fma(d, fma(-piv, d, 1.0), d);
+    d = fma(d, fma(-piv, d, 1.0), d);
+    const double rs = row * d;
     const bool pcol = (lane & 15) == K, prow = (lane >> 4) == (K & 3);
 #pragma unroll
     for (int r = 0; r < 4; r++) {
@@ -984,10 +989,25 @@ __global__ __launch_bounds__(256) void gram_dblk_q1_kernel(int d1, int m, const 
 // passes of memory about equally; as a row x 256 columns of scalar products and a second pass for the Grams a swap of two
 // groups of 64 rows, 4096 columns took 0.42 + 0.20 ms.
 constexpr int GU_LD = 36;
+// ROWS rows of a panel (q floats each, contiguous) into S[r * ks + k0 + c], c < kq, zeros past q and past the first `rows` rows;
+// by 256 threads, 256 / ROWS of them to a row, four floats at a time where the rows allow it
+template <int ROWS>
+__device__ __forceinline__ void stage_panel(float* S, int ks, int k0, int kq, const float* __restrict__ P, int q, int rows) {
+  constexpr int TPR = 256 / ROWS;
+  const int r = threadIdx.x / TPR, l = threadIdx.x % TPR;
+  if (r >= ROWS) return;
+  float* dst = S + r * ks + k0;
+  const float* src = P + (int64_t)r * q;
+  if ((q & 3) == 0 && (reinterpret_cast<uintptr_t>(P) & 15) == 0) {
+    for (int c = 4 * l; c < kq; c += 4 * TPR) *reinterpret_cast<float4*>(dst + c) = r < rows ? *reinterpret_cast<const float4*>(src + c) : float4{0.f, 0.f, 0.f, 0.f};
+  } else {
+    for (int c = l; c < kq; c += TPR) dst[c] = (r < rows && c < q) ? src[c] : 0.f;
+  }
+}
 template <int RT> struct GroupUpdLds { float zt[4][16 * RT][GU_LD]; };
 static __host__ __device__ inline int gu_kq(int q) { return (q + 3) / 4 * 4; }
 template <int RT>
-__global__ __launch_bounds__(256) void group_update_kernel(TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
+__global__ __launch_bounds__(256, 2) void group_update_kernel(TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
                                                             const float* __restrict__ P2, const float* __restrict__ rZ1,
                                                             const float* __restrict__ rZ2, int single, double* __restrict__ part,
                                                             int chunk_cols, const SearchCtrl* __restrict__ ctrl) {
@@ -999,9 +1019,9 @@ __global__ __launch_bounds__(256) void group_update_kernel(TabDims d, float* __r
   const int q = d.q, m = d.m, h = blockIdx.x, kq = gu_kq(q), K = P1 ? (single ? kq : 2 * kq) : 0, ks = 2 * kq + 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   float* Zh = Z + (int64_t)h * q * m;
-  for (int idx = tid; idx < 16 * RT * K; idx += 256) {
-    const int r = idx / K, kk = idx % K, half = kk >= kq, c = kk - half * kq;
-    Ps[r * ks + kk] = (r < q && c < q) ? (half ? P2 : P1)[((int64_t)h * q + r) * q + c] : 0.f;
+  if (K) {
+    stage_panel<16 * RT>(Ps, ks, 0, kq, P1 + (int64_t)h * q * q, q, q);
+    if (!single) stage_panel<16 * RT>(Ps, ks, kq, kq, P2 + (int64_t)h * q * q, q, q);
   }
   __syncthreads();
   swd4 g[NT];
@@ -1023,7 +1043,7 @@ __global__ __launch_bounds__(256) void group_update_kernel(TabDims d, float* __r
           z[t][j][r] = (row < q && col < m) ? Zh[(int64_t)row * m + col] : 0.f;
         }
       }
-#pragma unroll 8
+#pragma unroll 4
     for (int kk = 0; kk < K; kk += 4) {
       const int half = kk >= kq, c = kk + lr - half * kq;
       const float* rz = half ? rZ2 : rZ1;
@@ -1782,10 +1802,9 @@ __global__ __launch_bounds__(256) void update_N_kernel(TabDims d, float* __restr
     for (int b = 0; b < 2; b++)
 #pragma unroll
       for (int r = 0; r < 4; r++) old[a][b][r] = inside(a, b, r) ? N[at(a, b, r)] : 0.f;
-  for (int idx = tid; idx < 64 * K; idx += 256) {
-    const int r = idx / K, kk = idx % K, half = kk >= kq, c = kk - half * kq;
-    As[r * ks + kk] = (c < q && i0 + r < n) ? (half ? P2D : P1D)[(int64_t)(i0 + r) * q + c] : 0.f;
-    Bs[r * ks + kk] = (c < q && l0 + r < n) ? (half ? P2 : P1)[(int64_t)(l0 + r) * q + c] : 0.f;
+  for (int half = 0; half < (single ? 1 : 2); half++) {
+    stage_panel<64>(As, ks, half * kq, kq, (half ? P2D : P1D) + (int64_t)i0 * q, q, n - i0);
+    stage_panel<64>(Bs, ks, half * kq, kq, (half ? P2 : P1) + (int64_t)l0 * q, q, n - l0);
   }
   __syncthreads();
   f4v acc[2][2];
@@ -1942,15 +1961,37 @@ __global__ __launch_bounds__(1024) void greedy_pick_kernel(TabDims d, const int3
 
 // The same selection for p <= 1024 * KMAX groups with the eligible scores held in registers: every round is a local scan, a
 // shuffle reduction per wave and one more over the 16 wave records, instead of another pass over memory.
+// (value, index) of the smallest value, lowest index on ties (index -1: none), over the lanes of a row of 16, in all of them
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ void best_step(double& v, int& i) {
+  const int oi = __builtin_amdgcn_update_dpp(-1, i, CTRL, ROW_MASK, 0xF, false);
+  const double ov = __hiloint2double(__builtin_amdgcn_update_dpp(0x7FF00000, __double2hiint(v), CTRL, ROW_MASK, 0xF, false),
+                                     __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false));
+  if (oi >= 0 && (i < 0 || ov < v || (ov == v && oi < i))) { v = ov; i = oi; }
+}
+__device__ __forceinline__ void best_of_16(double& v, int& i) {
+  best_step<0xb1, 0xf>(v, i);      // quads: xor 1, xor 2
+  best_step<0x4e, 0xf>(v, i);
+  best_step<0x124, 0xf>(v, i);     // rows: rotate by 4, by 8
+  best_step<0x128, 0xf>(v, i);
+}
+// ... over the wave, in lane 63
+__device__ __forceinline__ void best_of_wave(double& v, int& i) {
+  best_of_16(v, i);
+  best_step<0x142, 0xa>(v, i);     // row 0 -> 1, 2 -> 3
+  best_step<0x143, 0xc>(v, i);     // rows 0, 1 -> 2, 3
+}
+// The same from registers (p <= 1024 KMAX).  A thread keeps the best of its own candidates, a wave the best of its threads
+// (lane 63, by data-parallel moves) in LDS; a round merges the 16 waves' records in every wave and only the wave that lost its
+// best looks for the next one.  One workgroup, bound by the chain of rounds: 10 of 8192 candidates in 9 us, 32 us with every
+// candidate scanned and shuffled in every round.
 template <int KMAX>
 __global__ __launch_bounds__(1024) void greedy_pick_reg_kernel(TabDims d, const int32_t* __restrict__ kept,
                                                                 const double* __restrict__ score, int take,
                                                                 int32_t* __restrict__ pick, float* __restrict__ gap,
                                                                 const SearchCtrl* __restrict__ ctrl, int side) {
-  __shared__ double w_v[16];
-  __shared__ int w_i[16];
-  __shared__ int chosen[65];
-  __shared__ double chosen_v[65];
+  __shared__ double w_v[2][16];
+  __shared__ int w_i[2][16];
   if (ctrl->done || ctrl->pause) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double v[KMAX];
@@ -1960,46 +2001,40 @@ __global__ __launch_bounds__(1024) void greedy_pick_reg_kernel(TabDims d, const 
     v[k] = INFINITY;
     if (h < d.p && ((kept[h] != 0) == (side == 0))) v[k] = side ? -score[h] : score[h];
   }
+  double best = INFINITY, prev = 0.0, edge = 0.0;
+  int ib = -1, c = -1;
   for (int round = 0; round <= take; round++) {
-    double best = INFINITY;
-    int ib = -1;
+    if (round == 0 || (c >= 0 && ((c & 1023) >> 6) == wave)) {      // uniform over the wave
+      if (round == 0 || (c & 1023) == tid) {
+        best = INFINITY; ib = -1;
 #pragma unroll
-    for (int k = 0; k < KMAX; k++)
-      if (v[k] < best) { best = v[k]; ib = tid + 1024 * k; }      // ascending index per thread: strict comparison keeps the lowest
-    for (int o = 32; o > 0; o >>= 1) {
-      const double b1 = __shfl_down(best, o, 64);
-      const int i2 = __shfl_down(ib, o, 64);
-      if (i2 >= 0 && (ib < 0 || b1 < best || (b1 == best && i2 < ib))) { best = b1; ib = i2; }
-    }
-    if (lane == 0) { w_v[wave] = best; w_i[wave] = ib; }
-    __syncthreads();
-    if (wave == 0) {
-      best = lane < 16 ? w_v[lane] : INFINITY;
-      ib = lane < 16 ? w_i[lane] : -1;
-      for (int o = 8; o > 0; o >>= 1) {
-        const double b1 = __shfl_down(best, o, 64);
-        const int i2 = __shfl_down(ib, o, 64);
-        if (i2 >= 0 && (ib < 0 || b1 < best || (b1 == best && i2 < ib))) { best = b1; ib = i2; }
+        for (int k = 0; k < KMAX; k++) {
+          if (round && k == (c >> 10)) v[k] = INFINITY;
+          if (v[k] < best) { best = v[k]; ib = tid + 1024 * k; }      // ascending index per thread: strict comparison keeps the lowest
+        }
       }
-      if (lane == 0) { chosen[round] = ib; chosen_v[round] = best; }
+      double wb = best;
+      int wi = ib;
+      best_of_wave(wb, wi);
+      if (lane == 63) { w_v[round & 1][wave] = wb; w_i[round & 1][wave] = wi; }
+    } else if (lane == 63) {
+      w_v[round & 1][wave] = w_v[(round & 1) ^ 1][wave]; w_i[round & 1][wave] = w_i[(round & 1) ^ 1][wave];
     }
     __syncthreads();
-    const int c = chosen[round];
-    if (c >= 0 && (c & 1023) == tid) {
-#pragma unroll
-      for (int k = 0; k < KMAX; k++) if (k == (c >> 10)) v[k] = INFINITY;
-    }
+    double rb = w_v[round & 1][lane & 15];
+    c = w_i[round & 1][lane & 15];
+    best_of_16(rb, c);                                              // the same in every row of lanes of every wave
+    prev = edge; edge = rb;
+    if (tid == 0 && round < take) pick[round] = c;
   }
-  if (tid < take) pick[tid] = chosen[tid];
-  if (tid == 0) {
-    const double edge = chosen_v[take - 1];
-    *gap = (chosen[take] >= 0) ? (float)(fabs(chosen_v[take] - edge) / fmax(fabs(edge), 1e-300)) : INFINITY;
-  }
+  if (tid == 0) *gap = (c >= 0) ? (float)(fabs(edge - prev) / fmax(fabs(prev), 1e-300)) : INFINITY;
 }
 
 hipError_t launch_greedy_pick(const TabDims& d, const TabPtrs& t, int take, int32_t* pick, float* gap, hipStream_t s, int side) {
   if (take < 1 || take > 64) return hipErrorInvalidValue;
-  if (d.p <= 1024 * 32)
+  if (d.p <= 1024 * 8)
+    hipLaunchKernelGGL(greedy_pick_reg_kernel<8>, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
+  else if (d.p <= 1024 * 32)
     hipLaunchKernelGGL(greedy_pick_reg_kernel<32>, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
   else
     hipLaunchKernelGGL(greedy_pick_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
