@@ -756,14 +756,35 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
         c->ev_g_rows = n_c;
       }
     } else {
-      // any alignment and float32: float64 sums straight from the caller's rows; patches are written out as rows first, as
-      // many at a time as the staging buffer holds
+      // any alignment and float32.  From 256 tiles of 128 x 128 and 1024 rows on: digits on the int8 matrix cores, as many rows at a
+      // time as the staging buffer packs (5461 columns, 32769 rows of bf16: 19.0 ms on the float64 matrix cores, 5.5 ms so).
+      // Smaller layers: float64 sums straight from the caller's rows.  Patches are written out as rows first.
       const size_t esz = bf16 ? 2 : 4;
-      const int64_t most = conv ? (int64_t)(gram_stage_bytes(d1) / ((size_t)d1 * 4)) : GEN_ROWS;
+      const int64_t t128 = (d1 + 127) / 128;
+      int64_t most = conv ? (int64_t)(gram_stage_bytes(d1) / ((size_t)d1 * 4)) : GEN_ROWS;
+      bool digits = g_i8_products && t128 * (t128 + 1) / 2 >= 256 && n_c >= I8_MIN_DIM && (size_t)(d1 + m) * 4 <= c->gemm_ws_size;
+      char* pack_x = reinterpret_cast<char*>(Xt);
+      if (digits) {
+        const int x16 = bf16 && !conv;
+        if (conv) {      // the rows in front, their digits behind them
+          most = (int64_t)(gram_stage_bytes(d1) / ((size_t)t128 * 128 * (4 + I8_S))) / 32 * 32;
+          pack_x += align_up((size_t)most * d1 * 4);
+          most = std::min<int64_t>(most, i8_gram_rows(gram_stage_bytes(d1) - (size_t)(pack_x - reinterpret_cast<char*>(Xt)), x16, d1));
+        } else {
+          most = i8_gram_rows(gram_stage_bytes(d1), x16, d1);
+        }
+        if (target) most = std::min<int64_t>(most, i8_gram_rows(target_stage_bytes(m), x16, m));
+      }
       for (int64_t r0 = 0; r0 < n_c; r0 += most) {
         const int64_t nr = std::min<int64_t>(most, n_c - r0);
         if (conv) HIPCHK(c, launch_im2col_rows(Xc, bf16, *conv, r0, nr, d1, reinterpret_cast<float*>(Xt), s));
         const void* src = conv ? Xt : reinterpret_cast<const char*>(Xc) + (size_t)r0 * ldx * esz;
+        if (digits) {
+          const void* ysrc = target ? reinterpret_cast<const char*>(Yc) + (size_t)r0 * ldy * esz : nullptr;
+          HIPCHK(c, launch_i8_gram(src, bf16 && !conv, conv ? d1 : ldx, d1, ysrc, ldy, m, (int)nr, H64, G64, pack_x, Ys,
+                                   reinterpret_cast<unsigned*>(c->gemm_ws), s));
+          continue;
+        }
         Gemm64 g{};      // H64 += Xc^T Xc
         g.M = d1; g.N = d1; g.K = (int)nr; g.lower = 1; g.A = g.B = src; g.lda = g.ldb = conv ? d1 : ldx;
         g.a_kind = g.b_kind = (bf16 && !conv) ? OPK_K_BF16 : OPK_K_F32;

@@ -30,20 +30,20 @@
 // (0.49 of the int8 peak); 42.0 ms while the compiler's own waits emptied the request queue every stage.  (4 waves of 64 x 64, one
 // per SIMD, took 51 ms where 8 took 41: nothing to run while a wave waits.)
 #include "internal.h"
+#include <algorithm>
 
 namespace osscar {
 namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr int S = I8_S;
-constexpr int BLK = S * 256;                       // packets of one (stage, panel) block
 
 __device__ __forceinline__ int expo_of(unsigned bits) {      // smallest e with v < 2^e (0 for v = 0)
   const float v = __uint_as_float(bits);
-  if (!(v > 0.f)) return 0;
+  if (!(v > 0.f) || bits >= 0x7F800000u) return 0;
   int e;
   frexpf(v, &e);
-  return e;
+  return max(e, -120);      // below, 2^-e would leave float32's range
 }
 
 // mx[r] = bit pattern of max |X[r, :]| (non-negative floats order like their bit patterns)
@@ -74,6 +74,7 @@ __global__ void i8_zero_kernel(unsigned* p, int n) {
 }
 
 // 16 scaled values -> S packets of 16 digits each (every step is exact in float32)
+template <int S>
 __device__ __forceinline__ void slice16(const float* v, uint4* out) {
   unsigned w[S][4];
 #pragma unroll
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(256) void i8_pack_rows_kernel(const float* __restri
     }
   }
   uint4 pk[S];
-  slice16(v, pk);
+  slice16<S>(v, pk);
   const int stage = kp >> 1, kh = kp & 1, panel = row >> 7, r = row & 127;
 #pragma unroll
   for (int t = 0; t < S; t++) out[(((int64_t)panel * nstages + stage) * S + t) * 256 + kh * 128 + r] = pk[t];
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(256) void i8_pack_cols_kernel(const float* __restri
         v[j] = ldexpf(X[(int64_t)(kp * 16 + j) * ld + col], kexp ? ks * kexp[kp * 16 + j] : 0) * sc;
   }
   uint4 pk[S];
-  slice16(v, pk);
+  slice16<S>(v, pk);
   const int stage = kp >> 1, kh = kp & 1, panel = col >> 7, r = col & 127;
 #pragma unroll
   for (int t = 0; t < S; t++) out[(((int64_t)panel * nstages + stage) * S + t) * 256 + kh * 128 + r] = pk[t];
@@ -183,6 +184,7 @@ struct I8Args {
   int M, N, tiles_m, tiles_n, lower_only;
   double alpha, beta, diag_add;
   const float* A; int64_t lda; const float* B; int64_t ldb; int diag_a, diag_b;      // the operands themselves, for the diagonal terms
+  double* C64;      // set: C64[row][col] += A B (leading dimension ldc, lower_only: on and below the diagonal) instead of C
 };
 
 // vmcnt <= N; lgkmcnt = 0, then the barrier: builtins, which the compiler takes into account where it places waits of its own
@@ -195,7 +197,11 @@ __device__ __forceinline__ void lds_only_barrier() {
   asm volatile("" ::: "memory");
 }
 
+template <int S>      // digits per operand (4 or 5)
 __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
+  constexpr int BLK = S * 256;                   // packets of one (stage, panel) block
+  constexpr int NG = 5;                          // digit weights t + u < NG that are summed, one accumulator set each
+  constexpr int NL = NG - S + 1;                 // row-side digits that the last column-side digit meets
   // Stage buffers, each the A block followed by the B block.  Three arrays and a steady loop without conditions: with one
   // array, or with conditional requests, the compiler cannot tell which requests a read of LDS depends on and waits for all
   // of them, the one just issued for three stages later included.
@@ -225,9 +231,9 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
   }
   const int nstages = g.nstages;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 2, wn = wave & 3;      // wave tile: 64 rows x 32 columns
-  v16i acc[S][2];
+  v16i acc[NG][2];
 #pragma unroll
-  for (int q = 0; q < S; q++)
+  for (int q = 0; q < NG; q++)
 #pragma unroll
     for (int a = 0; a < 2; a++)
 #pragma unroll
@@ -238,7 +244,7 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
   // [512 i + 64 wave, + 64) (the boundary 1280 is a multiple of 64: a wave's 64 lie in one block); lane l's 16 bytes
   // land at the LDS base + 16 l.
   constexpr int NI = (2 * BLK) / 512;
-  static_assert((2 * BLK) % 512 == 0 && BLK % 64 == 0, "every wave issues the same number of loads per stage");
+  static_assert(BLK % 256 == 0, "every wave issues the same number of loads per stage");
 #define OSSCAR_I8_ISSUE(st_, buf_)                                                                                               \
   {                                                                                                                              \
     _Pragma("unroll") for (int i = 0; i < NI; i++) {                                                                             \
@@ -253,7 +259,8 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
     uint4 q = buf_[t * 256 + oa + a * 32];                                                                                       \
     fa[a][t] = *reinterpret_cast<v4i*>(&q);                                                                                      \
   }
-  // A stage: column-side digits 0 .. S-2 against every row-side digit they meet (28 of its 30 products).  The last
+  // A stage: column-side digits 0 .. S-2 against every row-side digit they meet (28 of its 30 products, 22 of 26 with four
+  // digits).  The last
   // column-side digit goes to a register; then every wave has taken all it needs from this stage's buffer, which the barrier
   // establishes, and NEXT refills the buffer with the stage three ahead and requests the next stage's row-side operands
   // before the last two products.
@@ -263,15 +270,16 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
     _Pragma("unroll") for (int u = 0; u < S - 1; u++) {                                                                          \
       v4i fb;                                                                                                                    \
       { uint4 q = pb[u * 256 + ob]; fb = *reinterpret_cast<v4i*>(&q); }                                                          \
-      _Pragma("unroll") for (int t = 0; t + u < S; t++) _Pragma("unroll") for (int a = 0; a < 2; a++)                            \
+      _Pragma("unroll") for (int t = 0; t < S && t + u < NG; t++) _Pragma("unroll") for (int a = 0; a < 2; a++)                  \
         acc[t + u][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a][t], fb, acc[t + u][a], 0, 0, 0);                             \
     }                                                                                                                            \
     v4i fl;                                                                                                                      \
     { uint4 q = pb[(S - 1) * 256 + ob]; fl = *reinterpret_cast<v4i*>(&q); }                                                      \
-    v4i a0[2];                                                                                                                   \
-    a0[0] = fa[0][0]; a0[1] = fa[1][0];                                                                                          \
+    v4i a0[2][NL];                                                                                                               \
+    _Pragma("unroll") for (int t = 0; t < NL; t++) { a0[0][t] = fa[0][t]; a0[1][t] = fa[1][t]; }                                 \
     NEXT                                                                                                                         \
-    _Pragma("unroll") for (int a = 0; a < 2; a++) acc[S - 1][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0[a], fl, acc[S - 1][a], 0, 0, 0); \
+    _Pragma("unroll") for (int t = 0; t < NL; t++) _Pragma("unroll") for (int a = 0; a < 2; a++)                                 \
+      acc[S - 1 + t][a] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0[a][t], fl, acc[S - 1 + t][a], 0, 0, 0);                       \
   }
 #define OSSCAR_I8_STEADY(st_, cur_, nxt_)                                                                                        \
   OSSCAR_I8_STAGE(cur_, wait_loads<NI>(); lds_only_barrier(); OSSCAR_I8_ISSUE((st_) + 3, cur_); OSSCAR_I8_READ_A(nxt_))
@@ -319,9 +327,18 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
     for (int r = 0; r < 16; r++) {
       const int row = tm * 128 + wm * 64 + a * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
       if (row < g.M && col < g.N) {
+        if (g.C64) {      // the same digits, plain sum; a row or column with an infinity or a NaN gives NaN
+          double v = 0.0;
+#pragma unroll
+          for (int q = NG - 1; q >= 0; q--) v = v * (1.0 / 128.0) + (double)acc[q][a][r];
+          v = ldexp(v, expo_of(g.mxa[row]) + eb - 12);
+          if (g.mxa[row] >= 0x7F800000u || g.mxb[col] >= 0x7F800000u) v = __longlong_as_double(0x7FF8000000000000ll);
+          if (!g.lower_only || col <= row) g.C64[(int64_t)row * g.ldc + col] += v;
+          continue;
+        }
         double v = 0.0;
 #pragma unroll
-        for (int q = S - 1; q >= 0; q--) v = v * (1.0 / 128.0) + (double)acc[q][a][r];
+        for (int q = NG - 1; q >= 0; q--) v = v * (1.0 / 128.0) + (double)acc[q][a][r];
         v = ldexp(v, expo_of(g.mxa[row]) + eb - 12);
         // the diagonal terms that were left out of the digits: k = row of A (A square), k = col of B (B square)
         if (g.diag_a) v += (double)g.A[(int64_t)row * g.lda + row] * (double)g.B[(int64_t)row * g.ldb + col];
@@ -372,9 +389,91 @@ hipError_t launch_i8_gemm(const GemmArgs& g, void* packA, size_t capA, void* pac
   int nsb;
   if (g.lower_only) { const int nr = (npa + 7) / 8; nsb = nr * (nr + 1) / 2; }
   else nsb = ((npa + 7) / 8) * ((npb + 7) / 8);
-  hipLaunchKernelGGL(i8_gemm_kernel, dim3((unsigned)((nsb + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+  hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nsb + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
   gemm_log_close(log_slot, s);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// C64 (M x N float64) += X^T Y (Y == nullptr: X^T X, lower triangle) for rows of float32 or bf16 at any alignment: both operands
+// are packed as B-side operands, digits relative to their column's largest value in this call.  float32: five digits, what is
+// dropped is 2^-35 of the column's maximum per value; bf16: four (13 products), and a value within 2^-18 of the maximum is
+// carried whole.  Products of weight 2^-35 and less are dropped, of unequal digits only, whose signs are independent: on the
+// diagonal a dropped square would add up (with the weights below 2^-28 alone, 5e-6 on a column with one value of 400 sigma).
+// So the sum differs from the float64 one by about 1e-9 of sqrt(H_ii H_jj), far below the float32 that H is rounded to.
+// ------------------------------------------------------------------------------------------------
+namespace {
+__device__ __forceinline__ float load_as_float(const float* p) { return *p; }
+__device__ __forceinline__ float load_as_float(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
+// mx[c] = largest bit pattern of |X[:, c]| over the rows [128 y, 128 y + 128): infinities and NaN stand above every number
+template <typename T>
+__global__ __launch_bounds__(256) void i8_absbits_cols_kernel(const T* __restrict__ X, int K, int N, int64_t ld, unsigned* __restrict__ mx) {
+  const int col = blockIdx.x * 256 + threadIdx.x;
+  if (col >= N) return;
+  const int k0 = blockIdx.y * 128, k1 = min(K, k0 + 128);
+  unsigned v = 0u;
+#pragma unroll 8
+  for (int k = k0; k < k1; k++) v = max(v, __float_as_uint(load_as_float(X + (int64_t)k * ld + col)) & 0x7FFFFFFFu);
+  atomicMax(&mx[col], v);
+}
+template <int S, typename T>
+__global__ __launch_bounds__(256) void i8_pack_rows_of_x_kernel(const T* __restrict__ X, int K, int N, int64_t ld, const unsigned* __restrict__ mx,
+                                                                 uint4* __restrict__ out, int npanels, int nstages) {
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int cpad = npanels * 128;
+  const int kp = (int)(idx / cpad), col = (int)(idx % cpad);
+  if (kp >= nstages * 2) return;
+  float v[16];
+#pragma unroll
+  for (int j = 0; j < 16; j++) v[j] = 0.f;
+  if (col < N && mx[col] < 0x7F800000u) {
+    const int e = expo_of(mx[col]);
+#pragma unroll
+    for (int j = 0; j < 16; j++)
+      if (kp * 16 + j < K) v[j] = ldexpf(load_as_float(X + (int64_t)(kp * 16 + j) * ld + col), -e);
+  }
+  uint4 pk[S];
+  slice16<S>(v, pk);
+  const int stage = kp >> 1, kh = kp & 1, panel = col >> 7, r = col & 127;
+#pragma unroll
+  for (int t = 0; t < S; t++) out[(((int64_t)panel * nstages + stage) * S + t) * 256 + kh * 128 + r] = pk[t];
+}
+template <int S, typename T>
+void pack_columns(const T* X, int K, int N, int64_t ld, unsigned* mx, uint4* out, hipStream_t s) {
+  const int np = (N + 127) / 128, nst = (K + 31) / 32;
+  hipLaunchKernelGGL(i8_zero_kernel, dim3((N + 255) / 256), dim3(256), 0, s, mx, N);
+  hipLaunchKernelGGL(i8_absbits_cols_kernel<T>, dim3((N + 255) / 256, (K + 127) / 128), dim3(256), 0, s, X, K, N, ld, mx);
+  hipLaunchKernelGGL((i8_pack_rows_of_x_kernel<S, T>), dim3((unsigned)(((int64_t)nst * 2 * np * 128 + 255) / 256)), dim3(256), 0, s, X, K, N, ld, mx, out, np, nst);
+}
+template <int S, typename T>
+hipError_t i8_gram(const T* X, int64_t ldx, int d1, const T* Y, int64_t ldy, int m, int K, double* H64, double* G64, void* pack_x, void* pack_y,
+                   unsigned* mx, hipStream_t s) {
+  uint4 *px = reinterpret_cast<uint4*>(pack_x), *py = reinterpret_cast<uint4*>(pack_y);
+  pack_columns<S>(X, K, d1, ldx, mx, px, s);
+  I8Args a{};
+  a.Ap = a.Bp = px; a.nstages = (K + 31) / 32; a.mxa = a.mxb = mx; a.C64 = H64; a.ldc = d1; a.M = a.N = d1;
+  a.tiles_m = a.tiles_n = (d1 + 127) / 128; a.lower_only = 1;
+  const int nr = (a.tiles_m + 7) / 8;
+  hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nr * (nr + 1) / 2 + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+  if (Y) {
+    pack_columns<S>(Y, K, m, ldy, mx + d1, py, s);
+    a.Bp = py; a.mxb = mx + d1; a.C64 = G64; a.ldc = m; a.N = m; a.tiles_n = (m + 127) / 128; a.lower_only = 0;
+    hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nr * ((a.tiles_n + 7) / 8) + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+  }
+  return hipGetLastError();
+}
+}  // namespace
+// rows that a packing buffer of `bytes` bytes takes at a time (a whole number of stages, at most 16384)
+int64_t i8_gram_rows(size_t bytes, int x_bf16, int64_t cols) {
+  const int64_t per_stage = (int64_t)(x_bf16 ? I8_S_BF16 : I8_S) * 256 * 16 * ((cols + 127) / 128);
+  return std::min<int64_t>(16384, (int64_t)bytes / per_stage * 32);
+}
+hipError_t launch_i8_gram(const void* X, int x_bf16, int64_t ldx, int d1, const void* Y, int64_t ldy, int m, int K, double* H64, double* G64,
+                          void* pack_x, void* pack_y, unsigned* mx, hipStream_t s) {
+  if (K <= 0) return hipSuccess;
+  if (K > 16384 || (reinterpret_cast<uintptr_t>(pack_x) & 15) || (Y && (reinterpret_cast<uintptr_t>(pack_y) & 15))) return hipErrorInvalidValue;
+  if (x_bf16) return i8_gram<I8_S_BF16>(reinterpret_cast<const uint16_t*>(X), ldx, d1, reinterpret_cast<const uint16_t*>(Y), ldy, m, K, H64, G64, pack_x, pack_y, mx, s);
+  return i8_gram<I8_S>(reinterpret_cast<const float*>(X), ldx, d1, reinterpret_cast<const float*>(Y), ldy, m, K, H64, G64, pack_x, pack_y, mx, s);
 }
 
 }  // namespace osscar

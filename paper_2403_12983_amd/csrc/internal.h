@@ -62,9 +62,14 @@ hipError_t launch_gemm64(const Gemm64& q, hipStream_t s);
 // i8gemm.hip : the same product C = alpha A B + beta Cin (+ diag_add on the diagonal; lower_only) for float32 A, B, Cin, C
 // with the accuracy of float64 accumulation, computed on the int8 matrix cores from I8_S seven-bit digits per operand
 // ----------------------------------------------------------------------------------------------
-constexpr int I8_S = 5;
+constexpr int I8_S = 5, I8_S_BF16 = 4;
 size_t i8_pack_bytes(int64_t rows, int64_t K);          // packed size of an operand with `rows` rows (A) or columns (B)
 bool i8_gemm_fits(const GemmArgs& g);
+// H64 += X^T X (lower triangle) and, with Y, G64 += X^T Y for K <= 16384 rows of float32 or bf16 at any alignment; pack_x / pack_y
+// hold i8_gram_rows(bytes, ...) >= K rows, mx: d1 + m words
+int64_t i8_gram_rows(size_t bytes, int x_bf16, int64_t cols);
+hipError_t launch_i8_gram(const void* X, int x_bf16, int64_t ldx, int d1, const void* Y, int64_t ldy, int m, int K, double* H64, double* G64,
+                          void* pack_x, void* pack_y, unsigned* mx, hipStream_t s);
 // kexp[k] = round(log2 sqrt(D_kk)) from the diagonal of a Gram block (device, n ints)
 hipError_t launch_i8_kexp(const float* D, int n, int64_t ld, int* kexp, hipStream_t s);
 // packA / packB: scratch for the two packed operands (capacities in bytes), mx: M + N words for the scaling exponents

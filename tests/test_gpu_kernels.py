@@ -182,3 +182,38 @@ def test_swaps_of_groups_of_every_tile_count(q, p, m):
     s.osscar_init_greedy(2)
     check(s, set(s.osscar_get_tensor(8).cpu().tolist()))
     s.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,d1,m,pad", [(1024, 2817, 129, 1), (9001, 2945, 5, 0), (1500, 2943, 2050, 3)])
+def test_gram_in_digits(dtype, n, d1, m, pad):
+    """X^T X and X^T Y of rows that the packed kernels do not take, on the int8 matrix cores (in two pieces for 9001 rows), with
+    columns of very different sizes, rare large values and an empty column.  What the digits drop is 1e-9 of
+    sqrt(H_ii H_jj), so H and G are float32 roundings of the exact sums: 2^-24 + 1e-9."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    scale = torch.exp2(torch.randint(-20, 20, (d1,), generator=g, device=DEV).float())
+    X = torch.randn(n, d1 + pad, generator=g, device=DEV)
+    X[torch.randint(0, n, (50,), generator=g, device=DEV), torch.randint(0, d1, (50,), generator=g, device=DEV)] *= 100
+    X[:, :d1] *= scale
+    X[:, 7] = 0
+    X = X.to(dtype)[:, :d1]
+    Y = torch.randn(n, m, generator=g, device=DEV).to(dtype)
+    W = torch.zeros(d1, m, dtype=dtype, device=DEV)
+    s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, dtype, dtype, DEV, target_output=True)
+    s.osscar_gram_target(X, Y, True, W, 0.0, 0.0)
+    H, G = s.osscar_get_tensor(0), s.osscar_get_tensor(1)
+    Xd, Yd = X.double(), Y.double()
+    Hr, Gr = Xd.T @ Xd, Xd.T @ Yd
+    dx, dy = Hr.diagonal().sqrt().clamp_min(1e-300), Yd.square().sum(0).sqrt()
+    assert torch.equal(H, H.T) and ((H.double() - Hr).abs() / dx[:, None] / dx).max().item() <= 6.1e-8
+    assert ((G.double() - Gr).abs() / dx[:, None] / dy).max().item() <= 6.1e-8
+    # an infinity or a NaN spoils its own row and column and, through the trace in the ridge, the diagonal
+    Xb = X.clone()
+    Xb[3, 11], Xb[n - 1, d1 - 1] = float("nan"), float("inf")
+    s.osscar_gram_target(Xb, Y, True, W, 1.0, 0.0)
+    H2 = s.osscar_get_tensor(0)
+    s.close()
+    bad = torch.zeros(d1, dtype=torch.bool, device=DEV)
+    bad[11] = bad[d1 - 1] = True
+    expect = bad[:, None] | bad[None, :] | torch.eye(d1, dtype=torch.bool, device=DEV)
+    assert torch.equal(~torch.isfinite(H2), expect)
