@@ -66,7 +66,7 @@ __device__ __forceinline__ double wsum(double v) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63), hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
   return __hiloint2double(hi, lo);
 }
-__device__ __forceinline__ bool idle(const SearchCtrl* c) { return c->done || c->pause; }
+__device__ __forceinline__ bool idle(const SearchCtrl* c) { return (c->done | c->pause) != 0; }      // both in one round trip
 // pending pivots including those of the iteration that ran last (for kernels outside an iteration)
 __device__ __forceinline__ int tau_all(const SearchCtrl* c) { return c->tau + c->tau_inc; }
 
@@ -158,92 +158,130 @@ __global__ __launch_bounds__(64) void lazy_partials_kernel(LazyPtrs L, int p, co
 }
 
 // ---------------------------------------------------------------------------------------------- prep
+// (value, index): the smaller value, the lower index on ties, index -1 = none; six data-parallel steps leave the best of the
+// wave in lane 63
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ void dpp_min_step(double& v, int& i) {
+  const double ov = dpp_get_or<CTRL, ROW_MASK>(v, INFINITY);
+  const int oi = dpp_get_or<CTRL, ROW_MASK>(i, -1);
+  const bool t = (oi >= 0) && (i < 0 || ov < v || (ov == v && oi < i));
+  v = t ? ov : v; i = t ? oi : i;
+}
+__device__ __forceinline__ void wave_min(double& v, int& i) {
+  dpp_min_step<0xb1, 0xf>(v, i); dpp_min_step<0x4e, 0xf>(v, i); dpp_min_step<0x124, 0xf>(v, i);
+  dpp_min_step<0x128, 0xf>(v, i); dpp_min_step<0x142, 0xa>(v, i); dpp_min_step<0x143, 0xc>(v, i);
+}
+__device__ __forceinline__ double wave_min(double v) {
+  v = fmin(v, dpp_get_or<0xb1, 0xf>(v, INFINITY)); v = fmin(v, dpp_get_or<0x4e, 0xf>(v, INFINITY));
+  v = fmin(v, dpp_get_or<0x124, 0xf>(v, INFINITY)); v = fmin(v, dpp_get_or<0x128, 0xf>(v, INFINITY));
+  v = fmin(v, dpp_get_or<0x142, 0xa>(v, INFINITY)); v = fmin(v, dpp_get_or<0x143, 0xc>(v, INFINITY));
+  return v;
+}
+// One workgroup, a chain of round trips to memory (about 1.5 us each): the records, then everything that depends on the pick.
+// M^-1 (128 KB) does not, so it is requested first and waits in registers; the leaving and the entering side are picked by
+// four waves each, the second-best values (for the reported gaps) while the pivots' rows are on their way.  9.4 -> 6.9 us at 8192 rows.
 // single != nullptr: removal of the one row *single (Case 1 alone, nothing enters): the second pivot's quantities are zero.
-__global__ __launch_bounds__(256) void lazy_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int nrec,
+constexpr int PREP_T = 512;
+__global__ __launch_bounds__(PREP_T) void lazy_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int nrec,
                                                          const int32_t* __restrict__ kept, SearchCtrl* ctrl, const int32_t* __restrict__ single, int forced_g,
                                                          int forced_j) {
-  __shared__ double s_mn1[4], s_mn2[4], s_mx1[4], s_mx2[4];
-  __shared__ int s_imn[4], s_imx[4];
-  __shared__ double bg[LAZY_TM], bj[LAZY_TM], red[3][4], s_n0[3];
+  __shared__ double s_v[8], s_2nd[8];
+  __shared__ int s_i[8];
+  __shared__ double bg[LAZY_TM], bj[LAZY_TM], red[3][8], s_n0[3];
+  const int tid = threadIdx.x, wave = tid >> 6;
   if (idle(ctrl)) return;
-  const int tid = threadIdx.x;
   const int tau = tau_all(ctrl);           // every thread reads before thread 0 folds the increment in (after the barrier)
-  // argmin of the removal costs / argmax of the addition gains from the per-block records: each thread merges its
-  // records, the waves reduce by data-parallel moves, every thread merges the four wave results (lowest index wins
-  // ties, so the result does not depend on the order)
-  double mn1 = INFINITY, mn2 = INFINITY, mx1 = -INFINITY, mx2 = -INFINITY;
-  int imn = -1, imx = -1;
-  for (int r0 = tid; r0 < nrec; r0 += 1024) {          // four records in flight per thread
-    SelRec c[4];
+  // argmin of the removal costs (waves 0 - 3) / argmax of the addition gains (waves 4 - 7, as the smallest of the negated
+  // gains) from the per-block records (lowest index wins ties, so the result does not depend on the order)
+  const int add = wave >= 4;
+  const double sign = add ? -1.0 : 1.0;
+  double a1[4], a2[4];
+  int ai[4];
+  auto request = [&](int r0) {             // four records in flight per thread; past the end, the first one again (not merged)
 #pragma unroll
-    for (int k = 0; k < 4; k++) { const int r = r0 + 256 * k; c[k] = L.sel[r < nrec ? r : r0]; }
+    for (int k = 0; k < 4; k++) {
+      const SelRec* c = L.sel + (r0 + 256 * k < nrec ? r0 + 256 * k : 0);
+      a1[k] = (&c->mn1)[2 * add]; a2[k] = (&c->mn2)[2 * add]; ai[k] = (&c->imn)[add];
+    }
+  };
+  request(tid & 255);
+  // behind the records (loads return in order): four threads per row of M^-1, a pair of columns out of every eight each
+  const int r = tid >> 2, quarter = tid & 3;
+  double2 mv[16];
+#pragma unroll
+  for (int u = 0; u < 16; u++) mv[u] = *reinterpret_cast<const double2*>(L.Minv + r * LAZY_TM + 8 * u + 2 * quarter);
+  asm volatile("" ::: "memory");
+  double v1 = INFINITY, v2 = INFINITY;
+  int i1 = -1;
+  auto merge = [&](int r0) {
 #pragma unroll
     for (int k = 0; k < 4; k++)
-      if (r0 + 256 * k < nrec) {
-        merge_min(mn1, mn2, imn, c[k].mn1, c[k].mn2, c[k].imn);
-        merge_max(mx1, mx2, imx, c[k].mx1, c[k].mx2, c[k].imx);
-      }
-  }
-  wave_merge(mn1, mn2, imn, mx1, mx2, imx);
-  if ((tid & 63) == 63) { const int w = tid >> 6; s_mn1[w] = mn1; s_mn2[w] = mn2; s_imn[w] = imn; s_mx1[w] = mx1; s_mx2[w] = mx2; s_imx[w] = imx; }
+      if (r0 + 256 * k < nrec) merge_min(v1, v2, i1, sign * a1[k], sign * a2[k], ai[k]);
+  };
+  merge(tid & 255);                        // apart from the loop: its waits would count the requests for M^-1 in
+  for (int r0 = (tid & 255) + 1024; r0 < nrec; r0 += 1024) { request(r0); merge(r0); }
+  double wv = v1;
+  int wi = i1;
+  wave_min(wv, wi);
+  if ((tid & 63) == 63) { s_v[wave] = wv; s_i[wave] = wi; }
   __syncthreads();
   if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; }
-  mn1 = s_mn1[0]; mn2 = s_mn2[0]; imn = s_imn[0]; mx1 = s_mx1[0]; mx2 = s_mx2[0]; imx = s_imx[0];
-  for (int w = 1; w < 4; w++) { merge_min(mn1, mn2, imn, s_mn1[w], s_mn2[w], s_imn[w]); merge_max(mx1, mx2, imx, s_mx1[w], s_mx2[w], s_imx[w]); }
-  const int g = single ? *single : (forced_g >= 0 ? forced_g : imn);
-  const int j = single ? g : (forced_g >= 0 ? forced_j : imx);
+  // lanes 0 - 3 hold the leaving side's four results, 4 - 7 the entering side's: two steps leave each side's best in its quad
+  double qv = s_v[tid & 7];
+  int qi = s_i[tid & 7];
+  dpp_min_step<0xb1, 0xf>(qv, qi); dpp_min_step<0x4e, 0xf>(qv, qi);
+  const int pick_g = __builtin_amdgcn_readlane(qi, 0), pick_j = __builtin_amdgcn_readlane(qi, 4);
+  const int g = single ? *single : (forced_g >= 0 ? forced_g : pick_g);
+  const int j = single ? g : (forced_g >= 0 ? forced_j : pick_j);
   if (g < 0 || j < 0 || (forced_g >= 0 && (!kept[g] || kept[j]))) {
     if (tid == 0) { ctrl->done = 1; ctrl->g_out = -1; ctrl->g_in = -1; }
     return;
   }
-  // the three base entries of the pivot block: requested now by otherwise idle threads, used by thread 0 at the end
-  if (tid == 192) s_n0[0] = (double)nsym1(N0, d1, g, g);
-  if (tid == 193) s_n0[1] = (double)nsym1(N0, d1, j, g);
-  if (tid == 194) s_n0[2] = (double)nsym1(N0, d1, j, j);
-  const int sg0 = L.cslot[g], sj0 = L.cslot[j];
+  // everything that depends on the pick in one round trip: b = N0[T, {g, j}] (these are rows g, j of C0), zero beyond tau,
+  // the three base entries of the pivot block, the slots
+  // (unconditional loads: a load under a condition is waited for where the condition ends)
+  const int side_b = tid >> 7, col_b = tid & (LAZY_TM - 1);      // threads 0 - 127: row g, 128 - 255: row j
+  const float b_raw = L.C0R[(int64_t)(side_b & 1 ? j : g) * LAZY_TM + col_b];
+  const int nr = tid == 256 ? g : j, nc = tid == 258 ? j : g;    // threads 256 - 258: (g, g), (j, g), (j, j)
+  const float n0 = N0[(int64_t)max(nr, nc) * d1 + min(nr, nc)];
+  const int sg0 = L.cslot[g], sj0 = L.cslot[j], pg0 = L.pos[g], pj0 = L.pos[j], spare = L.misc[MI_SPARE];
+  // second-best values: every thread's best unless it is the pick
+  const double sec = wave_min(i1 >= 0 && i1 != (add ? pick_j : pick_g) ? v1 : v2);
+  if ((tid & 63) == 63) s_2nd[wave] = sec;
   const int need = (sg0 < 0 ? 1 : 0) + ((!single && sj0 < 0) ? 1 : 0);
-  if (L.pos[g] >= 0 || L.pos[j] >= 0 || tau + (single ? 1 : 2) > LAZY_TM || L.misc[MI_SPARE] + need > LAZY_NS) {
+  if (pg0 >= 0 || pj0 >= 0 || tau + (single ? 1 : 2) > LAZY_TM || spare + need > LAZY_NS) {
     if (tid == 0) ctrl->pause = 1;
     return;
   }
-  // b = N0[T, {g, j}] (these are rows g, j of C0), x = M^-1 b, zero beyond tau
-  for (int s = tid; s < LAZY_TM; s += 256) {
-    bg[s] = (s < tau) ? (double)L.C0R[(int64_t)g * LAZY_TM + s] : 0.0;
-    bj[s] = (s < tau && !single) ? (double)L.C0R[(int64_t)j * LAZY_TM + s] : 0.0;
-  }
+  if (side_b == 0) bg[col_b] = col_b < tau ? (double)b_raw : 0.0;
+  if (side_b == 1) bj[col_b] = (col_b < tau && !single) ? (double)b_raw : 0.0;
+  if (tid >= 256 && tid < 259) s_n0[tid - 256] = (double)n0;
   __syncthreads();
-  // two threads per row of M^-1, one half of the columns each
+  // x = M^-1 b (bg, bj are zero beyond tau, M^-1 is finite there)
+  double a = 0, b = 0;
+#pragma unroll
+  for (int u = 0; u < 16; u++) {
+    const double2 p = *reinterpret_cast<const double2*>(bg + 8 * u + 2 * quarter), q = *reinterpret_cast<const double2*>(bj + 8 * u + 2 * quarter);
+    a += mv[u].x * p.x + mv[u].y * p.y; b += mv[u].x * q.x + mv[u].y * q.y;
+  }
+  a += dpp_get<0xb1, 0xf>(a); b += dpp_get<0xb1, 0xf>(b);
+  a += dpp_get<0x4e, 0xf>(a); b += dpp_get<0x4e, 0xf>(b);
   double pgg = 0, pjg = 0, pjj = 0;
-  {
-    const int r = tid >> 1, half = tid & 1;
-    double a = 0, b = 0;
-    if (r < tau) {
-      // the whole half row is requested at once (bg, bj are zero beyond tau, M^-1 is finite there)
-      const double* mrow = L.Minv + r * LAZY_TM + half * (LAZY_TM / 2);
-      const double* pg = bg + half * (LAZY_TM / 2);
-      const double* pj = bj + half * (LAZY_TM / 2);
-      const int cnt = min(tau - half * (LAZY_TM / 2), LAZY_TM / 2);      // columns of this half below tau (may be <= 0)
-      for (int s0 = 0; s0 < cnt; s0 += 32) {
-        double mv[32];
-#pragma unroll
-        for (int u = 0; u < 32; u++) mv[u] = mrow[s0 + u];
-#pragma unroll
-        for (int u = 0; u < 32; u++) { a += mv[u] * pg[s0 + u]; b += mv[u] * pj[s0 + u]; }
-      }
-    }
-    a += __shfl_xor(a, 1, 64); b += __shfl_xor(b, 1, 64);
-    if (half == 0) {
-      L.xg[r] = a; L.xj[r] = b;
-      pgg = bg[r] * a; pjg = bj[r] * a; pjj = bj[r] * b;
-    }
+  if (quarter == 0) {
+    if (r >= tau) { a = 0; b = 0; }
+    L.xg[r] = a; L.xj[r] = b;
+    pgg = bg[r] * a; pjg = bj[r] * a; pjj = bj[r] * b;
   }
   pgg = wsum(pgg); pjg = wsum(pjg); pjj = wsum(pjj);
-  if ((tid & 63) == 0) { red[0][tid >> 6] = pgg; red[1][tid >> 6] = pjg; red[2][tid >> 6] = pjj; }
+  if ((tid & 63) == 0) { red[0][wave] = pgg; red[1][wave] = pjg; red[2][wave] = pjj; }
   __syncthreads();
   if (tid == 0) {
-    const double ngg = s_n0[0] - (red[0][0] + red[0][1] + red[0][2] + red[0][3]);
-    const double njg = s_n0[1] - (red[1][0] + red[1][1] + red[1][2] + red[1][3]);
-    const double njj = s_n0[2] - (red[2][0] + red[2][1] + red[2][2] + red[2][3]);
+    double sum[3];
+#pragma unroll
+    for (int k = 0; k < 3; k++) sum[k] = ((red[k][0] + red[k][1]) + (red[k][2] + red[k][3])) + ((red[k][4] + red[k][5]) + (red[k][6] + red[k][7]));
+    const double ngg = s_n0[0] - sum[0];
+    const double njg = s_n0[1] - sum[1];
+    const double njj = s_n0[2] - sum[2];
     const bool bad1 = !(ngg < 0.0);                         // kept pivot: N_gg = -P_gg
     const double Dg = 1.0 / (bad1 ? -1.0 : ngg);
     double M1 = Dg * njg;
@@ -255,13 +293,14 @@ __global__ __launch_bounds__(256) void lazy_prep_kernel(LazyPtrs L, const float*
     if (bad1 || bad2) ctrl->notpd = 1;
     ctrl->g_out = g; ctrl->g_in = j;
     // slots of the two base columns; a pivot that is not among the candidates takes a spare slot, filled by the next kernel
-    int ns = L.misc[MI_SPARE], miss = 0, sg = sg0, sj = sj0;
+    int ns = spare, miss = 0, sg = sg0, sj = sj0;
     if (sg < 0) { sg = LAZY_NC + ns++; L.cslot[g] = sg; L.cand[sg] = g; miss |= 1; }
     if (single) sj = sg;
     else if (sj < 0) { sj = LAZY_NC + ns++; L.cslot[j] = sj; L.cand[sj] = j; miss |= 2; }
     L.misc[MI_SPARE] = ns; L.misc[MI_MISS] = miss; L.misc[MI_SG] = sg; L.misc[MI_SJ] = sj;
     ctrl->misses += (miss & 1) + (miss >> 1);
-    const double m1 = mn1, m2 = mn2, x1 = mx1, x2 = mx2;
+    const double m2 = fmin(fmin(s_2nd[0], s_2nd[1]), fmin(s_2nd[2], s_2nd[3])), x2 = fmin(fmin(s_2nd[4], s_2nd[5]), fmin(s_2nd[6], s_2nd[7]));
+    const double m1 = fmin(fmin(s_v[0], s_v[1]), fmin(s_v[2], s_v[3])), x1 = fmin(fmin(s_v[4], s_v[5]), fmin(s_v[6], s_v[7]));
     ctrl->gap_rem = isfinite(m2) ? fabs(m2 - m1) / fmax(fabs(m1), 1e-300) : INFINITY;
     ctrl->gap_add = isfinite(x2) ? fabs(x1 - x2) / fmax(fabs(x1), 1e-300) : INFINITY;
   }
@@ -716,7 +755,7 @@ __global__ __launch_bounds__(256) void lazy_update_kernel(LazyPtrs L, const floa
 hipError_t launch_lazy_iteration(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int always_accept, hipStream_t s,
                                  hipEvent_t* ev, const int32_t* single, int forced_out, int forced_in) {
   const int rb = (d.d1 + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, cb = (d.m + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
-  hipLaunchKernelGGL(lazy_prep_kernel, dim3(1), dim3(256), 0, s, L, t.N, d.d1, rb, t.kept, t.ctrl, single, forced_out, forced_in);
+  hipLaunchKernelGGL(lazy_prep_kernel, dim3(1), dim3(PREP_T), 0, s, L, t.N, d.d1, rb, t.kept, t.ctrl, single, forced_out, forced_in);
   hipLaunchKernelGGL(lazy_vectors_kernel, dim3(rb + cb + (d.d1 + 63) / 64), dim3(256), 0, s, L, t.N, t.Z, d.d1, d.m, rb, cb, t.ctrl);
   const int gb = (d.d1 + GEMV_ROWS - 1) / GEMV_ROWS + LAZY_TM * GEMV_SPLIT;
   if (ev) hipEventRecord(ev[0], s);
