@@ -1524,51 +1524,62 @@ __global__ __launch_bounds__(256) void blk_prep_kernel(LazyPtrs L, const float* 
   if (tid == 0 && s_notpd) ctrl->notpd = 1;
 }
 
-// current rows of the picks, Y = D Z_G, and per column block the partial sums of Y Y^T and <Z_G[a], Y[a]>
+typedef double lzd4 __attribute__((ext_vector_type(4)));
+static_assert(BT == 16, "one 16 x 16 tile of picks");
+// Current rows of the picks, Y = D Z_G, and per column block the partial sums of Y Y^T and <Z_G[a], Y[a]>, all on
+// v_mfma_f64_16x16x4_f64: a wave takes 16 columns, lane (lr, lc) holds the picks 4 r + lr of column lc, which is also the
+// operand layout of the next product.  As scalar loops with one wave left for the sums this took 26 us for 2048 columns.
 __global__ __launch_bounds__(256) void blk_cols_kernel(LazyPtrs L, const float* __restrict__ Z0, int m, int t,
                                                         const SearchCtrl* __restrict__ ctrl) {
-  __shared__ double sb[LAZY_TM * BT], sD[BT * BT];
-  __shared__ double zred[3][COLS_PER_BLOCK][BT];
+  __shared__ double zl[BT][COLS_PER_BLOCK + 1], yl[BT][COLS_PER_BLOCK + 1];
   if (idle(ctrl)) return;
   const int tid = threadIdx.x, tau = ctrl->tau, cb = blockIdx.x;
-  const int slice = tid >> 6, lc = tid & 63, col = cb * COLS_PER_BLOCK + lc;
-  for (int idx = tid; idx < LAZY_TM * BT; idx += 256) sb[idx] = L.bB[idx];
-  for (int idx = tid; idx < BT * BT; idx += 256) sD[idx] = L.bD[idx];
-  __syncthreads();
-  double acc[BT];
+  const int lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15, col = cb * COLS_PER_BLOCK + wave * 16 + lc;
+  const int cc = min(col, m - 1);
+  float z0[4];
+  double d[4];
 #pragma unroll
-  for (int a = 0; a < BT; a++) acc[a] = 0.0;
-  if (col < m)
-    for (int r = slice; r < tau; r += 4) {
-      const double zt = L.ZT[(int64_t)r * m + col];
+  for (int r = 0; r < 4; r++) {
+    const int a = 4 * r + lr;
+    z0[r] = a < t ? Z0[(int64_t)L.bG[a] * m + cc] : 0.f;
+    d[r] = L.bD[lc * BT + a];
+  }
+  lzd4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int k0 = 0; k0 < tau; k0 += 32) {
+    double av[8], bv[8];
 #pragma unroll
-      for (int a = 0; a < BT; a++) acc[a] += sb[r * BT + a] * zt;
+    for (int u = 0; u < 8; u++) {
+      const int k = k0 + 4 * u + lr, kc = min(k, LAZY_TM - 1);
+      const double zt = L.ZT[(int64_t)kc * m + cc];
+      av[u] = L.bB[kc * BT + lc];                       // zero from tau on, where ZT holds anything
+      bv[u] = k < tau ? zt : 0.0;
     }
-  if (slice > 0) {
 #pragma unroll
-    for (int a = 0; a < BT; a++) zred[slice - 1][lc][a] = acc[a];
+    for (int u = 0; u < 8; u++) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u], acc, 0, 0, 0);
+  }
+  lzd4 y = {0.0, 0.0, 0.0, 0.0};
+  double zg[4];
+#pragma unroll
+  for (int r = 0; r < 4; r++) zg[r] = (4 * r + lr < t && col < m) ? (double)z0[r] - acc[r] : 0.0;
+#pragma unroll
+  for (int r = 0; r < 4; r++) y = __builtin_amdgcn_mfma_f64_16x16x4f64(d[r], zg[r], y, 0, 0, 0);
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int a = 4 * r + lr;
+    if (a < t && col < m) L.bY[(int64_t)a * m + col] = y[r];
+    zl[a][wave * 16 + lc] = zg[r]; yl[a][wave * 16 + lc] = y[r];
   }
   __syncthreads();
-  if (slice != 0) return;
-  double zg[BT], y[BT];
-#pragma unroll
-  for (int a = 0; a < BT; a++) {
-    zg[a] = 0.0;
-    if (a < t && col < m) zg[a] = (double)Z0[(int64_t)L.bG[a] * m + col] - (acc[a] + zred[0][lc][a] + zred[1][lc][a] + zred[2][lc][a]);
-  }
-#pragma unroll
-  for (int a = 0; a < BT; a++) {
-    double v = 0;
-#pragma unroll
-    for (int b = 0; b < BT; b++) v += sD[a * BT + b] * zg[b];
-    y[a] = v;
-    if (a < t && col < m) L.bY[(int64_t)a * m + col] = v;
-  }
+  if (wave > 1) return;
+  lzd4 p = {0.0, 0.0, 0.0, 0.0};                        // wave 0: Y Y^T; wave 1: Z_G Y^T, of which the diagonal
+#pragma unroll 4
+  for (int k0 = 0; k0 < COLS_PER_BLOCK; k0 += 4) p = __builtin_amdgcn_mfma_f64_16x16x4f64(wave ? zl[lc][k0 + lr] : yl[lc][k0 + lr], yl[lc][k0 + lr], p, 0, 0, 0);
   double* part = L.bpart + (int64_t)cb * (BT * BT + BT);
-  for (int a = 0; a < t; a++) {
-    for (int b = 0; b <= a; b++) { const double v = wsum(y[a] * y[b]); if (lc == 0) part[a * BT + b] = v; }
-    const double v = wsum(zg[a] * y[a]);
-    if (lc == 0) part[BT * BT + a] = v;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int a = 4 * r + lr;
+    if (wave == 0 && lc <= a) part[a * BT + lc] = p[r];
+    if (wave == 1 && lc == a) part[BT * BT + a] = p[r];
   }
 }
 
@@ -1635,124 +1646,124 @@ __global__ __launch_bounds__(256) void blk_gemv_kernel(LazyPtrs L, int m, int t,
   }
 }
 
-__global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int m, int t, int row_blocks,
+// Rows: the sums over the pending pivots, D wt and the two quadratic forms of every row on v_mfma_f64_16x16x4_f64.  A wave takes 16
+// rows, lane (lr, lc) holds the picks 4 r + lr of row lc; a workgroup of 64 rows leaves two selection records.  As 8 lanes per
+// row, with the forms left to one of them, a removal of 10 of 8192 rows took 35 us here.
+constexpr int BX_LD = 20;      // doubles per row of the X and U tables: the four k of an operand read lie in different banks
+__global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int m, int t, int row_groups,
                                                           int row_wgs, int col_blocks, SearchCtrl* ctrl, int32_t* __restrict__ kept,
                                                           double* __restrict__ rho, double* __restrict__ diag,
                                                           double* __restrict__ score) {
-  __shared__ double sX[LAZY_TM * BT], sU[LAZY_TM * BT], sD[BT * BT], sYY[BT * BT];
+  __shared__ double sX[LAZY_TM * BX_LD], sU[LAZY_TM * BX_LD], sD[BT * BT], sYY[BT * BT];
   __shared__ int sts[LAZY_TM], sG[BT], sSlot[BT];
-  __shared__ double w_mn1[4], w_mn2[4], w_mx1[4], w_mx2[4];
-  __shared__ int w_imn[4], w_imx[4];
+  __shared__ double s_sc[64];
+  __shared__ int s_kp[64];
   if (idle(ctrl)) return;
   const int tid = threadIdx.x, tau = ctrl->tau, b = blockIdx.x;
   if (b < row_wgs) {
-    // sX, sU transposed to [a][r]: the eight lanes of a row read eight consecutive r
     for (int idx = tid; idx < LAZY_TM * BT; idx += 256) {
       const int r = idx / BT, a = idx % BT;
       double u = 0;
 #pragma unroll
       for (int sl = 0; sl < BU_SLABS; sl++) u += L.bU[(int64_t)sl * LAZY_TM * BT + idx];
-      sX[a * LAZY_TM + r] = L.bX[idx]; sU[a * LAZY_TM + r] = u;
+      sX[r * BX_LD + a] = L.bX[idx]; sU[r * BX_LD + a] = r < tau ? u : 0.0;
     }
-    for (int idx = tid; idx < BT * BT; idx += 256) { sD[idx] = L.bD[idx]; sYY[idx] = L.bYY[idx]; }
+    for (int idx = tid; idx < BT * BT; idx += 256) { const int a = idx / BT, c = idx % BT; sD[idx] = L.bD[idx]; sYY[idx] = (a < t && c < t) ? L.bYY[idx] : 0.0; }
     for (int s = tid; s < LAZY_TM; s += 256) sts[s] = (s < tau) ? L.tslot[s] : 0;
-    if (tid < BT) { const int g = L.bG[tid]; sG[tid] = g; sSlot[tid] = (tid < t) ? L.cslot[g] : 0; }
+    if (tid < BT) { const int g = tid < t ? L.bG[tid] : 0; sG[tid] = g; sSlot[tid] = (tid < t) ? L.cslot[g] : 0; }
     __syncthreads();
-    // a workgroup walks blocks of 32 rows (one selection record each), so the tables above are loaded once for several
-    for (int rbk = b; rbk < row_blocks; rbk += row_wgs) {
-    const int row = rbk * ROWS_PER_BLOCK + (tid >> 3), l8 = tid & 7;
-    double mn1 = INFINITY, mx1 = -INFINITY;
-    int imn = -1, imx = -1;
-    if (row < d1) {
-      double dx[BT], du[BT], dw[BT];
+    const int lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+    // a workgroup walks groups of 64 rows (two selection records each), so the tables above are loaded once for several
+    for (int grp = b; grp < row_groups; grp += row_wgs) {
+      const int row = grp * 64 + wave * 16 + lc, rc = min(row, d1 - 1);
+      // requested first: the base entries N0[row, G] (new columns of C0), the products GbT[G, row], the row's own values
+      float n0[4];
+      double gb0[4];
 #pragma unroll
-      for (int a = 0; a < BT; a++) { dx[a] = 0.0; du[a] = 0.0; dw[a] = 0.0; }
-      const float* crow = L.C0R + (int64_t)row * LAZY_TM;
-      for (int r = l8; r < tau; r += 8) {
-        const double c = (double)crow[r];
-        const double gb = L.GbT[(int64_t)sts[r] * d1 + row];
+      for (int r = 0; r < 4; r++) {
+        const int a = 4 * r + lr;
+        n0[r] = nsym1(N0, d1, rc, sG[a]);
+        gb0[r] = L.GbT[(int64_t)sSlot[a] * d1 + rc];
+      }
+      const int ps = L.pos[rc], kp0 = kept[rc];
+      const double rho0 = rho[rc], diag0 = diag[rc];
+      lzd4 dx = {0.0, 0.0, 0.0, 0.0}, du = dx, dw = dx;
+      const float* crow = L.C0R + (int64_t)rc * LAZY_TM;
+      for (int k0 = 0; k0 < tau; k0 += 16) {              // k = k0 + 4 lr + e: a lane's four values of C0 are one load
+        const float4 c4 = *reinterpret_cast<const float4*>(crow + k0 + 4 * lr);
+        const float ce[4] = {c4.x, c4.y, c4.z, c4.w};
+        double gv[4];
 #pragma unroll
-        for (int a = 0; a < BT; a++) {
-          const double x = sX[a * LAZY_TM + r];
-          dx[a] += c * x; du[a] += c * sU[a * LAZY_TM + r]; dw[a] += gb * x;
+        for (int e = 0; e < 4; e++) gv[e] = L.GbT[(int64_t)sts[k0 + 4 * lr + e] * d1 + rc];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int k = k0 + 4 * lr + e;
+          const double x = sX[k * BX_LD + lc], u = sU[k * BX_LD + lc];      // zero from tau on
+          const double c = k < tau ? (double)ce[e] : 0.0;
+          dx = __builtin_amdgcn_mfma_f64_16x16x4f64(x, c, dx, 0, 0, 0);
+          du = __builtin_amdgcn_mfma_f64_16x16x4f64(u, c, du, 0, 0, 0);
+          dw = __builtin_amdgcn_mfma_f64_16x16x4f64(x, k < tau ? gv[e] : 0.0, dw, 0, 0, 0);
         }
       }
+      lzd4 w = {0.0, 0.0, 0.0, 0.0}, sy = w, sd = w;
 #pragma unroll
-      for (int a = 0; a < BT; a++) {
-        dx[a] = sum8(dx[a]); du[a] = sum8(du[a]); dw[a] = sum8(dw[a]);
+      for (int r = 0; r < 4; r++) {
+        const int a = 4 * r + lr;
+        w = __builtin_amdgcn_mfma_f64_16x16x4f64(sD[lc * BT + a], a < t ? gb0[r] - dw[r] : 0.0, w, 0, 0, 0);
+        if (a < t && row < d1) L.C0R[(int64_t)row * LAZY_TM + tau + a] = n0[r];
       }
-      // the base entries N0[row, G] (new columns of C0) and the products GbT[G, row]: lane l8 fetches a = l8 and l8 + 8
-      static_assert(BT == 16, "two picks per lane");
-      float n_lo = 0.f, n_hi = 0.f;
-      double g_lo = 0.0, g_hi = 0.0;
-      if (l8 < t) { n_lo = nsym1(N0, d1, row, sG[l8]); g_lo = L.GbT[(int64_t)sSlot[l8] * d1 + row]; L.C0R[(int64_t)row * LAZY_TM + tau + l8] = n_lo; }
-      if (l8 + 8 < t) { n_hi = nsym1(N0, d1, row, sG[l8 + 8]); g_hi = L.GbT[(int64_t)sSlot[l8 + 8] * d1 + row]; L.C0R[(int64_t)row * LAZY_TM + tau + l8 + 8] = n_hi; }
-      double nrow[BT], grow[BT];
-      const int lane0 = (tid & 63) & ~7;
+      double cg[4], zy[4];
+      const double sg = ps >= 0 ? (double)L.Jsg[ps] : 0.0;
 #pragma unroll
-      for (int a = 0; a < BT; a++) {
-        nrow[a] = (double)__shfl(a < 8 ? n_lo : n_hi, lane0 + (a & 7), 64);
-        grow[a] = __shfl(a < 8 ? g_lo : g_hi, lane0 + (a & 7), 64);
+      for (int r = 0; r < 4; r++) {
+        const int a = 4 * r + lr;
+        cg[r] = a >= t ? 0.0 : ps >= 0 ? sg * sX[ps * BX_LD + a] : (double)n0[r] - dx[r];
+        zy[r] = a >= t ? 0.0 : ps >= 0 ? sg * sU[ps * BX_LD + a] : w[r] - du[r];
       }
-      if (l8 == 0) {
-        int mine = -1;
-        for (int a = 0; a < t; a++) if (sG[a] == row) mine = a;
-        const int ps = L.pos[row];
-        double r, dn;
-        int kp;
-        if (mine >= 0) {
-          r = sYY[mine * BT + mine]; dn = -sD[mine * BT + mine]; kp = 0;
-          L.pos[row] = tau + mine; L.Tidx[tau + mine] = row; L.Jsg[tau + mine] = -1.f; L.tslot[tau + mine] = sSlot[mine];
-        } else {
-          double cg[BT], zy[BT];
-          if (ps >= 0) {
-            const double sg = (double)L.Jsg[ps];
 #pragma unroll
-            for (int a = 0; a < BT; a++) { cg[a] = sg * sX[a * LAZY_TM + ps]; zy[a] = sg * sU[a * LAZY_TM + ps]; }
+      for (int r = 0; r < 4; r++) {
+        sy = __builtin_amdgcn_mfma_f64_16x16x4f64(sYY[lc * BT + 4 * r + lr], cg[r], sy, 0, 0, 0);
+        sd = __builtin_amdgcn_mfma_f64_16x16x4f64(sD[lc * BT + 4 * r + lr], cg[r], sd, 0, 0, 0);
+      }
+      double lin = 0, quadY = 0, quadD = 0;
+#pragma unroll
+      for (int r = 0; r < 4; r++) { lin += cg[r] * zy[r]; quadY += cg[r] * sy[r]; quadD += cg[r] * sd[r]; }
+      lin += __shfl_xor(lin, 16, 64); quadY += __shfl_xor(quadY, 16, 64); quadD += __shfl_xor(quadD, 16, 64);
+      lin += __shfl_xor(lin, 32, 64); quadY += __shfl_xor(quadY, 32, 64); quadD += __shfl_xor(quadD, 32, 64);
+      if (lr == 0) {
+        int kp = -1;
+        double sc = 0.0;
+        if (row < d1) {
+          int mine = -1;
+          for (int a = 0; a < t; a++) if (sG[a] == row) mine = a;
+          double r, dn;
+          if (mine >= 0) {
+            r = sYY[mine * BT + mine]; dn = -sD[mine * BT + mine]; kp = 0;
+            L.pos[row] = tau + mine; L.Tidx[tau + mine] = row; L.Jsg[tau + mine] = -1.f; L.tslot[tau + mine] = sSlot[mine];
           } else {
-            double wt[BT];
-#pragma unroll
-            for (int a = 0; a < BT; a++) wt[a] = (a < t) ? grow[a] - dw[a] : 0.0;
-#pragma unroll
-            for (int a = 0; a < BT; a++) {
-              double w = 0;
-#pragma unroll
-              for (int bb = 0; bb < BT; bb++) w += sD[a * BT + bb] * wt[bb];
-              cg[a] = nrow[a] - dx[a];
-              zy[a] = w - du[a];
-            }
+            r = rho0 - 2.0 * lin + quadY;
+            if (r < 0.0) r = 0.0;
+            dn = diag0 - quadD;
+            kp = kp0;
           }
-          double lin = 0, quadY = 0, quadD = 0;
-#pragma unroll
-          for (int a = 0; a < BT; a++) {
-            lin += cg[a] * zy[a];
-            double sy = 0, sd = 0;
-#pragma unroll
-            for (int bb = 0; bb < BT; bb++) { sy += sYY[a * BT + bb] * cg[bb]; sd += sD[a * BT + bb] * cg[bb]; }
-            quadY += cg[a] * sy; quadD += cg[a] * sd;
-          }
-          r = rho[row] - 2.0 * lin + quadY;
-          if (r < 0.0) r = 0.0;
-          dn = diag[row] - quadD;
-          kp = kept[row];
+          rho[row] = r; diag[row] = dn; kept[row] = kp;
+          sc = r / fabs(dn);
+          score[row] = sc;
         }
-        rho[row] = r; diag[row] = dn; kept[row] = kp;
-        const double sc = r / fabs(dn);
-        score[row] = sc;
-        if (kp) { mn1 = sc; imn = row; } else { mx1 = sc; imx = row; }
+        s_sc[wave * 16 + lc] = sc; s_kp[wave * 16 + lc] = kp;
       }
-    }
-    double mn2 = INFINITY, mx2 = -INFINITY;
-    wave_merge(mn1, mn2, imn, mx1, mx2, imx);          // lanes that lead no row hold the neutral record
-    if ((tid & 63) == 63) { const int w = tid >> 6; w_mn1[w] = mn1; w_mn2[w] = mn2; w_imn[w] = imn; w_mx1[w] = mx1; w_mx2[w] = mx2; w_imx[w] = imx; }
-    __syncthreads();
-    if (tid == 0) {
-      mn1 = w_mn1[0]; mn2 = w_mn2[0]; imn = w_imn[0]; mx1 = w_mx1[0]; mx2 = w_mx2[0]; imx = w_imx[0];
-      for (int w = 1; w < 4; w++) { merge_min(mn1, mn2, imn, w_mn1[w], w_mn2[w], w_imn[w]); merge_max(mx1, mx2, imx, w_mx1[w], w_mx2[w], w_imx[w]); }
-      SelRec rec; rec.mn1 = mn1; rec.mn2 = mn2; rec.mx1 = mx1; rec.mx2 = mx2; rec.imn = imn; rec.imx = imx;
-      L.sel[rbk] = rec;
-    }
-    __syncthreads();
+      __syncthreads();
+      if (wave < 2 && grp * 2 + wave < (d1 + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) {
+        const int e = wave * 32 + (lane & 31), kp = lane < 32 ? s_kp[e] : -1;
+        double mn1 = kp > 0 ? s_sc[e] : INFINITY, mx1 = kp == 0 ? s_sc[e] : -INFINITY, mn2 = INFINITY, mx2 = -INFINITY;
+        int imn = kp > 0 ? grp * 64 + e : -1, imx = kp == 0 ? grp * 64 + e : -1;
+        wave_merge(mn1, mn2, imn, mx1, mx2, imx);          // lanes without a row hold the neutral record
+        if (lane == 63) {
+          SelRec rec; rec.mn1 = mn1; rec.mn2 = mn2; rec.mx1 = mx1; rec.mx2 = mx2; rec.imn = imn; rec.imx = imx;
+          L.sel[grp * 2 + wave] = rec;
+        }
+      }
+      __syncthreads();
     }
   } else if (b < row_wgs + col_blocks) {
     const int cb = b - row_wgs, slice = tid >> 6, col = cb * COLS_PER_BLOCK + (tid & 63);
@@ -1798,12 +1809,12 @@ __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float
 hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int take, const int32_t* pick,
                                     hipStream_t s) {
   if (take < 1 || take > BT) return hipErrorInvalidValue;
-  const int rb = (d.d1 + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, cb = (d.m + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
+  const int rg = (d.d1 + 63) / 64, cb = (d.m + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
   hipLaunchKernelGGL(blk_prep_kernel, dim3(1), dim3(256), 0, s, L, t.N, d.d1, take, pick, t.kept, t.ctrl);
   hipLaunchKernelGGL(blk_cols_kernel, dim3(cb), dim3(256), 0, s, L, t.Z, d.m, take, t.ctrl);
   hipLaunchKernelGGL(blk_gemv_kernel, dim3(LAZY_TM + 1), dim3(256), 0, s, L, d.m, take, cb, t.ctrl, t.trace_out);
-  const int row_wgs = std::min(rb, 256);
-  hipLaunchKernelGGL(blk_update_kernel, dim3(row_wgs + cb + 16), dim3(256), 0, s, L, t.N, d.d1, d.m, take, rb, row_wgs, cb, t.ctrl,
+  const int row_wgs = std::min(rg, 256);
+  hipLaunchKernelGGL(blk_update_kernel, dim3(row_wgs + cb + 16), dim3(256), 0, s, L, t.N, d.d1, d.m, take, rg, row_wgs, cb, t.ctrl,
                      t.kept, t.gram, t.dblk, t.score);
   return hipGetLastError();
 }
