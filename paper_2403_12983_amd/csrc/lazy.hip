@@ -29,6 +29,7 @@
 //   update  (rows|cols|M)  : norms, diagonal, scores and their partial records; C0 append; ZT and M^-1 update
 //                            (after a miss also w, whose missing column exists only since gemv)
 #include "internal.h"
+#include "inverse16.h"
 #include <algorithm>
 
 namespace osscar {
@@ -1456,76 +1457,77 @@ hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs&
 // ------------------------------------------------------------------------------------------------
 constexpr int BT = LAZY_BT;
 
-// n x n inverse (n <= BT) in shared memory by Gauss-Jordan without pivoting; every pivot must be negative (the block is
-// minus a principal block of a positive definite inverse), else *bad is set.  All threads of the workgroup call it.
-__device__ void blk_inverse(double* A, int n, int* bad) {
-  __shared__ double col[BT], rowk[BT];
-  const int tid = threadIdx.x;
-  for (int k = 0; k < n; k++) {
-    __syncthreads();
-    double piv = A[k * n + k];
-    if (!(piv < 0.0)) { if (tid == 0) *bad = 1; piv = -1.0; }
-    const double dinv = 1.0 / piv;
-    if (tid < n) { col[tid] = A[tid * n + k]; rowk[tid] = A[k * n + tid] * dinv; }
-    __syncthreads();
-    for (int idx = tid; idx < n * n; idx += blockDim.x) {
-      const int i = idx / n, j = idx % n;
-      double v;
-      if (i == k) v = (j == k) ? dinv : rowk[j];
-      else if (j == k) v = -col[i] * dinv;
-      else v = A[idx] - col[i] * rowk[j];
-      A[idx] = v;
-    }
-  }
-  __syncthreads();
-}
-
-__global__ __launch_bounds__(256) void blk_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int t,
-                                                        const int32_t* __restrict__ pick, const int32_t* __restrict__ kept,
-                                                        SearchCtrl* ctrl) {
-  __shared__ double sb[LAZY_TM * BT], sX[LAZY_TM * BT], sD[BT * BT];
-  __shared__ int sG[BT], s_bad, s_notpd;
-  if (idle(ctrl)) return;
-  const int tid = threadIdx.x, tau = tau_all(ctrl);      // every thread reads before thread 0 folds the increment in
-  if (tid == 0) { s_bad = 0; s_notpd = 0; }
-  __syncthreads();
-  if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; }
-  if (tid < t) {
-    const int g = pick[tid];
-    sG[tid] = g;
-    if (g < 0 || g >= d1 || !kept[g] || L.pos[g] >= 0 || L.cslot[g] < 0) s_bad = 1;
-  }
-  if (tid == 0 && tau + t > LAZY_TM) s_bad = 1;
-  __syncthreads();
-  if (s_bad) { if (tid == 0) ctrl->pause = 1; return; }
-  for (int idx = tid; idx < tau * t; idx += 256) { const int r = idx / t, a = idx % t; sb[r * BT + a] = (double)L.C0R[(int64_t)sG[a] * LAZY_TM + r]; }
-  __syncthreads();
-  for (int idx = tid; idx < tau * t; idx += 256) {
-    const int r = idx / t, a = idx % t;
-    double v = 0;
-    for (int q = 0; q < tau; q++) v += L.Minv[r * LAZY_TM + q] * sb[q * BT + a];
-    sX[r * BT + a] = v;
-  }
-  __syncthreads();
-  for (int idx = tid; idx < t * t; idx += 256) {
-    const int a = idx / t, b = idx % t;
-    double v = (double)nsym1(N0, d1, sG[a], sG[b]);
-    for (int r = 0; r < tau; r++) v -= sb[r * BT + a] * sX[r * BT + b];
-    sD[idx] = v;
-  }
-  blk_inverse(sD, t, &s_notpd);
-  for (int idx = tid; idx < LAZY_TM * BT; idx += 256) {
-    const int r = idx / BT, a = idx % BT;
-    const bool in = (r < tau && a < t);
-    L.bB[idx] = in ? sb[idx] : 0.0; L.bX[idx] = in ? sX[idx] : 0.0;
-  }
-  for (int idx = tid; idx < BT * BT; idx += 256) { const int a = idx / BT, b = idx % BT; L.bD[idx] = (a < t && b < t) ? sD[a * t + b] : 0.0; }
-  if (tid < BT) L.bG[tid] = tid < t ? sG[tid] : -1;
-  if (tid == 0 && s_notpd) ctrl->notpd = 1;
-}
-
 typedef double lzd4 __attribute__((ext_vector_type(4)));
 static_assert(BT == 16, "one 16 x 16 tile of picks");
+constexpr int BX_LD = 20;      // doubles per row of the tables of a block's columns: the k of an operand read lie in different banks
+// One workgroup: B = N0[T, G], X = M^-1 B, D = (N0[G, G] - B^T X)^-1 (negative definite: minus a principal block of a positive
+// definite inverse).  Bound by round trips to memory: the picks, then their rows of C0 with M^-1 requested before.  A wave has 16
+// rows of M^-1 in registers as a matrix-core operand; its rows of X are the operand of its share of B^T X; one wave inverts.
+__global__ __launch_bounds__(512) void blk_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int t,
+                                                        const int32_t* __restrict__ pick, const int32_t* __restrict__ kept,
+                                                        SearchCtrl* ctrl) {
+  __shared__ double sb[LAZY_TM * BX_LD], sP[8][BT][BT + 1];
+  if (idle(ctrl)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  const int tau = tau_all(ctrl);      // every thread reads before thread 0 folds the increment in (after the barrier)
+  const int g = pick[lane < t ? lane : 0];                // every wave holds all the picks
+  double2 mv[16];                                         // row 16 wave + lc of M^-1, columns 8 u + 2 lr, + 1
+#pragma unroll
+  for (int u = 0; u < 16; u++) mv[u] = *reinterpret_cast<const double2*>(L.Minv + (wave * 16 + lc) * LAZY_TM + 8 * u + 2 * lr);
+  const bool range = g >= 0 && g < d1;
+  const int gc = range ? g : 0;
+  const bool bad = !range || !kept[gc] || L.pos[gc] >= 0 || L.cslot[gc] < 0 || tau + t > LAZY_TM;
+  if (__any(bad)) {                                       // the same in every wave
+    if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; ctrl->pause = 1; }
+    return;
+  }
+  float bv[4], n0[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) bv[i] = L.C0R[(int64_t)__shfl(g, (tid >> 7) + 4 * i, 64) * LAZY_TM + (tid & 127)];
+#pragma unroll
+  for (int r = 0; r < 4; r++) n0[r] = nsym1(N0, d1, __shfl(g, 4 * r + lr, 64), __shfl(g, lc, 64));
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const int a = (tid >> 7) + 4 * i, r = tid & 127;
+    const double v = (r < tau && a < t) ? (double)bv[i] : 0.0;
+    sb[r * BX_LD + a] = v; L.bB[r * BT + a] = v;
+  }
+  __syncthreads();
+  if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; }
+  lzd4 x = {0.0, 0.0, 0.0, 0.0}, p = x;
+#pragma unroll
+  for (int u = 0; u < 16; u++) {                          // B is zero from tau on, M^-1 finite there
+    x = __builtin_amdgcn_mfma_f64_16x16x4f64(mv[u].x, sb[(8 * u + 2 * lr) * BX_LD + lc], x, 0, 0, 0);
+    x = __builtin_amdgcn_mfma_f64_16x16x4f64(mv[u].y, sb[(8 * u + 2 * lr + 1) * BX_LD + lc], x, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int row = wave * 16 + 4 * r + lr;
+    const double v = row < tau ? x[r] : 0.0;
+    L.bX[row * BT + lc] = v;
+    p = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[row * BX_LD + lc], v, p, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++) sP[wave][4 * r + lr][lc] = p[r];
+  __syncthreads();
+  if (wave != 0) return;
+  swd4 y;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int a = 4 * r + lr;
+    double v = (double)n0[r];
+#pragma unroll
+    for (int w = 0; w < 8; w++) v -= sP[w][a][lc];
+    y[r] = (a < t && lc < t) ? -v : (a == lc ? 1.0 : 0.0);
+  }
+  bool flag = false;
+  inv16_steps<0>(y, lane, t, flag);
+#pragma unroll
+  for (int r = 0; r < 4; r++) { const int a = 4 * r + lr; L.bD[a * BT + lc] = (a < t && lc < t) ? -y[r] : 0.0; }
+  if (lane < BT) L.bG[lane] = lane < t ? g : -1;
+  if (__any(flag) && lane == 0) ctrl->notpd = 1;
+}
+
 // Current rows of the picks, Y = D Z_G, and per column block the partial sums of Y Y^T and <Z_G[a], Y[a]>, all on
 // v_mfma_f64_16x16x4_f64: a wave takes 16 columns, lane (lr, lc) holds the picks 4 r + lr of column lc, which is also the
 // operand layout of the next product.  As scalar loops with one wave left for the sums this took 26 us for 2048 columns.
@@ -1649,7 +1651,6 @@ __global__ __launch_bounds__(256) void blk_gemv_kernel(LazyPtrs L, int m, int t,
 // Rows: the sums over the pending pivots, D wt and the two quadratic forms of every row on v_mfma_f64_16x16x4_f64.  A wave takes 16
 // rows, lane (lr, lc) holds the picks 4 r + lr of row lc; a workgroup of 64 rows leaves two selection records.  As 8 lanes per
 // row, with the forms left to one of them, a removal of 10 of 8192 rows took 35 us here.
-constexpr int BX_LD = 20;      // doubles per row of the X and U tables: the four k of an operand read lie in different banks
 __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int m, int t, int row_groups,
                                                           int row_wgs, int col_blocks, SearchCtrl* ctrl, int32_t* __restrict__ kept,
                                                           double* __restrict__ rho, double* __restrict__ diag,
@@ -1784,15 +1785,24 @@ __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float
   } else {
     const int mb = b - row_wgs - col_blocks, nmb = gridDim.x - row_wgs - col_blocks;
     double* Mi = L.Minv;
-    for (int idx = mb * 256 + tid; idx < tau * tau; idx += nmb * 256) {
-      const int r = idx / tau, s = idx % tau;
-      double v = 0;
-      for (int a = 0; a < t; a++) {
-        double xd = 0;
-        for (int bb = 0; bb < t; bb++) xd += L.bX[r * BT + bb] * L.bD[bb * BT + a];
-        v += xd * L.bX[s * BT + a];
+    // M^-1 += X D X^T: a wave per lower 16 x 16 tile (mirrored, so that M^-1 stays symmetric to the bit)
+    const int lane = tid & 63, lr = lane >> 4, lc = lane & 15;
+    for (int tile = mb * 4 + (tid >> 6); tile < 36; tile += nmb * 4) {
+      int I = 0, J = tile;
+      while (J > I) { J -= I + 1; I++; }
+      if (I * 16 >= tau) break;
+      lzd4 dx = {0.0, 0.0, 0.0, 0.0}, v = dx;
+#pragma unroll
+      for (int r = 0; r < 4; r++) dx = __builtin_amdgcn_mfma_f64_16x16x4f64(L.bD[lc * BT + 4 * r + lr], L.bX[(J * 16 + lc) * BT + 4 * r + lr], dx, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; r++) v = __builtin_amdgcn_mfma_f64_16x16x4f64(L.bX[(I * 16 + lc) * BT + 4 * r + lr], dx[r], v, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int i = I * 16 + 4 * r + lr, j = J * 16 + lc;
+        if (i >= tau || j > i) continue;
+        const double m2 = Mi[i * LAZY_TM + j] + v[r];
+        Mi[i * LAZY_TM + j] = m2; Mi[j * LAZY_TM + i] = m2;
       }
-      Mi[r * LAZY_TM + s] += v;
     }
     if (mb == 0) {
       for (int idx = tid; idx < tau * t; idx += 256) {
@@ -1810,7 +1820,7 @@ hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const La
                                     hipStream_t s) {
   if (take < 1 || take > BT) return hipErrorInvalidValue;
   const int rg = (d.d1 + 63) / 64, cb = (d.m + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
-  hipLaunchKernelGGL(blk_prep_kernel, dim3(1), dim3(256), 0, s, L, t.N, d.d1, take, pick, t.kept, t.ctrl);
+  hipLaunchKernelGGL(blk_prep_kernel, dim3(1), dim3(512), 0, s, L, t.N, d.d1, take, pick, t.kept, t.ctrl);
   hipLaunchKernelGGL(blk_cols_kernel, dim3(cb), dim3(256), 0, s, L, t.Z, d.m, take, t.ctrl);
   hipLaunchKernelGGL(blk_gemv_kernel, dim3(LAZY_TM + 1), dim3(256), 0, s, L, d.m, take, cb, t.ctrl, t.trace_out);
   const int row_wgs = std::min(rg, 256);
