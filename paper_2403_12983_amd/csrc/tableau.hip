@@ -1932,6 +1932,11 @@ __device__ __forceinline__ void best_step(double& v, int& i) {
                                      __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false));
   if (oi >= 0 && (i < 0 || ov < v || (ov == v && oi < i))) { v = ov; i = oi; }
 }
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_or_inf(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0x7FF00000, __double2hiint(v), CTRL, ROW_MASK, 0xF, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false));
+}
 __device__ __forceinline__ void best_of_16(double& v, int& i) {
   best_step<0xb1, 0xf>(v, i);      // quads: xor 1, xor 2
   best_step<0x4e, 0xf>(v, i);
@@ -1944,17 +1949,25 @@ __device__ __forceinline__ void best_of_wave(double& v, int& i) {
   best_step<0x142, 0xa>(v, i);     // row 0 -> 1, 2 -> 3
   best_step<0x143, 0xc>(v, i);     // rows 0, 1 -> 2, 3
 }
-// The same from registers (p <= 1024 KMAX).  A thread keeps the best of its own candidates, a wave the best of its threads
-// (lane 63, by data-parallel moves) in LDS; a round merges the 16 waves' records in every wave and only the wave that lost its
-// best looks for the next one.  One workgroup, bound by the chain of rounds: 10 of 8192 candidates in 9 us, 32 us with every
-// candidate scanned and shuffled in every round.
+__device__ __forceinline__ double wave_least(double v) {      // in lane 63
+  v = fmin(v, dpp_or_inf<0xb1, 0xf>(v)); v = fmin(v, dpp_or_inf<0x4e, 0xf>(v)); v = fmin(v, dpp_or_inf<0x124, 0xf>(v));
+  v = fmin(v, dpp_or_inf<0x128, 0xf>(v)); v = fmin(v, dpp_or_inf<0x142, 0xa>(v)); v = fmin(v, dpp_or_inf<0x143, 0xc>(v));
+  return v;
+}
+// The same from registers (p <= 1024 KMAX), one workgroup.  The least values of the 16 KMAX groups of 64 candidates are ranked by
+// counting; the (take + 1)-th of them bounds the (take + 1)-th candidate, so the few candidates up to it are listed and ranked
+// by counting as well: a fixed number of barriers whatever `take`.  Lists beyond PICK_CAP (many equal values, fewer groups than
+// picks) are picked one by one: a thread keeps the best of its own candidates, a wave the best of its threads, a round merges the
+// 16 waves' records in every wave and only the wave that lost its best looks for the next one.
+constexpr int PICK_CAP = 128;
 template <int KMAX>
 __global__ __launch_bounds__(1024) void greedy_pick_reg_kernel(TabDims d, const int32_t* __restrict__ kept,
                                                                 const double* __restrict__ score, int take,
                                                                 int32_t* __restrict__ pick, float* __restrict__ gap,
                                                                 const SearchCtrl* __restrict__ ctrl, int side) {
-  __shared__ double w_v[2][16];
-  __shared__ int w_i[2][16];
+  constexpr int NG = 16 * KMAX, PARTS = 1024 / NG;
+  __shared__ double w_v[2][16], g_v[NG], l_v[PICK_CAP], s_bound, s_edge[2];
+  __shared__ int w_i[2][16], g_rank[NG], l_i[PICK_CAP], l_rank[PICK_CAP], s_n;
   if (ctrl->done || ctrl->pause) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double v[KMAX];
@@ -1963,6 +1976,56 @@ __global__ __launch_bounds__(1024) void greedy_pick_reg_kernel(TabDims d, const 
     const int h = tid + 1024 * k;
     v[k] = INFINITY;
     if (h < d.p && ((kept[h] != 0) == (side == 0))) v[k] = side ? -score[h] : score[h];
+  }
+#pragma unroll
+  for (int k = 0; k < KMAX; k++) {
+    const double least = wave_least(v[k]);
+    if (lane == 63) g_v[k * 16 + wave] = least;
+  }
+  if (tid < NG) g_rank[tid] = 0;
+  if (tid < PICK_CAP) l_rank[tid] = 0;
+  if (tid == 0) { s_n = 0; s_bound = INFINITY; s_edge[0] = s_edge[1] = INFINITY; }
+  __syncthreads();
+  {
+    const int e = tid % NG, j0 = tid / NG * (NG / PARTS);
+    const double x = g_v[e];
+    int below = 0;
+#pragma unroll 8
+    for (int j = j0; j < j0 + NG / PARTS; j++) below += g_v[j] < x || (g_v[j] == x && j < e);
+    if (below) atomicAdd(&g_rank[e], below);
+  }
+  __syncthreads();
+  if (tid < NG && g_rank[tid] == take) s_bound = g_v[tid];
+  __syncthreads();
+  const double bound = s_bound;
+#pragma unroll
+  for (int k = 0; k < KMAX; k++)
+    if (v[k] <= bound && v[k] < INFINITY) {
+      const int at = atomicAdd(&s_n, 1);
+      if (at < PICK_CAP) { l_v[at] = v[k]; l_i[at] = tid + 1024 * k; }
+    }
+  __syncthreads();
+  const int n = s_n;
+  if (n <= PICK_CAP) {
+    const int e = tid % PICK_CAP, j0 = tid / PICK_CAP * (PICK_CAP * PICK_CAP / 1024);
+    if (e < n) {
+      const double x = l_v[e];
+      const int xi = l_i[e];
+      int below = 0;
+      for (int j = j0; j < min(n, j0 + PICK_CAP * PICK_CAP / 1024); j++) below += l_v[j] < x || (l_v[j] == x && l_i[j] < xi);
+      if (below) atomicAdd(&l_rank[e], below);
+    }
+    __syncthreads();
+    if (tid < n) {
+      const int r = l_rank[tid];
+      if (r < take) pick[r] = l_i[tid];
+      if (r == take - 1) s_edge[0] = l_v[tid];
+      if (r == take) s_edge[1] = l_v[tid];
+    }
+    if (tid >= n && tid < take) pick[tid] = -1;
+    __syncthreads();
+    if (tid == 0) *gap = n > take ? (float)(fabs(s_edge[1] - s_edge[0]) / fmax(fabs(s_edge[0]), 1e-300)) : INFINITY;
+    return;
   }
   double best = INFINITY, prev = 0.0, edge = 0.0;
   int ib = -1, c = -1;

@@ -217,3 +217,25 @@ def test_gram_in_digits(dtype, n, d1, m, pad):
     bad[11] = bad[d1 - 1] = True
     expect = bad[:, None] | bad[None, :] | torch.eye(d1, dtype=torch.bool, device=DEV)
     assert torch.equal(~torch.isfinite(H2), expect)
+
+
+@pytest.mark.parametrize("p,k,t_hat,equal", [(5, 2, 3, 0), (40, 3, 37, 0), (1000, 900, 7, 0), (1030, 1000, 10, 300), (3000, 2936, 64, 0),
+                                             (8193, 8140, 10, 0), (8193, 8100, 20, 8193)])
+def test_simultaneous_picks(p, k, t_hat, equal):
+    """The cheapest groups of the dense layer, by rank and (many equal costs: more than the list holds) one by one, on both
+    sides of the two register sizes.  H = 1 and G = diag: the cost of removing row i is G_i^2, whatever has been removed before, so the
+    picks are a stable sort (lowest index on ties)."""
+    pkg = _pkg()
+    rng = np.random.default_rng(p + k)
+    cost = rng.permutation(p).astype(np.float64) + 1
+    cost[rng.permutation(p)[:equal]] = 0.5 if equal < p else 7.0
+    s = pkg.Solver(p, 1, p, 1, k, 1, torch.float32, torch.float32, DEV, from_dense=True)
+    H = torch.eye(p, device=DEV)
+    G = torch.from_numpy(np.sqrt(cost)).float().to(DEV).reshape(p, 1)
+    s.osscar_set_quadratic(H, G, float(cost.sum()), np.ones(p))
+    s.osscar_init_greedy(t_hat)
+    kept = set(s.osscar_get_tensor(8).cpu().tolist())
+    s.close()
+    g2 = G.double().cpu().numpy().ravel() ** 2
+    order = np.lexsort((np.arange(p), np.round(g2, 3)))
+    assert kept == set(order[p - k:].tolist())
