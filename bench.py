@@ -23,7 +23,7 @@ import time
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 # HBM-side bytes per launch on cfg5 from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a 1 GiB copy
-# (profiles/gemm_f64acc_cfg5_pmc.md: mean over the launches of one layer; profiles/gram_packed_cfg5_pmc.md: one chunk)
+# (profiles/gemm_f64acc_cfg5_pmc.md: mean over the launches of one layer; profiles/gram_wide_cfg5_pmc.md: one chunk)
 GEMM64_TRAFFIC_CFG5 = 2.99e7
 GRAM_TRAFFIC_CFG5 = 93.9e9
 if ROOT not in sys.path:
@@ -288,7 +288,7 @@ def main():
         # Largest share of the layer time: the bf16 MFMA Gram kernel.  Unit of the roofline: one launch = one chunk of up to 16384
         # calibration rows: algorithmic SYRK flops rows * d1 * (d1 + 1) (the lower block triangle) over the mean duration of the
         # launches of the timed steps, each bracketed by HIP events on the library's stream (timer slot 13).
-        "roofline": {"kernel": "gram_packed_kernel (bf16 MFMA SYRK on the lower block triangle), one launch = one chunk of "
+        "roofline": {"kernel": "gram_wide_kernel (bf16 MFMA SYRK on the lower block triangle), one launch = one chunk of "
                                f"{rows_per_launch} calibration rows",
                      "bound": "mfma", "achieved": gl_flops / (gram_launch_ms * 1e-3) / 1e12 if gram_launch_ms > 0 else None,
                      "peak": 2500.0, "unit": "TFLOP/s",
@@ -328,7 +328,7 @@ def main():
         "roofline_gemm_f32acc": {"kernel": "gemm_f32acc_kernel (float32 MFMA accumulation)", "bound": "mfma", "peak": 157.3, "unit": "TFLOP/s",
                                  "achieved": w32, "frac": (w32 / 157.3) if w32 else None, "launches_per_layer": n32, "ms_per_layer": ms32},
         "state_build": {"candidate_side_products_ms": cand_ms, "inverse_correction_product_ms": gemm32_ms},
-        "roofline_gram_phase": {"kernel": "gram_pack_kernel + gram_packed_kernel, the whole Gram phase (repacking included)",
+        "roofline_gram_phase": {"kernel": "gram_pack_kernel + gram_wide_kernel, the whole Gram phase (repacking included)",
                                 "bound": "mfma", "achieved": gram_flops / phases["gram"] / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
                                 "frac": gram_flops / phases["gram"] / 1e12 / 2500.0,
                                 "note": "algorithmic SYRK flops n*d1*(d1+1); the kernel issues 2x that on diagonal tiles only"},
