@@ -93,43 +93,32 @@ __device__ __forceinline__ void slice16(const float* v, uint4* out) {
   for (int t = 0; t < S; t++) out[t] = uint4{w[t][0], w[t][1], w[t][2], w[t][3]};
 }
 
-// A-side: X is R x K, the contraction runs along a row.  Thread = (packet of 16 k, row), rows fastest.
-__global__ __launch_bounds__(256) void i8_pack_rows_kernel(const float* __restrict__ X, int R, int K, int64_t ld, int vec, int skip_diag,
-                                                            const int* __restrict__ kexp, int ks, const unsigned* __restrict__ mx, uint4* __restrict__ out, int npanels,
+// A-side: X is R x K, the contraction runs along a row.  64 rows x 64 k per workgroup through LDS, so that reads run along the
+// rows at any alignment and writes along the rows of a packet column (5461 x 5461 at odd alignment: 0.48 ms as 16 strided
+// loads per thread).
+__global__ __launch_bounds__(256) void i8_pack_rows_kernel(const float* __restrict__ X, int R, int K, int64_t ld, int skip_diag,
+                                                            const int* __restrict__ kexp, int ks, const unsigned* __restrict__ mx, uint4* __restrict__ out,
                                                             int nstages) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int rpad = npanels * 128;
-  const int kp = (int)(idx / rpad), row = (int)(idx % rpad);
+  __shared__ float T[64][65];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row0 = blockIdx.y * 64, k = blockIdx.x * 64 + lane;
+  const int e = (kexp && k < K) ? ks * kexp[k] : 0;
+#pragma unroll 8
+  for (int i = 0; i < 16; i++) {
+    const int r = wave + 4 * i, row = row0 + r;
+    float v = 0.f;
+    if (row < R && k < K && !(skip_diag && k == row)) {
+      v = X[(int64_t)row * ld + k] * ldexpf(1.f, -expo_of(mx[row]));
+      if (kexp) v = ldexpf(v, e);
+    }
+    T[r][lane] = v;
+  }
+  __syncthreads();
+  const int kp = blockIdx.x * 4 + wave, row = row0 + lane;      // a wave: one packet column of 64 rows
   if (kp >= nstages * 2) return;
   float v[16];
 #pragma unroll
-  for (int j = 0; j < 16; j++) v[j] = 0.f;
-  if (row < R) {
-    const float sc = ldexpf(1.f, -expo_of(mx[row]));
-    const float* p = X + (int64_t)row * ld + kp * 16;
-    if (vec) {            // K % 4 == 0, ld % 4 == 0, X 16-byte aligned: a group of four is inside or outside as a whole
-#pragma unroll
-      for (int j = 0; j < 4; j++)
-        if (kp * 16 + 4 * j < K) {
-          const float4 q = reinterpret_cast<const float4*>(p)[j];
-          v[4 * j] = q.x * sc; v[4 * j + 1] = q.y * sc; v[4 * j + 2] = q.z * sc; v[4 * j + 3] = q.w * sc;
-        }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 16; j++)
-        if (kp * 16 + j < K) v[j] = p[j] * sc;
-    }
-    if (kexp) {
-#pragma unroll
-      for (int j = 0; j < 16; j++)
-        if (kp * 16 + j < K) v[j] = ldexpf(v[j], ks * kexp[kp * 16 + j]);
-    }
-    if (skip_diag && (row >> 4) == kp) {
-#pragma unroll
-      for (int j = 0; j < 16; j++)
-        if (j == (row & 15)) v[j] = 0.f;
-    }
-  }
+  for (int j = 0; j < 16; j++) v[j] = T[lane][wave * 16 + j];
   uint4 pk[S];
   slice16<S>(v, pk);
   const int stage = kp >> 1, kh = kp & 1, panel = row >> 7, r = row & 127;
@@ -375,9 +364,8 @@ hipError_t launch_i8_gemm(const GemmArgs& g, void* packA, size_t capA, void* pac
   hipLaunchKernelGGL(i8_zero_kernel, dim3((g.N + 255) / 256), dim3(256), 0, s, mxb, g.N);
   hipLaunchKernelGGL(i8_absmax_rows_kernel, dim3((g.M + 3) / 4), dim3(256), 0, s, g.A, g.M, g.K, g.lda, g.i8_diag_a, g.i8_kexp, g.i8_ksign, mxa);
   hipLaunchKernelGGL(i8_absmax_cols_kernel, dim3((g.N + 255) / 256, (g.K + 255) / 256), dim3(256), 0, s, g.B, g.K, g.N, g.ldb, g.i8_diag_b, g.i8_kexp, -g.i8_ksign, mxb);
-  const int vec = (g.K % 4 == 0) && (g.lda % 4 == 0) && ((reinterpret_cast<uintptr_t>(g.A) & 15) == 0);
-  hipLaunchKernelGGL(i8_pack_rows_kernel, dim3((unsigned)(((int64_t)nst * 2 * npa * 128 + 255) / 256)), dim3(256), 0, s, g.A, g.M, g.K, g.lda, vec,
-                     g.i8_diag_a, g.i8_kexp, g.i8_ksign, mxa, reinterpret_cast<uint4*>(packA), npa, nst);
+  hipLaunchKernelGGL(i8_pack_rows_kernel, dim3((unsigned)((nst + 1) / 2), (unsigned)(npa * 2)), dim3(256), 0, s, g.A, g.M, g.K, g.lda, g.i8_diag_a, g.i8_kexp,
+                     g.i8_ksign, mxa, reinterpret_cast<uint4*>(packA), nst);
   hipLaunchKernelGGL(i8_pack_cols_kernel, dim3((unsigned)(((int64_t)nst * 2 * npb * 128 + 255) / 256)), dim3(256), 0, s, g.B, g.K, g.N, g.ldb,
                      g.i8_diag_b, g.i8_kexp, -g.i8_ksign, mxb, reinterpret_cast<uint4*>(packB), npb, nst);
   I8Args a{};
