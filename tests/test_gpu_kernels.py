@@ -239,3 +239,20 @@ def test_simultaneous_picks(p, k, t_hat, equal):
     g2 = G.double().cpu().numpy().ravel() ** 2
     order = np.lexsort((np.arange(p), np.round(g2, 3)))
     assert kept == set(order[p - k:].tolist())
+
+
+@pytest.mark.parametrize("dtype,B,C,S", [(torch.float32, 3, 320, 36), (torch.bfloat16, 2, 321, 24)])
+def test_patch_rows_in_digits(dtype, B, C, S):
+    """Wide patch matrices (2880 and 2889 columns) of maps that the packed kernels do not take: the patches are written out as rows
+    and cut into digits behind them, 3888 patches in two pieces.  H is the float32 rounding of the exact sums: 2^-24 + 1e-9."""
+    g = torch.Generator(device=DEV).manual_seed(C)
+    F = torch.randn(B, C, S, S, generator=g, device=DEV).clamp_min(0).to(dtype)
+    W = torch.randn(C * 9, 4, generator=g, device=DEV).to(dtype)
+    s = _pkg().Solver(C * 9, 4, C, 9, C // 2, 1, dtype, dtype, DEV)
+    s.osscar_gram_conv(F, 3, 3, 1, 1, True, W, 0.5, 0.0)
+    H = s.osscar_get_tensor(0).double()
+    s.close()
+    X = torch.nn.functional.unfold(F.double(), 3, padding=1).permute(0, 2, 1).reshape(-1, C * 9).contiguous()
+    Hr = X.T @ X + 0.5 * torch.eye(C * 9, dtype=torch.float64, device=DEV)
+    d = Hr.diagonal().sqrt()
+    assert torch.equal(H, H.T) and ((H - Hr).abs() / d[:, None] / d).max().item() <= 6.1e-8
