@@ -50,7 +50,7 @@ static void build_tile_list(int tiles, std::vector<int2>& out) {
 // reads MFMA operands as single ds_read_b128: 16 neighbouring lanes read 16 neighbouring packets.
 // Accuracy: the MFMA accumulators are added (v_add_f32, round to nearest) to a second float32 register set every
 // `window` stages and restarted from zero, so the accumulation inside the matrix core never spans more than
-// window*64 tokens; the second set is added to the float64 H once per launch.
+// window*64 tokens; the second set is added to the float64 H at the end of every range of the contraction.
 // ------------------------------------------------------------------------------------------------
 constexpr int PK_SLOTS = 8 * 64;    // packets per (panel, stage)
 // first packet of the 8 x 8 block (kg, columns 8 cg ..) of a pair of panels in a stage
@@ -135,8 +135,9 @@ __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __r
 template <int RT, int CT>
 __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (&acc2)[RT][CT], double* __restrict__ H64, int ldo, int row0,
                                          int col0, int rows_out, int cols_out, int symmetric, int lane) {
-  int ldv = ldo;      // opaque: keeps the compiler from computing all the addresses ahead of the main loop
-  asm volatile("" : "+s"(ldv));
+  // opaque: keeps the compiler from computing all the addresses and conditions ahead of the main loop
+  int ldv = ldo;
+  asm volatile("" : "+s"(ldv), "+v"(lane));
   const int rbase = row0 + (lane >> 5) * 4, cbase = col0 + (lane & 31);
   double* hbase = H64 + (int64_t)rbase * ldv + cbase;
   double old[2][4][CT];
@@ -171,7 +172,8 @@ __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (
 // Out (+)= A^T B for packed operands Ap (rows of the result) and Bp (columns of the result); symmetric: Ap == Bp and only
 // tiles on or below the diagonal are listed, the diagonal ones loading one operand.  blockIdx.y: the part of the contraction;
 // part y is added to copy y of Out (copy_stride doubles apart), so that parts that run side by side never meet.  Sums inside
-// the matrix core restart every `window` stages and at every multiple of `range` stages.
+// the matrix core restart every `window` stages, and every `range` stages (a part is a whole number of ranges) the sums go to
+// float64: float32 never spans more than one range.
 __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_packed_kernel(
     const uint4* __restrict__ Ap, const uint4* __restrict__ Bp, int nstages, int rows_out, int cols_out, int ldo,
     double* __restrict__ H64, int64_t copy_stride, const int2* __restrict__ tile_list, int stages_per_split, int window,
@@ -191,13 +193,6 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int wm = wave >> 1, wn = wave & 1;
 
   f16v acc[WT][WT], acc2[WT][WT];
-#pragma unroll
-  for (int a = 0; a < WT; a++)
-#pragma unroll
-    for (int b = 0; b < WT; b++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
-
   const int64_t pstride = (int64_t)nstages * PK_SLOTS;
   const uint4* ga = Ap + 2 * tm * pstride + tid;
   const uint4* gb = Bp + 2 * tn * pstride + tid;
@@ -226,54 +221,60 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   OSSCAR_GLOAD(s_begin);
   OSSCAR_SSTORE(0);
   __syncthreads();
-  int in_window = 0, in_range = 0;
   int buf = 0;
-  for (int st = s_begin; st < s_end; st++) {
-    const bool more = (st + 1 < s_end);
-    if (more) OSSCAR_GLOAD(st + 1);
-    const uint4* pa = lds + (buf * 4 + 0) * PK_SLOTS;
-    const uint4* pb = diag ? pa : lds + (buf * 4 + 2) * PK_SLOTS;
-    __builtin_amdgcn_s_setprio(1);        // the wave that is multiplying goes first; the other wave of the SIMD issues its loads and stores in between
+  for (int r_begin = s_begin; r_begin < s_end; r_begin += range) {
 #pragma unroll
-    for (int ks = 0; ks < GBK / 16; ks++) {
-      const int kgo = (ks * 2 + (lane >> 5)) * 64;
-      bf8 fa[WT], fb[WT];
+    for (int a = 0; a < WT; a++)
 #pragma unroll
-      for (int a = 0; a < WT; a++) {
-        uint4 v = pa[kgo + oa + a * 32];
-        fa[a] = *reinterpret_cast<bf8*>(&v);
+      for (int b = 0; b < WT; b++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
+    const int r_end = min(r_begin + range, s_end);
+    int in_window = 0;
+    for (int st = r_begin; st < r_end; st++) {
+      const bool more = (st + 1 < s_end);
+      if (more) OSSCAR_GLOAD(st + 1);
+      const uint4* pa = lds + (buf * 4 + 0) * PK_SLOTS;
+      const uint4* pb = diag ? pa : lds + (buf * 4 + 2) * PK_SLOTS;
+      __builtin_amdgcn_s_setprio(1);        // the wave that is multiplying goes first; the other wave of the SIMD issues its loads and stores in between
+#pragma unroll
+      for (int ks = 0; ks < GBK / 16; ks++) {
+        const int kgo = (ks * 2 + (lane >> 5)) * 64;
+        bf8 fa[WT], fb[WT];
+#pragma unroll
+        for (int a = 0; a < WT; a++) {
+          uint4 v = pa[kgo + oa + a * 32];
+          fa[a] = *reinterpret_cast<bf8*>(&v);
+        }
+#pragma unroll
+        for (int b = 0; b < WT; b++) {
+          uint4 v = pb[kgo + ob + b * 32];
+          fb[b] = *reinterpret_cast<bf8*>(&v);
+        }
+#pragma unroll
+        for (int a = 0; a < WT; a++)
+#pragma unroll
+          for (int b = 0; b < WT; b++)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
       }
+      __builtin_amdgcn_s_setprio(0);
+      if (++in_window >= window && st + 1 < r_end) {
+        in_window = 0;
 #pragma unroll
-      for (int b = 0; b < WT; b++) {
-        uint4 v = pb[kgo + ob + b * 32];
-        fb[b] = *reinterpret_cast<bf8*>(&v);
+        for (int a = 0; a < WT; a++)
+#pragma unroll
+          for (int b = 0; b < WT; b++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) { acc2[a][b][r] += acc[a][b][r]; acc[a][b][r] = 0.f; }
       }
-#pragma unroll
-      for (int a = 0; a < WT; a++)
-#pragma unroll
-        for (int b = 0; b < WT; b++)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+      if (more) OSSCAR_SSTORE(buf ^ 1);
+      __syncthreads();
+      buf ^= 1;
     }
-    __builtin_amdgcn_s_setprio(0);
-    ++in_range;
-    if ((++in_window >= window || in_range == range) && more) {
-      in_window = 0;
-      if (in_range == range) in_range = 0;
-#pragma unroll
-      for (int a = 0; a < WT; a++)
-#pragma unroll
-        for (int b = 0; b < WT; b++)
-#pragma unroll
-          for (int r = 0; r < 16; r++) { acc2[a][b][r] += acc[a][b][r]; acc[a][b][r] = 0.f; }
-    }
-    if (more) OSSCAR_SSTORE(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
+    add_tile<WT, WT>(acc, acc2, H64, ldo, i0 + wm * 64, j0 + wn * 64, rows_out, cols_out, symmetric, lane);
   }
 #undef OSSCAR_GLOAD
 #undef OSSCAR_SSTORE
-
-  add_tile<WT, WT>(acc, acc2, H64, ldo, i0 + wm * 64, j0 + wn * 64, rows_out, cols_out, symmetric, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -299,44 +300,16 @@ constexpr int GW_R = 256, GW_C = 192, GW_A = 1024, GW_ST = 1024 + 768;      // p
   }
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_wide_kernel(
     const uint4* __restrict__ Ap, int a_panels, const uint4* __restrict__ Bp, int b_panels, int nstages, int rows_out, int cols_out,
-    int ldo, double* __restrict__ H64, const int2* __restrict__ tile_list, int window, int symmetric) {
+    int ldo, double* __restrict__ H64, const int2* __restrict__ tile_list, int window, int range, int symmetric) {
   __shared__ uint4 lb0[GW_ST], lb1[GW_ST], lb2[GW_ST], lb3[GW_ST];
   const int2 tile = tile_list[blockIdx.x];
   if (tile.x < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int nst = nstages * 2;                       // stages of 32 tokens
-  f16v acc[2][3], acc2[2][3];
-#pragma unroll
-  for (int a = 0; a < 2; a++)
-#pragma unroll
-    for (int b = 0; b < 3; b++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
-  // Requests of 64 packets.  Waves 0 - 3: the four kg of one panel of A; waves 4 - 7: one kg of the three panels of B.
-  // Panels past the last one are read from the last one (their results are not written).
-  const bool ld_a = wave < 4;
-  const uint4* gp[4];
-  int ldst, lstep;
-  if (ld_a) {
-    const int p = min(tile.x * 4 + wave, a_panels - 1);
-#pragma unroll
-    for (int i = 0; i < 4; i++) gp[i] = Ap + (int64_t)p * nstages * PK_SLOTS + i * 64 + lane;
-    ldst = wave * 64; lstep = GW_R;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int p = min(tile.y * 3 + (i < 3 ? i : 2), b_panels - 1);
-      gp[i] = Bp + (int64_t)p * nstages * PK_SLOTS + (wave - 4) * 64 + lane;
-    }
-    ldst = GW_A + (wave - 4) * GW_C; lstep = 64;
-  }
-  // in LDS: A as [kg][256 columns], then B as [kg][192 columns]
-  const int oa = (lane >> 5) * GW_R + wm * 64 + (lane & 31), ob = GW_A + (lane >> 5) * GW_C + wn * 96 + (lane & 31);
-  bf8 fa[2][2], fb[2][3];
+  const int nst = nstages * 2;                       // stages of 32 tokens (so are window and range)
 #define OSSCAR_GW_LOAD(st_, buf_)                                                                               \
   {                                                                                                             \
-    _Pragma("unroll") for (int i = 0; i < 4; i++) if (i < NL)                                                   \
+    _Pragma("unroll") for (int i = 0; i < NL; i++)                                                              \
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gp[i] + (int64_t)(st_) * 256), \
                                        (__attribute__((address_space(3))) void*)(buf_ + ldst + i * lstep), 16, 0, 0); \
   }
@@ -359,13 +332,13 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     OSSCAR_GW_MULT(1);                                                                                          \
   }
 #define OSSCAR_GW_TAIL(st_, cur_, nxt_)                                                                         \
-  if ((st_) < nst) {                                                                                            \
+  if ((st_) < end) {                                                                                            \
     OSSCAR_GW_READ(1, cur_, 1);                                                                                 \
     OSSCAR_GW_MULT(0);                                                                                          \
-    if ((st_) + 1 < nst) {                                                                                      \
+    if ((st_) + 1 < end) {                                                                                      \
       OSSCAR_GW_WAIT(0);                                                                                        \
       OSSCAR_GW_BARRIER();                                                                                      \
-      if ((st_) + 4 < nst) OSSCAR_GW_LOAD((st_) + 4, cur_);                                                     \
+      if ((st_) + 4 < end) OSSCAR_GW_LOAD((st_) + 4, cur_);                                                     \
       OSSCAR_GW_READ(0, nxt_, 0);                                                                               \
     }                                                                                                           \
     OSSCAR_GW_MULT(1);                                                                                          \
@@ -376,36 +349,61 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < 3; b++)                 \
       _Pragma("unroll") for (int r = 0; r < 16; r++) { acc2[a][b][r] += acc[a][b][r]; acc[a][b][r] = 0.f; }     \
   }
-  // two copies of the loop: waves with four requests per stage and waves with three (the count of a wait is a constant)
+  // Two copies of the loops.  Requests of 64 packets.  Waves 0 - 3: the four kg of one panel of A, four requests per stage; waves
+  // 4 - 7: one kg of the three panels of B, three requests (the count of a wait is a constant).  Panels past the last one are
+  // read from the last one (their results are not written).
   auto run = [&](auto nl) {
     constexpr int NL = decltype(nl)::value;
-    OSSCAR_GW_LOAD(0, lb0); OSSCAR_GW_LOAD(1, lb1);      // nst is even
-    if (2 < nst) { OSSCAR_GW_LOAD(2, lb2); OSSCAR_GW_LOAD(3, lb3); }
-    if (nst >= 4) OSSCAR_GW_WAIT(3 * NL); else OSSCAR_GW_WAIT(0);
-    OSSCAR_GW_BARRIER();
-    OSSCAR_GW_READ(0, lb0, 0);
-    int in_window = 0, st = 0;
-    if (nst >= 8) {
-      do {
-        OSSCAR_GW_STEADY(st, lb0, lb1); OSSCAR_GW_STEADY(st + 1, lb1, lb2);
-        OSSCAR_GW_STEADY(st + 2, lb2, lb3); OSSCAR_GW_STEADY(st + 3, lb3, lb0);
-        OSSCAR_GW_FOLD();
-        st += 4;
-      } while (st + 8 <= nst);
-    }
-    for (; st < nst; st += 4) {
-      OSSCAR_GW_TAIL(st, lb0, lb1); OSSCAR_GW_TAIL(st + 1, lb1, lb2); OSSCAR_GW_TAIL(st + 2, lb2, lb3); OSSCAR_GW_TAIL(st + 3, lb3, lb0);
-      OSSCAR_GW_FOLD();
+    for (int beg = 0; beg < nst; beg += range) {
+      int lv = lane;      // opaque: the addresses are formed again in every range instead of being held while a tile is added
+      asm volatile("" : "+v"(lv));
+      const uint4* gp[NL];
+#pragma unroll
+      for (int i = 0; i < NL; i++) {
+        if (NL == 4) gp[i] = Ap + (int64_t)min(tile.x * 4 + wave, a_panels - 1) * nstages * PK_SLOTS + i * 64 + lv;
+        else gp[i] = Bp + (int64_t)min(tile.y * 3 + i, b_panels - 1) * nstages * PK_SLOTS + (wave - 4) * 64 + lv;
+      }
+      const int ldst = NL == 4 ? wave * 64 : GW_A + (wave - 4) * GW_C, lstep = NL == 4 ? GW_R : 64;
+      // in LDS: A as [kg][256 columns], then B as [kg][192 columns]
+      const int oa = (lv >> 5) * GW_R + wm * 64 + (lv & 31), ob = GW_A + (lv >> 5) * GW_C + wn * 96 + (lv & 31);
+      const int end = min(beg + range, nst);
+      bf8 fa[2][2], fb[2][3];
+      f16v acc[2][3], acc2[2][3];
+#pragma unroll
+      for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 3; b++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
+      if (beg) OSSCAR_GW_BARRIER();      // the buffers are about to be filled again
+      OSSCAR_GW_LOAD(beg, lb0); OSSCAR_GW_LOAD(beg + 1, lb1);      // a whole number of 64-token stages
+      if (beg + 2 < end) { OSSCAR_GW_LOAD(beg + 2, lb2); OSSCAR_GW_LOAD(beg + 3, lb3); }
+      if (beg + 4 <= end) OSSCAR_GW_WAIT(3 * NL); else OSSCAR_GW_WAIT(0);
+      OSSCAR_GW_BARRIER();
+      OSSCAR_GW_READ(0, lb0, 0);
+      int in_window = 0, st = beg;
+      if (beg + 8 <= end) {
+        do {
+          OSSCAR_GW_STEADY(st, lb0, lb1); OSSCAR_GW_STEADY(st + 1, lb1, lb2);
+          OSSCAR_GW_STEADY(st + 2, lb2, lb3); OSSCAR_GW_STEADY(st + 3, lb3, lb0);
+          OSSCAR_GW_FOLD();
+          st += 4;
+        } while (st + 8 <= end);
+      }
+      for (; st < end; st += 4) {
+        OSSCAR_GW_TAIL(st, lb0, lb1); OSSCAR_GW_TAIL(st + 1, lb1, lb2); OSSCAR_GW_TAIL(st + 2, lb2, lb3); OSSCAR_GW_TAIL(st + 3, lb3, lb0);
+        if (st + 4 < end) OSSCAR_GW_FOLD();      // the last window goes to float64 by itself
+      }
+      add_tile<2, 3>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * GW_C + wn * 96, rows_out, cols_out, symmetric, lane);
     }
   };
-  if (ld_a) run(std::integral_constant<int, 4>{}); else run(std::integral_constant<int, 3>{});
+  if (wave < 4) run(std::integral_constant<int, 4>{}); else run(std::integral_constant<int, 3>{});
 #undef OSSCAR_GW_LOAD
 #undef OSSCAR_GW_READ
 #undef OSSCAR_GW_MULT
 #undef OSSCAR_GW_STEADY
 #undef OSSCAR_GW_TAIL
 #undef OSSCAR_GW_FOLD
-  add_tile<2, 3>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * GW_C + wn * 96, rows_out, cols_out, symmetric, lane);
 }
 
 // Tiles of the wide kernel (blocks of 1024 x 1536).  symmetric: tiles that hold an element on or below the diagonal.
@@ -468,13 +466,15 @@ __global__ void fill_zero_f64_kernel(double* __restrict__ p, int64_t n) {
 }
 
 // Out += A^T B over all stages, one launch.  The contraction falls into ranges, as many as bring 2048 tiles together, of at
-// least 8 stages: sums restart at their ends, because the error of a window grows with its length.
+// least 8 stages: at their ends the sums go to float64, because the error of a float32 sum grows with its length (3000 columns of
+// ReLU rows, 16384 of them: rms 1.4e-8 of sqrt(H_ii H_jj), float32's rounding of H included, against 2.6e-8 joined in float32; the
+// additions cost 0.05 of 0.33 ms, and 0.01 of 0.052 ms at 2048 columns, 2048 rows).
 // From GW_MIN_TILES wide tiles (half of the compute units) and GW_MIN_STAGES stages on: the wide kernel, if its windows of 1024
-// tokens end with the ranges (8192 columns, 2048 rows: 0.19 ms, 0.29 in 128 x 128 tiles; 4096 columns, 16384 rows: 0.30 and 0.52).
+// tokens end with the ranges (8192 columns, 2048 rows: 0.21 ms, 0.35 in 128 x 128 tiles; 4096 columns, 16384 rows: 0.36 and 0.69).
 // Else 128 x 128 tiles, two workgroups per compute unit; when there are too few of them for the chip, the ranges are dealt to
 // up to acc.copies workgroups per tile, each adding to its own copy of Out; the caller adds the copies up in order (2048
-// columns, 2048 rows: 0.034 ms, 0.080 as four launches one after the other).
-// Either way every element of every copy receives one addition per launch, so the result does not depend on scheduling.
+// columns, 2048 rows: 0.052 ms, 0.084 as four launches one after the other).
+// Either way an element of a copy receives its additions from one thread, in order, so the result does not depend on scheduling.
 constexpr size_t GW_MIN_TILES = 128;
 constexpr int GW_MIN_STAGES = 32;
 static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int nstages, int rows_out, int cols_out, const PackedAcc& acc,
@@ -484,7 +484,7 @@ static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int nstages, i
   ranges = (nstages + range - 1) / range;
   if (t.wide && t.wide_entries >= GW_MIN_TILES && nstages >= GW_MIN_STAGES && (ranges == 1 || range % window == 0)) {
     hipLaunchKernelGGL(gram_wide_kernel, dim3((unsigned)t.wide_entries), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
-                       (cols_out + 127) / 128 * 2, nstages, rows_out, cols_out, cols_out, acc.out, t.wide, 2 * window, symmetric);
+                       (cols_out + 127) / 128 * 2, nstages, rows_out, cols_out, cols_out, acc.out, t.wide, 2 * window, 2 * range, symmetric);
     return hipGetLastError();
   }
   const int per = (ranges + acc.copies - 1) / acc.copies * range, parts = (nstages + per - 1) / per;

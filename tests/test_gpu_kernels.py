@@ -256,3 +256,50 @@ def test_patch_rows_in_digits(dtype, B, C, S):
     Hr = X.T @ X + 0.5 * torch.eye(C * 9, dtype=torch.float64, device=DEV)
     d = Hr.diagonal().sqrt()
     assert torch.equal(H, H.T) and ((H - Hr).abs() / d[:, None] / d).max().item() <= 6.1e-8
+
+
+def _range_rows(n, ntiles):
+    """rows of one range of a packed product's contraction: as many ranges as bring 2048 tiles together, of at least 8 stages of 64"""
+    stages = (n + 63) // 64
+    ranges = min(stages, -(-2048 // ntiles)) if ntiles < 1024 else 1
+    return 64 * max(-(-stages // ranges), min(stages, 8))
+
+
+@pytest.mark.parametrize("d1,m,n", [(1024, 512, 4096), (2048, 2048, 16384), (2056, 72, 9000), (4096, 8, 16384)])
+def test_packed_gram_joins_its_ranges_in_float64(d1, m, n):
+    """Three ranges of the contraction contribute 2^25, 1 and -2^25 to an entry: 1 if they meet in float64, 0 in float32.  With
+    one copy of the result per range, with several ranges to a copy, and in wide tiles."""
+    t, tm = (d1 + 127) // 128, (m + 127) // 128
+    for target, tiles in ((False, t * (t + 1) // 2), (True, t * tm)):
+        rows = _range_rows(n, tiles)
+        assert 2 * rows < n
+        X = torch.zeros(n, d1, dtype=torch.bfloat16, device=DEV)
+        Y = torch.zeros(n, m, dtype=torch.bfloat16, device=DEV)
+        X[0, 0::2], X[0, 1::2], Y[0] = 2.0 ** 12, 2.0 ** 13, 2.0 ** 13
+        X[rows], Y[rows] = 1.0, 1.0
+        X[2 * rows, 0::2], X[2 * rows, 1::2], Y[2 * rows] = 2.0 ** 12, -2.0 ** 13, -2.0 ** 13
+        s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, torch.bfloat16, torch.bfloat16, DEV, target_output=True)
+        s.osscar_gram_target(X, Y, True, torch.zeros(d1, m, dtype=torch.bfloat16, device=DEV), 0.0, 0.0)
+        H, G = s.osscar_get_tensor(0), s.osscar_get_tensor(1)
+        s.close()
+        got = G[0::2] if target else H[0::2, 1::2]
+        assert got.min().item() == 1.0 and got.max().item() == 1.0
+
+
+@pytest.mark.parametrize("d1,m", [(2048, 512), (4096, 2048)])
+def test_product_with_bf16_weights_joins_its_ranges_in_float64(d1, m):
+    """G = H W from three bf16 pieces of H: the rows k0, k1, k2 of three ranges contribute 2^25, 1 and -2^25."""
+    rows = _range_rows(d1, (d1 // 128) * (m // 128))
+    k = [0, rows, 2 * rows]
+    assert k[2] < d1
+    X = torch.zeros(64, d1, dtype=torch.bfloat16, device=DEV)
+    X[0], X[1] = 2.0 ** 12, 1.0
+    X[0, k], X[1, k] = torch.tensor([2.0 ** 13, 0, 2.0 ** 13], device=DEV).bfloat16(), torch.tensor([0, 1.0, 0], device=DEV).bfloat16()
+    W = torch.zeros(d1, m, dtype=torch.bfloat16, device=DEV)
+    W[k[0]], W[k[1]], W[k[2]] = 1.0, 1.0, -1.0
+    s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, torch.bfloat16, torch.bfloat16, DEV)
+    s.osscar_gram(X, True, W, 0.0, 0.0)
+    G = s.osscar_get_tensor(1)
+    s.close()
+    G = G[[i for i in range(d1) if i not in k]]
+    assert G.min().item() == 1.0 and G.max().item() == 1.0
