@@ -841,15 +841,10 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
       HIPCHK(c, launch_hw_split(c->H, d1, W, ldw, m, Gacc, c->tiles_g, pack_h, pack_w, prow, s));
       HIPCHK(c, launch_finalize_G(Gacc, Wf, c->scal + 13, c->G, (int64_t)d1 * m, s));
     } else {
-      // Digits on the int8 matrix cores from I8_MIN_DIM on (the packed H in the memory of the accumulator, the packed W in the
-      // staging buffer): 4096 x 4096 x 4096 in 1.1 ms, 2.35 ms with float64 sums; else tiles of 128 x 128 or 64 x 64 with float64 sums.
-      GemmArgs p{};
-      p.M = d1; p.N = m; p.K = d1; p.A = c->H; p.lda = d1; p.B = Wf; p.ldb = m; p.C = c->G; p.ldc = m; p.alpha = 1.0;
-      const size_t h64_bytes = (size_t)d1 * d1 * 8;
-      if (g_i8_products && d1 >= I8_MIN_DIM && m >= I8_MIN_DIM && i8_gemm_fits(p) && i8_pack_bytes(d1, d1) <= h64_bytes &&
-          i8_pack_bytes(m, d1) <= gram_stage_bytes(d1) && (size_t)(d1 + m) * 4 <= c->gemm_ws_size) {
-        HIPCHK(c, launch_i8_gemm(p, H64, h64_bytes, Xt, gram_stage_bytes(d1), reinterpret_cast<unsigned*>(c->gemm_ws), (size_t)(d1 + m), s));
-      } else if (d1 % 4 == 0 && m % 4 == 0 && (int64_t)((d1 + 127) / 128) * ((m + 127) / 128) >= 768) {
+      // Float64 sums.  Not digits on the int8 matrix cores (4096^3 in 1.1 ms against 2.26): they are relative to the largest entry of
+      // a row of H and a column of W, so weights that are small where activations are large (W ~ 1 / scale, eight channels x 100)
+      // put G off by 7e-7 - 1e-5, and a weight of 10^4 times its column costs 3e-6 of |H| |W| even with H levelled.
+      if (d1 % 4 == 0 && m % 4 == 0 && (int64_t)((d1 + 127) / 128) * ((m + 127) / 128) >= 768) {
         HIPCHK(c, gemm(c, d1, m, d1, c->H, d1, Wf, m, nullptr, 0, c->G, m, 1.0, 0.0));      // the size of the 128 x 128 tiles
       } else {
         Gemm64 g{};      // H is symmetric: its rows serve as the columns that the product contracts

@@ -303,3 +303,31 @@ def test_product_with_bf16_weights_joins_its_ranges_in_float64(d1, m):
     s.close()
     G = G[[i for i in range(d1) if i not in k]]
     assert G.min().item() == 1.0 and G.max().item() == 1.0
+
+
+@pytest.mark.parametrize("d1,m,dtype", [(1024, 1024, torch.float32), (1100, 1028, torch.float32), (1031, 1025, torch.float32),
+                                        (1031, 1025, torch.bfloat16), (1536, 1536, torch.bfloat16), (3584, 3520, torch.float32)])
+def test_product_with_weights_small_where_activations_are_large(d1, m, dtype):
+    """G = H W without the bf16 pieces, W inversely proportional to the channels' scales (eight of them 100 times the rest), where
+    every term counts alike, and with one weight per column 10^4 times the others.  Sums are float64, so an entry of G is the
+    float32 rounding of the exact one: 2^-24, and 2^-52 per term of |H| |W|."""
+    g = torch.Generator(device=DEV).manual_seed(d1)
+    rnd = lambda *a: torch.randn(*a, generator=g, device=DEV)
+    scale = torch.exp(rnd(d1))
+    scale[torch.randint(0, d1, (8,), generator=g, device=DEV)] *= 100
+    X = (rnd(2 * d1, d1) * scale).to(dtype)
+    W = (rnd(d1, m) / scale[:, None]).to(dtype)
+    W[torch.randint(0, d1, (m,), generator=g, device=DEV), torch.arange(m, device=DEV)] *= 1e4
+    s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, dtype, dtype, DEV)
+    s.osscar_gram(X, True, W, 0.0, 0.0)
+    H, G = s.osscar_get_tensor(0).double(), s.osscar_get_tensor(1).double()
+    Gr, size = H @ W.double(), H.abs() @ W.double().abs()
+    assert ((G - Gr).abs() <= 2.0 ** -24 * 1.01 * Gr.abs() + d1 * 2.0 ** -52 * size).all()
+    # an infinite weight and a NaN spoil their columns, and only those
+    W[5, 3], W[d1 - 1, m - 1] = float("inf"), float("nan")
+    s.osscar_gram(X, True, W, 0.0, 0.0)
+    G2 = s.osscar_get_tensor(1)
+    s.close()
+    bad = torch.zeros(m, dtype=torch.bool, device=DEV)
+    bad[3] = bad[m - 1] = True
+    assert torch.equal(~torch.isfinite(G2), bad.expand(d1, m)) and torch.equal(G2[:, ~bad].double(), G[:, ~bad])
