@@ -1482,7 +1482,8 @@ __global__ __launch_bounds__(512) void blk_prep_kernel(LazyPtrs L, const float* 
   const bool range = g >= 0 && g < d1;
   const int gc = range ? g : 0;
   const bool bad = !range || !kept[gc] || L.pos[gc] >= 0 || L.cslot[gc] < 0 || tau + t > LAZY_TM;
-  if (__any(bad)) {                                       // the same in every wave
+  if (__any(bad)) {                                       // the same in every wave: none writes before all have read
+    __syncthreads();
     if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; ctrl->pause = 1; }
     return;
   }

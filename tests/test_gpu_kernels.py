@@ -331,3 +331,29 @@ def test_product_with_weights_small_where_activations_are_large(d1, m, dtype):
     bad = torch.zeros(m, dtype=torch.bool, device=DEV)
     bad[3] = bad[m - 1] = True
     assert torch.equal(~torch.isfinite(G2), bad.expand(d1, m)) and torch.equal(G2[:, ~bad].double(), G[:, ~bad])
+
+
+@pytest.mark.parametrize("p,k,t_hat", [(1000, 872, 64), (1000, 800, 40), (2050, 1900, 50)])
+def test_block_removal_stops_at_a_row_that_was_not_looked_ahead(p, k, t_hat):
+    """Of every 1024 rows 32 have their products computed ahead, so an iteration of more than that meets rows without: the block
+    pivot asks for a stop, the host applies what is pending and removes the rest one by one.  Same removals as with the state updated in
+    place after each, and the weights of the float64 inverse (a float32 state after 150 removals, condition number below 20: 1e-5)."""
+    pkg = _pkg()
+    m = 24
+    g = torch.Generator().manual_seed(p + t_hat)
+    A = torch.randn(2 * p, p, generator=g, dtype=torch.float64)
+    H = (A.T @ A / (2 * p) + 0.2 * torch.eye(p, dtype=torch.float64)).float()
+    H = torch.tril(H) + torch.tril(H, -1).T
+    # half of the costs among the first 1024 rows, far below the others'
+    W = torch.randn(p, m, generator=g, dtype=torch.float64) * torch.linspace(0.5, 3.0, p, dtype=torch.float64)[:, None]
+    G = (H.double() @ W).float()
+    s = pkg.Solver(p, m, p, 1, k, 1, torch.float32, torch.float32, DEV, from_dense=True)
+    s.osscar_set_quadratic(H.to(DEV), G.to(DEV), float((W * G.double()).sum()), np.ones(p))
+    _, ahead, _ = s.osscar_init_greedy(t_hat)
+    kept, B = s.osscar_get_tensor(8).cpu().tolist(), s.osscar_get_tensor(3).cpu().double().numpy()
+    _, in_place, _ = s.osscar_init_greedy(t_hat, 0, pkg.OSSCAR_SEARCH_EAGER)
+    s.close()
+    assert ahead == in_place and len(kept) == k and not set(kept) & set(sum(ahead, []))
+    assert max(sum(x < 1024 for x in step) for step in ahead) > 32
+    Br = np.linalg.solve(H.double().numpy()[np.ix_(kept, kept)], G.double().numpy()[kept])
+    assert np.linalg.norm(B - Br) <= 1e-5 * np.linalg.norm(Br)
