@@ -414,7 +414,9 @@ void wide_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& 
 size_t wide_tile_entries(int64_t rows, int64_t cols) { return (size_t)((rows + GW_R - 1) / GW_R * ((cols + GW_C - 1) / GW_C) + 8); }
 
 // Rows r0 .. r0 + nr of the patch matrix as float32 (float32 maps and bf16 maps of other than a multiple of eight columns).
-// Thread = one column of 16 patches, so that writes run along the rows; bound by writing the rows (115 MB in 0.06 ms).
+// Thread = one column of 16 patches, so that writes run along the rows; bound by writing the rows (115 MB in 0.06 ms).  Idx: type
+// of a patch's number, 64 bits wide only if the map has more than 2^31 - 1 patches.
+template <typename Idx>
 __global__ __launch_bounds__(256) void im2col_rows_kernel(const void* __restrict__ F, int is_bf16, ConvSpec cs, int64_t r0, int64_t nr,
                                                            int d1, float* __restrict__ out) {
   const int col = blockIdx.x * 256 + threadIdx.x;
@@ -423,8 +425,8 @@ __global__ __launch_bounds__(256) void im2col_rows_kernel(const void* __restrict
   for (int u = 0; u < 16; u++) {
     const int64_t r = (int64_t)blockIdx.y * 16 + u;
     if (r >= nr) return;
-    const uint32_t pr = (uint32_t)(r0 + r);                       // the same for the whole workgroup
-    const int ox = (int)(pr % (uint32_t)cs.Wout), oy = (int)((pr / (uint32_t)cs.Wout) % (uint32_t)cs.Hout), b = (int)(pr / (uint32_t)(cs.Wout * cs.Hout));
+    const Idx pr = (Idx)(r0 + r), line = pr / (Idx)cs.Wout;        // the same for the whole workgroup
+    const int ox = (int)(pr % (Idx)cs.Wout), oy = (int)(line % (Idx)cs.Hout), b = (int)(line / (Idx)cs.Hout);
     const int y = oy * cs.stride + dy, x = ox * cs.stride + dx;
     float v = 0.f;
     if (y >= 0 && y < cs.Hin && x >= 0 && x < cs.Win) {
@@ -436,8 +438,9 @@ __global__ __launch_bounds__(256) void im2col_rows_kernel(const void* __restrict
 }
 hipError_t launch_im2col_rows(const void* F, int is_bf16, const ConvSpec& cs, int64_t r0, int64_t nr, int d1, float* out, hipStream_t s) {
   if (nr <= 0) return hipSuccess;
-  if (r0 + nr > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(im2col_rows_kernel, dim3((d1 + 255) / 256, (unsigned)((nr + 15) / 16)), dim3(256), 0, s, F, is_bf16, cs, r0, nr, d1, out);
+  const dim3 grid((d1 + 255) / 256, (unsigned)((nr + 15) / 16));
+  if ((int64_t)cs.Hout * cs.Wout <= INT32_MAX / std::max(cs.B, 1)) hipLaunchKernelGGL(im2col_rows_kernel<uint32_t>, grid, dim3(256), 0, s, F, is_bf16, cs, r0, nr, d1, out);
+  else hipLaunchKernelGGL(im2col_rows_kernel<uint64_t>, grid, dim3(256), 0, s, F, is_bf16, cs, r0, nr, d1, out);
   return hipGetLastError();
 }
 

@@ -357,3 +357,19 @@ def test_block_removal_stops_at_a_row_that_was_not_looked_ahead(p, k, t_hat):
     assert max(sum(x < 1024 for x in step) for step in ahead) > 32
     Br = np.linalg.solve(H.double().numpy()[np.ix_(kept, kept)], G.double().numpy()[kept])
     assert np.linalg.norm(B - Br) <= 1e-5 * np.linalg.norm(Br)
+
+
+def test_map_of_more_than_2_to_the_31_patches():
+    """A tall narrow float32 map with wide padding: 33 * (2^26 + 32) patches of two columns, all but 2^26 of them zero.  H is the
+    float32 rounding of the float64 sums, whose 2^26 additions are in order within ranges: 2^-24 + 2^-53 * 2^20."""
+    g = torch.Generator(device=DEV).manual_seed(31)
+    F = torch.randn(1, 2, 1 << 26, 1, generator=g, device=DEV)
+    W = torch.ones(2, 3, device=DEV)
+    s = _pkg().Solver(2, 3, 2, 1, 1, 1, torch.float32, torch.float32, DEV)
+    s.osscar_gram_conv(F, 1, 1, 1, 16, True, W, 0.0, 0.0)
+    H = s.osscar_get_tensor(0).double().cpu()
+    s.close()
+    X = F.reshape(2, -1).double()
+    Hr = torch.tensor([[(X[i] * X[j]).sum().item() for j in range(2)] for i in range(2)], dtype=torch.float64)
+    d = Hr.diagonal().sqrt()
+    assert ((H - Hr).abs() / d[:, None] / d).max().item() <= 6.1e-8
