@@ -373,3 +373,24 @@ def test_map_of_more_than_2_to_the_31_patches():
     Hr = torch.tensor([[(X[i] * X[j]).sum().item() for j in range(2)] for i in range(2)], dtype=torch.float64)
     d = Hr.diagonal().sqrt()
     assert ((H - Hr).abs() / d[:, None] / d).max().item() <= 6.1e-8
+
+
+@pytest.mark.parametrize("q", [2, 17])
+def test_reciprocals_of_pivots_are_rounded_correctly(q):
+    """Groups whose diagonal block is diagonal: the gain of adding one is the sum of its squares over the diagonal, with two nonzero
+    terms a bit-exact chain of one division, product and sum.  An infinite diagonal entry adds nothing."""
+    pkg = _pkg()
+    p, k = 200, 1
+    rng = np.random.default_rng(q)
+    h = np.exp(rng.uniform(-3, 3, (p, q))).astype(np.float32)
+    b = rng.standard_normal((p, q)).astype(np.float32)
+    b[:, 2:] = 0
+    h[7, 0] = np.inf
+    s = pkg.Solver(p * q, 1, p, q, k, 1, torch.float32, torch.float32, DEV)
+    s.osscar_set_quadratic(torch.diag(torch.from_numpy(h.ravel())).to(DEV), torch.from_numpy(b.reshape(-1, 1)).to(DEV), 1e6, np.ones(p))
+    s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, [0])
+    add = s.osscar_get_tensor(7).cpu().numpy()
+    s.close()
+    hd, b2 = h.astype(np.float64), b.astype(np.float64) ** 2
+    ref = (1.0 / hd[:, 0]) * b2[:, 0] + (1.0 / hd[:, 1]) * b2[:, 1]
+    assert np.array_equal(add[1:], ref[1:])
