@@ -16,8 +16,8 @@
  * Conventions for every call
  *   - "dev" pointers are device (HBM) addresses on the current HIP device, "host" pointers are host
  *     addresses.  All matrices are row-major; leading dimensions are in elements.
- *   - The library allocates no device memory.  The caller hands one workspace of at least
- *     osscar_workspace_bytes() bytes (256-byte aligned) to osscar_create and owns it, X, W and What.
+ *   - The library allocates no device memory.  The caller hands one workspace (256-byte aligned), of
+ *     osscar_workspace_bytes() bytes or somewhat less, to osscar_create and owns it, X, W and What.
  *     The context keeps pointers into the workspace only; W is read only during osscar_gram.
  *   - All work is ordered on the stream given to osscar_create.  Calls that return host values
  *     synchronise that stream; osscar_gram without finalize does not (bf16 chunks on the matrix-core path; other chunks
@@ -74,10 +74,14 @@ typedef struct {
   int32_t target_output; /* nonzero: size the workspace for osscar_gram_target too */
 } osscar_desc;
 
-/* Bytes of device workspace osscar_create needs for this description (0 if the description is invalid). */
+/* Bytes of device workspace with which every phase of this description runs at its best (0 if the description is invalid).
+ * Small layers use two to four times what their arrays need (288 x 64 float32: 48 MB against 14.5; 8192 x 2048: 2.06 GB
+ * against 2.02): copies of the float64 accumulators and partial tiles, which let the ranges of a contraction run side by side. */
 size_t osscar_workspace_bytes(const osscar_desc* desc);
 
-/* Creates a context.  workspace_dev: device, >= osscar_workspace_bytes(desc) bytes, 256-byte aligned.
+/* Creates a context.  workspace_dev: device, 256-byte aligned.  With fewer than osscar_workspace_bytes(desc) bytes the context does
+ * without those copies and partial tiles (the same results, sums in another order; small layers are slower); OSSCAR_ENOMEM
+ * if the arrays themselves do not fit.
  * hip_stream: a hipStream_t (NULL = the default stream).  *out receives the context. */
 osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* workspace_dev, size_t workspace_bytes,
                             void* hip_stream);

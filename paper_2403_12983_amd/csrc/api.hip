@@ -48,8 +48,8 @@ size_t split_bytes(size_t a, size_t b, size_t m) {
 }
 size_t gram_tile_entries(int64_t d1) { size_t t = (size_t)(d1 + 127) / 128; return 8 * (t * t / 2 + t + 8); }
 // room for any tile list of the state build: shapes up to d1 x max(d1, m), rectangular or lower triangle
-size_t state_tile_entries(int64_t d1, int64_t m) {
-  return std::max(rect_tile_entries(d1, std::max(d1, m)) + wide_tile_entries(d1, std::max(d1, m)), gram_tile_entries(d1));
+size_t state_tile_entries(int64_t d1, int64_t m, bool extras) {
+  return std::max(rect_tile_entries(d1, std::max(d1, m)) + (extras ? wide_tile_entries(d1, std::max(d1, m)) : 0), gram_tile_entries(d1));
 }
 
 struct Carve {
@@ -106,7 +106,6 @@ struct osscar_ctx {
   float *H, *G, *N, *Z;
   double *norms2, *score, *gram, *dblk, *small, *scal, *partial, *dpart;
   double *cross, *xgram, *xdblk, *xscore;   // exact entering rule
-  double* gpart;                            // column chunks of the groups' Grams
   int32_t *kept, *rowsK, *rowsC, *notpd;
   float *C1, *C2, *Cblk, *rZ1, *rZ2;
   SearchCtrl* ctrl;
@@ -114,8 +113,9 @@ struct osscar_ctx {
   int32_t *g_pick, *g_removed; float* g_gap;   // nested schedule from the dense layer
   int2* tiles;                                 // tile schedules of the bf16 matrix-core products (uploaded once at create)
   PackedTiles tiles_h, tiles_g;                // of a d1 x d1 result (lower triangle) and of a d1 x m one, in `tiles`
+  bool extras = true;                          // the workspace holds what only makes the layer faster (see carve_all)
   int h_copies = 1, g_copies = 1;              // copies of the float64 accumulators that the layer's chunks have used so far
-  double* gemm_ws; size_t gemm_ws_size;        // partial tiles of the 64 x 64 float64 products (this stream only)
+  double* gemm_ws; size_t gemm_ws_size;        // partial tiles of the 64 x 64 float64 products (this stream only; 0: they never cut)
   int2* tiles_state;                           // two schedules of the corrections' products (shapes follow the kept count)
   std::vector<int2> tl_host[2];                // their host copies stay alive while the copies to the device are in flight
   int64_t counters[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -147,16 +147,19 @@ struct Layout {
 };
 
 // Copies of the float64 accumulators of X^T X and X^T Y: float32 activations take another path, with one.
-int h_copies_of(const osscar_desc& ds) {
+int h_copies_of(const osscar_desc& ds, bool extras) {
   const int64_t t = (ds.d1 + 127) / 128;
-  return ds.x_dtype == OSSCAR_BF16 ? packed_copies(ds.d1 * ds.d1, t * (t + 1) / 2) : 1;
+  return extras && ds.x_dtype == OSSCAR_BF16 ? packed_copies(ds.d1 * ds.d1, t * (t + 1) / 2) : 1;
 }
-int g_copies_of(const osscar_desc& ds) {
-  return ds.x_dtype == OSSCAR_BF16 ? packed_copies(ds.d1 * ds.m, (ds.d1 + 127) / 128 * ((ds.m + 127) / 128)) : 1;
+int g_copies_of(const osscar_desc& ds, bool extras) {
+  return extras && ds.x_dtype == OSSCAR_BF16 ? packed_copies(ds.d1 * ds.m, (ds.d1 + 127) / 128 * ((ds.m + 127) / 128)) : 1;
 }
 
-// Carves (or just sizes, when base == nullptr) the workspace for a description.
-Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
+// Carves (or just sizes, when base == nullptr) the workspace for a description.  extras: with the memory that only makes small
+// layers faster - copies of the float64 accumulators, partial tiles of cut contractions, schedules of the wide tiles.
+// It is up to three quarters of a small layer's workspace (14.5 of 47 MB for 288 x 64, nothing to speak of at 28672 x 7168), so a
+// caller with less is served without: the same sums, in 128 x 128 tiles and uncut contractions.
+Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) {
   const int64_t d1 = ds.d1, m = ds.m, p = ds.p, q = ds.q, kr = (int64_t)ds.k * q, cr = d1 - kr;
   const int64_t ms = std::max<int32_t>(ds.max_swaps, 1);
   Carve cv(base);
@@ -173,7 +176,6 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
   double* xgram = cv.take<double>(p * q * q);
   double* xdblk = cv.take<double>(p * q * q);
   double* xscore = cv.take<double>(p);
-  double* gpart = cv.take<double>(group_part_doubles(p, q, m));
   double* scal = cv.take<double>(1024);
   double* partial = cv.take<double>(2048);
   double* dpart = cv.take<double>((m + 15) / 16 + 64);
@@ -195,9 +197,10 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
   int32_t* g_removed = cv.take<int32_t>(p);
   float* g_gap = cv.take<float>(p);
   float* Wdense = cv.take<float>(d1 * m);
-  int2* tiles = cv.take<int2>(gram_tile_entries(d1) + rect_tile_entries(d1, m) + wide_tile_entries(d1, d1) + wide_tile_entries(d1, m));
-  int2* tiles_state = cv.take<int2>(2 * state_tile_entries(d1, m));
-  double* gemm_ws = reinterpret_cast<double*>(cv.take<char>(gemm_ws_bytes(d1, m)));
+  int2* tiles = cv.take<int2>(gram_tile_entries(d1) + rect_tile_entries(d1, m) + (extras ? wide_tile_entries(d1, d1) + wide_tile_entries(d1, m) : 0));
+  int2* tiles_state = cv.take<int2>(2 * state_tile_entries(d1, m, extras));
+  const size_t gemm_ws_size = extras ? gemm_ws_bytes(d1, m) : 0;
+  double* gemm_ws = reinterpret_cast<double*>(cv.take<char>(gemm_ws_size));
   LazyPtrs L{};
   if (q == 1) {
     const int64_t TM = LAZY_TM;
@@ -222,8 +225,8 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
     L.bG = cv.take<int32_t>(LAZY_BT);
   }
   // scratch: the larger of the Gram phase and the init / refresh / backsolve phase
-  size_t gram_phase = align_up((size_t)d1 * d1 * 8 * h_copies_of(ds)) + align_up((size_t)d1 * m * 4) + align_up(gram_stage_bytes(d1));
-  if (ds.target_output) gram_phase += align_up((size_t)d1 * m * 8 * g_copies_of(ds)) + align_up(target_stage_bytes(m));
+  size_t gram_phase = align_up((size_t)d1 * d1 * 8 * h_copies_of(ds, extras)) + align_up((size_t)d1 * m * 4) + align_up(gram_stage_bytes(d1));
+  if (ds.target_output) gram_phase += align_up((size_t)d1 * m * 8 * g_copies_of(ds, extras)) + align_up(target_stage_bytes(m));
   auto init_bytes = [&](size_t a, size_t b) {   // kept rows a, candidate rows b
     return 4 * align_up(a * a * 4) + 3 * align_up(a * b * 4) + align_up(b * b * 4) + 4 * align_up(a * m * 4) + align_up(b * m * 4) +
            align_up(10 * a * INV_NB * 4) + split_bytes(a, b, m) + i8_bytes(a, b, m) + 4096;
@@ -233,17 +236,18 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c) {
     init_phase = std::max(init_phase, init_bytes(d1, 0));
     init_phase = std::max(init_phase, init_bytes(d1 / 2, d1 - d1 / 2));
   }
-  size_t scratch_bytes = std::max(gram_phase, init_phase);
+  // the column chunks of the groups' Grams, formed when nothing else of a phase is needed any more, lie at its start
+  size_t scratch_bytes = std::max({gram_phase, init_phase, group_part_doubles(p, q, m) * 8});
   char* scratch = cv.take<char>(scratch_bytes);
   if (c) {
     c->H = H; c->G = G; c->N = N; c->Z = Z; c->norms2 = norms2; c->score = score; c->gram = gram; c->dblk = dblk;
-    c->cross = cross; c->xgram = xgram; c->xdblk = xdblk; c->xscore = xscore; c->gpart = gpart;
+    c->cross = cross; c->xgram = xgram; c->xdblk = xdblk; c->xscore = xscore;
     c->small = small; c->scal = scal; c->partial = partial; c->dpart = dpart; c->kept = kept; c->rowsK = rowsK; c->rowsC = rowsC;
     c->notpd = notpd; c->C1 = C1; c->C2 = C2; c->Cblk = Cblk; c->rZ1 = rZ1; c->rZ2 = rZ2; c->ctrl = ctrl;
     c->trace_out = trace_out; c->trace_in = trace_in; c->trace_gap = trace_gap; c->trace_obj = trace_obj;
     c->g_pick = g_pick; c->g_removed = g_removed; c->g_gap = g_gap; c->Wdense = Wdense;
     c->tiles = tiles; c->tiles_state = tiles_state;
-    c->gemm_ws = gemm_ws; c->gemm_ws_size = gemm_ws_bytes(d1, m); L.gemm_ws = gemm_ws; L.gemm_ws_bytes = c->gemm_ws_size;
+    c->extras = extras; c->gemm_ws = gemm_ws; c->gemm_ws_size = gemm_ws_size; L.gemm_ws = gemm_ws; L.gemm_ws_bytes = gemm_ws_size;
     c->scratch = scratch; c->scratch_bytes = scratch_bytes; c->lazy = L;
   }
   Layout lay; lay.total = cv.off; lay.scratch_bytes = scratch_bytes;
@@ -280,7 +284,7 @@ TabPtrs ptrs(const osscar_ctx* c) {
   t.N = c->N; t.Z = c->Z; t.kept = c->kept; t.score = c->score; t.gram = c->gram; t.dblk = c->dblk;
   t.C1 = c->C1; t.C2 = c->C2; t.C1D = c->Cblk; t.C2D = c->Cblk + (int64_t)c->d1 * c->q;
   t.rZ1 = c->rZ1; t.rZ2 = c->rZ2; t.small = c->small; t.dpart = c->dpart; t.ctrl = c->ctrl;
-  t.cross = c->cross; t.xgram = c->xgram; t.xdblk = c->xdblk; t.xscore = c->xscore; t.part = c->gpart;
+  t.cross = c->cross; t.xgram = c->xgram; t.xdblk = c->xdblk; t.xscore = c->xscore; t.part = reinterpret_cast<double*>(c->scratch);
   t.trace_out = c->trace_out; t.trace_in = c->trace_in; t.trace_gap = c->trace_gap; t.trace_obj = c->trace_obj;
   return t;
 }
@@ -352,14 +356,14 @@ osscar_status stage_tiles(osscar_ctx* c, int slot, int M, int N, bool lower, Til
   std::vector<int2>& v = c->tl_host[slot];
   std::vector<int2> wide;
   if (lower) gram_tile_list_host(M, v);
-  else { rect_tile_list_host(M, N, v); wide_tile_list_host(M, N, false, wide); }
-  const size_t n = v.size(), cap = state_tile_entries(c->d1, c->m);
+  else { rect_tile_list_host(M, N, v); if (c->extras) wide_tile_list_host(M, N, false, wide); }
+  const size_t n = v.size(), cap = state_tile_entries(c->d1, c->m, c->extras);
   v.insert(v.end(), wide.begin(), wide.end());
   if (v.size() > cap) return fail(c, OSSCAR_ENOMEM, "internal: tile schedule of a %d x %d product exceeds its buffer", M, N);
   int2* dev = c->tiles_state + (size_t)slot * cap;
   HIPCHK(c, hipMemcpyAsync(dev, v.data(), v.size() * sizeof(int2), hipMemcpyHostToDevice, c->stream));
   const int tm = (M + 127) / 128, tn = (N + 127) / 128;
-  out->tiles = PackedTiles{dev, n, lower ? nullptr : dev + n, wide.size()}; out->ntiles = lower ? tm * (tm + 1) / 2 : tm * tn;
+  out->tiles = PackedTiles{dev, n, wide.empty() ? nullptr : dev + n, wide.size()}; out->ntiles = lower ? tm * (tm + 1) / 2 : tm * tn;
   return OSSCAR_OK;
 }
 
@@ -596,7 +600,6 @@ osscar_status build_state(osscar_ctx* c, double* obj_out, const float* B_known =
   }
   HIPCHK(c, launch_scatter(b.P, kr, c->rowsK, kr, c->rowsK, kr, c->N, d1, -1.f, 1, s));
   HIPCHK(c, launch_scatter_rows(b.B, m, c->rowsK, kr, m, c->Z, m, 0, s));
-  HIPCHK(c, launch_refresh_scores(dims(c), ptrs(c), s));
   double obj = 0;
   if (c->have_Wdense && c->dense_is_exact) {
     // obj(K) = c0 - <G_K, B> = <W_c, R_c> over the pruned rows c (B = W_K + V W_c, so <G_K, B> = <G_K, W_K> + <V^T G_K, W_c>).
@@ -611,6 +614,7 @@ osscar_status build_state(osscar_ctx* c, double* obj_out, const float* B_known =
     st = objective_from(c, b.GK, b.B, &obj);     // synchronises the stream
     if (st != OSSCAR_OK) return st;
   }
+  HIPCHK(c, launch_refresh_scores(dims(c), ptrs(c), s));      // last: groups of several rows use the start of the scratch
   if (cr > 0) { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[0][0], c->ev_s[0][1]); c->timers[12] = ms; }
   if (obj_out) *obj_out = obj;
   return OSSCAR_OK;
@@ -641,7 +645,7 @@ extern "C" {
 
 size_t osscar_workspace_bytes(const osscar_desc* desc) {
   if (!desc_ok(desc)) return 0;
-  return carve_all(*desc, nullptr, nullptr).total + 256;
+  return carve_all(*desc, nullptr, nullptr, true).total + 256;
 }
 
 osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* workspace_dev, size_t workspace_bytes,
@@ -650,20 +654,20 @@ osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* wor
   *out = nullptr;
   if (!desc_ok(desc) || !workspace_dev) return OSSCAR_EINVAL;
   if ((reinterpret_cast<uintptr_t>(workspace_dev) & 255) != 0) return OSSCAR_EINVAL;
-  size_t need = carve_all(*desc, nullptr, nullptr).total + 256;
-  if (workspace_bytes < need) return OSSCAR_ENOMEM;
+  const bool extras = workspace_bytes >= carve_all(*desc, nullptr, nullptr, true).total + 256;
+  if (!extras && workspace_bytes < carve_all(*desc, nullptr, nullptr, false).total + 256) return OSSCAR_ENOMEM;
   osscar_ctx* c = new (std::nothrow) osscar_ctx();
   if (!c) return OSSCAR_ENOMEM;
   c->desc = *desc;
   c->stream = reinterpret_cast<hipStream_t>(hip_stream);
   c->d1 = (int)desc->d1; c->m = (int)desc->m; c->p = desc->p; c->q = desc->q; c->k = desc->k;
   c->kr = desc->k * desc->q; c->cr = c->d1 - c->kr;
-  carve_all(*desc, workspace_dev, c);
+  carve_all(*desc, workspace_dev, c, extras);
   {   // tile schedules of the packed matrix-core products: built and uploaded once, so that no chunk call waits for the stream
     std::vector<int2> all, ts, tr, ws, wr;
     gram_tile_list_host(c->d1, ts);
     rect_tile_list_host(c->d1, c->m, tr);
-    if (desc->x_dtype == OSSCAR_BF16 || desc->w_dtype == OSSCAR_BF16) {
+    if (extras && (desc->x_dtype == OSSCAR_BF16 || desc->w_dtype == OSSCAR_BF16)) {
       wide_tile_list_host(c->d1, c->d1, true, ws);
       wide_tile_list_host(c->d1, c->m, false, wr);
     }
@@ -722,12 +726,13 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   hipStream_t s = c->stream;
   const int d1 = c->d1, m = c->m;
   Carve cv(c->scratch);
-  double* H64 = cv.take<double>((int64_t)d1 * d1 * h_copies_of(c->desc));
+  const int h_copies = h_copies_of(c->desc, c->extras), g_copies = g_copies_of(c->desc, c->extras);
+  double* H64 = cv.take<double>((int64_t)d1 * d1 * h_copies);
   float* Wf = cv.take<float>((int64_t)d1 * m);
   void* Xt = cv.take<char>(gram_stage_bytes(d1));
   double* G64 = nullptr; void* Ys = nullptr;
   if (c->desc.target_output) {
-    G64 = cv.take<double>((int64_t)d1 * m * g_copies_of(c->desc));
+    G64 = cv.take<double>((int64_t)d1 * m * g_copies);
     Ys = cv.take<char>(target_stage_bytes(m));
   }
   if (c->phase != osscar_ctx::ACCUM) {   // first chunk of a layer
@@ -748,7 +753,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     if (target) fast = fast && (m % 8 == 0) && (ldy % 8 == 0) && ((reinterpret_cast<uintptr_t>(Yc) & 15) == 0);
     if (target) HIPCHK(c, launch_sumsq(Yc, bf16, n_c, m, ldy, c->scal + 12, c->partial, s));
     if (fast) {
-      const PackedAcc acc_h{H64, h_copies_of(c->desc), &c->h_copies}, acc_g{G64, g_copies_of(c->desc), &c->g_copies};
+      const PackedAcc acc_h{H64, h_copies, &c->h_copies}, acc_g{G64, g_copies, &c->g_copies};
       if (target) HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, acc_h, c->tiles_h, Xt, PACK_ROWS, s, Yc, ldy, m, acc_g, c->tiles_g, Ys));
       else {
         HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, acc_h, c->tiles_h, Xt, PACK_ROWS, s, nullptr, 0, 0, PackedAcc(), PackedTiles(), nullptr, conv,

@@ -394,3 +394,46 @@ def test_reciprocals_of_pivots_are_rounded_correctly(q):
     hd, b2 = h.astype(np.float64), b.astype(np.float64) ** 2
     ref = (1.0 / hd[:, 0]) * b2[:, 0] + (1.0 / hd[:, 1]) * b2[:, 1]
     assert np.array_equal(add[1:], ref[1:])
+
+
+@pytest.mark.parametrize("d1,m,p,q,k,swaps,dtype,dense,target,nbytes", [
+    (288, 64, 32, 9, 16, 50, torch.float32, False, False, 14547200), (576, 64, 64, 9, 32, 50, torch.bfloat16, True, False, 27382016),
+    (1024, 512, 16, 64, 8, 20, torch.bfloat16, False, False, 63750400), (1536, 640, 1536, 1, 768, 60, torch.bfloat16, False, True, 144641536),
+    (3001, 40, 3001, 1, 1499, 60, torch.float32, False, False, 263547392)])
+def test_a_workspace_without_the_extras_serves_the_layer(monkeypatch, d1, m, p, q, k, swaps, dtype, dense, target, nbytes):
+    """A context takes less than osscar_workspace_bytes, down to what the arrays themselves need (the sizes here), and gives the same
+    layer: sums in another order only (float64), so the kept sets are equal and the weights agree to float32 (1e-6 in the
+    2-norm, cond below 100).  Below that it refuses."""
+    pkg = _pkg()
+    g = torch.Generator(device=DEV).manual_seed(d1)
+    n = 3 * d1 + 77
+    X = torch.randn(n, d1, generator=g, device=DEV).clamp_min(0).to(dtype)
+    W = torch.randn(d1, m, generator=g, device=DEV).to(dtype)
+    Y = torch.randn(n, m, generator=g, device=DEV).to(dtype)
+    lib = pkg.load_library()
+
+    def layer():
+        s = pkg.Solver(d1, m, p, q, k, swaps, dtype, dtype, DEV, from_dense=dense, target_output=target)
+        for r0 in range(0, n, 2048):
+            more = (True, W, 0.0, 1e-2) if r0 + 2048 >= n else (False,)
+            if target:
+                s.osscar_gram_target(X[r0:r0 + 2048], Y[r0:r0 + 2048], *more)
+            else:
+                s.osscar_gram(X[r0:r0 + 2048], *more)
+        s.osscar_init_greedy(2) if dense else s.osscar_init_support()
+        s.osscar_local_search(swaps)
+        What, support, obj = s.osscar_backsolve()
+        size = s.workspace_bytes
+        s.close()
+        return What.double(), support.tolist(), obj, size
+
+    full = layer()
+    assert full[3] > nbytes
+    monkeypatch.setattr(lib, "osscar_workspace_bytes", lambda desc: nbytes)
+    less = layer()
+    assert less[1] == full[1] and abs(less[2] - full[2]) <= 1e-6 * abs(full[2])
+    assert (less[0] - full[0]).norm().item() <= 1e-6 * full[0].norm().item()
+    monkeypatch.setattr(lib, "osscar_workspace_bytes", lambda desc: nbytes // 2)
+    with pytest.raises(pkg.OsscarError) as e:
+        layer()
+    assert e.value.status == 2
