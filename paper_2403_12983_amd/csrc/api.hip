@@ -764,11 +764,13 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
       // any alignment and float32.  From 256 tiles of 128 x 128 and 1024 rows on: digits on the int8 matrix cores, as many rows at a
       // time as the staging buffer packs (5461 columns, 32769 rows of bf16: 19.0 ms on the float64 matrix cores, 6.5 ms so; 3001
       // columns, 7777 rows of float32, 300 tiles: 1.63 and 0.75 ms).  With fewer tiles than compute units the digit product leaves
-      // some idle (2304 columns, 12544 rows, 171 tiles: 1.04 and 1.3 ms): float64 sums straight from the caller's rows.  Patches are written out as rows first.
+      // some idle (2304 columns, 12544 rows, 171 tiles: 1.04 and 1.3 ms): float64 sums straight from the caller's rows.  So are the tiles
+      // of columns with rare large values (3001 columns, 7777 rows: 1.3 ms with one such column, 1.55 with all).  Patches are written
+      // out as rows first.
       const size_t esz = bf16 ? 2 : 4;
       const int64_t t128 = (d1 + 127) / 128;
       int64_t most = conv ? (int64_t)(gram_stage_bytes(d1) / ((size_t)d1 * 4)) : GEN_ROWS;
-      bool digits = g_i8_products && t128 * (t128 + 1) / 2 >= 256 && n_c >= I8_MIN_DIM && (size_t)(d1 + m) * 4 <= c->gemm_ws_size;
+      bool digits = g_i8_products && t128 * (t128 + 1) / 2 >= 256 && n_c >= I8_MIN_DIM && i8_gram_word_bytes(d1, m) <= c->gemm_ws_size;
       char* pack_x = reinterpret_cast<char*>(Xt);
       if (digits) {
         const int x16 = bf16 && !conv;
@@ -785,20 +787,19 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
         const int64_t nr = std::min<int64_t>(most, n_c - r0);
         if (conv) HIPCHK(c, launch_im2col_rows(Xc, bf16, *conv, r0, nr, d1, reinterpret_cast<float*>(Xt), s));
         const void* src = conv ? Xt : reinterpret_cast<const char*>(Xc) + (size_t)r0 * ldx * esz;
-        if (digits) {
-          const void* ysrc = target ? reinterpret_cast<const char*>(Yc) + (size_t)r0 * ldy * esz : nullptr;
-          HIPCHK(c, launch_i8_gram(src, bf16 && !conv, conv ? d1 : ldx, d1, ysrc, ldy, m, (int)nr, H64, G64, pack_x, Ys,
-                                   reinterpret_cast<unsigned*>(c->gemm_ws), s));
-          continue;
-        }
+        const void* ysrc = target ? reinterpret_cast<const char*>(Yc) + (size_t)r0 * ldy * esz : nullptr;
+        const int *flag_x = nullptr, *flag_y = nullptr;      // digits: the panels whose tiles are left to the float64 sums
+        if (digits) HIPCHK(c, launch_i8_gram(src, bf16 && !conv, conv ? d1 : ldx, d1, ysrc, ldy, m, (int)nr, H64, G64, pack_x, Ys,
+                                             reinterpret_cast<unsigned*>(c->gemm_ws), &flag_x, &flag_y, s));
         Gemm64 g{};      // H64 += Xc^T Xc
         g.M = d1; g.N = d1; g.K = (int)nr; g.lower = 1; g.A = g.B = src; g.lda = g.ldb = conv ? d1 : ldx;
         g.a_kind = g.b_kind = (bf16 && !conv) ? OPK_K_BF16 : OPK_K_F32;
         g.Cin = H64; g.ldcin = d1; g.C = H64; g.ldc = d1; g.c_is_f64 = 1; g.alpha = 1.0; g.beta = 1.0; g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
+        g.panels_m = g.panels_n = flag_x;
         HIPCHK(c, launch_gemm64(g, s));
         if (target) {      // G64 += Xc^T Yc
           Gemm64 y = g;
-          y.N = m; y.lower = 0; y.B = reinterpret_cast<const char*>(Yc) + (size_t)r0 * ldy * esz; y.ldb = ldy;
+          y.N = m; y.lower = 0; y.B = ysrc; y.ldb = ldy; y.panels_n = flag_y;
           y.Cin = G64; y.ldcin = m; y.C = G64; y.ldc = m;
           HIPCHK(c, launch_gemm64(y, s));
         }

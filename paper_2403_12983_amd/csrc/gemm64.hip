@@ -35,6 +35,7 @@ struct Args64 {
   const void* Cin; int64_t ldcin; void* C; int64_t ldc;
   double alpha, beta, diag_add;
   int c_is_f64, vecA, vecB;
+  const int *panels_m, *panels_n;
 };
 
 __device__ __forceinline__ void tile_of(const Args64& g, int t, int& tm, int& tn) {
@@ -131,6 +132,7 @@ __global__ __launch_bounds__(256) void gemm64_kernel(Args64 g) {
   int tm, tn;
   tile_of(g, t, tm, tn);
   const int m0 = tm * T64, n0 = tn * T64;
+  if (g.panels_m && !(g.panels_m[m0 >> 7] | g.panels_n[n0 >> 7])) return;
   const int kbeg = split * g.kper, kend = min(g.K, kbeg + g.kper);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
   const bool one = g.same && tm == tn;            // a diagonal tile of A^T A: one operand serves as both
@@ -260,7 +262,8 @@ hipError_t launch_gemm64(const Gemm64& q, hipStream_t s) {
   g.vecA = (q.lda % 4 == 0) && ((reinterpret_cast<uintptr_t>(q.A) & 15) == 0);
   g.vecB = (q.ldb % 4 == 0) && ((reinterpret_cast<uintptr_t>(q.B) & 15) == 0);
   const int stages = std::max(1, (q.K + KS - 1) / KS);
-  g.splits = gemm64_splits(g.tiles, q.K, q.ws ? q.ws_bytes : 0);
+  g.panels_m = q.panels_m; g.panels_n = q.panels_n;
+  g.splits = gemm64_splits(g.tiles, q.K, q.ws && !q.panels_m ? q.ws_bytes : 0);
   g.kper = (stages + g.splits - 1) / g.splits * KS;
   g.part = q.ws;
   switch (q.a_kind * 8 + q.b_kind) {

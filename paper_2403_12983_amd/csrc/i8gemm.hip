@@ -174,6 +174,7 @@ struct I8Args {
   double alpha, beta, diag_add;
   const float* A; int64_t lda; const float* B; int64_t ldb; int diag_a, diag_b;      // the operands themselves, for the diagonal terms
   double* C64;      // set: C64[row][col] += A B (leading dimension ldc, lower_only: on and below the diagonal) instead of C
+  const int* skip_a; const int* skip_b;      // with C64: tiles of these row or column panels are left to another kernel
 };
 
 // vmcnt <= N; lgkmcnt = 0, then the barrier: builtins, which the compiler takes into account where it places waits of its own
@@ -218,6 +219,7 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
       if (tm >= g.tiles_m || tn >= g.tiles_n) return;
     }
   }
+  if (g.skip_a && (g.skip_a[tm] | g.skip_b[tn])) return;
   const int nstages = g.nstages;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 2, wn = wave & 3;      // wave tile: 64 rows x 32 columns
   v16i acc[NG][2];
@@ -229,8 +231,8 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
       for (int r = 0; r < 16; r++) acc[q][a][r] = 0;
   const uint4* ga = g.Ap + (int64_t)tm * nstages * BLK;
   const uint4* gb = g.Bp + (int64_t)tn * nstages * BLK;
-  // A stage is the A block followed by the B block, 2 BLK = 2560 packets; instruction i of a wave moves packets
-  // [512 i + 64 wave, + 64) (the boundary 1280 is a multiple of 64: a wave's 64 lie in one block); lane l's 16 bytes
+  // A stage is the A block followed by the B block, 2 BLK packets; instruction i of a wave moves packets
+  // [512 i + 64 wave, + 64) (the boundary BLK is a multiple of 64: a wave's 64 lie in one block); lane l's 16 bytes
   // land at the LDS base + 16 l.
   constexpr int NI = (2 * BLK) / 512;
   static_assert(BLK % 256 == 0, "every wave issues the same number of loads per stage");
@@ -316,12 +318,11 @@ __global__ __launch_bounds__(512, 1) void i8_gemm_kernel(I8Args g) {
     for (int r = 0; r < 16; r++) {
       const int row = tm * 128 + wm * 64 + a * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
       if (row < g.M && col < g.N) {
-        if (g.C64) {      // the same digits, plain sum; a row or column with an infinity or a NaN gives NaN
+        if (g.C64) {      // the same digits, plain sum
           double v = 0.0;
 #pragma unroll
           for (int q = NG - 1; q >= 0; q--) v = v * (1.0 / 128.0) + (double)acc[q][a][r];
           v = ldexp(v, expo_of(g.mxa[row]) + eb - 12);
-          if (g.mxa[row] >= 0x7F800000u || g.mxb[col] >= 0x7F800000u) v = __longlong_as_double(0x7FF8000000000000ll);
           if (!g.lower_only || col <= row) g.C64[(int64_t)row * g.ldc + col] += v;
           continue;
         }
@@ -384,11 +385,16 @@ hipError_t launch_i8_gemm(const GemmArgs& g, void* packA, size_t capA, void* pac
 
 // ------------------------------------------------------------------------------------------------
 // C64 (M x N float64) += X^T Y (Y == nullptr: X^T X, lower triangle) for rows of float32 or bf16 at any alignment: both operands
-// are packed as B-side operands, digits relative to their column's largest value in this call.  float32: five digits, what is
-// dropped is 2^-35 of the column's maximum per value; bf16: four (13 products), and a value within 2^-18 of the maximum is
-// carried whole.  Products of weight 2^-35 and less are dropped, of unequal digits only, whose signs are independent: on the
-// diagonal a dropped square would add up (with the weights below 2^-28 alone, 5e-6 on a column with one value of 400 sigma).
-// So the sum differs from the float64 one by about 1e-9 of sqrt(H_ii H_jj), far below the float32 that H is rounded to.
+// are packed as B-side operands, digits relative to their column's largest value in this call: float32 five digits, so a value is
+// carried to 2^-35 of the maximum; bf16 four (13 products), so a value within 2^-18 of the maximum is carried whole.  Products
+// of digits t + u >= 5 are dropped: unequal digits first, whose signs are independent; dropped squares start at t + u = 6, at most
+// 2^-42 of the maximum's square per row, 2^-28 over 16384 rows.  (With four digits and t + u < 4 alone a diagonal came out 5e-6
+// off.)  All that is relative to the two columns' maxima, while H is of the size of their norms: for 7777 rows
+// of independent normal values the 2-norm of H's error off the diagonal is 2.529e-8 of H, 2.528e-8 with float64 sums (both
+// float32's rounding of H), but 1.3e-7 with one value of 100 sigma in every column.  So a column counts, while it is packed, its
+// nonzero values and the squares of their first digits; if their rms is below 1/16 of the power of two above the maximum (normal
+// values: 1/8 or more; the dropped products grow with the square), or if a value is not finite, its panel of 128 columns is
+// left out here and the caller forms the tiles that it takes part in with float64 sums.
 // ------------------------------------------------------------------------------------------------
 namespace {
 __device__ __forceinline__ float load_as_float(const float* p) { return *p; }
@@ -406,7 +412,7 @@ __global__ __launch_bounds__(256) void i8_absbits_cols_kernel(const T* __restric
 }
 template <int S, typename T>
 __global__ __launch_bounds__(256) void i8_pack_rows_of_x_kernel(const T* __restrict__ X, int K, int N, int64_t ld, const unsigned* __restrict__ mx,
-                                                                 uint4* __restrict__ out, int npanels, int nstages) {
+                                                                 unsigned long long* __restrict__ stat, uint4* __restrict__ out, int npanels, int nstages) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int cpad = npanels * 128;
   const int kp = (int)(idx / cpad), col = (int)(idx % cpad);
@@ -422,31 +428,56 @@ __global__ __launch_bounds__(256) void i8_pack_rows_of_x_kernel(const T* __restr
   }
   uint4 pk[S];
   slice16<S>(v, pk);
+  int nonzero = 0, squares = 0;      // squares of the first digits: 16384 rows of 64^2 fit
+#pragma unroll
+  for (int j = 0; j < 16; j++) nonzero += v[j] != 0.f;
+  squares = __builtin_amdgcn_sdot4((int)pk[0].x, (int)pk[0].x, squares, false);
+  squares = __builtin_amdgcn_sdot4((int)pk[0].y, (int)pk[0].y, squares, false);
+  squares = __builtin_amdgcn_sdot4((int)pk[0].z, (int)pk[0].z, squares, false);
+  squares = __builtin_amdgcn_sdot4((int)pk[0].w, (int)pk[0].w, squares, false);
+  if (nonzero) atomicAdd(&stat[col], ((unsigned long long)nonzero << 32) + (unsigned)squares);
   const int stage = kp >> 1, kh = kp & 1, panel = col >> 7, r = col & 127;
 #pragma unroll
   for (int t = 0; t < S; t++) out[(((int64_t)panel * nstages + stage) * S + t) * 256 + kh * 128 + r] = pk[t];
 }
+// flag[panel] = 1 if a column of the panel holds a value that is not finite or has its values far below its maximum
+__global__ __launch_bounds__(128) void i8_flag_panels_kernel(const unsigned* __restrict__ mx, const unsigned long long* __restrict__ stat, int N,
+                                                              int* __restrict__ flag) {
+  const int col = blockIdx.x * 128 + threadIdx.x;
+  const unsigned long long q = col < N ? stat[col] : 0;
+  const int bad = (col < N && mx[col] >= 0x7F800000u) || (unsigned)q < 16ull * (q >> 32);
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) flag[blockIdx.x] = any != 0;
+}
+struct ColumnWords { unsigned long long* stat; unsigned* mx; int* flag; };
+size_t column_words(int64_t N) { return (size_t)(3 * N + (N + 127) / 128 + 1) / 2 * 2; }
+ColumnWords column_words_at(unsigned* w, int N) { return ColumnWords{reinterpret_cast<unsigned long long*>(w), w + 2 * (size_t)N, reinterpret_cast<int*>(w + 3 * (size_t)N)}; }
 template <int S, typename T>
-void pack_columns(const T* X, int K, int N, int64_t ld, unsigned* mx, uint4* out, hipStream_t s) {
+void pack_columns(const T* X, int K, int N, int64_t ld, const ColumnWords& w, uint4* out, hipStream_t s) {
   const int np = (N + 127) / 128, nst = (K + 31) / 32;
-  hipLaunchKernelGGL(i8_zero_kernel, dim3((N + 255) / 256), dim3(256), 0, s, mx, N);
-  hipLaunchKernelGGL(i8_absbits_cols_kernel<T>, dim3((N + 255) / 256, (K + 127) / 128), dim3(256), 0, s, X, K, N, ld, mx);
-  hipLaunchKernelGGL((i8_pack_rows_of_x_kernel<S, T>), dim3((unsigned)(((int64_t)nst * 2 * np * 128 + 255) / 256)), dim3(256), 0, s, X, K, N, ld, mx, out, np, nst);
+  hipLaunchKernelGGL(i8_zero_kernel, dim3((3 * N + 255) / 256), dim3(256), 0, s, reinterpret_cast<unsigned*>(w.stat), 3 * N);      // stat and mx
+  hipLaunchKernelGGL(i8_absbits_cols_kernel<T>, dim3((N + 255) / 256, (K + 127) / 128), dim3(256), 0, s, X, K, N, ld, w.mx);
+  hipLaunchKernelGGL((i8_pack_rows_of_x_kernel<S, T>), dim3((unsigned)(((int64_t)nst * 2 * np * 128 + 255) / 256)), dim3(256), 0, s, X, K, N, ld, w.mx, w.stat, out, np, nst);
+  hipLaunchKernelGGL(i8_flag_panels_kernel, dim3(np), dim3(128), 0, s, w.mx, w.stat, N, w.flag);
 }
 template <int S, typename T>
 hipError_t i8_gram(const T* X, int64_t ldx, int d1, const T* Y, int64_t ldy, int m, int K, double* H64, double* G64, void* pack_x, void* pack_y,
-                   unsigned* mx, hipStream_t s) {
+                   unsigned* words, const int** flag_x, const int** flag_y, hipStream_t s) {
   uint4 *px = reinterpret_cast<uint4*>(pack_x), *py = reinterpret_cast<uint4*>(pack_y);
-  pack_columns<S>(X, K, d1, ldx, mx, px, s);
+  const ColumnWords wx = column_words_at(words, d1);
+  pack_columns<S>(X, K, d1, ldx, wx, px, s);
   I8Args a{};
-  a.Ap = a.Bp = px; a.nstages = (K + 31) / 32; a.mxa = a.mxb = mx; a.C64 = H64; a.ldc = d1; a.M = a.N = d1;
-  a.tiles_m = a.tiles_n = (d1 + 127) / 128; a.lower_only = 1;
+  a.Ap = a.Bp = px; a.nstages = (K + 31) / 32; a.mxa = a.mxb = wx.mx; a.C64 = H64; a.ldc = d1; a.M = a.N = d1;
+  a.tiles_m = a.tiles_n = (d1 + 127) / 128; a.lower_only = 1; a.skip_a = a.skip_b = wx.flag;
   const int nr = (a.tiles_m + 7) / 8;
   hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nr * (nr + 1) / 2 + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+  *flag_x = wx.flag;
   if (Y) {
-    pack_columns<S>(Y, K, m, ldy, mx + d1, py, s);
-    a.Bp = py; a.mxb = mx + d1; a.C64 = G64; a.ldc = m; a.N = m; a.tiles_n = (m + 127) / 128; a.lower_only = 0;
+    const ColumnWords wy = column_words_at(words + column_words(d1), m);
+    pack_columns<S>(Y, K, m, ldy, wy, py, s);
+    a.Bp = py; a.mxb = wy.mx; a.C64 = G64; a.ldc = m; a.N = m; a.tiles_n = (m + 127) / 128; a.lower_only = 0; a.skip_b = wy.flag;
     hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nr * ((a.tiles_n + 7) / 8) + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+    *flag_y = wy.flag;
   }
   return hipGetLastError();
 }
@@ -456,12 +487,13 @@ int64_t i8_gram_rows(size_t bytes, int x_bf16, int64_t cols) {
   const int64_t per_stage = (int64_t)(x_bf16 ? I8_S_BF16 : I8_S) * 256 * 16 * ((cols + 127) / 128);
   return std::min<int64_t>(16384, (int64_t)bytes / per_stage * 32);
 }
+size_t i8_gram_word_bytes(int64_t d1, int64_t m) { return (column_words(d1) + column_words(m)) * 4; }
 hipError_t launch_i8_gram(const void* X, int x_bf16, int64_t ldx, int d1, const void* Y, int64_t ldy, int m, int K, double* H64, double* G64,
-                          void* pack_x, void* pack_y, unsigned* mx, hipStream_t s) {
-  if (K <= 0) return hipSuccess;
-  if (K > 16384 || (reinterpret_cast<uintptr_t>(pack_x) & 15) || (Y && (reinterpret_cast<uintptr_t>(pack_y) & 15))) return hipErrorInvalidValue;
-  if (x_bf16) return i8_gram<I8_S_BF16>(reinterpret_cast<const uint16_t*>(X), ldx, d1, reinterpret_cast<const uint16_t*>(Y), ldy, m, K, H64, G64, pack_x, pack_y, mx, s);
-  return i8_gram<I8_S>(reinterpret_cast<const float*>(X), ldx, d1, reinterpret_cast<const float*>(Y), ldy, m, K, H64, G64, pack_x, pack_y, mx, s);
+                          void* pack_x, void* pack_y, unsigned* words, const int** flag_x, const int** flag_y, hipStream_t s) {
+  if (K <= 0) return hipErrorInvalidValue;
+  if (K > 16384 || (reinterpret_cast<uintptr_t>(pack_x) & 15) || (Y && (reinterpret_cast<uintptr_t>(pack_y) & 15)) || (reinterpret_cast<uintptr_t>(words) & 7)) return hipErrorInvalidValue;
+  if (x_bf16) return i8_gram<I8_S_BF16>(reinterpret_cast<const uint16_t*>(X), ldx, d1, reinterpret_cast<const uint16_t*>(Y), ldy, m, K, H64, G64, pack_x, pack_y, words, flag_x, flag_y, s);
+  return i8_gram<I8_S>(reinterpret_cast<const float*>(X), ldx, d1, reinterpret_cast<const float*>(Y), ldy, m, K, H64, G64, pack_x, pack_y, words, flag_x, flag_y, s);
 }
 
 }  // namespace osscar

@@ -54,6 +54,7 @@ struct Gemm64 {
   const void* Cin; int64_t ldcin; void* C; int64_t ldc; int c_is_f64;
   double alpha, beta, diag_add;
   double* ws; size_t ws_bytes;                // partial tiles of a cut contraction (none: never cut)
+  const int *panels_m, *panels_n;             // set (never cut then): only the tiles in a marked panel of 128 rows or columns
 };
 constexpr size_t GEMM64_TILE_BYTES = 64 * 64 * 8;
 hipError_t launch_gemm64(const Gemm64& q, hipStream_t s);
@@ -65,11 +66,13 @@ hipError_t launch_gemm64(const Gemm64& q, hipStream_t s);
 constexpr int I8_S = 5, I8_S_BF16 = 4;
 size_t i8_pack_bytes(int64_t rows, int64_t K);          // packed size of an operand with `rows` rows (A) or columns (B)
 bool i8_gemm_fits(const GemmArgs& g);
-// H64 += X^T X (lower triangle) and, with Y, G64 += X^T Y for K <= 16384 rows of float32 or bf16 at any alignment; pack_x / pack_y
-// hold i8_gram_rows(bytes, ...) >= K rows, mx: d1 + m words
+// H64 += X^T X (lower triangle) and, with Y, G64 += X^T Y for K <= 16384 rows of float32 or bf16 at any alignment, except the tiles
+// of the 128-column panels that *flag_x / *flag_y mark (device, in `words`): those the caller adds.  pack_x / pack_y
+// hold i8_gram_rows(bytes, ...) >= K rows, words: i8_gram_word_bytes, 8-byte aligned
 int64_t i8_gram_rows(size_t bytes, int x_bf16, int64_t cols);
+size_t i8_gram_word_bytes(int64_t d1, int64_t m);
 hipError_t launch_i8_gram(const void* X, int x_bf16, int64_t ldx, int d1, const void* Y, int64_t ldy, int m, int K, double* H64, double* G64,
-                          void* pack_x, void* pack_y, unsigned* mx, hipStream_t s);
+                          void* pack_x, void* pack_y, unsigned* words, const int** flag_x, const int** flag_y, hipStream_t s);
 // kexp[k] = round(log2 sqrt(D_kk)) from the diagonal of a Gram block (device, n ints)
 hipError_t launch_i8_kexp(const float* D, int n, int64_t ld, int* kexp, hipStream_t s);
 // packA / packB: scratch for the two packed operands (capacities in bytes), mx: M + N words for the scaling exponents

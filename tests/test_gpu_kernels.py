@@ -437,3 +437,29 @@ def test_a_workspace_without_the_extras_serves_the_layer(monkeypatch, d1, m, p, 
     with pytest.raises(pkg.OsscarError) as e:
         layer()
     assert e.value.status == 2
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,d1,m,where", [(1500, 2901, 130, None), (9001, 2817, 70, None), (2500, 2945, 257, (128, 256)), (1100, 2883, 5, (2816, 2883))])
+def test_gram_of_columns_with_rare_large_values(dtype, n, d1, m, where):
+    """One value of 300 sigma in every column, or in those of one panel of 128 (a full one and the last): digits relative to it would leave
+    the column's other products with too few bits, so the tiles of such panels are float64 sums: the float32 rounding of the
+    exact entry, 2^-24, and 2^-53 per term.  The other tiles are digits: 2^-24 + 1e-9 of sqrt(H_ii H_jj)."""
+    g = torch.Generator(device=DEV).manual_seed(n + d1)
+    X = torch.randn(n, d1 + 1, generator=g, device=DEV)
+    lo, hi = where or (0, d1)
+    X[torch.randint(0, n, (hi - lo,), generator=g, device=DEV), torch.arange(lo, hi, device=DEV)] = 300.0
+    X, Y = X.to(dtype)[:, :d1], torch.randn(n, m, generator=g, device=DEV).to(dtype)
+    W = torch.zeros(d1, m, dtype=dtype, device=DEV)
+    s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, dtype, dtype, DEV, target_output=True)
+    s.osscar_gram_target(X, Y, True, W, 0.0, 0.0)
+    H, G = s.osscar_get_tensor(0).double(), s.osscar_get_tensor(1).double()
+    s.close()
+    Xd, Yd = X.double(), Y.double()
+    exact = torch.zeros(d1, dtype=torch.bool, device=DEV)
+    exact[lo:hi] = True
+    for got, A, B, ex in ((H, Xd, Xd, exact[:, None] | exact), (G, Xd, Yd, exact[:, None].expand(d1, m))):
+        ref, size = A.T @ B, A.abs().T @ B.abs()
+        norm = A.square().sum(0).sqrt()[:, None] * B.square().sum(0).sqrt()
+        assert ((got - ref).abs() <= 2.0 ** -24 * 1.01 * ref.abs() + n * 2.0 ** -53 * size)[ex].all()
+        assert ((got - ref).abs() <= 6.1e-8 * norm).all()
