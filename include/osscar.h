@@ -250,7 +250,8 @@ osscar_status osscar_get_counters(osscar_ctx* ctx, int64_t* out_host);
  * osscar_debug_gemm_log(1) clears the log and starts recording: every launch is bracketed by two events on its stream.
  * osscar_debug_gemm_log(0) stops and clears.  osscar_debug_gemm_log_read waits for the recorded launches and writes up to
  * `capacity` rows of five float64 {M, N, K, kind, milliseconds} (kind: 1 = float32 accumulation, + 2 = float64 output,
- * + 4 = lower-triangle tiles only, + 8 = second operand transposed, 16 = int8-digit product, packing included) to out_host; returns the number of rows, -1 on a bad
+ * + 4 = lower-triangle tiles only, + 8 = second operand transposed, 16 = int8-digit product, packing included; a Gram
+ * product X^T X is a lower triangle with the second operand transposed) to out_host; returns the number of rows, -1 on a bad
  * argument.  At most 16384 launches are kept. */
 osscar_status osscar_debug_gemm_log(int32_t enable);
 int32_t osscar_debug_gemm_log_read(double* out_host, int32_t capacity);

@@ -796,12 +796,12 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
         g.a_kind = g.b_kind = (bf16 && !conv) ? OPK_K_BF16 : OPK_K_F32;
         g.Cin = H64; g.ldcin = d1; g.C = H64; g.ldc = d1; g.c_is_f64 = 1; g.alpha = 1.0; g.beta = 1.0; g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
         g.panels_m = g.panels_n = flag_x;
-        HIPCHK(c, launch_gemm64(g, s));
+        HIPCHK(c, digits ? launch_gemm64(g, s) : launch_gemm64_logged(g, s));      // (in the log: the digit product)
         if (target) {      // G64 += Xc^T Yc
           Gemm64 y = g;
           y.N = m; y.lower = 0; y.B = ysrc; y.ldb = ldy; y.panels_n = flag_y;
           y.Cin = G64; y.ldcin = m; y.C = G64; y.ldc = m;
-          HIPCHK(c, launch_gemm64(y, s));
+          HIPCHK(c, digits ? launch_gemm64(y, s) : launch_gemm64_logged(y, s));
         }
       }
     }
@@ -856,7 +856,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
         Gemm64 g{};      // H is symmetric: its rows serve as the columns that the product contracts
         g.M = d1; g.N = m; g.K = d1; g.a_kind = OPK_K_F32; g.A = c->H; g.lda = d1; g.b_kind = OPK_K_F32; g.B = Wf; g.ldb = m;
         g.C = c->G; g.ldc = m; g.alpha = 1.0; g.ws = c->gemm_ws; g.ws_bytes = c->gemm_ws_size;
-        HIPCHK(c, launch_gemm64(g, s));
+        HIPCHK(c, launch_gemm64_logged(g, s));
       }
     }
     HIPCHK(c, hipEventRecord(c->ev_s[0][1], s));

@@ -278,4 +278,12 @@ hipError_t launch_gemm64(const Gemm64& q, hipStream_t s) {
   return hipGetLastError();
 }
 
+hipError_t launch_gemm64_logged(const Gemm64& q, hipStream_t s) {
+  int slot = -1;
+  gemm_log_open(q.M, q.N, q.K, (q.c_is_f64 ? 2 : 0) | (q.lower ? 4 : 0) | (q.lower && q.A == q.B ? 8 : 0), s, &slot);
+  const hipError_t e = launch_gemm64(q, s);
+  gemm_log_close(slot, s);
+  return e;
+}
+
 }  // namespace osscar

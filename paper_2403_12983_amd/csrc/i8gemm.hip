@@ -465,18 +465,23 @@ hipError_t i8_gram(const T* X, int64_t ldx, int d1, const T* Y, int64_t ldy, int
                    unsigned* words, const int** flag_x, const int** flag_y, hipStream_t s) {
   uint4 *px = reinterpret_cast<uint4*>(pack_x), *py = reinterpret_cast<uint4*>(pack_y);
   const ColumnWords wx = column_words_at(words, d1);
+  int log_slot = -1;
+  gemm_log_open(d1, d1, K, 16 | 2 | 4 | 8, s, &log_slot);
   pack_columns<S>(X, K, d1, ldx, wx, px, s);
   I8Args a{};
   a.Ap = a.Bp = px; a.nstages = (K + 31) / 32; a.mxa = a.mxb = wx.mx; a.C64 = H64; a.ldc = d1; a.M = a.N = d1;
   a.tiles_m = a.tiles_n = (d1 + 127) / 128; a.lower_only = 1; a.skip_a = a.skip_b = wx.flag;
   const int nr = (a.tiles_m + 7) / 8;
   hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nr * (nr + 1) / 2 + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+  gemm_log_close(log_slot, s);
   *flag_x = wx.flag;
   if (Y) {
+    gemm_log_open(d1, m, K, 16 | 2, s, &log_slot);
     const ColumnWords wy = column_words_at(words + column_words(d1), m);
     pack_columns<S>(Y, K, m, ldy, wy, py, s);
     a.Bp = py; a.mxb = wy.mx; a.C64 = G64; a.ldc = m; a.N = m; a.tiles_n = (m + 127) / 128; a.lower_only = 0; a.skip_b = wy.flag;
     hipLaunchKernelGGL(i8_gemm_kernel<S>, dim3((unsigned)((nr * ((a.tiles_n + 7) / 8) + 7) / 8 * 8 * 64)), dim3(512), 0, s, a);
+    gemm_log_close(log_slot, s);
     *flag_y = wy.flag;
   }
   return hipGetLastError();

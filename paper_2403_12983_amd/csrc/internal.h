@@ -58,6 +58,7 @@ struct Gemm64 {
 };
 constexpr size_t GEMM64_TILE_BYTES = 64 * 64 * 8;
 hipError_t launch_gemm64(const Gemm64& q, hipStream_t s);
+hipError_t launch_gemm64_logged(const Gemm64& q, hipStream_t s);      // with an entry in the log above: for callers outside gemm.hip
 
 // ----------------------------------------------------------------------------------------------
 // i8gemm.hip : the same product C = alpha A B + beta Cin (+ diag_add on the diagonal; lower_only) for float32 A, B, Cin, C

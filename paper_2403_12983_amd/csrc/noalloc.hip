@@ -90,7 +90,7 @@ extern "C" osscar_status osscar_gram_static(const void* X_dev, int64_t n, int64_
     g.M = D; g.N = D; g.K = (int)std::min<int64_t>(ST_ROWS, n - r0); g.lower = 1;
     g.A = g.B = reinterpret_cast<const char*>(X_dev) + (size_t)r0 * ldx * esz; g.lda = g.ldb = ldx; g.a_kind = g.b_kind = xbf ? OPK_K_BF16 : OPK_K_F32;
     g.Cin = r0 ? H64 : nullptr; g.ldcin = D; g.C = H64; g.ldc = D; g.c_is_f64 = 1; g.alpha = 1.0; g.beta = 1.0; g.ws = part; g.ws_bytes = ST_PART;
-    e = launch_gemm64(g, s);
+    e = launch_gemm64_logged(g, s);
   }
   if (e == hipSuccess) e = launch_trace64(H64, D, scal, s);
   if (e == hipSuccess) {
@@ -102,7 +102,7 @@ extern "C" osscar_status osscar_gram_static(const void* X_dev, int64_t n, int64_
     Gemm64 g{};      // G = H W (H is symmetric: its rows serve as the columns that the product contracts)
     g.M = D; g.N = M; g.K = D; g.A = H_dev; g.lda = D; g.a_kind = OPK_K_F32; g.B = Wf; g.ldb = M; g.b_kind = OPK_K_F32; g.C = G_dev; g.ldc = M;
     g.alpha = 1.0; g.ws = part; g.ws_bytes = ST_PART;
-    e = launch_gemm64(g, s);
+    e = launch_gemm64_logged(g, s);
   }
   if (e == hipSuccess) e = launch_dot64(Wf, G_dev, d1 * m, scal + 2, partial, s);      // c0 = Tr(W^T G)
   if (e == hipSuccess) {

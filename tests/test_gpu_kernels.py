@@ -463,3 +463,35 @@ def test_gram_of_columns_with_rare_large_values(dtype, n, d1, m, where):
         norm = A.square().sum(0).sqrt()[:, None] * B.square().sum(0).sqrt()
         assert ((got - ref).abs() <= 2.0 ** -24 * 1.01 * ref.abs() + n * 2.0 ** -53 * size)[ex].all()
         assert ((got - ref).abs() <= 6.1e-8 * norm).all()
+
+
+@pytest.mark.parametrize("n,d1,m,kind", [(3000, 130, 20, 14), (3000, 2881, 20, 30)])
+def test_the_log_holds_the_products_of_the_gram_phase(n, d1, m, kind):
+    """X^T X (float64 sums, and in digits for wide layers: 16 more), X^T Y and G = H W of float32 rows, and the allocation-free call's."""
+    from paper_2403_12983_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(d1)
+    X, W = torch.randn(n, d1, generator=g, device=DEV), torch.randn(d1, m, generator=g, device=DEV)
+    s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, torch.float32, torch.float32, DEV, target_output=True)
+    B.gemm_log(True)
+    try:
+        s.osscar_gram(X, True, W, 0.0, 1e-2)
+        one = B.gemm_log_read()
+        B.gemm_log(True)
+        s.osscar_gram_target(X, X[:, :m].contiguous(), True, W, 0.0, 1e-2)
+        two = B.gemm_log_read()
+        B.gemm_log(True)
+        if d1 <= 1024:
+            _pkg().osscar_gram_static(X, W, torch.empty(d1, d1, device=DEV), torch.empty(d1, m, device=DEV),
+                                      torch.empty(2, dtype=torch.float64, device=DEV))
+        static = B.gemm_log_read()
+    finally:
+        B.gemm_log(False)
+        s.close()
+    def rows_of(log, M, N, k):
+        """contraction lengths of the products of this shape and kind, durations positive"""
+        assert (log[:, 4] > 0).all()
+        return log[(log[:, 0] == M) & (log[:, 1] == N) & (log[:, 3] == k)][:, 2].sum()
+    assert rows_of(one, d1, d1, kind) == n and rows_of(one, d1, m, 0) == d1
+    assert rows_of(two, d1, d1, kind) == n and rows_of(two, d1, m, 2 + (kind & 16)) == n
+    if d1 <= 1024:
+        assert rows_of(static, d1, d1, 14) == n and rows_of(static, d1, m, 0) == d1
