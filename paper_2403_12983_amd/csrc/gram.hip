@@ -130,11 +130,12 @@ __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __r
 
 // H64 += acc + acc2 for a wave's RT x CT MFMA tiles at (row0, col0); symmetric: on and below the diagonal only.  C layout of the
 // 32 x 32 MFMA: register r = rr*4 + r3 holds row rr*8 + (lane/32)*4 + r3, column lane%32.  A workgroup is the only one that
-// touches its tile in a launch, so these are plain loads and stores, a batch of 4 CT loads ahead of the batch that is stored:
-// float64 atomic adds cost 0.12 ms more on 8192 columns (0.305 against 0.251 ms for 2048 rows, 0.19 without reading H64).
+// touches its tile in a launch, so these are plain loads and stores, a batch of 4 CT loads ahead of the batch that is stored
+// (or, atomics, additions that the few workgroups of a small launch do not wait for):
+// with atomics throughout 8192 columns, 2048 rows took 0.305 ms, 0.251 so, 0.19 without reading H64.
 template <int RT, int CT>
 __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (&acc2)[RT][CT], double* __restrict__ H64, int ldo, int row0,
-                                         int col0, int rows_out, int cols_out, int symmetric, int lane) {
+                                         int col0, int rows_out, int cols_out, int symmetric, int lane, int atomics = 0) {
   // opaque: keeps the compiler from computing all the addresses and conditions ahead of the main loop
   int ldv = ldo;
   asm volatile("" : "+s"(ldv), "+v"(lane));
@@ -145,6 +146,18 @@ __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (
     const int row = rbase + ro, col = cbase + b * 32;
     return row < rows_out && col < cols_out && (!symmetric || col <= row);
   };
+  if (atomics) {
+#pragma unroll
+    for (int batch = 0; batch < RT * 4; batch++)
+#pragma unroll
+      for (int r3 = 0; r3 < 4; r3++)
+#pragma unroll
+        for (int b = 0; b < CT; b++) {
+          const int a = batch >> 2, r = (batch & 3) * 4 + r3, ro = a * 32 + (batch & 3) * 8 + r3;
+          if (inside(ro, b)) unsafeAtomicAdd(hbase + (int64_t)ro * ldv + b * 32, (double)acc[a][b][r] + (double)acc2[a][b][r]);
+        }
+    return;
+  }
   auto load = [&](int batch) {
 #pragma unroll
     for (int r3 = 0; r3 < 4; r3++)
@@ -177,7 +190,7 @@ __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (
 __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_packed_kernel(
     const uint4* __restrict__ Ap, const uint4* __restrict__ Bp, int nstages, int rows_out, int cols_out, int ldo,
     double* __restrict__ H64, int64_t copy_stride, const int2* __restrict__ tile_list, int stages_per_split, int window,
-    int range, int symmetric) {
+    int range, int symmetric, int atomics) {
   constexpr int WT = 2, TS = 128;
   extern __shared__ uint4 lds[];             // [2 buffers][2 operands][2 panels][PK_SLOTS]
   const int2 tile = tile_list[blockIdx.x];
@@ -271,7 +284,7 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
       __syncthreads();
       buf ^= 1;
     }
-    add_tile<WT, WT>(acc, acc2, H64, ldo, i0 + wm * 64, j0 + wn * 64, rows_out, cols_out, symmetric, lane);
+    add_tile<WT, WT>(acc, acc2, H64, ldo, i0 + wm * 64, j0 + wn * 64, rows_out, cols_out, symmetric, lane, atomics);
   }
 #undef OSSCAR_GLOAD
 #undef OSSCAR_SSTORE
@@ -480,6 +493,10 @@ __global__ void fill_zero_f64_kernel(double* __restrict__ p, int64_t n) {
 // Either way an element of a copy receives its additions from one thread, in order, so the result does not depend on scheduling.
 constexpr size_t GW_MIN_TILES = 128;
 constexpr int GW_MIN_STAGES = 32;
+// A launch of the 128 x 128 kernel with fewer workgroups than this adds with atomics, which nobody waits for: 64 columns, 64 rows 7.7 us
+// against 11.3 with loads and stores, 1000 columns, 512 rows (36 workgroups) 13.7 and 18.7; 1000 columns, 2048 rows (144) 27.9 both;
+// 2048 columns, 2048 rows (272) 67.6 and 51.3.  Either way one thread adds to an element, in order.
+constexpr int64_t PLAIN_FROM = 128;
 static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int nstages, int rows_out, int cols_out, const PackedAcc& acc,
                                 const PackedTiles& t, int ntiles, int window, int symmetric, hipStream_t s) {
   int ranges = ntiles < 1024 ? std::min(nstages, (2048 + ntiles - 1) / ntiles) : 1;
@@ -497,7 +514,7 @@ static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int nstages, i
     *acc.cleared = parts;
   }
   hipLaunchKernelGGL(gram_packed_kernel, dim3((unsigned)t.entries, (unsigned)parts), dim3(256), (size_t)2 * 4 * PK_SLOTS * 16, s, Ap, Bp, nstages,
-                     rows_out, cols_out, cols_out, acc.out, elems, t.list, per, window, range, symmetric);
+                     rows_out, cols_out, cols_out, acc.out, elems, t.list, per, window, range, symmetric, (int64_t)ntiles * parts < PLAIN_FROM);
   return hipGetLastError();
 }
 

@@ -495,3 +495,24 @@ def test_the_log_holds_the_products_of_the_gram_phase(n, d1, m, kind):
     assert rows_of(two, d1, d1, kind) == n and rows_of(two, d1, m, 2 + (kind & 16)) == n
     if d1 <= 1024:
         assert rows_of(static, d1, d1, 14) == n and rows_of(static, d1, m, 0) == d1
+
+
+@pytest.mark.parametrize("d1,n", [(64, 64), (8, 1), (1000, 1000), (1000, 2100), (2048, 130)])
+def test_packed_gram_adds_the_same_in_small_and_large_launches(d1, n):
+    """Launches of few workgroups add to the float64 result with atomics, larger ones with loads and stores: two equal chunks give
+    exactly twice the sums of one, and again the same bits."""
+    g = torch.Generator(device=DEV).manual_seed(d1 + n)
+    X = torch.randn(n, d1, generator=g, device=DEV).bfloat16()
+    W = torch.zeros(d1, 8, dtype=torch.bfloat16, device=DEV)
+    s = _pkg().Solver(d1, 8, d1, 1, d1 // 2, 1, torch.bfloat16, torch.bfloat16, DEV)
+    H = []
+    for chunks in (1, 2, 2):
+        for _ in range(chunks - 1):
+            s.osscar_gram(X)
+        s.osscar_gram(X, True, W, 0.0, 0.0)
+        H.append(s.osscar_get_tensor(0))
+    s.close()
+    assert torch.equal(H[1], H[2]) and torch.equal(H[1], 2 * H[0])
+    Hr = (X.double().T @ X.double()).cpu().numpy()
+    d = np.sqrt(np.diag(Hr))
+    assert np.max(np.abs(H[0].cpu().double().numpy() - Hr) / np.outer(d, d)) <= 1e-6
