@@ -259,8 +259,10 @@ int32_t osscar_debug_gemm_log_read(double* out_host, int32_t capacity);
 /* The large products that define the state of a support (every dimension >= 1024: B = P G_K, V = P H_{K,Kc}, the Schur
  * complement S and R of Proposition 4.1's closed forms) run on the int8 matrix cores from five 7-bit digits per float32
  * operand, with exact integer sums (kind 16 in the log above), and so does the residual of the back-solve; smaller ones, and
- * the residuals that involve the inverse, on the float64-accumulating kernel.  osscar_debug_int_products(0) sends all of them to the
- * float64-accumulating kernel, osscar_debug_int_products(1) restores the default.  Process-wide, for tests that hold the two
+ * the residuals that involve the inverse, on the float64-accumulating kernel.  So does X^T X of rows that the bf16 kernel does not
+ * take (float32, or bf16 at other alignments) from 256 tiles of 128 x 128 and 1024 rows per call on, except for columns with
+ * rare large values.  osscar_debug_int_products(0) sends all of them to the float64-accumulating kernels,
+ * osscar_debug_int_products(1) restores the default.  Process-wide, for tests that hold the two
  * against each other. */
 osscar_status osscar_debug_int_products(int32_t enable);
 
@@ -294,7 +296,7 @@ int32_t osscar_debug_tile_schedule(int64_t d1, int32_t* out_host, int32_t capaci
  * H_dev, G_dev: dev outputs, dense (leading dimensions d1 and m); scalars_dev: dev, 2 float64 = {lambda, c0}.
  * Everything is enqueued on hip_stream (a hipStream_t, NULL = default stream); the call does not wait for it and
  * calls no hipMalloc, hipFree or other allocating routine.  What osscar_gram keeps in the caller's workspace meanwhile
- * (float64 accumulator, float32 W, transposed staging of X) lives in a device array of OSSCAR_STATIC_SCRATCH_BYTES that
+ * (float64 accumulator, float32 W, partial tiles) lives in a device array of OSSCAR_STATIC_SCRATCH_BYTES that
  * every GPU the library runs on holds until the process ends.  Limits: d1, m <= OSSCAR_STATIC_MAX_DIM, any n >= 0;
  * larger sizes return OSSCAR_ENOMEM.  All calls on one GPU share that array: calls that overlap in time on one GPU
  * (different streams or host threads) race and must be serialised by the caller.  After a failure

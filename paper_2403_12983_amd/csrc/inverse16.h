@@ -24,8 +24,8 @@ __device__ __forceinline__ void inv16_steps(swd4& x, int lane, int n, bool& flag
     const double row = __hiloint2double(__builtin_amdgcn_ds_bpermute(from, __double2hiint(mine)),
                                         __builtin_amdgcn_ds_bpermute(from, __double2loint(mine)));
     // the pivot goes by v_readlane, ahead of the row; its reciprocal is a division, rounded correctly and 0 for an infinite pivot
-    // (v_rcp_f64 and two Newton steps are not, and give NaN there; the inverse of 128 rows takes 37 us either way, a layer of 256
-    // groups of nine 8.05 ms against 7.85)
+    // (v_rcp_f64 and two Newton steps are not, and give NaN there; the inverse of 128 rows takes 37 us either way, and a layer of
+    // 256 groups of nine between the same 8.5 ms and 0.2 ms more)
     double piv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), ((K & 3) << 4) | K),
                                   __builtin_amdgcn_readlane(__double2loint(mine), ((K & 3) << 4) | K));
     if (!(piv > 0.0)) { flag = true; piv = 1.0; }

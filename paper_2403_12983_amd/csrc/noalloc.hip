@@ -1,7 +1,7 @@
 // osscar_gram_static: the quadratic form of one small layer, H = X^T X + lambda I and G = H W (Section 3, dense-layer
 // paragraph), in one call that allocates nothing.  It is osscar_gram (one chunk plus finalize) for callers that cannot
 // allocate device memory: there is no context and no workspace argument; what osscar_gram keeps in the caller's workspace
-// during the Gram phase -- the float64 accumulator of H, the float32 copy of W, the transposed float32 staging of X and a
+// during the Gram phase -- the float64 accumulator of H, the float32 copy of W, the partial tiles of cut contractions and a
 // few scalars -- lives in a fixed device array of this file instead.
 #include "../../include/osscar.h"
 #include "internal.h"

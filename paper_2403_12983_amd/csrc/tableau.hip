@@ -2100,7 +2100,7 @@ hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int force
   const size_t ps_lds = (size_t)3 * q * (q + 1) * 8;
   const int ncb = (d.m + PC_COLS - 1) / PC_COLS;
   OSSCAR_BY_TILES(q, {
-    if (ps_lds > 32768) {      // beside the inverse's 35 KB
+    if (ps_lds > 32768) {      // beside the inverse's 30 KB
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pair_small_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ps_lds);
       if (e != hipSuccess) return e;
     }
