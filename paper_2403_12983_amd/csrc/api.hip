@@ -157,7 +157,7 @@ int g_copies_of(const osscar_desc& ds, bool extras) {
 
 // Carves (or just sizes, when base == nullptr) the workspace for a description.  extras: with the memory that only makes small
 // layers faster - copies of the float64 accumulators, partial tiles of cut contractions, schedules of the wide tiles.
-// It is up to three quarters of a small layer's workspace (14.5 of 47 MB for 288 x 64, nothing to speak of at 28672 x 7168), so a
+// It is up to three quarters of a small layer's workspace (34 of 48 MB for 288 x 64, nothing to speak of at 28672 x 7168), so a
 // caller with less is served without: the same sums, in 128 x 128 tiles and uncut contractions.
 Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) {
   const int64_t d1 = ds.d1, m = ds.m, p = ds.p, q = ds.q, kr = (int64_t)ds.k * q, cr = d1 - kr;
