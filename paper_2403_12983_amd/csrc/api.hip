@@ -142,6 +142,18 @@ struct osscar_ctx {
 
 namespace {
 
+// What the one-launch swaps share between workgroups lies at the start of the phases' scratch, which no search uses otherwise
+// (a rebuild of the state inside a search starts them anew).
+size_t swap_scratch(void* base, int64_t d1, LazyPtrs* L) {
+  Carve cv(base);
+  double* M = cv.take<double>(LAZY_TM * LAZY_TM);
+  double* KT = cv.take<double>(LAZY_TM * LAZY_TM);
+  double* K = cv.take<double>((LAZY_NC + LAZY_NS) * (LAZY_NC + LAZY_NS));
+  SwapRec *rec = cv.take<SwapRec>(swap_record_count(d1)), *rec2 = cv.take<SwapRec>(swap_record_count(d1));
+  if (L) { L->Minv2 = M; L->KT = KT; L->K = K; L->rec = rec; L->rec2 = rec2; }
+  return cv.off;
+}
+
 struct Layout {
   size_t total = 0, scratch_bytes = 0;
 };
@@ -205,7 +217,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
   if (q == 1) {
     const int64_t TM = LAZY_TM;
     L.pos = cv.take<int32_t>(d1); L.Tidx = cv.take<int32_t>(TM); L.Jsg = cv.take<float>(TM);
-    L.C0R = cv.take<float>(d1 * TM); L.Minv = cv.take<double>(TM * TM); L.Minv32 = cv.take<float>(TM * TM);
+    L.C0R = cv.take<float>(d1 * TM); L.Minv = cv.take<double>(TM * TM);
     L.ZT = cv.take<double>(TM * m); L.ZT32 = cv.take<float>(TM * m); L.E = cv.take<float>(d1 * TM);
     L.xg = cv.take<double>(TM); L.xj = cv.take<double>(TM); L.u1 = cv.take<double>(4 * TM); L.u2 = cv.take<double>(4 * TM);      // GEMV_SPLIT partial sums per pending row
     L.cg = cv.take<double>(d1); L.cj = cv.take<double>(d1); L.w1 = cv.take<double>(d1); L.w2 = cv.take<double>(d1);
@@ -238,7 +250,9 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
   }
   // the column chunks of the groups' Grams, formed when nothing else of a phase is needed any more, lie at its start
   size_t scratch_bytes = std::max({gram_phase, init_phase, group_part_doubles(p, q, m) * 8});
+  if (q == 1) scratch_bytes = std::max(scratch_bytes, swap_scratch(nullptr, d1, nullptr));
   char* scratch = cv.take<char>(scratch_bytes);
+  if (q == 1 && scratch) swap_scratch(scratch, d1, &L);
   if (c) {
     c->H = H; c->G = G; c->N = N; c->Z = Z; c->norms2 = norms2; c->score = score; c->gram = gram; c->dblk = dblk;
     c->cross = cross; c->xgram = xgram; c->xdblk = xdblk; c->xscore = xscore;
@@ -965,14 +979,38 @@ osscar_status osscar_init_support(osscar_ctx* c, int mode, const int32_t* groups
   return OSSCAR_OK;
 }
 
-static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h) {
+static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h, const SearchCtrl* from = nullptr) {
   // through pinned memory: the search waits on this copy once per 64 swaps with the device idle meanwhile
   SearchCtrl* dst = c->snap ? c->snap : h;
-  HIPCHK(c, hipMemcpyAsync(dst, c->ctrl, sizeof *h, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipMemcpyAsync(dst, from ? from : c->ctrl, sizeof *h, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   if (dst != h) *h = *dst;
   return OSSCAR_OK;
 }
+
+// The delayed-update search on one-launch swaps: every launch reads one copy of the control block, of M^-1 and of the records and writes
+// the other, so the current ones change place; settle() brings the control block back to where every other call expects it.
+struct SwapRun {
+  osscar_ctx* c; TabDims d; TabPtrs t; LazyPtrs L; int mode;
+  int tau_most = 0;              // pending pivots after the launches so far, at most
+  SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) {}
+  hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode, true); }
+  hipError_t swap(int always, int limit, int g = -1, int j = -1) {
+    SearchCtrl* next = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
+    const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, nullptr, g, j);
+    t.ctrl = next;
+    std::swap(L.Minv, L.Minv2); std::swap(L.rec, L.rec2);
+    tau_most = std::min(tau_most + 2, LAZY_TM);
+    return e;
+  }
+  hipError_t flush() { tau_most = 0; return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c), true); }
+  hipError_t settle() {
+    if (t.ctrl == c->ctrl) return hipSuccess;
+    const hipError_t e = hipMemcpyAsync(c->ctrl, t.ctrl, sizeof(SearchCtrl), hipMemcpyDeviceToDevice, c->stream);
+    t.ctrl = c->ctrl;
+    return e;
+  }
+};
 
 osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_every, uint32_t flags, int32_t* removed_host,
                                  float* gaps_host, double* obj_host) {
@@ -996,7 +1034,7 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
   if (st != OSSCAR_OK) return st;
   SearchCtrl h{};
   h.obj = c->dense_is_exact ? 0.0 : obj;   // the dense layer reproduces its own output exactly; a target output it does not
-  h.g_out = -1; h.g_in = -1; h.tau = 0; h.tau_inc = 0; h.pause = 0;
+  h.g_out = -1; h.g_in = -1; h.tau = 0; h.tau_inc = 0; h.pause = 0; h.spare = 0;
   HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
   TabDims d = dims(c);
   TabPtrs t = ptrs(c);
@@ -1110,7 +1148,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
   if (st != OSSCAR_OK) return st;
   const double obj0 = h.obj;
   h.done = (c->cr == 0) ? 1 : 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1;
-  h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0;
+  h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0; h.spare = 0;
   for (auto& v : c->counters) v = 0;
   HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
   HIPCHK(c, hipStreamSynchronize(s));
@@ -1124,13 +1162,13 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
   const bool use_lazy = (c->q == 1) && !(flags & OSSCAR_SEARCH_EAGER) && !exact_in;
   if (use_lazy) {
     // delayed-update search: the tableau in HBM is only touched by a flush every FLUSH iterations
-    const LazyPtrs& L = c->lazy;
     // The host waits once per flush interval (to read the control block); the flush and the next interval's iterations are
     // enqueued behind it without another wait, and the flush's time is read at the next wait.
     const int FLUSH = LAZY_TM / 2, BATCH = FLUSH;
     const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
-    HIPCHK(c, launch_lazy_init(d, t, L, s, la_mode));
-    int since_flush = 0;
+    SwapRun run(c, d, t, la_mode);
+    HIPCHK(c, run.init());
+    int since_flush = 0, extra = 0;
     double flush_ms = 0; int flushes = 0, pauses = 0;
     bool flush_open = false;                 // a flush whose events have not been read yet
     auto collect = [&]() {                   // only after the stream has been waited for
@@ -1139,7 +1177,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     };
     auto flush = [&]() -> osscar_status {
       HIPCHK(c, hipEventRecord(c->ev_s[0][0], s));
-      HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c)));
+      HIPCHK(c, run.flush());
       HIPCHK(c, hipEventRecord(c->ev_s[0][1], s));
       flush_open = true; flushes++;
       since_flush = 0;
@@ -1149,19 +1187,24 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       int nb = std::min(std::min(BATCH, max_swaps - h.iters), FLUSH - since_flush);
       if (refresh_every > 0) nb = std::min(nb, std::max(1, refresh_every - (h.accepted - since_refresh_base)));
       const bool sample = samples + 1 < EV_SAMPLES;
-      for (int i = 0; i < nb; i++)
-        HIPCHK(c, launch_lazy_iteration(d, t, L, always, s, (i == 0 && sample) ? c->ev_s[samples + 1] : nullptr));
-      const int before = h.iters;
-      st = read_ctrl(c, &h);
+      // a launch that fetches products makes no swap: as many more as the last interval had of those (idle past the limit)
+      const int before = h.iters, before_misses = h.misses;
+      for (int i = 0; i < nb + extra; i++) {
+        if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][0], s));
+        HIPCHK(c, run.swap(always, before + nb));
+        if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][1], s));
+      }
+      st = read_ctrl(c, &h, run.t.ctrl);
       if (st != OSSCAR_OK) return st;
+      extra = std::min(h.misses - before_misses, 4);
+      run.tau_most = h.tau;
       collect();
       if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_local_search: a pivot lost definiteness at iteration %d", h.iters);
       since_flush += h.iters - before;
       if (sample && h.iters > before) {
-        float a = 0, b = 0;
+        float a = 0;
         hipEventElapsedTime(&a, c->ev_s[samples + 1][0], c->ev_s[samples + 1][1]);
-        hipEventElapsedTime(&b, c->ev_s[samples + 1][0], c->ev_s[samples + 1][2]);
-        upd_n_ms += a; upd_z_ms += b; samples++;
+        upd_n_ms += a; upd_z_ms += a; samples++;
       }
       const bool want_refresh = !h.done && refresh_every > 0 && h.accepted - since_refresh_base >= refresh_every && h.iters < max_swaps;
       if (h.pause) pauses++;
@@ -1178,8 +1221,8 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
         double obj = 0;
         st = build_state(c, &obj);
         if (st != OSSCAR_OK) return st;
-        HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(c->ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
-        HIPCHK(c, launch_lazy_init(d, t, L, s, la_mode));     // selection records and look-ahead products of the rebuilt state
+        HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(run.t.ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
+        HIPCHK(c, run.init());     // selection records and look-ahead products of the rebuilt state
         HIPCHK(c, hipEventRecord(r1, s));
         HIPCHK(c, hipStreamSynchronize(s));
         float ms = 0; hipEventElapsedTime(&ms, r0, r1); refresh_ms += ms;
@@ -1188,6 +1231,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       }
     }
     if (h.tau + h.tau_inc > 0) { st = flush(); if (st != OSSCAR_OK) return st; }
+    HIPCHK(c, run.settle());
     if (flush_open) { HIPCHK(c, hipStreamSynchronize(s)); collect(); }
     c->timers[6] = refresh_ms + flush_ms;
     c->counters[0] = flushes; c->counters[1] = pauses; c->counters[2] = h.misses; c->counters[3] = h.iters;
@@ -1260,6 +1304,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   if (st != OSSCAR_OK) return st;
   const double obj0 = h.obj;
   h.done = 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1; h.pause = 0; h.tau = 0; h.tau_inc = 0;
+  h.spare = 0;
   HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
   HIPCHK(c, hipStreamSynchronize(s));
   const bool always = (flags & OSSCAR_SEARCH_ALWAYS_ACCEPT) != 0;
@@ -1269,27 +1314,31 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   TabDims d = dims(c);
   TabPtrs t = ptrs(c);
   t.trace_out = nullptr; t.trace_in = nullptr; t.trace_gap = nullptr; t.trace_obj = nullptr;   // pairs are recorded on the host
-  const LazyPtrs& L = c->lazy;
+  SwapRun run(c, d, t, la_mode);
   HIPCHK(c, hipEventRecord(c->ev_a, s));
-  if (use_lazy) HIPCHK(c, launch_lazy_init(d, t, L, s, la_mode));
+  if (use_lazy) HIPCHK(c, run.init());
   int pending = 0, done_pairs = 0, blocks = 0, accepted = 0;
   // applies the pairs one after the other (each unconditionally); resumes after a flush when the kernels had to stop
   auto run_pairs = [&](const std::vector<int32_t>& out, const std::vector<int32_t>& inn) -> osscar_status {
     size_t idx = 0;
+    int misses = h.misses;
     while (idx < out.size()) {
       for (size_t r = idx; r < out.size(); r++) {
-        if (use_lazy) HIPCHK(c, launch_lazy_iteration(d, t, L, 1, s, nullptr, nullptr, out[r], inn[r]));
+        if (use_lazy) HIPCHK(c, run.swap(1, done_pairs + (int)(r - idx) + 1, out[r], inn[r]));
         else HIPCHK(c, launch_search_iteration(d, t, out[r], inn[r], 1, s));
       }
-      osscar_status q = read_ctrl(c, &h);
+      osscar_status q = read_ctrl(c, &h, run.t.ctrl);
       if (q != OSSCAR_OK) return q;
+      run.tau_most = h.tau;
       if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_block_search: a pivot lost definiteness in move %d", blocks);
       const int did = h.iters - done_pairs;
       if (did < 0 || did > (int)(out.size() - idx)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search lost count of its pairs");
       done_pairs += did; idx += did; pending += 2 * did;
       if (idx < out.size()) {
-        if (!use_lazy || !h.pause) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
-        HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c)));
+        if (!use_lazy || (!h.pause && h.misses == misses)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
+        misses = h.misses;
+        if (!h.pause) continue;                // a pair's launch fetched the products of its pivots: the pairs from it on again
+        HIPCHK(c, run.flush());
         pending = 0;
       }
     }
@@ -1298,7 +1347,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   std::vector<int32_t> out(take), inn(take);
   float gaps[2] = {0, 0};
   while (take > 0 && blocks < max_iters) {
-    if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c))); pending = 0; }
+    if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = 0; }
     HIPCHK(c, launch_greedy_pick(d, t, take, c->g_pick, c->g_gap, s, 0));
     HIPCHK(c, launch_greedy_pick(d, t, take, c->g_pick + 64, c->g_gap + 1, s, 1));
     HIPCHK(c, hipMemcpyAsync(out.data(), c->g_pick, (size_t)take * 4, hipMemcpyDeviceToHost, s));
@@ -1319,17 +1368,18 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
     blocks++;
     if (!ok) {
       // take the move back: the same pairs in reverse (the pending pivots must reach the tableau first)
-      if (use_lazy && pending > 0) { HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c))); pending = 0; }
+      if (use_lazy && pending > 0) { HIPCHK(c, run.flush()); pending = 0; }
       std::vector<int32_t> bo(inn.rbegin(), inn.rend()), bi(out.rbegin(), out.rend());
       st = run_pairs(bo, bi);
       if (st != OSSCAR_OK) return st;
       h.obj = obj_before;
-      HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(c->ctrl) + offsetof(SearchCtrl, obj), &h.obj, 8, hipMemcpyHostToDevice, s));
+      HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(run.t.ctrl) + offsetof(SearchCtrl, obj), &h.obj, 8, hipMemcpyHostToDevice, s));
       break;
     }
     accepted++;
   }
-  if (use_lazy && pending > 0) HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c)));
+  if (use_lazy && pending > 0) HIPCHK(c, run.flush());
+  HIPCHK(c, run.settle());
   HIPCHK(c, hipEventRecord(c->ev_b, s));
   HIPCHK(c, hipStreamSynchronize(s));
   c->timers[3] = elapsed(c);

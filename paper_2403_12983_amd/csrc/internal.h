@@ -163,6 +163,7 @@ struct SearchCtrl {          // lives in device memory
   double rel_tol;
   double delta;              // exact change of the current pair
   double gap_rem, gap_add;
+  int32_t spare;             // one-launch swaps: spare slots of the look-ahead products in use
 };
 
 struct TabDims { int d1, m, p, q; };
@@ -230,13 +231,14 @@ constexpr int LAZY_NPICK_OUT = 88;  // swap search: kept rows picked by cost of 
 constexpr int LAZY_NPICK_IN = 72;   // ... and rows outside the kept set picked by gain; together a multiple of 32
 constexpr int LAZY_BT = 16;      // rows that one block removal of the nested schedule takes at most
 struct SelRec { double mn1, mn2, mx1, mx2; int32_t imn, imx; };   // best / second-best scores of a block of rows
+// the same for the one-launch swaps: [0] cheapest removal, [1] largest gain (negated); slot of the best row's products, -1 none
+struct SwapRec { double best[2], second[2]; int32_t row[2], slot[2]; };
 struct LazyPtrs {
   int32_t* pos;     // d1: position in the pending set or -1
   int32_t* Tidx;    // LAZY_TM pivot indices
   float* Jsg;       // LAZY_TM: -1 for pivots that left the kept set, +1 for pivots that entered
   float* C0R;       // d1 x LAZY_TM row-major: base columns N0[:, T_s]
   double* Minv;     // LAZY_TM x LAZY_TM: inverse of N0[T, T]
-  float* Minv32;    // float copy for the flush
   double* ZT;       // LAZY_TM x m: Minv * Z0[T, :]
   float* ZT32;      // LAZY_TM x m (flush)
   float* E;         // d1 x LAZY_TM: C0 * Minv (flush)
@@ -260,6 +262,9 @@ struct LazyPtrs {
   int32_t* cand;    // LAZY_NC + LAZY_NS: row held by a slot or -1
   int32_t* tslot;   // LAZY_TM: slot of each pending pivot
   int32_t* misc;    // [0] spare slots in use, [1] miss mask of the current pair (1: g, 2: j), [2] slot of g, [3] slot of j
+  // one-launch swaps (in the phases' scratch, see carve_all): the other copy of M^-1, two copies of a record per workgroup, Gram
+  // matrix of the base rows in the slots (LAZY_NC + LAZY_NS squared) and its part for the pending pivots (LAZY_TM squared)
+  double* Minv2; SwapRec* rec; SwapRec* rec2; double* K; double* KT;
   double* lkey; int32_t* lidx;   // 2 x 64 x 32: per-block winners of the candidate selection
   // block removal (nested schedule): b = N0[T, G], X = M^-1 b (LAZY_TM x LAZY_BT each), U = ZT Y^T (four partial sums of that
   // shape, one per quarter of the columns), D, Y Y^T (LAZY_BT^2),
@@ -268,7 +273,16 @@ struct LazyPtrs {
 };
 // mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NC/2 cheapest removals + LAZY_NC/2 largest gains,
 // 1 = LAZY_NC cheapest removals (removal-only loops), 2 = none (every pivot then costs a pass over Z0)
-hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0);
+// swaps: the iterations are launch_lazy_swap's (else launch_lazy_iteration's and launch_lazy_block_remove's)
+hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0, bool swaps = false);
+// swap.hip: one swap in one launch, from the control block t.ctrl, L.Minv and L.rec to *next, L.Minv2 and L.rec2 (the caller exchanges
+// them after every launch); tau_most: at most this many pivots are pending
+hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int tau_most,
+                            hipStream_t s, const int32_t* single = nullptr, int forced_out = -1, int forced_in = -1);
+int swap_record_count(int64_t d1);
+hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
+hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);
+hipError_t launch_zt(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
 // ev (optional): events recorded before and after the pass over Z0, and at the end of the iteration
 // single (optional, device): removal of the one row *single instead of a swap; adds one pending pivot instead of two
 hipError_t launch_lazy_iteration(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int always_accept, hipStream_t s,
@@ -285,7 +299,7 @@ hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const La
 struct SideStream { hipStream_t stream = nullptr; hipEvent_t fork = nullptr, join = nullptr; };
 // side == nullptr (or no stream in it): everything in order on s
 hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0,
-                             const SideStream* side = nullptr);
+                             const SideStream* side = nullptr, bool swaps = false);
 
 hipError_t launch_scatter_rows(const float* src, int64_t lds, const int32_t* rows, int nrows, int ncols, void* dst,
                                int64_t ldd, int dst_is_bf16, hipStream_t s);

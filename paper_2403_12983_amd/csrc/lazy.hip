@@ -20,7 +20,7 @@
 // LAZY_TM/2 iterations the pending rank-tau correction is applied to N0 and Z0 by matrix products on the
 // matrix cores.  The sequence of swaps is exactly that of the eager search (Proposition 4.1, Cases 1-3).
 //
-// Four launches per iteration:
+// A swap is one launch (swap.hip).  A removal alone (the nested schedule's rows one by one) is four:
 //   prep    (1 workgroup)  : argmin / argmax from per-block partial records; x = M^-1 N0[T, {g, j}]; pivots
 //   vectors (rows | cols | rows) : current columns g, j of N; current rows g, j of Z scaled to y1, y2; partial sums;
 //                            and, independent of these, w = Z0 [y1 y2] from the cached products
@@ -30,43 +30,11 @@
 //                            (after a miss also w, whose missing column exists only since gemv)
 #include "internal.h"
 #include "inverse16.h"
+#include "wave.h"
 #include <algorithm>
 
 namespace osscar {
 
-__device__ __forceinline__ float nsym1(const float* __restrict__ N, int64_t ld, int i, int t) {
-  return (i >= t) ? N[(int64_t)i * ld + t] : N[(int64_t)t * ld + i];
-}
-// Sum over the 64 lanes of a wave by data-parallel-primitive moves (no trip through the LDS crossbar, which costs a
-// shuffle about 40 ns here and made the reductions the longest part of the small kernels): pairs and quads by quad
-// permutations, the four quads of a row of 16 by row rotations, then row 0 -> 1 and 2 -> 3 (row_bcast:15) and
-// rows 0-1 -> 3 (row_bcast:31); lane 63 holds the total, which every lane receives.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_get(double v) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROW_MASK, 0xf, false);
-  hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROW_MASK, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_get_or(double v, double dflt) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  lo = __builtin_amdgcn_update_dpp(__double2loint(dflt), lo, CTRL, ROW_MASK, 0xf, false);
-  hi = __builtin_amdgcn_update_dpp(__double2hiint(dflt), hi, CTRL, ROW_MASK, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_get_or(int v, int dflt) { return __builtin_amdgcn_update_dpp(dflt, v, CTRL, ROW_MASK, 0xf, false); }
-__device__ __forceinline__ double wsum(double v) {
-  v += dpp_get<0xb1, 0xf>(v);        // quad_perm [1, 0, 3, 2]
-  v += dpp_get<0x4e, 0xf>(v);        // quad_perm [2, 3, 0, 1]
-  v += dpp_get<0x124, 0xf>(v);       // row_ror:4
-  v += dpp_get<0x128, 0xf>(v);       // row_ror:8
-  v += dpp_get<0x142, 0xa>(v);       // row_bcast:15 into rows 1 and 3 (other rows add zero)
-  v += dpp_get<0x143, 0xc>(v);       // row_bcast:31 into rows 2 and 3
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63), hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-  return __hiloint2double(hi, lo);
-}
 __device__ __forceinline__ bool idle(const SearchCtrl* c) { return (c->done | c->pause) != 0; }      // both in one round trip
 // pending pivots including those of the iteration that ran last (for kernels outside an iteration)
 __device__ __forceinline__ int tau_all(const SearchCtrl* c) { return c->tau + c->tau_inc; }
@@ -78,64 +46,6 @@ constexpr int COLS_PER_BLOCK = 64;   // column kernels: 64 columns x 4 slices of
 enum { LS_DG = 0, LS_NJG = 1, LS_M1 = 2, LS_DJ = 3, LS_Y11 = 4, LS_Y22 = 5, LS_Y12 = 6, LS_OBJ = 8 };
 // misc[] slots
 enum { MI_SPARE = 0, MI_MISS = 1, MI_SG = 2, MI_SJ = 3 };
-
-// merge of two (best, second, index) records; lowest index wins ties
-__device__ __forceinline__ void merge_min(double& a1, double& a2, int& ia, double b1, double b2, int ib) {
-  const bool takeb = (ib >= 0) && (ia < 0 || b1 < a1 || (b1 == a1 && ib < ia));
-  const double n1 = takeb ? b1 : a1, other = takeb ? a1 : b1;
-  a2 = fmin(fmin(a2, b2), other); a1 = n1; ia = takeb ? ib : ia;
-}
-__device__ __forceinline__ void merge_max(double& a1, double& a2, int& ia, double b1, double b2, int ib) {
-  const bool takeb = (ib >= 0) && (ia < 0 || b1 > a1 || (b1 == a1 && ib < ia));
-  const double n1 = takeb ? b1 : a1, other = takeb ? a1 : b1;
-  a2 = fmax(fmax(a2, b2), other); a1 = n1; ia = takeb ? ib : ia;
-}
-
-// Sum over each group of eight consecutive lanes (every lane of the group receives it): pairs and quads by quad
-// permutations, the two quads of a half row by row_half_mirror (lane i of the half row reads lane 7 - i, which by then
-// holds the other quad's sum).
-__device__ __forceinline__ double sum8(double v) {
-  v += dpp_get<0xb1, 0xf>(v);
-  v += dpp_get<0x4e, 0xf>(v);
-  v += dpp_get<0x141, 0xf>(v);
-  return v;
-}
-
-// The (best, second, index) records of the 64 lanes of a wave merged into lane 63, by the same data-parallel moves as
-// wsum (each step joins disjoint sets of lanes, so no record meets itself; lanes that a row mask leaves out see the
-// neutral record).  Lanes without a candidate hold the neutral record (+-inf, index -1).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_merge_step(double& mn1, double& mn2, int& imn, double& mx1, double& mx2, int& imx) {
-  const double b1 = dpp_get_or<CTRL, ROW_MASK>(mn1, INFINITY), b2 = dpp_get_or<CTRL, ROW_MASK>(mn2, INFINITY);
-  const int ib = dpp_get_or<CTRL, ROW_MASK>(imn, -1);
-  const double c1 = dpp_get_or<CTRL, ROW_MASK>(mx1, -INFINITY), c2 = dpp_get_or<CTRL, ROW_MASK>(mx2, -INFINITY);
-  const int ic = dpp_get_or<CTRL, ROW_MASK>(imx, -1);
-  merge_min(mn1, mn2, imn, b1, b2, ib);
-  merge_max(mx1, mx2, imx, c1, c2, ic);
-}
-__device__ __forceinline__ void wave_merge(double& mn1, double& mn2, int& imn, double& mx1, double& mx2, int& imx) {
-  dpp_merge_step<0xb1, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x4e, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x124, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x128, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x142, 0xa>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x143, 0xc>(mn1, mn2, imn, mx1, mx2, imx);
-}
-
-// The same moves on (value, index) alone: lane 63 ends with the smallest value (lowest index on ties) and the largest.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_best_step(double& mn, int& imn, double& mx, int& imx) {
-  const double b = dpp_get_or<CTRL, ROW_MASK>(mn, INFINITY), c = dpp_get_or<CTRL, ROW_MASK>(mx, -INFINITY);
-  const int ib = dpp_get_or<CTRL, ROW_MASK>(imn, -1), ic = dpp_get_or<CTRL, ROW_MASK>(imx, -1);
-  const bool tb = (ib >= 0) && (imn < 0 || b < mn || (b == mn && ib < imn));
-  const bool tc = (ic >= 0) && (imx < 0 || c > mx || (c == mx && ic < imx));
-  mn = tb ? b : mn; imn = tb ? ib : imn; mx = tc ? c : mx; imx = tc ? ic : imx;
-}
-// ... and on plain values: lane 63 ends with the minimum of lo and the maximum of hi over the wave
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_minmax_step(double& lo, double& hi) {
-  lo = fmin(lo, dpp_get_or<CTRL, ROW_MASK>(lo, INFINITY)); hi = fmax(hi, dpp_get_or<CTRL, ROW_MASK>(hi, -INFINITY));
-}
 
 // per-block record of the scores of rows [32 b, 32 b + 32): used after a flush; the update kernel writes the same records
 __global__ __launch_bounds__(64) void lazy_partials_kernel(LazyPtrs L, int p, const int32_t* __restrict__ kept,
@@ -159,25 +69,6 @@ __global__ __launch_bounds__(64) void lazy_partials_kernel(LazyPtrs L, int p, co
 }
 
 // ---------------------------------------------------------------------------------------------- prep
-// (value, index): the smaller value, the lower index on ties, index -1 = none; six data-parallel steps leave the best of the
-// wave in lane 63
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_min_step(double& v, int& i) {
-  const double ov = dpp_get_or<CTRL, ROW_MASK>(v, INFINITY);
-  const int oi = dpp_get_or<CTRL, ROW_MASK>(i, -1);
-  const bool t = (oi >= 0) && (i < 0 || ov < v || (ov == v && oi < i));
-  v = t ? ov : v; i = t ? oi : i;
-}
-__device__ __forceinline__ void wave_min(double& v, int& i) {
-  dpp_min_step<0xb1, 0xf>(v, i); dpp_min_step<0x4e, 0xf>(v, i); dpp_min_step<0x124, 0xf>(v, i);
-  dpp_min_step<0x128, 0xf>(v, i); dpp_min_step<0x142, 0xa>(v, i); dpp_min_step<0x143, 0xc>(v, i);
-}
-__device__ __forceinline__ double wave_min(double v) {
-  v = fmin(v, dpp_get_or<0xb1, 0xf>(v, INFINITY)); v = fmin(v, dpp_get_or<0x4e, 0xf>(v, INFINITY));
-  v = fmin(v, dpp_get_or<0x124, 0xf>(v, INFINITY)); v = fmin(v, dpp_get_or<0x128, 0xf>(v, INFINITY));
-  v = fmin(v, dpp_get_or<0x142, 0xa>(v, INFINITY)); v = fmin(v, dpp_get_or<0x143, 0xc>(v, INFINITY));
-  return v;
-}
 // One workgroup, a chain of round trips to memory (about 1.5 us each): the records, then everything that depends on the pick.
 // M^-1 (128 KB) does not, so it is requested first and waits in registers; the leaving and the entering side are picked by
 // four waves each, the second-best values (for the reported gaps) while the pivots' rows are on their way.  9.4 -> 6.9 us at 8192 rows.
@@ -772,19 +663,13 @@ hipError_t launch_lazy_iteration(const TabDims& d, const TabPtrs& t, const LazyP
 // ------------------------------------------------------------------------------------------------
 // flush: apply the pending correction to N0, Z0 and empty T
 // ------------------------------------------------------------------------------------------------
-// float32 copies of M^-1 and ZT, zero beyond tau (so that stale columns of C0 drop out of the products)
+// float32 copy of ZT, zero beyond tau (so that stale columns of C0 drop out of the products)
 __global__ __launch_bounds__(256) void lazy_convert_kernel(LazyPtrs L, int m, const SearchCtrl* __restrict__ ctrl) {
   const int tau = tau_all(ctrl);
-  const int64_t nz = (int64_t)LAZY_TM * m, nm = (int64_t)LAZY_TM * LAZY_TM;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < nz + nm; idx += (int64_t)gridDim.x * 256) {
-    if (idx < nz) {
-      const int s = (int)(idx / m);
-      L.ZT32[idx] = (s < tau) ? (float)L.ZT[idx] : 0.f;
-    } else {
-      const int64_t k = idx - nz;
-      const int r = (int)(k / LAZY_TM), s = (int)(k % LAZY_TM);
-      L.Minv32[k] = (r < tau && s < tau) ? (float)L.Minv[k] : 0.f;
-    }
+  const int64_t nz = (int64_t)LAZY_TM * m;
+  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < nz; idx += (int64_t)gridDim.x * 256) {
+    const int s = (int)(idx / m);
+    L.ZT32[idx] = (s < tau) ? (float)L.ZT[idx] : 0.f;
   }
 }
 
@@ -825,7 +710,7 @@ __global__ __launch_bounds__(256) void lazy_reset_kernel(LazyPtrs L, SearchCtrl*
   const int tau = tau_all(ctrl);
   for (int s = threadIdx.x; s < tau; s += 256) L.pos[L.Tidx[s]] = -1;
   __syncthreads();
-  if (threadIdx.x == 0) { ctrl->tau = 0; ctrl->tau_inc = 0; ctrl->pause = 0; }
+  if (threadIdx.x == 0) { ctrl->tau = 0; ctrl->tau_inc = 0; ctrl->pause = 0; ctrl->spare = 0; }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1113,9 +998,11 @@ static hipError_t launch_candidate_products(const TabDims& d, const TabPtrs& t, 
   g.C = L.GbT; g.ldc = d.d1; g.alpha = 1.0; g.beta = 0.0; g.c_is_f64 = 1; g.ws = L.gemm_ws; g.ws_bytes = L.gemm_ws_bytes;
   return launch_gemm_f64acc(g, s);
 }
-static hipError_t launch_candidates(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
-  const hipError_t e = launch_candidate_pick(d, t, L, s, mode);
-  return e != hipSuccess ? e : launch_candidate_products(d, t, L, s, mode);
+static hipError_t launch_candidates(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode, bool swaps) {
+  hipError_t e = launch_candidate_pick(d, t, L, s, mode);
+  if (e != hipSuccess) return e;
+  if (swaps && (e = launch_cand_gram(d, t, L, cand_counts(mode).n_k + cand_counts(mode).n_c, s)) != hipSuccess) return e;
+  return launch_candidate_products(d, t, L, s, mode);
 }
 
 static hipError_t launch_partials(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s) {
@@ -1311,20 +1198,23 @@ __global__ __launch_bounds__(256, 2) void rk_update_kernel(const uint4* __restri
 // E = C0 M^-1 of the flush (d1 x 128 times 128 x 128, float32 operands, float64 sums on v_mfma_f64_16x16x4_f64, float32
 // result).  It stands at the head of the flush's longest chain, so what counts is its latency: the general matrix-product
 // kernel runs it as 224 workgroups of one 128 x 128 tile each (0.085 ms); here a workgroup takes 64 rows with all of M^-1
-// and its rows of C0 in shared memory (448 workgroups, no barrier inside the contraction).  M^-1 is symmetric bit for bit,
-// so its rows serve as the columns the product needs.  Wave w: rows 16 w .. 16 w + 15, eight 16 x 16 tiles.
+// and its rows of C0 in shared memory (448 workgroups, no barrier inside the contraction).  M^-1 (rounded to float32 here, zero
+// from tau on) is symmetric bit for bit, so its rows serve as the columns the product needs.  Wave w: rows 16 w .. 16 w + 15, eight 16 x 16 tiles.
 typedef double te_d4 __attribute__((ext_vector_type(4)));
 constexpr int TE_LD = LAZY_TM + 4;       // row stride in shared memory (floats): a quarter wave's 16 rows x 4 k fall on 32 banks twice
-__global__ __launch_bounds__(256) void thin_e_kernel(const float* __restrict__ C0R, const float* __restrict__ M32, float* __restrict__ E,
-                                                      int d1) {
+__global__ __launch_bounds__(256) void thin_e_kernel(LazyPtrs L, int d1, const SearchCtrl* __restrict__ ctrl) {
   static_assert(LAZY_TM == 128, "eight column tiles, thirty-two steps of four");
   extern __shared__ float te_lds[];      // [128 rows of M^-1 | 64 rows of C0][TE_LD]
   float* Ms = te_lds;
   float* As = te_lds + LAZY_TM * TE_LD;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i0 = blockIdx.x * 64;
-  for (int idx = tid; idx < LAZY_TM * (LAZY_TM / 4); idx += 256) {
-    const int r = idx >> 5, c4 = (idx & 31) * 4;
-    *reinterpret_cast<float4*>(Ms + r * TE_LD + c4) = *reinterpret_cast<const float4*>(M32 + r * LAZY_TM + c4);
+  const float* C0R = L.C0R;
+  const double* Mi = L.Minv;
+  const int tau = tau_all(ctrl);
+  for (int idx = tid; idx < LAZY_TM * (LAZY_TM / 2); idx += 256) {
+    const int r = idx >> 6, c = (idx & 63) * 2;
+    const double2 v = *reinterpret_cast<const double2*>(Mi + r * LAZY_TM + c);
+    *reinterpret_cast<float2*>(Ms + r * TE_LD + c) = float2{r < tau && c < tau ? (float)v.x : 0.f, r < tau && c + 1 < tau ? (float)v.y : 0.f};
   }
   for (int idx = tid; idx < 64 * (LAZY_TM / 4); idx += 256) {
     const int r = idx >> 5, c4 = (idx & 31) * 4;
@@ -1349,7 +1239,7 @@ __global__ __launch_bounds__(256) void thin_e_kernel(const float* __restrict__ C
     const int row = i0 + wave * 16 + 4 * r + (lane >> 4);
     if (row < d1) {
 #pragma unroll
-      for (int ct = 0; ct < 8; ct++) E[(int64_t)row * LAZY_TM + ct * 16 + (lane & 15)] = (float)acc[ct][r];
+      for (int ct = 0; ct < 8; ct++) L.E[(int64_t)row * LAZY_TM + ct * 16 + (lane & 15)] = (float)acc[ct][r];
     }
   }
 }
@@ -1391,19 +1281,20 @@ __global__ __launch_bounds__(256) void norms_from_stretches_kernel(LazyPtrs L, i
 }
 
 hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode,
-                             const SideStream* side) {
+                             const SideStream* side, bool swaps) {
   const int rb = (d.d1 + 255) / 256, mb = (d.m + 255) / 256;
   const bool two = side && side->stream;
   hipStream_t sn = two ? side->stream : s;          // stream of the N0 update
   hipError_t err;
-  hipLaunchKernelGGL(lazy_convert_kernel, dim3(512), dim3(256), 0, s, L, d.m, t.ctrl);
+  if (swaps) { if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err; }
+  else hipLaunchKernelGGL(lazy_convert_kernel, dim3(512), dim3(256), 0, s, L, d.m, t.ctrl);
   {                                     // E = C0 M^-1 (entered in the log of matrix products like the general kernel's launches)
     const size_t shmem = (size_t)(LAZY_TM + 64) * TE_LD * sizeof(float);
     if ((err = hipFuncSetAttribute(reinterpret_cast<const void*>(thin_e_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)) != hipSuccess)
       return err;
     int log_slot = -1;
     gemm_log_open(d.d1, LAZY_TM, LAZY_TM, 0, s, &log_slot);
-    hipLaunchKernelGGL(thin_e_kernel, dim3((d.d1 + 63) / 64), dim3(256), shmem, s, L.C0R, L.Minv32, L.E, d.d1);
+    hipLaunchKernelGGL(thin_e_kernel, dim3((d.d1 + 63) / 64), dim3(256), shmem, s, L, d.d1, t.ctrl);
     gemm_log_close(log_slot, s);
   }
   // the three thin operands in matrix-core order (C0's pieces serve both updates)
@@ -1437,16 +1328,15 @@ hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs&
     // The candidates of the next cycle, from the scores as the swaps left them (the refresh below changes them in the last
     // digits only, and the choice of candidates decides what is computed ahead, not any result): two sorts of one
     // workgroup each; this stream has the time, the second one's chain is the longer.
-    err = launch_candidates(d, t, L, s, mode);
+    err = launch_candidates(d, t, L, s, mode, swaps);
     if (err != hipSuccess) return err;
     if ((err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
   }
   hipLaunchKernelGGL(lazy_reset_kernel, dim3(1), dim3(256), 0, s, L, t.ctrl);
   err = two ? launch_refresh_from_blocks(d, t, s) : launch_refresh_scores(d, t, s);
   if (err != hipSuccess) return err;
-  err = launch_partials(d, t, L, s);
-  if (err != hipSuccess) return err;
-  return two ? hipGetLastError() : launch_candidates(d, t, L, s, mode);
+  if (!two && (err = launch_candidates(d, t, L, s, mode, swaps)) != hipSuccess) return err;
+  return swaps ? launch_swap_records(d, t, L, s) : launch_partials(d, t, L, s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1835,16 +1725,22 @@ hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const La
   return hipGetLastError();
 }
 
-hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
+hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode, bool swaps) {
   hipError_t e = hipMemsetAsync(L.pos, 0xFF, (size_t)d.d1 * 4, s);
   if (e != hipSuccess) return e;
   e = hipMemsetAsync(L.Minv, 0, (size_t)LAZY_TM * LAZY_TM * 8, s);
   if (e != hipSuccess) return e;
   e = hipMemsetAsync(L.C0R, 0, (size_t)d.d1 * LAZY_TM * 4, s);
   if (e != hipSuccess) return e;
-  e = launch_partials(d, t, L, s);
+  if (swaps) {
+    e = hipMemsetAsync(L.Minv2, 0, (size_t)LAZY_TM * LAZY_TM * 8, s);
+    if (e != hipSuccess) return e;
+    e = hipMemsetAsync(L.KT, 0, (size_t)LAZY_TM * LAZY_TM * 8, s);
+    if (e != hipSuccess) return e;
+  }
+  e = launch_candidates(d, t, L, s, mode, swaps);
   if (e != hipSuccess) return e;
-  return launch_candidates(d, t, L, s, mode);
+  return swaps ? launch_swap_records(d, t, L, s) : launch_partials(d, t, L, s);
 }
 
 }  // namespace osscar

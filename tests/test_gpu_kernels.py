@@ -516,3 +516,33 @@ def test_packed_gram_adds_the_same_in_small_and_large_launches(d1, n):
     Hr = (X.double().T @ X.double()).cpu().numpy()
     d = np.sqrt(np.diag(Hr))
     assert np.max(np.abs(H[0].cpu().double().numpy() - Hr) / np.outer(d, d)) <= 1e-6
+
+
+@pytest.mark.parametrize("p,m,k,swaps", [(31, 3, 15, 40), (33, 20, 17, 40), (257, 36, 100, 90), (8192, 33, 4000, 70), (8193, 8, 4100, 70),
+                                         (16384, 40, 8000, 66), (16385, 17, 8001, 66)])
+def test_swaps_in_one_launch(p, m, k, swaps):
+    """One launch per swap, at the edges of its workgroups' rows (32, 64 and 128), past a flush: the same swaps as with the state updated in
+    place, with the products computed ahead and without (then every pivot's are fetched).  The runs may part only where two groups
+    score alike (1e-5, the bar on choices); up to there the exact changes agree to 1e-6 of the objective (float32 storage)."""
+    pkg = _pkg()
+    g = torch.Generator().manual_seed(p)
+    X = (torch.randn(2 * p + 64 if p < 1000 else 1024, p, generator=g) * torch.exp(0.5 * torch.randn(p, generator=g))).to(DEV)
+    W = (torch.randn(p, m, generator=g) / p ** 0.5).to(DEV)
+    s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
+    s.osscar_gram(X, True, W, 0.0, 5e-2)
+    runs = []
+    for flags in (pkg.OSSCAR_SEARCH_EAGER, 0, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD):
+        s.osscar_init_support()
+        r = s.osscar_local_search(swaps, 0.0, flags | pkg.OSSCAR_SEARCH_ALWAYS_ACCEPT)
+        assert r["iters"] == r["accepted"] == swaps
+        runs.append((r, s.osscar_get_counters(), s.osscar_backsolve()))
+    s.close()
+    (e, _, (We, Se, _)), (a, ca, _), (b, cb, _) = runs
+    assert cb["lookahead_misses"] >= 2 * min(swaps, k) and ca["lookahead_misses"] < cb["lookahead_misses"]
+    for r, _, (Wr, Sr, _) in runs[1:]:
+        same = (r["trace_out"] == e["trace_out"]) & (r["trace_in"] == e["trace_in"])
+        n = swaps if same.all() else int(np.argmin(same))
+        assert n == swaps or e["trace_gap"][n].min() <= 1e-5
+        assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-6, atol=0)
+        if n == swaps:
+            assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
