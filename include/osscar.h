@@ -235,7 +235,7 @@ osscar_status osscar_get_scalars(osscar_ctx* ctx, double* lambda_host, double* c
  * measure of the conditioning of H_KK.  [12] the candidate-side products V, S, R of the last state build together.
  * [13] mean duration of one launch of the bf16 Gram kernel (one launch per 16384 calibration rows) in the last
  * osscar_gram call that added rows on that path before the last finalize, [14] the number of launches averaged, [15] the rows
- * that call added.  out_host: 16 doubles. */
+ * of these launches (they include rows of earlier calls that were still waiting for their product).  out_host: 16 doubles. */
 osscar_status osscar_get_timers(osscar_ctx* ctx, double* out_host);
 
 /* Diagnostics of the last osscar_local_search call on the delayed-update path (all zero otherwise), 8 values:

@@ -135,7 +135,7 @@ struct osscar_ctx {
   hipEvent_t ev_s[EV_SAMPLES][3];
   hipEvent_t ev_g[2 * EV_SAMPLES];   // pairs around the launches of the Gram kernel of the last chunk call
   SearchCtrl* snap = nullptr;         // pinned host memory for reading the control block
-  int ev_g_used = 0; int64_t ev_g_rows = 0;
+  PackQueue queue;                    // bf16 rows of the layer that wait for their product
   SideStream side;   // the flush of the delayed-update search overlaps two of its products
   bool ev_ok = false;
 };
@@ -688,10 +688,22 @@ osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* wor
     if (ts.size() > gram_tile_entries(c->d1) || tr.size() > rect_tile_entries(c->d1, c->m) || ws.size() > wide_tile_entries(c->d1, c->d1) ||
         wr.size() > wide_tile_entries(c->d1, c->m)) { delete c; return OSSCAR_ENOMEM; }
     for (const auto* v : {&ts, &tr, &ws, &wr}) all.insert(all.end(), v->begin(), v->end());
+    // the tiles of queued products lie in what the first list leaves of its room
+    std::vector<int2> hs, hr;
+    const size_t cap = gram_tile_entries(c->d1) + rect_tile_entries(c->d1, c->m) + wide_tile_entries(c->d1, c->d1) + wide_tile_entries(c->d1, c->m);
+    if (!ws.empty() && desc->x_dtype == OSSCAR_BF16) {
+      tall_tile_list_host(c->d1, c->d1, true, hs);
+      if (desc->target_output) tall_tile_list_host(c->d1, c->m, false, hr);
+    }
+    if (all.size() + hs.size() + hr.size() > cap) { hs.clear(); hr.clear(); }
+    const size_t at_hs = all.size();
+    for (const auto* v : {&hs, &hr}) all.insert(all.end(), v->begin(), v->end());
     if (hipMemcpy(c->tiles, all.data(), all.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess) { delete c; return OSSCAR_EHIP; }
     const int2 *sym = c->tiles, *rect = sym + ts.size(), *wsym = rect + tr.size(), *wrect = wsym + ws.size();
     c->tiles_h = PackedTiles{sym, ts.size(), ws.empty() ? nullptr : wsym, ws.size()};
     c->tiles_g = PackedTiles{rect, tr.size(), wr.empty() ? nullptr : wrect, wr.size()};
+    if (!hs.empty()) { c->tiles_h.tall = c->tiles + at_hs; c->tiles_h.tall_entries = hs.size(); }
+    if (!hr.empty()) { c->tiles_g.tall = c->tiles + at_hs + hs.size(); c->tiles_g.tall_entries = hr.size(); }
     c->lazy.tiles_sym = sym; c->lazy.n_tiles_sym = ts.size(); c->lazy.tiles_rect = rect; c->lazy.n_tiles_rect = tr.size();
   }
   c->ev_ok = (hipEventCreate(&c->ev_a) == hipSuccess) && (hipEventCreate(&c->ev_b) == hipSuccess);
@@ -758,8 +770,11 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     c->phase = osscar_ctx::ACCUM;
     c->accum_target = target;
     c->h_copies = c->g_copies = 1;
+    c->queue.clear();
     c->timers[0] = 0;
   }
+  const PackedGram packed{&c->queue, d1, PackedAcc{H64, h_copies, &c->h_copies}, c->tiles_h, Xt, m, PackedAcc{G64, g_copies, &c->g_copies}, c->tiles_g,
+                          target ? Ys : nullptr, (int)(PACK_ROWS / 64), target ? nullptr : c->ev_g, EV_SAMPLES};
   if (n_c > 0) {
     HIPCHK(c, hipEventRecord(c->ev_a, s));
     const bool bf16 = c->desc.x_dtype == OSSCAR_BF16;
@@ -767,14 +782,11 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     if (target) fast = fast && (m % 8 == 0) && (ldy % 8 == 0) && ((reinterpret_cast<uintptr_t>(Yc) & 15) == 0);
     if (target) HIPCHK(c, launch_sumsq(Yc, bf16, n_c, m, ldy, c->scal + 12, c->partial, s));
     if (fast) {
-      const PackedAcc acc_h{H64, h_copies, &c->h_copies}, acc_g{G64, g_copies, &c->g_copies};
-      if (target) HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, acc_h, c->tiles_h, Xt, PACK_ROWS, s, Yc, ldy, m, acc_g, c->tiles_g, Ys));
-      else {
-        HIPCHK(c, launch_gram_packed(Xc, n_c, ldx, d1, acc_h, c->tiles_h, Xt, PACK_ROWS, s, nullptr, 0, 0, PackedAcc(), PackedTiles(), nullptr, conv,
-                                     c->ev_g, EV_SAMPLES, &c->ev_g_used));
-        c->ev_g_rows = n_c;
-      }
+      c->queue.ev_used = 0; c->queue.ev_rows = 0;
+      HIPCHK(c, launch_gram_packed(packed, Xc, n_c, ldx, target ? Yc : nullptr, ldy, conv, s));
+      if (finalize) HIPCHK(c, launch_gram_queue(packed, s));
     } else {
+      HIPCHK(c, launch_gram_queue(packed, s));      // this path uses the same buffers
       // any alignment and float32.  From 256 tiles of 128 x 128 and 1024 rows on: digits on the int8 matrix cores, as many rows at a
       // time as the staging buffer packs (5461 columns, 32769 rows of bf16: 19.0 ms on the float64 matrix cores, 6.5 ms so; 3001
       // columns, 7777 rows of float32, 300 tiles: 1.63 and 0.75 ms).  With fewer tiles than compute units the digit product leaves
@@ -824,6 +836,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   }
   if (!finalize) return OSSCAR_OK;
 
+  HIPCHK(c, launch_gram_queue(packed, s));      // (a call without rows finalizes)
   HIPCHK(c, hipEventRecord(c->ev_a, s));
   HIPCHK(c, launch_sum_copies(H64, c->h_copies, d1, d1, 1, s));
   HIPCHK(c, launch_trace64(H64, d1, c->scal, s));
@@ -894,12 +907,12 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   c->timers[1] = elapsed(c);
   {   // mean duration of the Gram kernel's launches in the last chunk call that took the matrix-core path
     double tot = 0; int n = 0;
-    for (int i = 0; i < c->ev_g_used; i++) {
+    for (int i = 0; i < c->queue.ev_used; i++) {
       float ms = 0;
       if (hipEventElapsedTime(&ms, c->ev_g[2 * i], c->ev_g[2 * i + 1]) == hipSuccess) { tot += ms; n++; }
     }
-    c->timers[13] = n ? tot / n : 0; c->timers[14] = n; c->timers[15] = (double)c->ev_g_rows;
-    c->ev_g_used = 0;
+    c->timers[13] = n ? tot / n : 0; c->timers[14] = n; c->timers[15] = (double)c->queue.ev_rows;
+    c->queue.ev_used = 0; c->queue.ev_rows = 0;
   }
   for (auto& v : c->norms_host) v = std::sqrt(v);
   c->phase = osscar_ctx::FINAL;

@@ -50,16 +50,17 @@ static void build_tile_list(int tiles, std::vector<int2>& out) {
 // reads MFMA operands as single ds_read_b128: 16 neighbouring lanes read 16 neighbouring packets.
 // Accuracy: the MFMA accumulators are added (v_add_f32, round to nearest) to a second float32 register set every
 // `window` stages and restarted from zero, so the accumulation inside the matrix core never spans more than
-// window*64 tokens; the second set is added to the float64 H at the end of every range of the contraction.
+// window*64 tokens; the second set is added to the float64 H at the end of every range of the contraction.  (The wide kernel's
+// second set is float64.)
 // ------------------------------------------------------------------------------------------------
 constexpr int PK_SLOTS = 8 * 64;    // packets per (panel, stage)
-// first packet of the 8 x 8 block (kg, columns 8 cg ..) of a pair of panels in a stage
-__device__ __forceinline__ int64_t pack_slot(int pair, int nstages, int stage, int kg, int cg) {
-  return ((int64_t)(pair * 2 + (cg >> 3)) * nstages + stage) * PK_SLOTS + kg * 64 + (cg & 7) * 8;
+// first packet of the 8 x 8 block (kg, columns 8 cg ..) of a pair of panels in a stage; pstages: stages that a panel has room for
+__device__ __forceinline__ int64_t pack_slot(int pair, int pstages, int stage, int kg, int cg) {
+  return ((int64_t)(pair * 2 + (cg >> 3)) * pstages + stage) * PK_SLOTS + kg * 64 + (cg & 7) * 8;
 }
 
 __global__ __launch_bounds__(256) void gram_pack_kernel(const uint16_t* __restrict__ X, int64_t n_c, int64_t ldx, int d1,
-                                                         int npanels, uint4* __restrict__ Xp) {
+                                                         int npanels, uint4* __restrict__ Xp, int pstages, int stage0) {
   const int tid = threadIdx.x;
   const int panel = blockIdx.x * 2 + (tid >> 7);
   if (panel >= npanels) return;
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256) void gram_pack_kernel(const uint16_t* __restri
 #pragma unroll
   for (int r = 0; r < 8; r++)
     if (!live || row0 + r >= n_c) st[r] = uint4{0u, 0u, 0u, 0u};
-  uint4* out = Xp + pack_slot(panel, gridDim.y, blockIdx.y, kg, cg);
+  uint4* out = Xp + pack_slot(panel, pstages, stage0 + blockIdx.y, kg, cg);
 #define OSSCAR_PACK_LO(F) uint4{(st[0].F & 0xFFFFu) | (st[1].F << 16), (st[2].F & 0xFFFFu) | (st[3].F << 16), \
                                 (st[4].F & 0xFFFFu) | (st[5].F << 16), (st[6].F & 0xFFFFu) | (st[7].F << 16)}
 #define OSSCAR_PACK_HI(F) uint4{(st[0].F >> 16) | (st[1].F & 0xFFFF0000u), (st[2].F >> 16) | (st[3].F & 0xFFFF0000u), \
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(256) void gram_pack_kernel(const uint16_t* __restri
 
 // The same repacking for a convolutional layer: the 8 x 8 blocks are gathered from the feature map, patch by patch.
 __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __restrict__ F, ConvSpec cs, int64_t r0, int64_t n_c,
-                                                              int d1, int npanels, uint4* __restrict__ Xp) {
+                                                              int d1, int npanels, uint4* __restrict__ Xp, int pstages, int stage0) {
   const int tid = threadIdx.x;
   const int panel = blockIdx.x * 2 + (tid >> 7);
   if (panel >= npanels) return;
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __r
       v[j][r >> 1] |= (r & 1) ? (e << 16) : e;
     }
   }
-  uint4* out = Xp + pack_slot(panel, gridDim.y, blockIdx.y, kg, cg);
+  uint4* out = Xp + pack_slot(panel, pstages, stage0 + blockIdx.y, kg, cg);
 #pragma unroll
   for (int j = 0; j < 8; j++) out[j] = uint4{v[j][0], v[j][1], v[j][2], v[j][3]};
 }
@@ -133,8 +134,8 @@ __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __r
 // touches its tile in a launch, so these are plain loads and stores, a batch of 4 CT loads ahead of the batch that is stored
 // (or, atomics, additions that the few workgroups of a small launch do not wait for):
 // with atomics throughout 8192 columns, 2048 rows took 0.305 ms, 0.251 so, 0.19 without reading H64.
-template <int RT, int CT>
-__device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (&acc2)[RT][CT], double* __restrict__ H64, int ldo, int row0,
+template <int RT, int CT, typename A2>
+__device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const A2 (&acc2)[RT][CT], double* __restrict__ H64, int ldo, int row0,
                                          int col0, int rows_out, int cols_out, int symmetric, int lane, int atomics = 0) {
   // opaque: keeps the compiler from computing all the addresses and conditions ahead of the main loop
   int ldv = ldo;
@@ -188,7 +189,7 @@ __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const f16v (
 // the matrix core restart every `window` stages, and every `range` stages (a part is a whole number of ranges) the sums go to
 // float64: float32 never spans more than one range.
 __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_packed_kernel(
-    const uint4* __restrict__ Ap, const uint4* __restrict__ Bp, int nstages, int rows_out, int cols_out, int ldo,
+    const uint4* __restrict__ Ap, const uint4* __restrict__ Bp, int pstages, int nstages, int rows_out, int cols_out, int ldo,
     double* __restrict__ H64, int64_t copy_stride, const int2* __restrict__ tile_list, int stages_per_split, int window,
     int range, int symmetric, int atomics) {
   constexpr int WT = 2, TS = 128;
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int wm = wave >> 1, wn = wave & 1;
 
   f16v acc[WT][WT], acc2[WT][WT];
-  const int64_t pstride = (int64_t)nstages * PK_SLOTS;
+  const int64_t pstride = (int64_t)pstages * PK_SLOTS;
   const uint4* ga = Ap + 2 * tm * pstride + tid;
   const uint4* gb = Bp + 2 * tn * pstride + tid;
   uint4 ra0, ra1, ra2, ra3, rb0, rb1, rb2, rb3;
@@ -301,8 +302,10 @@ __global__ __launch_bounds__(256, 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // that way, 13.6 ms as here, 16.0 ms in 128 x 128 tiles; the layer's own activations: 11.5 against 16.3 ms.  Five buffers
 // were 1 % faster still, but their loop cannot end an accumulation window at 1024 tokens.  What bounds it: the matrix cores
 // are busy 55 % of the cycles, the requests' way into LDS takes most of the rest, and the clock falls to 1.8 GHz under this load.
+// CT = 2: the same in 256 x 128 tiles with the second accumulator set in float64 (the registers of a third column of MFMA tiles),
+// which takes every window's sums whole: for the rows of many calls in one launch, whose sums went to the float64 result one call at a time.
 // ------------------------------------------------------------------------------------------------
-constexpr int GW_R = 256, GW_C = 192, GW_A = 1024, GW_ST = 1024 + 768;      // packets of a 32-token stage: 4 panels of A, 3 of B
+constexpr int GW_R = 256, GW_C = 192, GW_A = 1024;      // packets of A in a 32-token stage: 4 panels (of B: CT panels)
 #define OSSCAR_GW_WAIT(n_) __builtin_amdgcn_s_waitcnt(((n_) & 15) | (7 << 4) | (15 << 8) | (((n_) >> 4) << 14))      // vmcnt <= n_
 #define OSSCAR_GW_BARRIER()                                                                                        \
   {                                                                                                                \
@@ -311,15 +314,24 @@ constexpr int GW_R = 256, GW_C = 192, GW_A = 1024, GW_ST = 1024 + 768;      // p
     __builtin_amdgcn_s_barrier();                                                                                  \
     asm volatile("" ::: "memory");                                                                                 \
   }
+typedef double d16v __attribute__((ext_vector_type(16)));
+template <int CT>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_wide_kernel(
-    const uint4* __restrict__ Ap, int a_panels, const uint4* __restrict__ Bp, int b_panels, int nstages, int rows_out, int cols_out,
-    int ldo, double* __restrict__ H64, const int2* __restrict__ tile_list, int window, int range, int symmetric) {
+    const uint4* __restrict__ Ap, int a_panels, const uint4* __restrict__ Bp, int b_panels, int pstages, int nstages, int rows_out,
+    int cols_out, int ldo, double* __restrict__ H64, int64_t copy_stride, const int2* __restrict__ tile_list, int per, int window, int range,
+    uint64_t ends_lo, uint64_t ends_hi, int symmetric) {
+  constexpr int TC = CT * 64, GW_ST = GW_A + CT * 256;
+  typedef typename std::conditional<CT == 2, double, float>::type A2;
+  typedef typename std::conditional<CT == 2, d16v, f16v>::type A2v;
   __shared__ uint4 lb0[GW_ST], lb1[GW_ST], lb2[GW_ST], lb3[GW_ST];
   const int2 tile = tile_list[blockIdx.x];
   if (tile.x < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int nst = nstages * 2;                       // stages of 32 tokens (so are window and range)
+  // stages of 32 tokens from here on (so are window and range); the part of the contraction that this workgroup takes
+  const int part = 2 * per * (int)blockIdx.y, nst = min(2 * nstages, part + 2 * per);
+  if (part >= nst) return;
+  H64 += (int64_t)blockIdx.y * copy_stride;
 #define OSSCAR_GW_LOAD(st_, buf_)                                                                               \
   {                                                                                                             \
     _Pragma("unroll") for (int i = 0; i < NL; i++)                                                              \
@@ -329,10 +341,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 #define OSSCAR_GW_READ(set_, buf_, ks_)                                                                         \
   {                                                                                                             \
     _Pragma("unroll") for (int a = 0; a < 2; a++) { uint4 v = buf_[oa + (ks_) * 2 * GW_R + a * 32]; fa[set_][a] = *reinterpret_cast<bf8*>(&v); } \
-    _Pragma("unroll") for (int b = 0; b < 3; b++) { uint4 v = buf_[ob + (ks_) * 2 * GW_C + b * 32]; fb[set_][b] = *reinterpret_cast<bf8*>(&v); } \
+    _Pragma("unroll") for (int b = 0; b < CT; b++) { uint4 v = buf_[ob + (ks_) * 2 * TC + b * 32]; fb[set_][b] = *reinterpret_cast<bf8*>(&v); } \
   }
 #define OSSCAR_GW_MULT(set_)                                                                                    \
-  _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < 3; b++)                   \
+  _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < CT; b++)                   \
     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set_][a], fb[set_][b], acc[a][b], 0, 0, 0);
 #define OSSCAR_GW_STEADY(st_, cur_, nxt_)                                                                       \
   {                                                                                                             \
@@ -356,39 +368,45 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     }                                                                                                           \
     OSSCAR_GW_MULT(1);                                                                                          \
   }
-#define OSSCAR_GW_FOLD()                                                                                        \
-  if ((in_window += 4) == window) {                                                                             \
-    in_window = 0;                                                                                              \
-    _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < 3; b++)                 \
-      _Pragma("unroll") for (int r = 0; r < 16; r++) { acc2[a][b][r] += acc[a][b][r]; acc[a][b][r] = 0.f; }     \
+// a window ends every 1024 tokens (window stages) and where the rows of a call end; four stages ending at st_ + 4 have been added
+#define OSSCAR_GW_FOLD(st_)                                                                                     \
+  {                                                                                                             \
+    const int quad_ = (st_) >> 2;                                                                               \
+    in_window += 4;                                                                                             \
+    if (in_window >= window || (CT == 2 && (((quad_ < 64 ? ends_lo : ends_hi) >> (quad_ & 63)) & 1))) {         \
+      in_window = 0;                                                                                            \
+      _Pragma("unroll") for (int a = 0; a < 2; a++) _Pragma("unroll") for (int b = 0; b < CT; b++)               \
+        _Pragma("unroll") for (int r = 0; r < 16; r++) { acc2[a][b][r] += (A2)acc[a][b][r]; acc[a][b][r] = 0.f; } \
+    }                                                                                                           \
   }
   // Two copies of the loops.  Requests of 64 packets.  Waves 0 - 3: the four kg of one panel of A, four requests per stage; waves
-  // 4 - 7: one kg of the three panels of B, three requests (the count of a wait is a constant).  Panels past the last one are
+  // 4 - 7: one kg of the CT panels of B, CT requests (the count of a wait is a constant).  Panels past the last one are
   // read from the last one (their results are not written).
   auto run = [&](auto nl) {
     constexpr int NL = decltype(nl)::value;
-    for (int beg = 0; beg < nst; beg += range) {
+    for (int beg = part; beg < nst; beg += range) {
       int lv = lane;      // opaque: the addresses are formed again in every range instead of being held while a tile is added
       asm volatile("" : "+v"(lv));
       const uint4* gp[NL];
 #pragma unroll
       for (int i = 0; i < NL; i++) {
-        if (NL == 4) gp[i] = Ap + (int64_t)min(tile.x * 4 + wave, a_panels - 1) * nstages * PK_SLOTS + i * 64 + lv;
-        else gp[i] = Bp + (int64_t)min(tile.y * 3 + i, b_panels - 1) * nstages * PK_SLOTS + (wave - 4) * 64 + lv;
+        if (NL == 4) gp[i] = Ap + (int64_t)min(tile.x * 4 + wave, a_panels - 1) * pstages * PK_SLOTS + i * 64 + lv;
+        else gp[i] = Bp + (int64_t)min(tile.y * CT + i, b_panels - 1) * pstages * PK_SLOTS + (wave - 4) * 64 + lv;
       }
-      const int ldst = NL == 4 ? wave * 64 : GW_A + (wave - 4) * GW_C, lstep = NL == 4 ? GW_R : 64;
-      // in LDS: A as [kg][256 columns], then B as [kg][192 columns]
-      const int oa = (lv >> 5) * GW_R + wm * 64 + (lv & 31), ob = GW_A + (lv >> 5) * GW_C + wn * 96 + (lv & 31);
+      const int ldst = NL == 4 ? wave * 64 : GW_A + (wave - 4) * TC, lstep = NL == 4 ? GW_R : 64;
+      // in LDS: A as [kg][256 columns], then B as [kg][TC columns]
+      const int oa = (lv >> 5) * GW_R + wm * 64 + (lv & 31), ob = GW_A + (lv >> 5) * TC + wn * (TC / 2) + (lv & 31);
       const int end = min(beg + range, nst);
-      bf8 fa[2][2], fb[2][3];
-      f16v acc[2][3], acc2[2][3];
+      bf8 fa[2][2], fb[2][CT];
+      f16v acc[2][CT];
+      A2v acc2[2][CT];
 #pragma unroll
       for (int a = 0; a < 2; a++)
 #pragma unroll
-        for (int b = 0; b < 3; b++)
+        for (int b = 0; b < CT; b++)
 #pragma unroll
-          for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = 0.f; }
-      if (beg) OSSCAR_GW_BARRIER();      // the buffers are about to be filled again
+          for (int r = 0; r < 16; r++) { acc[a][b][r] = 0.f; acc2[a][b][r] = (A2)0; }
+      if (beg > part) OSSCAR_GW_BARRIER();      // the buffers are about to be filled again
       OSSCAR_GW_LOAD(beg, lb0); OSSCAR_GW_LOAD(beg + 1, lb1);      // a whole number of 64-token stages
       if (beg + 2 < end) { OSSCAR_GW_LOAD(beg + 2, lb2); OSSCAR_GW_LOAD(beg + 3, lb3); }
       if (beg + 4 <= end) OSSCAR_GW_WAIT(3 * NL); else OSSCAR_GW_WAIT(0);
@@ -399,18 +417,18 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         do {
           OSSCAR_GW_STEADY(st, lb0, lb1); OSSCAR_GW_STEADY(st + 1, lb1, lb2);
           OSSCAR_GW_STEADY(st + 2, lb2, lb3); OSSCAR_GW_STEADY(st + 3, lb3, lb0);
-          OSSCAR_GW_FOLD();
+          OSSCAR_GW_FOLD(st);
           st += 4;
         } while (st + 8 <= end);
       }
       for (; st < end; st += 4) {
         OSSCAR_GW_TAIL(st, lb0, lb1); OSSCAR_GW_TAIL(st + 1, lb1, lb2); OSSCAR_GW_TAIL(st + 2, lb2, lb3); OSSCAR_GW_TAIL(st + 3, lb3, lb0);
-        if (st + 4 < end) OSSCAR_GW_FOLD();      // the last window goes to float64 by itself
+        if (st + 4 < end) OSSCAR_GW_FOLD(st);      // the last window goes to float64 by itself
       }
-      add_tile<2, 3>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * GW_C + wn * 96, rows_out, cols_out, symmetric, lane);
+      add_tile<2, CT>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * TC + wn * (TC / 2), rows_out, cols_out, symmetric, lane);
     }
   };
-  if (wave < 4) run(std::integral_constant<int, 4>{}); else run(std::integral_constant<int, 3>{});
+  if (wave < 4) run(std::integral_constant<int, 4>{}); else run(std::integral_constant<int, CT>{});
 #undef OSSCAR_GW_LOAD
 #undef OSSCAR_GW_READ
 #undef OSSCAR_GW_MULT
@@ -423,6 +441,10 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 void wide_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& out) {
   deal_tiles((rows + GW_R - 1) / GW_R, (cols + GW_C - 1) / GW_C, 4, 8,
              [&](int r, int c) { return !symmetric || c * GW_C <= std::min(rows, (r + 1) * GW_R) - 1; }, out);
+}
+// The same for its 256 x 128 tiles (blocks of 1024 x 1024).
+void tall_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& out) {
+  deal_tiles((rows + GW_R - 1) / GW_R, (cols + 127) / 128, 4, 8, [&](int r, int c) { return !symmetric || c * 128 <= std::min(rows, (r + 1) * GW_R) - 1; }, out);
 }
 size_t wide_tile_entries(int64_t rows, int64_t cols) { return (size_t)((rows + GW_R - 1) / GW_R * ((cols + GW_C - 1) / GW_C) + 8); }
 
@@ -490,65 +512,111 @@ __global__ void fill_zero_f64_kernel(double* __restrict__ p, int64_t n) {
 // Else 128 x 128 tiles, two workgroups per compute unit; when there are too few of them for the chip, the ranges are dealt to
 // up to acc.copies workgroups per tile, each adding to its own copy of Out; the caller adds the copies up in order (2048
 // columns, 2048 rows: 0.052 ms, 0.084 as four launches one after the other).
+// Rows of several calls (launch_gram_queue): 256 x 128 tiles with float64 windows, Out touched once.
 // Either way an element of a copy receives its additions from one thread, in order, so the result does not depend on scheduling.
 constexpr size_t GW_MIN_TILES = 128;
-constexpr int GW_MIN_STAGES = 32;
+constexpr int GW_MIN_STAGES = 32, GW_MIN_PART = 16;
 // A launch of the 128 x 128 kernel with fewer workgroups than this adds with atomics, which nobody waits for: 64 columns, 64 rows 7.7 us
 // against 11.3 with loads and stores, 1000 columns, 512 rows (36 workgroups) 13.7 and 18.7; 1000 columns, 2048 rows (144) 27.9 both;
 // 2048 columns, 2048 rows (272) 67.6 and 51.3.  Either way one thread adds to an element, in order.
 constexpr int64_t PLAIN_FROM = 128;
-static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int nstages, int rows_out, int cols_out, const PackedAcc& acc,
+// stages of a range of the 128 x 128 kernel
+static int packed_range(int nstages, int ntiles) {
+  const int ranges = ntiles < 1024 ? std::min(nstages, (2048 + ntiles - 1) / ntiles) : 1;
+  return std::max((nstages + ranges - 1) / ranges, std::min(nstages, 8));
+}
+// copies of a result that no earlier launch has used
+static void clear_copies(const PackedAcc& acc, int parts, int64_t elems, hipStream_t s) {
+  if (!acc.cleared || *acc.cleared >= parts) return;
+  hipLaunchKernelGGL(fill_zero_f64_kernel, dim3(2048), dim3(256), 0, s, acc.out + *acc.cleared * elems, (parts - *acc.cleared) * elems);
+  *acc.cleared = parts;
+}
+static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int pstages, int nstages, int rows_out, int cols_out, const PackedAcc& acc,
                                 const PackedTiles& t, int ntiles, int window, int symmetric, hipStream_t s) {
-  int ranges = ntiles < 1024 ? std::min(nstages, (2048 + ntiles - 1) / ntiles) : 1;
-  const int range = std::max((nstages + ranges - 1) / ranges, std::min(nstages, 8));
-  ranges = (nstages + range - 1) / range;
+  const int range = packed_range(nstages, ntiles), ranges = (nstages + range - 1) / range;
+  const int64_t elems = (int64_t)rows_out * cols_out;
   if (t.wide && t.wide_entries >= GW_MIN_TILES && nstages >= GW_MIN_STAGES && (ranges == 1 || range % window == 0)) {
-    hipLaunchKernelGGL(gram_wide_kernel, dim3((unsigned)t.wide_entries), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
-                       (cols_out + 127) / 128 * 2, nstages, rows_out, cols_out, cols_out, acc.out, t.wide, 2 * window, 2 * range, symmetric);
+    hipLaunchKernelGGL(gram_wide_kernel<3>, dim3((unsigned)t.wide_entries), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
+                       (cols_out + 127) / 128 * 2, pstages, nstages, rows_out, cols_out, cols_out, acc.out, elems, t.wide, nstages, 2 * window,
+                       2 * range, 0ull, 0ull, symmetric);
     return hipGetLastError();
   }
   const int per = (ranges + acc.copies - 1) / acc.copies * range, parts = (nstages + per - 1) / per;
+  clear_copies(acc, parts, elems, s);
+  hipLaunchKernelGGL(gram_packed_kernel, dim3((unsigned)t.entries, (unsigned)parts), dim3(256), (size_t)2 * 4 * PK_SLOTS * 16, s, Ap, Bp, pstages,
+                     nstages, rows_out, cols_out, cols_out, acc.out, elems, t.list, per, window, range, symmetric,
+                     (int64_t)ntiles * parts < PLAIN_FROM);
+  return hipGetLastError();
+}
+// Parts that the contraction of a queued product is cut into, each with its copy of the result: one workgroup per compute unit, and
+// at least GW_MIN_PART stages each; 0: too few workgroups even so (GW_MIN_TILES)
+static int queue_parts(int nstages, const PackedTiles& t, int copies) {
+  if (!t.tall || t.tall_entries == 0) return 0;
+  const int parts = std::max(1, std::min({copies, nstages / GW_MIN_PART, (int)((256 + t.tall_entries - 1) / t.tall_entries)}));
+  return t.tall_entries * parts >= GW_MIN_TILES ? parts : 0;
+}
+static hipError_t launch_queued(const uint4* Ap, const uint4* Bp, int pstages, const PackQueue& q, int window, int rows_out, int cols_out,
+                                const PackedAcc& acc, const PackedTiles& t, int symmetric, hipStream_t s) {
   const int64_t elems = (int64_t)rows_out * cols_out;
-  if (acc.cleared && *acc.cleared < parts) {      // copies that no earlier call of this result has used
-    hipLaunchKernelGGL(fill_zero_f64_kernel, dim3(2048), dim3(256), 0, s, acc.out + *acc.cleared * elems, (parts - *acc.cleared) * elems);
-    *acc.cleared = parts;
-  }
-  hipLaunchKernelGGL(gram_packed_kernel, dim3((unsigned)t.entries, (unsigned)parts), dim3(256), (size_t)2 * 4 * PK_SLOTS * 16, s, Ap, Bp, nstages,
-                     rows_out, cols_out, cols_out, acc.out, elems, t.list, per, window, range, symmetric, (int64_t)ntiles * parts < PLAIN_FROM);
+  const int most = std::max(1, queue_parts(q.stages, t, acc.copies)), per = ((q.stages + most - 1) / most + 1) / 2 * 2, parts = (q.stages + per - 1) / per;
+  clear_copies(acc, parts, elems, s);
+  hipLaunchKernelGGL(gram_wide_kernel<2>, dim3((unsigned)t.tall_entries, (unsigned)parts), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
+                     (cols_out + 127) / 128 * 2, pstages, q.stages, rows_out, cols_out, cols_out, acc.out, elems, t.tall, per, 2 * window, 2 * per,
+                     q.ends[0], q.ends[1], symmetric);
   return hipGetLastError();
 }
 
-hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, const PackedAcc& H64, const PackedTiles& tiles,
-                              void* pack_buf, int64_t pack_rows, hipStream_t s, const void* Yc, int64_t ldy, int m, const PackedAcc& G64,
-                              const PackedTiles& tiles_y, void* pack_buf_y, const ConvSpec* conv, hipEvent_t* ev, int ev_pairs, int* ev_used) {
-  if (ev_used) *ev_used = 0;
+// Rows of calls that do not fill pack_x (and pack_y) wait there until it is full: a launch per call of 2048 rows reads and writes all of
+// the float64 result for them.  Every call's rows begin a window of their own and the windows are no longer than the call by itself
+// would make them, so no float32 sum is longer than in a launch per call.  16384 rows in calls of 2048: 8192 columns 1.23 ms (8 launches of
+// 0.20 before), 2048 columns 0.093 ms (8 of 0.043); the error of H is the same (rms 1.29e-8 and 9.2e-9 of sqrt(H_ii H_jj) either way).
+hipError_t launch_gram_queue(const PackedGram& g, hipStream_t s) {
+  PackQueue& q = *g.q;
+  if (q.stages == 0) return hipSuccess;
+  const int npairs = (g.d1 + 127) / 128, npairs_y = g.pack_y ? (g.m + 127) / 128 : 0;
+  const uint4 *Xp = reinterpret_cast<const uint4*>(g.pack_x), *Yp = reinterpret_cast<const uint4*>(g.pack_y);
+  const bool timed = g.ev && q.ev_used < g.ev_pairs, several = q.calls > 1;
+  if (timed) hipEventRecord(g.ev[2 * q.ev_used], s);
+  hipError_t e = several ? launch_queued(Xp, Xp, g.pack_stages, q, q.window, g.d1, g.d1, g.H64, g.tiles, 1, s)
+                         : launch_packed(Xp, Xp, g.pack_stages, q.last, g.d1, g.d1, g.H64, g.tiles, npairs * (npairs + 1) / 2, 16, 1, s);
+  if (e != hipSuccess) return e;
+  if (timed) { hipEventRecord(g.ev[2 * q.ev_used + 1], s); q.ev_used++; q.ev_rows += q.rows; }
+  if (g.pack_y)
+    e = several ? launch_queued(Xp, Yp, g.pack_stages, q, q.window_y, g.d1, g.m, g.G64, g.tiles_y, 0, s)
+                : launch_packed(Xp, Yp, g.pack_stages, q.last, g.d1, g.m, g.G64, g.tiles_y, npairs * npairs_y, 16, 0, s);
+  q.clear();
+  return e;
+}
+hipError_t launch_gram_packed(const PackedGram& g, const void* Xc, int64_t n_c, int64_t ldx, const void* Yc, int64_t ldy, const ConvSpec* conv,
+                              hipStream_t s) {
+  PackQueue& q = *g.q;
   if (n_c <= 0) return hipSuccess;
-  if (pack_rows < GBK || pack_rows % GBK || !tiles.list || tiles.entries == 0) return hipErrorInvalidValue;
-  if (Yc && (!tiles_y.list || tiles_y.entries == 0)) return hipErrorInvalidValue;
-  const int npairs = (d1 + 127) / 128, npairs_y = Yc ? (m + 127) / 128 : 0;
-  const int ntiles = npairs * (npairs + 1) / 2, window = 16;   // 1024 tokens per MFMA accumulation window
-  for (int64_t r0 = 0; r0 < n_c; r0 += pack_rows) {
-    const int64_t nr = std::min<int64_t>(pack_rows, n_c - r0);
-    const int nstages = (int)((nr + GBK - 1) / GBK);
-    const uint16_t* src = reinterpret_cast<const uint16_t*>(Xc) + r0 * ldx;
-    const uint4* Xp = reinterpret_cast<const uint4*>(pack_buf);
+  if (g.pack_stages < 2 || g.pack_stages > 256 || g.pack_stages % 2 || !g.tiles.list || g.tiles.entries == 0) return hipErrorInvalidValue;
+  if (Yc && (!g.pack_y || !g.tiles_y.list || g.tiles_y.entries == 0)) return hipErrorInvalidValue;
+  const int npairs = (g.d1 + 127) / 128, npairs_y = Yc ? (g.m + 127) / 128 : 0, ntiles = npairs * (npairs + 1) / 2;
+  const bool waits = queue_parts(g.pack_stages, g.tiles, g.H64.copies) > 0 && (!Yc || queue_parts(g.pack_stages, g.tiles_y, g.G64.copies) > 0);
+  for (int64_t r0 = 0; r0 < n_c;) {
+    const int64_t nr = std::min<int64_t>((int64_t)(g.pack_stages - q.stages) * GBK, n_c - r0);
+    const int nst = (int)((nr + GBK - 1) / GBK), used = (nst + 1) / 2 * 2;      // an even number of stages: the wide kernel's windows
     if (conv)
-      hipLaunchKernelGGL(gram_pack_conv_kernel, dim3((npairs + 1) / 2, nstages), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(Xc),
-                         *conv, r0, nr, d1, npairs, reinterpret_cast<uint4*>(pack_buf));
+      hipLaunchKernelGGL(gram_pack_conv_kernel, dim3((npairs + 1) / 2, used), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(Xc),
+                         *conv, r0, nr, g.d1, npairs, reinterpret_cast<uint4*>(g.pack_x), g.pack_stages, q.stages);
     else
-      hipLaunchKernelGGL(gram_pack_kernel, dim3((npairs + 1) / 2, nstages), dim3(256), 0, s, src, nr, ldx, d1, npairs,
-                         reinterpret_cast<uint4*>(pack_buf));
-    const bool timed = ev && ev_used && *ev_used < ev_pairs;
-    if (timed) hipEventRecord(ev[2 * *ev_used], s);
-    hipError_t e = launch_packed(Xp, Xp, nstages, d1, d1, H64, tiles, ntiles, window, 1, s);
-    if (e != hipSuccess) return e;
-    if (timed) { hipEventRecord(ev[2 * *ev_used + 1], s); ++*ev_used; }
-    if (Yc) {
-      const uint16_t* srcy = reinterpret_cast<const uint16_t*>(Yc) + r0 * ldy;
-      const uint4* Yp = reinterpret_cast<const uint4*>(pack_buf_y);
-      hipLaunchKernelGGL(gram_pack_kernel, dim3((npairs_y + 1) / 2, nstages), dim3(256), 0, s, srcy, nr, ldy, m, npairs_y,
-                         reinterpret_cast<uint4*>(pack_buf_y));
-      if ((e = launch_packed(Xp, Yp, nstages, d1, m, G64, tiles_y, npairs * npairs_y, window, 0, s)) != hipSuccess) return e;
+      hipLaunchKernelGGL(gram_pack_kernel, dim3((npairs + 1) / 2, used), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(Xc) + r0 * ldx, nr, ldx,
+                         g.d1, npairs, reinterpret_cast<uint4*>(g.pack_x), g.pack_stages, q.stages);
+    if (Yc)
+      hipLaunchKernelGGL(gram_pack_kernel, dim3((npairs_y + 1) / 2, used), dim3(256), 0, s, reinterpret_cast<const uint16_t*>(Yc) + r0 * ldy, nr, ldy,
+                         g.m, npairs_y, reinterpret_cast<uint4*>(g.pack_y), g.pack_stages, q.stages);
+    q.stages += used; q.last = nst; q.rows += nr; q.calls++;
+    auto shorten = [&](int& window, int range) { if (range < nst) window = std::min(window, std::max(2, range / 2 * 2)); };
+    shorten(q.window, packed_range(nst, ntiles));
+    if (Yc) shorten(q.window_y, packed_range(nst, npairs * npairs_y));
+    const int pair = q.stages / 2 - 1;
+    q.ends[pair >> 6] |= 1ull << (pair & 63);
+    r0 += nr;
+    if (!waits || q.stages == g.pack_stages) {
+      const hipError_t e = launch_gram_queue(g, s);
+      if (e != hipSuccess) return e;
     }
   }
   return hipGetLastError();
@@ -612,11 +680,11 @@ hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, i
     const int64_t nr = std::min<int64_t>(pack_rows, d1 - r0);
     const int nstages = (int)((nr + GBK - 1) / GBK);
     hipLaunchKernelGGL(gram_pack_kernel, dim3((npanels_w + 1) / 2, nstages), dim3(256), 0, s,
-                       reinterpret_cast<const uint16_t*>(W) + r0 * ldw, nr, ldw, m, npanels_w, reinterpret_cast<uint4*>(pack_w));
+                       reinterpret_cast<const uint16_t*>(W) + r0 * ldw, nr, ldw, m, npanels_w, reinterpret_cast<uint4*>(pack_w), nstages, 0);
     for (int piece = 0; piece < 3; piece++) {
       hipLaunchKernelGGL(gram_pack_split_kernel, dim3((npanels + 1) / 2, nstages), dim3(256), 0, s, H + r0 * d1, nr, (int64_t)d1, d1,
                          npanels, piece, reinterpret_cast<uint4*>(pack_h));
-      const hipError_t e = launch_packed(reinterpret_cast<const uint4*>(pack_h), reinterpret_cast<const uint4*>(pack_w), nstages, d1, m,
+      const hipError_t e = launch_packed(reinterpret_cast<const uint4*>(pack_h), reinterpret_cast<const uint4*>(pack_w), nstages, nstages, d1, m,
                                          PackedAcc{G64, 1, nullptr}, tiles, npanels * npanels_w, window, 0, s);
       if (e != hipSuccess) return e;
     }
@@ -670,7 +738,7 @@ hipError_t launch_split_product(const void* packA, int M, const void* packB, int
   static const int combo[6][2] = {{0, 0}, {0, 1}, {1, 0}, {1, 1}, {0, 2}, {2, 0}};
   for (int c = 0; c < nprod; c++)
     if ((e = launch_packed(reinterpret_cast<const uint4*>(packA) + combo[c][0] * pieceA, reinterpret_cast<const uint4*>(packB) + combo[c][1] * pieceB,
-                           nstages, M, N, PackedAcc{acc, 1, nullptr}, tiles, ntiles, 16, 0, s)) != hipSuccess) return e;
+                           nstages, nstages, M, N, PackedAcc{acc, 1, nullptr}, tiles, ntiles, 16, 0, s)) != hipSuccess) return e;
   return hipGetLastError();
 }
 

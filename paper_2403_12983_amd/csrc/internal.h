@@ -84,8 +84,10 @@ hipError_t launch_i8_gemm(const GemmArgs& g, void* packA, size_t capA, void* pac
 // gram.hip : H64 (+)= Xc^T Xc on the lower-triangle tiles (bf16 X, d1 % 8 == 0, ldx % 8 == 0, 16-byte aligned)
 // ----------------------------------------------------------------------------------------------
 // Tile schedules of a packed product on the device, uploaded once by the caller (no call here waits for the stream): 128 x 128
-// tiles (gram_tile_list_host / rect_tile_list_host) and, optionally, 256 x 192 tiles (wide_tile_list_host).
-struct PackedTiles { const int2* list = nullptr; size_t entries = 0; const int2* wide = nullptr; size_t wide_entries = 0; };
+// tiles (gram_tile_list_host / rect_tile_list_host) and, optionally, 256 x 192 tiles (wide_tile_list_host) and 256 x 128 tiles
+// (tall_tile_list_host).
+struct PackedTiles { const int2* list = nullptr; size_t entries = 0; const int2* wide = nullptr; size_t wide_entries = 0;
+                     const int2* tall = nullptr; size_t tall_entries = 0; };
 // A float64 result that is accumulated over calls, as the sum of up to `copies` consecutive copies of it; *cleared = how many of
 // them hold something (or zeros) so far, nullptr: the caller has cleared all.
 struct PackedAcc { double* out = nullptr; int copies = 1; int* cleared = nullptr; };
@@ -94,23 +96,34 @@ int packed_copies(int64_t elems, int64_t ntiles);      // copies worth keeping f
 // Patch geometry of a convolutional layer: row (b*Hout + oy)*Wout + ox, column (c*kh + dy)*kw + dx of the patch matrix is
 // F[b][c][oy*stride + dy - pad][ox*stride + dx - pad] (zero outside the map).
 struct ConvSpec { int B, C, Hin, Win, kh, kw, stride, pad, Hout, Wout; };
-// Repacks `pack_rows`-token chunks of Xc into MFMA operand order in pack_buf (pack_rows * 128*ceil(d1/128) * 2 bytes)
-// and accumulates them into H64.
-hipError_t launch_gram_packed(const void* Xc, int64_t n_c, int64_t ldx, int d1, const PackedAcc& H64, const PackedTiles& tiles,
-                              void* pack_buf, int64_t pack_rows, hipStream_t s, const void* Yc = nullptr, int64_t ldy = 0, int m = 0,
-                              const PackedAcc& G64 = PackedAcc(), const PackedTiles& tiles_y = PackedTiles(), void* pack_buf_y = nullptr,
-                              const ConvSpec* conv = nullptr, hipEvent_t* ev = nullptr, int ev_pairs = 0, int* ev_used = nullptr);
-// ev (optional, 2 * ev_pairs events): recorded before and after each launch of the symmetric product kernel (one per
-// pack_rows chunk), *ev_used = pairs recorded
+// What waits in the pack buffers: stages of 64 rows, where the rows of a call end (a bit per pair of stages), the windows' length
+struct PackQueue {
+  int stages = 0, last = 0, calls = 0, window = 16, window_y = 16;      // last: stages of the last call's rows
+  uint64_t ends[2] = {0, 0};
+  int64_t rows = 0;
+  int ev_used = 0; int64_t ev_rows = 0;      // event pairs recorded by the launches since the caller cleared them, rows of these launches
+  void clear() { stages = calls = 0; window = window_y = 16; ends[0] = ends[1] = 0; rows = 0; }
+};
+// H64 += X^T X (lower triangle) and, with pack_y, G64 += X^T Y from bf16 rows.  pack_x: pack_stages (<= 256) * 64 rows of 128*ceil(d1/128)
+// bf16, pack_y of 128*ceil(m/128).  ev (optional, 2 * ev_pairs events): recorded before and after launches of the symmetric product.
+struct PackedGram {
+  PackQueue* q;
+  int d1; PackedAcc H64; PackedTiles tiles; void* pack_x;
+  int m; PackedAcc G64; PackedTiles tiles_y; void* pack_y;
+  int pack_stages; hipEvent_t* ev; int ev_pairs;
+};
+// Repacks rows into MFMA operand order and accumulates their products, at once or when the buffer is full; launch_gram_queue adds
+// what still waits.  conv (optional): Xc is a feature map (NCHW, bf16) and the rows are its patches.
+hipError_t launch_gram_packed(const PackedGram& g, const void* Xc, int64_t n_c, int64_t ldx, const void* Yc, int64_t ldy, const ConvSpec* conv,
+                              hipStream_t s);
+hipError_t launch_gram_queue(const PackedGram& g, hipStream_t s);
 // host-side schedules: lower-triangle tiles of a d1 x d1 result / all tiles of a d1 x m result (128 x 128 tiles)
 void gram_tile_list_host(int d1, std::vector<int2>& out);
 void rect_tile_list_host(int d1, int m, std::vector<int2>& out);
 // the same for the 256 x 192 tiles of a rows x cols result (symmetric: of its lower triangle)
 void wide_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& out);
+void tall_tile_list_host(int rows, int cols, bool symmetric, std::vector<int2>& out);
 size_t wide_tile_entries(int64_t rows, int64_t cols);      // an upper bound of that list's length
-// conv (optional): Xc is a feature map (NCHW, bf16) and the rows are its patches
-// Yc (optional, bf16 n_c x m): also G64 (d1 x m, float64) += Xc^T Yc, with its own tile list (>= 8 * (ceil(d1/128) *
-// ceil(m/128) / 8 + 64) entries) and pack buffer (pack_rows * 128*ceil(m/128) * 2 bytes)
 int gram_tile_schedule(int tiles_per_side, int32_t* out, int capacity);   // host only: the tile order of the SYRK kernel
 // G64 (zeroed by the caller) += H W for bf16 W through three bf16 pieces of the float32 H (see gram.hip)
 hipError_t launch_hw_split(const float* H, int d1, const void* W, int64_t ldw, int m, double* G64, const PackedTiles& tiles,

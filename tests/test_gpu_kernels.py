@@ -546,3 +546,40 @@ def test_swaps_in_one_launch(p, m, k, swaps):
         assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-6, atol=0)
         if n == swaps:
             assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
+
+
+@pytest.mark.parametrize("target", [False, True])
+@pytest.mark.parametrize("d1,m,chunks", [(1096, 72, [1, 2048, 63, 700, 0]), (2048, 8, [2048] * 9), (2056, 520, [16384 - 128, 64, 64, 1, -130, 200]),
+                                         (1504, 40, [5000, 20000, 5000, 0]), (8, 8, [70, 1, 300])])
+def test_rows_of_several_calls_in_one_product(d1, m, chunks, target):
+    """Calls whose rows wait for a full buffer: one row, rows up to the buffer's last stage, more than a buffer, a chunk at another alignment
+    in between (negative), a last call without rows.  The activations are small whole numbers, so every sum is exact in float32 (below
+    2^24) and H and G must be exact; in the first two columns only three rows, of different calls, are not zero: they contribute 2^25, 1 and
+    -2^25 to an entry, and meet in float64."""
+    n = sum(abs(c) for c in chunks)
+    g = torch.Generator(device=DEV).manual_seed(d1 + n)
+    X = torch.randint(-3, 4, (n, d1), generator=g, device=DEV).bfloat16()
+    Y = torch.randint(-3, 4, (n, m), generator=g, device=DEV).bfloat16()
+    X[:, :2] = 0.0
+    X[0, :2] = torch.tensor([2.0 ** 12, 2.0 ** 13], device=DEV).bfloat16()
+    X[abs(chunks[0]) + abs(chunks[1]) // 2, :2] = 1.0
+    X[n - 1, :2] = torch.tensor([2.0 ** 12, -2.0 ** 13], device=DEV).bfloat16()
+    W = torch.zeros(d1, m, dtype=torch.bfloat16, device=DEV)
+    s = _pkg().Solver(d1, m, d1, 1, d1 // 2, 1, torch.bfloat16, torch.bfloat16, DEV, target_output=target)
+    r0 = 0
+    for i, c in enumerate(chunks):
+        x, y = X[r0:r0 + abs(c)], Y[r0:r0 + abs(c)]
+        if c < 0:
+            x = torch.cat([x[:, :1], x], 1)[:, 1:]
+        args = (True, W, 0.0, 0.0) if i + 1 == len(chunks) else (False,)
+        s.osscar_gram_target(x, y, *args) if target else s.osscar_gram(x, *args)
+        r0 += abs(c)
+    H, G = s.osscar_get_tensor(0).double(), s.osscar_get_tensor(1).double()
+    s.close()
+    Xd = X.double()
+    Hr = Xd.T @ Xd
+    off = torch.ones(d1, d1, dtype=torch.bool, device=DEV)
+    off[0], off[:, 0], off[1], off[:, 1] = False, False, False, False      # beyond 2^24 but for the entry where the large terms cancel
+    assert torch.equal(H[off], Hr[off]) and H[0, 1] == Hr[0, 1] == H[1, 0] == 1.0
+    if target:
+        assert torch.equal(G[2:], (Xd.T @ Y.double())[2:])
