@@ -150,7 +150,9 @@ size_t swap_scratch(void* base, int64_t d1, LazyPtrs* L) {
   double* KT = cv.take<double>(LAZY_TM * LAZY_TM);
   double* K = cv.take<double>((LAZY_NC + LAZY_NS) * (LAZY_NC + LAZY_NS));
   SwapRec *rec = cv.take<SwapRec>(swap_record_count(d1)), *rec2 = cv.take<SwapRec>(swap_record_count(d1));
-  if (L) { L->Minv2 = M; L->KT = KT; L->K = K; L->rec = rec; L->rec2 = rec2; }
+  double* lval = cv.take<double>((LAZY_BT + 1) * (size_t)removal_list_count(d1));
+  int32_t* lrow = cv.take<int32_t>((LAZY_BT + 1) * (size_t)removal_list_count(d1));
+  if (L) { L->lval = lval; L->lrow = lrow; L->Minv2 = M; L->KT = KT; L->K = K; L->rec = rec; L->rec2 = rec2; }
   return cv.off;
 }
 
@@ -219,21 +221,15 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
     L.pos = cv.take<int32_t>(d1); L.Tidx = cv.take<int32_t>(TM); L.Jsg = cv.take<float>(TM);
     L.C0R = cv.take<float>(d1 * TM); L.Minv = cv.take<double>(TM * TM);
     L.ZT = cv.take<double>(TM * m); L.ZT32 = cv.take<float>(TM * m); L.E = cv.take<float>(d1 * TM);
-    L.xg = cv.take<double>(TM); L.xj = cv.take<double>(TM); L.u1 = cv.take<double>(4 * TM); L.u2 = cv.take<double>(4 * TM);      // GEMV_SPLIT partial sums per pending row
-    L.cg = cv.take<double>(d1); L.cj = cv.take<double>(d1); L.w1 = cv.take<double>(d1); L.w2 = cv.take<double>(d1);
-    L.y1 = cv.take<double>(m); L.y2 = cv.take<double>(m); L.y1f = cv.take<float>(m); L.y2f = cv.take<float>(m);
-    L.part = cv.take<double>(((m + 63) / 64) * 5); L.ls = cv.take<double>(16);
-    L.sel = cv.take<SelRec>((d1 + 31) / 32);
     L.GbT = cv.take<double>((int64_t)(LAZY_NC + LAZY_NS) * d1); L.Zc = cv.take<float>((int64_t)LAZY_NC * m);
     L.rowsq = cv.take<double>((int64_t)2 * ((m + 127) / 128) * d1);
     L.ZcP = cv.take<char>((int64_t)LAZY_NC * ((m + 31) / 32 * 32) * 6);
     L.Epk = cv.take<char>((int64_t)768 * ((d1 + 127) / 128 * 128)); L.Cpk = cv.take<char>((int64_t)768 * ((d1 + 127) / 128 * 128));
     L.Zpk = cv.take<char>((int64_t)768 * ((m + 127) / 128 * 128));
     L.cslot = cv.take<int32_t>(d1); L.cand = cv.take<int32_t>(LAZY_NC + LAZY_NS); L.tslot = cv.take<int32_t>(LAZY_TM);
-    L.misc = cv.take<int32_t>(8); L.lkey = cv.take<double>(2 * 64 * 32); L.lidx = cv.take<int32_t>(2 * 64 * 32);
-    L.bB = cv.take<double>(TM * LAZY_BT); L.bX = cv.take<double>(TM * LAZY_BT); L.bU = cv.take<double>(4 * TM * LAZY_BT);
-    L.bD = cv.take<double>(LAZY_BT * LAZY_BT); L.bYY = cv.take<double>(LAZY_BT * LAZY_BT); L.bY = cv.take<double>((int64_t)LAZY_BT * m);
-    L.bpart = cv.take<double>(((m + 63) / 64) * (LAZY_BT * LAZY_BT + LAZY_BT)); L.bdl = cv.take<double>(LAZY_BT);
+    L.lkey = cv.take<double>(2 * 64 * 32); L.lidx = cv.take<int32_t>(2 * 64 * 32);
+    L.bX = cv.take<double>(TM * LAZY_BT); L.bU = cv.take<double>(TM * LAZY_BT);
+    L.bD = cv.take<double>(LAZY_BT * LAZY_BT); L.bYY = cv.take<double>(LAZY_BT * LAZY_BT);
     L.bG = cv.take<int32_t>(LAZY_BT);
   }
   // scratch: the larger of the Gram phase and the init / refresh / backsolve phase
@@ -1007,16 +1003,21 @@ struct SwapRun {
   osscar_ctx* c; TabDims d; TabPtrs t; LazyPtrs L; int mode;
   int tau_most = 0;              // pending pivots after the launches so far, at most
   SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) {}
-  hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode, true); }
-  hipError_t swap(int always, int limit, int g = -1, int j = -1) {
+  hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode); }
+  hipError_t swap(int always, int limit, int g = -1, int j = -1, const int32_t* single = nullptr) {
     SearchCtrl* next = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
-    const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, nullptr, g, j);
+    const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, single, g, j);
     t.ctrl = next;
     std::swap(L.Minv, L.Minv2); std::swap(L.rec, L.rec2);
     tau_most = std::min(tau_most + 2, LAZY_TM);
     return e;
   }
-  hipError_t flush() { tau_most = 0; return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c), true); }
+  // removal of the row *single, iteration `iter` of the call: the second launch does it if the first had to fetch the row's products
+  hipError_t remove(const int32_t* single, int iter) {
+    const hipError_t e = swap(1, iter, -1, -1, single);
+    return e != hipSuccess ? e : swap(1, iter, -1, -1, single);
+  }
+  hipError_t flush() { tau_most = 0; return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c)); }
   hipError_t settle() {
     if (t.ctrl == c->ctrl) return hipSuccess;
     const hipError_t e = hipMemcpyAsync(c->ctrl, t.ctrl, sizeof(SearchCtrl), hipMemcpyDeviceToDevice, c->stream);
@@ -1055,22 +1056,21 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
   // groups of one row: delayed updates (the removals accumulate as pending pivots and reach N, Z by matrix products
   // once LAZY_TM of them are pending); larger groups: in-place rank-q updates
   const bool use_lazy = (q == 1) && !(flags & OSSCAR_SEARCH_EAGER);
-  const LazyPtrs& L = c->lazy;
   const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 1;
-  if (use_lazy) HIPCHK(c, launch_lazy_init(d, t, L, s, la_mode));
+  SwapRun run(c, d, t, la_mode);
+  if (use_lazy) HIPCHK(c, run.init());
   // Work is enqueued one batch at a time (a batch = the iterations that fit the pending set, or 256 removals in place) and
   // then checked: the delayed-update kernels may stop (pause) when a removed row was not among the rows whose products
   // were computed ahead and the spare slots ran out; the batch is then resumed after a flush from where it stopped.
-  // With the products computed ahead, the rows of one iteration leave as one block pivot (four launches per iteration
-  // instead of four per row; LAZY_BT rows per pivot at most); a block whose rows are not all among those products stops
+  // With the products computed ahead, the rows of one iteration leave as one block pivot (two launches per iteration,
+  // the pick among them; LAZY_BT rows per pivot at most); a block whose rows are not all among those products stops
   // the batch like a miss does, and the rest of its iteration is then applied row by row, which can fetch the missing
   // products.
   const bool use_block = use_lazy && la_mode == 1;
   int kept_now = p, iter = 0, since_refresh = 0, pending = 0, expected = 0;
   std::vector<int> takes;
-  auto step = [&](int i) -> hipError_t {
-    return use_lazy ? launch_lazy_iteration(d, t, L, 1, s, nullptr, c->g_pick + i)
-                    : launch_search_iteration(d, t, -1, -1, 1, s, nullptr, c->g_pick + i);
+  auto step = [&](int i, int iter_no) -> hipError_t {      // removal of the i-th pick, the iter_no-th of the call
+    return use_lazy ? run.remove(c->g_pick + i, iter_no) : launch_search_iteration(d, t, -1, -1, 1, s, nullptr, c->g_pick + i);
   };
   while (kept_now > k) {
     takes.clear();
@@ -1078,21 +1078,29 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
     while (kept_b > k) {
       const int take = std::min<int>(t_hat, kept_b - k);
       if (use_lazy ? (pending + batch + take > LAZY_TM) : (batch >= 256)) break;
-      HIPCHK(c, launch_greedy_pick(d, t, take, c->g_pick, c->g_gap + iter + (int)takes.size(), s));
-      if (use_block) {
-        for (int off = 0; off < take; off += LAZY_BT)      // more than LAZY_BT rows: several block pivots, same result
-          HIPCHK(c, launch_lazy_block_remove(d, t, L, std::min(LAZY_BT, take - off), c->g_pick + off, s));
+      float* gap = c->g_gap + iter + (int)takes.size();
+      if (use_block && take <= LAZY_BT) {
+        HIPCHK(c, launch_lazy_block_remove(d, run.t, run.L, take, true, run.tau_most, c->g_pick, gap, s));
+        run.tau_most = std::min(run.tau_most + take, LAZY_TM);
       } else {
-        for (int i = 0; i < take; i++) HIPCHK(c, step(i));
+        HIPCHK(c, launch_greedy_pick(d, run.t, take, c->g_pick, gap, s));
+        if (use_block) {
+          for (int off = 0; off < take; off += LAZY_BT) {      // more than LAZY_BT rows: several block pivots, same result
+            HIPCHK(c, launch_lazy_block_remove(d, run.t, run.L, std::min(LAZY_BT, take - off), false, run.tau_most, c->g_pick + off, nullptr, s));
+            run.tau_most = std::min(run.tau_most + LAZY_BT, LAZY_TM);
+          }
+        } else {
+          for (int i = 0; i < take; i++) HIPCHK(c, step(i, expected + batch + i + 1));
+        }
       }
       takes.push_back(take); batch += take; kept_b -= take;
     }
     if (takes.empty()) {   // the pending set is full: apply it and try again
-      HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c)));
+      HIPCHK(c, run.flush());
       pending = 0;
       continue;
     }
-    st = read_ctrl(c, &h);
+    st = read_ctrl(c, &h, run.t.ctrl);
     if (st != OSSCAR_OK) return st;
     if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_init_greedy: a pivot block lost definiteness after %d removals", h.iters);
     int done = h.iters - expected;
@@ -1102,8 +1110,9 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
       int acc = 0, it_idx = 0;
       while (acc + takes[it_idx] <= done) { acc += takes[it_idx]; it_idx++; }
       const int off = done - acc;                       // removals of iteration it_idx already applied
-      HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c)));       // also clears pause
-      for (int i = off; i < takes[it_idx]; i++) HIPCHK(c, step(i));   // its pick list is still on the device
+      HIPCHK(c, run.flush());       // also clears pause
+      for (int i = off; i < takes[it_idx]; i++) HIPCHK(c, step(i, h.iters + i - off + 1));   // its pick list is still on the device
+      if (use_block) HIPCHK(c, launch_removal_lists(d, run.t, run.L, s));
       pending = takes[it_idx] - off;
       batch = acc + takes[it_idx];
       iter += it_idx + 1;
@@ -1115,18 +1124,19 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
     kept_now -= batch;
     since_refresh += batch;
     const bool refresh = refresh_every > 0 && since_refresh >= refresh_every && kept_now > k;
-    if (use_lazy && (refresh || kept_now == k) && pending > 0) { HIPCHK(c, launch_lazy_flush(d, t, L, s, la_mode, side_of(c))); pending = 0; }
+    if (use_lazy && (refresh || kept_now == k) && pending > 0) { HIPCHK(c, run.flush()); pending = 0; }
     if (refresh) {
       st = read_kept(c);
       if (st != OSSCAR_OK) return st;
       c->kr = kept_now * q; c->cr = c->d1 - c->kr;
       st = build_state(c, &obj);
       if (st != OSSCAR_OK) return st;
-      HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(c->ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
-      if (use_lazy) HIPCHK(c, launch_lazy_init(d, t, L, s, la_mode));
+      HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(run.t.ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
+      if (use_lazy) HIPCHK(c, run.init());
       since_refresh = 0;
     }
   }
+  HIPCHK(c, run.settle());
   c->kr = k * q; c->cr = c->d1 - c->kr;
   st = read_ctrl(c, &h);
   if (st != OSSCAR_OK) return st;

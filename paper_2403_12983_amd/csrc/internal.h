@@ -243,8 +243,7 @@ constexpr int LAZY_NS = 64;      // spare slots for pivots that were not among t
 constexpr int LAZY_NPICK_OUT = 88;  // swap search: kept rows picked by cost of removal ...
 constexpr int LAZY_NPICK_IN = 72;   // ... and rows outside the kept set picked by gain; together a multiple of 32
 constexpr int LAZY_BT = 16;      // rows that one block removal of the nested schedule takes at most
-struct SelRec { double mn1, mn2, mx1, mx2; int32_t imn, imx; };   // best / second-best scores of a block of rows
-// the same for the one-launch swaps: [0] cheapest removal, [1] largest gain (negated); slot of the best row's products, -1 none
+// best and second best score of a block of rows: [0] cheapest removal, [1] largest gain (negated); slot of the best row's products, -1 none
 struct SwapRec { double best[2], second[2]; int32_t row[2], slot[2]; };
 struct LazyPtrs {
   int32_t* pos;     // d1: position in the pending set or -1
@@ -255,12 +254,6 @@ struct LazyPtrs {
   double* ZT;       // LAZY_TM x m: Minv * Z0[T, :]
   float* ZT32;      // LAZY_TM x m (flush)
   float* E;         // d1 x LAZY_TM: C0 * Minv (flush)
-  double* xg; double* xj; double* u1; double* u2;   // LAZY_TM
-  double* cg; double* cj; double* w1; double* w2;   // d1
-  double* y1; double* y2; float* y1f; float* y2f;   // m
-  double* part;     // ceil(m/64) * 5 partial sums
-  double* ls;       // 16 scalars
-  SelRec* sel;      // ceil(d1/32) per-block score records
   // products of Z0 with the rows of Z0 that are likely to become pivots before the next flush
   double* GbT;      // (LAZY_NC + LAZY_NS) x d1: row s = Z0 Z0[cand[s], :]^T
   double* rowsq;    // 2 ceil(m / 128) x d1: sums of squares of every row's 64-column stretches, left by Z0's update in the flush
@@ -274,20 +267,18 @@ struct LazyPtrs {
   int32_t* cslot;   // d1: slot of a row in GbT or -1
   int32_t* cand;    // LAZY_NC + LAZY_NS: row held by a slot or -1
   int32_t* tslot;   // LAZY_TM: slot of each pending pivot
-  int32_t* misc;    // [0] spare slots in use, [1] miss mask of the current pair (1: g, 2: j), [2] slot of g, [3] slot of j
   // one-launch swaps (in the phases' scratch, see carve_all): the other copy of M^-1, two copies of a record per workgroup, Gram
   // matrix of the base rows in the slots (LAZY_NC + LAZY_NS squared) and its part for the pending pivots (LAZY_TM squared)
   double* Minv2; SwapRec* rec; SwapRec* rec2; double* K; double* KT;
   double* lkey; int32_t* lidx;   // 2 x 64 x 32: per-block winners of the candidate selection
-  // block removal (nested schedule): b = N0[T, G], X = M^-1 b (LAZY_TM x LAZY_BT each), U = ZT Y^T (four partial sums of that
-  // shape, one per quarter of the columns), D, Y Y^T (LAZY_BT^2),
-  // Y (LAZY_BT x m), per-column-block partial sums, the changes of the objective, the picks
-  double* bB; double* bX; double* bU; double* bD; double* bYY; double* bY; double* bpart; double* bdl; int32_t* bG;
+  // block removal (nested schedule): X = M^-1 N0[T, G], U = ZT Y^T (LAZY_TM x LAZY_BT each), D, Y Y^T (LAZY_BT^2), the picks; the
+  // removal lists of every 64 rows (in the phases' scratch)
+  double* bX; double* bU; double* bD; double* bYY; int32_t* bG;
+  double* lval; int32_t* lrow;
 };
 // mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NC/2 cheapest removals + LAZY_NC/2 largest gains,
 // 1 = LAZY_NC cheapest removals (removal-only loops), 2 = none (every pivot then costs a pass over Z0)
-// swaps: the iterations are launch_lazy_swap's (else launch_lazy_iteration's and launch_lazy_block_remove's)
-hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0, bool swaps = false);
+hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0);
 // swap.hip: one swap in one launch, from the control block t.ctrl, L.Minv and L.rec to *next, L.Minv2 and L.rec2 (the caller exchanges
 // them after every launch); tau_most: at most this many pivots are pending
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int tau_most,
@@ -296,23 +287,21 @@ int swap_record_count(int64_t d1);
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
 hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);
 hipError_t launch_zt(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
-// ev (optional): events recorded before and after the pass over Z0, and at the end of the iteration
-// single (optional, device): removal of the one row *single instead of a swap; adds one pending pivot instead of two
-hipError_t launch_lazy_iteration(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int always_accept, hipStream_t s,
-                                 hipEvent_t* ev = nullptr, const int32_t* single = nullptr, int forced_out = -1,
-                                 int forced_in = -1);
 // A second stream and two events: the flush runs its update of N0 there, beside the candidate selection and the look-ahead
 // product on the main stream (they touch disjoint data), and joins before the scores are refreshed.
-// The `take` <= LAZY_BT rows in pick (device) leave the kept set as one block pivot (nested schedule, q = 1); does nothing
-// but set ctrl->pause if a pick is pending, is not among the rows whose products were computed ahead, or the pending set
+// `take` <= LAZY_BT rows leave the kept set as one block pivot (nested schedule, q = 1): those in pick (device), or (own_pick) the
+// cheapest ones, which are left there, with the relative gap to the next one in *gap; at most tau_most pivots are pending.  Does nothing
+// else but set ctrl->pause if a pick is pending, is not among the rows whose products were computed ahead, or the pending set
 // has no room for all of them.
-hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int take, const int32_t* pick,
-                                    hipStream_t s);
+hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int take, bool own_pick, int tau_most, int32_t* pick,
+                                    float* gap, hipStream_t s);
+int removal_list_count(int64_t d1);
+hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
 
 struct SideStream { hipStream_t stream = nullptr; hipEvent_t fork = nullptr, join = nullptr; };
 // side == nullptr (or no stream in it): everything in order on s
 hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0,
-                             const SideStream* side = nullptr, bool swaps = false);
+                             const SideStream* side = nullptr);
 
 hipError_t launch_scatter_rows(const float* src, int64_t lds, const int32_t* rows, int nrows, int ncols, void* dst,
                                int64_t ldd, int dst_is_bf16, hipStream_t s);

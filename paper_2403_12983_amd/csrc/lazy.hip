@@ -7,7 +7,7 @@
 //     N_cur[i, l] = N0[i, l] - C0[i, :] M^-1 C0[l, :]^T                (i, l outside T)
 //     N_cur[T, l] = J M^-1 C0[l, :]^T,    N_cur[T, T] = -J M^-1 J
 //     Z_cur[i, :] = Z0[i, :] - C0[i, :] ZT,   Z_cur[T, :] = J ZT,       ZT = M^-1 Z0[T, :]
-// so one iteration needs only two columns of N_cur and two rows of Z_cur (O(tau (d1 + m))), the diagonal
+// so one iteration needs only two columns of N_cur and the inner products of two rows of Z_cur, the diagonal
 // and the squared row norms of Z_cur for the scores of eq. (impact) -- both updated incrementally, the
 // norms through w = Z0 [y1 y2] -- and a bordering update of M^-1.
 // w without a pass over Z0: y1, y2 are combinations of the current rows g, j of Z, and these of base rows:
@@ -20,14 +20,8 @@
 // LAZY_TM/2 iterations the pending rank-tau correction is applied to N0 and Z0 by matrix products on the
 // matrix cores.  The sequence of swaps is exactly that of the eager search (Proposition 4.1, Cases 1-3).
 //
-// A swap is one launch (swap.hip).  A removal alone (the nested schedule's rows one by one) is four:
-//   prep    (1 workgroup)  : argmin / argmax from per-block partial records; x = M^-1 N0[T, {g, j}]; pivots
-//   vectors (rows | cols | rows) : current columns g, j of N; current rows g, j of Z scaled to y1, y2; partial sums;
-//                            and, independent of these, w = Z0 [y1 y2] from the cached products
-//   gemv    (rows)         : exact change of the objective and the acceptance test; u = ZT [y1 y2]; for a pivot that is
-//                            not among the candidates, its column Z0 Z0[g, :]^T by a pass over Z0
-//   update  (rows|cols|M)  : norms, diagonal, scores and their partial records; C0 append; ZT and M^-1 update
-//                            (after a miss also w, whose missing column exists only since gemv)
+// A swap, or the removal of one row, is one launch (swap.hip); the rows that an iteration of the nested schedule prunes leave as one block
+// pivot in two launches (below).
 #include "internal.h"
 #include "inverse16.h"
 #include "wave.h"
@@ -35,644 +29,12 @@
 
 namespace osscar {
 
-__device__ __forceinline__ bool idle(const SearchCtrl* c) { return (c->done | c->pause) != 0; }      // both in one round trip
 // pending pivots including those of the iteration that ran last (for kernels outside an iteration)
 __device__ __forceinline__ int tau_all(const SearchCtrl* c) { return c->tau + c->tau_inc; }
-
-constexpr int ROWS_PER_BLOCK = 32;   // row kernels: 8 lanes per row, 256 threads
-constexpr int COLS_PER_BLOCK = 64;   // column kernels: 64 columns x 4 slices of the pending set
-
-// ls[] slots
-enum { LS_DG = 0, LS_NJG = 1, LS_M1 = 2, LS_DJ = 3, LS_Y11 = 4, LS_Y22 = 5, LS_Y12 = 6, LS_OBJ = 8 };
-// misc[] slots
-enum { MI_SPARE = 0, MI_MISS = 1, MI_SG = 2, MI_SJ = 3 };
-
-// per-block record of the scores of rows [32 b, 32 b + 32): used after a flush; the update kernel writes the same records
-__global__ __launch_bounds__(64) void lazy_partials_kernel(LazyPtrs L, int p, const int32_t* __restrict__ kept,
-                                                            const double* __restrict__ score) {
-  const int h = blockIdx.x * ROWS_PER_BLOCK + threadIdx.x;
-  double mn1 = INFINITY, mn2 = INFINITY, mx1 = -INFINITY, mx2 = -INFINITY;
-  int imn = -1, imx = -1;
-  if (threadIdx.x < ROWS_PER_BLOCK && h < p) {
-    if (kept[h]) { mn1 = score[h]; imn = h; } else { mx1 = score[h]; imx = h; }
-  }
-  for (int o = 16; o > 0; o >>= 1) {
-    double b1 = __shfl_down(mn1, o, 64), b2 = __shfl_down(mn2, o, 64); int ib = __shfl_down(imn, o, 64);
-    merge_min(mn1, mn2, imn, b1, b2, ib);
-    b1 = __shfl_down(mx1, o, 64); b2 = __shfl_down(mx2, o, 64); ib = __shfl_down(imx, o, 64);
-    merge_max(mx1, mx2, imx, b1, b2, ib);
-  }
-  if (threadIdx.x == 0) {
-    SelRec r; r.mn1 = mn1; r.mn2 = mn2; r.mx1 = mx1; r.mx2 = mx2; r.imn = imn; r.imx = imx;
-    L.sel[blockIdx.x] = r;
-  }
-}
-
-// ---------------------------------------------------------------------------------------------- prep
-// One workgroup, a chain of round trips to memory (about 1.5 us each): the records, then everything that depends on the pick.
-// M^-1 (128 KB) does not, so it is requested first and waits in registers; the leaving and the entering side are picked by
-// four waves each, the second-best values (for the reported gaps) while the pivots' rows are on their way.  9.4 -> 6.9 us at 8192 rows.
-// single != nullptr: removal of the one row *single (Case 1 alone, nothing enters): the second pivot's quantities are zero.
-constexpr int PREP_T = 512;
-__global__ __launch_bounds__(PREP_T) void lazy_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int nrec,
-                                                         const int32_t* __restrict__ kept, SearchCtrl* ctrl, const int32_t* __restrict__ single, int forced_g,
-                                                         int forced_j) {
-  __shared__ double s_v[8], s_2nd[8];
-  __shared__ int s_i[8];
-  __shared__ double bg[LAZY_TM], bj[LAZY_TM], red[3][8], s_n0[3];
-  const int tid = threadIdx.x, wave = tid >> 6;
-  if (idle(ctrl)) return;
-  const int tau = tau_all(ctrl);           // every thread reads before thread 0 folds the increment in (after the barrier)
-  // argmin of the removal costs (waves 0 - 3) / argmax of the addition gains (waves 4 - 7, as the smallest of the negated
-  // gains) from the per-block records (lowest index wins ties, so the result does not depend on the order)
-  const int add = wave >= 4;
-  const double sign = add ? -1.0 : 1.0;
-  double a1[4], a2[4];
-  int ai[4];
-  auto request = [&](int r0) {             // four records in flight per thread; past the end, the first one again (not merged)
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const SelRec* c = L.sel + (r0 + 256 * k < nrec ? r0 + 256 * k : 0);
-      a1[k] = (&c->mn1)[2 * add]; a2[k] = (&c->mn2)[2 * add]; ai[k] = (&c->imn)[add];
-    }
-  };
-  request(tid & 255);
-  // behind the records (loads return in order): four threads per row of M^-1, a pair of columns out of every eight each
-  const int r = tid >> 2, quarter = tid & 3;
-  double2 mv[16];
-#pragma unroll
-  for (int u = 0; u < 16; u++) mv[u] = *reinterpret_cast<const double2*>(L.Minv + r * LAZY_TM + 8 * u + 2 * quarter);
-  asm volatile("" ::: "memory");
-  double v1 = INFINITY, v2 = INFINITY;
-  int i1 = -1;
-  auto merge = [&](int r0) {
-#pragma unroll
-    for (int k = 0; k < 4; k++)
-      if (r0 + 256 * k < nrec) merge_min(v1, v2, i1, sign * a1[k], sign * a2[k], ai[k]);
-  };
-  merge(tid & 255);                        // apart from the loop: its waits would count the requests for M^-1 in
-  for (int r0 = (tid & 255) + 1024; r0 < nrec; r0 += 1024) { request(r0); merge(r0); }
-  double wv = v1;
-  int wi = i1;
-  wave_min(wv, wi);
-  if ((tid & 63) == 63) { s_v[wave] = wv; s_i[wave] = wi; }
-  __syncthreads();
-  if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; }
-  // lanes 0 - 3 hold the leaving side's four results, 4 - 7 the entering side's: two steps leave each side's best in its quad
-  double qv = s_v[tid & 7];
-  int qi = s_i[tid & 7];
-  dpp_min_step<0xb1, 0xf>(qv, qi); dpp_min_step<0x4e, 0xf>(qv, qi);
-  const int pick_g = __builtin_amdgcn_readlane(qi, 0), pick_j = __builtin_amdgcn_readlane(qi, 4);
-  const int g = single ? *single : (forced_g >= 0 ? forced_g : pick_g);
-  const int j = single ? g : (forced_g >= 0 ? forced_j : pick_j);
-  if (g < 0 || j < 0 || (forced_g >= 0 && (!kept[g] || kept[j]))) {
-    if (tid == 0) { ctrl->done = 1; ctrl->g_out = -1; ctrl->g_in = -1; }
-    return;
-  }
-  // everything that depends on the pick in one round trip: b = N0[T, {g, j}] (these are rows g, j of C0), zero beyond tau,
-  // the three base entries of the pivot block, the slots
-  // (unconditional loads: a load under a condition is waited for where the condition ends)
-  const int side_b = tid >> 7, col_b = tid & (LAZY_TM - 1);      // threads 0 - 127: row g, 128 - 255: row j
-  const float b_raw = L.C0R[(int64_t)(side_b & 1 ? j : g) * LAZY_TM + col_b];
-  const int nr = tid == 256 ? g : j, nc = tid == 258 ? j : g;    // threads 256 - 258: (g, g), (j, g), (j, j)
-  const float n0 = N0[(int64_t)max(nr, nc) * d1 + min(nr, nc)];
-  const int sg0 = L.cslot[g], sj0 = L.cslot[j], pg0 = L.pos[g], pj0 = L.pos[j], spare = L.misc[MI_SPARE];
-  // second-best values: every thread's best unless it is the pick
-  const double sec = wave_min(i1 >= 0 && i1 != (add ? pick_j : pick_g) ? v1 : v2);
-  if ((tid & 63) == 63) s_2nd[wave] = sec;
-  const int need = (sg0 < 0 ? 1 : 0) + ((!single && sj0 < 0) ? 1 : 0);
-  if (pg0 >= 0 || pj0 >= 0 || tau + (single ? 1 : 2) > LAZY_TM || spare + need > LAZY_NS) {
-    if (tid == 0) ctrl->pause = 1;
-    return;
-  }
-  if (side_b == 0) bg[col_b] = col_b < tau ? (double)b_raw : 0.0;
-  if (side_b == 1) bj[col_b] = (col_b < tau && !single) ? (double)b_raw : 0.0;
-  if (tid >= 256 && tid < 259) s_n0[tid - 256] = (double)n0;
-  __syncthreads();
-  // x = M^-1 b (bg, bj are zero beyond tau, M^-1 is finite there)
-  double a = 0, b = 0;
-#pragma unroll
-  for (int u = 0; u < 16; u++) {
-    const double2 p = *reinterpret_cast<const double2*>(bg + 8 * u + 2 * quarter), q = *reinterpret_cast<const double2*>(bj + 8 * u + 2 * quarter);
-    a += mv[u].x * p.x + mv[u].y * p.y; b += mv[u].x * q.x + mv[u].y * q.y;
-  }
-  a += dpp_get<0xb1, 0xf>(a); b += dpp_get<0xb1, 0xf>(b);
-  a += dpp_get<0x4e, 0xf>(a); b += dpp_get<0x4e, 0xf>(b);
-  double pgg = 0, pjg = 0, pjj = 0;
-  if (quarter == 0) {
-    if (r >= tau) { a = 0; b = 0; }
-    L.xg[r] = a; L.xj[r] = b;
-    pgg = bg[r] * a; pjg = bj[r] * a; pjj = bj[r] * b;
-  }
-  pgg = wsum(pgg); pjg = wsum(pjg); pjj = wsum(pjj);
-  if ((tid & 63) == 0) { red[0][wave] = pgg; red[1][wave] = pjg; red[2][wave] = pjj; }
-  __syncthreads();
-  if (tid == 0) {
-    double sum[3];
-#pragma unroll
-    for (int k = 0; k < 3; k++) sum[k] = ((red[k][0] + red[k][1]) + (red[k][2] + red[k][3])) + ((red[k][4] + red[k][5]) + (red[k][6] + red[k][7]));
-    const double ngg = s_n0[0] - sum[0];
-    const double njg = s_n0[1] - sum[1];
-    const double njj = s_n0[2] - sum[2];
-    const bool bad1 = !(ngg < 0.0);                         // kept pivot: N_gg = -P_gg
-    const double Dg = 1.0 / (bad1 ? -1.0 : ngg);
-    double M1 = Dg * njg;
-    const double njjp = njj - njg * M1;                     // entering pivot after the first sweep: a Schur complement
-    bool bad2 = !(njjp > 0.0);
-    double Dj = 1.0 / (bad2 ? 1.0 : njjp);
-    if (single) { M1 = 0.0; Dj = 0.0; bad2 = false; }
-    L.ls[LS_DG] = Dg; L.ls[LS_NJG] = single ? 0.0 : njg; L.ls[LS_M1] = M1; L.ls[LS_DJ] = Dj; L.ls[LS_OBJ] = ctrl->obj;
-    if (bad1 || bad2) ctrl->notpd = 1;
-    ctrl->g_out = g; ctrl->g_in = j;
-    // slots of the two base columns; a pivot that is not among the candidates takes a spare slot, filled by the next kernel
-    int ns = spare, miss = 0, sg = sg0, sj = sj0;
-    if (sg < 0) { sg = LAZY_NC + ns++; L.cslot[g] = sg; L.cand[sg] = g; miss |= 1; }
-    if (single) sj = sg;
-    else if (sj < 0) { sj = LAZY_NC + ns++; L.cslot[j] = sj; L.cand[sj] = j; miss |= 2; }
-    L.misc[MI_SPARE] = ns; L.misc[MI_MISS] = miss; L.misc[MI_SG] = sg; L.misc[MI_SJ] = sj;
-    ctrl->misses += (miss & 1) + (miss >> 1);
-    const double m2 = fmin(fmin(s_2nd[0], s_2nd[1]), fmin(s_2nd[2], s_2nd[3])), x2 = fmin(fmin(s_2nd[4], s_2nd[5]), fmin(s_2nd[6], s_2nd[7]));
-    const double m1 = fmin(fmin(s_v[0], s_v[1]), fmin(s_v[2], s_v[3])), x1 = fmin(fmin(s_v[4], s_v[5]), fmin(s_v[6], s_v[7]));
-    ctrl->gap_rem = isfinite(m2) ? fabs(m2 - m1) / fmax(fabs(m1), 1e-300) : INFINITY;
-    ctrl->gap_add = isfinite(x2) ? fabs(x1 - x2) / fmax(fabs(x1), 1e-300) : INFINITY;
-  }
-}
-
-// ---------------------------------------------------------------------------------------------- vectors
-__device__ __forceinline__ void wcache_block(const LazyPtrs& L, int d1, const SearchCtrl* __restrict__ ctrl, int block);
-// 8 lanes of a row: sum_s C0R[row][s] * (xa[s], xb[s]) over the LAZY_TM columns (x is zero beyond tau)
-__device__ __forceinline__ void row_dots(const float* __restrict__ crow, const double* __restrict__ xa,
-                                         const double* __restrict__ xb, int l8, double& a, double& b) {
-  a = 0; b = 0;
-#pragma unroll
-  for (int t = 0; t < LAZY_TM / 32; t++) {
-    const int s = (l8 + 8 * t) * 4;
-    const float4 c = *reinterpret_cast<const float4*>(crow + s);
-    a += (double)c.x * xa[s] + (double)c.y * xa[s + 1] + (double)c.z * xa[s + 2] + (double)c.w * xa[s + 3];
-    b += (double)c.x * xb[s] + (double)c.y * xb[s + 1] + (double)c.z * xb[s + 2] + (double)c.w * xb[s + 3];
-  }
-  a = sum8(a); b = sum8(b);
-}
-
-__global__ __launch_bounds__(256) void lazy_vectors_kernel(LazyPtrs L, const float* __restrict__ N0, const float* __restrict__ Z0,
-                                                            int d1, int m, int row_blocks, int col_blocks,
-                                                            const SearchCtrl* __restrict__ ctrl) {
-  __shared__ double sa[LAZY_TM], sb[LAZY_TM];
-  __shared__ double zred[2][4][COLS_PER_BLOCK];
-  if (idle(ctrl)) return;
-  if ((int)blockIdx.x >= row_blocks + col_blocks) {   // w from the cached products (see wcache_block)
-    if (L.misc[MI_MISS] == 0) wcache_block(L, d1, ctrl, blockIdx.x - row_blocks - col_blocks);
-    return;
-  }
-  const int tid = threadIdx.x, g = ctrl->g_out, j = ctrl->g_in, tau = ctrl->tau;
-  if ((int)blockIdx.x < row_blocks) {
-    // current columns g and j of N
-    for (int s = tid; s < LAZY_TM; s += 256) { sa[s] = L.xg[s]; sb[s] = L.xj[s]; }
-    __syncthreads();
-    const int row = blockIdx.x * ROWS_PER_BLOCK + (tid >> 3), l8 = tid & 7;
-    if (row >= d1) return;
-    const int ps = L.pos[row];
-    double a, b;
-    row_dots(L.C0R + (int64_t)row * LAZY_TM, sa, sb, l8, a, b);
-    if (l8 == 0) {
-      if (ps >= 0) {
-        const double sg = (double)L.Jsg[ps];
-        L.cg[row] = sg * sa[ps]; L.cj[row] = sg * sb[ps];
-      } else {
-        L.cg[row] = (double)nsym1(N0, d1, row, g) - a;
-        L.cj[row] = (double)nsym1(N0, d1, row, j) - b;
-      }
-    }
-    return;
-  }
-  // current rows g and j of Z, scaled: y1 = Dg z_g, y2 = Dj (z_j - n_jg y1)
-  const int cb = blockIdx.x - row_blocks;
-  const int slice = tid >> 6, lc = tid & 63, col = cb * COLS_PER_BLOCK + lc;
-  // the base rows g, j of Z are requested first: their latency passes while ZT is read
-  float z0g = 0.f, z0j = 0.f;
-  if (slice == 0 && col < m) { z0g = Z0[(int64_t)g * m + col]; z0j = Z0[(int64_t)j * m + col]; }
-  for (int s = tid; s < LAZY_TM; s += 256) {
-    sa[s] = (s < tau) ? (double)L.C0R[(int64_t)g * LAZY_TM + s] : 0.0;
-    sb[s] = (s < tau) ? (double)L.C0R[(int64_t)j * LAZY_TM + s] : 0.0;
-  }
-  __syncthreads();
-  double pg = 0, pj = 0;
-  if (col < m)
-    for (int s = slice; s < tau; s += 64) {               // sixteen loads in flight
-      double zt[16];
-#pragma unroll
-      for (int u = 0; u < 16; u++) { const int ss = s + 4 * u; zt[u] = L.ZT[(int64_t)(ss < tau ? ss : s) * m + col]; }
-#pragma unroll
-      for (int u = 0; u < 16; u++) { const int ss = s + 4 * u; if (ss < tau) { pg += sa[ss] * zt[u]; pj += sb[ss] * zt[u]; } }
-    }
-  zred[0][slice][lc] = pg; zred[1][slice][lc] = pj;
-  __syncthreads();
-  if (slice != 0) return;
-  double v[5] = {0, 0, 0, 0, 0};
-  if (col < m) {
-    const double Dg = L.ls[LS_DG], njg = L.ls[LS_NJG], Dj = L.ls[LS_DJ];
-    const double zg = (double)z0g - (zred[0][0][lc] + zred[0][1][lc] + zred[0][2][lc] + zred[0][3][lc]);
-    const double zj = (double)z0j - (zred[1][0][lc] + zred[1][1][lc] + zred[1][2][lc] + zred[1][3][lc]);
-    const double y1 = Dg * zg, zjp = zj - njg * y1, y2 = Dj * zjp;
-    L.y1[col] = y1; L.y2[col] = y2; L.y1f[col] = (float)y1; L.y2f[col] = (float)y2;
-    v[0] = zg * y1; v[1] = zjp * y2; v[2] = y1 * y1; v[3] = y2 * y2; v[4] = y1 * y2;
-  }
-#pragma unroll
-  for (int k = 0; k < 5; k++) { const double t = wsum(v[k]); if (lc == 0) L.part[cb * 5 + k] = t; }
-}
-
-// ---------------------------------------------------------------------------------------------- gemv + accept
-// Every workgroup sums the partial records to the exact change of the objective (Case 3) and takes the same
-// accept / reject decision; workgroup 0 records it.  Then w1 = Z0 y1, w2 = Z0 y2 (read-only pass over Z0) and
-// u = ZT [y1 y2] in the leading workgroups.  Each wave owns 8 rows; y1, y2 are staged through LDS.
-constexpr int LAZY_CH = 4096;
-constexpr int GEMV_RPW = 4;        // rows per wave
-constexpr int GEMV_UNR = 4;        // float4 loads in flight per row and lane
-constexpr int GEMV_ROWS = 4 * GEMV_RPW;
-constexpr int GEMV_SPLIT = 4;      // leading workgroups per pending row of ZT (u1, u2 hold one partial sum per workgroup)
-
-__global__ __launch_bounds__(256) void lazy_gemv_kernel(LazyPtrs L, const float* __restrict__ Z0, int d1, int m, int col_blocks,
-                                                         SearchCtrl* ctrl, int always_accept, int32_t* trace_out,
-                                                         int32_t* trace_in, float* trace_gap, double* trace_obj, int npiv) {
-  __shared__ float sy1[LAZY_CH], sy2[LAZY_CH];
-  __shared__ int s_ok;
-  if (idle(ctrl)) return;
-  constexpr int ZTB = LAZY_TM * GEMV_SPLIT;           // leading workgroups: a GEMV_SPLIT-th of one pending row of ZT each
-  // the row workgroups have work only when a pivot's products were not computed ahead (workgroup 0 records the decision)
-  if ((int)blockIdx.x >= ZTB && L.misc[MI_MISS] == 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // The partial records of the acceptance sums are requested first (wave 0; lane l takes the records l, l + 64, ...), then
-  // the workgroup's part of u: both are in flight together and neither waits for the other's round trip.
-  double pr[2][5];
-#pragma unroll
-  for (int h = 0; h < 2; h++)
-#pragma unroll
-    for (int k = 0; k < 5; k++) { const int b = lane + 64 * h; pr[h][k] = (wave == 0 && b < col_blocks) ? L.part[b * 5 + k] : 0.0; }
-  // u = ZT [y1 y2]: started before the acceptance sums (it does not depend on them; a rejected swap, which ends the search,
-  // just discards it).  Each leading workgroup takes one stretch of columns of one pending row, so that a thread has all its
-  // loads in flight at once; the stretches' sums are added in a fixed order by the kernel that uses u.
-  double ua = 0, ub = 0;
-  const int urow = (int)blockIdx.x / GEMV_SPLIT, upart = (int)blockIdx.x % GEMV_SPLIT;
-  if ((int)blockIdx.x < ZTB && urow < ctrl->tau) {
-    const double* zt = L.ZT + (int64_t)urow * m;
-    const int chunk = (m + GEMV_SPLIT * 256 - 1) / (GEMV_SPLIT * 256) * 256;
-    const int c_begin = upart * chunk, c_end = min(m, c_begin + chunk);
-    for (int c0 = c_begin + tid; c0 < c_end; c0 += 2048) {             // eight columns in flight per thread
-      double z[8], p1[8], p2[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++) { const int c = c0 + 256 * u, cc = c < c_end ? c : c0; z[u] = zt[cc]; p1[u] = L.y1[cc]; p2[u] = L.y2[cc]; }
-#pragma unroll
-      for (int u = 0; u < 8; u++) if (c0 + 256 * u < c_end) { ua += z[u] * p1[u]; ub += z[u] * p2[u]; }
-    }
-  }
-  if (wave == 0) {
-    // partial sums in a fixed order: lane l adds the records l, l + 64, ...; then a wave reduction
-    double sk[5];
-#pragma unroll
-    for (int k = 0; k < 5; k++) sk[k] = pr[0][k] + pr[1][k];
-    for (int b = lane + 128; b < col_blocks; b += 64)
-#pragma unroll
-      for (int k = 0; k < 5; k++) sk[k] += L.part[b * 5 + k];
-#pragma unroll
-    for (int k = 0; k < 5; k++) { sk[k] = wsum(sk[k]); }
-    if (lane == 0) {
-      const double delta = -sk[0] - sk[1];
-      const double obj = L.ls[LS_OBJ];
-      const bool ok = !ctrl->notpd && (always_accept || delta < -ctrl->rel_tol * obj);
-      s_ok = ok ? 1 : 0;
-      if (blockIdx.x == 0) {
-        L.ls[LS_Y11] = sk[2]; L.ls[LS_Y22] = sk[3]; L.ls[LS_Y12] = sk[4];
-        ctrl->delta = delta;
-        const int it = ctrl->iters;
-        ctrl->iters = it + 1;
-        if (ok) { ctrl->obj = obj + delta; ctrl->accepted += 1; ctrl->tau_inc = npiv; } else { ctrl->done = 1; }
-        if (trace_out) trace_out[it] = ctrl->g_out;
-        if (trace_in) trace_in[it] = ctrl->g_in;
-        if (trace_gap) { trace_gap[2 * it] = (float)ctrl->gap_rem; trace_gap[2 * it + 1] = (float)ctrl->gap_add; }
-        if (trace_obj) trace_obj[it] = ok ? obj + delta : obj;
-      }
-    }
-  }
-  __syncthreads();
-  if (!s_ok) return;
-  if ((int)blockIdx.x < ZTB) {
-    __shared__ double ured[2][4];
-    const double a = wsum(ua), b = wsum(ub);
-    if (lane == 0) { ured[0][wave] = a; ured[1][wave] = b; }
-    __syncthreads();
-    if (tid == 0) {                                      // zero beyond tau
-      L.u1[upart * LAZY_TM + urow] = ured[0][0] + ured[0][1] + ured[0][2] + ured[0][3];
-      L.u2[upart * LAZY_TM + urow] = ured[1][0] + ured[1][1] + ured[1][2] + ured[1][3];
-    }
-    return;
-  }
-  // Pivots outside the candidate set: their columns Z0 Z0[g, :]^T, Z0 Z0[j, :]^T by one pass over Z0.  Each wave owns
-  // GEMV_RPW rows.  Products are summed four at a time in float32 (one float4 of Z0 against one of the pivot row) and the
-  // partial sums are accumulated in float64: the rounding this adds is below that of Z0's own float32 storage.
-  const int miss = L.misc[MI_MISS];
-  if (miss == 0) return;
-  const float* yg = Z0 + (int64_t)ctrl->g_out * m;
-  const float* yj = Z0 + (int64_t)ctrl->g_in * m;
-  const int row0 = ((int)blockIdx.x - ZTB) * GEMV_ROWS + wave * GEMV_RPW;
-  double a1[GEMV_RPW], a2[GEMV_RPW];
-  const float* rp[GEMV_RPW];
-#pragma unroll
-  for (int r = 0; r < GEMV_RPW; r++) {
-    a1[r] = 0; a2[r] = 0;
-    int row = row0 + r;
-    if (row > d1 - 1) row = d1 - 1;                 // clamped rows: their sums are discarded
-    rp[r] = Z0 + (int64_t)row * m;
-  }
-  const bool vec = (m % 4 == 0);
-  for (int c0 = 0; c0 < m; c0 += LAZY_CH) {
-    const int cw = (m - c0 < LAZY_CH) ? m - c0 : LAZY_CH;
-    __syncthreads();
-    for (int c = tid; c < cw; c += 256) { sy1[c] = yg[c0 + c]; sy2[c] = yj[c0 + c]; }
-    __syncthreads();
-    if (vec) {
-      for (int c = lane * 4; c < cw; c += 256 * GEMV_UNR) {
-        float4 z[GEMV_UNR][GEMV_RPW];
-#pragma unroll
-        for (int u = 0; u < GEMV_UNR; u++)
-#pragma unroll
-          for (int r = 0; r < GEMV_RPW; r++) {
-            const int cc = c + u * 256;
-            z[u][r] = (cc < cw) ? *reinterpret_cast<const float4*>(rp[r] + c0 + cc) : float4{0.f, 0.f, 0.f, 0.f};
-          }
-#pragma unroll
-        for (int u = 0; u < GEMV_UNR; u++) {
-          int cc = c + u * 256;
-          if (cc >= cw) cc = 0;
-          const float4 p1 = *reinterpret_cast<const float4*>(&sy1[cc]);
-          const float4 p2 = *reinterpret_cast<const float4*>(&sy2[cc]);
-#pragma unroll
-          for (int r = 0; r < GEMV_RPW; r++) {
-            const float4 v = z[u][r];
-            const float s1 = v.x * p1.x + v.y * p1.y + v.z * p1.z + v.w * p1.w;
-            const float s2 = v.x * p2.x + v.y * p2.y + v.z * p2.z + v.w * p2.w;
-            a1[r] += (double)s1; a2[r] += (double)s2;
-          }
-        }
-      }
-    } else {
-      for (int c = lane; c < cw; c += 64) {
-        const double p1 = sy1[c], p2 = sy2[c];
-#pragma unroll
-        for (int r = 0; r < GEMV_RPW; r++) {
-          const double z = (double)rp[r][c0 + c];
-          a1[r] += z * p1; a2[r] += z * p2;
-        }
-      }
-    }
-  }
-  double* colg = L.GbT + (int64_t)L.misc[MI_SG] * d1;
-  double* colj = L.GbT + (int64_t)L.misc[MI_SJ] * d1;
-#pragma unroll
-  for (int r = 0; r < GEMV_RPW; r++) {
-    double t1 = wsum(a1[r]), t2 = wsum(a2[r]);
-    const int row = row0 + r;
-    if (lane == 0 && row < d1) {
-      if (miss & 1) colg[row] = t1;
-      if (miss & 2) colj[row] = t2;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------- wcache
-// w1 = Z0 y1, w2 = Z0 y2 from the cached base products: with a_g = col(g) - sum_r x_g[r] col(T_r) (= Z0 z_g^T) and a_j
-// likewise, w1 = Dg a_g and w2 = Dj (a_j - n_jg w1).  64 rows x 4 slices of the pending set per workgroup.
-__device__ __forceinline__ void wcache_block(const LazyPtrs& L, int d1, const SearchCtrl* __restrict__ ctrl, int block) {
-  __shared__ double sxg[LAZY_TM], sxj[LAZY_TM];
-  __shared__ int sts[LAZY_TM];
-  __shared__ double red[2][4][64];
-  const int tid = threadIdx.x, tau = ctrl->tau;
-  const int slice = tid >> 6, lr = tid & 63, row = block * 64 + lr;
-  const int rc = row < d1 ? row : d1 - 1;
-  // the pivots' own products are requested first: their latency passes while the pending pivots' are summed
-  double bgv = 0, bjv = 0;
-  if (slice == 0) { bgv = L.GbT[(int64_t)L.misc[MI_SG] * d1 + rc]; bjv = L.GbT[(int64_t)L.misc[MI_SJ] * d1 + rc]; }
-  for (int s = tid; s < LAZY_TM; s += 256) { sxg[s] = L.xg[s]; sxj[s] = L.xj[s]; sts[s] = (s < tau) ? L.tslot[s] : 0; }
-  __syncthreads();
-  double ag = 0, aj = 0;
-  for (int r = slice; r < tau; r += 64) {                 // sixteen loads in flight
-    double bv[16];
-#pragma unroll
-    for (int u = 0; u < 16; u++) { const int rr = r + 4 * u; bv[u] = L.GbT[(int64_t)sts[rr < tau ? rr : r] * d1 + rc]; }
-#pragma unroll
-    for (int u = 0; u < 16; u++) { const int rr = r + 4 * u; if (rr < tau) { ag += sxg[rr] * bv[u]; aj += sxj[rr] * bv[u]; } }
-  }
-  red[0][slice][lr] = ag; red[1][slice][lr] = aj;
-  __syncthreads();
-  if (slice != 0 || row >= d1) return;
-  const double Dg = L.ls[LS_DG], njg = L.ls[LS_NJG], Dj = L.ls[LS_DJ];
-  const double tg = bgv - (red[0][0][lr] + red[0][1][lr] + red[0][2][lr] + red[0][3][lr]);
-  const double tj = bjv - (red[1][0][lr] + red[1][1][lr] + red[1][2][lr] + red[1][3][lr]);
-  const double w1 = Dg * tg;
-  L.w1[row] = w1;
-  L.w2[row] = Dj * (tj - njg * w1);
-}
-// w = Z0 [y1 y2] from the cached products runs inside lazy_vectors_kernel's launch, beside the work it does not depend on, when
-// both pivots' products were computed ahead (the usual case); after a miss the update kernel forms the sums itself.
-
-// ---------------------------------------------------------------------------------------------- update
-// rows    : squared row norms, diagonal, scores (and their per-block records), the two new columns of C0
-// columns : ZT <- M'^-1 Z0[T', :] for T' = T + {g, j}
-// M       : bordering of M^-1 by g then j
-// tau itself is not touched here: the acceptance step has recorded the increment and the next iteration's prep folds it in.
-__global__ __launch_bounds__(256) void lazy_update_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int m, int row_blocks,
-                                                           int col_blocks, SearchCtrl* ctrl, int32_t* __restrict__ kept,
-                                                           double* __restrict__ rho, double* __restrict__ diag,
-                                                           double* __restrict__ score, int single) {
-  __shared__ double sa[LAZY_TM], sb[LAZY_TM];
-  __shared__ double s_mn[ROWS_PER_BLOCK], s_mx[ROWS_PER_BLOCK];
-  __shared__ int s_imn[ROWS_PER_BLOCK], s_imx[ROWS_PER_BLOCK];
-  if (idle(ctrl)) return;
-  const int tid = threadIdx.x, g = ctrl->g_out, j = ctrl->g_in, tau = ctrl->tau;
-  const double Dg = L.ls[LS_DG], M1 = L.ls[LS_M1], Dj = L.ls[LS_DJ];
-  const int b = blockIdx.x;
-  if (b < row_blocks) {
-    for (int s = tid; s < LAZY_TM; s += 256) {            // u = the partial sums of the acceptance kernel's workgroups, in order
-      double a = 0, c = 0;
-#pragma unroll
-      for (int h = 0; h < GEMV_SPLIT; h++) { a += L.u1[h * LAZY_TM + s]; c += L.u2[h * LAZY_TM + s]; }
-      sa[s] = a; sb[s] = c;
-    }
-    __syncthreads();
-    const double y11 = L.ls[LS_Y11], y22 = L.ls[LS_Y22], y12 = L.ls[LS_Y12];
-    const bool miss = L.misc[MI_MISS] != 0;
-    const int row = b * ROWS_PER_BLOCK + (tid >> 3), l8 = tid & 7;
-    double mn1 = INFINITY, mx1 = -INFINITY;
-    int imn = -1, imx = -1;
-    if (row < d1) {
-      // what the row's leader needs from memory is requested before the dot products, not after them
-      float n0g = 0.f, n0j = 0.f;
-      double c1 = 0, cjv = 0, rho0 = 0, diag0 = 0, w1c = 0, w2c = 0;
-      int ps = -1, kp0 = 0;
-      if (l8 == 0) {
-        n0g = nsym1(N0, d1, row, g);
-        if (!single) n0j = nsym1(N0, d1, row, j);
-        ps = L.pos[row]; c1 = L.cg[row]; cjv = L.cj[row]; rho0 = rho[row]; diag0 = diag[row]; kp0 = kept[row];
-        if (!miss) { w1c = L.w1[row]; w2c = L.w2[row]; }
-      }
-      double da, db;
-      row_dots(L.C0R + (int64_t)row * LAZY_TM, sa, sb, l8, da, db);
-      // w = Z0 [y1 y2] of this row: computed ahead in lazy_vectors_kernel's launch, unless a pivot's products with Z0 were
-      // not among the candidates; its column has existed only since lazy_gemv_kernel's pass, so the sum is formed here
-      double w1r, w2r;
-      if (miss) {
-        double ag = 0, aj = 0;
-        for (int r = l8; r < tau; r += 8) {
-          const double b = L.GbT[(int64_t)L.tslot[r] * d1 + row];
-          ag += L.xg[r] * b; aj += L.xj[r] * b;
-        }
-        ag = sum8(ag); aj = sum8(aj);
-        const double tg = L.GbT[(int64_t)L.misc[MI_SG] * d1 + row] - ag;
-        const double tj = L.GbT[(int64_t)L.misc[MI_SJ] * d1 + row] - aj;
-        w1r = Dg * tg;
-        w2r = Dj * (tj - L.ls[LS_NJG] * w1r);
-      } else { w1r = w1c; w2r = w2c; }
-      if (l8 == 0) {
-        // the base columns of g and j become columns tau, tau + 1 of C0
-        L.C0R[(int64_t)row * LAZY_TM + tau] = n0g;
-        if (!single) L.C0R[(int64_t)row * LAZY_TM + tau + 1] = n0j;
-        double r, dn;
-        int kp;
-        if (row == g) {
-          r = y11 - 2.0 * M1 * y12 + M1 * M1 * y22;          // || -y1 + M1 y2 ||^2
-          dn = -Dg - M1 * M1 * Dj;
-          kp = 0;
-          L.pos[row] = tau; L.Tidx[tau] = row; L.Jsg[tau] = -1.f; L.tslot[tau] = L.misc[MI_SG];
-        } else if (row == j) {
-          r = y22; dn = -Dj; kp = 1;
-          L.pos[row] = tau + 1; L.Tidx[tau + 1] = row; L.Jsg[tau + 1] = 1.f; L.tslot[tau + 1] = L.misc[MI_SJ];
-        } else {
-          double zy1, zy2;
-          if (ps >= 0) { const double sg = (double)L.Jsg[ps]; zy1 = sg * sa[ps]; zy2 = sg * sb[ps]; }
-          else { zy1 = w1r - da; zy2 = w2r - db; }
-          const double c2 = cjv - c1 * M1;
-          r = rho0 - 2.0 * c1 * zy1 + c1 * c1 * y11;           // after the reverse sweep on g
-          const double zy2p = zy2 - c1 * y12;                  // (Z_i - c1 y1) . y2
-          r += -2.0 * c2 * zy2p + c2 * c2 * y22;               // after the forward sweep on j
-          if (r < 0.0) r = 0.0;
-          dn = diag0 - c1 * c1 * Dg - c2 * c2 * Dj;
-          kp = kp0;
-        }
-        rho[row] = r; diag[row] = dn; kept[row] = kp;
-        const double sc = r / fabs(dn);
-        score[row] = sc;
-        if (kp) { mn1 = sc; imn = row; } else { mx1 = sc; imx = row; }
-      }
-    }
-    // Per-block record.  The 32 row leaders (lanes 0, 8, 16, ... of each wave) hand their (cost, index) and (gain, index) to
-    // the first wave through shared memory; it picks the best of each side by data-parallel moves on (value, index) alone,
-    // then the second best as a plain minimum / maximum over the rows that did not win: half the instructions of merging
-    // full (best, second, index) records at every step, on what is the longest path through this kernel.
-    if ((tid & 7) == 0) { const int e = tid >> 3; s_mn[e] = mn1; s_imn[e] = imn; s_mx[e] = mx1; s_imx[e] = imx; }
-    __syncthreads();
-    if (tid < 64) {
-      const bool have = tid < ROWS_PER_BLOCK;
-      double vmn = have ? s_mn[tid & 31] : INFINITY, vmx = have ? s_mx[tid & 31] : -INFINITY;
-      int vin = have ? s_imn[tid & 31] : -1, vix = have ? s_imx[tid & 31] : -1;
-      const double own_mn = vmn, own_mx = vmx;
-      const int own_in = vin, own_ix = vix;
-      dpp_best_step<0xb1, 0xf>(vmn, vin, vmx, vix);
-      dpp_best_step<0x4e, 0xf>(vmn, vin, vmx, vix);
-      dpp_best_step<0x124, 0xf>(vmn, vin, vmx, vix);
-      dpp_best_step<0x128, 0xf>(vmn, vin, vmx, vix);
-      dpp_best_step<0x142, 0xa>(vmn, vin, vmx, vix);
-      dpp_best_step<0x143, 0xc>(vmn, vin, vmx, vix);
-      const int win_n = __builtin_amdgcn_readlane(vin, 63), win_x = __builtin_amdgcn_readlane(vix, 63);
-      double lo = (own_in >= 0 && own_in != win_n) ? own_mn : INFINITY, hi = (own_ix >= 0 && own_ix != win_x) ? own_mx : -INFINITY;
-      dpp_minmax_step<0xb1, 0xf>(lo, hi);
-      dpp_minmax_step<0x4e, 0xf>(lo, hi);
-      dpp_minmax_step<0x124, 0xf>(lo, hi);
-      dpp_minmax_step<0x128, 0xf>(lo, hi);
-      dpp_minmax_step<0x142, 0xa>(lo, hi);
-      dpp_minmax_step<0x143, 0xc>(lo, hi);
-      if (tid == 63) {
-        SelRec rec; rec.mn1 = vmn; rec.mn2 = lo; rec.mx1 = vmx; rec.mx2 = hi; rec.imn = vin; rec.imx = vix;
-        L.sel[b] = rec;
-      }
-    }
-  } else if (b < row_blocks + col_blocks) {
-    const int cb = b - row_blocks, slice = tid >> 6, col = cb * COLS_PER_BLOCK + (tid & 63);
-    for (int s = tid; s < LAZY_TM; s += 256) { const double xg = L.xg[s]; sa[s] = xg; sb[s] = L.xj[s] - xg * M1; }
-    __syncthreads();
-    if (col < m) {
-      const double y1 = L.y1[col], y2 = L.y2[col];
-      // independent read-modify-writes: issue several before waiting
-      int s = slice;
-      for (; s + 28 < tau; s += 32) {
-        double z[8];
-#pragma unroll
-        for (int u = 0; u < 8; u++) z[u] = L.ZT[(int64_t)(s + 4 * u) * m + col];
-#pragma unroll
-        for (int u = 0; u < 8; u++) L.ZT[(int64_t)(s + 4 * u) * m + col] = z[u] - (sa[s + 4 * u] * y1 + sb[s + 4 * u] * y2);
-      }
-      for (; s < tau; s += 4) L.ZT[(int64_t)s * m + col] -= sa[s] * y1 + sb[s] * y2;
-      if (slice == 0) {
-        L.ZT[(int64_t)tau * m + col] = y1 - M1 * y2;
-        if (!single) L.ZT[(int64_t)(tau + 1) * m + col] = y2;
-      }
-    }
-  } else {
-    const int mb = b - row_blocks - col_blocks, nmb = gridDim.x - row_blocks - col_blocks;
-    double* Mi = L.Minv;
-    for (int idx = mb * 256 + tid; idx < tau * tau; idx += nmb * 256) {
-      const int r = idx / tau, s = idx % tau;
-      const double xr = L.xg[r], xs = L.xg[s];
-      const double pr = L.xj[r] - xr * M1, ps = L.xj[s] - xs * M1;
-      Mi[r * LAZY_TM + s] += xr * xs * Dg + pr * ps * Dj;
-    }
-    if (mb == 0) {
-      for (int r = tid; r < tau; r += 256) {
-        const double xr = L.xg[r], pr = L.xj[r] - xr * M1;
-        const double v = -xr * Dg + pr * M1 * Dj;          // bordered by g, then corrected by the sweep on j
-        Mi[r * LAZY_TM + tau] = v; Mi[tau * LAZY_TM + r] = v;
-        if (single) continue;
-        const double w = -pr * Dj;
-        Mi[r * LAZY_TM + tau + 1] = w; Mi[(tau + 1) * LAZY_TM + r] = w;
-      }
-      if (tid == 0) {
-        Mi[tau * LAZY_TM + tau] = Dg + M1 * M1 * Dj;
-        if (!single) {
-          Mi[tau * LAZY_TM + tau + 1] = -M1 * Dj; Mi[(tau + 1) * LAZY_TM + tau] = -M1 * Dj;
-          Mi[(tau + 1) * LAZY_TM + tau + 1] = Dj;
-        }
-      }
-    }
-  }
-}
-
-hipError_t launch_lazy_iteration(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int always_accept, hipStream_t s,
-                                 hipEvent_t* ev, const int32_t* single, int forced_out, int forced_in) {
-  const int rb = (d.d1 + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, cb = (d.m + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
-  hipLaunchKernelGGL(lazy_prep_kernel, dim3(1), dim3(PREP_T), 0, s, L, t.N, d.d1, rb, t.kept, t.ctrl, single, forced_out, forced_in);
-  hipLaunchKernelGGL(lazy_vectors_kernel, dim3(rb + cb + (d.d1 + 63) / 64), dim3(256), 0, s, L, t.N, t.Z, d.d1, d.m, rb, cb, t.ctrl);
-  const int gb = (d.d1 + GEMV_ROWS - 1) / GEMV_ROWS + LAZY_TM * GEMV_SPLIT;
-  if (ev) hipEventRecord(ev[0], s);
-  hipLaunchKernelGGL(lazy_gemv_kernel, dim3(gb), dim3(256), 0, s, L, t.Z, d.d1, d.m, cb, t.ctrl, always_accept, t.trace_out,
-                     t.trace_in, t.trace_gap, t.trace_obj, single ? 1 : 2);
-  if (ev) hipEventRecord(ev[1], s);
-  hipLaunchKernelGGL(lazy_update_kernel, dim3(rb + cb + 16), dim3(256), 0, s, L, t.N, d.d1, d.m, rb, cb, t.ctrl, t.kept, t.gram,
-                     t.dblk, t.score, single ? 1 : 0);
-  if (ev) hipEventRecord(ev[2], s);
-  return hipGetLastError();
-}
 
 // ------------------------------------------------------------------------------------------------
 // flush: apply the pending correction to N0, Z0 and empty T
 // ------------------------------------------------------------------------------------------------
-// float32 copy of ZT, zero beyond tau (so that stale columns of C0 drop out of the products)
-__global__ __launch_bounds__(256) void lazy_convert_kernel(LazyPtrs L, int m, const SearchCtrl* __restrict__ ctrl) {
-  const int tau = tau_all(ctrl);
-  const int64_t nz = (int64_t)LAZY_TM * m;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < nz; idx += (int64_t)gridDim.x * 256) {
-    const int s = (int)(idx / m);
-    L.ZT32[idx] = (s < tau) ? (float)L.ZT[idx] : 0.f;
-  }
-}
-
 // pivot rows / columns of N0 and pivot rows of Z0.  Every entry is written by exactly one thread (the pending pivots are
 // distinct), so the pivots are spread over blockIdx.y: FIX_SPB of them per thread.
 constexpr int FIX_SPB = 8;
@@ -774,7 +136,6 @@ __global__ __launch_bounds__(1024) void cand_merge_kernel(LazyPtrs L, int nblk, 
   }
   if (side == 0) {
     for (int s = n_k + n_c + tid; s < LAZY_NC + LAZY_NS; s += 1024) L.cand[s] = -1;
-    if (tid < 8) L.misc[tid] = 0;
   }
 }
 
@@ -998,17 +359,16 @@ static hipError_t launch_candidate_products(const TabDims& d, const TabPtrs& t, 
   g.C = L.GbT; g.ldc = d.d1; g.alpha = 1.0; g.beta = 0.0; g.c_is_f64 = 1; g.ws = L.gemm_ws; g.ws_bytes = L.gemm_ws_bytes;
   return launch_gemm_f64acc(g, s);
 }
-static hipError_t launch_candidates(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode, bool swaps) {
+static hipError_t launch_candidates(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
   hipError_t e = launch_candidate_pick(d, t, L, s, mode);
   if (e != hipSuccess) return e;
-  if (swaps && (e = launch_cand_gram(d, t, L, cand_counts(mode).n_k + cand_counts(mode).n_c, s)) != hipSuccess) return e;
+  if ((e = launch_cand_gram(d, t, L, cand_counts(mode).n_k + cand_counts(mode).n_c, s)) != hipSuccess) return e;
   return launch_candidate_products(d, t, L, s, mode);
 }
 
-static hipError_t launch_partials(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s) {
-  const int rb = (d.d1 + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
-  hipLaunchKernelGGL(lazy_partials_kernel, dim3(rb), dim3(64), 0, s, L, d.p, t.kept, t.score);
-  return hipGetLastError();
+// what the next iteration picks from: the removal lists of the removal-only loops, the records of the swaps
+static hipError_t launch_picks(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
+  return mode == 1 ? launch_removal_lists(d, t, L, s) : launch_swap_records(d, t, L, s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1281,13 +641,12 @@ __global__ __launch_bounds__(256) void norms_from_stretches_kernel(LazyPtrs L, i
 }
 
 hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode,
-                             const SideStream* side, bool swaps) {
+                             const SideStream* side) {
   const int rb = (d.d1 + 255) / 256, mb = (d.m + 255) / 256;
   const bool two = side && side->stream;
   hipStream_t sn = two ? side->stream : s;          // stream of the N0 update
   hipError_t err;
-  if (swaps) { if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err; }
-  else hipLaunchKernelGGL(lazy_convert_kernel, dim3(512), dim3(256), 0, s, L, d.m, t.ctrl);
+  if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err;
   {                                     // E = C0 M^-1 (entered in the log of matrix products like the general kernel's launches)
     const size_t shmem = (size_t)(LAZY_TM + 64) * TE_LD * sizeof(float);
     if ((err = hipFuncSetAttribute(reinterpret_cast<const void*>(thin_e_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)) != hipSuccess)
@@ -1328,242 +687,341 @@ hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs&
     // The candidates of the next cycle, from the scores as the swaps left them (the refresh below changes them in the last
     // digits only, and the choice of candidates decides what is computed ahead, not any result): two sorts of one
     // workgroup each; this stream has the time, the second one's chain is the longer.
-    err = launch_candidates(d, t, L, s, mode, swaps);
+    err = launch_candidates(d, t, L, s, mode);
     if (err != hipSuccess) return err;
     if ((err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
   }
   hipLaunchKernelGGL(lazy_reset_kernel, dim3(1), dim3(256), 0, s, L, t.ctrl);
   err = two ? launch_refresh_from_blocks(d, t, s) : launch_refresh_scores(d, t, s);
   if (err != hipSuccess) return err;
-  if (!two && (err = launch_candidates(d, t, L, s, mode, swaps)) != hipSuccess) return err;
-  return swaps ? launch_swap_records(d, t, L, s) : launch_partials(d, t, L, s);
+  if (!two && (err = launch_candidates(d, t, L, s, mode)) != hipSuccess) return err;
+  return launch_picks(d, t, L, s, mode);
 }
 
 // ------------------------------------------------------------------------------------------------
 // Block removal: the t <= LAZY_BT rows that one iteration of the nested schedule prunes (Algorithm 1 with p-hat = t-hat:
 // all of them scored at the state the iteration starts from) leave as ONE block pivot instead of t pivots in a row.
-// With G the picks, b = N0[T, G] (tau x t), X = M^-1 b, the current block N_GG = N0[G, G] - b^T X and D = N_GG^-1:
-//   Y = D Z_G (t x m), Z_G = Z0[G, :] - b^T ZT the current rows;       obj rises by -sum_a <Z_G[a], Y[a]>
+// With G the picks, b = N0[T, G], X = M^-1 b (tau x t), the current block N_GG = N0[G, G] - b^T X and D = N_GG^-1:
+//   Y = D Z_G (t x m), Z_G = Z0[G, :] - X^T Z0[T, :] the current rows;       obj rises by -sum_a <Z_G[a], Y[a]>
 //   every other row i: c_i = N[i, G] = N0[i, G] - C0[i, :] X,  Z_i -= c_i Y,  N_ii -= c_i D c_i^T
 //   |Z_i|^2 changes by -2 c_i (Y Z_i^T) + c_i (Y Y^T) c_i^T,  Y Z_i^T = W_i - (ZT Y^T)^T C0[i, :]^T,
 //   W_i = Z0_i Y^T = D (GbT[G, i] - X^T GbT[T, i])  from the products computed ahead
-//   M^-1 grows by the block [[X D X^T, -X D], [-D X^T, D]],  ZT <- [ZT - X Y; Y].
-// Four launches per iteration of t removals (prep, cols, gemv, update) instead of four per removal.
+//   M^-1 grows by the block [[X D X^T, -X D], [-D X^T, D]].
+// As for the swaps (swap.hip), nothing of width m is touched: with K the Gram matrix of the base rows and Q = K_TG - K_TT X,
+//   Z_G Z_G^T = K_GG - X^T (K_TG + Q),   Y Y^T = D Z_G Z_G^T D,   ZT Y^T = M^-1 Q D.
+// Two launches per iteration of t removals: the pick and the algebra by one workgroup, then the rows.  With ZT and Y formed over all
+// columns and the pick a launch of its own it was five, 58 us at 8192 x 2048 (t = 10) with what lies between them; now 35.
 // ------------------------------------------------------------------------------------------------
 constexpr int BT = LAZY_BT;
 
 typedef double lzd4 __attribute__((ext_vector_type(4)));
 static_assert(BT == 16, "one 16 x 16 tile of picks");
 constexpr int BX_LD = 20;      // doubles per row of the tables of a block's columns: the k of an operand read lie in different banks
-// One workgroup: B = N0[T, G], X = M^-1 B, D = (N0[G, G] - B^T X)^-1 (negative definite: minus a principal block of a positive
-// definite inverse).  Bound by round trips to memory: the picks, then their rows of C0 with M^-1 requested before.  A wave has 16
-// rows of M^-1 in registers as a matrix-core operand; its rows of X are the operand of its share of B^T X; one wave inverts.
-__global__ __launch_bounds__(512) void blk_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int t,
-                                                        const int32_t* __restrict__ pick, const int32_t* __restrict__ kept,
-                                                        SearchCtrl* ctrl) {
-  __shared__ double sb[LAZY_TM * BX_LD], sP[8][BT][BT + 1];
-  if (idle(ctrl)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
-  const int tau = tau_all(ctrl);      // every thread reads before thread 0 folds the increment in (after the barrier)
-  const int g = pick[lane < t ? lane : 0];                // every wave holds all the picks
-  double2 mv[16];                                         // row 16 wave + lc of M^-1, columns 8 u + 2 lr, + 1
+constexpr int KLD = LAZY_NC + LAZY_NS;      // row length of K
+// Removal lists: of every 64 rows the LIST_N kept ones of smallest removal cost (finite ones only), ascending, lowest index first on
+// ties; an entry's number is row * 512 + slot of its products + 1, -1: no entry
+constexpr int LIST_ROWS = 64, LIST_N = BT + 1;
+static_assert(LAZY_NC + LAZY_NS < 512 && 65536 <= (1 << 22), "row and slot in one int");
+// By a workgroup of four waves: sc (INFINITY where the row is not kept) of 64 rows in shared memory, slot of lane's row in the first
+// wave; a wave counts the 16 rows of its own that come before the lane's, the first one adds up.  s_cnt: shared memory
+__device__ __forceinline__ void write_list(double* __restrict__ val, int32_t* __restrict__ rows, const double* sc, int (*s_cnt)[LIST_ROWS], int row0,
+                                           int slot, int lane, int wave) {
+  const double x = sc[lane];
+  int below = 0;
 #pragma unroll
-  for (int u = 0; u < 16; u++) mv[u] = *reinterpret_cast<const double2*>(L.Minv + (wave * 16 + lc) * LAZY_TM + 8 * u + 2 * lr);
-  const bool range = g >= 0 && g < d1;
-  const int gc = range ? g : 0;
-  const bool bad = !range || !kept[gc] || L.pos[gc] >= 0 || L.cslot[gc] < 0 || tau + t > LAZY_TM;
+  for (int k = 0; k < 16; k++) {
+    const int e = wave * 16 + k;
+    const double y = sc[e];
+    below += (int)((y < x) | ((y == x) & (e < lane)));
+  }
+  s_cnt[wave][lane] = below;
+  __syncthreads();
+  if (wave != 0) return;
+  below = (s_cnt[0][lane] + s_cnt[1][lane]) + (s_cnt[2][lane] + s_cnt[3][lane]);
+  const bool mine = x < INFINITY;
+  const int n = (int)__popcll(__ballot(mine));
+  if (mine && below < LIST_N) { val[below] = x; rows[below] = (row0 + lane) * 512 + slot + 1; }
+  if (lane < LIST_N && lane >= n) { val[lane] = INFINITY; rows[lane] = -1; }
+}
+// a score as the lists count it: only finite costs of kept rows
+__device__ __forceinline__ double list_score(bool kept, double score) { return kept && score < INFINITY ? score : INFINITY; }
+__global__ __launch_bounds__(256) void removal_lists_kernel(LazyPtrs L, int d1, const int32_t* __restrict__ kept, const double* __restrict__ score) {
+  __shared__ double sc[LIST_ROWS];
+  __shared__ int s_cnt[4][LIST_ROWS];
+  const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x * LIST_ROWS + lane, rc = min(row, d1 - 1);
+  const int slot = L.cslot[rc];
+  if (tid < LIST_ROWS) sc[tid] = list_score(row < d1 && kept[rc] != 0, score[rc]);
+  __syncthreads();
+  write_list(L.lval + (int64_t)blockIdx.x * LIST_N, L.lrow + (int64_t)blockIdx.x * LIST_N, sc, s_cnt, blockIdx.x * LIST_ROWS, slot, lane, tid >> 6);
+}
+int removal_list_count(int64_t d1) { return (int)((d1 + LIST_ROWS - 1) / LIST_ROWS); }
+hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s) {
+  hipLaunchKernelGGL(removal_lists_kernel, dim3(removal_list_count(d.d1)), dim3(256), 0, s, L, d.d1, t.kept, t.score);
+  return hipGetLastError();
+}
+
+// One workgroup: the t cheapest removals from the lists (own_pick; else the picks are in `pick`), then B = N0[T, G], X = M^-1 B,
+// Q = K_TG - K_TT X, P = M^-1 Q, D = (N0[G, G] - B^T X)^-1 (negative definite: minus a principal block of a positive definite inverse),
+// Y Y^T and U = P D.  Bound by round trips to memory (lists, picks' rows), by what one compute unit can fetch of M^-1 and K_TT (requested
+// first, and only the 32-row blocks that can be pending: all 256 KB took 8 us), the counting of the pick and the inversion of 16 x 16
+// (by the last wave, beside the others' product with M^-1; its own rows, the last sixteen pending pivots, come after it).  A wave has
+// 16 rows of M^-1 and of K_TT in registers as matrix-core operands.
+constexpr int PREP_T = 512, PREP_LISTS = 1024;
+__global__ __launch_bounds__(PREP_T) void blk_prep_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int t, int own_pick, int nlists, int tau_most,
+                                                           int32_t* __restrict__ pick, float* __restrict__ gap, const int32_t* __restrict__ kept,
+                                                           SearchCtrl* ctrl, int32_t* __restrict__ trace_out) {
+  // the tables of the algebra, and before it the lists
+  constexpr int HEADS = 128, CAND = LIST_N * LIST_N * (PREP_LISTS / HEADS);
+  constexpr int TAB = LAZY_TM * BX_LD, SUM = 8 * BT * (BT + 1), POOL = 3 * TAB + 2 * SUM, LDS_ENT = POOL * 2 / 3 / 8 * 8;
+  __shared__ __attribute__((aligned(16))) double pool[POOL];
+  double *sb = pool, *sx = pool + TAB, *sq = pool + 2 * TAB;
+  double (*sS)[BT][BT + 1] = reinterpret_cast<double (*)[BT][BT + 1]>(pool + 3 * TAB);
+  double (*sZ)[BT][BT + 1] = sS + 8;
+  double* lv = pool;
+  int* ln = reinterpret_cast<int*>(pool + LDS_ENT);
+  __shared__ double sD[BT][BT + 1], sW[BT][BT + 1], s_h[HEADS], s_cv[CAND];
+  __shared__ int s_pick[BT], sts[LAZY_TM], s_hi[HEADS], s_ci[CAND], s_n, s_bi;
+  __shared__ double s_bv, s_edge[2];
+  if (ctrl->done | ctrl->pause) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  const int tau = tau_all(ctrl);      // every thread reads before thread 0 folds the increment in (after a barrier)
+  const int E = min(LIST_N, LDS_ENT / nlists);      // entries of each list that fit (all up to 30000 rows); the others are read where they lie
+  if (own_pick) {
+    for (int i0 = tid; i0 < nlists * E; i0 += 5 * PREP_T) {
+      double x[5];
+      int n[5];
+#pragma unroll
+      for (int u = 0; u < 5; u++) {
+        const int i = min(i0 + u * PREP_T, nlists * E - 1);
+        const int64_t at = E == LIST_N ? i : (int64_t)(i / E) * LIST_N + i % E;
+        x[u] = L.lval[at]; n[u] = L.lrow[at];
+      }
+#pragma unroll
+      for (int u = 0; u < 5; u++) if (i0 + u * PREP_T < nlists * E) { lv[i0 + u * PREP_T] = x[u]; ln[i0 + u * PREP_T] = n[u]; }
+    }
+  }
+  if (tid < LAZY_TM) sts[tid] = tid < tau ? L.tslot[tid] : 0;
+  double2 mv[16], kv[16];                                 // row 16 wave + lc of M^-1 and K_TT, columns 8 u + 2 lr, + 1
+  const int mrow = wave * 16 + lc;
+  const int th = min(LAZY_TM, (tau_most + 31) & ~31);
+#pragma unroll
+  for (int u0 = 0; u0 < 16; u0 += 4)
+    if (wave * 16 < th && 8 * u0 < th)
+#pragma unroll
+      for (int u = u0; u < u0 + 4; u++) mv[u] = *reinterpret_cast<const double2*>(L.Minv + mrow * LAZY_TM + 8 * u + 2 * lr);
+#pragma unroll
+  for (int u0 = 0; u0 < 16; u0 += 4)
+    if (wave * 16 < th && 8 * u0 < th)
+#pragma unroll
+      for (int u = u0; u < u0 + 4; u++) kv[u] = *reinterpret_cast<const double2*>(L.KT + mrow * LAZY_TM + 8 * u + 2 * lr);
+  if (own_pick) {
+    // (value, number) pairs are ordered by value, then number (the lowest row first).  The bound: of the least entries of HEADS groups of
+    // lists the (t + 1)-th, found by counting; no entry above it is among the t + 1 smallest.  Then the entries up to it, ranked by counting.
+    auto before = [](double x, int i, double y, int j) { return (x < y) | ((x == y) & (i < j)); };
+    __syncthreads();
+    if (tid < HEADS) {
+      double hv = INFINITY;
+      int hn = 0x7fffffff - HEADS + tid;                  // no entry: behind all others, each another number
+      for (int l = tid; l < nlists; l += HEADS) if (ln[l * E] >= 0 && before(lv[l * E], ln[l * E], hv, hn)) { hv = lv[l * E]; hn = ln[l * E]; }
+      s_h[tid] = hv; s_hi[tid] = hn;
+    }
+    if (tid == 0) { s_n = 0; s_edge[0] = s_edge[1] = INFINITY; }
+    if (tid < BT) s_pick[tid] = -1;
+    __syncthreads();
+    {
+      const int h = tid >> 2;                             // four threads to a head
+      const double x = s_h[h];
+      const int xi = s_hi[h];
+      int below = 0;
+#pragma unroll 8
+      for (int k = 0; k < HEADS / 4; k++) { const int e = (tid & 3) * (HEADS / 4) + k; below += (int)before(s_h[e], s_hi[e], x, xi); }
+      below += __builtin_amdgcn_update_dpp(0, below, 0xb1, 0xf, 0xf, true);
+      below += __builtin_amdgcn_update_dpp(0, below, 0x4e, 0xf, 0xf, true);
+      if ((tid & 3) == 0 && below == t) { s_bv = x; s_bi = xi; }      // t < HEADS: one of them
+    }
+    __syncthreads();
+    const double bound = s_bv;
+    const int bound_i = s_bi;
+    for (int l = tid; l < nlists; l += PREP_T)
+      for (int e = 0; e < LIST_N; e++) {
+        const double x = e < E ? lv[l * E + e] : L.lval[(int64_t)l * LIST_N + e];
+        const int n = e < E ? ln[l * E + e] : L.lrow[(int64_t)l * LIST_N + e];
+        if (n < 0 || before(bound, bound_i, x, n)) break;
+        const int at = atomicAdd(&s_n, 1);
+        s_cv[at] = x; s_ci[at] = n;                       // t + 1 <= LIST_N groups have a head up to the bound: CAND is enough
+      }
+    __syncthreads();
+    const int found = s_n;
+    for (int i = tid; i < found; i += PREP_T) {
+      const double x = s_cv[i];
+      const int xi = s_ci[i];
+      int rank = 0;
+      for (int k = 0; k < found; k++) rank += (int)before(s_cv[k], s_ci[k], x, xi);
+      if (rank < t) s_pick[rank] = xi;
+      if (rank == t - 1) s_edge[0] = x;
+      if (rank == t) s_edge[1] = x;
+    }
+    __syncthreads();
+    if (tid < t) { const int c = s_pick[tid]; pick[tid] = c < 0 ? -1 : c >> 9; }
+    if (tid == 0) *gap = found > t ? (float)(fabs(s_edge[1] - s_edge[0]) / fmax(fabs(s_edge[0]), 1e-300)) : INFINITY;
+  } else if (tid < t) {
+    const int g = pick[tid];
+    s_pick[tid] = (g >= 0 && g < d1) ? g * 512 + L.cslot[g] + 1 : -1;
+  }
+  __syncthreads();
+  // every wave holds all the picks; what depends on them in one round trip
+  const int n = s_pick[lane < t ? lane : 0], g = n >= 0 ? n >> 9 : 0, slot = n >= 0 ? max((n & 511) - 1, 0) : 0;
+  const int gl = __shfl(g, lc < t ? lc : 0, 64), sl = __shfl(slot, lc < t ? lc : 0, 64);      // the pick of column lc
+  const int kept_g = kept[g], pos_g = L.pos[g];
+  double kq[4], kgg[4], x4[4], p4[4];
+  float raw[4], n0[4];
+#pragma unroll
+  for (int r = 0; r < 4; r++) {      // rows of b and K_TG, the picks' own block of N0 and K
+    const int k = wave * 16 + 4 * r + lr, a = 4 * r + lr, ga = __shfl(g, a < t ? a : 0, 64), sa = __shfl(slot, a < t ? a : 0, 64);
+    raw[r] = L.C0R[(int64_t)gl * LAZY_TM + k];
+    kq[r] = L.K[sts[k] * KLD + sl];
+    n0[r] = nsym1(N0, d1, ga, gl); kgg[r] = L.K[sa * KLD + sl];
+  }
+  const bool bad = n < 0 || (n & 511) == 0 || !kept_g || pos_g >= 0 || tau + t > LAZY_TM;
   if (__any(bad)) {                                       // the same in every wave: none writes before all have read
     __syncthreads();
     if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; ctrl->pause = 1; }
     return;
   }
-  float bv[4], n0[4];
 #pragma unroll
-  for (int i = 0; i < 4; i++) bv[i] = L.C0R[(int64_t)__shfl(g, (tid >> 7) + 4 * i, 64) * LAZY_TM + (tid & 127)];
-#pragma unroll
-  for (int r = 0; r < 4; r++) n0[r] = nsym1(N0, d1, __shfl(g, 4 * r + lr, 64), __shfl(g, lc, 64));
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    const int a = (tid >> 7) + 4 * i, r = tid & 127;
-    const double v = (r < tau && a < t) ? (double)bv[i] : 0.0;
-    sb[r * BX_LD + a] = v; L.bB[r * BT + a] = v;
+  for (int r = 0; r < 4; r++) {
+    const int k = wave * 16 + 4 * r + lr;
+    const bool use = k < tau && lc < t;
+    sb[k * BX_LD + lc] = use ? (double)raw[r] : 0.0;
+    if (!use) kq[r] = 0.0;
   }
   __syncthreads();
   if (tid == 0) { ctrl->tau = tau; ctrl->tau_inc = 0; }
-  lzd4 x = {0.0, 0.0, 0.0, 0.0}, p = x;
+  auto product = [&](const double2* A, const double* B) {
+    lzd4 x = {0.0, 0.0, 0.0, 0.0};
+    if (wave * 16 >= tau) return x;
 #pragma unroll
-  for (int u = 0; u < 16; u++) {                          // B is zero from tau on, M^-1 finite there
-    x = __builtin_amdgcn_mfma_f64_16x16x4f64(mv[u].x, sb[(8 * u + 2 * lr) * BX_LD + lc], x, 0, 0, 0);
-    x = __builtin_amdgcn_mfma_f64_16x16x4f64(mv[u].y, sb[(8 * u + 2 * lr + 1) * BX_LD + lc], x, 0, 0, 0);
-  }
+    for (int u = 0; u < 16; u++) {                        // B is zero from tau on, the matrices are finite there
+      if (8 * u >= tau) break;
+      x = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].x, B[(8 * u + 2 * lr) * BX_LD + lc], x, 0, 0, 0);
+      x = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].y, B[(8 * u + 2 * lr + 1) * BX_LD + lc], x, 0, 0, 0);
+    }
+    return x;
+  };
+  {
+    const lzd4 x = product(mv, sb);
+    lzd4 p = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int row = wave * 16 + 4 * r + lr;
-    const double v = row < tau ? x[r] : 0.0;
-    L.bX[row * BT + lc] = v;
-    p = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[row * BX_LD + lc], v, p, 0, 0, 0);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; r++) sP[wave][4 * r + lr][lc] = p[r];
-  __syncthreads();
-  if (wave != 0) return;
-  swd4 y;
-#pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int a = 4 * r + lr;
-    double v = (double)n0[r];
-#pragma unroll
-    for (int w = 0; w < 8; w++) v -= sP[w][a][lc];
-    y[r] = (a < t && lc < t) ? -v : (a == lc ? 1.0 : 0.0);
-  }
-  bool flag = false;
-  inv16_steps<0>(y, lane, t, flag);
-#pragma unroll
-  for (int r = 0; r < 4; r++) { const int a = 4 * r + lr; L.bD[a * BT + lc] = (a < t && lc < t) ? -y[r] : 0.0; }
-  if (lane < BT) L.bG[lane] = lane < t ? g : -1;
-  if (__any(flag) && lane == 0) ctrl->notpd = 1;
-}
-
-// Current rows of the picks, Y = D Z_G, and per column block the partial sums of Y Y^T and <Z_G[a], Y[a]>, all on
-// v_mfma_f64_16x16x4_f64: a wave takes 16 columns, lane (lr, lc) holds the picks 4 r + lr of column lc, which is also the
-// operand layout of the next product.  As scalar loops with one wave left for the sums this took 26 us for 2048 columns.
-__global__ __launch_bounds__(256) void blk_cols_kernel(LazyPtrs L, const float* __restrict__ Z0, int m, int t,
-                                                        const SearchCtrl* __restrict__ ctrl) {
-  __shared__ double zl[BT][COLS_PER_BLOCK + 1], yl[BT][COLS_PER_BLOCK + 1];
-  if (idle(ctrl)) return;
-  const int tid = threadIdx.x, tau = ctrl->tau, cb = blockIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15, col = cb * COLS_PER_BLOCK + wave * 16 + lc;
-  const int cc = min(col, m - 1);
-  float z0[4];
-  double d[4];
-#pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int a = 4 * r + lr;
-    z0[r] = a < t ? Z0[(int64_t)L.bG[a] * m + cc] : 0.f;
-    d[r] = L.bD[lc * BT + a];
-  }
-  lzd4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < tau; k0 += 32) {
-    double av[8], bv[8];
-#pragma unroll
-    for (int u = 0; u < 8; u++) {
-      const int k = k0 + 4 * u + lr, kc = min(k, LAZY_TM - 1);
-      const double zt = L.ZT[(int64_t)kc * m + cc];
-      av[u] = L.bB[kc * BT + lc];                       // zero from tau on, where ZT holds anything
-      bv[u] = k < tau ? zt : 0.0;
+    for (int r = 0; r < 4; r++) {
+      const int row = wave * 16 + 4 * r + lr;
+      x4[r] = row < tau ? x[r] : 0.0;
+      sx[row * BX_LD + lc] = x4[r]; L.bX[row * BT + lc] = x4[r];
+      p = __builtin_amdgcn_mfma_f64_16x16x4f64(sb[row * BX_LD + lc], x4[r], p, 0, 0, 0);
     }
 #pragma unroll
-    for (int u = 0; u < 8; u++) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u], acc, 0, 0, 0);
-  }
-  lzd4 y = {0.0, 0.0, 0.0, 0.0};
-  double zg[4];
-#pragma unroll
-  for (int r = 0; r < 4; r++) zg[r] = (4 * r + lr < t && col < m) ? (double)z0[r] - acc[r] : 0.0;
-#pragma unroll
-  for (int r = 0; r < 4; r++) y = __builtin_amdgcn_mfma_f64_16x16x4f64(d[r], zg[r], y, 0, 0, 0);
-#pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int a = 4 * r + lr;
-    if (a < t && col < m) L.bY[(int64_t)a * m + col] = y[r];
-    zl[a][wave * 16 + lc] = zg[r]; yl[a][wave * 16 + lc] = y[r];
+    for (int r = 0; r < 4; r++) sS[wave][4 * r + lr][lc] = p[r];
   }
   __syncthreads();
-  if (wave > 1) return;
-  lzd4 p = {0.0, 0.0, 0.0, 0.0};                        // wave 0: Y Y^T; wave 1: Z_G Y^T, of which the diagonal
-#pragma unroll 4
-  for (int k0 = 0; k0 < COLS_PER_BLOCK; k0 += 4) p = __builtin_amdgcn_mfma_f64_16x16x4f64(wave ? zl[lc][k0 + lr] : yl[lc][k0 + lr], yl[lc][k0 + lr], p, 0, 0, 0);
-  double* part = L.bpart + (int64_t)cb * (BT * BT + BT);
+  {
+    const lzd4 q = product(kv, sx);
+    lzd4 z = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int r = 0; r < 4; r++) {
-    const int a = 4 * r + lr;
-    if (wave == 0 && lc <= a) part[a * BT + lc] = p[r];
-    if (wave == 1 && lc == a) part[BT * BT + a] = p[r];
-  }
-}
-
-// U = ZT Y^T: workgroup (rg, slab) takes four pending pivots and a quarter of the columns and leaves its part in
-// bU[slab] (the reader adds the four up); the last workgroup adds up the column blocks' sums and books the move
-constexpr int BU_SLABS = 4;
-__global__ __launch_bounds__(256) void blk_gemv_kernel(LazyPtrs L, int m, int t, int col_blocks, SearchCtrl* ctrl,
-                                                        int32_t* __restrict__ trace_out) {
-  __shared__ double red[4][4 * BT];
-  if (idle(ctrl)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tau = ctrl->tau;
-  if ((int)blockIdx.x < LAZY_TM) {
-    const int r0 = ((int)blockIdx.x / BU_SLABS) * 4, slab = (int)blockIdx.x % BU_SLABS;
-    const int cs = (m + BU_SLABS - 1) / BU_SLABS, c0 = slab * cs, c1 = min(m, c0 + cs);
-    double acc[4][BT];
-#pragma unroll
-    for (int e = 0; e < 4; e++)
-#pragma unroll
-      for (int a = 0; a < BT; a++) acc[e][a] = 0.0;
-    if (r0 < tau) {
-      for (int c = c0 + tid; c < c1; c += 256) {
-        double z[4], y[BT];
-#pragma unroll
-        for (int e = 0; e < 4; e++) z[e] = (r0 + e < tau) ? L.ZT[(int64_t)(r0 + e) * m + c] : 0.0;
-#pragma unroll
-        for (int a = 0; a < BT; a++) y[a] = (a < t) ? L.bY[(int64_t)a * m + c] : 0.0;
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-#pragma unroll
-          for (int a = 0; a < BT; a++) acc[e][a] += z[e] * y[a];
-      }
+    for (int r = 0; r < 4; r++) {
+      const int row = wave * 16 + 4 * r + lr;
+      const double v = row < tau ? kq[r] - q[r] : 0.0;
+      sq[row * BX_LD + lc] = v;
+      z = __builtin_amdgcn_mfma_f64_16x16x4f64(x4[r], kq[r] + v, z, 0, 0, 0);
     }
 #pragma unroll
-    for (int e = 0; e < 4; e++)
-#pragma unroll
-      for (int a = 0; a < BT; a++) { const double v = wsum(acc[e][a]); if (lane == 0) red[wave][e * BT + a] = v; }
-    __syncthreads();
-    if (tid < 4 * BT) L.bU[(int64_t)slab * LAZY_TM * BT + r0 * BT + tid] = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
-    return;
-  }
-  // sums in a fixed order: thread (a, b) walks the column blocks
-  for (int idx = tid; idx < BT * BT + BT; idx += 256) {
-    double v = 0;
-    int cb = 0;
-    for (; cb + 8 <= col_blocks; cb += 8) {     // eight loads in flight; the order of the sum stays fixed
-      double pv[8];
-#pragma unroll
-      for (int u = 0; u < 8; u++) pv[u] = L.bpart[(int64_t)(cb + u) * (BT * BT + BT) + idx];
-#pragma unroll
-      for (int u = 0; u < 8; u++) v += pv[u];
-    }
-    for (; cb < col_blocks; cb++) v += L.bpart[(int64_t)cb * (BT * BT + BT) + idx];
-    if (idx < BT * BT) { const int a = idx / BT, b = idx % BT; if (b <= a && a < t) { L.bYY[a * BT + b] = v; L.bYY[b * BT + a] = v; } }
-    else if (idx - BT * BT < t) L.bdl[idx - BT * BT] = v;
+    for (int r = 0; r < 4; r++) sZ[wave][4 * r + lr][lc] = z[r];
   }
   __syncthreads();
-  if (tid == 0) {
-    double dsum = 0;
-    for (int a = 0; a < t; a++) dsum += L.bdl[a];
-    const int it = ctrl->iters;
-    ctrl->obj = ctrl->obj - dsum;            // D is negative definite: -sum <Z_G[a], Y[a]> >= 0
-    ctrl->iters = it + t; ctrl->accepted += t; ctrl->tau_inc = t;
-    if (trace_out) for (int a = 0; a < t; a++) trace_out[it + a] = L.bG[a];
+  if (wave == 7) {
+    swd4 y;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int a = 4 * r + lr;
+      double v = (double)n0[r], z = kgg[r];
+#pragma unroll
+      for (int w = 0; w < 8; w++) { v -= sS[w][a][lc]; z -= sZ[w][a][lc]; }
+      y[r] = (a < t && lc < t) ? -v : (a == lc ? 1.0 : 0.0);
+      sW[a][lc] = (a < t && lc < t) ? z : 0.0;            // Z_G Z_G^T
+    }
+    bool flag = false;
+    inv16_steps<0>(y, lane, t, flag);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int a = 4 * r + lr;
+      const double v = (a < t && lc < t) ? -y[r] : 0.0;
+      sD[a][lc] = v; L.bD[a * BT + lc] = v;
+    }
+    if (lane < BT) L.bG[lane] = lane < t ? g : -1;
+    if (__any(flag) && lane == 0) ctrl->notpd = 1;
+  }
+  {
+    const lzd4 p = product(mv, sq);
+#pragma unroll
+    for (int r = 0; r < 4; r++) p4[r] = wave * 16 + 4 * r + lr < tau ? p[r] : 0.0;
+  }
+  __syncthreads();
+  // the tables of Q have been read: P takes their place as an operand (rows = picks of D to contract)
+  {
+#pragma unroll
+    for (int r = 0; r < 4; r++) sq[(wave * 16 + 4 * r + lr) * BX_LD + lc] = p4[r];      // this wave's rows only
+    asm volatile("" ::: "memory");      // (a wave's shared-memory operations are in order; the compiler must keep them so)
+    lzd4 u = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 4; k++) u = __builtin_amdgcn_mfma_f64_16x16x4f64(sq[(wave * 16 + lc) * BX_LD + 4 * k + lr], sD[4 * k + lr][lc], u, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; r++) L.bU[(wave * 16 + 4 * r + lr) * BT + lc] = u[r];
+    // K_TT grows by the picks
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int k = wave * 16 + 4 * r + lr;
+      if (k < tau && lc < t) { L.KT[k * LAZY_TM + tau + lc] = kq[r]; L.KT[(tau + lc) * LAZY_TM + k] = kq[r]; }
+    }
+  }
+  if (wave == 7) {
+    lzd4 dz = {0.0, 0.0, 0.0, 0.0}, yy = dz;
+#pragma unroll
+    for (int k = 0; k < 4; k++) dz = __builtin_amdgcn_mfma_f64_16x16x4f64(sD[lc][4 * k + lr], sW[4 * k + lr][lc], dz, 0, 0, 0);      // D Z_G Z_G^T
+    double dsum = 0.0;                                    // sum_a <Z_G[a], Y[a]>: its trace
+#pragma unroll
+    for (int r = 0; r < 4; r++) { if (4 * r + lr == lc) dsum += dz[r]; if (4 * r + lr < t && lc < t) L.KT[(tau + 4 * r + lr) * LAZY_TM + tau + lc] = kgg[r]; }
+    dsum = wsum(dsum);
+#pragma unroll
+    for (int r = 0; r < 4; r++) sW[4 * r + lr][lc] = dz[r];      // (read above by this wave alone)
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int k = 0; k < 4; k++) yy = __builtin_amdgcn_mfma_f64_16x16x4f64(sW[lc][4 * k + lr], sD[4 * k + lr][lc], yy, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; r++) L.bYY[(4 * r + lr) * BT + lc] = yy[r];
+    if (lane == 0) {
+      const int it = ctrl->iters;
+      ctrl->obj = ctrl->obj - dsum;            // D is negative definite: the objective rises
+      ctrl->iters = it + t; ctrl->accepted += t; ctrl->tau_inc = t;
+      if (trace_out) for (int a = 0; a < t; a++) trace_out[it + a] = s_pick[a] >> 9;
+    }
   }
 }
 
 // Rows: the sums over the pending pivots, D wt and the two quadratic forms of every row on v_mfma_f64_16x16x4_f64.  A wave takes 16
-// rows, lane (lr, lc) holds the picks 4 r + lr of row lc; a workgroup of 64 rows leaves two selection records.  As 8 lanes per
+// rows, lane (lr, lc) holds the picks 4 r + lr of row lc; a workgroup of 64 rows leaves their removal list.  As 8 lanes per
 // row, with the forms left to one of them, a removal of 10 of 8192 rows took 35 us here.
-__global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int m, int t, int row_groups,
-                                                          int row_wgs, int col_blocks, SearchCtrl* ctrl, int32_t* __restrict__ kept,
+__global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float* __restrict__ N0, int d1, int t, int row_groups,
+                                                          int row_wgs, SearchCtrl* ctrl, int32_t* __restrict__ kept,
                                                           double* __restrict__ rho, double* __restrict__ diag,
                                                           double* __restrict__ score) {
   __shared__ double sX[LAZY_TM * BX_LD], sU[LAZY_TM * BX_LD], sD[BT * BT], sYY[BT * BT];
   __shared__ int sts[LAZY_TM], sG[BT], sSlot[BT];
-  __shared__ double s_sc[64];
-  __shared__ int s_kp[64];
-  if (idle(ctrl)) return;
+  __shared__ double s_sc[LIST_ROWS];
+  __shared__ int s_cnt[4][LIST_ROWS];
+  if ((ctrl->done | ctrl->pause) != 0) return;
   const int tid = threadIdx.x, tau = ctrl->tau, b = blockIdx.x;
   if (b < row_wgs) {
-    for (int idx = tid; idx < LAZY_TM * BT; idx += 256) {
+    for (int idx = tid; idx < (tau + 15) / 16 * 16 * BT; idx += 256) {      // what the loop below reads: zero from tau on
       const int r = idx / BT, a = idx % BT;
-      double u = 0;
-#pragma unroll
-      for (int sl = 0; sl < BU_SLABS; sl++) u += L.bU[(int64_t)sl * LAZY_TM * BT + idx];
-      sX[r * BX_LD + a] = L.bX[idx]; sU[r * BX_LD + a] = r < tau ? u : 0.0;
+      sX[r * BX_LD + a] = L.bX[idx]; sU[r * BX_LD + a] = L.bU[idx];
     }
     for (int idx = tid; idx < BT * BT; idx += 256) { const int a = idx / BT, c = idx % BT; sD[idx] = L.bD[idx]; sYY[idx] = (a < t && c < t) ? L.bYY[idx] : 0.0; }
     for (int s = tid; s < LAZY_TM; s += 256) sts[s] = (s < tau) ? L.tslot[s] : 0;
@@ -1582,7 +1040,7 @@ __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float
         n0[r] = nsym1(N0, d1, rc, sG[a]);
         gb0[r] = L.GbT[(int64_t)sSlot[a] * d1 + rc];
       }
-      const int ps = L.pos[rc], kp0 = kept[rc];
+      const int ps = L.pos[rc], kp0 = kept[rc], slot0 = L.cslot[min(grp * LIST_ROWS + lane, d1 - 1)];
       const double rho0 = rho[rc], diag0 = diag[rc];
       lzd4 dx = {0.0, 0.0, 0.0, 0.0}, du = dx, dw = dx;
       const float* crow = L.C0R + (int64_t)rc * LAZY_TM;
@@ -1647,39 +1105,14 @@ __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float
           sc = r / fabs(dn);
           score[row] = sc;
         }
-        s_sc[wave * 16 + lc] = sc; s_kp[wave * 16 + lc] = kp;
+        s_sc[wave * 16 + lc] = list_score(kp > 0, sc);
       }
       __syncthreads();
-      if (wave < 2 && grp * 2 + wave < (d1 + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK) {
-        const int e = wave * 32 + (lane & 31), kp = lane < 32 ? s_kp[e] : -1;
-        double mn1 = kp > 0 ? s_sc[e] : INFINITY, mx1 = kp == 0 ? s_sc[e] : -INFINITY, mn2 = INFINITY, mx2 = -INFINITY;
-        int imn = kp > 0 ? grp * 64 + e : -1, imx = kp == 0 ? grp * 64 + e : -1;
-        wave_merge(mn1, mn2, imn, mx1, mx2, imx);          // lanes without a row hold the neutral record
-        if (lane == 63) {
-          SelRec rec; rec.mn1 = mn1; rec.mn2 = mn2; rec.mx1 = mx1; rec.mx2 = mx2; rec.imn = imn; rec.imx = imx;
-          L.sel[grp * 2 + wave] = rec;
-        }
-      }
+      write_list(L.lval + (int64_t)grp * LIST_N, L.lrow + (int64_t)grp * LIST_N, s_sc, s_cnt, grp * LIST_ROWS, slot0, lane, wave);
       __syncthreads();
-    }
-  } else if (b < row_wgs + col_blocks) {
-    const int cb = b - row_wgs, slice = tid >> 6, col = cb * COLS_PER_BLOCK + (tid & 63);
-    for (int idx = tid; idx < LAZY_TM * BT; idx += 256) sX[idx] = L.bX[idx];
-    __syncthreads();
-    if (col < m) {
-      double y[BT];
-#pragma unroll
-      for (int a = 0; a < BT; a++) y[a] = (a < t) ? L.bY[(int64_t)a * m + col] : 0.0;
-      for (int r = slice; r < tau; r += 4) {
-        double v = 0;
-#pragma unroll
-        for (int a = 0; a < BT; a++) v += sX[r * BT + a] * y[a];
-        L.ZT[(int64_t)r * m + col] -= v;
-      }
-      for (int a = slice; a < t; a += 4) L.ZT[(int64_t)(tau + a) * m + col] = y[a];
     }
   } else {
-    const int mb = b - row_wgs - col_blocks, nmb = gridDim.x - row_wgs - col_blocks;
+    const int mb = b - row_wgs, nmb = gridDim.x - row_wgs;
     double* Mi = L.Minv;
     // M^-1 += X D X^T: a wave per lower 16 x 16 tile (mirrored, so that M^-1 stays symmetric to the bit)
     const int lane = tid & 63, lr = lane >> 4, lc = lane & 15;
@@ -1712,35 +1145,26 @@ __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float
   }
 }
 
-hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int take, const int32_t* pick,
-                                    hipStream_t s) {
-  if (take < 1 || take > BT) return hipErrorInvalidValue;
-  const int rg = (d.d1 + 63) / 64, cb = (d.m + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
-  hipLaunchKernelGGL(blk_prep_kernel, dim3(1), dim3(512), 0, s, L, t.N, d.d1, take, pick, t.kept, t.ctrl);
-  hipLaunchKernelGGL(blk_cols_kernel, dim3(cb), dim3(256), 0, s, L, t.Z, d.m, take, t.ctrl);
-  hipLaunchKernelGGL(blk_gemv_kernel, dim3(LAZY_TM + 1), dim3(256), 0, s, L, d.m, take, cb, t.ctrl, t.trace_out);
-  const int row_wgs = std::min(rg, 256);
-  hipLaunchKernelGGL(blk_update_kernel, dim3(row_wgs + cb + 16), dim3(256), 0, s, L, t.N, d.d1, d.m, take, rg, row_wgs, cb, t.ctrl,
-                     t.kept, t.gram, t.dblk, t.score);
+hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int take, bool own_pick, int tau_most, int32_t* pick,
+                                    float* gap, hipStream_t s) {
+  if (take < 1 || take > BT || removal_list_count(d.d1) > PREP_LISTS) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(blk_prep_kernel, dim3(1), dim3(PREP_T), 0, s, L, t.N, d.d1, take, own_pick ? 1 : 0, removal_list_count(d.d1), tau_most, pick, gap, t.kept,
+                     t.ctrl, t.trace_out);
+  const int rg = (d.d1 + 63) / 64, row_wgs = std::min(rg, 256);
+  hipLaunchKernelGGL(blk_update_kernel, dim3(row_wgs + 16), dim3(256), 0, s, L, t.N, d.d1, take, rg, row_wgs, t.ctrl, t.kept, t.gram, t.dblk, t.score);
   return hipGetLastError();
 }
 
-hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode, bool swaps) {
+hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
   hipError_t e = hipMemsetAsync(L.pos, 0xFF, (size_t)d.d1 * 4, s);
   if (e != hipSuccess) return e;
-  e = hipMemsetAsync(L.Minv, 0, (size_t)LAZY_TM * LAZY_TM * 8, s);
-  if (e != hipSuccess) return e;
+  for (double* M : {L.Minv, L.Minv2, L.KT})      // finite beyond the pending pivots
+    if ((e = hipMemsetAsync(M, 0, (size_t)LAZY_TM * LAZY_TM * 8, s)) != hipSuccess) return e;
   e = hipMemsetAsync(L.C0R, 0, (size_t)d.d1 * LAZY_TM * 4, s);
   if (e != hipSuccess) return e;
-  if (swaps) {
-    e = hipMemsetAsync(L.Minv2, 0, (size_t)LAZY_TM * LAZY_TM * 8, s);
-    if (e != hipSuccess) return e;
-    e = hipMemsetAsync(L.KT, 0, (size_t)LAZY_TM * LAZY_TM * 8, s);
-    if (e != hipSuccess) return e;
-  }
-  e = launch_candidates(d, t, L, s, mode, swaps);
+  e = launch_candidates(d, t, L, s, mode);
   if (e != hipSuccess) return e;
-  return swaps ? launch_swap_records(d, t, L, s) : launch_partials(d, t, L, s);
+  return launch_picks(d, t, L, s, mode);
 }
 
 }  // namespace osscar

@@ -129,7 +129,7 @@ __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* _
 }
 
 // NT threads, RPW rows per workgroup, NT / RPW lanes per row.  cin: control block before this launch, cout: after it.
-// limit: iterations to have run after this launch at most; beyond it a launch does nothing, and neither does a forced pair whose
+// limit: iterations to have run after this launch at most; beyond it a launch does nothing, and neither does a given pair or row whose
 // predecessor has not run (its launch fetched products).  single != nullptr: removal of the one row *single (Case 1 alone).
 template <int NT, int RPW>
 __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* __restrict__ N0, const float* __restrict__ Z0, int d1, int m,
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
       L.rec2[wg] = r;
     }
   };
-  const bool idle = (cin->done | cin->pause) != 0 || cin->iters >= limit || (forced_g >= 0 && cin->iters < limit - 1);
+  const bool idle = (cin->done | cin->pause) != 0 || cin->iters >= limit || ((forced_g >= 0 || single) && cin->iters < limit - 1);
   // ---- pick: lanes of the first half of the workgroup hold the leaving side's records, the others the entering side's
   if (rt >= nwg) { v1 = INFINITY; v2 = INFINITY; i1 = -1; sl1 = -1; }
   double wv = v1;

@@ -38,18 +38,6 @@ __device__ __forceinline__ double wsum(double v) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63), hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
   return __hiloint2double(hi, lo);
 }
-// merge of two (best, second, index) records; lowest index wins ties
-__device__ __forceinline__ void merge_min(double& a1, double& a2, int& ia, double b1, double b2, int ib) {
-  const bool takeb = (ib >= 0) && (ia < 0 || b1 < a1 || (b1 == a1 && ib < ia));
-  const double n1 = takeb ? b1 : a1, other = takeb ? a1 : b1;
-  a2 = fmin(fmin(a2, b2), other); a1 = n1; ia = takeb ? ib : ia;
-}
-__device__ __forceinline__ void merge_max(double& a1, double& a2, int& ia, double b1, double b2, int ib) {
-  const bool takeb = (ib >= 0) && (ia < 0 || b1 > a1 || (b1 == a1 && ib < ia));
-  const double n1 = takeb ? b1 : a1, other = takeb ? a1 : b1;
-  a2 = fmax(fmax(a2, b2), other); a1 = n1; ia = takeb ? ib : ia;
-}
-
 // Sum over each group of eight consecutive lanes (every lane of the group receives it): pairs and quads by quad
 // permutations, the two quads of a half row by row_half_mirror (lane i of the half row reads lane 7 - i, which by then
 // holds the other quad's sum).
@@ -58,42 +46,6 @@ __device__ __forceinline__ double sum8(double v) {
   v += dpp_get<0x4e, 0xf>(v);
   v += dpp_get<0x141, 0xf>(v);
   return v;
-}
-
-// The (best, second, index) records of the 64 lanes of a wave merged into lane 63, by the same data-parallel moves as
-// wsum (each step joins disjoint sets of lanes, so no record meets itself; lanes that a row mask leaves out see the
-// neutral record).  Lanes without a candidate hold the neutral record (+-inf, index -1).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_merge_step(double& mn1, double& mn2, int& imn, double& mx1, double& mx2, int& imx) {
-  const double b1 = dpp_get_or<CTRL, ROW_MASK>(mn1, INFINITY), b2 = dpp_get_or<CTRL, ROW_MASK>(mn2, INFINITY);
-  const int ib = dpp_get_or<CTRL, ROW_MASK>(imn, -1);
-  const double c1 = dpp_get_or<CTRL, ROW_MASK>(mx1, -INFINITY), c2 = dpp_get_or<CTRL, ROW_MASK>(mx2, -INFINITY);
-  const int ic = dpp_get_or<CTRL, ROW_MASK>(imx, -1);
-  merge_min(mn1, mn2, imn, b1, b2, ib);
-  merge_max(mx1, mx2, imx, c1, c2, ic);
-}
-__device__ __forceinline__ void wave_merge(double& mn1, double& mn2, int& imn, double& mx1, double& mx2, int& imx) {
-  dpp_merge_step<0xb1, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x4e, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x124, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x128, 0xf>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x142, 0xa>(mn1, mn2, imn, mx1, mx2, imx);
-  dpp_merge_step<0x143, 0xc>(mn1, mn2, imn, mx1, mx2, imx);
-}
-
-// The same moves on (value, index) alone: lane 63 ends with the smallest value (lowest index on ties) and the largest.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_best_step(double& mn, int& imn, double& mx, int& imx) {
-  const double b = dpp_get_or<CTRL, ROW_MASK>(mn, INFINITY), c = dpp_get_or<CTRL, ROW_MASK>(mx, -INFINITY);
-  const int ib = dpp_get_or<CTRL, ROW_MASK>(imn, -1), ic = dpp_get_or<CTRL, ROW_MASK>(imx, -1);
-  const bool tb = (ib >= 0) & ((imn < 0) | (b < mn) | ((b == mn) & (ib < imn)));      // (no branches)
-  const bool tc = (ic >= 0) & ((imx < 0) | (c > mx) | ((c == mx) & (ic < imx)));
-  mn = tb ? b : mn; imn = tb ? ib : imn; mx = tc ? c : mx; imx = tc ? ic : imx;
-}
-// ... and on plain values: lane 63 ends with the minimum of lo and the maximum of hi over the wave
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_minmax_step(double& lo, double& hi) {
-  lo = fmin(lo, dpp_get_or<CTRL, ROW_MASK>(lo, INFINITY)); hi = fmax(hi, dpp_get_or<CTRL, ROW_MASK>(hi, -INFINITY));
 }
 
 // (value, index): the smaller value, the lower index on ties, index -1 = none; six data-parallel steps leave the best of the

@@ -583,3 +583,28 @@ def test_rows_of_several_calls_in_one_product(d1, m, chunks, target):
     assert torch.equal(H[off], Hr[off]) and H[0, 1] == Hr[0, 1] == H[1, 0] == 1.0
     if target:
         assert torch.equal(G[2:], (Xd.T @ Y.double())[2:])
+
+
+@pytest.mark.parametrize("equal", [False, True])
+@pytest.mark.parametrize("p,t_hat", [(40, 3), (70, 16), (1030, 10), (8192, 16), (8193, 7), (30100, 16)])
+def test_picks_of_block_removals(p, t_hat, equal):
+    """The rows of an iteration come from sorted lists of every 64 rows: fewer rows than a list, more lists than groups of them, more entries
+    than are staged (from 30081 rows on).  With H = I the cost of a row is its weights' squared norm, whatever has left, so the
+    removals go by that norm; of equal ones the lowest rows leave first, past those whose products are computed ahead."""
+    pkg = _pkg()
+    m, iters = 8, 3
+    k = p - iters * t_hat
+    g = torch.Generator().manual_seed(p)
+    scale = torch.ones(p) if equal else 1.0 + torch.randperm(p, generator=g).float() / p
+    W = (torch.ones(p, m) * scale[:, None]).to(DEV)
+    H = torch.eye(p, device=DEV)
+    s = pkg.Solver(p, m, p, 1, k, 1, torch.float32, torch.float32, DEV, from_dense=True)
+    s.osscar_set_quadratic(H, W, float((W.double() ** 2).sum()), np.ones(p))
+    obj, steps, gaps = s.osscar_init_greedy(t_hat)
+    s.close()
+    order = np.argsort(scale.double().numpy(), kind="stable")
+    assert [len(x) for x in steps] == [t_hat] * iters and sum(steps, []) == order[:iters * t_hat].tolist()
+    cost = np.append(scale.double().numpy()[order] ** 2, np.inf)
+    for i, gap in enumerate(gaps):
+        lo, hi = cost[(i + 1) * t_hat - 1], cost[(i + 1) * t_hat]
+        assert abs(gap - (hi - lo) / lo) <= 1e-6
