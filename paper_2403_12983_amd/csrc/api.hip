@@ -1112,7 +1112,7 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
       const int off = done - acc;                       // removals of iteration it_idx already applied
       HIPCHK(c, run.flush());       // also clears pause
       for (int i = off; i < takes[it_idx]; i++) HIPCHK(c, step(i, h.iters + i - off + 1));   // its pick list is still on the device
-      if (use_block) HIPCHK(c, launch_removal_lists(d, run.t, run.L, s));
+      if (use_block) HIPCHK(c, launch_removal_lists(d, run.t, run.L, s, false));
       pending = takes[it_idx] - off;
       batch = acc + takes[it_idx];
       iter += it_idx + 1;

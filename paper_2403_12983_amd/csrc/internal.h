@@ -220,9 +220,7 @@ struct TabPtrs {
 };
 
 size_t group_part_doubles(int64_t p, int64_t q, int64_t m);
-hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s);
-hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s);        // first half: Gram and diagonal blocks
-hipError_t launch_refresh_from_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s);   // second half: the scores from them   // gram, dblk, score from N, Z
+hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s);   // gram, dblk, score from N, Z
 // ev (optional): three events recorded before the bulk update of N, after it, and after the update of Z.
 // single (optional, device): removal of the one group *single instead of a swap (Case 1 alone; no selection kernel).
 // exact_in: the entering group is the argmax of the exact gain of the pair with the selected leaving group.
@@ -284,7 +282,7 @@ hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& 
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int tau_most,
                             hipStream_t s, const int32_t* single = nullptr, int forced_out = -1, int forced_in = -1);
 int swap_record_count(int64_t d1);
-hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
+hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);
 hipError_t launch_zt(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
 // A second stream and two events: the flush runs its update of N0 there, beside the candidate selection and the look-ahead
@@ -296,7 +294,7 @@ hipError_t launch_zt(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipS
 hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int take, bool own_pick, int tau_most, int32_t* pick,
                                     float* gap, hipStream_t s);
 int removal_list_count(int64_t d1);
-hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
+hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 
 struct SideStream { hipStream_t stream = nullptr; hipEvent_t fork = nullptr, join = nullptr; };
 // side == nullptr (or no stream in it): everything in order on s

@@ -24,13 +24,12 @@
 // pivot in two launches (below).
 #include "internal.h"
 #include "inverse16.h"
+#include "lazy_device.h"
 #include "wave.h"
 #include <algorithm>
 
 namespace osscar {
 
-// pending pivots including those of the iteration that ran last (for kernels outside an iteration)
-__device__ __forceinline__ int tau_all(const SearchCtrl* c) { return c->tau + c->tau_inc; }
 
 // ------------------------------------------------------------------------------------------------
 // flush: apply the pending correction to N0, Z0 and empty T
@@ -68,12 +67,7 @@ __global__ __launch_bounds__(256) void lazy_fix_z_kernel(LazyPtrs L, float* __re
   const int s0 = blockIdx.y * FIX_SPB, s1 = min(tau, s0 + FIX_SPB);
   for (int s = s0; s < s1; s++) Z0[(int64_t)L.Tidx[s] * m + col] = (float)((double)L.Jsg[s] * L.ZT[(int64_t)s * m + col]);
 }
-__global__ __launch_bounds__(256) void lazy_reset_kernel(LazyPtrs L, SearchCtrl* ctrl) {
-  const int tau = tau_all(ctrl);
-  for (int s = threadIdx.x; s < tau; s += 256) L.pos[L.Tidx[s]] = -1;
-  __syncthreads();
-  if (threadIdx.x == 0) { ctrl->tau = 0; ctrl->tau_inc = 0; ctrl->pause = 0; ctrl->spare = 0; }
-}
+__global__ __launch_bounds__(256) void lazy_reset_kernel(LazyPtrs L, SearchCtrl* ctrl) { empty_pending(L, ctrl, 256); }
 
 // ------------------------------------------------------------------------------------------------
 // candidate rows and their products with Z0 (after every flush)
@@ -327,11 +321,13 @@ static hipError_t launch_candidate_pick(const TabDims& d, const TabPtrs& t, cons
   hipLaunchKernelGGL(cand_merge_kernel, dim3(2), dim3(1024), 0, s, L, nblk, per_block, cc.n_k, cc.n_c);
   return hipGetLastError();
 }
-// the products of the picked rows with the (flushed) Z0
+// the products of the picked rows with one another and with the (flushed) Z0
 static hipError_t launch_candidate_products(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
   const CandCounts cc = cand_counts(mode);
   const int n_k = cc.n_k, n_c = cc.n_c;
   if (mode == 2) return hipSuccess;
+  const hipError_t ek = launch_cand_gram(d, t, L, n_k + n_c, s);
+  if (ek != hipSuccess) return ek;
   // one block of 32 NT candidates per workgroup: 128 (and multiples of it, block by block), 160 or 192
   const int ncand = n_k + n_c;
   const int nt = (ncand % 128 == 0) ? 4 : ((ncand == 160) ? 5 : ((ncand == 192) ? 6 : 0));
@@ -359,16 +355,10 @@ static hipError_t launch_candidate_products(const TabDims& d, const TabPtrs& t, 
   g.C = L.GbT; g.ldc = d.d1; g.alpha = 1.0; g.beta = 0.0; g.c_is_f64 = 1; g.ws = L.gemm_ws; g.ws_bytes = L.gemm_ws_bytes;
   return launch_gemm_f64acc(g, s);
 }
-static hipError_t launch_candidates(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
-  hipError_t e = launch_candidate_pick(d, t, L, s, mode);
-  if (e != hipSuccess) return e;
-  if ((e = launch_cand_gram(d, t, L, cand_counts(mode).n_k + cand_counts(mode).n_c, s)) != hipSuccess) return e;
-  return launch_candidate_products(d, t, L, s, mode);
-}
-
 // what the next iteration picks from: the removal lists of the removal-only loops, the records of the swaps
-static hipError_t launch_picks(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
-  return mode == 1 ? launch_removal_lists(d, t, L, s) : launch_swap_records(d, t, L, s);
+// (refresh: after a flush, with the second half of the score refresh and the pending set emptied in the same launch)
+static hipError_t launch_picks(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode, bool refresh) {
+  return mode == 1 ? launch_removal_lists(d, t, L, s, refresh) : launch_swap_records(d, t, L, s, refresh);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -646,26 +636,39 @@ hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs&
   const bool two = side && side->stream;
   hipStream_t sn = two ? side->stream : s;          // stream of the N0 update
   hipError_t err;
-  if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err;
+  // With two streams the chains of N0 (pick of the candidates, E, its pieces, update, fix, diagonal) and of Z0 (ZT, pieces, update, fix,
+  // the candidates' products) run side by side from the start; the events between them: the pieces of C0 are packed here, the
+  // pick is done there, both matrices are final.  (With E, all pieces and the pick before or between them on this stream a flush
+  // of 8192 x 2048 was 0.06 ms longer.)
+  auto here_to_there = [&]() -> hipError_t {
+    if (!two) return hipSuccess;
+    const hipError_t e = hipEventRecord(side->fork, s);
+    return e != hipSuccess ? e : hipStreamWaitEvent(sn, side->fork, 0);
+  };
+  if ((err = here_to_there()) != hipSuccess) return err;
+  if (two) {
+    // The candidates of the next cycle, from the scores as the swaps left them (the refresh below changes them in the last
+    // digits only, and the choice of candidates decides what is computed ahead, not any result)
+    if ((err = launch_candidate_pick(d, t, L, sn, mode)) != hipSuccess) return err;
+    if ((err = hipEventRecord(side->join, sn)) != hipSuccess) return err;
+  }
   {                                     // E = C0 M^-1 (entered in the log of matrix products like the general kernel's launches)
     const size_t shmem = (size_t)(LAZY_TM + 64) * TE_LD * sizeof(float);
     if ((err = hipFuncSetAttribute(reinterpret_cast<const void*>(thin_e_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)) != hipSuccess)
       return err;
     int log_slot = -1;
-    gemm_log_open(d.d1, LAZY_TM, LAZY_TM, 0, s, &log_slot);
-    hipLaunchKernelGGL(thin_e_kernel, dim3((d.d1 + 63) / 64), dim3(256), shmem, s, L, d.d1, t.ctrl);
-    gemm_log_close(log_slot, s);
+    gemm_log_open(d.d1, LAZY_TM, LAZY_TM, 0, sn, &log_slot);
+    hipLaunchKernelGGL(thin_e_kernel, dim3((d.d1 + 63) / 64), dim3(256), shmem, sn, L, d.d1, t.ctrl);
+    gemm_log_close(log_slot, sn);
   }
   // the three thin operands in matrix-core order (C0's pieces serve both updates)
   const int dpad = (d.d1 + 127) / 128 * 128, mpad = (d.m + 127) / 128 * 128;
   uint4* Epk = reinterpret_cast<uint4*>(L.Epk); uint4* Cpk = reinterpret_cast<uint4*>(L.Cpk); uint4* Zpk = reinterpret_cast<uint4*>(L.Zpk);
+  hipLaunchKernelGGL(rk_pack_rows_kernel, dim3((16 * dpad + 255) / 256), dim3(256), 0, sn, L.E, d.d1, dpad, Epk);
   hipLaunchKernelGGL(rk_pack_rows_kernel, dim3((16 * dpad + 255) / 256), dim3(256), 0, s, L.C0R, d.d1, dpad, Cpk);
-  hipLaunchKernelGGL(rk_pack_rows_kernel, dim3((16 * dpad + 255) / 256), dim3(256), 0, s, L.E, d.d1, dpad, Epk);
+  if ((err = here_to_there()) != hipSuccess) return err;
+  if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err;
   hipLaunchKernelGGL(rk_pack_cols_kernel, dim3((16 * mpad + 255) / 256), dim3(256), 0, s, L.ZT32, d.m, mpad, Zpk);
-  if (two) {
-    if ((err = hipEventRecord(side->fork, s)) != hipSuccess) return err;
-    if ((err = hipStreamWaitEvent(sn, side->fork, 0)) != hipSuccess) return err;
-  }
   // N0 -= E C0^T on the lower block triangle (pivot rows and columns are rewritten below)
   hipLaunchKernelGGL(rk_update_kernel, dim3((unsigned)L.n_tiles_sym), dim3(256), 0, sn, Epk, dpad, Cpk, dpad, t.N, (int64_t)d.d1, d.d1, d.d1,
                      L.tiles_sym, (double*)nullptr);
@@ -676,26 +679,23 @@ hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs&
   hipLaunchKernelGGL(rk_update_kernel, dim3((unsigned)L.n_tiles_rect), dim3(256), 0, s, Cpk, dpad, Zpk, mpad, t.Z, (int64_t)d.m, d.d1, d.m,
                      L.tiles_rect, two ? L.rowsq : (double*)nullptr);
   hipLaunchKernelGGL(lazy_fix_z_kernel, dim3(mb, LAZY_TM / FIX_SPB), dim3(256), 0, s, L, t.Z, d.m, t.ctrl);
-  if (two) {
-    // The second stream goes on, once both matrices are final, with the first half of the score refresh (row norms from the
-    // stretch sums, diagonal of N0); this one with the products of the picked rows with the new Z0.
-    if ((err = hipEventRecord(side->fork, s)) != hipSuccess) return err;
-    if ((err = hipStreamWaitEvent(sn, side->fork, 0)) != hipSuccess) return err;
-    hipLaunchKernelGGL(norms_from_stretches_kernel, dim3((d.d1 + 255) / 256 + LAZY_TM), dim3(256), 0, sn, L, d.d1, d.m, 2 * ((d.m + 127) / 128),
-                       (d.d1 + 255) / 256, t.N, t.Z, t.gram, t.dblk, t.ctrl);
-    if ((err = hipEventRecord(side->join, sn)) != hipSuccess) return err;
-    // The candidates of the next cycle, from the scores as the swaps left them (the refresh below changes them in the last
-    // digits only, and the choice of candidates decides what is computed ahead, not any result): two sorts of one
-    // workgroup each; this stream has the time, the second one's chain is the longer.
-    err = launch_candidates(d, t, L, s, mode);
-    if (err != hipSuccess) return err;
-    if ((err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
+  if (!two) {
+    hipLaunchKernelGGL(lazy_reset_kernel, dim3(1), dim3(256), 0, s, L, t.ctrl);
+    if ((err = launch_refresh_scores(d, t, s)) != hipSuccess) return err;
+    if ((err = launch_candidate_pick(d, t, L, s, mode)) != hipSuccess) return err;
+    if ((err = launch_candidate_products(d, t, L, s, mode)) != hipSuccess) return err;
+    return launch_picks(d, t, L, s, mode, false);
   }
-  hipLaunchKernelGGL(lazy_reset_kernel, dim3(1), dim3(256), 0, s, L, t.ctrl);
-  err = two ? launch_refresh_from_blocks(d, t, s) : launch_refresh_scores(d, t, s);
-  if (err != hipSuccess) return err;
-  if (!two && (err = launch_candidates(d, t, L, s, mode)) != hipSuccess) return err;
-  return launch_picks(d, t, L, s, mode);
+  // The second stream goes on, once both matrices are final, with the first half of the score refresh (row norms from the
+  // stretch sums, diagonal of N0); this one with the products of the picked rows with the new Z0.
+  if ((err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;      // the pick
+  if ((err = here_to_there()) != hipSuccess) return err;
+  hipLaunchKernelGGL(norms_from_stretches_kernel, dim3((d.d1 + 255) / 256 + LAZY_TM), dim3(256), 0, sn, L, d.d1, d.m, 2 * ((d.m + 127) / 128),
+                     (d.d1 + 255) / 256, t.N, t.Z, t.gram, t.dblk, t.ctrl);
+  if ((err = hipEventRecord(side->join, sn)) != hipSuccess) return err;
+  if ((err = launch_candidate_products(d, t, L, s, mode)) != hipSuccess) return err;
+  if ((err = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return err;
+  return launch_picks(d, t, L, s, mode, true);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -745,18 +745,21 @@ __device__ __forceinline__ void write_list(double* __restrict__ val, int32_t* __
 }
 // a score as the lists count it: only finite costs of kept rows
 __device__ __forceinline__ double list_score(bool kept, double score) { return kept && score < INFINITY ? score : INFINITY; }
-__global__ __launch_bounds__(256) void removal_lists_kernel(LazyPtrs L, int d1, const int32_t* __restrict__ kept, const double* __restrict__ score) {
+__global__ __launch_bounds__(256) void removal_lists_kernel(LazyPtrs L, int d1, const int32_t* __restrict__ kept, double* __restrict__ score,
+                                                             const double* __restrict__ gram, const double* __restrict__ dblk, SearchCtrl* ctrl, int refresh) {
   __shared__ double sc[LIST_ROWS];
   __shared__ int s_cnt[4][LIST_ROWS];
   const int tid = threadIdx.x, lane = tid & 63, row = blockIdx.x * LIST_ROWS + lane, rc = min(row, d1 - 1);
   const int slot = L.cslot[rc];
-  if (tid < LIST_ROWS) sc[tid] = list_score(row < d1 && kept[rc] != 0, score[rc]);
+  if (tid < LIST_ROWS) sc[tid] = row < d1 ? list_score(kept[rc] != 0, refresh ? fresh_score(rc, kept, gram, dblk, score, ctrl) : score[rc]) : INFINITY;
+  if (refresh && blockIdx.x == 0) empty_pending(L, ctrl, 256);
   __syncthreads();
   write_list(L.lval + (int64_t)blockIdx.x * LIST_N, L.lrow + (int64_t)blockIdx.x * LIST_N, sc, s_cnt, blockIdx.x * LIST_ROWS, slot, lane, tid >> 6);
 }
 int removal_list_count(int64_t d1) { return (int)((d1 + LIST_ROWS - 1) / LIST_ROWS); }
-hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s) {
-  hipLaunchKernelGGL(removal_lists_kernel, dim3(removal_list_count(d.d1)), dim3(256), 0, s, L, d.d1, t.kept, t.score);
+hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh) {
+  hipLaunchKernelGGL(removal_lists_kernel, dim3(removal_list_count(d.d1)), dim3(256), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl,
+                     refresh ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1162,9 +1165,8 @@ hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& 
     if ((e = hipMemsetAsync(M, 0, (size_t)LAZY_TM * LAZY_TM * 8, s)) != hipSuccess) return e;
   e = hipMemsetAsync(L.C0R, 0, (size_t)d.d1 * LAZY_TM * 4, s);
   if (e != hipSuccess) return e;
-  e = launch_candidates(d, t, L, s, mode);
-  if (e != hipSuccess) return e;
-  return launch_picks(d, t, L, s, mode);
+  if ((e = launch_candidate_pick(d, t, L, s, mode)) != hipSuccess || (e = launch_candidate_products(d, t, L, s, mode)) != hipSuccess) return e;
+  return launch_picks(d, t, L, s, mode, false);
 }
 
 }  // namespace osscar

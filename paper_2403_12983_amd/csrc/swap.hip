@@ -16,6 +16,7 @@
 // launches, the first of them one workgroup, with ZT (128 x m) updated and read by every swap, a swap took 25 us at 8192 x 2048 (flushes
 // and waits apart) and 31 at 28672 x 7168; in one launch 13 and 19.
 #include "internal.h"
+#include "lazy_device.h"
 #include "wave.h"
 #include <algorithm>
 
@@ -57,17 +58,19 @@ __device__ __forceinline__ void write_record(SwapRec* rec, const double* sc, con
   }
 }
 
-// the records of the scores as they stand (nothing pending)
+// the records of the scores as they stand (nothing pending); refresh: of the scores from the norms and the diagonal, after a flush
 template <int RPW>
-__global__ __launch_bounds__(128) void swap_records_kernel(LazyPtrs L, int d1, const int32_t* __restrict__ kept, const double* __restrict__ score) {
+__global__ __launch_bounds__(128) void swap_records_kernel(LazyPtrs L, int d1, const int32_t* __restrict__ kept, double* __restrict__ score,
+                                                            const double* __restrict__ gram, const double* __restrict__ dblk, SearchCtrl* ctrl, int refresh) {
   __shared__ double sc[RPW];
   __shared__ int kp[RPW], sl[RPW];
   const int tid = threadIdx.x, row = blockIdx.x * RPW + tid;
   if (tid < RPW) {
     const bool in = row < d1;
-    sc[tid] = in ? score[row] : 0.0; kp[tid] = in ? (kept[row] != 0) : -1; sl[tid] = in ? L.cslot[row] : -1;
+    sc[tid] = !in ? 0.0 : refresh ? fresh_score(row, kept, gram, dblk, score, ctrl) : score[row]; kp[tid] = in ? (kept[row] != 0) : -1; sl[tid] = in ? L.cslot[row] : -1;
   }
   __syncthreads();
+  if (refresh && blockIdx.x == 0) empty_pending(L, ctrl, 128);
   write_record<RPW>(L.rec + blockIdx.x, sc, kp, sl, blockIdx.x * RPW, tid >> 6, tid & 63);
 }
 
@@ -497,12 +500,12 @@ hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& 
   return hipGetLastError();
 }
 
-hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s) {
-  const int nwg = swap_record_count(d.d1);
+hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh) {
+  const int nwg = swap_record_count(d.d1), fr = refresh ? 1 : 0;
   switch (swap_rows_per_wg(d.d1)) {
-    case 32: hipLaunchKernelGGL(swap_records_kernel<32>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score); break;
-    case 64: hipLaunchKernelGGL(swap_records_kernel<64>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score); break;
-    default: hipLaunchKernelGGL(swap_records_kernel<128>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score); break;
+    case 32: hipLaunchKernelGGL(swap_records_kernel<32>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr); break;
+    case 64: hipLaunchKernelGGL(swap_records_kernel<64>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr); break;
+    default: hipLaunchKernelGGL(swap_records_kernel<128>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr); break;
   }
   return hipGetLastError();
 }
@@ -510,8 +513,7 @@ hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtr
 // ---------------------------------------------------------------------------------------------- K and ZT
 typedef double sw_d4 __attribute__((ext_vector_type(4)));
 // K of the picked rows, Zc Zc^T with float64 sums, a workgroup per 16 x 16 tile of its lower triangle (n slots): every wave takes every
-// W-th stretch of 16 columns on v_mfma_f64_16x16x4_f64, the waves' tiles are added in order.  A few microseconds of one chain per
-// wave; m = 7168: 28 stretches per wave.
+// W-th stretch of 16 columns on v_mfma_f64_16x16x4_f64, the waves' tiles are added in order.  Bound by the latency of a wave's loads.
 constexpr int KW = 16;
 __global__ __launch_bounds__(64 * KW) void cand_gram_kernel(LazyPtrs L, const float* __restrict__ Z0, int m) {
   __shared__ double part[KW][16][17];
@@ -522,27 +524,33 @@ __global__ __launch_bounds__(64 * KW) void cand_gram_kernel(LazyPtrs L, const fl
   const float *pa = Z0 + (int64_t)max(ra, 0) * m, *pb = Z0 + (int64_t)max(rb, 0) * m;
   sw_d4 acc = {0.0, 0.0, 0.0, 0.0};
   const int stretches = (m + 15) / 16;
-  if (m % 4 == 0) {
-#pragma unroll 4
-    for (int c = wave; c < stretches; c += KW) {
-      const int k = c * 16 + 4 * lr;                       // a lane's four values are one load; the order of the sum is free
-      const bool in = k < m;
-      const float4 a = *reinterpret_cast<const float4*>(pa + (in ? k : 0)), b = *reinterpret_cast<const float4*>(pb + (in ? k : 0));
-      const bool ia = in && ra >= 0, ib = in && rb >= 0;
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ia ? (double)a.x : 0.0, ib ? (double)b.x : 0.0, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ia ? (double)a.y : 0.0, ib ? (double)b.y : 0.0, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ia ? (double)a.z : 0.0, ib ? (double)b.z : 0.0, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ia ? (double)a.w : 0.0, ib ? (double)b.w : 0.0, acc, 0, 0, 0);
-    }
-  } else {
-    for (int c = wave; c < stretches; c += KW)
+  const bool vec = m % 4 == 0;
+  for (int c0 = wave; c0 < stretches; c0 += 4 * KW) {        // four stretches requested at a time
+    float a[4][4], b[4][4];
 #pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const int k = c * 16 + 4 * e + lr;
+    for (int u = 0; u < 4; u++) {
+      const int c = c0 + u * KW, k0 = c * 16;
+      if (vec) {                                             // a lane's four values are one load; the order of the sum is free
+        const int k = k0 + 4 * lr;
         const bool in = k < m;
-        const double a = (in && ra >= 0) ? (double)pa[k] : 0.0, b = (in && rb >= 0) ? (double)pb[k] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+        const float4 x = *reinterpret_cast<const float4*>(pa + (in ? k : 0)), y = *reinterpret_cast<const float4*>(pb + (in ? k : 0));
+        const bool ia = in && ra >= 0, ib = in && rb >= 0;
+        a[u][0] = ia ? x.x : 0.f; a[u][1] = ia ? x.y : 0.f; a[u][2] = ia ? x.z : 0.f; a[u][3] = ia ? x.w : 0.f;
+        b[u][0] = ib ? y.x : 0.f; b[u][1] = ib ? y.y : 0.f; b[u][2] = ib ? y.z : 0.f; b[u][3] = ib ? y.w : 0.f;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int k = k0 + 4 * e + lr;
+          const bool in = k < m;
+          const float x = pa[in ? k : 0], y = pb[in ? k : 0];
+          a[u][e] = in && ra >= 0 ? x : 0.f; b[u][e] = in && rb >= 0 ? y : 0.f;
+        }
       }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[u][e], (double)b[u][e], acc, 0, 0, 0);
   }
 #pragma unroll
   for (int r = 0; r < 4; r++) part[wave][4 * r + lr][lc] = acc[r];

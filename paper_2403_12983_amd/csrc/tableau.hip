@@ -1194,7 +1194,7 @@ static void launch_score(const TabDims& d, const int32_t* kept, double* gram, do
 
 // the two halves of the refresh: the per-group Gram blocks and diagonal blocks (one pass over Z and the diagonal of N),
 // then the scores from them; a caller may run the first half on another stream
-hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s) {
+static hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s) {
   if (d.q == 1) {
     hipLaunchKernelGGL(gram_dblk_q1_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d.d1, d.m, t.N, t.Z, t.gram, t.dblk);
   } else {
@@ -1204,15 +1204,13 @@ hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipStream_t
   }
   return hipGetLastError();
 }
-hipError_t launch_refresh_from_blocks(const TabDims& d, const TabPtrs& t, hipStream_t s) {
+hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s) {
+  const hipError_t e = launch_refresh_blocks(d, t, s);
+  if (e != hipSuccess) return e;
   ScoreUpdate u;
   u.part = t.part;
   launch_score(d, t.kept, t.gram, t.dblk, t.score, t.ctrl, 0, s, u);
   return hipGetLastError();
-}
-hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s) {
-  const hipError_t e = launch_refresh_blocks(d, t, s);
-  return e != hipSuccess ? e : launch_refresh_from_blocks(d, t, s);
 }
 
 // ------------------------------------------------------------------------------------------------
