@@ -177,6 +177,7 @@ struct SearchCtrl {          // lives in device memory
   double delta;              // exact change of the current pair
   double gap_rem, gap_add;
   int32_t spare;             // one-launch swaps: spare slots of the look-ahead products in use
+  int32_t taken;             // groups: whether the pair of this iteration is taken, until the scores' launch records it
 };
 
 struct TabDims { int d1, m, p, q; };
@@ -221,7 +222,8 @@ struct TabPtrs {
 
 size_t group_part_doubles(int64_t p, int64_t q, int64_t m);
 hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t s);   // gram, dblk, score from N, Z
-// ev (optional): three events recorded before the bulk update of N, after it, and after the update of Z.
+// ev (optional): three events recorded before the bulk update of N, after it, and after the update of Z.  Groups of
+// more than one row: the one launch of both lies between the first two.
 // single (optional, device): removal of the one group *single instead of a swap (Case 1 alone; no selection kernel).
 // exact_in: the entering group is the argmax of the exact gain of the pair with the selected leaving group.
 hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int forced_out, int forced_in, int always_accept,

@@ -969,29 +969,47 @@ __device__ __forceinline__ void stage_panel(float* S, int ks, int k0, int kq, co
 }
 template <int RT> struct GroupUpdLds { float zt[4][16 * RT][GU_LD]; };
 static __host__ __device__ inline int gu_kq(int q) { return (q + 3) / 4 * 4; }
+// The groups of a move's own pivots (g, j; -1: none) take their new rows instead: Z''_g = M1 rZ2 - rZ1 in float64, Z''_j = rZ2.
 template <int RT>
-__global__ __launch_bounds__(256, 2) void group_update_kernel(TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
-                                                            const float* __restrict__ P2, const float* __restrict__ rZ1,
-                                                            const float* __restrict__ rZ2, int single, double* __restrict__ part,
-                                                            int chunk_cols, const SearchCtrl* __restrict__ ctrl) {
-  extern __shared__ float gu_lds[];
-  if (ctrl && ctrl->done) return;
+__device__ __forceinline__ void group_update(float* gu_lds, TabDims d, float* __restrict__ Z, const float* __restrict__ P1,
+                                             const float* __restrict__ P2, const float* __restrict__ rZ1, const float* __restrict__ rZ2,
+                                             const double* __restrict__ M1, int single, double* __restrict__ part, int chunk_cols, int chunks,
+                                             int g, int j, int h, int chunk) {
   constexpr int NT = RT * (RT + 1) / 2;
   float (*zt)[16 * RT][GU_LD] = reinterpret_cast<float (*)[16 * RT][GU_LD]>(gu_lds);
   float* Ps = gu_lds + 4 * 16 * RT * GU_LD;               // [16 RT][ks]: the rows' coefficients, both pivots' halves side by side
-  const int q = d.q, m = d.m, h = blockIdx.x, kq = gu_kq(q), K = P1 ? (single ? kq : 2 * kq) : 0, ks = 2 * kq + 4;
+  const int q = d.q, m = d.m, kq = gu_kq(q), K = (P1 && h != g && h != j) ? (single ? kq : 2 * kq) : 0, ks = 2 * kq + 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   float* Zh = Z + (int64_t)h * q * m;
-  if (K) {
+  const int c_end = min(m, (chunk + 1) * chunk_cols);
+  if (h == g || h == j) {
+    for (int col = chunk * chunk_cols + wave * 16 + lc; col - lc < c_end; col += 64)
+      for (int i0 = 0; i0 < q; i0 += 16) {
+        swd4 acc = {0.0, 0.0, 0.0, 0.0};
+        if (h == g && !single) {
+#pragma unroll 4
+          for (int k0 = 0; k0 < q; k0 += 4) {
+            const int k = k0 + lr;
+            const double av = (i0 + lc < q && k < q) ? M1[(i0 + lc) * q + k] : 0.0, bv = (k < q && col < m) ? (double)rZ2[(int64_t)k * m + col] : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int i = i0 + 4 * r + lr;
+          const int64_t o = (int64_t)i * m + col;
+          if (i < q && col < m) Zh[o] = h == g ? (float)(acc[r] - (double)rZ1[o]) : rZ2[o];
+        }
+      }
+  } else if (K) {
     stage_panel<16 * RT>(Ps, ks, 0, kq, P1 + (int64_t)h * q * q, q, q);
     if (!single) stage_panel<16 * RT>(Ps, ks, kq, kq, P2 + (int64_t)h * q * q, q, q);
   }
   __syncthreads();
-  swd4 g[NT];
+  swd4 gr[NT];
 #pragma unroll
-  for (int t = 0; t < NT; t++) g[t] = swd4{0.0, 0.0, 0.0, 0.0};
-  const int c_end = min(m, ((int)blockIdx.y + 1) * chunk_cols);
-  for (int c0 = blockIdx.y * chunk_cols + wave * 32; c0 < c_end; c0 += 128) {
+  for (int t = 0; t < NT; t++) gr[t] = swd4{0.0, 0.0, 0.0, 0.0};
+  for (int c0 = chunk * chunk_cols + wave * 32; c0 < c_end; c0 += 128) {
     typedef float f4v __attribute__((ext_vector_type(4)));
     f4v acc[RT][2];
     float z[RT][2][4];
@@ -1042,7 +1060,7 @@ __global__ __launch_bounds__(256, 2) void group_update_kernel(TabDims d, float* 
 #pragma unroll
       for (int t = 0, n = 0; t < RT; t++)
 #pragma unroll
-        for (int u = 0; u <= t; u++, n++) g[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t], v[u], g[n], 0, 0, 0);
+        for (int u = 0; u <= t; u++, n++) gr[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t], v[u], gr[n], 0, 0, 0);
     }
     asm volatile("" ::: "memory");
     __builtin_amdgcn_wave_barrier();
@@ -1056,13 +1074,21 @@ __global__ __launch_bounds__(256, 2) void group_update_kernel(TabDims d, float* 
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           double* p = red + t * 256 + r * 64 + lane;
-          *p = w ? *p + g[t][r] : g[t][r];
+          *p = w ? *p + gr[t][r] : gr[t][r];
         }
     }
   }
   __syncthreads();
-  double* out = part + ((int64_t)h * gridDim.y + blockIdx.y) * (NT * 256);
+  double* out = part + ((int64_t)h * chunks + chunk) * (NT * 256);
   for (int idx = tid; idx < NT * 256; idx += 256) out[idx] = red[idx];
+}
+template <int RT>
+constexpr size_t group_update_lds(int kq) { return (size_t)(4 * 16 * RT * GU_LD + 16 * RT * (2 * kq + 4)) * 4; }
+// the groups' Grams of Z as it stands
+template <int RT>
+__global__ __launch_bounds__(256, 2) void group_gram_kernel(TabDims d, float* __restrict__ Z, double* __restrict__ part, int chunk_cols) {
+  extern __shared__ float gu_lds[];
+  group_update<RT>(gu_lds, d, Z, nullptr, nullptr, nullptr, nullptr, nullptr, 0, part, chunk_cols, gridDim.y, -1, -1, blockIdx.x, blockIdx.y);
 }
 // columns per chunk of the pass over Z: about 1024 workgroups, whole steps of 128 columns
 static int gu_chunk_cols(int p, int m) {
@@ -1074,17 +1100,16 @@ size_t group_part_doubles(int64_t p, int64_t q, int64_t m) {
   const int64_t rt = (q + 15) / 16, cc = gu_chunk_cols((int)p, (int)m);
   return (size_t)(p * ((m + cc - 1) / cc) * (rt * (rt + 1) / 2) * 256);
 }
-static hipError_t launch_group_update(const TabDims& d, const TabPtrs& t, const float* P1, const float* P2, int single, const SearchCtrl* ctrl,
-                                      hipStream_t s) {
+static hipError_t launch_group_gram(const TabDims& d, const TabPtrs& t, hipStream_t s) {
   const int cc = gu_chunk_cols(d.p, d.m);
   OSSCAR_BY_TILES(d.q, {
-    const size_t lds = (size_t)(4 * 16 * RT * GU_LD + 16 * RT * (2 * gu_kq(d.q) + 4)) * 4;
+    const size_t lds = group_update_lds<RT>(gu_kq(d.q));
     static_assert(sizeof(GroupUpdLds<RT>) >= RT * (RT + 1) / 2 * 256 * 8, "the reduction shares the tiles' memory");
     if (lds > 65536) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(group_update_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(group_gram_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(group_update_kernel<RT>, dim3(d.p, (d.m + cc - 1) / cc), dim3(256), lds, s, d, t.Z, P1, P2, t.rZ1, t.rZ2, single, t.part, cc, ctrl);
+    hipLaunchKernelGGL(group_gram_kernel<RT>, dim3(d.p, (d.m + cc - 1) / cc), dim3(256), lds, s, d, t.Z, t.part, cc);
   })
   return hipGetLastError();
 }
@@ -1097,18 +1122,46 @@ __global__ __launch_bounds__(256) void dblk_copy_kernel(TabDims d, const float* 
   }
 }
 
+// The exact change of the objective and whether the pair is taken, from the partial sums of the column phase: lane l adds the
+// sums l, l + 64, ... in that order; then the fixed tree of the wave sum.  Known to every lane of every wave that calls it.
+__device__ __forceinline__ bool pair_taken(const SearchCtrl* ctrl, int always_accept, const double* __restrict__ dpart, int nparts, double& delta) {
+  double dsum = 0;
+#pragma unroll 4
+  for (int b = threadIdx.x & 63; b < nparts; b += 64) dsum += dpart[b];
+  delta = __shfl(wave_sum(dsum), 0);
+  return ctrl->notpd == 0 && (always_accept || delta < -ctrl->rel_tol * ctrl->obj);
+}
+// the outcome of a move, into ctrl and the trace (one thread)
+struct PairTrace { int32_t* out = nullptr; int32_t* in = nullptr; float* gap = nullptr; double* obj = nullptr; };
+__device__ __forceinline__ void pair_commit(SearchCtrl* ctrl, bool ok, double delta, const int32_t* single, const PairTrace& tr) {
+  ctrl->delta = delta;
+  const int it = ctrl->iters;
+  ctrl->iters = it + 1;
+  if (single) { ctrl->g_out = *single; ctrl->g_in = -1; }
+  if (ok) { ctrl->obj += delta; ctrl->accepted += 1; } else { ctrl->done = 1; }
+  if (tr.out) tr.out[it] = ctrl->g_out;
+  if (tr.in) tr.in[it] = ctrl->g_in;
+  if (tr.gap) { tr.gap[2 * it] = (float)ctrl->gap_rem; tr.gap[2 * it + 1] = (float)ctrl->gap_add; }
+  if (tr.obj) tr.obj[it] = ctrl->obj;
+}
 // score[h] = Tr(gram_h (sigma dblk_h)^-1), sigma = -1 for kept groups (N_hh = -P_hh), +1 otherwise; one workgroup per group.
-// Before that, if given: gram_h = the sum of its column chunks (part), and the float64 diagonal block of a group outside the
+// After a move (P1): nothing if it was turned down, and the first workgroup records it (pair_commit) where no other reads it.
+// Before the scores, if given: gram_h = the sum of its column chunks (part), and the float64 diagonal block of a group outside the
 // pivots takes -= P1D_h P1_h^T + P2D_h P2_h^T (P1; single: the first term only).
 template <int RT>
 __global__ __launch_bounds__(256) void score_kernel(TabDims d, const int32_t* __restrict__ kept, double* gram, double* dblk,
                                                      double* __restrict__ score, SearchCtrl* ctrl, int skip_if_done,
                                                      const double* __restrict__ part, int chunks, const float* __restrict__ P1,
                                                      const float* __restrict__ P2, const float* __restrict__ P1D,
-                                                     const float* __restrict__ P2D, const int32_t* __restrict__ single) {
+                                                     const float* __restrict__ P2D, const int32_t* __restrict__ single, PairTrace tr) {
   __shared__ InvLds<RT> L;
   __shared__ double red[4];
   if (skip_if_done && ctrl->done) return;          // a search iteration that changed nothing
+  if (P1) {
+    const bool ok = ctrl->taken != 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) pair_commit(ctrl, ok, ctrl->delta, single, tr);
+    if (!ok) return;
+  }
   constexpr int NT = RT * (RT + 1) / 2;
   const int h = blockIdx.x, q = d.q, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   double* gram_h = gram + (int64_t)h * q * q;
@@ -1130,7 +1183,7 @@ __global__ __launch_bounds__(256) void score_kernel(TabDims d, const int32_t* __
   }
   if (P1) {
     const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in;
-    if (h != g && h != j) {                       // pivot groups get their blocks in pair_fix_kernel
+    if (h != g && h != j) {                       // pivot groups get their blocks in pair_fix_rows
       const int64_t base = (int64_t)h * q * q;
       for (int t = wave; t < NT; t += 4) {
         int br = 0, bc = t;
@@ -1180,7 +1233,7 @@ __global__ __launch_bounds__(256) void score_q1_kernel(int p, const int32_t* __r
   if (!(a > 0.0)) { ctrl->notpd = 1; a = 1.0; }
   score[h] = gram[h] / a;
 }
-struct ScoreUpdate { const double* part = nullptr; const float *P1 = nullptr, *P2 = nullptr, *P1D = nullptr, *P2D = nullptr; const int32_t* single = nullptr; };
+struct ScoreUpdate { const double* part = nullptr; const float *P1 = nullptr, *P2 = nullptr, *P1D = nullptr, *P2D = nullptr; const int32_t* single = nullptr; PairTrace trace; };
 static void launch_score(const TabDims& d, const int32_t* kept, double* gram, double* dblk, double* score, SearchCtrl* ctrl, int skip_if_done,
                          hipStream_t s, const ScoreUpdate& u = ScoreUpdate()) {
   if (d.q == 1) {
@@ -1189,7 +1242,7 @@ static void launch_score(const TabDims& d, const int32_t* kept, double* gram, do
   }
   const int cc = gu_chunk_cols(d.p, d.m);
   OSSCAR_BY_TILES(d.q, hipLaunchKernelGGL(score_kernel<RT>, dim3(d.p), dim3(256), 0, s, d, kept, gram, dblk, score, ctrl, skip_if_done, u.part,
-                                          (d.m + cc - 1) / cc, u.P1, u.P2, u.P1D, u.P2D, u.single))
+                                          (d.m + cc - 1) / cc, u.P1, u.P2, u.P1D, u.P2D, u.single, u.trace))
 }
 
 // the two halves of the refresh: the per-group Gram blocks and diagonal blocks (one pass over Z and the diagonal of N),
@@ -1198,7 +1251,7 @@ static hipError_t launch_refresh_blocks(const TabDims& d, const TabPtrs& t, hipS
   if (d.q == 1) {
     hipLaunchKernelGGL(gram_dblk_q1_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d.d1, d.m, t.N, t.Z, t.gram, t.dblk);
   } else {
-    const hipError_t e = launch_group_update(d, t, nullptr, nullptr, 0, nullptr, s);
+    const hipError_t e = launch_group_gram(d, t, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(dblk_copy_kernel, dim3(d.p), dim3(256), 0, s, d, t.N, t.dblk);
   }
@@ -1218,58 +1271,74 @@ hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t
 // ------------------------------------------------------------------------------------------------
 // argmin of the removal costs over kept groups, argmax of the addition gains over the others (lowest
 // index on ties), and the relative gap to the second best of each.
+// the best value (smallest), the next one, and the index of the best, the lowest of equal ones; -1: none
+struct TwoBest {
+  double v1, v2;
+  int i;
+  __device__ __forceinline__ void clear() { v1 = v2 = INFINITY; i = -1; }
+  __device__ __forceinline__ void take(double v, int h) {          // ascending h: a strict comparison keeps the lowest index
+    const bool lt = v < v1;
+    v2 = lt ? v1 : fmin(v2, v);
+    v1 = lt ? v : v1; i = lt ? h : i;
+  }
+  __device__ __forceinline__ void join(const TwoBest& b) {
+    const bool t = (b.i >= 0) & ((i < 0) | (b.v1 < v1) | ((b.v1 == v1) & (b.i < i)));
+    v2 = fmin(fmin(v2, b.v2), t ? v1 : b.v1);
+    v1 = t ? b.v1 : v1; i = t ? b.i : i;
+  }
+  // the best of the wave, in every lane
+  __device__ __forceinline__ void over_wave() {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      TwoBest b;
+      b.v1 = __shfl_xor(v1, o); b.v2 = __shfl_xor(v2, o); b.i = __shfl_xor(i, o);
+      join(b);
+    }
+  }
+  __device__ __forceinline__ double gap() const { return isfinite(v2) ? fabs(v2 - v1) / fmax(fabs(v1), 1e-300) : INFINITY; }
+};
+// Leaving group (of the kept ones: the smallest score) and entering group (of the others: the largest, held negated), known to
+// every thread of a workgroup of T.  In steps of a wave and one exchange through LDS: as a tree over 1024 threads in LDS the
+// selection was a launch of 4.1 us at 256 groups.
+template <int T>
+__device__ __forceinline__ void pick_pair(int p, const int32_t* __restrict__ kept, const double* __restrict__ score, TwoBest& out, TwoBest& in) {
+  __shared__ TwoBest s_out[T / 64], s_in[T / 64];
+  const int tid = threadIdx.x;
+  out.clear(); in.clear();
+#pragma unroll 4
+  for (int h = tid; h < p; h += T) {
+    const double v = score[h];
+    const bool k = kept[h] != 0;
+    out.take(k ? v : INFINITY, h);
+    in.take(k ? INFINITY : -v, h);
+  }
+  out.over_wave(); in.over_wave();
+  if ((tid & 63) == 0) { s_out[tid >> 6] = out; s_in[tid >> 6] = in; }
+  __syncthreads();
+  out = s_out[0]; in = s_in[0];
+#pragma unroll 3
+  for (int w = 1; w < T / 64; w++) { out.join(s_out[w]); in.join(s_in[w]); }
+}
+// the pair a move takes: the picked one, or the one the caller names; false (of every thread alike): there is none.
+// record: this thread writes it to ctrl
+__device__ __forceinline__ bool settle_pair(const TwoBest& out, const TwoBest& in, int forced_out, int forced_in, const int32_t* __restrict__ kept,
+                                            SearchCtrl* ctrl, bool record, int& g, int& j) {
+  g = forced_out >= 0 ? forced_out : out.i; j = forced_out >= 0 ? forced_in : in.i;
+  if (g < 0 || j < 0 || (forced_out >= 0 && (!kept[g] || kept[j]))) {
+    if (record) { ctrl->done = 1; ctrl->g_out = -1; ctrl->g_in = -1; }
+    return false;
+  }
+  if (record) { ctrl->g_out = g; ctrl->g_in = j; ctrl->gap_rem = out.gap(); ctrl->gap_add = in.gap(); }
+  return true;
+}
 __global__ __launch_bounds__(1024) void select_kernel(TabDims d, const int32_t* __restrict__ kept,
                                                        const double* __restrict__ score, SearchCtrl* ctrl, int forced_out,
                                                        int forced_in) {
-  __shared__ double s_min1[1024], s_min2[1024], s_max1[1024], s_max2[1024];
-  __shared__ int s_imin[1024], s_imax[1024];
   if (ctrl->done || ctrl->pause) return;
-  const int tid = threadIdx.x;
-  double mn1 = INFINITY, mn2 = INFINITY, mx1 = -INFINITY, mx2 = -INFINITY;
-  int imn = -1, imx = -1;
-  for (int h = tid; h < d.p; h += 1024) {     // ascending h per thread: strict comparisons keep the lowest index
-    double v = score[h];
-    if (kept[h]) {
-      if (v < mn1) { mn2 = mn1; mn1 = v; imn = h; } else if (v < mn2) mn2 = v;
-    } else {
-      if (v > mx1) { mx2 = mx1; mx1 = v; imx = h; } else if (v > mx2) mx2 = v;
-    }
-  }
-  s_min1[tid] = mn1; s_min2[tid] = mn2; s_imin[tid] = imn;
-  s_max1[tid] = mx1; s_max2[tid] = mx2; s_imax[tid] = imx;
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (tid < o) {
-      {  // min side
-        double a1 = s_min1[tid], a2 = s_min2[tid], b1 = s_min1[tid + o], b2 = s_min2[tid + o];
-        int ia = s_imin[tid], ib = s_imin[tid + o];
-        bool takeb = (ib >= 0) && (ia < 0 || b1 < a1 || (b1 == a1 && ib < ia));
-        double n1 = takeb ? b1 : a1; int in_ = takeb ? ib : ia;
-        double other1 = takeb ? a1 : b1;
-        double n2 = fmin(fmin(a2, b2), other1);
-        s_min1[tid] = n1; s_min2[tid] = n2; s_imin[tid] = in_;
-      }
-      {  // max side
-        double a1 = s_max1[tid], a2 = s_max2[tid], b1 = s_max1[tid + o], b2 = s_max2[tid + o];
-        int ia = s_imax[tid], ib = s_imax[tid + o];
-        bool takeb = (ib >= 0) && (ia < 0 || b1 > a1 || (b1 == a1 && ib < ia));
-        double n1 = takeb ? b1 : a1; int in_ = takeb ? ib : ia;
-        double other1 = takeb ? a1 : b1;
-        double n2 = fmax(fmax(a2, b2), other1);
-        s_max1[tid] = n1; s_max2[tid] = n2; s_imax[tid] = in_;
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    int g = s_imin[0], j = s_imax[0];
-    if (forced_out >= 0) { g = forced_out; j = forced_in; }
-    if (g < 0 || j < 0 || (forced_out >= 0 && (!kept[g] || kept[j]))) { ctrl->done = 1; ctrl->g_out = -1; ctrl->g_in = -1; return; }
-    ctrl->g_out = g; ctrl->g_in = j;
-    double m1 = s_min1[0], m2 = s_min2[0], x1 = s_max1[0], x2 = s_max2[0];
-    ctrl->gap_rem = isfinite(m2) ? fabs(m2 - m1) / fmax(fabs(m1), 1e-300) : INFINITY;
-    ctrl->gap_add = isfinite(x2) ? fabs(x1 - x2) / fmax(fabs(x1), 1e-300) : INFINITY;
-  }
+  TwoBest out, in;
+  pick_pair<1024>(d.p, kept, score, out, in);
+  int g, j;
+  settle_pair(out, in, forced_out, forced_in, kept, ctrl, threadIdx.x == 0, g, j);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1372,132 +1441,118 @@ __global__ __launch_bounds__(256) void exact_blocks_kernel(TabDims d, const floa
 // entering group = argmax of the exact scores over the groups outside the kept set (lowest index on ties)
 __global__ __launch_bounds__(1024) void select_in_kernel(TabDims d, const int32_t* __restrict__ kept,
                                                           const double* __restrict__ xscore, SearchCtrl* ctrl) {
-  __shared__ double s1[1024], s2[1024];
-  __shared__ int si[1024];
   if (ctrl->done) return;
-  const int tid = threadIdx.x;
-  double mx1 = -INFINITY, mx2 = -INFINITY;
-  int imx = -1;
-  for (int h = tid; h < d.p; h += 1024) {
-    if (kept[h]) continue;
-    const double v = xscore[h];
-    if (v > mx1) { mx2 = mx1; mx1 = v; imx = h; } else if (v > mx2) mx2 = v;
-  }
-  s1[tid] = mx1; s2[tid] = mx2; si[tid] = imx;
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (tid < o) {
-      const double a1 = s1[tid], a2 = s2[tid], b1 = s1[tid + o], b2 = s2[tid + o];
-      const int ia = si[tid], ib = si[tid + o];
-      const bool takeb = (ib >= 0) && (ia < 0 || b1 > a1 || (b1 == a1 && ib < ia));
-      s1[tid] = takeb ? b1 : a1; si[tid] = takeb ? ib : ia;
-      s2[tid] = fmax(fmax(a2, b2), takeb ? a1 : b1);
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    if (si[0] < 0) { ctrl->done = 1; ctrl->g_out = -1; ctrl->g_in = -1; return; }
-    ctrl->g_in = si[0];
-    ctrl->gap_add = isfinite(s2[0]) ? fabs(s1[0] - s2[0]) / fmax(fabs(s1[0]), 1e-300) : INFINITY;
-  }
+  TwoBest out, in;
+  pick_pair<1024>(d.p, kept, xscore, out, in);
+  if (threadIdx.x != 0) return;
+  if (in.i < 0) { ctrl->done = 1; ctrl->g_out = -1; ctrl->g_in = -1; return; }
+  ctrl->g_in = in.i;
+  ctrl->gap_add = in.gap();
 }
 
-// panels of both pivots (blockIdx.y = 0, 1: C1, C2; 64 rows per workgroup, through LDS where the pivot rows of N hold them) and
-// copies of their Z rows (blockIdx.y = 2, 3).  single != nullptr: removal of the one group *single, no second pivot.
-__global__ __launch_bounds__(256) void extract_pair_kernel(TabDims d, const float* __restrict__ N, const float* __restrict__ Z,
-                                                            const SearchCtrl* __restrict__ ctrl, float* __restrict__ C1,
-                                                            float* __restrict__ C2, float* __restrict__ Zg,
-                                                            float* __restrict__ Zj, const int32_t* __restrict__ single) {
-  __shared__ float T[64][65];
-  if (ctrl->done) return;
-  const int q = d.q, second = blockIdx.y & 1, tid = threadIdx.x;
-  const int t0 = (single ? *single : second ? ctrl->g_in : ctrl->g_out) * q;
-  if (blockIdx.y >= 2) {
-    const float* src = Z + (int64_t)t0 * d.m;
-    float* dst = second ? Zj : Zg;
-    for (int64_t idx = blockIdx.x * 256 + tid; idx < (int64_t)q * d.m; idx += (int64_t)gridDim.x * 256) dst[idx] = src[idx];
-    return;
-  }
-  float* C = second ? C2 : C1;
-  const int i0 = blockIdx.x * 64, ni = min(64, d.d1 - i0);
-  if (i0 + ni <= t0) {                                   // above the pivot: the pivot's rows of N, along i
-    for (int idx = tid; idx < 64 * q; idx += 256) {
-      const int c = idx >> 6, r = idx & 63;
-      if (r < ni) T[r][c] = N[(int64_t)(t0 + c) * d.d1 + i0 + r];
-    }
-    __syncthreads();
-    for (int idx = tid; idx < ni * q; idx += 256) C[(int64_t)i0 * q + idx] = T[idx / q][idx % q];
-    return;
-  }
-  for (int idx = tid; idx < ni * q; idx += 256) C[(int64_t)i0 * q + idx] = nsym(N, d.d1, i0 + idx / q, t0 + idx % q);
-}
-
-// q x q algebra of the pair (the exact change of the objective and the acceptance test follow in pair_cols_kernel and
-// pair_accept_kernel).
+// Opening of a move: the selection, the panels of both pivots (C1, C2; 64 rows per workgroup, through LDS where the pivot rows
+// of N hold them), copies of their Z rows, and the q x q algebra.  Nothing here waits for anything but the selection, which
+// every workgroup makes for itself (`pick`; otherwise ctrl holds the pair).  single != nullptr: removal of the one group
+// *single, no second pivot.  Workgroups: with `algebra` the first one makes the q x q matrices straight from N; then
+// `row_blocks` each for C1, C2 and the two copies.
 // small layout (doubles, each q*q): [0] Dg, [1] Njg, [2] M1 = Dg Ngj, [3] Dj' , [4] W2Dj = -M1 Dj'; single: Dg only (the
-// others are written as zeros for one-row groups, whose bulk kernels always take both terms).  One workgroup: bound by the
-// two chains of q pivots.
+// others are written as zeros for one-row groups, whose bulk kernels always take both terms).
+// Bound by the algebra's two chains of q pivots; the panels run beside it.  As three launches (selection, panels, algebra) the
+// same work took 4.1 + 3.5 + 9.8 us at 256 groups of 9 rows, as one 11.3 us.
+// PICK_MOST: every workgroup reads all scores; past 8 per thread a launch of its own makes the selection.
+constexpr int PICK_MOST = 2048;
 template <int RT>
-__global__ __launch_bounds__(256) void pair_small_kernel(TabDims d, const float* __restrict__ C1, const float* __restrict__ C2,
-                                                          double* __restrict__ small, SearchCtrl* ctrl,
-                                                          const int32_t* __restrict__ single) {
-  extern __shared__ double psm[];      // three q x q matrices with rows of q + 1
+__global__ __launch_bounds__(256) void pair_open_kernel(TabDims d, const float* __restrict__ N, const float* __restrict__ Z,
+                                                         const int32_t* __restrict__ kept, const double* __restrict__ score, SearchCtrl* ctrl,
+                                                         float* __restrict__ C1, float* __restrict__ C2, float* __restrict__ Zg,
+                                                         float* __restrict__ Zj, double* __restrict__ small, const int32_t* __restrict__ single,
+                                                         int pick, int forced_out, int forced_in, int algebra, int row_blocks) {
+  extern __shared__ double psm[];      // three q x q matrices with rows of q + 1, or 64 x 65 floats
   __shared__ InvLds<RT> L;
   if (ctrl->done) return;
+  const int q = d.q, tid = threadIdx.x;
+  int g, j;
+  if (single) g = j = *single;
+  else if (pick) {
+    TwoBest out, in;
+    pick_pair<256>(d.p, kept, score, out, in);
+    if (!settle_pair(out, in, forced_out, forced_in, kept, ctrl, blockIdx.x == 0 && tid == 0, g, j)) return;
+  } else { g = ctrl->g_out; j = ctrl->g_in; }
+  const int64_t ld = d.d1;
+  const int b = (int)blockIdx.x - algebra;
+  if (b >= 0) {
+    const int part = b / row_blocks, x = b % row_blocks, second = part & 1, t0 = (second ? j : g) * q;
+    if (part >= 2) {
+      const float* src = Z + (int64_t)t0 * d.m;
+      float* dst = second ? Zj : Zg;
+      for (int64_t idx = x * 256 + tid; idx < (int64_t)q * d.m; idx += (int64_t)row_blocks * 256) dst[idx] = src[idx];
+      return;
+    }
+    float (*T)[65] = reinterpret_cast<float (*)[65]>(psm);
+    float* C = second ? C2 : C1;
+    const int i0 = x * 64, ni = min(64, d.d1 - i0);
+    if (i0 + ni <= t0) {                                   // above the pivot: the pivot's rows of N, along i
+      for (int idx = tid; idx < 64 * q; idx += 256) {
+        const int c = idx >> 6, r = idx & 63;
+        if (r < ni) T[r][c] = N[(int64_t)(t0 + c) * ld + i0 + r];
+      }
+      __syncthreads();
+      for (int idx = tid; idx < ni * q; idx += 256) C[(int64_t)i0 * q + idx] = T[idx / q][idx % q];
+      return;
+    }
+    for (int idx = tid; idx < ni * q; idx += 256) C[(int64_t)i0 * q + idx] = nsym(N, ld, i0 + idx / q, t0 + idx % q);
+    return;
+  }
   constexpr int T = (RT * (RT + 1) / 2 + 3) / 4;
-  const int q = d.q, qq = q * q, qs = q + 1, tid = threadIdx.x;
-  const int g0 = (single ? *single : ctrl->g_out) * q, j0 = (single ? *single : ctrl->g_in) * q;
+  const int qq = q * q, qs = q + 1, g0 = g * q, j0 = j * q;
   double* Dg = small; double* Njg = small + qq; double* M1 = small + 2 * qq; double* Dj = small + 3 * qq;
   double* W2Dj = small + 4 * qq;
   double* X0 = psm; double* X1 = psm + q * qs; double* X2 = psm + 2 * q * qs;
   if (!single)
     for (int idx = tid; idx < qq; idx += 256) {
-      const double njg = (double)C1[(int64_t)j0 * q + idx];      // N(j_r, g_c)
+      const double njg = (double)nsym(N, ld, j0 + idx / q, g0 + idx % q);      // N(j_r, g_c)
       Njg[idx] = njg;
       X1[idx / q * qs + idx % q] = njg;
     }
   // kept pivot: N_gg = -P_gg is negative definite
-  bool bad = inv_sym<4, T, RT>(q, L, [&](int i, int j) { return -(double)C1[(int64_t)(g0 + i) * q + j]; },
-                               [&](int i, int j, double v) { X0[i * qs + j] = X0[j * qs + i] = -v; Dg[i * q + j] = Dg[j * q + i] = -v; });
+  bool bad = inv_sym<4, T, RT>(q, L, [&](int r, int c) { return -(double)nsym(N, ld, g0 + r, g0 + c); },
+                               [&](int r, int c, double v) { X0[r * qs + c] = X0[c * qs + r] = -v; Dg[r * q + c] = Dg[c * q + r] = -v; });
   __syncthreads();
   if (single) {
     // Case 1 alone: with M1 = 0 and Dj' = 0 every term of the second sweep vanishes
     if (q == 1 && tid == 0) { M1[0] = 0.0; Dj[0] = 0.0; W2Dj[0] = 0.0; Njg[0] = 0.0; }
   } else {
-    mm_small<RT>(q, [&](int i, int k) { return X0[i * qs + k]; }, [&](int k, int j) { return X1[j * qs + k]; },      // M1 = Dg Ngj
-                 [&](int i, int j, double v) { X2[i * qs + j] = v; M1[i * q + j] = v; });
+    mm_small<RT>(q, [&](int i, int k) { return X0[i * qs + k]; }, [&](int k, int c) { return X1[c * qs + k]; },      // M1 = Dg Ngj
+                 [&](int i, int c, double v) { X2[i * qs + c] = v; M1[i * q + c] = v; });
     __syncthreads();
-    mm_small<RT>(q, [&](int i, int k) { return X1[i * qs + k]; }, [&](int k, int j) { return X2[k * qs + j]; },      // N'_jj = N_jj - N_jg M1
-                 [&](int i, int j, double v) { X0[i * qs + j] = (double)C2[(int64_t)(j0 + i) * q + j] - v; });
+    mm_small<RT>(q, [&](int i, int k) { return X1[i * qs + k]; }, [&](int k, int c) { return X2[k * qs + c]; },      // N'_jj = N_jj - N_jg M1
+                 [&](int i, int c, double v) { X0[i * qs + c] = (double)nsym(N, ld, j0 + i, j0 + c) - v; });
     __syncthreads();
     // entering pivot: Schur complement, positive definite
-    bad |= inv_sym<4, T, RT>(q, L, [&](int i, int j) { return X0[i * qs + j]; },
-                             [&](int i, int j, double v) { X1[i * qs + j] = X1[j * qs + i] = v; Dj[i * q + j] = Dj[j * q + i] = v; });
+    bad |= inv_sym<4, T, RT>(q, L, [&](int r, int c) { return X0[r * qs + c]; },
+                             [&](int r, int c, double v) { X1[r * qs + c] = X1[c * qs + r] = v; Dj[r * q + c] = Dj[c * q + r] = v; });
     __syncthreads();
-    mm_small<RT>(q, [&](int i, int k) { return -X2[i * qs + k]; }, [&](int k, int j) { return X1[k * qs + j]; },     // W2Dj, W2 = N'_gj = -M1
-                 [&](int i, int j, double v) { W2Dj[i * q + j] = v; });
+    mm_small<RT>(q, [&](int i, int k) { return -X2[i * qs + k]; }, [&](int k, int c) { return X1[k * qs + c]; },     // W2Dj, W2 = N'_gj = -M1
+                 [&](int i, int c, double v) { W2Dj[i * q + c] = v; });
   }
-  if (tid == 0) ctrl->delta = 0.0;
   if (bad && (tid & 63) == 0) ctrl->notpd = 1;
 }
 
 // Column phase of the pair: rZ1 = Dg Zg ; Z'j = Zj - Njg rZ1 ; rZ2 = Dj' Z'j (both written in place of Zg, Zj) and
 // delta = -<Zg, rZ1> - <Z'j, rZ2>, one partial sum per workgroup in dpart (added up in a fixed order by the acceptance
-// kernel, so that the result does not depend on scheduling).  16 columns per workgroup, a wave = 16 rows, float64 matrix cores;
+// test, so that the result does not depend on scheduling).  16 columns per workgroup, a wave = 16 rows, float64 matrix cores;
 // the q x q matrices come from L2 (a row's 4 k are 32 bytes).
 constexpr int PC_COLS = 16;
 template <int RT>
-__global__ __launch_bounds__(256) void pair_cols_kernel(TabDims d, float* __restrict__ Zg, float* __restrict__ Zj,
-                                                         const double* __restrict__ small, SearchCtrl* ctrl, double* __restrict__ dpart,
-                                                         const int32_t* __restrict__ single) {
+__device__ __forceinline__ void pair_cols(TabDims d, float* __restrict__ Zg, float* __restrict__ Zj, const double* __restrict__ small,
+                                          double* __restrict__ dpart, const int32_t* __restrict__ single, int block) {
   __shared__ double ta[16 * RT][PC_COLS + 1], tb[16 * RT][PC_COLS + 1];
   __shared__ double red[4];
-  if (ctrl->done) return;
   const int q = d.q, qq = q * q, m = d.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   const double* Dg = small; const double* Njg = small + qq; const double* Dj = small + 3 * qq;
-  const int i0 = wave * 16, col = blockIdx.x * PC_COLS + lc;
+  const int i0 = wave * 16, col = block * PC_COLS + lc;
   const bool live = col < m, mine = i0 < q;
-  for (int r = tid >> 4; r < q; r += 16) ta[r][tid & 15] = blockIdx.x * PC_COLS + (tid & 15) < m ? (double)Zg[(int64_t)r * m + blockIdx.x * PC_COLS + (tid & 15)] : 0.0;
+  for (int r = tid >> 4; r < q; r += 16) ta[r][tid & 15] = block * PC_COLS + (tid & 15) < m ? (double)Zg[(int64_t)r * m + block * PC_COLS + (tid & 15)] : 0.0;
   __syncthreads();
   auto product = [&](const double* A, double (*B)[PC_COLS + 1]) {
     swd4 acc = {0.0, 0.0, 0.0, 0.0};
@@ -1546,48 +1601,30 @@ __global__ __launch_bounds__(256) void pair_cols_kernel(TabDims d, float* __rest
   part = wave_sum(part);
   if (lane == 0) red[wave] = part;
   __syncthreads();
-  if (tid == 0) dpart[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+  if (tid == 0) dpart[block] = red[0] + red[1] + red[2] + red[3];
 }
 
-// the acceptance test and the trace
-__global__ __launch_bounds__(64) void pair_accept_kernel(SearchCtrl* ctrl, int always_accept, int32_t* trace_out, int32_t* trace_in,
-                                                         float* trace_gap, double* trace_obj, const int32_t* __restrict__ single,
+// groups of one row: the test in a launch of its own, before the bulk kernels
+__global__ __launch_bounds__(64) void pair_accept_kernel(SearchCtrl* ctrl, int always_accept, PairTrace tr, const int32_t* __restrict__ single,
                                                          const double* __restrict__ dpart, int nparts) {
   if (ctrl->done) return;
-  // lane l adds the partial sums l, l + 64, ... in that order; then the fixed tree of the wave sum
-  double dsum = 0;
-  for (int b = threadIdx.x; b < nparts; b += 64) dsum += dpart[b];
-  dsum = wave_sum(dsum);
-  if (threadIdx.x != 0) return;
-  const double delta = dsum;
-  ctrl->delta = delta;
-  const int it = ctrl->iters;
-  const bool bad = ctrl->notpd != 0;
-  const bool ok = !bad && (always_accept || delta < -ctrl->rel_tol * ctrl->obj);
-  ctrl->iters = it + 1;
-  if (single) { ctrl->g_out = *single; ctrl->g_in = -1; }
-  if (ok) { ctrl->obj += delta; ctrl->accepted += 1; } else { ctrl->done = 1; }
-  if (trace_out) trace_out[it] = ctrl->g_out;
-  if (trace_in) trace_in[it] = ctrl->g_in;
-  if (trace_gap) { trace_gap[2 * it] = (float)ctrl->gap_rem; trace_gap[2 * it + 1] = (float)ctrl->gap_add; }
-  if (trace_obj) trace_obj[it] = ctrl->obj;
+  double delta;
+  const bool ok = pair_taken(ctrl, always_accept, dpart, nparts, delta);
+  if (threadIdx.x == 0) pair_commit(ctrl, ok, delta, single, tr);
 }
 
 // bulk panels: P1 = C1, P2 = C2 - C1 M1, P1D = P1 Dg, P2D = P2 Dj', with the rows of both pivots zeroed;
 // and the new pivot rows of N and Z, the diagonal blocks (float64) and the membership flags.
 // 16 rows per workgroup, a wave = 16 columns, float64 matrix cores; the q x q matrices come from L2.  single: P1 and P1D only.
 template <int RT>
-__global__ __launch_bounds__(256) void pair_panels_kernel(TabDims d, const float* __restrict__ C1, const float* __restrict__ C2,
-                                                           const double* __restrict__ small, const SearchCtrl* __restrict__ ctrl,
-                                                           float* __restrict__ P1, float* __restrict__ P2,
-                                                           float* __restrict__ P1D, float* __restrict__ P2D,
-                                                           const int32_t* __restrict__ single) {
+__device__ __forceinline__ void pair_panels(TabDims d, const float* __restrict__ C1, const float* __restrict__ C2, const double* __restrict__ small,
+                                            const SearchCtrl* __restrict__ ctrl, float* __restrict__ P1, float* __restrict__ P2,
+                                            float* __restrict__ P1D, float* __restrict__ P2D, const int32_t* __restrict__ single, int block) {
   __shared__ double sc1[16][16 * RT + 1], sc2[16][16 * RT + 1];
-  if (ctrl->done) return;
   const int q = d.q, qq = q * q, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   const int g0 = (single ? *single : ctrl->g_out) * q, j0 = (single ? *single : ctrl->g_in) * q;
   const double* Dg = small; const double* M1 = small + 2 * qq; const double* Dj = small + 3 * qq;
-  const int i0 = blockIdx.x * 16, j = wave * 16 + lc, ni = min(16, d.d1 - i0);
+  const int i0 = block * 16, j = wave * 16 + lc, ni = min(16, d.d1 - i0);
   for (int idx = tid; idx < 16 * q; idx += 256) sc1[idx / q][idx % q] = idx < ni * q ? (double)C1[(int64_t)i0 * q + idx] : 0.0;
   __syncthreads();
   auto product = [&](const double (*A)[16 * RT + 1], const double* B) {
@@ -1629,49 +1666,34 @@ __global__ __launch_bounds__(256) void pair_panels_kernel(TabDims d, const float
   }
 }
 
+// Both follow from the q x q matrices alone, so they share a launch (rows of the panels first, then the columns): apart, with
+// the acceptance test between them, they took 6.1 + 2.3 + 7.0 us at 256 groups of 9 rows, as one 6.9 us.
+template <int RT>
+__global__ __launch_bounds__(256) void pair_mid_kernel(TabDims d, const float* __restrict__ C1, const float* __restrict__ C2,
+                                                        const double* __restrict__ small, const SearchCtrl* __restrict__ ctrl,
+                                                        float* __restrict__ P1, float* __restrict__ P2, float* __restrict__ P1D,
+                                                        float* __restrict__ P2D, float* __restrict__ Zg, float* __restrict__ Zj,
+                                                        double* __restrict__ dpart, const int32_t* __restrict__ single, int row_blocks) {
+  if (ctrl->done) return;
+  if ((int)blockIdx.x < row_blocks) pair_panels<RT>(d, C1, C2, small, ctrl, P1, P2, P1D, P2D, single, blockIdx.x);
+  else pair_cols<RT>(d, Zg, Zj, small, dpart, single, (int)blockIdx.x - row_blocks);
+}
+
 // New pivot rows (after both sweeps), for every l outside the pivots:
 //   N''(g_r, l) = -P1D[l][r] - sum_c W2[r][c] P2D[l][c],  W2 = -M1     (= -P1D[l][r] + sum_c M1[r][c] P2D[l][c])
 //   N''(j_r, l) =  P2D[l][r]
 // pivot-pivot blocks: N''_gg = -Dg - W2 Dj' W2^T, N''_jj = -Dj', N''(g, j) = W2 Dj'.
 // Z''_g = -rZ1 + M1 rZ2, Z''_j = rZ2.  Diagonal blocks of the other groups are updated in float64.
-// Workgroups: 16 rows l of N each (row_blocks of them), then 64 columns of the Z rows each; the first one also writes the
-// pivot-pivot blocks and the flags.
+// 16 rows l of N per workgroup; the first one also writes the pivot-pivot blocks and the flags.
 template <int RT>
-__global__ __launch_bounds__(256) void pair_fix_kernel(TabDims d, float* __restrict__ N, float* __restrict__ Z,
-                                                        const float* __restrict__ P1D, const float* __restrict__ P2D,
-                                                        const float* __restrict__ rZ1, const float* __restrict__ rZ2,
-                                                        const double* __restrict__ small, const SearchCtrl* __restrict__ ctrl,
-                                                        double* __restrict__ dblk, int32_t* __restrict__ kept,
-                                                        const int32_t* __restrict__ single, int row_blocks) {
+__device__ __forceinline__ void pair_fix_rows(TabDims d, float* __restrict__ N, const float* __restrict__ P1D, const float* __restrict__ P2D,
+                                              const double* __restrict__ small, double* __restrict__ dblk, int32_t* __restrict__ kept,
+                                              const int32_t* __restrict__ single, int g, int j, int block) {
   __shared__ float tg[16][16 * RT + 1], tj[16][16 * RT + 1];
-  if (ctrl->done) return;
-  const int q = d.q, qq = q * q, m = d.m, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
-  const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in, g0 = g * q, j0 = j * q;
+  const int q = d.q, qq = q * q, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15, g0 = g * q, j0 = j * q;
   const double* Dg = small; const double* M1 = small + 2 * qq; const double* Dj = small + 3 * qq; const double* W2Dj = small + 4 * qq;
   const int64_t ld = d.d1;
-  if ((int)blockIdx.x >= row_blocks) {
-    const int col = ((int)blockIdx.x - row_blocks) * 64 + wave * 16 + lc;
-    for (int i0 = 0; i0 < q; i0 += 16) {
-      swd4 acc = {0.0, 0.0, 0.0, 0.0};
-      if (!single) {
-#pragma unroll 4
-        for (int k0 = 0; k0 < q; k0 += 4) {
-          const int k = k0 + lr;
-          const double av = (i0 + lc < q && k < q) ? M1[(i0 + lc) * q + k] : 0.0, bv = (k < q && col < m) ? (double)rZ2[(int64_t)k * m + col] : 0.0;
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int i = i0 + 4 * r + lr;
-        if (i >= q || col >= m) continue;
-        Z[(int64_t)(g0 + i) * m + col] = (float)(acc[r] - (double)rZ1[(int64_t)i * m + col]);
-        if (!single) Z[(int64_t)(j0 + i) * m + col] = rZ2[(int64_t)i * m + col];
-      }
-    }
-    return;
-  }
-  const int l0 = blockIdx.x * 16, nl = min(16, d.d1 - l0);
+  const int l0 = block * 16, nl = min(16, d.d1 - l0);
   if (!single) {
     for (int idx = tid; idx < 16 * q; idx += 256) tj[idx / q][idx % q] = idx < nl * q ? P2D[(int64_t)l0 * q + idx] : 0.f;
     __syncthreads();
@@ -1711,7 +1733,7 @@ __global__ __launch_bounds__(256) void pair_fix_kernel(TabDims d, float* __restr
   };
   write(g0, tg, j0);
   if (!single) write(j0, tj, g0);
-  if (blockIdx.x != 0) return;
+  if (block != 0) return;
   auto set_gg = [&](int r, int c, double ngg) {    // N''_gg
     dblk[(int64_t)g * qq + r * q + c] = ngg;
     if (c <= r) N[(int64_t)(g0 + r) * ld + g0 + c] = (float)ngg;
@@ -1733,24 +1755,39 @@ __global__ __launch_bounds__(256) void pair_fix_kernel(TabDims d, float* __restr
   }
   if (tid == 0) { kept[g] = 0; if (!single) kept[j] = 1; }
 }
+// groups of one row: these rows of N (row_blocks workgroups), then 64 columns of the two rows of Z each
+__global__ __launch_bounds__(256) void pair_fix_q1_kernel(TabDims d, float* __restrict__ N, float* __restrict__ Z,
+                                                           const float* __restrict__ P1D, const float* __restrict__ P2D,
+                                                           const float* __restrict__ rZ1, const float* __restrict__ rZ2,
+                                                           const double* __restrict__ small, const SearchCtrl* __restrict__ ctrl,
+                                                           double* __restrict__ dblk, int32_t* __restrict__ kept,
+                                                           const int32_t* __restrict__ single, int row_blocks) {
+  if (ctrl->done) return;
+  const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in, m = d.m;
+  if ((int)blockIdx.x < row_blocks) { pair_fix_rows<1>(d, N, P1D, P2D, small, dblk, kept, single, g, j, blockIdx.x); return; }
+  const int col = ((int)blockIdx.x - row_blocks) * 64 + (int)threadIdx.x;
+  if (threadIdx.x >= 64 || col >= m) return;
+  Z[(int64_t)g * m + col] = (float)((single ? 0.0 : small[2] * (double)rZ2[col]) - (double)rZ1[col]);
+  if (!single) Z[(int64_t)j * m + col] = rZ2[col];
+}
 
 // bulk update of the lower triangle: N[i][l] -= sum_c P1D[i][c] P1[l][c] + P2D[i][c] P2[l][c] (single: the first term only).
 // 64 x 64 tiles, four waves x (2 x 2) v_mfma_f32_16x16x4_f32, the panels' rows whole in LDS (rows of 2 kq + 4 floats: the 16
 // rows x 4 k of an operand read lie in different banks).  Bound by N's read and write; the requests for N go first.
-__global__ __launch_bounds__(256) void update_N_kernel(TabDims d, float* __restrict__ N, const float* __restrict__ P1,
-                                                        const float* __restrict__ P2, const float* __restrict__ P1D,
-                                                        const float* __restrict__ P2D, const SearchCtrl* __restrict__ ctrl, int single) {
-  extern __shared__ float un_lds[];
-  if (ctrl->done) return;
+// The pivots' rows and columns are left to pair_fix_rows (g0, j0: their first rows; single: j0 = g0).
+__device__ __forceinline__ void update_N(float* un_lds, TabDims d, float* __restrict__ N, const float* __restrict__ P1,
+                                         const float* __restrict__ P2, const float* __restrict__ P1D, const float* __restrict__ P2D,
+                                         int single, int g0, int j0, int tile) {
   typedef float f4v __attribute__((ext_vector_type(4)));
-  int tr = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
-  while ((int64_t)(tr + 1) * (tr + 2) / 2 <= (int64_t)blockIdx.x) tr++;
-  while ((int64_t)tr * (tr + 1) / 2 > (int64_t)blockIdx.x) tr--;
-  const int tc = (int)(blockIdx.x - (int64_t)tr * (tr + 1) / 2);
+  int tr = (int)((sqrtf(8.f * (float)tile + 1.f) - 1.f) * 0.5f);
+  while ((int64_t)(tr + 1) * (tr + 2) / 2 <= (int64_t)tile) tr++;
+  while ((int64_t)tr * (tr + 1) / 2 > (int64_t)tile) tr--;
+  const int tc = (int)(tile - (int64_t)tr * (tr + 1) / 2);
   const int q = d.q, n = d.d1, kq = gu_kq(q), K = single ? kq : 2 * kq, ks = 2 * kq + 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
   const int i0 = tr * 64, l0 = tc * 64, wi = (wave >> 1) * 32, wl = (wave & 1) * 32;
   float* As = un_lds; float* Bs = un_lds + 64 * ks;
+  auto outside = [&](int l) { return !(l >= g0 && l < g0 + q) && !(l >= j0 && l < j0 + q); };
   float old[2][2][4];
   auto at = [&](int a, int b, int r) { return (int64_t)(i0 + wi + a * 16 + 4 * lr + r) * n + l0 + wl + b * 16 + lc; };
   auto inside = [&](int a, int b, int r) {
@@ -1789,10 +1826,38 @@ __global__ __launch_bounds__(256) void update_N_kernel(TabDims d, float* __restr
     for (int b = 0; b < 2; b++)
 #pragma unroll
       for (int r = 0; r < 4; r++)
-        if (inside(a, b, r)) N[at(a, b, r)] = old[a][b][r] - acc[a][b][r];
+        if (inside(a, b, r) && outside(i0 + wi + a * 16 + 4 * lr + r) && outside(l0 + wl + b * 16 + lc)) N[at(a, b, r)] = old[a][b][r] - acc[a][b][r];
 }
 
-// groups of one row: the float64 diagonal of the rows outside the pivots (theirs is written by pair_fix_kernel)
+// The state after the move: the pivots' rows of N (fix_blocks workgroups), Z and the columns' shares of the groups' Grams
+// (p x chunks) and the bulk of N (its lower tiles), none of which reads what another writes, each after the acceptance test for
+// itself; the first workgroup leaves the outcome in ctrl for the scores' launch.  As three launches after the one of the test:
+// 4.5 + 10.2 + 6.3 us at 256 groups of 9 rows, 12.7 us as one, and a move is four launches, 40 us, instead of ten, 62 us.
+// Bound by a pass over N and one over Z.
+template <int RT>
+__global__ __launch_bounds__(256, 2) void pair_state_kernel(TabDims d, float* __restrict__ N, float* __restrict__ Z, const float* __restrict__ P1,
+                                                            const float* __restrict__ P2, const float* __restrict__ P1D,
+                                                            const float* __restrict__ P2D, const float* __restrict__ rZ1,
+                                                            const float* __restrict__ rZ2, const double* __restrict__ small, SearchCtrl* ctrl,
+                                                            double* __restrict__ dblk, int32_t* __restrict__ kept, double* __restrict__ part,
+                                                            const int32_t* __restrict__ single, int always_accept, const double* __restrict__ dpart,
+                                                            int nparts, int fix_blocks, int chunk_cols, int chunks) {
+  extern __shared__ float ps_lds[];
+  if (ctrl->done) return;
+  const int g = single ? *single : ctrl->g_out, j = single ? g : ctrl->g_in;
+  double delta;
+  const bool ok = pair_taken(ctrl, always_accept, dpart, nparts, delta);
+  if (blockIdx.x == 0 && threadIdx.x == 0) { ctrl->delta = delta; ctrl->taken = ok; }
+  if (!ok) return;
+  const int b = blockIdx.x, groups = d.p * chunks;
+  if (b < fix_blocks) pair_fix_rows<RT>(d, N, P1D, P2D, small, dblk, kept, single, g, j, b);
+  else if (b < fix_blocks + groups)
+    group_update<RT>(ps_lds, d, Z, P1, P2, rZ1, rZ2, small + 2 * d.q * d.q, single != nullptr, part, chunk_cols, chunks, g, j, (b - fix_blocks) / chunks,
+                     (b - fix_blocks) % chunks);
+  else update_N(ps_lds, d, N, P1, P2, P1D, P2D, single != nullptr, g * d.q, j * d.q, b - fix_blocks - groups);
+}
+
+// groups of one row: the float64 diagonal of the rows outside the pivots (theirs is written by pair_fix_rows)
 __global__ __launch_bounds__(256) void pair_dblk_q1_kernel(TabDims d, const float* __restrict__ P1, const float* __restrict__ P2,
                                                             const float* __restrict__ P1D, const float* __restrict__ P2D,
                                                             const SearchCtrl* __restrict__ ctrl, double* __restrict__ dblk,
@@ -2072,11 +2137,29 @@ hipError_t launch_select(const TabDims& d, const TabPtrs& t, int forced_out, int
 
 hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int forced_out, int forced_in, int always_accept,
                                    hipStream_t s, hipEvent_t* ev, const int32_t* single, int exact_in) {
-  const int q = d.q;
-  const dim3 ex_grid((d.d1 + 63) / 64, 4);
-  if (!single) hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, t.ctrl, forced_out, forced_in);
-  hipLaunchKernelGGL(extract_pair_kernel, ex_grid, dim3(256), 0, s, d, t.N, t.Z, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2, single);
-  if (exact_in && !single && forced_out < 0) {
+  const int q = d.q, rows64 = (d.d1 + 63) / 64;
+  auto dynamic_lds = [](const void* kernel, size_t bytes, size_t beside) {
+    return bytes + beside > 65536 ? hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) : hipSuccess;
+  };
+  int pick = single == nullptr;
+  if (pick && d.p > PICK_MOST) {
+    hipLaunchKernelGGL(select_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, t.ctrl, forced_out, forced_in);
+    pick = 0;
+  }
+  auto open = [&](int algebra) -> hipError_t {
+    OSSCAR_BY_TILES(q, {
+      const size_t lds = std::max((size_t)64 * 65 * 4, (size_t)3 * q * (q + 1) * 8);
+      const hipError_t e = dynamic_lds(reinterpret_cast<const void*>(pair_open_kernel<RT>), lds, sizeof(InvLds<RT>) + 1024);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(pair_open_kernel<RT>, dim3(4 * rows64 + algebra), dim3(256), lds, s, d, t.N, t.Z, t.kept, t.score, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2,
+                         t.small, single, pick, forced_out, forced_in, algebra, rows64);
+    })
+    return hipGetLastError();
+  };
+  const int exact = exact_in && !single && forced_out < 0;
+  hipError_t e = open(!exact);
+  if (e != hipSuccess) return e;
+  if (exact) {
     // the leaving group stands; choose the entering one by the exact gain of the pair and extract its panel again
     hipLaunchKernelGGL(exact_cross_kernel, dim3((d.d1 + 3) / 4), dim3(256), 0, s, d, t.Z, t.rZ1, t.ctrl, t.cross);
     if (q == 1) {
@@ -2084,62 +2167,51 @@ hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int force
                          t.xscore);
     } else {
       const size_t xb_lds = (size_t)(3 * q * q + 256) * 8;
-      if (xb_lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(exact_blocks_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)xb_lds);
-        if (e != hipSuccess) return e;
-      }
+      e = dynamic_lds(reinterpret_cast<const void*>(exact_blocks_kernel), xb_lds, 0);
+      if (e != hipSuccess) return e;
       hipLaunchKernelGGL(exact_blocks_kernel, dim3(d.p), dim3(256), xb_lds, s, d, t.C1, t.cross, t.gram, t.dblk, t.kept, t.ctrl,
                          t.xgram, t.xdblk);
       launch_score(d, t.kept, t.xgram, t.xdblk, t.xscore, t.ctrl, 1, s);
     }
     hipLaunchKernelGGL(select_in_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.xscore, t.ctrl);
-    hipLaunchKernelGGL(extract_pair_kernel, ex_grid, dim3(256), 0, s, d, t.N, t.Z, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2, single);
+    pick = 0;
+    e = open(1);
+    if (e != hipSuccess) return e;
   }
-  const size_t ps_lds = (size_t)3 * q * (q + 1) * 8;
-  const int ncb = (d.m + PC_COLS - 1) / PC_COLS;
-  OSSCAR_BY_TILES(q, {
-    if (ps_lds > 32768) {      // beside the inverse's 30 KB
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pair_small_kernel<RT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)ps_lds);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(pair_small_kernel<RT>, dim3(1), dim3(256), ps_lds, s, d, t.C1, t.C2, t.small, t.ctrl, single);
-    hipLaunchKernelGGL(pair_cols_kernel<RT>, dim3(ncb), dim3(256), 0, s, d, t.rZ1, t.rZ2, t.small, t.ctrl, t.dpart, single);
-  })
-  hipLaunchKernelGGL(pair_accept_kernel, dim3(1), dim3(64), 0, s, t.ctrl, always_accept, t.trace_out, t.trace_in, t.trace_gap,
-                     t.trace_obj, single, t.dpart, ncb);
   // bulk panels go to C1D/C2D (times D) and to two further panels stored behind them
   float* P1 = t.C1D + (int64_t)2 * d.d1 * q;
   float* P2 = P1 + (int64_t)d.d1 * q;
   float* P1D = t.C1D;
   float* P2D = t.C2D;
-  const int rows16 = (d.d1 + 15) / 16;
-  OSSCAR_BY_TILES(q, {
-    hipLaunchKernelGGL(pair_panels_kernel<RT>, dim3(rows16), dim3(256), 0, s, d, t.C1, t.C2, t.small, t.ctrl, P1, P2, P1D, P2D, single);
-    hipLaunchKernelGGL(pair_fix_kernel<RT>, dim3(rows16 + (d.m + 63) / 64), dim3(256), 0, s, d, t.N, t.Z, P1D, P2D, t.rZ1, t.rZ2, t.small, t.ctrl,
-                       t.dblk, t.kept, single, rows16);
-  })
-  if (ev) hipEventRecord(ev[0], s);
+  const int rows16 = (d.d1 + 15) / 16, ncb = (d.m + PC_COLS - 1) / PC_COLS;
+  OSSCAR_BY_TILES(q, hipLaunchKernelGGL(pair_mid_kernel<RT>, dim3(rows16 + ncb), dim3(256), 0, s, d, t.C1, t.C2, t.small, t.ctrl, P1, P2, P1D, P2D,
+                                        t.rZ1, t.rZ2, t.dpart, single, rows16))
+  PairTrace tr;
+  tr.out = t.trace_out; tr.in = t.trace_in; tr.gap = t.trace_gap; tr.obj = t.trace_obj;
+  ScoreUpdate u;
   if (q == 1) {
+    hipLaunchKernelGGL(pair_accept_kernel, dim3(1), dim3(64), 0, s, t.ctrl, always_accept, tr, single, t.dpart, ncb);
+    hipLaunchKernelGGL(pair_fix_q1_kernel, dim3(rows16 + (d.m + 63) / 64), dim3(256), 0, s, d, t.N, t.Z, P1D, P2D, t.rZ1, t.rZ2, t.small, t.ctrl,
+                       t.dblk, t.kept, single, rows16);
+    if (ev) hipEventRecord(ev[0], s);
     hipLaunchKernelGGL(pair_dblk_q1_kernel, dim3((d.p + 255) / 256), dim3(256), 0, s, d, P1, P2, P1D, P2D, t.ctrl, t.dblk, single);
     dim3 grid((d.d1 + 1023) / 1024, (d.d1 + 31) / 32);
     hipLaunchKernelGGL(update_N_q1_kernel, grid, dim3(256), 0, s, d.d1, t.N, P1, P2, P1D, P2D, t.ctrl);
-  } else {
-    const int64_t tiles = (d.d1 + 63) / 64;
-    const size_t lds = (size_t)2 * 64 * (2 * gu_kq(q) + 4) * 4;
-    if (lds > 65536) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(update_N_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(update_N_kernel, dim3((unsigned)(tiles * (tiles + 1) / 2)), dim3(256), lds, s, d, t.N, P1, P2, P1D, P2D, t.ctrl, single != nullptr);
-  }
-  if (ev) hipEventRecord(ev[1], s);
-  ScoreUpdate u;
-  if (q == 1) {
+    if (ev) hipEventRecord(ev[1], s);
     hipLaunchKernelGGL(update_Z_kernel, dim3(d.p), dim3(256), 0, s, d, t.Z, P1, P2, t.rZ1, t.rZ2, t.gram, t.ctrl);
   } else {
-    const hipError_t e = launch_group_update(d, t, P1, P2, single != nullptr, t.ctrl, s);
-    if (e != hipSuccess) return e;
-    u = ScoreUpdate{t.part, P1, P2, P1D, P2D, single};
+    if (ev) hipEventRecord(ev[0], s);
+    const int64_t tiles = (int64_t)rows64 * (rows64 + 1) / 2;
+    const int cc = gu_chunk_cols(d.p, d.m), chunks = (d.m + cc - 1) / cc;
+    OSSCAR_BY_TILES(q, {
+      const size_t lds = std::max((size_t)2 * 64 * (2 * gu_kq(q) + 4) * 4, group_update_lds<RT>(gu_kq(q)));
+      e = dynamic_lds(reinterpret_cast<const void*>(pair_state_kernel<RT>), lds, 2 * 16 * (16 * RT + 1) * 4);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(pair_state_kernel<RT>, dim3((unsigned)(rows16 + (int64_t)d.p * chunks + tiles)), dim3(256), lds, s, d, t.N, t.Z, P1, P2, P1D, P2D,
+                         t.rZ1, t.rZ2, t.small, t.ctrl, t.dblk, t.kept, t.part, single, always_accept, t.dpart, ncb, rows16, cc, chunks);
+    })
+    if (ev) hipEventRecord(ev[1], s);
+    u = ScoreUpdate{t.part, P1, P2, P1D, P2D, single, tr};
   }
   if (ev) hipEventRecord(ev[2], s);
   launch_score(d, t.kept, t.gram, t.dblk, t.score, t.ctrl, 1, s, u);

@@ -608,3 +608,36 @@ def test_picks_of_block_removals(p, t_hat, equal):
     for i, gap in enumerate(gaps):
         lo, hi = cost[(i + 1) * t_hat - 1], cost[(i + 1) * t_hat]
         assert abs(gap - (hi - lo) / lo) <= 1e-6
+
+
+@pytest.mark.parametrize("p", [2, 255, 257, 2048, 2049])
+def test_selection_of_groups(p):
+    """Groups of two rows around the selection's sizes: one score, a wave and a workgroup more or less, and on either side of the
+    size from which a launch of its own selects.  H = the identity times the group's own factor, so that a group's cost and gain are
+    its own rows' squares over that factor, and every value that can be asked for is known: three moves take the smallest kept
+    and the largest excluded score, the lowest index of equal ones (there are many), and the objective follows exactly up to
+    its float64 sums (scores are sums of two small whole numbers)."""
+    pkg = _pkg()
+    q, m, d1, k = 2, 3, 2 * p, p // 2
+    gen = torch.Generator().manual_seed(p)
+    val = torch.randint(1, 6, (p,), generator=gen)                              # a group's rows: (val, 0, 0), (0, 1, 0)
+    G = torch.zeros(d1, m)
+    G[0::2, 0] = val.float()
+    G[1::2, 1] = 1.0
+    kept = set(torch.randperm(p, generator=gen)[:k].tolist())
+    score = [float(v) ** 2 + 1.0 for v in val.tolist()]
+    s = pkg.Solver(d1, m, p, q, k, 4, torch.float32, torch.float32, DEV)
+    s.osscar_set_quadratic(torch.eye(d1).to(DEV), G.to(DEV), 0.0, np.ones(p))
+    s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, sorted(kept))
+    moves = []
+    for _ in range(3):
+        r = s.osscar_local_search(max_swaps=1, rel_tol=0.0)
+        g, j = min((score[x], x) for x in kept)[1], min((-score[x], x) for x in range(p) if x not in kept)[1]
+        if score[j] <= score[g]:
+            assert r["accepted"] == 0
+            break
+        assert r["accepted"] == 1 and (r["trace_out"][0], r["trace_in"][0]) == (g, j)
+        assert abs((r["obj_initial"] - r["obj_final"]) - (score[j] - score[g])) <= 1e-9 * sum(score)
+        kept = kept - {g} | {j}
+        moves.append((g, j))
+    assert s.osscar_get_tensor(8).cpu().numpy().astype(int).tolist() == sorted(kept)
