@@ -950,7 +950,8 @@ __global__ __launch_bounds__(256) void gram_dblk_q1_kernel(int d1, int m, const 
 // through LDS into operand order, their products on v_mfma_f64_16x16x4_f64.  The waves' sums are added in order and left in
 // part[h][chunk][lower tile][256]; score_kernel adds the chunks in order.  Bound by the float32 matrix cores and Z's two
 // passes of memory about equally; as a row x 256 columns of scalar products and a second pass for the Grams a swap of two
-// groups of 64 rows, 4096 columns took 0.42 + 0.20 ms.
+// groups of 64 rows, 4096 columns took 0.42 + 0.20 ms.  Loads are made from clamped places and dropped where they lie outside: under
+// a condition each was waited for by itself, and the launch of both updates took 120 us there instead of 104.
 constexpr int GU_LD = 36;
 // ROWS rows of a panel (q floats each, contiguous) into S[r * ks + k0 + c], c < kq, zeros past q and past the first `rows` rows;
 // by 256 threads, 256 / ROWS of them to a row, four floats at a time where the rows allow it
@@ -960,11 +961,20 @@ __device__ __forceinline__ void stage_panel(float* S, int ks, int k0, int kq, co
   const int r = threadIdx.x / TPR, l = threadIdx.x % TPR;
   if (r >= ROWS) return;
   float* dst = S + r * ks + k0;
-  const float* src = P + (int64_t)r * q;
+  const bool live = r < rows;
+  const float* src = P + (int64_t)(live ? r : rows - 1) * q;      // (a load under a condition is waited for where the branch ends)
   if ((q & 3) == 0 && (reinterpret_cast<uintptr_t>(P) & 15) == 0) {
-    for (int c = 4 * l; c < kq; c += 4 * TPR) *reinterpret_cast<float4*>(dst + c) = r < rows ? *reinterpret_cast<const float4*>(src + c) : float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int c = 4 * l; c < kq; c += 4 * TPR) {
+      const float4 v = *reinterpret_cast<const float4*>(src + c);
+      *reinterpret_cast<float4*>(dst + c) = float4{live ? v.x : 0.f, live ? v.y : 0.f, live ? v.z : 0.f, live ? v.w : 0.f};
+    }
   } else {
-    for (int c = l; c < kq; c += TPR) dst[c] = (r < rows && c < q) ? src[c] : 0.f;
+#pragma unroll 4
+    for (int c = l; c < kq; c += TPR) {
+      const float v = src[min(c, q - 1)];
+      dst[c] = (live & (c < q)) ? v : 0.f;
+    }
   }
 }
 template <int RT> struct GroupUpdLds { float zt[4][16 * RT][GU_LD]; };
@@ -1021,21 +1031,24 @@ __device__ __forceinline__ void group_update(float* gu_lds, TabDims d, float* __
 #pragma unroll
         for (int r = 0; r < 4; r++) {                     // C layout: row 4 (lane / 16) + r, column lane % 16
           const int row = t * 16 + 4 * lr + r, col = c0 + j * 16 + lc;
-          z[t][j][r] = (row < q && col < m) ? Zh[(int64_t)row * m + col] : 0.f;
+          z[t][j][r] = Zh[(int64_t)min(row, q - 1) * m + min(col, m - 1)];
         }
       }
-#pragma unroll 4
-    for (int kk = 0; kk < K; kk += 4) {
-      const int half = kk >= kq, c = kk + lr - half * kq;
+    for (int half = 0; half * kq < K; half++) {
       const float* rz = half ? rZ2 : rZ1;
-      float b[2];
+      const float* b0 = rz + min(c0 + lc, m - 1);
+      const float* b1 = rz + min(c0 + 16 + lc, m - 1);
+      const float* ap = Ps + lc * ks + half * kq + lr;
+#pragma unroll 8
+      for (int kk = 0; kk < kq; kk += 4) {                  // past q the coefficients are zeros
+        const int64_t o = (int64_t)min(kk + lr, q - 1) * m;
+        const float b[2] = {b0[o], b1[o]};
 #pragma unroll
-      for (int j = 0; j < 2; j++) b[j] = (c < q && c0 + j * 16 + lc < m) ? rz[(int64_t)c * m + c0 + j * 16 + lc] : 0.f;
+        for (int t = 0; t < RT; t++) {
+          const float av = ap[t * 16 * ks + kk];
 #pragma unroll
-      for (int t = 0; t < RT; t++) {
-        const float av = Ps[(t * 16 + lc) * ks + kk + lr];
-#pragma unroll
-        for (int j = 0; j < 2; j++) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[j], acc[t][j], 0, 0, 0);
+          for (int j = 0; j < 2; j++) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b[j], acc[t][j], 0, 0, 0);
+        }
       }
     }
 #pragma unroll
@@ -1045,8 +1058,9 @@ __device__ __forceinline__ void group_update(float* gu_lds, TabDims d, float* __
 #pragma unroll
         for (int r = 0; r < 4; r++) {
           const int row = t * 16 + 4 * lr + r, col = c0 + j * 16 + lc;
-          const float v = z[t][j][r] - acc[t][j][r];
-          if (K && row < q && col < m) Zh[(int64_t)row * m + col] = v;
+          const bool inside = (row < q) & (col < m);
+          const float v = inside ? z[t][j][r] - acc[t][j][r] : 0.f;
+          if (K && inside) Zh[(int64_t)row * m + col] = v;
           zt[wave][row][j * 16 + lc] = v;
         }
     // the wave's own part of LDS: in order, no barrier
@@ -1799,7 +1813,7 @@ __device__ __forceinline__ void update_N(float* un_lds, TabDims d, float* __rest
 #pragma unroll
     for (int b = 0; b < 2; b++)
 #pragma unroll
-      for (int r = 0; r < 4; r++) old[a][b][r] = inside(a, b, r) ? N[at(a, b, r)] : 0.f;
+      for (int r = 0; r < 4; r++) old[a][b][r] = N[(int64_t)min(i0 + wi + a * 16 + 4 * lr + r, n - 1) * n + min(l0 + wl + b * 16 + lc, n - 1)];
   for (int half = 0; half < (single ? 1 : 2); half++) {
     stage_panel<64>(As, ks, half * kq, kq, (half ? P2D : P1D) + (int64_t)i0 * q, q, n - i0);
     stage_panel<64>(Bs, ks, half * kq, kq, (half ? P2 : P1) + (int64_t)l0 * q, q, n - l0);
