@@ -120,7 +120,8 @@ __device__ __forceinline__ bool inv_sym(int w, InvLds<NB>& L, Get get, Put put) 
     for (int r = 0; r < 4; r++) {
       const int i = ti[s] * 16 + 4 * r + lr, j = tj[s] * 16 + lc;
       const int hi = i > j ? i : j, lo = i > j ? j : i;
-      x[s][r] = hi < w ? get(hi, lo) : (i == j ? 1.0 : 0.0);
+      const double v = get(hi < w ? hi : w - 1, lo < w ? lo : w - 1);      // (a load under a condition is waited for by itself)
+      x[s][r] = hi < w ? v : (i == j ? 1.0 : 0.0);
     }
   }
   auto invert = [&](const swd4& a, int kb) {
@@ -193,10 +194,11 @@ __device__ __forceinline__ void mm_small(int q, FA a, FB b, FO out) {
     const int i0 = t / RT * 16, j0 = t % RT * 16;
     if (i0 >= q || j0 >= q) continue;
     swd4 acc = {0.0, 0.0, 0.0, 0.0};
+    const int ia = min(i0 + lc, q - 1), jb = min(j0 + lc, q - 1);      // rows and columns past the end are dropped
 #pragma unroll 4
     for (int k0 = 0; k0 < q; k0 += 4) {
-      const int k = k0 + lr;
-      const double av = (i0 + lc < q && k < q) ? a(i0 + lc, k) : 0.0, bv = (j0 + lc < q && k < q) ? b(k, j0 + lc) : 0.0;
+      const int k = k0 + lr, kc = min(k, q - 1);
+      const double at = a(ia, kc), bt = b(kc, jb), av = k < q ? at : 0.0, bv = k < q ? bt : 0.0;
       acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
     }
 #pragma unroll
@@ -997,10 +999,14 @@ __device__ __forceinline__ void group_update(float* gu_lds, TabDims d, float* __
       for (int i0 = 0; i0 < q; i0 += 16) {
         swd4 acc = {0.0, 0.0, 0.0, 0.0};
         if (h == g && !single) {
-#pragma unroll 4
+          const double* Mi = M1 + min(i0 + lc, q - 1) * q;
+          const float* rz = rZ2 + min(col, m - 1);
+#pragma unroll 8
           for (int k0 = 0; k0 < q; k0 += 4) {
-            const int k = k0 + lr;
-            const double av = (i0 + lc < q && k < q) ? M1[(i0 + lc) * q + k] : 0.0, bv = (k < q && col < m) ? (double)rZ2[(int64_t)k * m + col] : 0.0;
+            const int k = k0 + lr, kc = min(k, q - 1);
+            const double at = Mi[kc];
+            const float bt = rz[(int64_t)kc * m];
+            const double av = k < q ? at : 0.0, bv = k < q ? (double)bt : 0.0;
             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
           }
         }
@@ -1182,13 +1188,26 @@ __global__ __launch_bounds__(256) void score_kernel(TabDims d, const int32_t* __
   double* dblk_h = dblk + (int64_t)h * q * q;
   if (part) {
     const double* ph = part + (int64_t)h * chunks * (NT * 256);
-    for (int idx = tid; idx < NT * 256; idx += 256) {
-      double v = 0;
-#pragma unroll 4
-      for (int ch = 0; ch < chunks; ch++) v += ph[(int64_t)ch * (NT * 256) + idx];
-      int t = idx >> 8, br = 0;
+    double sum[NT];
+#pragma unroll
+    for (int n = 0; n < NT; n++) sum[n] = 0;
+    for (int ch = 0; ch < chunks; ch += 4) {              // four chunks of every tile in flight, added in order
+      double v[4][NT];
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+#pragma unroll
+        for (int n = 0; n < NT; n++) v[u][n] = ph[(int64_t)min(ch + u, chunks - 1) * (NT * 256) + n * 256 + tid];
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+#pragma unroll
+        for (int n = 0; n < NT; n++) sum[n] = ch + u < chunks ? sum[n] + v[u][n] : sum[n];
+    }
+#pragma unroll
+    for (int n = 0; n < NT; n++) {
+      const double v = sum[n];
+      int t = n, br = 0;
       while (t > br) { t -= br + 1; br++; }
-      const int r = br * 16 + ((idx & 255) >> 4), c = t * 16 + (idx & 15);
+      const int r = br * 16 + (tid >> 4), c = t * 16 + (tid & 15);
       if (r < q && c < q) {
         gram_h[r * q + c] = v;
         if (br != t) gram_h[c * q + r] = v;
@@ -1207,10 +1226,13 @@ __global__ __launch_bounds__(256) void score_kernel(TabDims d, const int32_t* __
         for (int half = 0; half < (single ? 1 : 2); half++) {
           const float* A = half ? P2D : P1D;
           const float* B = half ? P2 : P1;
-#pragma unroll 4
+          const float* Ai = A + base + min(i, q - 1) * q;
+          const float* Bl = B + base + min(l, q - 1) * q;
+#pragma unroll 8
           for (int k0 = 0; k0 < q; k0 += 4) {
-            const int k = k0 + lr;
-            const double av = (i < q && k < q) ? (double)A[base + i * q + k] : 0.0, bv = (l < q && k < q) ? (double)B[base + l * q + k] : 0.0;
+            const int k = k0 + lr, kc = min(k, q - 1);
+            const float at = Ai[kc], bt = Bl[kc];
+            const double av = k < q ? (double)at : 0.0, bv = k < q ? (double)bt : 0.0;
             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
           }
         }
@@ -1481,7 +1503,7 @@ __global__ __launch_bounds__(256) void pair_open_kernel(TabDims d, const float* 
                                                          float* __restrict__ C1, float* __restrict__ C2, float* __restrict__ Zg,
                                                          float* __restrict__ Zj, double* __restrict__ small, const int32_t* __restrict__ single,
                                                          int pick, int forced_out, int forced_in, int algebra, int row_blocks) {
-  extern __shared__ double psm[];      // three q x q matrices with rows of q + 1, or 64 x 65 floats
+  extern __shared__ double psm[];      // three q x q matrices with rows of q + 1 and one of floats, or 64 x 65 floats
   __shared__ InvLds<RT> L;
   if (ctrl->done) return;
   const int q = d.q, tid = threadIdx.x;
@@ -1522,12 +1544,17 @@ __global__ __launch_bounds__(256) void pair_open_kernel(TabDims d, const float* 
   double* Dg = small; double* Njg = small + qq; double* M1 = small + 2 * qq; double* Dj = small + 3 * qq;
   double* W2Dj = small + 4 * qq;
   double* X0 = psm; double* X1 = psm + q * qs; double* X2 = psm + 2 * q * qs;
-  if (!single)
+  float* X3 = reinterpret_cast<float*>(psm + 3 * q * qs);       // N_jj
+  if (!single) {
+#pragma unroll 4
     for (int idx = tid; idx < qq; idx += 256) {
-      const double njg = (double)nsym(N, ld, j0 + idx / q, g0 + idx % q);      // N(j_r, g_c)
-      Njg[idx] = njg;
-      X1[idx / q * qs + idx % q] = njg;
+      const int r = idx / q, c = idx % q;
+      const float ngj = nsym(N, ld, j0 + r, g0 + c), njj = nsym(N, ld, j0 + r, j0 + c);
+      Njg[idx] = (double)ngj;                                   // N(j_r, g_c)
+      X1[r * qs + c] = (double)ngj;
+      X3[r * qs + c] = njj;
     }
+  }
   // kept pivot: N_gg = -P_gg is negative definite
   bool bad = inv_sym<4, T, RT>(q, L, [&](int r, int c) { return -(double)nsym(N, ld, g0 + r, g0 + c); },
                                [&](int r, int c, double v) { X0[r * qs + c] = X0[c * qs + r] = -v; Dg[r * q + c] = Dg[c * q + r] = -v; });
@@ -1540,7 +1567,7 @@ __global__ __launch_bounds__(256) void pair_open_kernel(TabDims d, const float* 
                  [&](int i, int c, double v) { X2[i * qs + c] = v; M1[i * q + c] = v; });
     __syncthreads();
     mm_small<RT>(q, [&](int i, int k) { return X1[i * qs + k]; }, [&](int k, int c) { return X2[k * qs + c]; },      // N'_jj = N_jj - N_jg M1
-                 [&](int i, int c, double v) { X0[i * qs + c] = (double)nsym(N, ld, j0 + i, j0 + c) - v; });
+                 [&](int i, int c, double v) { X0[i * qs + c] = (double)X3[i * qs + c] - v; });
     __syncthreads();
     // entering pivot: Schur complement, positive definite
     bad |= inv_sym<4, T, RT>(q, L, [&](int r, int c) { return X0[r * qs + c]; },
@@ -1566,15 +1593,25 @@ __device__ __forceinline__ void pair_cols(TabDims d, float* __restrict__ Zg, flo
   const double* Dg = small; const double* Njg = small + qq; const double* Dj = small + 3 * qq;
   const int i0 = wave * 16, col = block * PC_COLS + lc;
   const bool live = col < m, mine = i0 < q;
-  for (int r = tid >> 4; r < q; r += 16) ta[r][tid & 15] = block * PC_COLS + (tid & 15) < m ? (double)Zg[(int64_t)r * m + block * PC_COLS + (tid & 15)] : 0.0;
+  const int tcol = block * PC_COLS + (tid & 15);
+#pragma unroll
+  for (int u = 0; u < RT; u++) {                             // (loads from clamped places: under a condition each is waited for)
+    const int r = (tid >> 4) + 16 * u;
+    const float v = Zg[(int64_t)min(r, q - 1) * m + min(tcol, m - 1)];
+    ta[r][tid & 15] = ((r < q) & (tcol < m)) ? (double)v : 0.0;
+  }
+  float zj[4];
+#pragma unroll
+  for (int r = 0; r < 4; r++) zj[r] = single ? 0.f : Zj[(int64_t)min(i0 + 4 * r + lr, q - 1) * m + min(col, m - 1)];
   __syncthreads();
   auto product = [&](const double* A, double (*B)[PC_COLS + 1]) {
     swd4 acc = {0.0, 0.0, 0.0, 0.0};
     if (mine) {
-#pragma unroll 4
+      const double* Ai = A + min(i0 + lc, q - 1) * q;
+#pragma unroll 8
       for (int k0 = 0; k0 < q; k0 += 4) {
         const int k = k0 + lr;
-        const double av = (i0 + lc < q && k < q) ? A[(i0 + lc) * q + k] : 0.0, bv = k < q ? B[k][lc] : 0.0;
+        const double at = Ai[min(k, q - 1)], av = k < q ? at : 0.0, bv = k < q ? B[k][lc] : 0.0;
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
       }
     }
@@ -1597,7 +1634,7 @@ __device__ __forceinline__ void pair_cols(TabDims d, float* __restrict__ Zg, flo
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       const int i = i0 + 4 * r + lr;
-      if (mine && i < q) ta[i][lc] = (live ? (double)Zj[(int64_t)i * m + col] : 0.0) - v[r];
+      if (mine && i < q) ta[i][lc] = (live ? (double)zj[r] : 0.0) - v[r];
     }
     __syncthreads();
     v = product(Dj, ta);                                     // rZ2 = Dj' z'j
@@ -1639,14 +1676,22 @@ __device__ __forceinline__ void pair_panels(TabDims d, const float* __restrict__
   const int g0 = (single ? *single : ctrl->g_out) * q, j0 = (single ? *single : ctrl->g_in) * q;
   const double* Dg = small; const double* M1 = small + 2 * qq; const double* Dj = small + 3 * qq;
   const int i0 = block * 16, j = wave * 16 + lc, ni = min(16, d.d1 - i0);
-  for (int idx = tid; idx < 16 * q; idx += 256) sc1[idx / q][idx % q] = idx < ni * q ? (double)C1[(int64_t)i0 * q + idx] : 0.0;
+#pragma unroll 4
+  for (int idx = tid; idx < 16 * q; idx += 256) {
+    const float v = C1[(int64_t)i0 * q + min(idx, ni * q - 1)];
+    sc1[idx / q][idx % q] = idx < ni * q ? (double)v : 0.0;
+  }
+  float c2[4];
+#pragma unroll
+  for (int r = 0; r < 4; r++) c2[r] = single ? 0.f : C2[(int64_t)(i0 + min(4 * r + lr, ni - 1)) * q + min(j, q - 1)];
   __syncthreads();
   auto product = [&](const double (*A)[16 * RT + 1], const double* B) {
     swd4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
+    const double* Bj = B + min(j, q - 1);
+#pragma unroll 8
     for (int k0 = 0; k0 < q; k0 += 4) {
       const int k = k0 + lr;
-      const double av = k < q ? A[lc][k] : 0.0, bv = (k < q && j < q) ? B[k * q + j] : 0.0;
+      const double bt = Bj[min(k, q - 1) * q], av = k < q ? A[lc][k] : 0.0, bv = k < q ? bt : 0.0;
       acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
     }
     return acc;
@@ -1660,7 +1705,7 @@ __device__ __forceinline__ void pair_panels(TabDims d, const float* __restrict__
 #pragma unroll
       for (int r = 0; r < 4; r++) {
         const int i = 4 * r + lr;
-        sc2[i][j] = (i < ni && j < q) ? (double)C2[(int64_t)(i0 + i) * q + j] - v[r] : 0.0;
+        sc2[i][j] = (i < ni && j < q) ? (double)c2[r] - v[r] : 0.0;
       }
     }
     __syncthreads();
@@ -1709,17 +1754,22 @@ __device__ __forceinline__ void pair_fix_rows(TabDims d, float* __restrict__ N, 
   const int64_t ld = d.d1;
   const int l0 = block * 16, nl = min(16, d.d1 - l0);
   if (!single) {
-    for (int idx = tid; idx < 16 * q; idx += 256) tj[idx / q][idx % q] = idx < nl * q ? P2D[(int64_t)l0 * q + idx] : 0.f;
+#pragma unroll 4
+    for (int idx = tid; idx < 16 * q; idx += 256) {
+      const float v = P2D[(int64_t)l0 * q + min(idx, nl * q - 1)];
+      tj[idx / q][idx % q] = idx < nl * q ? v : 0.f;
+    }
     __syncthreads();
   }
   if (wave < RT) {
     const int r0 = wave * 16 + lc;                 // pivot row
     swd4 acc = {0.0, 0.0, 0.0, 0.0};
     if (!single) {
-#pragma unroll 4
+      const double* Mr = M1 + min(r0, q - 1) * q;
+#pragma unroll 8
       for (int k0 = 0; k0 < q; k0 += 4) {
         const int k = k0 + lr;
-        const double av = k < q ? (double)tj[lc][k] : 0.0, bv = (k < q && r0 < q) ? M1[r0 * q + k] : 0.0;
+        const double bt = Mr[min(k, q - 1)], av = k < q ? (double)tj[lc][k] : 0.0, bv = k < q ? bt : 0.0;
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
       }
     }
@@ -2162,7 +2212,7 @@ hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int force
   }
   auto open = [&](int algebra) -> hipError_t {
     OSSCAR_BY_TILES(q, {
-      const size_t lds = std::max((size_t)64 * 65 * 4, (size_t)3 * q * (q + 1) * 8);
+      const size_t lds = std::max((size_t)64 * 65 * 4, (size_t)q * (q + 1) * 28);
       const hipError_t e = dynamic_lds(reinterpret_cast<const void*>(pair_open_kernel<RT>), lds, sizeof(InvLds<RT>) + 1024);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(pair_open_kernel<RT>, dim3(4 * rows64 + algebra), dim3(256), lds, s, d, t.N, t.Z, t.kept, t.score, t.ctrl, t.C1, t.C2, t.rZ1, t.rZ2,
