@@ -134,7 +134,8 @@ struct osscar_ctx {
   hipEvent_t ev_a = nullptr, ev_b = nullptr;
   hipEvent_t ev_s[EV_SAMPLES][3];
   hipEvent_t ev_g[2 * EV_SAMPLES];   // pairs around the launches of the Gram kernel of the last chunk call
-  SearchCtrl* snap = nullptr;         // pinned host memory for reading the control block
+  struct Snap { SearchCtrl ctrl; int32_t pick[128]; float gap[2]; };
+  Snap* snap = nullptr;               // pinned host memory for reading the control block and a block move's picks
   PackQueue queue;                    // bf16 rows of the layer that wait for their product
   SideStream side;   // the flush of the delayed-update search overlaps two of its products
   bool ev_ok = false;
@@ -706,7 +707,7 @@ osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* wor
   for (int i = 0; i < EV_SAMPLES && c->ev_ok; i++)
     for (int j = 0; j < 3; j++) c->ev_ok = c->ev_ok && (hipEventCreate(&c->ev_s[i][j]) == hipSuccess);
   for (int i = 0; i < 2 * EV_SAMPLES && c->ev_ok; i++) c->ev_ok = c->ev_ok && (hipEventCreate(&c->ev_g[i]) == hipSuccess);
-  c->ev_ok = c->ev_ok && hipHostMalloc(reinterpret_cast<void**>(&c->snap), sizeof(SearchCtrl), hipHostMallocDefault) == hipSuccess;
+  c->ev_ok = c->ev_ok && hipHostMalloc(reinterpret_cast<void**>(&c->snap), sizeof(*c->snap), hipHostMallocDefault) == hipSuccess;
   c->ev_ok = c->ev_ok && hipStreamCreateWithFlags(&c->side.stream, hipStreamNonBlocking) == hipSuccess &&
              hipEventCreateWithFlags(&c->side.fork, hipEventDisableTiming) == hipSuccess &&
              hipEventCreateWithFlags(&c->side.join, hipEventDisableTiming) == hipSuccess;
@@ -990,10 +991,10 @@ osscar_status osscar_init_support(osscar_ctx* c, int mode, const int32_t* groups
 
 static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h, const SearchCtrl* from = nullptr) {
   // through pinned memory: the search waits on this copy once per 64 swaps with the device idle meanwhile
-  SearchCtrl* dst = c->snap ? c->snap : h;
+  SearchCtrl* dst = &c->snap->ctrl;
   HIPCHK(c, hipMemcpyAsync(dst, from ? from : c->ctrl, sizeof *h, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
-  if (dst != h) *h = *dst;
+  *h = *dst;
   return OSSCAR_OK;
 }
 
@@ -1004,7 +1005,7 @@ struct SwapRun {
   int tau_most = 0;              // pending pivots after the launches so far, at most
   SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) {}
   hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode); }
-  hipError_t swap(int always, int limit, int g = -1, int j = -1, const int32_t* single = nullptr) {
+  hipError_t swap(int always, int limit, const int32_t* g = nullptr, const int32_t* j = nullptr, const int32_t* single = nullptr) {
     SearchCtrl* next = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
     const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, single, g, j);
     t.ctrl = next;
@@ -1014,8 +1015,8 @@ struct SwapRun {
   }
   // removal of the row *single, iteration `iter` of the call: the second launch does it if the first had to fetch the row's products
   hipError_t remove(const int32_t* single, int iter) {
-    const hipError_t e = swap(1, iter, -1, -1, single);
-    return e != hipSuccess ? e : swap(1, iter, -1, -1, single);
+    const hipError_t e = swap(1, iter, nullptr, nullptr, single);
+    return e != hipSuccess ? e : swap(1, iter, nullptr, nullptr, single);
   }
   hipError_t flush() { tau_most = 0; return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c)); }
   hipError_t settle() {
@@ -1341,23 +1342,27 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   HIPCHK(c, hipEventRecord(c->ev_a, s));
   if (use_lazy) HIPCHK(c, run.init());
   int pending = 0, done_pairs = 0, blocks = 0, accepted = 0;
-  // applies the pairs one after the other (each unconditionally); resumes after a flush when the kernels had to stop
-  auto run_pairs = [&](const std::vector<int32_t>& out, const std::vector<int32_t>& inn) -> osscar_status {
-    size_t idx = 0;
+  // applies the picked pairs one after the other (each unconditionally; back: each the other way round, from the last one);
+  // resumes after a flush when the kernels had to stop.  The one-launch swaps read the pairs where the pick left them, so that
+  // the host waits once per move; the picks are in pinned memory by the time it has waited.
+  auto run_pairs = [&](bool back) -> osscar_status {
+    auto out = [&](int r) { return back ? 64 + take - 1 - r : r; };
+    auto inn = [&](int r) { return back ? take - 1 - r : 64 + r; };
+    int idx = 0;
     int misses = h.misses;
-    while (idx < out.size()) {
-      for (size_t r = idx; r < out.size(); r++) {
-        if (use_lazy) HIPCHK(c, run.swap(1, done_pairs + (int)(r - idx) + 1, out[r], inn[r]));
-        else HIPCHK(c, launch_search_iteration(d, t, out[r], inn[r], 1, s));
+    while (idx < take) {
+      for (int r = idx; r < take; r++) {
+        if (use_lazy) HIPCHK(c, run.swap(1, done_pairs + r - idx + 1, c->g_pick + out(r), c->g_pick + inn(r)));
+        else HIPCHK(c, launch_search_iteration(d, t, c->snap->pick[out(r)], c->snap->pick[inn(r)], 1, s));
       }
       osscar_status q = read_ctrl(c, &h, run.t.ctrl);
       if (q != OSSCAR_OK) return q;
       run.tau_most = h.tau;
       if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_block_search: a pivot lost definiteness in move %d", blocks);
       const int did = h.iters - done_pairs;
-      if (did < 0 || did > (int)(out.size() - idx)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search lost count of its pairs");
+      if (did < 0 || did > take - idx) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search lost count of its pairs");
       done_pairs += did; idx += did; pending += 2 * did;
-      if (idx < out.size()) {
+      if (idx < take) {
         if (!use_lazy || (!h.pause && h.misses == misses)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
         misses = h.misses;
         if (!h.pause) continue;                // a pair's launch fetched the products of its pivots: the pairs from it on again
@@ -1367,33 +1372,29 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
     }
     return OSSCAR_OK;
   };
-  std::vector<int32_t> out(take), inn(take);
-  float gaps[2] = {0, 0};
   while (take > 0 && blocks < max_iters) {
     if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = 0; }
-    HIPCHK(c, launch_greedy_pick(d, t, take, c->g_pick, c->g_gap, s, 0));
-    HIPCHK(c, launch_greedy_pick(d, t, take, c->g_pick + 64, c->g_gap + 1, s, 1));
-    HIPCHK(c, hipMemcpyAsync(out.data(), c->g_pick, (size_t)take * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(inn.data(), c->g_pick + 64, (size_t)take * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(gaps, c->g_gap, 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    HIPCHK(c, launch_greedy_pick(d, run.t, take, c->g_pick, c->g_gap, s, 2));
+    HIPCHK(c, hipMemcpyAsync(c->snap->pick, c->g_pick, sizeof c->snap->pick, hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipMemcpyAsync(c->snap->gap, c->g_gap, sizeof c->snap->gap, hipMemcpyDeviceToHost, s));
+    if (!use_lazy) HIPCHK(c, hipStreamSynchronize(s));
     const double obj_before = h.obj;
-    st = run_pairs(out, inn);
+    st = run_pairs(false);
     if (st != OSSCAR_OK) return st;
     const double delta = h.obj - obj_before;
     const bool ok = always || delta < -rel_tol * obj_before;
-    if (t_out) std::copy(out.begin(), out.end(), t_out + (size_t)blocks * block);
-    if (t_in) std::copy(inn.begin(), inn.end(), t_in + (size_t)blocks * block);
+    const int32_t* picks = c->snap->pick;
+    if (t_out) std::copy(picks, picks + take, t_out + (size_t)blocks * block);
+    if (t_in) std::copy(picks + 64, picks + 64 + take, t_in + (size_t)blocks * block);
     if (t_out) std::fill(t_out + (size_t)blocks * block + take, t_out + (size_t)(blocks + 1) * block, -1);
     if (t_in) std::fill(t_in + (size_t)blocks * block + take, t_in + (size_t)(blocks + 1) * block, -1);
-    if (t_gap) { t_gap[2 * blocks] = gaps[0]; t_gap[2 * blocks + 1] = gaps[1]; }
+    if (t_gap) { t_gap[2 * blocks] = c->snap->gap[0]; t_gap[2 * blocks + 1] = c->snap->gap[1]; }
     if (t_obj) t_obj[blocks] = ok ? h.obj : obj_before;
     blocks++;
     if (!ok) {
       // take the move back: the same pairs in reverse (the pending pivots must reach the tableau first)
       if (use_lazy && pending > 0) { HIPCHK(c, run.flush()); pending = 0; }
-      std::vector<int32_t> bo(inn.rbegin(), inn.rend()), bi(out.rbegin(), out.rend());
-      st = run_pairs(bo, bi);
+      st = run_pairs(true);
       if (st != OSSCAR_OK) return st;
       h.obj = obj_before;
       HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(run.t.ctrl) + offsetof(SearchCtrl, obj), &h.obj, 8, hipMemcpyHostToDevice, s));

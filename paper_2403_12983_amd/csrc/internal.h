@@ -229,7 +229,8 @@ hipError_t launch_refresh_scores(const TabDims& d, const TabPtrs& t, hipStream_t
 hipError_t launch_search_iteration(const TabDims& d, const TabPtrs& t, int forced_out, int forced_in, int always_accept,
                                    hipStream_t s, hipEvent_t* ev = nullptr, const int32_t* single = nullptr, int exact_in = 0);
 // pick[0..take) = the kept groups of smallest removal cost (ascending), *gap = relative gap to the next one; take <= 64
-// side 1: the groups outside the kept set with the largest addition gain (descending) instead
+// side 1: the groups outside the kept set with the largest addition gain (descending) instead; side 2: both in one launch,
+// side 1's into pick + 64 and gap + 1
 hipError_t launch_greedy_pick(const TabDims& d, const TabPtrs& t, int take, int32_t* pick, float* gap, hipStream_t s,
                               int side = 0);
 hipError_t launch_select(const TabDims& d, const TabPtrs& t, int forced_out, int forced_in, hipStream_t s);
@@ -282,7 +283,7 @@ hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& 
 // swap.hip: one swap in one launch, from the control block t.ctrl, L.Minv and L.rec to *next, L.Minv2 and L.rec2 (the caller exchanges
 // them after every launch); tau_most: at most this many pivots are pending
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int tau_most,
-                            hipStream_t s, const int32_t* single = nullptr, int forced_out = -1, int forced_in = -1);
+                            hipStream_t s, const int32_t* single = nullptr, const int32_t* given_out = nullptr, const int32_t* given_in = nullptr);
 int swap_record_count(int64_t d1);
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);

@@ -133,12 +133,13 @@ __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* _
 
 // NT threads, RPW rows per workgroup, NT / RPW lanes per row.  cin: control block before this launch, cout: after it.
 // limit: iterations to have run after this launch at most; beyond it a launch does nothing, and neither does a given pair or row whose
-// predecessor has not run (its launch fetched products).  single != nullptr: removal of the one row *single (Case 1 alone).
+// predecessor has not run (its launch fetched products).  single != nullptr: removal of the one row *single (Case 1 alone); given_g,
+// given_j != nullptr: the pair (*given_g, *given_j) if *given_g is a row (otherwise the pick, as if there were none).
 template <int NT, int RPW>
 __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* __restrict__ N0, const float* __restrict__ Z0, int d1, int m,
                                                         const SearchCtrl* __restrict__ cin, SearchCtrl* __restrict__ cout, int32_t* __restrict__ kept,
                                                         double* __restrict__ rho, double* __restrict__ diag, double* __restrict__ score, int always, int tau_most,
-                                                        const int32_t* __restrict__ single, int forced_g, int forced_j, int limit, int32_t* __restrict__ trace_out,
+                                                        const int32_t* __restrict__ single, const int32_t* __restrict__ given_g, const int32_t* __restrict__ given_j, int limit, int32_t* __restrict__ trace_out,
                                                         int32_t* __restrict__ trace_in, float* __restrict__ trace_gap, double* __restrict__ trace_obj) {
   constexpr int TM = LAZY_TM, W = NT / 64, H = NT / 2;
   constexpr int TPR = NT / TM, MU = TM / (2 * TPR);             // threads per row of M^-1, pairs of columns per thread
@@ -196,6 +197,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
       L.rec2[wg] = r;
     }
   };
+  const int forced_g = given_g ? *given_g : -1, forced_j = given_j ? *given_j : -1;
   const bool idle = (cin->done | cin->pause) != 0 || cin->iters >= limit || ((forced_g >= 0 || single) && cin->iters < limit - 1);
   // ---- pick: lanes of the first half of the workgroup hold the leaving side's records, the others the entering side's
   if (rt >= nwg) { v1 = INFINITY; v2 = INFINITY; i1 = -1; sl1 = -1; }
@@ -486,11 +488,11 @@ static int swap_rows_per_wg(int d1) { return d1 <= 8192 ? 32 : d1 <= 16384 ? 64 
 int swap_record_count(int64_t d1) { const int r = swap_rows_per_wg((int)d1); return (int)((d1 + r - 1) / r); }
 
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always, int limit, int tau_most,
-                            hipStream_t s,                            const int32_t* single, int forced_out, int forced_in) {
+                            hipStream_t s, const int32_t* single, const int32_t* given_out, const int32_t* given_in) {
   const int nwg = swap_record_count(d.d1);
 #define OSSCAR_SWAP(NT, RPW)                                                                                                         \
   hipLaunchKernelGGL((lazy_swap_kernel<NT, RPW>), dim3(nwg), dim3(NT), 0, s, L, t.N, t.Z, d.d1, d.m, t.ctrl, next, t.kept, t.gram, t.dblk, \
-                     t.score, always, tau_most, single, forced_out, forced_in, limit, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
+                     t.score, always, tau_most, single, given_out, given_in, limit, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
   switch (swap_rows_per_wg(d.d1)) {
     case 32: OSSCAR_SWAP(512, 32); break;
     case 64: OSSCAR_SWAP(1024, 64); break;

@@ -2016,6 +2016,7 @@ __global__ __launch_bounds__(1024) void greedy_pick_kernel(TabDims d, const int3
   __shared__ int s_i[1024];
   __shared__ int chosen[65];
   __shared__ double chosen_v[65];
+  if (side == 2) { side = blockIdx.x; pick += 64 * side; gap += side; }
   if (ctrl->done || ctrl->pause) return;
   const int tid = threadIdx.x;
   for (int round = 0; round <= take; round++) {
@@ -2095,6 +2096,7 @@ __global__ __launch_bounds__(1024) void greedy_pick_reg_kernel(TabDims d, const 
   constexpr int NG = 16 * KMAX, PARTS = 1024 / NG;
   __shared__ double w_v[2][16], g_v[NG], l_v[PICK_CAP], s_bound, s_edge[2];
   __shared__ int w_i[2][16], g_rank[NG], l_i[PICK_CAP], l_rank[PICK_CAP], s_n;
+  if (side == 2) { side = blockIdx.x; pick += 64 * side; gap += side; }
   if (ctrl->done || ctrl->pause) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   double v[KMAX];
@@ -2185,12 +2187,13 @@ __global__ __launch_bounds__(1024) void greedy_pick_reg_kernel(TabDims d, const 
 
 hipError_t launch_greedy_pick(const TabDims& d, const TabPtrs& t, int take, int32_t* pick, float* gap, hipStream_t s, int side) {
   if (take < 1 || take > 64) return hipErrorInvalidValue;
+  const dim3 grid(side == 2 ? 2 : 1);
   if (d.p <= 1024 * 8)
-    hipLaunchKernelGGL(greedy_pick_reg_kernel<8>, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
+    hipLaunchKernelGGL(greedy_pick_reg_kernel<8>, grid, dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
   else if (d.p <= 1024 * 32)
-    hipLaunchKernelGGL(greedy_pick_reg_kernel<32>, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
+    hipLaunchKernelGGL(greedy_pick_reg_kernel<32>, grid, dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
   else
-    hipLaunchKernelGGL(greedy_pick_kernel, dim3(1), dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
+    hipLaunchKernelGGL(greedy_pick_kernel, grid, dim3(1024), 0, s, d, t.kept, t.score, take, pick, gap, t.ctrl, side);
   return hipGetLastError();
 }
 

@@ -641,3 +641,32 @@ def test_selection_of_groups(p):
         kept = kept - {g} | {j}
         moves.append((g, j))
     assert s.osscar_get_tensor(8).cpu().numpy().astype(int).tolist() == sorted(kept)
+
+
+@pytest.mark.parametrize("p,q,block", [(3, 1, 1), (40, 1, 20), (130, 1, 64), (70, 2, 5), (8193, 1, 10)])
+def test_pairs_of_block_moves(p, q, block):
+    """Block moves of rows and of groups, the smallest and the largest block: H = the identity, so that a score is the sum of the group's own squares and
+    stays what it is; a move takes the cheapest kept and the dearest excluded groups, the lowest index of equal ones first, until
+    a move does not pay, which is taken back (the whole block, from its last pair)."""
+    pkg = _pkg()
+    gen = torch.Generator().manual_seed(p)
+    val = torch.randint(1, 6, (p,), generator=gen)
+    G = torch.zeros(p * q, 3)
+    G[0::q, 0] = val.float()
+    kept = set(torch.randperm(p, generator=gen)[:p // 2].tolist())
+    score = [float(v) ** 2 for v in val.tolist()]
+    s = pkg.Solver(p * q, 3, p, q, p // 2, 4, torch.float32, torch.float32, DEV)
+    s.osscar_set_quadratic(torch.eye(p * q).to(DEV), G.to(DEV), 0.0, np.ones(p))
+    s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, sorted(kept))
+    r = s.osscar_block_search(max_iters=4, block=block, rel_tol=0.0)
+    moves = 0
+    for i in range(r["iters"]):
+        out = sorted(kept, key=lambda x: (score[x], x))[:block]
+        inn = sorted(set(range(p)) - kept, key=lambda x: (-score[x], x))[:block]
+        take = min(len(out), len(inn))
+        assert (r["moves"][i][0], r["moves"][i][1]) == (out[:take], inn[:take])
+        if sum(score[x] for x in inn[:take]) > sum(score[x] for x in out[:take]):
+            kept = kept - set(out[:take]) | set(inn[:take])
+            moves += 1
+    assert r["accepted"] == moves and s.osscar_get_tensor(8).cpu().numpy().astype(int).tolist() == sorted(kept)
+    assert abs(r["obj_final"] + sum(score[x] for x in kept)) <= 1e-9 * sum(score)
