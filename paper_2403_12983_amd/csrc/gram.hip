@@ -566,7 +566,7 @@ static hipError_t launch_queued(const uint4* Ap, const uint4* Bp, int pstages, c
   return hipGetLastError();
 }
 
-// Rows of calls that do not fill pack_x (and pack_y) wait there until it is full: a launch per call of 2048 rows reads and writes all of
+// Rows of calls that are shorter than pack_x (and pack_y) wait there until it is full: a launch per call of 2048 rows reads and writes all of
 // the float64 result for them.  Every call's rows begin a window of their own and the windows are no longer than the call by itself
 // would make them, so no float32 sum is longer than in a launch per call.  16384 rows in calls of 2048: 8192 columns 1.23 ms (8 launches of
 // 0.20 before), 2048 columns 0.093 ms (8 of 0.043); the error of H is the same (rms 1.29e-8 and 9.2e-9 of sqrt(H_ii H_jj) either way).
@@ -594,7 +594,14 @@ hipError_t launch_gram_packed(const PackedGram& g, const void* Xc, int64_t n_c, 
   if (g.pack_stages < 2 || g.pack_stages > 256 || g.pack_stages % 2 || !g.tiles.list || g.tiles.entries == 0) return hipErrorInvalidValue;
   if (Yc && (!g.pack_y || !g.tiles_y.list || g.tiles_y.entries == 0)) return hipErrorInvalidValue;
   const int npairs = (g.d1 + 127) / 128, npairs_y = Yc ? (g.m + 127) / 128 : 0, ntiles = npairs * (npairs + 1) / 2;
-  const bool waits = queue_parts(g.pack_stages, g.tiles, g.H64.copies) > 0 && (!Yc || queue_parts(g.pack_stages, g.tiles_y, g.G64.copies) > 0);
+  // A call that fills the buffer by itself is multiplied by itself, its last rows included: they are a small part of it, and its H does not
+  // depend on the calls around it.
+  const bool whole = n_c >= (int64_t)g.pack_stages * GBK;
+  if (whole) {
+    const hipError_t e = launch_gram_queue(g, s);
+    if (e != hipSuccess) return e;
+  }
+  const bool waits = !whole && queue_parts(g.pack_stages, g.tiles, g.H64.copies) > 0 && (!Yc || queue_parts(g.pack_stages, g.tiles_y, g.G64.copies) > 0);
   for (int64_t r0 = 0; r0 < n_c;) {
     const int64_t nr = std::min<int64_t>((int64_t)(g.pack_stages - q.stages) * GBK, n_c - r0);
     const int nst = (int)((nr + GBK - 1) / GBK), used = (nst + 1) / 2 * 2;      // an even number of stages: the wide kernel's windows

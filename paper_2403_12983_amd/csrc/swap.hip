@@ -14,7 +14,7 @@
 // Bound by latency: three dependent round trips to memory (records, pivots' rows, launch to launch), five barriers and three products
 // of a 128 x 128 matrix with two vectors; at 28672 rows also by what the rows read (15 MB of products and 7 MB of C0 on average).  As four
 // launches, the first of them one workgroup, with ZT (128 x m) updated and read by every swap, a swap took 25 us at 8192 x 2048 (flushes
-// and waits apart) and 31 at 28672 x 7168; in one launch 13 and 19.
+// and waits apart) and 31 at 28672 x 7168; in one launch 11 and 21.
 #include "internal.h"
 #include "lazy_device.h"
 #include "wave.h"
