@@ -339,7 +339,8 @@ def main():
                               "ms_per_swap": ms_swap, "swap_launch_ms": 1e3 * upd_n,
                               "flushes_total_ms": flush_ms, "bytes_per_swap_eager": bytes_swap_alg,
                               "last_layer_counts": info.get("counters")} if lazy else
-                             {"note": "in-place search: every swap is one rank-2q pass over the tableau (N: lower triangle, Z)",
+                             {"note": "in-place search: every swap is one rank-2q pass over the tableau (N: lower triangle, Z; groups of more "
+                                      "than one row: one launch, all of it under update_N_ms)",
                               "ms_per_swap": ms_swap, "update_N_ms": 1e3 * upd_n, "update_Z_ms": 1e3 * upd_z,
                               "bytes_per_swap": bytes_swap_alg,
                               "update_GBps": bytes_swap_alg / max(upd_n + upd_z, 1e-12) / 1e9,
