@@ -1130,6 +1130,7 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
       st = read_kept(c);
       if (st != OSSCAR_OK) return st;
       c->kr = kept_now * q; c->cr = c->d1 - c->kr;
+      if (use_lazy) HIPCHK(c, run.settle());      // the rebuilt scores leave their verdict in c->ctrl
       st = build_state(c, &obj);
       if (st != OSSCAR_OK) return st;
       HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(run.t.ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
@@ -1242,6 +1243,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
         HIPCHK(c, hipEventRecord(r0, s));
         st = read_kept(c);
         if (st != OSSCAR_OK) return st;
+        HIPCHK(c, run.settle());                // the rebuilt scores leave their verdict (notpd) in c->ctrl
         double obj = 0;
         st = build_state(c, &obj);
         if (st != OSSCAR_OK) return st;

@@ -670,3 +670,43 @@ def test_pairs_of_block_moves(p, q, block):
             moves += 1
     assert r["accepted"] == moves and s.osscar_get_tensor(8).cpu().numpy().astype(int).tolist() == sorted(kept)
     assert abs(r["obj_final"] + sum(score[x] for x in kept)) <= 1e-9 * sum(score)
+
+
+@pytest.mark.parametrize("before", [1, 2, 3])
+def test_rebuilt_state_that_is_not_definite_is_an_error(before):
+    """H with two equal rows a, b: once a is kept, the Schur complement of b is rounding, of either sign.  a enters by the `before`-th
+    swap, after which the state is rebuilt.  Whether the rebuilt one is positive shows in a state built from that kept set at once: the score of b is
+    its squared norm over it, or over one where it is not.  Where it is not the search is an error, whatever the number of launches before."""
+    pkg = _pkg()
+    p, k, m, a, b = 40, 20, 3, 30, 35
+    wrong = 0
+    for seed in range(16):
+        g = torch.Generator().manual_seed(seed)
+        X = torch.randn(400, p, generator=g, dtype=torch.float64)
+        X[:, b] = X[:, a]
+        H = (X.T @ X).float()
+        H[b], H[:, b] = H[a], H[:, a]
+        H[b, b] = H[a, a]
+        G = torch.randn(p, m, generator=g)
+        for i in range(before):
+            G[20 + i] = 1000.0 / 2.0 ** i                   # enter first, in this order
+        G[20 + before - 1] = 1.0
+        G[a] = G[b] = 1000.0 / 2.0 ** (before - 1)
+        s = pkg.Solver(p, m, p, 1, k, 8, torch.float32, torch.float32, DEV)
+        s.osscar_set_quadratic(H.to(DEV), G.to(DEV), 1e6, np.ones(p))
+        s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, list(range(k)))
+        r = s.osscar_local_search(before, 0.0, pkg.OSSCAR_SEARCH_ALWAYS_ACCEPT)
+        assert r["trace_in"].tolist() == [20 + i for i in range(before - 1)] + [a]
+        kept = sorted(set(range(k)) - set(r["trace_out"].tolist()) | set(r["trace_in"].tolist()))
+        s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, kept)
+        gain = float(s.osscar_get_tensor(7)[b])
+        row = s.osscar_get_tensor(5)[sorted(set(range(p)) - set(kept)).index(b)].double()
+        positive = gain > 2.0 * float((row * row).sum())    # (the complement is far below one)
+        s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, list(range(k)))
+        if not positive:
+            wrong += 1
+            with pytest.raises(pkg.OsscarError) as e:
+                s.osscar_local_search(before + 1, 0.0, pkg.OSSCAR_SEARCH_ALWAYS_ACCEPT, refresh_every=before)
+            assert e.value.status == 3
+        s.close()
+    assert wrong > 0
