@@ -1005,18 +1005,19 @@ struct SwapRun {
   int tau_most = 0;              // pending pivots after the launches so far, at most
   SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) {}
   hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode); }
-  hipError_t swap(int always, int limit, const int32_t* g = nullptr, const int32_t* j = nullptr, const int32_t* single = nullptr) {
+  hipError_t swap(int always, int limit, const SwapList& list = SwapList()) {
     SearchCtrl* next = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
-    const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, single, g, j);
+    const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, list);
     t.ctrl = next;
     std::swap(L.Minv, L.Minv2); std::swap(L.rec, L.rec2);
     tau_most = std::min(tau_most + 2, LAZY_TM);
     return e;
   }
-  // removal of the row *single, iteration `iter` of the call: the second launch does it if the first had to fetch the row's products
-  hipError_t remove(const int32_t* single, int iter) {
-    const hipError_t e = swap(1, iter, nullptr, nullptr, single);
-    return e != hipSuccess ? e : swap(1, iter, nullptr, nullptr, single);
+  // removal of n rows, after which `iters` iterations of the call have run: a launch each and one for its products
+  hipError_t remove(const int32_t* rows, int n, int iters) {
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < 2 * n && e == hipSuccess; i++) e = swap(1, iters, SwapList{rows, nullptr, n, 1});
+    return e;
   }
   hipError_t flush() { tau_most = 0; return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c)); }
   hipError_t settle() {
@@ -1070,8 +1071,11 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
   const bool use_block = use_lazy && la_mode == 1;
   int kept_now = p, iter = 0, since_refresh = 0, pending = 0, expected = 0;
   std::vector<int> takes;
-  auto step = [&](int i, int iter_no) -> hipError_t {      // removal of the i-th pick, the iter_no-th of the call
-    return use_lazy ? run.remove(c->g_pick + i, iter_no) : launch_search_iteration(d, t, -1, -1, 1, s, nullptr, c->g_pick + i);
+  auto one_by_one = [&](int from, int to, int iters) -> hipError_t {      // picks [from, to), the call's last ones so far
+    if (use_lazy) return run.remove(c->g_pick + from, to - from, iters);
+    hipError_t e = hipSuccess;
+    for (int i = from; i < to && e == hipSuccess; i++) e = launch_search_iteration(d, t, -1, -1, 1, s, nullptr, c->g_pick + i);
+    return e;
   };
   while (kept_now > k) {
     takes.clear();
@@ -1091,7 +1095,7 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
             run.tau_most = std::min(run.tau_most + LAZY_BT, LAZY_TM);
           }
         } else {
-          for (int i = 0; i < take; i++) HIPCHK(c, step(i, expected + batch + i + 1));
+          HIPCHK(c, one_by_one(0, take, expected + batch + take));
         }
       }
       takes.push_back(take); batch += take; kept_b -= take;
@@ -1112,7 +1116,7 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
       while (acc + takes[it_idx] <= done) { acc += takes[it_idx]; it_idx++; }
       const int off = done - acc;                       // removals of iteration it_idx already applied
       HIPCHK(c, run.flush());       // also clears pause
-      for (int i = off; i < takes[it_idx]; i++) HIPCHK(c, step(i, h.iters + i - off + 1));   // its pick list is still on the device
+      HIPCHK(c, one_by_one(off, takes[it_idx], h.iters + takes[it_idx] - off));   // its pick list is still on the device
       if (use_block) HIPCHK(c, launch_removal_lists(d, run.t, run.L, s, false));
       pending = takes[it_idx] - off;
       batch = acc + takes[it_idx];
@@ -1346,17 +1350,24 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   int pending = 0, done_pairs = 0, blocks = 0, accepted = 0;
   // applies the picked pairs one after the other (each unconditionally; back: each the other way round, from the last one);
   // resumes after a flush when the kernels had to stop.  The one-launch swaps read the pairs where the pick left them, so that
-  // the host waits once per move; the picks are in pinned memory by the time it has waited.
+  // the host waits once per move; the picks are in pinned memory by the time it has waited.  A launch that fetches a pair's products
+  // makes no swap: as many more are enqueued as the last move had of those (a pair that goes back has just left the rows that are
+  // computed ahead, and without these every pair fetches); they are idle if there are fewer now.
+  int fetched = la_mode == 2 ? take : 0;
   auto run_pairs = [&](bool back) -> osscar_status {
     auto out = [&](int r) { return back ? 64 + take - 1 - r : r; };
     auto inn = [&](int r) { return back ? take - 1 - r : 64 + r; };
-    int idx = 0;
-    int misses = h.misses;
+    const SwapList list{c->g_pick + out(0), c->g_pick + inn(0), take, back ? -1 : 1};
+    const int last = done_pairs + take;
+    int idx = 0, extra = back ? take : fetched;
+    fetched = 0;
     while (idx < take) {
-      for (int r = idx; r < take; r++) {
-        if (use_lazy) HIPCHK(c, run.swap(1, done_pairs + r - idx + 1, c->g_pick + out(r), c->g_pick + inn(r)));
-        else HIPCHK(c, launch_search_iteration(d, t, c->snap->pick[out(r)], c->snap->pick[inn(r)], 1, s));
-      }
+      // where every pair is expected to fetch, the spare slots end the pass (the pair behind the last one that fits makes it stop)
+      const int fits = extra < take - idx ? take - idx : std::min(take - idx, (LAZY_NS - h.spare) / 2);
+      const int launches = fits + std::min(extra, fits) + (fits < take - idx ? 1 : 0);
+      if (use_lazy) for (int r = 0; r < launches; r++) HIPCHK(c, run.swap(1, last, list));
+      else for (int r = idx; r < take; r++) HIPCHK(c, launch_search_iteration(d, t, c->snap->pick[out(r)], c->snap->pick[inn(r)], 1, s));
+      const int misses = h.misses;
       osscar_status q = read_ctrl(c, &h, run.t.ctrl);
       if (q != OSSCAR_OK) return q;
       run.tau_most = h.tau;
@@ -1364,18 +1375,19 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
       const int did = h.iters - done_pairs;
       if (did < 0 || did > take - idx) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search lost count of its pairs");
       done_pairs += did; idx += did; pending += 2 * did;
+      extra = std::min(h.misses - misses, launches - did);      // of its launches at most so many fetched
+      fetched += extra;
       if (idx < take) {
-        if (!use_lazy || (!h.pause && h.misses == misses)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
-        misses = h.misses;
-        if (!h.pause) continue;                // a pair's launch fetched the products of its pivots: the pairs from it on again
+        if (!use_lazy || (!h.pause && extra == 0 && did == 0)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
+        if (!h.pause) continue;
         HIPCHK(c, run.flush());
-        pending = 0;
+        pending = h.spare = 0;
       }
     }
     return OSSCAR_OK;
   };
   while (take > 0 && blocks < max_iters) {
-    if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = 0; }
+    if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = h.spare = 0; }
     HIPCHK(c, launch_greedy_pick(d, run.t, take, c->g_pick, c->g_gap, s, 2));
     HIPCHK(c, hipMemcpyAsync(c->snap->pick, c->g_pick, sizeof c->snap->pick, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipMemcpyAsync(c->snap->gap, c->g_gap, sizeof c->snap->gap, hipMemcpyDeviceToHost, s));
@@ -1395,7 +1407,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
     blocks++;
     if (!ok) {
       // take the move back: the same pairs in reverse (the pending pivots must reach the tableau first)
-      if (use_lazy && pending > 0) { HIPCHK(c, run.flush()); pending = 0; }
+      if (use_lazy && pending > 0) { HIPCHK(c, run.flush()); pending = h.spare = 0; }
       st = run_pairs(true);
       if (st != OSSCAR_OK) return st;
       h.obj = obj_before;

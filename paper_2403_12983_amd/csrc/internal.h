@@ -280,10 +280,13 @@ struct LazyPtrs {
 // mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NC/2 cheapest removals + LAZY_NC/2 largest gains,
 // 1 = LAZY_NC cheapest removals (removal-only loops), 2 = none (every pivot then costs a pass over Z0)
 hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0);
+// Pairs on the device that swaps take in turn, out[r * step] and in[r * step] for r < n <= 64; in == nullptr: rows out[r * step] to remove
+struct SwapList { const int32_t* out = nullptr; const int32_t* in = nullptr; int n = 0, step = 1; };
 // swap.hip: one swap in one launch, from the control block t.ctrl, L.Minv and L.rec to *next, L.Minv2 and L.rec2 (the caller exchanges
-// them after every launch); tau_most: at most this many pivots are pending
+// them after every launch); at most `limit` iterations will have run, the last l.n of them the list's; tau_most: at most this many pivots
+// are pending.  A pivot whose products have not been computed ahead takes a launch of its own, which fetches them.
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int tau_most,
-                            hipStream_t s, const int32_t* single = nullptr, const int32_t* given_out = nullptr, const int32_t* given_in = nullptr);
+                            hipStream_t s, const SwapList& l = SwapList());
 int swap_record_count(int64_t d1);
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);

@@ -24,6 +24,7 @@ namespace osscar {
 
 constexpr int KLD = LAZY_NC + LAZY_NS;      // row length of K
 constexpr int PENDING = 1 << 30;            // flag in a record's slot: the row is a pending pivot
+constexpr int LIST_MOST = 64;               // pairs (rows) of a list: one per lane
 
 // p[i] with a byte offset of 32 bits (C0: 65536 rows of 512 bytes; the products: 320 rows of 65536 doubles)
 template <typename T>
@@ -132,14 +133,17 @@ __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* _
 }
 
 // NT threads, RPW rows per workgroup, NT / RPW lanes per row.  cin: control block before this launch, cout: after it.
-// limit: iterations to have run after this launch at most; beyond it a launch does nothing, and neither does a given pair or row whose
-// predecessor has not run (its launch fetched products).  single != nullptr: removal of the one row *single (Case 1 alone); given_g,
-// given_j != nullptr: the pair (*given_g, *given_j) if *given_g is a row (otherwise the pick, as if there were none).
+// limit: iterations to have run after this launch at most; beyond it a launch does nothing.  list_n > 0: the last list_n of them take the
+// pairs (list_g[r * list_step], list_j[r * list_step]), r = 0, 1, ... (the pick, where an entry of list_g is no row), list_j == nullptr:
+// remove the rows of list_g (Case 1 alone).  The launch finds its place in the list by the iterations that have run, so a pair whose
+// launch had to fetch products is the next launch's: with a place fixed when it is enqueued, the launches behind a fetch were idle and
+// were enqueued again after a wait (layer of 700 rows in moves of 32 pairs: 15.3 ms, so 6.6).  A pair that is not (kept, not
+// kept) has no definite pivots and is refused as such.
 template <int NT, int RPW>
 __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* __restrict__ N0, const float* __restrict__ Z0, int d1, int m,
                                                         const SearchCtrl* __restrict__ cin, SearchCtrl* __restrict__ cout, int32_t* __restrict__ kept,
                                                         double* __restrict__ rho, double* __restrict__ diag, double* __restrict__ score, int always, int tau_most,
-                                                        const int32_t* __restrict__ single, const int32_t* __restrict__ given_g, const int32_t* __restrict__ given_j, int limit, int32_t* __restrict__ trace_out,
+                                                        const int32_t* __restrict__ list_g, const int32_t* __restrict__ list_j, int list_n, int list_step, int limit, int32_t* __restrict__ trace_out,
                                                         int32_t* __restrict__ trace_in, float* __restrict__ trace_gap, double* __restrict__ trace_obj) {
   constexpr int TM = LAZY_TM, W = NT / 64, H = NT / 2;
   constexpr int TPR = NT / TM, MU = TM / (2 * TPR);             // threads per row of M^-1, pairs of columns per thread
@@ -164,6 +168,9 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   double v1 = rp->best[side], v2 = rp->second[side];
   int i1 = rp->row[side], sl1 = rp->slot[side];
   const int ts = tid < TM ? L.tslot[tid] : 0;
+  const bool single = list_n > 0 && !list_j;
+  const int at = list_n > 0 ? min(lane, list_n - 1) * list_step : 0;      // the whole list (a row each lane): which entry is known later
+  const int lg = (list_n > 0 ? list_g : L.cand)[at], lj = (list_n > 0 && list_j ? list_j : L.cand)[at];
   const int mr = tid / TPR, mq = tid % TPR;
   const bool mine = __builtin_amdgcn_readfirstlane(mr) < th;      // 64 / TPR rows a wave: all of them or none
   double2 mv[MU], kv[KT_LDS ? 1 : MU];
@@ -197,8 +204,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
       L.rec2[wg] = r;
     }
   };
-  const int forced_g = given_g ? *given_g : -1, forced_j = given_j ? *given_j : -1;
-  const bool idle = (cin->done | cin->pause) != 0 || cin->iters >= limit || ((forced_g >= 0 || single) && cin->iters < limit - 1);
+  const bool idle = (cin->done | cin->pause) != 0 || cin->iters >= limit;
   // ---- pick: lanes of the first half of the workgroup hold the leaving side's records, the others the entering side's
   if (rt >= nwg) { v1 = INFINITY; v2 = INFINITY; i1 = -1; sl1 = -1; }
   double wv = v1;
@@ -230,8 +236,10 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   const uint64_t has_g = __ballot(lane < W / 2 && qi0 == g), has_j = __ballot(lane >= W / 2 && lane < W && qi0 == j);
   int sg = __builtin_amdgcn_readlane(qs0, has_g ? (int)__builtin_ctzll(has_g) : 0), sj = __builtin_amdgcn_readlane(qs0, has_j ? (int)__builtin_ctzll(has_j) : W / 2);
   const int pick_g = g, pick_j = j;
+  const int entry = cin->iters - (limit - list_n), entry_c = __builtin_amdgcn_readfirstlane(min(max(entry, 0), LIST_MOST - 1));
+  const int forced_g = (list_n > 0 && entry >= 0) ? __builtin_amdgcn_readlane(lg, entry_c) : -1;
   if (single || forced_g >= 0) {
-    g = single ? *single : forced_g; j = single ? g : forced_j;
+    g = forced_g; j = single ? g : __builtin_amdgcn_readlane(lj, entry_c);
     if (g < 0 || g >= d1 || j < 0 || j >= d1) { g = -1; j = -1; }
     else {
       // another workgroup may already have entered the row as this launch's pivot (pos = tau) or taken it a slot (from
@@ -488,11 +496,12 @@ static int swap_rows_per_wg(int d1) { return d1 <= 8192 ? 32 : d1 <= 16384 ? 64 
 int swap_record_count(int64_t d1) { const int r = swap_rows_per_wg((int)d1); return (int)((d1 + r - 1) / r); }
 
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always, int limit, int tau_most,
-                            hipStream_t s, const int32_t* single, const int32_t* given_out, const int32_t* given_in) {
+                            hipStream_t s, const SwapList& l) {
+  if (l.n < 0 || l.n > LIST_MOST || (l.n > 0 && !l.out)) return hipErrorInvalidValue;
   const int nwg = swap_record_count(d.d1);
 #define OSSCAR_SWAP(NT, RPW)                                                                                                         \
   hipLaunchKernelGGL((lazy_swap_kernel<NT, RPW>), dim3(nwg), dim3(NT), 0, s, L, t.N, t.Z, d.d1, d.m, t.ctrl, next, t.kept, t.gram, t.dblk, \
-                     t.score, always, tau_most, single, given_out, given_in, limit, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
+                     t.score, always, tau_most, l.out, l.in, l.n, l.step, limit, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
   switch (swap_rows_per_wg(d.d1)) {
     case 32: OSSCAR_SWAP(512, 32); break;
     case 64: OSSCAR_SWAP(1024, 64); break;

@@ -710,3 +710,37 @@ def test_rebuilt_state_that_is_not_definite_is_an_error(before):
             assert e.value.status == 3
         s.close()
     assert wrong > 0
+
+
+@pytest.mark.parametrize("p,m,block", [(300, 20, 64), (300, 20, 17), (700, 192, 32), (1030, 8, 10)])
+def test_block_moves_whose_products_are_not_computed_ahead(p, m, block):
+    """Moves in which every pair (no look-ahead) or most pairs (few rows are looked ahead in a small layer) have to fetch their products:
+    the same moves as in place, to 1e-6 of the objective (float32 storage), and no more than about two launches a pair.  Launches enqueued
+    again after every fetch took up to 6.5 times as long as four launches a pair here and are now as long or shorter; the search in place takes
+    about as long, and the bar is twice its time."""
+    pkg = _pkg()
+    g = torch.Generator().manual_seed(p)
+    X = (torch.randn(2 * p + 64, p, generator=g) * torch.exp(0.5 * torch.randn(p, generator=g))).to(DEV)
+    W = (torch.randn(p, m, generator=g) / p ** 0.5).to(DEV)
+    s = pkg.Solver(p, m, p, 1, p // 2, 1, torch.float32, torch.float32, DEV)
+    s.osscar_gram(X, True, W, 0.0, 5e-2)
+    runs = []
+    for flags in (pkg.OSSCAR_SEARCH_EAGER, 0, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD):
+        ms = []
+        for _ in range(3):
+            s.osscar_init_support()
+            r = s.osscar_block_search(3, block, 0.0, flags | pkg.OSSCAR_SEARCH_ALWAYS_ACCEPT)
+            ms.append(s.osscar_get_timers()[3])
+        s.osscar_init_support()
+        back = s.osscar_block_search(3, block, 0.9, flags)      # turned down: taken back, the last pair first
+        assert r["iters"] == r["accepted"] == 3 and back["iters"] == 1 and back["accepted"] == 0
+        assert back["obj_final"] == back["obj_initial"]
+        runs.append((r, min(ms), s.osscar_backsolve()))
+    s.close()
+    (e, te, (We, Se, _)), others = runs[0], runs[1:]
+    for r, t, (Wr, Sr, _) in others:
+        assert r["moves"] == e["moves"]
+        assert np.allclose(r["trace_obj"], e["trace_obj"], rtol=1e-6, atol=0)
+        assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
+        print(f"p {p} block {block}: in place {te:.2f} ms, delayed {t:.2f} ms")
+        assert t <= 2.0 * te
