@@ -549,16 +549,18 @@ static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int pstages, i
   return hipGetLastError();
 }
 // Parts that the contraction of a queued product is cut into, each with its copy of the result: one workgroup per compute unit, and
-// at least GW_MIN_PART stages each; 0: too few workgroups even so (GW_MIN_TILES)
+// at least GW_MIN_PART stages each
 static int queue_parts(int nstages, const PackedTiles& t, int copies) {
-  if (!t.tall || t.tall_entries == 0) return 0;
-  const int parts = std::max(1, std::min({copies, nstages / GW_MIN_PART, (int)((256 + t.tall_entries - 1) / t.tall_entries)}));
-  return t.tall_entries * parts >= GW_MIN_TILES ? parts : 0;
+  return std::max(1, std::min({copies, nstages / GW_MIN_PART, (int)((256 + t.tall_entries - 1) / t.tall_entries)}));
+}
+// half of the compute units have a workgroup of a queued product
+static bool queue_fills(int nstages, const PackedTiles& t, int copies) {
+  return t.tall && t.tall_entries > 0 && t.tall_entries * queue_parts(nstages, t, copies) >= GW_MIN_TILES;
 }
 static hipError_t launch_queued(const uint4* Ap, const uint4* Bp, int pstages, const PackQueue& q, int window, int rows_out, int cols_out,
                                 const PackedAcc& acc, const PackedTiles& t, int symmetric, hipStream_t s) {
   const int64_t elems = (int64_t)rows_out * cols_out;
-  const int most = std::max(1, queue_parts(q.stages, t, acc.copies)), per = ((q.stages + most - 1) / most + 1) / 2 * 2, parts = (q.stages + per - 1) / per;
+  const int most = queue_parts(q.stages, t, acc.copies), per = ((q.stages + most - 1) / most + 1) / 2 * 2, parts = (q.stages + per - 1) / per;
   clear_copies(acc, parts, elems, s);
   hipLaunchKernelGGL(gram_wide_kernel<2>, dim3((unsigned)t.tall_entries, (unsigned)parts), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
                      (cols_out + 127) / 128 * 2, pstages, q.stages, rows_out, cols_out, cols_out, acc.out, elems, t.tall, per, 2 * window, 2 * per,
@@ -575,15 +577,27 @@ hipError_t launch_gram_queue(const PackedGram& g, hipStream_t s) {
   if (q.stages == 0) return hipSuccess;
   const int npairs = (g.d1 + 127) / 128, npairs_y = g.pack_y ? (g.m + 127) / 128 : 0;
   const uint4 *Xp = reinterpret_cast<const uint4*>(g.pack_x), *Yp = reinterpret_cast<const uint4*>(g.pack_y);
-  const bool timed = g.ev && q.ev_used < g.ev_pairs, several = q.calls > 1;
-  if (timed) hipEventRecord(g.ev[2 * q.ev_used], s);
-  hipError_t e = several ? launch_queued(Xp, Xp, g.pack_stages, q, q.window, g.d1, g.d1, g.H64, g.tiles, 1, s)
-                         : launch_packed(Xp, Xp, g.pack_stages, q.last, g.d1, g.d1, g.H64, g.tiles, npairs * (npairs + 1) / 2, 16, 1, s);
-  if (e != hipSuccess) return e;
-  if (timed) { hipEventRecord(g.ev[2 * q.ev_used + 1], s); q.ev_used++; q.ev_rows += q.rows; }
-  if (g.pack_y)
-    e = several ? launch_queued(Xp, Yp, g.pack_stages, q, q.window_y, g.d1, g.m, g.G64, g.tiles_y, 0, s)
-                : launch_packed(Xp, Yp, g.pack_stages, q.last, g.d1, g.m, g.G64, g.tiles_y, npairs * npairs_y, 16, 0, s);
+  // Rows that wait when the layer ends may fill fewer workgroups.  Calls of up to GW_MIN_PART stages are still multiplied together, longer
+  // ones each in a launch of its own, cut into as many ranges as it can be (512 columns, two calls of 6000 rows, whole quadratic form:
+  // 0.40 ms in one launch of eight workgroups, 0.29 so; 1280 columns, three calls of 1024 rows: 0.35 ms together, 0.38 apart).
+  auto ends = [&](int stage) { const int pair = stage / 2 - 1; return ((q.ends[pair >> 6] >> (pair & 63)) & 1) != 0; };      // stage: even, above 0
+  auto product = [&](const uint4* Bp, int window, int cols, const PackedAcc& acc, const PackedTiles& t, int ntiles, int symmetric) -> hipError_t {
+    const bool together = q.calls > 1 && (q.stages <= q.calls * GW_MIN_PART || queue_fills(q.stages, t, acc.copies));
+    for (int st = 0, end; st < q.stages; st = end) {
+      for (end = together ? q.stages : st + 2; end < q.stages && !ends(end);) end += 2;
+      const int n = q.calls > 1 ? end - st : q.last;
+      const int64_t at = (int64_t)st * PK_SLOTS;
+      const bool timed = symmetric && g.ev && q.ev_used < g.ev_pairs;
+      if (timed) hipEventRecord(g.ev[2 * q.ev_used], s);
+      const hipError_t e = together ? launch_queued(Xp, Bp, g.pack_stages, q, window, g.d1, cols, acc, t, symmetric, s)
+                                    : launch_packed(Xp + at, Bp + at, g.pack_stages, n, g.d1, cols, acc, t, ntiles, 16, symmetric, s);
+      if (e != hipSuccess) return e;
+      if (timed) { hipEventRecord(g.ev[2 * q.ev_used + 1], s); q.ev_used++; q.ev_rows += (together || q.calls == 1) ? q.rows : std::min<int64_t>(n * GBK, q.rows); }
+    }
+    return hipSuccess;
+  };
+  hipError_t e = product(Xp, q.window, g.d1, g.H64, g.tiles, npairs * (npairs + 1) / 2, 1);
+  if (e == hipSuccess && g.pack_y) e = product(Yp, q.window_y, g.m, g.G64, g.tiles_y, npairs * npairs_y, 0);
   q.clear();
   return e;
 }
@@ -601,7 +615,7 @@ hipError_t launch_gram_packed(const PackedGram& g, const void* Xc, int64_t n_c, 
     const hipError_t e = launch_gram_queue(g, s);
     if (e != hipSuccess) return e;
   }
-  const bool waits = !whole && queue_parts(g.pack_stages, g.tiles, g.H64.copies) > 0 && (!Yc || queue_parts(g.pack_stages, g.tiles_y, g.G64.copies) > 0);
+  const bool waits = !whole && queue_fills(g.pack_stages, g.tiles, g.H64.copies) && (!Yc || queue_fills(g.pack_stages, g.tiles_y, g.G64.copies));
   for (int64_t r0 = 0; r0 < n_c;) {
     const int64_t nr = std::min<int64_t>((int64_t)(g.pack_stages - q.stages) * GBK, n_c - r0);
     const int nst = (int)((nr + GBK - 1) / GBK), used = (nst + 1) / 2 * 2;      // an even number of stages: the wide kernel's windows

@@ -744,3 +744,36 @@ def test_block_moves_whose_products_are_not_computed_ahead(p, m, block):
         assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
         print(f"p {p} block {block}: in place {te:.2f} ms, delayed {t:.2f} ms")
         assert t <= 2.0 * te
+
+
+def _exact_gram(d1, m, chunks, target):
+    """H and G of calls of `chunks` rows of small whole numbers (every sum exact in float32), the timers, the same in float64"""
+    n = sum(chunks)
+    g = torch.Generator(device=DEV).manual_seed(d1 + n)
+    X = torch.randint(-3, 4, (n, d1), generator=g, device=DEV).bfloat16()
+    Y = torch.randint(-3, 4, (n, m), generator=g, device=DEV).bfloat16()
+    W = torch.zeros(d1, m, dtype=torch.bfloat16, device=DEV)
+    s = _pkg().Solver(d1, m, d1, 1, 1, 1, torch.bfloat16, torch.bfloat16, DEV, target_output=target)
+    r0 = 0
+    for i, c in enumerate(chunks):
+        args = (True, W, 0.0, 0.0) if i + 1 == len(chunks) else (False,)
+        s.osscar_gram_target(X[r0:r0 + c], Y[r0:r0 + c], *args) if target else s.osscar_gram(X[r0:r0 + c], *args)
+        r0 += c
+    H, G, t = s.osscar_get_tensor(0).double(), s.osscar_get_tensor(1).double(), s.osscar_get_timers()
+    s.close()
+    Xd = X.double()
+    assert torch.equal(H, Xd.T @ Xd) and (not target or torch.equal(G, Xd.T @ Y.double()))
+    return t
+
+
+@pytest.mark.parametrize("d1,m,chunks,launches", [(512, 64, [6000, 6000], 2), (1000, 72, [2100, 3000, 1], 3), (520, 8, [2048, 2048, 65, 700], 4),
+                                                  (1000, 72, [1024, 1000, 900], 1), (2048, 512, [2048, 3000], 1)])
+def test_rows_that_wait_when_the_layer_ends(d1, m, chunks, launches):
+    """Rows of several calls that do not fill the buffer: together where they keep half of the compute units busy or the calls are short, else a
+    launch per call.  Sums of small whole numbers are exact either way.  (512 columns, two calls of 6000 rows: eight workgroups took the
+    whole contraction, three times as long as the two launches.)"""
+    t = _exact_gram(d1, m, chunks, False)
+    assert t[14] == launches and sum(chunks) <= t[15] < sum(chunks) + 128 * len(chunks)
+    if launches == 2:
+        assert t[13] * t[14] <= 2.0 * min(u[13] * u[14] for u in [_exact_gram(d1, m, [sum(chunks)], False) for _ in range(3)])
+    _exact_gram(d1, m, chunks, True)
