@@ -515,7 +515,7 @@ __global__ void fill_zero_f64_kernel(double* __restrict__ p, int64_t n) {
 // Rows of several calls (launch_gram_queue): 256 x 128 tiles with float64 windows, Out touched once.
 // Either way an element of a copy receives its additions from one thread, in order, so the result does not depend on scheduling.
 constexpr size_t GW_MIN_TILES = 128;
-constexpr int GW_MIN_STAGES = 32, GW_MIN_PART = 16;
+constexpr int GW_MIN_STAGES = 32, GW_MIN_PART = 16, LONG_STAGES = 72;
 // A launch of the 128 x 128 kernel with fewer workgroups than this adds with atomics, which nobody waits for: 64 columns, 64 rows 7.7 us
 // against 11.3 with loads and stores, 1000 columns, 512 rows (36 workgroups) 13.7 and 18.7; 1000 columns, 2048 rows (144) 27.9 both;
 // 2048 columns, 2048 rows (272) 67.6 and 51.3.  Either way one thread adds to an element, in order.
@@ -531,11 +531,15 @@ static void clear_copies(const PackedAcc& acc, int parts, int64_t elems, hipStre
   hipLaunchKernelGGL(fill_zero_f64_kernel, dim3(2048), dim3(256), 0, s, acc.out + *acc.cleared * elems, (parts - *acc.cleared) * elems);
   *acc.cleared = parts;
 }
+static bool takes_wide(const PackedTiles& t, int nstages, int ntiles, int window) {
+  const int range = packed_range(nstages, ntiles);
+  return t.wide && t.wide_entries >= GW_MIN_TILES && nstages >= GW_MIN_STAGES && (range >= nstages || range % window == 0);
+}
 static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int pstages, int nstages, int rows_out, int cols_out, const PackedAcc& acc,
                                 const PackedTiles& t, int ntiles, int window, int symmetric, hipStream_t s) {
   const int range = packed_range(nstages, ntiles), ranges = (nstages + range - 1) / range;
   const int64_t elems = (int64_t)rows_out * cols_out;
-  if (t.wide && t.wide_entries >= GW_MIN_TILES && nstages >= GW_MIN_STAGES && (ranges == 1 || range % window == 0)) {
+  if (takes_wide(t, nstages, ntiles, window)) {
     hipLaunchKernelGGL(gram_wide_kernel<3>, dim3((unsigned)t.wide_entries), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
                        (cols_out + 127) / 128 * 2, pstages, nstages, rows_out, cols_out, cols_out, acc.out, elems, t.wide, nstages, 2 * window,
                        2 * range, 0ull, 0ull, symmetric);
@@ -609,8 +613,13 @@ hipError_t launch_gram_packed(const PackedGram& g, const void* Xc, int64_t n_c, 
   if (Yc && (!g.pack_y || !g.tiles_y.list || g.tiles_y.entries == 0)) return hipErrorInvalidValue;
   const int npairs = (g.d1 + 127) / 128, npairs_y = Yc ? (g.m + 127) / 128 : 0, ntiles = npairs * (npairs + 1) / 2;
   // A call that fills the buffer by itself is multiplied by itself, its last rows included: they are a small part of it, and its H does not
-  // depend on the calls around it.
-  const bool whole = n_c >= (int64_t)g.pack_stages * GBK;
+  // depend on the calls around it.  So is one of more than LONG_STAGES where the wide tiles fill four fifths of their rounds of the
+  // compute units: from there on the wide kernel's higher rate is more than the pass over the result that waiting would save (whole
+  // quadratic form, rows that wait / calls by themselves: 8192 columns, two calls of 4608 rows 2.06 / 2.01 ms, of 8192 rows 2.64 / 2.45, three of
+  // 12000 rows 4.34 / 3.78; 28672 columns, three of 12000 41.6 / 38.5, of 4096 20.1 / 20.5; 5120 columns, 287 tiles, two of 8192 rows 1.18 / 1.43).
+  const bool whole = n_c >= (int64_t)g.pack_stages * GBK ||
+                     (n_c > (int64_t)LONG_STAGES * GBK && g.tiles.wide_entries * 5 >= (g.tiles.wide_entries + 255) / 256 * 256 * 4 &&
+                      takes_wide(g.tiles, (int)((n_c + GBK - 1) / GBK), ntiles, 16));
   if (whole) {
     const hipError_t e = launch_gram_queue(g, s);
     if (e != hipSuccess) return e;

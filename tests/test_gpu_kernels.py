@@ -777,3 +777,12 @@ def test_rows_that_wait_when_the_layer_ends(d1, m, chunks, launches):
     if launches == 2:
         assert t[13] * t[14] <= 2.0 * min(u[13] * u[14] for u in [_exact_gram(d1, m, [sum(chunks)], False) for _ in range(3)])
     _exact_gram(d1, m, chunks, True)
+
+
+@pytest.mark.parametrize("d1,chunks,launches,rows", [(8192, [9000, 9000], 1, 9000), (8192, [300, 5000], 2, 5300), (8192, [4608, 4608], 1, 9216),
+                                                     (5120, [9000, 9000], 2, 18000)])
+def test_long_calls_are_multiplied_by_themselves(d1, chunks, launches, rows):
+    """Where the 256 x 192 tiles fill the chip, a call of more than 4608 rows does not wait (launches and rows are those of the last call): collected
+    in the buffer, calls of 12000 rows of 8192 columns took 1.15 times as long.  At 5120 columns, 287 tiles, they wait."""
+    t = _exact_gram(d1, 8, chunks, False)
+    assert (t[14], t[15]) == (launches, rows)
