@@ -224,7 +224,8 @@ osscar_status osscar_get_tensor(osscar_ctx* ctx, int which, void* dst_dev, size_
 osscar_status osscar_get_scalars(osscar_ctx* ctx, double* lambda_host, double* c0_host);
 
 /* Device times of the last call of each kind, in milliseconds (HIP events on the context's stream):
- * [0] the Gram accumulation of the chunk passed together with finalize, [1] finalize, [2] init_support,
+ * [0] the Gram accumulation of the chunk passed together with finalize, with the products of earlier calls' rows that were
+ * still waiting for theirs (these alone if the finalizing call has no rows), [1] finalize, [2] init_support,
  * [3] local_search, [4] backsolve, [6] total time of the search's refreshes and flushes.  Sampled once
  * per batch of iterations: eager search [5] mean duration of one bulk update of N, [7] of one update of Z (groups of
  * more than one row: [5] of both, which share a launch);

@@ -833,7 +833,12 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   }
   if (!finalize) return OSSCAR_OK;
 
-  HIPCHK(c, launch_gram_queue(packed, s));      // (a call without rows finalizes)
+  if (c->queue.stages > 0) {      // a call without rows finalizes
+    HIPCHK(c, hipEventRecord(c->ev_a, s));
+    HIPCHK(c, launch_gram_queue(packed, s));
+    HIPCHK(c, hipEventRecord(c->ev_b, s));
+    c->timers[0] += elapsed(c);
+  }
   HIPCHK(c, hipEventRecord(c->ev_a, s));
   HIPCHK(c, launch_sum_copies(H64, c->h_copies, d1, d1, 1, s));
   HIPCHK(c, launch_trace64(H64, d1, c->scal, s));

@@ -786,3 +786,17 @@ def test_long_calls_are_multiplied_by_themselves(d1, chunks, launches, rows):
     in the buffer, calls of 12000 rows of 8192 columns took 1.15 times as long.  At 5120 columns, 287 tiles, they wait."""
     t = _exact_gram(d1, 8, chunks, False)
     assert (t[14], t[15]) == (launches, rows)
+
+
+def test_the_timers_hold_the_products_of_rows_that_waited():
+    """A finalizing call without rows multiplies the rows of the calls before it: their time is the Gram accumulation's."""
+    g = torch.Generator(device=DEV).manual_seed(1)
+    X = torch.randn(4096, 2048, generator=g, device=DEV).bfloat16()
+    W = torch.zeros(2048, 8, dtype=torch.bfloat16, device=DEV)
+    s = _pkg().Solver(2048, 8, 2048, 1, 1, 1, torch.bfloat16, torch.bfloat16, DEV)
+    s.osscar_gram(X[:2048])
+    s.osscar_gram(X[2048:])
+    s.osscar_gram(None, True, W, 0.0, 1e-2)
+    t = s.osscar_get_timers()
+    s.close()
+    assert t[14] == 1 and 0.5 * t[13] <= t[0] <= t[13] + 1.0      # ms; the product is 0.05
