@@ -197,7 +197,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   auto pass_on = [&](int g, int slot_g, int j, int slot_j) {      // no swap: the state as it stands, with new slots of rows g, j
     for (int u = own; u < MU && mr < th && 2 * TPR * u < th; u += nwg)
       *reinterpret_cast<double2*>(L.Minv2 + piece(u)) = *reinterpret_cast<const double2*>(L.Minv + piece(u));
-    if (tid == 0) {
+    if (tid == 0 && !single) {
       SwapRec r = L.rec[wg];
       if (r.row[0] == g) r.slot[0] = slot_g;
       if (r.row[1] == j) r.slot[1] = slot_j;
@@ -206,7 +206,8 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   };
   const bool idle = (cin->done | cin->pause) != 0 || cin->iters >= limit;
   // ---- pick: lanes of the first half of the workgroup hold the leaving side's records, the others the entering side's
-  if (rt >= nwg) { v1 = INFINITY; v2 = INFINITY; i1 = -1; sl1 = -1; }
+  // (the removal-only loops keep lists instead of records: removals of given rows leave the records alone, and their gaps are infinite)
+  if (rt >= nwg || single) { v1 = INFINITY; v2 = INFINITY; i1 = -1; sl1 = -1; }
   double wv = v1;
   int wi = i1;
   wave_min(wv, wi);
