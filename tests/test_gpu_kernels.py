@@ -585,17 +585,19 @@ def test_rows_of_several_calls_in_one_product(d1, m, chunks, target):
         assert torch.equal(G[2:], (Xd.T @ Y.double())[2:])
 
 
-@pytest.mark.parametrize("equal", [False, True])
-@pytest.mark.parametrize("p,t_hat", [(40, 3), (70, 16), (1030, 10), (8192, 16), (8193, 7), (30100, 16)])
-def test_picks_of_block_removals(p, t_hat, equal):
-    """The rows of an iteration come from sorted lists of every 64 rows: fewer rows than a list, more lists than groups of them, more entries
-    than are staged (from 30081 rows on).  With H = I the cost of a row is its weights' squared norm, whatever has left, so the
-    removals go by that norm; of equal ones the lowest rows leave first, past those whose products are computed ahead."""
+@pytest.mark.parametrize("costs", ["shuffled", "equal", "ascending"])
+@pytest.mark.parametrize("p,t_hat", [(40, 3), (70, 16), (1030, 10), (8192, 16), (8193, 7), (30100, 16), (30144, 16), (30145, 16)])
+def test_picks_of_block_removals(p, t_hat, costs):
+    """The rows of an iteration come from sorted lists of every 64 rows: fewer rows than a list, more lists than groups of them, the last size
+    whose entries are all staged (30144 rows, 471 lists of 17) and the first with 16 of each (30145), where the 17th of a list, read
+    where it lies, is the one that ends the gap when one list holds the cheapest rows (ascending costs).  With H = I the cost of a row
+    is its weights' squared norm, whatever has left, so the removals go by that norm; of equal ones the lowest rows leave first, past
+    those whose products are computed ahead."""
     pkg = _pkg()
     m, iters = 8, 3
     k = p - iters * t_hat
     g = torch.Generator().manual_seed(p)
-    scale = torch.ones(p) if equal else 1.0 + torch.randperm(p, generator=g).float() / p
+    scale = torch.ones(p) if costs == "equal" else 1.0 + (torch.arange(p) if costs == "ascending" else torch.randperm(p, generator=g)).float() / p
     W = (torch.ones(p, m) * scale[:, None]).to(DEV)
     H = torch.eye(p, device=DEV)
     s = pkg.Solver(p, m, p, 1, k, 1, torch.float32, torch.float32, DEV, from_dense=True)
@@ -607,7 +609,7 @@ def test_picks_of_block_removals(p, t_hat, equal):
     cost = np.append(scale.double().numpy()[order] ** 2, np.inf)
     for i, gap in enumerate(gaps):
         lo, hi = cost[(i + 1) * t_hat - 1], cost[(i + 1) * t_hat]
-        assert abs(gap - (hi - lo) / lo) <= 1e-6
+        assert abs(gap - (hi - lo) / lo) <= 1e-6      # (neighbours differ by 2 / p, 6.6e-5 at the largest p)
 
 
 @pytest.mark.parametrize("p", [2, 255, 257, 2048, 2049])
@@ -800,3 +802,36 @@ def test_the_timers_hold_the_products_of_rows_that_waited():
     t = s.osscar_get_timers()
     s.close()
     assert t[14] == 1 and 0.5 * t[13] <= t[0] <= t[13] + 1.0      # ms; the product is 0.05
+
+
+@pytest.mark.parametrize("p,k", [(32768, 300), (32769, 70)])
+def test_swaps_in_more_workgroups_than_compute_units(p, k):
+    """One launch per swap with 128 rows a workgroup: 256 of them, and one more, which starts when others have ended and have entered the swap
+    in what only grows.  H = the identity with neighbouring rows coupled by 0.3: the same swaps as with the state updated in place (rows that
+    score alike to 1e-5 apart), past a flush, with and without products computed ahead."""
+    pkg = _pkg()
+    m, swaps = 8, 66
+    g = torch.Generator(device=DEV).manual_seed(p)
+    H = torch.eye(p, device=DEV)
+    H.diagonal(1).fill_(0.3)
+    H.diagonal(-1).fill_(0.3)
+    G = torch.randn(p, m, generator=g, device=DEV)
+    s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
+    s.osscar_set_quadratic(H, G, 10.0 * float((G.double() ** 2).sum()), np.ones(p))
+    del H
+    kept = torch.randperm(p, generator=torch.Generator().manual_seed(p))[:k].tolist()
+    runs = []
+    for flags in (pkg.OSSCAR_SEARCH_EAGER, 0, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD):
+        s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, kept)
+        r = s.osscar_local_search(swaps, 0.0, flags | pkg.OSSCAR_SEARCH_ALWAYS_ACCEPT)
+        assert r["iters"] == r["accepted"] == swaps
+        runs.append((r, s.osscar_backsolve()))
+    s.close()
+    e, (We, Se, _) = runs[0]
+    for r, (Wr, Sr, _) in runs[1:]:
+        same = (r["trace_out"] == e["trace_out"]) & (r["trace_in"] == e["trace_in"])
+        n = swaps if same.all() else int(np.argmin(same))
+        assert n == swaps or e["trace_gap"][n].min() <= 1e-5
+        assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-6, atol=0)
+        if n == swaps:
+            assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
