@@ -75,38 +75,39 @@ __global__ __launch_bounds__(128) void swap_records_kernel(LazyPtrs L, int d1, c
   write_record<RPW>(L.rec + blockIdx.x, sc, kp, sl, blockIdx.x * RPW, tid >> 6, tid & 63);
 }
 
-// A pivot whose products were not computed ahead: its column of Z0 Z0^T by a pass over the workgroup's rows (products four at a
-// time in float32, their sums in float64), its row of K by float64 dot products with the rows in the other slots, a wave each.
-// miss: 1 for g, 2 for j, slots sg, sj; `used` slots of K beyond the picked rows are taken once these are in.
+// A pivot whose products were not computed ahead: its column of Z0 Z0^T by a pass over the workgroup's rows, its row of K by dot products
+// with the rows in the other slots, a wave each (products and sums in float64).  miss: 1 for g, 2 for j, slots sg, sj; `used` slots of K
+// beyond the picked rows are taken once these are in.  Bound by memory where the rows fill the chip; with few of them, by the chain of
+// requests that a wave makes along a row, so rows of any length are read four columns a lane.  Column by column where the length is no
+// multiple of four, and with one request of a row of K in flight, all of them by neighbouring workgroups: 28672 x 7168, every pivot
+// fetched, 318 us a swap, 259 so; 1000 x 4093 79 us, 47 so (a fetch and a swap each).
+typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));      // four columns of a row of any length
 template <int NT, int RPW>
 __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* __restrict__ Z0, int d1, int m, int g, int j, int miss, int sg, int sj,
                                                int used) {
-  constexpr int W = NT / 64, R = 4;
+  constexpr int W = NT / 64, R = 4, UN = NT == 512 ? 4 : 1;      // (more, or in arrays: the kernel spills, and the swaps that fetch nothing are slower)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wg = blockIdx.x, nwg = gridDim.x;
   const float *yg = Z0 + (int64_t)g * m, *yj = Z0 + (int64_t)j * m;
-  const bool vec = m % 4 == 0;
+  const int m4 = m & ~3;
   for (int r0 = wg * RPW + wave * R; r0 < min(d1, (wg + 1) * RPW); r0 += W * R) {
     double a[R], b[R];
     const float* rp[R];
 #pragma unroll
     for (int r = 0; r < R; r++) { a[r] = 0; b[r] = 0; rp[r] = Z0 + (int64_t)min(r0 + r, d1 - 1) * m; }
-    if (vec) {
-#pragma unroll 2
-      for (int c = lane * 4; c < m; c += 256) {
-        const float4 p = *reinterpret_cast<const float4*>(yg + c), q = *reinterpret_cast<const float4*>(yj + c);
+#pragma unroll UN
+    for (int c = lane * 4; c < m4; c += 256) {
+      const row4 p = *reinterpret_cast<const row4*>(yg + c), q = *reinterpret_cast<const row4*>(yj + c);
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-          const float4 v = *reinterpret_cast<const float4*>(rp[r] + c);
-          a[r] += (double)(v.x * p.x + v.y * p.y + v.z * p.z + v.w * p.w);
-          b[r] += (double)(v.x * q.x + v.y * q.y + v.z * q.z + v.w * q.w);
-        }
-      }
-    } else {
-      for (int c = lane; c < m; c += 64) {
-        const double p = yg[c], q = yj[c];
+      for (int r = 0; r < R; r++) {
+        const row4 v = *reinterpret_cast<const row4*>(rp[r] + c);
 #pragma unroll
-        for (int r = 0; r < R; r++) { const double v = rp[r][c]; a[r] += v * p; b[r] += v * q; }
+        for (int e = 0; e < 4; e++) { a[r] += (double)v[e] * (double)p[e]; b[r] += (double)v[e] * (double)q[e]; }
       }
+    }
+    if (m4 + lane < m) {
+      const double p = yg[m4 + lane], q = yj[m4 + lane];
+#pragma unroll
+      for (int r = 0; r < R; r++) { const double v = rp[r][m4 + lane]; a[r] += v * p; b[r] += v * q; }
     }
 #pragma unroll
     for (int r = 0; r < R; r++) {
@@ -118,12 +119,26 @@ __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* _
       }
     }
   }
-  for (int t = wg * W + wave; t < LAZY_NC + used; t += nwg * W) {
+  for (int t = wg + nwg * wave; t < LAZY_NC + used; t += nwg * W) {
     const int h = ((miss & 1) && t == sg) ? g : ((miss & 2) && t == sj) ? j : L.cand[t];
     if (h < 0) continue;
     const float* z = Z0 + (int64_t)h * m;
     double a = 0, b = 0;
-    for (int c = lane; c < m; c += 64) { const double v = z[c]; a += v * (double)yg[c]; b += v * (double)yj[c]; }
+    for (int c0 = lane * 4; c0 < m4; c0 += 1024) {      // four requests of each row in flight: a chain of one wave's loads
+      row4 v[4], p[4], q[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int c = c0 + 256 * u < m4 ? c0 + 256 * u : 0;
+        v[u] = *reinterpret_cast<const row4*>(z + c); p[u] = *reinterpret_cast<const row4*>(yg + c); q[u] = *reinterpret_cast<const row4*>(yj + c);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        if (c0 + 256 * u >= m4) break;
+#pragma unroll
+        for (int e = 0; e < 4; e++) { a += (double)v[u][e] * (double)p[u][e]; b += (double)v[u][e] * (double)q[u][e]; }
+      }
+    }
+    if (m4 + lane < m) { const double v = z[m4 + lane]; a += v * (double)yg[m4 + lane]; b += v * (double)yj[m4 + lane]; }
     a = wsum(a); b = wsum(b);
     if (lane == 0) {
       if (miss & 1) { L.K[sg * KLD + t] = a; L.K[t * KLD + sg] = a; }

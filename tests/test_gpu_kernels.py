@@ -835,3 +835,29 @@ def test_swaps_in_more_workgroups_than_compute_units(p, k):
         assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-6, atol=0)
         if n == swaps:
             assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
+
+
+def test_products_fetched_for_long_rows():
+    """Pivots whose products are fetched, rows of 16383 columns (read four at a time, the last three apart): the same swaps as in place, and no more
+    than three times its time.  Column by column, with one request of a row of K in flight at a time, it took six times as long."""
+    pkg = _pkg()
+    p, m, swaps = 1024, 16383, 30
+    g = torch.Generator(device=DEV).manual_seed(5)
+    X = torch.randn(2200, p, generator=g, device=DEV) * torch.exp(0.5 * torch.randn(p, generator=g, device=DEV))
+    W = torch.randn(p, m, generator=g, device=DEV) / p ** 0.5 * (1.0 + torch.arange(p, device=DEV)[:, None] / p)
+    s = pkg.Solver(p, m, p, 1, p // 2, swaps, torch.float32, torch.float32, DEV)
+    s.osscar_gram(X, True, W, 0.0, 5e-2)
+    runs = []
+    for flags in (pkg.OSSCAR_SEARCH_EAGER, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD):
+        ms = []
+        for _ in range(3):
+            s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, list(range(0, p, 2)))
+            r = s.osscar_local_search(swaps, 0.0, flags)
+            ms.append(s.osscar_get_timers()[3])
+        runs.append((r, min(ms)))
+    s.close()
+    (e, te), (r, t) = runs
+    print(f"in place {te:.2f} ms, fetched {t:.2f} ms")
+    assert e["iters"] == swaps and r["trace_out"].tolist() == e["trace_out"].tolist() and r["trace_in"].tolist() == e["trace_in"].tolist()
+    assert np.allclose(r["trace_obj"], e["trace_obj"], rtol=1e-6, atol=0)
+    assert t <= 3.0 * te
