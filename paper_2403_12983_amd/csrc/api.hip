@@ -1008,7 +1008,7 @@ static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h, const SearchCtrl* f
 struct SwapRun {
   osscar_ctx* c; TabDims d; TabPtrs t; LazyPtrs L; int mode;
   int tau_most = 0;              // pending pivots after the launches so far, at most
-  SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) {}
+  SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) { L.spare0 = spare_start(mode); }
   hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode); }
   hipError_t swap(int always, int limit, const SwapList& list = SwapList()) {
     SearchCtrl* next = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
@@ -1055,7 +1055,8 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
   if (st != OSSCAR_OK) return st;
   SearchCtrl h{};
   h.obj = c->dense_is_exact ? 0.0 : obj;   // the dense layer reproduces its own output exactly; a target output it does not
-  h.g_out = -1; h.g_in = -1; h.tau = 0; h.tau_inc = 0; h.pause = 0; h.spare = 0;
+  h.g_out = -1; h.g_in = -1; h.tau = 0; h.tau_inc = 0; h.pause = 0;
+  h.spare = spare_start((flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 1);
   HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
   TabDims d = dims(c);
   TabPtrs t = ptrs(c);
@@ -1182,7 +1183,9 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
   if (st != OSSCAR_OK) return st;
   const double obj0 = h.obj;
   h.done = (c->cr == 0) ? 1 : 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1;
-  h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0; h.spare = 0;
+  h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0;
+  const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
+  h.spare = spare_start(la_mode);
   for (auto& v : c->counters) v = 0;
   HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
   HIPCHK(c, hipStreamSynchronize(s));
@@ -1199,10 +1202,9 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     // The host waits once per flush interval (to read the control block); the flush and the next interval's iterations are
     // enqueued behind it without another wait, and the flush's time is read at the next wait.
     const int FLUSH = LAZY_TM / 2, BATCH = FLUSH;
-    const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
     SwapRun run(c, d, t, la_mode);
     HIPCHK(c, run.init());
-    int since_flush = 0, extra = 0;
+    int since_flush = 0, extra = la_mode == 2 ? FLUSH : 0;
     double flush_ms = 0; int flushes = 0, pauses = 0;
     bool flush_open = false;                 // a flush whose events have not been read yet
     auto collect = [&]() {                   // only after the stream has been waited for
@@ -1221,16 +1223,18 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       int nb = std::min(std::min(BATCH, max_swaps - h.iters), FLUSH - since_flush);
       if (refresh_every > 0) nb = std::min(nb, std::max(1, refresh_every - (h.accepted - since_refresh_base)));
       const bool sample = samples + 1 < EV_SAMPLES;
-      // a launch that fetches products makes no swap: as many more as the last interval had of those (idle past the limit)
+      // a launch that fetches products makes no swap: as many more as the last interval had of those, up to four (idle past the limit; 826
+      // rows, 199 swaps: 5.0 ms so, 5.2 with none, 5.5 with up to 64), and one per swap without products computed ahead, unless the last
+      // interval was cut short by a row that was pending
       const int before = h.iters, before_misses = h.misses;
-      for (int i = 0; i < nb + extra; i++) {
+      for (int i = 0; i < nb + std::min(extra, nb); i++) {
         if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][0], s));
         HIPCHK(c, run.swap(always, before + nb));
         if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][1], s));
       }
       st = read_ctrl(c, &h, run.t.ctrl);
       if (st != OSSCAR_OK) return st;
-      extra = std::min(h.misses - before_misses, 4);
+      extra = la_mode == 2 && !h.pause ? FLUSH : std::min(h.misses - before_misses, 4);
       run.tau_most = h.tau;
       collect();
       if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_local_search: a pivot lost definiteness at iteration %d", h.iters);
@@ -1339,12 +1343,12 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   if (st != OSSCAR_OK) return st;
   const double obj0 = h.obj;
   h.done = 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1; h.pause = 0; h.tau = 0; h.tau_inc = 0;
-  h.spare = 0;
+  const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
+  h.spare = spare_start(la_mode);
   HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
   HIPCHK(c, hipStreamSynchronize(s));
   const bool always = (flags & OSSCAR_SEARCH_ALWAYS_ACCEPT) != 0;
   const bool use_lazy = (c->q == 1) && !(flags & OSSCAR_SEARCH_EAGER);
-  const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
   const int take = std::min<int>(block, std::min(c->k, c->p - c->k));
   TabDims d = dims(c);
   TabPtrs t = ptrs(c);
@@ -1386,13 +1390,13 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
         if (!use_lazy || (!h.pause && extra == 0 && did == 0)) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
         if (!h.pause) continue;
         HIPCHK(c, run.flush());
-        pending = h.spare = 0;
+        pending = 0; h.spare = run.L.spare0;
       }
     }
     return OSSCAR_OK;
   };
   while (take > 0 && blocks < max_iters) {
-    if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = h.spare = 0; }
+    if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = 0; h.spare = run.L.spare0; }
     HIPCHK(c, launch_greedy_pick(d, run.t, take, c->g_pick, c->g_gap, s, 2));
     HIPCHK(c, hipMemcpyAsync(c->snap->pick, c->g_pick, sizeof c->snap->pick, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipMemcpyAsync(c->snap->gap, c->g_gap, sizeof c->snap->gap, hipMemcpyDeviceToHost, s));
@@ -1412,7 +1416,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
     blocks++;
     if (!ok) {
       // take the move back: the same pairs in reverse (the pending pivots must reach the tableau first)
-      if (use_lazy && pending > 0) { HIPCHK(c, run.flush()); pending = h.spare = 0; }
+      if (use_lazy && pending > 0) { HIPCHK(c, run.flush()); pending = 0; h.spare = run.L.spare0; }
       st = run_pairs(true);
       if (st != OSSCAR_OK) return st;
       h.obj = obj_before;

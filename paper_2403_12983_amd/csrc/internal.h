@@ -176,7 +176,7 @@ struct SearchCtrl {          // lives in device memory
   double rel_tol;
   double delta;              // exact change of the current pair
   double gap_rem, gap_add;
-  int32_t spare;             // one-launch swaps: spare slots of the look-ahead products in use
+  int32_t spare;             // one-launch swaps: spare slots of the look-ahead products in use (below zero: slots of picked rows are spare too)
   int32_t taken;             // groups: whether the pair of this iteration is taken, until the scores' launch records it
 };
 
@@ -276,7 +276,10 @@ struct LazyPtrs {
   // removal lists of every 64 rows (in the phases' scratch)
   double* bX; double* bU; double* bD; double* bYY; int32_t* bG;
   double* lval; int32_t* lrow;
+  int spare0;       // SearchCtrl::spare with nothing pending
 };
+// With no rows picked every pivot takes a spare slot: as many as can be pending (64 let the swaps flush after 32 instead of 64)
+constexpr int spare_start(int mode) { return mode == 2 ? LAZY_NS - LAZY_TM : 0; }
 // mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NC/2 cheapest removals + LAZY_NC/2 largest gains,
 // 1 = LAZY_NC cheapest removals (removal-only loops), 2 = none (every pivot then costs a pass over Z0)
 hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0);

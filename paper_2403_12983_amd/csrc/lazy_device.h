@@ -11,7 +11,7 @@ __device__ __forceinline__ void empty_pending(const LazyPtrs& L, SearchCtrl* ctr
   const int tau = tau_all(ctrl);
   for (int s = threadIdx.x; s < tau; s += nt) L.pos[L.Tidx[s]] = -1;
   __syncthreads();
-  if (threadIdx.x == 0) { ctrl->tau = 0; ctrl->tau_inc = 0; ctrl->pause = 0; ctrl->spare = 0; }
+  if (threadIdx.x == 0) { ctrl->tau = 0; ctrl->tau_inc = 0; ctrl->pause = 0; ctrl->spare = L.spare0; }
 }
 // the score of a row from its squared norm and diagonal element
 __device__ __forceinline__ double fresh_score(int h, const int32_t* __restrict__ kept, const double* __restrict__ gram, const double* __restrict__ dblk,

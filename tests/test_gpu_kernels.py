@@ -861,3 +861,22 @@ def test_products_fetched_for_long_rows():
     assert e["iters"] == swaps and r["trace_out"].tolist() == e["trace_out"].tolist() and r["trace_in"].tolist() == e["trace_in"].tolist()
     assert np.allclose(r["trace_obj"], e["trace_obj"], rtol=1e-6, atol=0)
     assert t <= 3.0 * te
+
+
+def test_flushes_without_products_computed_ahead():
+    """Every pending pivot has a slot for its products when none are computed ahead: 128 swaps of rows that are not swapped twice are two flushes
+    and no pause, and so are 256 removals."""
+    pkg = _pkg()
+    p, m = 600, 4
+    G = (1.0 + torch.randperm(p, generator=torch.Generator().manual_seed(1)).float() / p)[:, None] * torch.ones(p, m)
+    s = pkg.Solver(p, m, p, 1, 300, 128, torch.float32, torch.float32, DEV, from_dense=True)
+    s.osscar_set_quadratic(torch.eye(p).to(DEV), G.to(DEV), 1e4, np.ones(p))
+    worst = torch.argsort(G[:, 0])[:300].tolist()
+    s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, sorted(worst))
+    r = s.osscar_local_search(128, 0.0, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD)
+    c = s.osscar_get_counters()
+    assert r["accepted"] == 128 and r["trace_out"].tolist() == worst[:128]
+    assert (c["lookahead_misses"], c["flushes"], c["pauses"]) == (256, 2, 0)
+    obj, steps, _ = s.osscar_init_greedy(7, 0, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD)
+    assert sum(steps, []) == worst
+    s.close()
