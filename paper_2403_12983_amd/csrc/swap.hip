@@ -80,16 +80,17 @@ __global__ __launch_bounds__(128) void swap_records_kernel(LazyPtrs L, int d1, c
 // beyond the picked rows are taken once these are in.  Bound by memory where the rows fill the chip; with few of them, by the chain of
 // requests that a wave makes along a row, so rows of any length are read four columns a lane.  Column by column where the length is no
 // multiple of four, and with one request of a row of K in flight, all of them by neighbouring workgroups: 28672 x 7168, every pivot
-// fetched, 318 us a swap, 259 so; 1000 x 4093 79 us, 47 so (a fetch and a swap each).
+// fetched, 318 us a swap, 228 so; 1000 x 4093 79 us, 41 so (a fetch and a swap each, and the flushes).
 typedef float row4 __attribute__((ext_vector_type(4), aligned(4)));      // four columns of a row of any length
-template <int NT, int RPW>
+template <int NT>
 __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* __restrict__ Z0, int d1, int m, int g, int j, int miss, int sg, int sj,
                                                int used) {
   constexpr int W = NT / 64, R = 4, UN = NT == 512 ? 4 : 1;      // (more, or in arrays: the kernel spills, and the swaps that fetch nothing are slower)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wg = blockIdx.x, nwg = gridDim.x;
   const float *yg = Z0 + (int64_t)g * m, *yj = Z0 + (int64_t)j * m;
   const int m4 = m & ~3;
-  for (int r0 = wg * RPW + wave * R; r0 < min(d1, (wg + 1) * RPW); r0 += W * R) {
+  const int per = (d1 + R * nwg - 1) / (R * nwg) * R;      // neighbouring rows, as the lines that they are written to
+  for (int r0 = wg * per + wave * R; r0 < min(d1, (wg + 1) * per); r0 += W * R) {
     double a[R], b[R];
     const float* rp[R];
 #pragma unroll
@@ -113,13 +114,13 @@ __device__ __forceinline__ void fetch_products(const LazyPtrs& L, const float* _
     for (int r = 0; r < R; r++) {
       const double t = wsum(a[r]), u = wsum(b[r]);
       const int row = r0 + r;
-      if (lane == 0 && row < min(d1, (wg + 1) * RPW)) {
+      if (lane == 0 && row < d1) {
         if (miss & 1) L.GbT[(int64_t)sg * d1 + row] = t;
         if (miss & 2) L.GbT[(int64_t)sj * d1 + row] = u;
       }
     }
   }
-  for (int t = wg + nwg * wave; t < LAZY_NC + used; t += nwg * W) {
+  for (int t = wg + nwg * (W - 1 - wave); t < LAZY_NC + used; t += nwg * W) {
     const int h = ((miss & 1) && t == sg) ? g : ((miss & 2) && t == sj) ? j : L.cand[t];
     if (h < 0) continue;
     const float* z = Z0 + (int64_t)h * m;
@@ -158,7 +159,7 @@ template <int NT, int RPW>
 __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* __restrict__ N0, const float* __restrict__ Z0, int d1, int m,
                                                         const SearchCtrl* __restrict__ cin, SearchCtrl* __restrict__ cout, int32_t* __restrict__ kept,
                                                         double* __restrict__ rho, double* __restrict__ diag, double* __restrict__ score, int always, int tau_most,
-                                                        const int32_t* __restrict__ list_g, const int32_t* __restrict__ list_j, int list_n, int list_step, int limit, int32_t* __restrict__ trace_out,
+                                                        const int32_t* __restrict__ list_g, const int32_t* __restrict__ list_j, int list_n, int list_step, int limit, int nwg, int32_t* __restrict__ trace_out,
                                                         int32_t* __restrict__ trace_in, float* __restrict__ trace_gap, double* __restrict__ trace_obj) {
   constexpr int TM = LAZY_TM, W = NT / 64, H = NT / 2;
   constexpr int TPR = NT / TM, MU = TM / (2 * TPR);             // threads per row of M^-1, pairs of columns per thread
@@ -174,10 +175,11 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   // 1024 threads have 128 registers each: K_TT waits in shared memory instead, put there by direct loads (rows from tau on: anything)
   constexpr bool KT_LDS = NT == 1024;
   __shared__ __attribute__((aligned(16))) double s_kt[KT_LDS ? TM * TM : 2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wg = blockIdx.x, nwg = gridDim.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wg = blockIdx.x;
+  const bool helper = wg >= nwg;      // no rows: picks and fetches only
   // ---- requests that do not depend on the pick, in the order in which they are needed (loads return in order); only what can be
   // pending: blocks of 32 rows and columns (the loads of all 128 took 1.8 us at the 64 bytes a cycle that a compute unit receives)
-  const int th = min(TM, (tau_most + 2 + 31) & ~31);      // this launch's pivots included
+  const int th = helper ? 0 : min(TM, (tau_most + 2 + 31) & ~31);      // this launch's pivots included
   const int side = tid >= H, rt = tid & (H - 1);
   const SwapRec* rp = L.rec + (rt < nwg ? rt : 0);
   double v1 = rp->best[side], v2 = rp->second[side];
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   const int act = idle ? IDLE : (g < 0 || j < 0) ? NONE : (pending || tau + npiv > TM || spare + need > LAZY_NS) ? PAUSE : miss ? FETCH : SWAP;
   if (act != SWAP) {
     const int ng = (miss & 1) ? LAZY_NC + spare : sg, nj = (miss & 2) ? LAZY_NC + spare + (miss & 1) : sj;
-    if (act == FETCH) fetch_products<NT, RPW>(L, Z0, d1, m, g, j, miss, ng, nj, spare + need);      // the next launch finds them
+    if (act == FETCH) fetch_products<NT>(L, Z0, d1, m, g, j, miss, ng, nj, spare + need);      // the next launch finds them
     if (wg == 0 && tid == 0) {
       SearchCtrl c = *cin;
       if (act == NONE) { c.done = 1; c.g_out = -1; c.g_in = -1; }
@@ -287,9 +289,10 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
       }
       *cout = c;
     }
-    pass_on(act == FETCH && (miss & 1) ? g : -2, ng, act == FETCH && (miss & 2) ? j : -2, nj);
+    if (!helper) pass_on(act == FETCH && (miss & 1) ? g : -2, ng, act == FETCH && (miss & 2) ? j : -2, nj);
     return;
   }
+  if (helper) return;
   // ---- everything that depends on the pick, in one round trip (loads without conditions: one under a condition is waited for where
   // the condition ends)
   const int jc = single ? g : j, sjc = single ? sg : sj;
@@ -514,10 +517,12 @@ int swap_record_count(int64_t d1) { const int r = swap_rows_per_wg((int)d1); ret
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always, int limit, int tau_most,
                             hipStream_t s, const SwapList& l) {
   if (l.n < 0 || l.n > LIST_MOST || (l.n > 0 && !l.out)) return hipErrorInvalidValue;
-  const int nwg = swap_record_count(d.d1);
+  // rows of more than 4096 columns: a workgroup for every compute unit, so that a fetch of few long rows is not left to a few of them (100
+  // swaps, 72 pivots fetched: 1000 x 16384 8.4 ms without, 6.4 so; 300 x 8192, 60 swaps 3.0 and 2.4)
+  const int nwg = swap_record_count(d.d1), grid = d.m > 4096 ? std::max(nwg, 256) : nwg;
 #define OSSCAR_SWAP(NT, RPW)                                                                                                         \
-  hipLaunchKernelGGL((lazy_swap_kernel<NT, RPW>), dim3(nwg), dim3(NT), 0, s, L, t.N, t.Z, d.d1, d.m, t.ctrl, next, t.kept, t.gram, t.dblk, \
-                     t.score, always, tau_most, l.out, l.in, l.n, l.step, limit, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
+  hipLaunchKernelGGL((lazy_swap_kernel<NT, RPW>), dim3(grid), dim3(NT), 0, s, L, t.N, t.Z, d.d1, d.m, t.ctrl, next, t.kept, t.gram, t.dblk, \
+                     t.score, always, tau_most, l.out, l.in, l.n, l.step, limit, nwg, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
   switch (swap_rows_per_wg(d.d1)) {
     case 32: OSSCAR_SWAP(512, 32); break;
     case 64: OSSCAR_SWAP(1024, 64); break;
