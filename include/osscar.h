@@ -229,7 +229,8 @@ osscar_status osscar_get_scalars(osscar_ctx* ctx, double* lambda_host, double* c
  * [3] local_search, [4] backsolve, [6] total time of the search's refreshes and flushes.  Sampled once
  * per batch of iterations: eager search [5] mean duration of one bulk update of N, [7] of one update of Z (groups of
  * more than one row: [5] of both, which share a launch);
- * delayed-update search [5] and [7] mean duration of one swap's launch (the first of a batch).
+ * delayed-update search [5] and [7] mean duration of a swap's launch (the first of a batch, also where that one fetches the
+ * products of a pivot that were not computed ahead and makes no swap).
  * [8] the product G = H W inside finalize (one GEMM launch, or the three bf16 products and their repacking when W is
  * bf16).  [9] the inverse of H on the kept rows in the last state build: the blocked sweep on a float64 copy of H_KK
  * (about 2 kr^3 flops on the float64 matrix cores).  [10] zero.  [11] not a time: the largest P_ii H_ii over the kept rows

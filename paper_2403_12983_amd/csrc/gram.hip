@@ -553,7 +553,8 @@ static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int pstages, i
   return hipGetLastError();
 }
 // Parts that the contraction of a queued product is cut into, each with its copy of the result: one workgroup per compute unit, and
-// at least GW_MIN_PART stages each
+// at least GW_MIN_PART stages each (512 to 3000 columns, two to four calls of 64 to 6000 rows: 8, 16 and 32 within the 5 % by which runs
+// differ, with 4 calls of 256 to 512 rows 3 - 8 % slower; with 32, 512 columns do not fill the chip and their rows do not wait)
 static int queue_parts(int nstages, const PackedTiles& t, int copies) {
   return std::max(1, std::min({copies, nstages / GW_MIN_PART, (int)((256 + t.tall_entries - 1) / t.tall_entries)}));
 }

@@ -280,8 +280,8 @@ struct LazyPtrs {
 };
 // With no rows picked every pivot takes a spare slot: as many as can be pending (64 let the swaps flush after 32 instead of 64)
 constexpr int spare_start(int mode) { return mode == 2 ? LAZY_NS - LAZY_TM : 0; }
-// mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NC/2 cheapest removals + LAZY_NC/2 largest gains,
-// 1 = LAZY_NC cheapest removals (removal-only loops), 2 = none (every pivot then costs a pass over Z0)
+// mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NPICK_OUT cheapest removals + LAZY_NPICK_IN largest gains,
+// 1 = LAZY_NC cheapest removals (removal-only loops), at most 32 a side of every 1024 rows; 2 = none (every pivot then costs a pass over Z0)
 hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0);
 // Pairs on the device that swaps take in turn, out[r * step] and in[r * step] for r < n <= 64; in == nullptr: rows out[r * step] to remove
 struct SwapList { const int32_t* out = nullptr; const int32_t* in = nullptr; int n = 0, step = 1; };
@@ -294,8 +294,6 @@ int swap_record_count(int64_t d1);
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);
 hipError_t launch_zt(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s);
-// A second stream and two events: the flush runs its update of N0 there, beside the candidate selection and the look-ahead
-// product on the main stream (they touch disjoint data), and joins before the scores are refreshed.
 // `take` <= LAZY_BT rows leave the kept set as one block pivot (nested schedule, q = 1): those in pick (device), or (own_pick) the
 // cheapest ones, which are left there, with the relative gap to the next one in *gap; at most tau_most pivots are pending.  Does nothing
 // else but set ctrl->pause if a pick is pending, is not among the rows whose products were computed ahead, or the pending set
@@ -305,6 +303,8 @@ hipError_t launch_lazy_block_remove(const TabDims& d, const TabPtrs& t, const La
 int removal_list_count(int64_t d1);
 hipError_t launch_removal_lists(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 
+// A second stream and two events: the flush runs the candidate selection and its update of N0 there, beside the update of Z0 and the
+// look-ahead product on the main stream (they touch disjoint data but for what the events order), and joins before the scores are refreshed.
 struct SideStream { hipStream_t stream = nullptr; hipEvent_t fork = nullptr, join = nullptr; };
 // side == nullptr (or no stream in it): everything in order on s
 hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0,

@@ -13,10 +13,12 @@
 // w without a pass over Z0: y1, y2 are combinations of the current rows g, j of Z, and these of base rows:
 //     Z0 z_g^T = Z0 Z0[g, :]^T - sum_r x_g[r] Z0 Z0[T_r, :]^T,     x_g = M^-1 C0[g, :]^T,
 // so it is enough to know the products of Z0 with the base rows of g, j and of the pending pivots.  Which rows
-// will be pivots before the next flush is predictable (the LAZY_NPICK_OUT cheapest removals and LAZY_NPICK_IN largest
-// gains at flush time cover all but a few per thousand of them), so right after each flush one matrix product Zc Z0^T
-// computes those products for these candidate rows (GbT); a pivot outside the candidates costs one read-only pass over
-// Z0 for its column (kept in one of LAZY_NS spare slots).  Every
+// will be pivots before the next flush is predictable (in the largest layers the LAZY_NPICK_OUT cheapest removals and
+// LAZY_NPICK_IN largest gains at flush time cover all but a few per thousand of them), so right after each flush one matrix
+// product Zc Z0^T computes those products for these candidate rows (GbT); a pivot outside the candidates costs one read-only pass
+// over Z0 for its column (kept in one of LAZY_NS spare slots), a launch of its own.  At most 32 candidates a side come from each
+// 1024 rows, so layers of up to 2048 rows have 32 or 64 a side and miss more often (826 rows, 199 swaps: 192 pivots of 398), and the
+// removal-only loops have their LAZY_NC from 7169 rows on.  Every
 // LAZY_TM/2 iterations the pending rank-tau correction is applied to N0 and Z0 by matrix products on the
 // matrix cores.  The sequence of swaps is exactly that of the eager search (Proposition 4.1, Cases 1-3).
 //
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(256, 2) void la_product_kernel(const uint4* __restr
   }
 }
 
-// mode 0: half of the slots for kept rows, half for the others; 1: all for kept rows (removal-only loops); 2: none
+// mode 0: LAZY_NPICK_OUT slots for kept rows, LAZY_NPICK_IN for the others; 1: LAZY_NC for kept rows (removal-only loops); 2: none
 struct CandCounts { int n_k, n_c; };
 static CandCounts cand_counts(int mode) {
   // Swap search: a cycle of 64 swaps takes 64 pivots from each side, and which rows they will be is known at flush time only
@@ -313,7 +315,7 @@ static CandCounts cand_counts(int mode) {
 // the pick: reads the scores and the kept flags only (two sorts in one workgroup each: latency, no bandwidth)
 static hipError_t launch_candidate_pick(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
   const int nblk = (d.p + 1023) / 1024;               // <= 64 (d1 <= 65536)
-  const int per_block = std::min(32, 1024 / nblk);
+  const int per_block = std::min(32, 1024 / nblk);    // a side's winners are merged by one workgroup of 1024
   hipError_t e = hipMemsetAsync(L.cslot, 0xFF, (size_t)d.d1 * 4, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(cand_local_kernel, dim3(nblk, 2), dim3(1024), 0, s, L, d.p, t.kept, t.score, per_block);
@@ -1031,7 +1033,7 @@ __global__ __launch_bounds__(256) void blk_update_kernel(LazyPtrs L, const float
     if (tid < BT) { const int g = tid < t ? L.bG[tid] : 0; sG[tid] = g; sSlot[tid] = (tid < t) ? L.cslot[g] : 0; }
     __syncthreads();
     const int lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
-    // a workgroup walks groups of 64 rows (two selection records each), so the tables above are loaded once for several
+    // a workgroup walks groups of 64 rows (a removal list each), so the tables above are loaded once for several
     for (int grp = b; grp < row_groups; grp += row_wgs) {
       const int row = grp * 64 + wave * 16 + lc, rc = min(row, d1 - 1);
       // requested first: the base entries N0[row, G] (new columns of C0), the products GbT[G, row], the row's own values
