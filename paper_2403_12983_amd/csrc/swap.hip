@@ -275,7 +275,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   const int miss = (hit_g ? 0 : 1) | (hit_j ? 0 : 2), need = (hit_g ? 0 : 1) + (hit_j ? 0 : 1);
   enum { SWAP, IDLE, NONE, PAUSE, FETCH };
   const int act = idle ? IDLE : (g < 0 || j < 0) ? NONE : (pending || tau + npiv > TM || spare + need > LAZY_NS) ? PAUSE : miss ? FETCH : SWAP;
-  if (act != SWAP) {
+  if (__builtin_expect(act != SWAP, 0)) {      // laid out behind the swap: in between, its code made the swaps 2 % slower
     const int ng = (miss & 1) ? LAZY_NC + spare : sg, nj = (miss & 2) ? LAZY_NC + spare + (miss & 1) : sj;
     if (act == FETCH) fetch_products<NT>(L, Z0, d1, m, g, j, miss, ng, nj, spare + need);      // the next launch finds them
     if (wg == 0 && tid == 0) {
