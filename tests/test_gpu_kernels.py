@@ -777,7 +777,8 @@ def test_rows_that_wait_when_the_layer_ends(d1, m, chunks, launches):
     t = _exact_gram(d1, m, chunks, False)
     assert t[14] == launches and sum(chunks) <= t[15] < sum(chunks) + 128 * len(chunks)
     if launches == 2:
-        assert t[13] * t[14] <= 2.0 * min(u[13] * u[14] for u in [_exact_gram(d1, m, [sum(chunks)], False) for _ in range(3)])
+        ms = [min(u[13] * u[14] for u in [_exact_gram(d1, m, c, False) for _ in range(3)]) for c in (chunks, [sum(chunks)])]
+        assert ms[0] <= 2.0 * ms[1]
     _exact_gram(d1, m, chunks, True)
 
 
