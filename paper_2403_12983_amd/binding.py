@@ -15,6 +15,8 @@ OSSCAR_SEARCH_ALWAYS_ACCEPT = 1
 OSSCAR_SEARCH_EAGER = 2
 OSSCAR_SEARCH_NO_LOOKAHEAD = 4
 OSSCAR_SEARCH_EXACT_IN = 8
+OSSCAR_SEARCH_LAUNCH_PER_SWAP = 16
+OSSCAR_SEARCH_IMPATIENT = 32
 T_H, T_G, T_P, T_B, T_V, T_R, T_REM, T_ADD, T_KEPT, T_CAND = range(10)
 _STATUS = {0: "OK", 1: "EINVAL", 2: "ENOMEM", 3: "ENOTPD", 4: "EHIP", 5: "ESTATE"}
 
@@ -294,7 +296,7 @@ class Solver:
     def osscar_get_counters(self):
         arr = (C.c_int64 * 8)()
         self._check(self.lib.osscar_get_counters(self.ctx, arr))
-        return dict(flushes=arr[0], pauses=arr[1], lookahead_misses=arr[2], iters=arr[3])
+        return dict(flushes=arr[0], pauses=arr[1], lookahead_misses=arr[2], iters=arr[3], runs=arr[4])
 
 
 def gemm_log(enable: bool):

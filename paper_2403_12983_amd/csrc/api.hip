@@ -114,6 +114,7 @@ struct osscar_ctx {
   int2* tiles;                                 // tile schedules of the bf16 matrix-core products (uploaded once at create)
   PackedTiles tiles_h, tiles_g;                // of a d1 x d1 result (lower triangle) and of a d1 x m one, in `tiles`
   bool extras = true;                          // the workspace holds what only makes the layer faster (see carve_all)
+  bool runs_fit = false;                       // the workgroups of a run of swaps are resident together
   int h_copies = 1, g_copies = 1;              // copies of the float64 accumulators that the layer's chunks have used so far
   double* gemm_ws; size_t gemm_ws_size;        // partial tiles of the 64 x 64 float64 products (this stream only; 0: they never cut)
   int2* tiles_state;                           // two schedules of the corrections' products (shapes follow the kept count)
@@ -227,6 +228,9 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
     L.ZcP = cv.take<char>((int64_t)LAZY_NC * ((m + 31) / 32 * 32) * 6);
     L.Epk = cv.take<char>((int64_t)768 * ((d1 + 127) / 128 * 128)); L.Cpk = cv.take<char>((int64_t)768 * ((d1 + 127) / 128 * 128));
     L.Zpk = cv.take<char>((int64_t)768 * ((m + 127) / 128 * 128));
+    // runs of swaps: between two flushes in the memory of the flush's packed operands (ZcP to Zpk, 344064 bytes at least)
+    const size_t words = align_up((size_t)swap_run_shared_words() * 8);
+    L.run_shared = L.ZcP; L.LL = reinterpret_cast<double*>(reinterpret_cast<char*>(L.ZcP) + words); L.LL2 = L.LL + TM * TM;
     L.cslot = cv.take<int32_t>(d1); L.cand = cv.take<int32_t>(LAZY_NC + LAZY_NS); L.tslot = cv.take<int32_t>(LAZY_TM);
     L.lkey = cv.take<double>(2 * 64 * 32); L.lidx = cv.take<int32_t>(2 * 64 * 32);
     L.bX = cv.take<double>(TM * LAZY_BT); L.bU = cv.take<double>(TM * LAZY_BT);
@@ -703,6 +707,7 @@ osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* wor
     if (!hr.empty()) { c->tiles_g.tall = c->tiles + at_hs + hs.size(); c->tiles_g.tall_entries = hr.size(); }
     c->lazy.tiles_sym = sym; c->lazy.n_tiles_sym = ts.size(); c->lazy.tiles_rect = rect; c->lazy.n_tiles_rect = tr.size();
   }
+  c->runs_fit = c->q == 1 && swap_run_fits(c->d1);
   c->ev_ok = (hipEventCreate(&c->ev_a) == hipSuccess) && (hipEventCreate(&c->ev_b) == hipSuccess);
   for (int i = 0; i < EV_SAMPLES && c->ev_ok; i++)
     for (int j = 0; j < 3; j++) c->ev_ok = c->ev_ok && (hipEventCreate(&c->ev_s[i][j]) == hipSuccess);
@@ -1003,19 +1008,42 @@ static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h, const SearchCtrl* f
   return OSSCAR_OK;
 }
 
+// Ticks (10 ns) that a workgroup of a run of swaps waits for the others: a thousand exchanges.  They can only be that late where other work
+// holds compute units; each run that gives up costs about this long.
+constexpr uint32_t RUN_PATIENCE = 200000;
+// Pivots whose products are missing, in an interval of 64 swaps, up to which the next one is made of runs only; with more, the swaps behind the
+// first missing pivot are a launch each (a run, a launch that fetches and the next run cost about four swaps more than two launches).
+constexpr int RUN_MISSES = 16;
+
 // The delayed-update search on one-launch swaps: every launch reads one copy of the control block, of M^-1 and of the records and writes
 // the other, so the current ones change place; settle() brings the control block back to where every other call expects it.
+// run(): as many swaps as there are up to `limit` in one launch (swaprun.hip).  can_run(): where nothing pending comes from swaps that were a
+// launch each.
 struct SwapRun {
   osscar_ctx* c; TabDims d; TabPtrs t; LazyPtrs L; int mode;
   int tau_most = 0;              // pending pivots after the launches so far, at most
+  int runs = 0, all_runs = 0;    // since the last flush, of the call
+  bool whole = true;             // no swaps but those of runs since then
   SwapRun(osscar_ctx* c_, const TabDims& d_, const TabPtrs& t_, int mode_) : c(c_), d(d_), t(t_), L(c_->lazy), mode(mode_) { L.spare0 = spare_start(mode); }
-  hipError_t init() { tau_most = 0; return launch_lazy_init(d, t, L, c->stream, mode); }
-  hipError_t swap(int always, int limit, const SwapList& list = SwapList()) {
-    SearchCtrl* next = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
-    const hipError_t e = launch_lazy_swap(d, t, L, next, always, limit, tau_most, c->stream, list);
-    t.ctrl = next;
+  void emptied() { tau_most = 0; runs = 0; whole = true; }
+  hipError_t init() { emptied(); return launch_lazy_init(d, t, L, c->stream, mode); }
+  void moved_on() {
+    t.ctrl = c->ctrl + (t.ctrl == c->ctrl ? 1 : 0);
     std::swap(L.Minv, L.Minv2); std::swap(L.rec, L.rec2);
-    tau_most = std::min(tau_most + 2, LAZY_TM);
+  }
+  hipError_t swap(int always, int limit, const SwapList& list = SwapList(), bool fetch_only = false) {
+    const hipError_t e = launch_lazy_swap(d, t, L, c->ctrl + (t.ctrl == c->ctrl ? 1 : 0), always, limit, tau_most, c->stream, list, fetch_only);
+    moved_on();
+    if (!fetch_only) { tau_most = std::min(tau_most + 2, LAZY_TM); whole = false; }
+    return e;
+  }
+  bool can_run() const { return whole && runs < RUN_MOST; }
+  hipError_t run(int always, int limit, int most, uint32_t patience, const SwapList& list = SwapList()) {
+    const hipError_t e = launch_swap_run(d, t, L, c->ctrl + (t.ctrl == c->ctrl ? 1 : 0), always, limit, runs, patience, c->stream, list);
+    moved_on();
+    std::swap(L.LL, L.LL2);
+    runs++; all_runs++;
+    tau_most = std::min(tau_most + 2 * most, LAZY_TM);
     return e;
   }
   // removal of n rows, after which `iters` iterations of the call have run: a launch each and one for its products
@@ -1024,7 +1052,7 @@ struct SwapRun {
     for (int i = 0; i < 2 * n && e == hipSuccess; i++) e = swap(1, iters, SwapList{rows, nullptr, n, 1});
     return e;
   }
-  hipError_t flush() { tau_most = 0; return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c)); }
+  hipError_t flush() { emptied(); return launch_lazy_flush(d, t, L, c->stream, mode, side_of(c)); }
   hipError_t settle() {
     if (t.ctrl == c->ctrl) return hipSuccess;
     const hipError_t e = hipMemcpyAsync(c->ctrl, t.ctrl, sizeof(SearchCtrl), hipMemcpyDeviceToDevice, c->stream);
@@ -1183,7 +1211,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
   if (st != OSSCAR_OK) return st;
   const double obj0 = h.obj;
   h.done = (c->cr == 0) ? 1 : 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1;
-  h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0;
+  h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0; h.stalled = 0;
   const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
   h.spare = spare_start(la_mode);
   for (auto& v : c->counters) v = 0;
@@ -1205,6 +1233,12 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     SwapRun run(c, d, t, la_mode);
     HIPCHK(c, run.init());
     int since_flush = 0, extra = la_mode == 2 ? FLUSH : 0;
+    // what the first interval will miss: 32 rows a side of every 1024 have their products
+    const int picked = 32 * ((c->p + 1023) / 1024);
+    int missed = picked < std::min({FLUSH, (int)max_swaps, std::max(c->k, c->p - c->k)}) ? RUN_MISSES + 1 : 0;      // in the last interval
+    int missing = 0;                                             // in this one so far
+    bool runs = c->runs_fit && la_mode == 0 && !(flags & OSSCAR_SEARCH_LAUNCH_PER_SWAP), owed = false;
+    const uint32_t patience = (flags & OSSCAR_SEARCH_IMPATIENT) ? 0u : RUN_PATIENCE;
     double flush_ms = 0; int flushes = 0, pauses = 0;
     bool flush_open = false;                 // a flush whose events have not been read yet
     auto collect = [&]() {                   // only after the stream has been waited for
@@ -1217,6 +1251,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       HIPCHK(c, hipEventRecord(c->ev_s[0][1], s));
       flush_open = true; flushes++;
       since_flush = 0;
+      missed = missing; missing = 0;
       return OSSCAR_OK;
     };
     while (h.iters < max_swaps && !h.done) {
@@ -1227,21 +1262,42 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       // rows, 199 swaps: 5.0 ms so, 5.2 with none, 5.5 with up to 64), and one per swap without products computed ahead, unless the last
       // interval was cut short by a row that was pending
       const int before = h.iters, before_misses = h.misses;
-      for (int i = 0; i < nb + std::min(extra, nb); i++) {
-        if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][0], s));
-        HIPCHK(c, run.swap(always, before + nb));
-        if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][1], s));
+      const bool many = std::max(missed, missing) > RUN_MISSES;
+      const bool by_run = runs && run.can_run() && !(owed && many);
+      bool sampled = sample;
+      if (by_run) {
+        // a run ends before a pivot whose products are missing; the launch behind it fetches them, and the next run goes on
+        const int more = many ? 0 : std::min(extra, 4);
+        sampled = sample && !owed && more == 0;
+        if (owed) HIPCHK(c, run.swap(always, before + nb, SwapList(), true));
+        if (sampled) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][0], s));
+        HIPCHK(c, run.run(always, before + nb, nb, patience));
+        if (sampled) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][1], s));
+        for (int i = 0; i < more && run.can_run(); i++) {
+          HIPCHK(c, run.swap(always, before + nb, SwapList(), true));
+          HIPCHK(c, run.run(always, before + nb, nb, patience));
+        }
+      } else {
+        for (int i = 0; i < nb + std::min(extra, nb); i++) {
+          if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][0], s));
+          HIPCHK(c, run.swap(always, before + nb));
+          if (i == 0 && sample) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][1], s));
+        }
       }
       st = read_ctrl(c, &h, run.t.ctrl);
       if (st != OSSCAR_OK) return st;
       extra = la_mode == 2 && !h.pause ? FLUSH : std::min(h.misses - before_misses, 4);
       run.tau_most = h.tau;
+      owed = by_run && h.iters < before + nb && !h.pause && !h.done;
+      missing += h.misses - before_misses;
+      if (h.stalled) runs = false;      // something else holds part of the compute units: a launch per swap for the rest of the call
       collect();
       if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_local_search: a pivot lost definiteness at iteration %d", h.iters);
       since_flush += h.iters - before;
-      if (sample && h.iters > before) {
+      if (sampled && h.iters > before) {
         float a = 0;
         hipEventElapsedTime(&a, c->ev_s[samples + 1][0], c->ev_s[samples + 1][1]);
+        if (by_run) a /= (float)(h.iters - before);
         upd_n_ms += a; upd_z_ms += a; samples++;
       }
       const bool want_refresh = !h.done && refresh_every > 0 && h.accepted - since_refresh_base >= refresh_every && h.iters < max_swaps;
@@ -1273,7 +1329,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     HIPCHK(c, run.settle());
     if (flush_open) { HIPCHK(c, hipStreamSynchronize(s)); collect(); }
     c->timers[6] = refresh_ms + flush_ms;
-    c->counters[0] = flushes; c->counters[1] = pauses; c->counters[2] = h.misses; c->counters[3] = h.iters;
+    c->counters[0] = flushes; c->counters[1] = pauses; c->counters[2] = h.misses; c->counters[3] = h.iters; c->counters[4] = run.all_runs;
   } else {
   const int BATCH = 32;
   while (launched < max_swaps && !h.done) {
@@ -1363,14 +1419,38 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   // makes no swap: as many more are enqueued as the last move had of those (a pair that goes back has just left the rows that are
   // computed ahead, and without these every pair fetches); they are idle if there are fewer now.
   int fetched = la_mode == 2 ? take : 0;
+  const bool runs = la_mode == 0 && !(flags & OSSCAR_SEARCH_LAUNCH_PER_SWAP);
   auto run_pairs = [&](bool back) -> osscar_status {
     auto out = [&](int r) { return back ? 64 + take - 1 - r : r; };
     auto inn = [&](int r) { return back ? take - 1 - r : 64 + r; };
     const SwapList list{c->g_pick + out(0), c->g_pick + inn(0), take, back ? -1 : 1};
     const int last = done_pairs + take;
     int idx = 0, extra = back ? take : fetched;
+    const bool by_run = use_lazy && runs && extra * 8 <= take;
+    bool owed = false;
     fetched = 0;
     while (idx < take) {
+      if (by_run && run.can_run()) {      // all pairs in one launch, up to one whose products are missing
+        const int misses = h.misses;
+        if (owed) HIPCHK(c, run.swap(1, last, list, true));
+        HIPCHK(c, run.run(1, last, take - idx, RUN_PATIENCE, list));
+        osscar_status q = read_ctrl(c, &h, run.t.ctrl);
+        if (q != OSSCAR_OK) return q;
+        run.tau_most = h.tau;
+        if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_block_search: a pivot lost definiteness in move %d", blocks);
+        const int did = h.iters - done_pairs;
+        if (did < 0 || did > take - idx) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search lost count of its pairs");
+        done_pairs += did; idx += did; pending += 2 * did;
+        fetched += h.misses - misses;
+        if (idx < take && !h.pause) {
+          if (owed && did == 0 && h.misses == misses) return fail(c, OSSCAR_ESTATE, "internal: osscar_block_search stopped without a reason");
+          owed = true;
+        } else if (idx < take) {
+          HIPCHK(c, run.flush());
+          pending = 0; h.spare = run.L.spare0; owed = false;
+        }
+        continue;
+      }
       // where every pair is expected to fetch, the spare slots end the pass (the pair behind the last one that fits makes it stop)
       const int fits = extra < take - idx ? take - idx : std::min(take - idx, (LAZY_NS - h.spare) / 2);
       const int launches = fits + std::min(extra, fits) + (fits < take - idx ? 1 : 0);

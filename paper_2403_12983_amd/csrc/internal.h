@@ -176,6 +176,7 @@ struct SearchCtrl {          // lives in device memory
   double rel_tol;
   double delta;              // exact change of the current pair
   double gap_rem, gap_add;
+  int32_t stalled;           // a run of swaps (swaprun.hip) waited too long and left everything as it was
   int32_t spare;             // one-launch swaps: spare slots of the look-ahead products in use (below zero: slots of picked rows are spare too)
   int32_t taken;             // groups: whether the pair of this iteration is taken, until the scores' launch records it
 };
@@ -271,6 +272,8 @@ struct LazyPtrs {
   // one-launch swaps (in the phases' scratch, see carve_all): the other copy of M^-1, two copies of a record per workgroup, Gram
   // matrix of the base rows in the slots (LAZY_NC + LAZY_NS squared) and its part for the pending pivots (LAZY_TM squared)
   double* Minv2; SwapRec* rec; SwapRec* rec2; double* K; double* KT;
+  // runs of swaps: their shared words and two copies of ZT ZT^T for the pending pivots, where a flush has its packed operands (ZcP .. Zpk)
+  void* run_shared; double* LL; double* LL2;
   double* lkey; int32_t* lidx;   // 2 x 64 x 32: per-block winners of the candidate selection
   // block removal (nested schedule): X = M^-1 N0[T, G], U = ZT Y^T (LAZY_TM x LAZY_BT each), D, Y Y^T (LAZY_BT^2), the picks; the
   // removal lists of every 64 rows (in the phases' scratch)
@@ -288,8 +291,22 @@ struct SwapList { const int32_t* out = nullptr; const int32_t* in = nullptr; int
 // swap.hip: one swap in one launch, from the control block t.ctrl, L.Minv and L.rec to *next, L.Minv2 and L.rec2 (the caller exchanges
 // them after every launch); at most `limit` iterations will have run, the last l.n of them the list's; tau_most: at most this many pivots
 // are pending.  A pivot whose products have not been computed ahead takes a launch of its own, which fetches them.
+// fetch_only: it does nothing else.
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int tau_most,
-                            hipStream_t s, const SwapList& l = SwapList());
+                            hipStream_t s, const SwapList& l = SwapList(), bool fetch_only = false);
+// swaprun.hip: the swaps up to `limit` iterations in one launch, between the same copies; it ends before a pivot whose products have not been
+// computed ahead, which launch_lazy_swap then fetches.  run: number of the launch since the records were last refreshed, below RUN_MOST;
+// patience: ticks of 10 ns that a workgroup waits for the others before all give up (SearchCtrl::stalled).  Lists: pairs only.
+// The workgroups wait for one another, so all have to be resident at once (swap_run_fits); with a list they don't.  Their shared words are
+// cleared with the records.  It takes ZT ZT^T from L.LL and leaves it in L.LL2 (exchanged after it, too), so all pending pivots have to come from runs.
+constexpr int RUN_MOST = 64;
+hipError_t launch_swap_run(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int run, uint32_t patience,
+                           hipStream_t s, const SwapList& l = SwapList());
+bool swap_run_fits(int64_t d1);
+int64_t swap_run_shared_words();
+// Rows per workgroup: one workgroup per compute unit where the rows allow it (8192 = 256 x 32, 16384 = 256 x 64, 28672 = 224 x 128).
+// More than 256 workgroups would run one after the other, and the algebra of order |T| is the same for each of them.
+constexpr int swap_rows_per_wg(int d1) { return d1 <= 8192 ? 32 : d1 <= 16384 ? 64 : 128; }
 int swap_record_count(int64_t d1);
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh);
 hipError_t launch_cand_gram(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, int ncand, hipStream_t s);

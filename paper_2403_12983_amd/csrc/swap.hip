@@ -1,4 +1,5 @@
-// One swap of the delayed-update search (q = 1) in one launch.
+// One swap of the delayed-update search (q = 1) in one launch: swaps that fetch products, removals, and layers or GPUs on which the workgroups
+// of many swaps in one launch (swaprun.hip) are not resident together.
 //
 // The tableau in HBM stays at its base state (N0, Z0) between two flushes; T is the set of pivots swept since, M = N0[T, T], x_h = M^-1
 // N0[T, h] (lazy.hip has the algebra).  The current row h of Z is z_h = Z0[h] - x_h^T Z0[T], so every inner product that a swap of
@@ -59,13 +60,15 @@ __device__ __forceinline__ void write_record(SwapRec* rec, const double* sc, con
   }
 }
 
-// the records of the scores as they stand (nothing pending); refresh: of the scores from the norms and the diagonal, after a flush
+// the records of the scores as they stand (nothing pending); refresh: of the scores from the norms and the diagonal, after a flush.
+// Clears the `words` shared words of the runs of swaps.
 template <int RPW>
 __global__ __launch_bounds__(128) void swap_records_kernel(LazyPtrs L, int d1, const int32_t* __restrict__ kept, double* __restrict__ score,
-                                                            const double* __restrict__ gram, const double* __restrict__ dblk, SearchCtrl* ctrl, int refresh) {
+                                                            const double* __restrict__ gram, const double* __restrict__ dblk, SearchCtrl* ctrl, int refresh, uint64_t* __restrict__ shared, int words) {
   __shared__ double sc[RPW];
   __shared__ int kp[RPW], sl[RPW];
   const int tid = threadIdx.x, row = blockIdx.x * RPW + tid;
+  for (int i = blockIdx.x * 128 + tid; i < words; i += gridDim.x * 128) shared[i] = 0;
   if (tid < RPW) {
     const bool in = row < d1;
     sc[tid] = !in ? 0.0 : refresh ? fresh_score(row, kept, gram, dblk, score, ctrl) : score[row]; kp[tid] = in ? (kept[row] != 0) : -1; sl[tid] = in ? L.cslot[row] : -1;
@@ -159,7 +162,7 @@ template <int NT, int RPW>
 __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* __restrict__ N0, const float* __restrict__ Z0, int d1, int m,
                                                         const SearchCtrl* __restrict__ cin, SearchCtrl* __restrict__ cout, int32_t* __restrict__ kept,
                                                         double* __restrict__ rho, double* __restrict__ diag, double* __restrict__ score, int always, int tau_most,
-                                                        const int32_t* __restrict__ list_g, const int32_t* __restrict__ list_j, int list_n, int list_step, int limit, int nwg, int32_t* __restrict__ trace_out,
+                                                        const int32_t* __restrict__ list_g, const int32_t* __restrict__ list_j, int list_n, int list_step, int limit, int fetch_only, int nwg, int32_t* __restrict__ trace_out,
                                                         int32_t* __restrict__ trace_in, float* __restrict__ trace_gap, double* __restrict__ trace_obj) {
   constexpr int TM = LAZY_TM, W = NT / 64, H = NT / 2;
   constexpr int TPR = NT / TM, MU = TM / (2 * TPR);             // threads per row of M^-1, pairs of columns per thread
@@ -274,7 +277,7 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   const bool pending = sg == PENDING || (!single && sj == PENDING);
   const int miss = (hit_g ? 0 : 1) | (hit_j ? 0 : 2), need = (hit_g ? 0 : 1) + (hit_j ? 0 : 1);
   enum { SWAP, IDLE, NONE, PAUSE, FETCH };
-  const int act = idle ? IDLE : (g < 0 || j < 0) ? NONE : (pending || tau + npiv > TM || spare + need > LAZY_NS) ? PAUSE : miss ? FETCH : SWAP;
+  const int act = idle ? IDLE : (g < 0 || j < 0) ? NONE : (pending || tau + npiv > TM || spare + need > LAZY_NS) ? PAUSE : miss ? FETCH : fetch_only ? IDLE : SWAP;
   if (__builtin_expect(act != SWAP, 0)) {      // laid out behind the swap: in between, its code made the swaps 2 % slower
     const int ng = (miss & 1) ? LAZY_NC + spare : sg, nj = (miss & 2) ? LAZY_NC + spare + (miss & 1) : sj;
     if (act == FETCH) fetch_products<NT>(L, Z0, d1, m, g, j, miss, ng, nj, spare + need);      // the next launch finds them
@@ -509,20 +512,17 @@ __global__ __launch_bounds__(NT) void lazy_swap_kernel(LazyPtrs L, const float* 
   write_record<RPW>(L.rec2 + wg, s_sc, s_kp, s_sl, wg * RPW, wave, lane);
 }
 
-// Rows per workgroup: one workgroup per compute unit where the rows allow it (8192 = 256 x 32, 16384 = 256 x 64, 28672 = 224 x 128).
-// More than 256 workgroups would run one after the other, and the algebra of order |T| is the same for each of them.
-static int swap_rows_per_wg(int d1) { return d1 <= 8192 ? 32 : d1 <= 16384 ? 64 : 128; }
 int swap_record_count(int64_t d1) { const int r = swap_rows_per_wg((int)d1); return (int)((d1 + r - 1) / r); }
 
 hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always, int limit, int tau_most,
-                            hipStream_t s, const SwapList& l) {
+                            hipStream_t s, const SwapList& l, bool fetch_only) {
   if (l.n < 0 || l.n > LIST_MOST || (l.n > 0 && !l.out)) return hipErrorInvalidValue;
   // rows of more than 4096 columns: a workgroup for every compute unit, so that a fetch of few long rows is not left to a few of them (100
   // swaps, 72 pivots fetched: 1000 x 16384 8.4 ms without, 6.4 so; 300 x 8192, 60 swaps 3.0 and 2.4)
   const int nwg = swap_record_count(d.d1), grid = d.m > 4096 ? std::max(nwg, 256) : nwg;
 #define OSSCAR_SWAP(NT, RPW)                                                                                                         \
   hipLaunchKernelGGL((lazy_swap_kernel<NT, RPW>), dim3(grid), dim3(NT), 0, s, L, t.N, t.Z, d.d1, d.m, t.ctrl, next, t.kept, t.gram, t.dblk, \
-                     t.score, always, tau_most, l.out, l.in, l.n, l.step, limit, nwg, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
+                     t.score, always, tau_most, l.out, l.in, l.n, l.step, limit, fetch_only ? 1 : 0, nwg, t.trace_out, t.trace_in, t.trace_gap, t.trace_obj)
   switch (swap_rows_per_wg(d.d1)) {
     case 32: OSSCAR_SWAP(512, 32); break;
     case 64: OSSCAR_SWAP(1024, 64); break;
@@ -533,11 +533,12 @@ hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& 
 }
 
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh) {
-  const int nwg = swap_record_count(d.d1), fr = refresh ? 1 : 0;
+  const int nwg = swap_record_count(d.d1), fr = refresh ? 1 : 0, words = (int)swap_run_shared_words();
+  uint64_t* shared = reinterpret_cast<uint64_t*>(L.run_shared);
   switch (swap_rows_per_wg(d.d1)) {
-    case 32: hipLaunchKernelGGL(swap_records_kernel<32>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr); break;
-    case 64: hipLaunchKernelGGL(swap_records_kernel<64>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr); break;
-    default: hipLaunchKernelGGL(swap_records_kernel<128>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr); break;
+    case 32: hipLaunchKernelGGL(swap_records_kernel<32>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr, shared, words); break;
+    case 64: hipLaunchKernelGGL(swap_records_kernel<64>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr, shared, words); break;
+    default: hipLaunchKernelGGL(swap_records_kernel<128>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr, shared, words); break;
   }
   return hipGetLastError();
 }

@@ -548,6 +548,45 @@ def test_swaps_in_one_launch(p, m, k, swaps):
             assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
 
 
+@pytest.mark.parametrize("p,m,k,swaps", [(31, 3, 15, 40), (32, 8, 16, 40), (600, 72, 300, 90), (8192, 40, 4000, 150), (8193, 8, 4100, 70),
+                                         (16384, 40, 8000, 66), (16385, 16, 8001, 66), (32768, 8, 16384, 66), (32769, 8, 16384, 10)])
+def test_runs_of_swaps(p, m, k, swaps):
+    """Many swaps in one launch, at the edges of the workgroups' rows and on either side of the 256 workgroups that can be resident together, and
+    moves of given pairs: the same swaps as with a launch each, also where every wait is given up at once.  Both ways are float64 algebra on
+    the same stored numbers, in another order: the objective agrees to 1e-9 (1e-16 times the square of |z0| / |z|, below 1e3 here), and the
+    choices part only where two groups score alike."""
+    pkg = _pkg()
+    g = torch.Generator(device=DEV).manual_seed(p)
+    X = torch.randn(2 * p + 64 if p < 1000 else 1024, p, generator=g, device=DEV) * torch.exp(0.5 * torch.randn(p, generator=g, device=DEV))
+    W = torch.randn(p, m, generator=g, device=DEV) / p ** 0.5
+    s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
+    s.osscar_gram(X, True, W, 0.0, 5e-2)
+    out = []
+    for flags in (pkg.OSSCAR_SEARCH_LAUNCH_PER_SWAP, 0, pkg.OSSCAR_SEARCH_IMPATIENT):
+        s.osscar_init_support()
+        r = s.osscar_local_search(swaps, 0.0, flags)
+        out.append((r, s.osscar_get_counters(), s.osscar_backsolve()))
+    moves = []
+    for flags in (pkg.OSSCAR_SEARCH_LAUNCH_PER_SWAP, 0):
+        s.osscar_init_support()
+        moves.append((s.osscar_block_search(5, min(7, k), 0.0, flags), s.osscar_backsolve()))
+    s.close()
+    (e, ce, (We, Se, _)) = out[0]
+    assert ce["runs"] == 0 and (out[1][1]["runs"] > 0) == (p <= 32768)
+    for r, c, (Wr, Sr, _) in out[1:]:
+        n = min(r["iters"], e["iters"])
+        same = (r["trace_out"][:n] == e["trace_out"][:n]) & (r["trace_in"][:n] == e["trace_in"][:n])
+        n = n if same.all() else int(np.argmin(same))
+        assert n == e["iters"] == r["iters"] or e["trace_gap"][n].min() <= 1e-9
+        assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-9, atol=0)
+        assert np.allclose(r["trace_gap"][:n], e["trace_gap"][:n], rtol=1e-5, atol=1e-9)
+        if n == e["iters"]:
+            assert r["accepted"] == e["accepted"] and Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-6 * torch.linalg.norm(We)
+    (a, (Wa, Sa, _)), (b, (Wb, Sb, _)) = moves
+    assert a["moves"] == b["moves"] and a["accepted"] == b["accepted"] and Sa.tolist() == Sb.tolist()
+    assert abs(a["obj_final"] - b["obj_final"]) <= 1e-9 * abs(a["obj_final"]) and torch.linalg.norm(Wa - Wb) <= 1e-6 * torch.linalg.norm(Wa)
+
+
 @pytest.mark.parametrize("target", [False, True])
 @pytest.mark.parametrize("d1,m,chunks", [(1096, 72, [1, 2048, 63, 700, 0]), (2048, 8, [2048] * 9), (2056, 520, [16384 - 128, 64, 64, 1, -130, 200]),
                                          (1504, 40, [5000, 20000, 5000, 0]), (8, 8, [70, 1, 300])])
