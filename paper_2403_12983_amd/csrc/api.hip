@@ -135,8 +135,16 @@ struct osscar_ctx {
   hipEvent_t ev_a = nullptr, ev_b = nullptr;
   hipEvent_t ev_s[EV_SAMPLES][3];
   hipEvent_t ev_g[2 * EV_SAMPLES];   // pairs around the launches of the Gram kernel of the last chunk call
-  struct Snap { SearchCtrl ctrl; int32_t pick[128]; float gap[2]; };
-  Snap* snap = nullptr;               // pinned host memory for reading the control block and a block move's picks
+  // Pinned host memory (one allocation): what the host waits for arrives here by one copy each, and the row lists leave from here without a wait
+  // (copies to and from pageable memory cost 20 - 60 us each, some thirty of them were a third of a small layer's time).
+  struct Snap { SearchCtrl ctrl; int32_t pick[128]; float gap[2]; double num[32]; };
+  Snap* snap = nullptr;
+  double* pin_norms = nullptr;        // p and 512 bytes: the norms; the removed groups and the gaps of the nested schedule
+  char* pin_rows = nullptr;           // kept, rowsK, rowsC as they lie on the device
+  int32_t* pin_kept = nullptr;        // p
+  char* pin_trace = nullptr; size_t pin_trace_bytes = 0;      // the four traces as they lie on the device; none beyond 1 MB
+  bool rows_leaving = false;          // pin_rows may not be written before the stream has been waited for
+  double obj = 0;                     // the tracked objective, when READY
   PackQueue queue;                    // bf16 rows of the layer that wait for their product
   SideStream side;   // the flush of the delayed-update search overlaps two of its products
   bool ev_ok = false;
@@ -293,6 +301,19 @@ osscar_status fail(osscar_ctx* c, osscar_status st, const char* fmt, ...) {
     if (e__ != hipSuccess) return fail((c), OSSCAR_EHIP, "%s failed: %s", #expr, hipGetErrorString(e__)); \
   } while (0)
 
+hipError_t wait(osscar_ctx* c) {
+  const hipError_t e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) c->rows_leaving = false;
+  return e;
+}
+// a control block on its way to the device as the argument of a launch, which takes no wait and no host memory
+__global__ void set_ctrl_kernel(SearchCtrl* dst, SearchCtrl h) { *dst = h; }
+hipError_t set_ctrl(const osscar_ctx* c, const SearchCtrl& h) {
+  hipLaunchKernelGGL(set_ctrl_kernel, dim3(1), dim3(1), 0, c->stream, c->ctrl, h);
+  return hipGetLastError();
+}
+__global__ void lambda_kernel(double* scal, double lambda_abs, double lambda_rel, int d1) { scal[1] = lambda_abs + lambda_rel * scal[0] / (double)d1; }
+
 TabDims dims(const osscar_ctx* c) { return TabDims{c->d1, c->m, c->p, c->q}; }
 TabPtrs ptrs(const osscar_ctx* c) {
   TabPtrs t{};
@@ -339,16 +360,22 @@ hipError_t big_gemm(const osscar_ctx* c, const I8Bufs* ib, int M, int N, int K, 
   return launch_gemm_f64acc(g, c->stream);
 }
 
-// Host copy of the membership flags -> sorted row lists on the device.
+// Host copy of the membership flags -> flags and sorted row lists on the device, in one copy (they lie behind one another).
 osscar_status upload_rows(osscar_ctx* c) {
-  std::vector<int32_t> rk, rc;
-  rk.reserve(c->kr); rc.reserve(c->cr);
+  if (c->rows_leaving) HIPCHK(c, wait(c));
+  const size_t at_k = (size_t)(reinterpret_cast<char*>(c->rowsK) - reinterpret_cast<char*>(c->kept));
+  const size_t at_c = (size_t)(reinterpret_cast<char*>(c->rowsC) - reinterpret_cast<char*>(c->kept));
+  int32_t *rk = reinterpret_cast<int32_t*>(c->pin_rows + at_k), *rc = reinterpret_cast<int32_t*>(c->pin_rows + at_c);
+  std::memcpy(c->pin_rows, c->kept_host.data(), (size_t)c->p * 4);
+  int nk = 0, nc = 0;
   for (int g = 0; g < c->p; g++)
-    for (int r = 0; r < c->q; r++) (c->kept_host[g] ? rk : rc).push_back(g * c->q + r);
-  if ((int)rk.size() != c->kr) return fail(c, OSSCAR_ESTATE, "internal: kept set has %zu rows, expected %d", rk.size(), c->kr);
-  HIPCHK(c, hipMemcpyAsync(c->rowsK, rk.data(), rk.size() * 4, hipMemcpyHostToDevice, c->stream));
-  if (!rc.empty()) HIPCHK(c, hipMemcpyAsync(c->rowsC, rc.data(), rc.size() * 4, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));   // the vectors die at return
+    for (int r = 0; r < c->q; r++) {
+      if (c->kept_host[g]) rk[nk++] = g * c->q + r;
+      else rc[nc++] = g * c->q + r;
+    }
+  if (nk != c->kr) return fail(c, OSSCAR_ESTATE, "internal: kept set has %d rows, expected %d", nk, c->kr);
+  HIPCHK(c, hipMemcpyAsync(c->kept, c->pin_rows, at_c + (size_t)nc * 4, hipMemcpyHostToDevice, c->stream));
+  c->rows_leaving = true;
   return OSSCAR_OK;
 }
 
@@ -400,21 +427,25 @@ osscar_status split_gemm(osscar_ctx* c, const SplitBufs& sp, const void* packA, 
 }
 
 // out[0] = max_i P_ii H_ii (the largest variance inflation factor 1 / (1 - R_i^2) of a kept row: how much of row i the other
-// kept rows explain), out[1] = 1 if any entry of the diagonal of P is not finite.  One workgroup.
-__global__ __launch_bounds__(1024) void vif_max_kernel(const float* __restrict__ P, const float* __restrict__ H, int n, double* __restrict__ out) {
+// kept rows explain), out[1] = 1 if any entry of the diagonal of P is not finite, out[2] = the largest of the 256 values part (NaN if one is),
+// out[3] = the pivot flag.  One workgroup.
+__global__ __launch_bounds__(1024) void vif_max_kernel(const float* __restrict__ P, const float* __restrict__ H, int n, const double* __restrict__ part,
+                                                       const int32_t* __restrict__ notpd, double* __restrict__ out) {
   __shared__ double sh[16];
   __shared__ int bad[16];
-  double v = 0.0; int b = 0;
+  __shared__ double most[16];
+  double v = 0.0, pm = threadIdx.x < 256 ? part[threadIdx.x] : 0.0; int b = 0;
   for (int i = threadIdx.x; i < n; i += 1024) {
     const double x = (double)P[(int64_t)i * n + i] * (double)H[(int64_t)i * n + i];
     if (!(x == x) || !(fabs(x) < 1e300)) b = 1; else v = fmax(v, x);
   }
-  for (int o = 32; o > 0; o >>= 1) { v = fmax(v, __shfl_down(v, o, 64)); b |= __shfl_down(b, o, 64); }
-  if ((threadIdx.x & 63) == 0) { sh[threadIdx.x >> 6] = v; bad[threadIdx.x >> 6] = b; }
+  auto larger = [](double x, double y) { return (y > x || y != y) ? y : x; };      // keeps a NaN
+  for (int o = 32; o > 0; o >>= 1) { v = fmax(v, __shfl_down(v, o, 64)); b |= __shfl_down(b, o, 64); pm = larger(pm, __shfl_down(pm, o, 64)); }
+  if ((threadIdx.x & 63) == 0) { sh[threadIdx.x >> 6] = v; bad[threadIdx.x >> 6] = b; most[threadIdx.x >> 6] = pm; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int i = 1; i < 16; i++) { v = fmax(v, sh[i]); b |= bad[i]; }
-    out[0] = v; out[1] = (double)b;
+    for (int i = 1; i < 16; i++) { v = fmax(v, sh[i]); b |= bad[i]; pm = larger(pm, most[i]); }
+    out[0] = v; out[1] = (double)b; out[2] = pm; out[3] = (double)*notpd;
   }
 }
 
@@ -436,10 +467,7 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
   osscar_status st = OSSCAR_OK;
   bool correct = false;          // does B = P G_K get its residual correction?
   TileRef t_low{}, t_b{};
-  if (sp) {
-    if ((st = stage_tiles(c, 0, kr, kr, true, &t_low)) != OSSCAR_OK) return st;
-    if ((st = stage_tiles(c, 1, kr, m, false, &t_b)) != OSSCAR_OK) return st;
-  }
+  if (sp && g_refined_inverse && (st = stage_tiles(c, 0, kr, kr, true, &t_low)) != OSSCAR_OK) return st;
   if (!g_refined_inverse) {
     // The sweep on a float64 copy of H_KK (in the memory of T1 and T2), rounded to float32 once: exact to that rounding.
     HIPCHK(c, hipEventRecord(c->ev_s[2][0], s));
@@ -447,16 +475,14 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
                               side_of(c)));
     HIPCHK(c, hipEventRecord(c->ev_s[2][1], s));
     HIPCHK(c, launch_absmax(b.P, (int64_t)kr * kr, c->partial, s));
-    hipLaunchKernelGGL(vif_max_kernel, dim3(1), dim3(1024), 0, s, b.P, b.HKK, kr, c->scal + 20);
-    double part[256], vif[2] = {0, 0}; int32_t bad = 0;
-    HIPCHK(c, hipMemcpyAsync(part, c->partial, sizeof part, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(vif, c->scal + 20, 16, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(&bad, c->notpd, 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    hipLaunchKernelGGL(vif_max_kernel, dim3(1), dim3(1024), 0, s, b.P, b.HKK, kr, c->partial, c->notpd, c->scal + 20);
+    HIPCHK(c, hipMemcpyAsync(c->snap->num + 16, c->scal + 20, 32, hipMemcpyDeviceToHost, s));
+    HIPCHK(c, wait(c));
+    const double* vif = c->snap->num + 16;
+    const double pmax = vif[2];      // a NaN anywhere in P makes it NaN
+    const int bad = vif[3] != 0.0;
     { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[2][0], c->ev_s[2][1]); c->timers[9] = ms; }
     c->timers[10] = 0; c->timers[11] = vif[0];
-    double pmax = 0;
-    for (double v : part) if (v > pmax || v != v) pmax = v;      // a NaN anywhere in P makes pmax NaN
     if (bad || vif[1] != 0.0 || !(pmax < 1e300) || !(vif[0] >= 0.999))
       return fail(c, OSSCAR_ENOTPD, "H restricted to the kept rows is not positive definite to working precision "
                                      "(pivot flag %d, largest |P| %.3g, largest P_ii H_ii %.3g)", bad, pmax, vif[0]);
@@ -495,7 +521,7 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
     double part[256]; int32_t bad = 0;
     HIPCHK(c, hipMemcpyAsync(part, c->partial, sizeof part, hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipMemcpyAsync(&bad, c->notpd, 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    HIPCHK(c, wait(c));
     { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[1][0], c->ev_s[1][1]); c->timers[10] = ms; }
     { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[2][0], c->ev_s[2][1]); c->timers[9] = ms; }
     double resid = 0;
@@ -525,6 +551,7 @@ osscar_status inverse_and_weights(osscar_ctx* c, const InvBufs& b, const float* 
   if (!correct) return OSSCAR_OK;
   HIPCHK(c, gemm(c, kr, m, kr, b.HKK, kr, b.T3, m, b.GK, m, b.T4, m, -1.0, 1.0));      // the residual: float64 accumulation
   if (sp) {
+    if ((st = stage_tiles(c, 1, kr, m, false, &t_b)) != OSSCAR_OK) return st;
     if ((st = pack_into(c, *sp, sp->packP, b.P, kr, kr, kr)) != OSSCAR_OK) return st;      // the refined inverse
     if ((st = pack_into(c, *sp, sp->packX, b.T4, m, kr, m)) != OSSCAR_OK) return st;
     if ((st = split_gemm(c, *sp, sp->packP, kr, sp->packX, m, kr, 3, t_b, b.T3, m, b.B, m, 1.0, 1.0)) != OSSCAR_OK) return st;
@@ -567,23 +594,19 @@ InvBufs carve_inv(osscar_ctx* c, Carve& cv) {
   return b;
 }
 
-// obj = c0 - <G_K, B>
-osscar_status objective_from(osscar_ctx* c, const float* GK, const float* B, double* obj) {
+// <G_K, B>, of obj = c0 - <G_K, B>: in snap->num[8] once the stream has been waited for
+osscar_status objective_dot(osscar_ctx* c, const float* GK, const float* B) {
   HIPCHK(c, launch_dot64(GK, B, (int64_t)c->kr * c->m, c->scal + 8, c->partial, c->stream));
-  double dot = 0;
-  HIPCHK(c, hipMemcpyAsync(&dot, c->scal + 8, 8, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  *obj = c->c0 - dot;
+  HIPCHK(c, hipMemcpyAsync(c->snap->num + 8, c->scal + 8, 8, hipMemcpyDeviceToHost, c->stream));
   return OSSCAR_OK;
 }
 
 // Builds N, Z, the scores and the tracked objective for the kept set in c->kept_host.
-osscar_status build_state(osscar_ctx* c, double* obj_out, const float* B_known = nullptr) {
+osscar_status build_state(osscar_ctx* c, double* obj_out, const float* B_known = nullptr, hipEvent_t last = nullptr) {
   hipStream_t s = c->stream;
   const int d1 = c->d1, m = c->m, kr = c->kr, cr = c->cr;
   osscar_status st = upload_rows(c);
   if (st != OSSCAR_OK) return st;
-  HIPCHK(c, hipMemcpyAsync(c->kept, c->kept_host.data(), c->p * 4, hipMemcpyHostToDevice, s));
   Carve cv(c->scratch);
   InvBufs b = carve_inv(c, cv);
   float* HKC = cv.take<float>((int64_t)kr * cr);
@@ -615,30 +638,31 @@ osscar_status build_state(osscar_ctx* c, double* obj_out, const float* B_known =
   }
   HIPCHK(c, launch_scatter(b.P, kr, c->rowsK, kr, c->rowsK, kr, c->N, d1, -1.f, 1, s));
   HIPCHK(c, launch_scatter_rows(b.B, m, c->rowsK, kr, m, c->Z, m, 0, s));
-  double obj = 0;
-  if (c->have_Wdense && c->dense_is_exact) {
+  const bool pruned_rows = c->have_Wdense && c->dense_is_exact;
+  if (pruned_rows) {
     // obj(K) = c0 - <G_K, B> = <W_c, R_c> over the pruned rows c (B = W_K + V W_c, so <G_K, B> = <G_K, W_K> + <V^T G_K, W_c>).
     // The first form subtracts two numbers of the size of c0 and inherits the float32 rounding of B at that size; the
     // second has terms of the size of the loss itself, which matters when the kept rows carry most of Tr(W^T H W).
     if (cr > 0) {
       HIPCHK(c, launch_dot64_rows(c->Wdense, c->rowsC, R, cr, m, c->scal + 8, c->partial, s));
-      HIPCHK(c, hipMemcpyAsync(&obj, c->scal + 8, 8, hipMemcpyDeviceToHost, s));
+      HIPCHK(c, hipMemcpyAsync(c->snap->num + 8, c->scal + 8, 8, hipMemcpyDeviceToHost, s));
     }
-    HIPCHK(c, hipStreamSynchronize(s));
-  } else {
-    st = objective_from(c, b.GK, b.B, &obj);     // synchronises the stream
-    if (st != OSSCAR_OK) return st;
+  } else if ((st = objective_dot(c, b.GK, b.B)) != OSSCAR_OK) {
+    return st;
   }
   HIPCHK(c, launch_refresh_scores(dims(c), ptrs(c), s));      // last: groups of several rows use the start of the scratch
+  if (last) HIPCHK(c, hipEventRecord(last, s));
+  HIPCHK(c, wait(c));
+  const double obj = !pruned_rows ? c->c0 - c->snap->num[8] : cr > 0 ? c->snap->num[8] : 0.0;
   if (cr > 0) { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[0][0], c->ev_s[0][1]); c->timers[12] = ms; }
   if (obj_out) *obj_out = obj;
   return OSSCAR_OK;
 }
 
 osscar_status read_kept(osscar_ctx* c) {
-  c->kept_host.resize(c->p);
-  HIPCHK(c, hipMemcpyAsync(c->kept_host.data(), c->kept, c->p * 4, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  HIPCHK(c, hipMemcpyAsync(c->pin_kept, c->kept, (size_t)c->p * 4, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, wait(c));
+  c->kept_host.assign(c->pin_kept, c->pin_kept + c->p);
   return OSSCAR_OK;
 }
 
@@ -712,7 +736,19 @@ osscar_status osscar_create(osscar_ctx** out, const osscar_desc* desc, void* wor
   for (int i = 0; i < EV_SAMPLES && c->ev_ok; i++)
     for (int j = 0; j < 3; j++) c->ev_ok = c->ev_ok && (hipEventCreate(&c->ev_s[i][j]) == hipSuccess);
   for (int i = 0; i < 2 * EV_SAMPLES && c->ev_ok; i++) c->ev_ok = c->ev_ok && (hipEventCreate(&c->ev_g[i]) == hipSuccess);
-  c->ev_ok = c->ev_ok && hipHostMalloc(reinterpret_cast<void**>(&c->snap), sizeof(*c->snap), hipHostMallocDefault) == hipSuccess;
+  {
+    const size_t rows = (size_t)(reinterpret_cast<char*>(c->rowsC + c->d1) - reinterpret_cast<char*>(c->kept));
+    size_t trace = (size_t)(reinterpret_cast<char*>(c->trace_obj + std::max(c->desc.max_swaps, 1)) - reinterpret_cast<char*>(c->trace_out));
+    if (trace > ((size_t)1 << 20)) trace = 0;
+    const size_t at_norms = align_up(sizeof(*c->snap)), at_rows = at_norms + align_up((size_t)c->p * 8) + 512, at_kept = at_rows + align_up(rows);
+    const size_t at_trace = at_kept + align_up((size_t)c->p * 4);
+    char* pin = nullptr;
+    c->ev_ok = c->ev_ok && hipHostMalloc(reinterpret_cast<void**>(&pin), at_trace + trace + 256, hipHostMallocDefault) == hipSuccess;
+    if (c->ev_ok) {
+      c->snap = reinterpret_cast<osscar_ctx::Snap*>(pin); c->pin_norms = reinterpret_cast<double*>(pin + at_norms); c->pin_rows = pin + at_rows;
+      c->pin_kept = reinterpret_cast<int32_t*>(pin + at_kept); c->pin_trace = pin + at_trace; c->pin_trace_bytes = trace;
+    }
+  }
   c->ev_ok = c->ev_ok && hipStreamCreateWithFlags(&c->side.stream, hipStreamNonBlocking) == hipSuccess &&
              hipEventCreateWithFlags(&c->side.fork, hipEventDisableTiming) == hipSuccess &&
              hipEventCreateWithFlags(&c->side.join, hipEventDisableTiming) == hipSuccess;
@@ -756,7 +792,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   Carve cv(c->scratch);
   const int h_copies = h_copies_of(c->desc, c->extras), g_copies = g_copies_of(c->desc, c->extras);
   double* H64 = cv.take<double>((int64_t)d1 * d1 * h_copies);
-  float* Wf = cv.take<float>((int64_t)d1 * m);
+  float* const Wf = c->Wdense;
   void* Xt = cv.take<char>(gram_stage_bytes(d1));
   double* G64 = nullptr; void* Ys = nullptr;
   if (c->desc.target_output) {
@@ -778,7 +814,7 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   const PackedGram packed{&c->queue, d1, PackedAcc{H64, h_copies, &c->h_copies}, c->tiles_h, Xt, m, PackedAcc{G64, g_copies, &c->g_copies}, c->tiles_g,
                           target ? Ys : nullptr, (int)(PACK_ROWS / 64), target ? nullptr : c->ev_g, EV_SAMPLES};
   if (n_c > 0) {
-    HIPCHK(c, hipEventRecord(c->ev_a, s));
+    if (finalize) HIPCHK(c, hipEventRecord(c->ev_a, s));      // (the last call's time is the one that is kept)
     const bool bf16 = c->desc.x_dtype == OSSCAR_BF16;
     bool fast = bf16 && (d1 % 8 == 0) && (conv || ((ldx % 8 == 0) && ((reinterpret_cast<uintptr_t>(Xc) & 15) == 0)));
     if (target) fast = fast && (m % 8 == 0) && (ldy % 8 == 0) && ((reinterpret_cast<uintptr_t>(Yc) & 15) == 0);
@@ -833,34 +869,28 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
         }
       }
     }
-    HIPCHK(c, hipEventRecord(c->ev_b, s));
-    if (finalize) c->timers[0] += elapsed(c);
+    if (finalize) HIPCHK(c, hipEventRecord(c->ev_b, s));
   }
   if (!finalize) return OSSCAR_OK;
 
+  bool timed = n_c > 0;
   if (c->queue.stages > 0) {      // a call without rows finalizes
     HIPCHK(c, hipEventRecord(c->ev_a, s));
     HIPCHK(c, launch_gram_queue(packed, s));
     HIPCHK(c, hipEventRecord(c->ev_b, s));
-    c->timers[0] += elapsed(c);
+    timed = true;
   }
-  HIPCHK(c, hipEventRecord(c->ev_a, s));
+  HIPCHK(c, hipEventRecord(c->ev_s[1][0], s));
   HIPCHK(c, launch_sum_copies(H64, c->h_copies, d1, d1, 1, s));
   HIPCHK(c, launch_trace64(H64, d1, c->scal, s));
-  double tr = 0;
-  HIPCHK(c, hipMemcpyAsync(&tr, c->scal, 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipStreamSynchronize(s));
-  c->lambda = lambda_abs + lambda_rel * tr / d1;
-  HIPCHK(c, hipMemcpyAsync(c->scal + 1, &c->lambda, 8, hipMemcpyHostToDevice, s));
+  hipLaunchKernelGGL(lambda_kernel, dim3(1), dim3(1), 0, s, c->scal, lambda_abs, lambda_rel, d1);
   HIPCHK(c, launch_finalize_H(H64, c->H, d1, c->scal + 1, s));
   HIPCHK(c, launch_convert_to_f32(W, c->desc.w_dtype == OSSCAR_BF16, d1, m, ldw, Wf, s));
-  double yy = 0;
   if (target) {
     // G = X^T Y + lambda W, c0 = ||Y||^2 + lambda ||W||^2
     HIPCHK(c, launch_sum_copies(G64, c->g_copies, d1, m, 0, s));
     HIPCHK(c, launch_finalize_G(G64, Wf, c->scal + 1, c->G, (int64_t)d1 * m, s));
     HIPCHK(c, launch_dot64(Wf, Wf, (int64_t)d1 * m, c->scal + 2, c->partial, s));
-    HIPCHK(c, hipMemcpyAsync(&yy, c->scal + 12, 8, hipMemcpyDeviceToHost, s));
   } else {
     // G = H W.  bf16 W: three bf16-MFMA products with the pieces of H, in the memory the float64 Gram accumulator has
     // just left; otherwise (or if that memory is too small) the float64-accumulating GEMM.
@@ -897,21 +927,18 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     HIPCHK(c, launch_dot64(Wf, c->G, (int64_t)d1 * m, c->scal + 2, c->partial, s));
   }
   HIPCHK(c, launch_group_norms(Wf, c->p, c->q, m, c->norms2, s));
-  c->norms_host.resize(c->p);
-  HIPCHK(c, hipMemcpyAsync(&c->c0, c->scal + 2, 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipMemcpyAsync(c->norms_host.data(), c->norms2, c->p * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipEventRecord(c->ev_b, s));
-  HIPCHK(c, hipStreamSynchronize(s));
-  c->have_Wdense = false;
-  if (!target) {
-    HIPCHK(c, hipMemcpyAsync(c->Wdense, Wf, (size_t)d1 * m * 4, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipStreamSynchronize(s));
-    c->have_Wdense = true;
-  }
-  if (target) c->c0 = yy + c->lambda * c->c0;
+  HIPCHK(c, hipMemcpyAsync(c->snap->num, c->scal, 16 * 8, hipMemcpyDeviceToHost, s));
+  HIPCHK(c, hipMemcpyAsync(c->pin_norms, c->norms2, (size_t)c->p * 8, hipMemcpyDeviceToHost, s));
+  HIPCHK(c, hipEventRecord(c->ev_s[1][1], s));
+  HIPCHK(c, wait(c));
+  c->lambda = c->snap->num[1]; c->c0 = c->snap->num[2];
+  c->norms_host.assign(c->pin_norms, c->pin_norms + c->p);
+  c->have_Wdense = !target;
+  if (timed) c->timers[0] += elapsed(c);
+  if (target) c->c0 = c->snap->num[12] + c->lambda * c->c0;
   else { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[0][0], c->ev_s[0][1]); c->timers[8] = ms; }
   c->dense_is_exact = !target;
-  c->timers[1] = elapsed(c);
+  { float ms = 0; hipEventElapsedTime(&ms, c->ev_s[1][0], c->ev_s[1][1]); c->timers[1] = ms; }
   {   // mean duration of the Gram kernel's launches in the last chunk call that took the matrix-core path
     double tot = 0; int n = 0;
     for (int i = 0; i < c->queue.ev_used; i++) {
@@ -956,7 +983,7 @@ osscar_status osscar_set_quadratic(osscar_ctx* c, const float* H_dev, const floa
   hipStream_t s = c->stream;
   HIPCHK(c, hipMemcpyAsync(c->H, H_dev, (size_t)c->d1 * c->d1 * 4, hipMemcpyDeviceToDevice, s));
   HIPCHK(c, hipMemcpyAsync(c->G, G_dev, (size_t)c->d1 * c->m * 4, hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, wait(c));
   c->c0 = c0; c->lambda = 0; c->dense_is_exact = false; c->have_Wdense = false;
   c->norms_host.assign(norms, norms + c->p);
   c->phase = osscar_ctx::FINAL;
@@ -970,10 +997,11 @@ osscar_status osscar_init_support(osscar_ctx* c, int mode, const int32_t* groups
     return fail(c, OSSCAR_ESTATE, "osscar_init_support: no quadratic form yet (call osscar_gram with finalize first)");
   c->kept_host.assign(c->p, 0);
   if (mode == OSSCAR_INIT_MAGNITUDE) {
-    std::vector<int32_t> order(c->p);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return c->norms_host[a] > c->norms_host[b]; });
-    for (int i = 0; i < c->k; i++) c->kept_host[order[i]] = 1;
+    // the k largest norms, of equal ones the lower group (a NaN is below everything)
+    std::vector<std::pair<double, int32_t>> order(c->p);
+    for (int g = 0; g < c->p; g++) { const double v = c->norms_host[g]; order[g] = {v == v ? -v : INFINITY, g}; }
+    std::nth_element(order.begin(), order.begin() + (c->k - 1), order.end());
+    for (int i = 0; i < c->k; i++) c->kept_host[order[i].second] = 1;
   } else if (mode == OSSCAR_INIT_GIVEN) {
     if (!groups) return fail(c, OSSCAR_EINVAL, "osscar_init_support: groups_host is NULL");
     for (int i = 0; i < c->k; i++) {
@@ -986,25 +1014,31 @@ osscar_status osscar_init_support(osscar_ctx* c, int mode, const int32_t* groups
   }
   HIPCHK(c, hipEventRecord(c->ev_a, c->stream));
   double obj = 0;
-  st = build_state(c, &obj);
+  st = build_state(c, &obj, nullptr, c->ev_b);
   if (st != OSSCAR_OK) return st;
+  c->timers[2] = elapsed(c);
   SearchCtrl h{};
   h.obj = obj; h.g_out = -1; h.g_in = -1;
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipEventRecord(c->ev_b, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  c->timers[2] = elapsed(c);
+  HIPCHK(c, set_ctrl(c, h));
+  c->obj = obj;
   if (obj_host) *obj_host = obj;
   c->phase = osscar_ctx::READY;
   return OSSCAR_OK;
 }
 
-static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h, const SearchCtrl* from = nullptr) {
-  // through pinned memory: the search waits on this copy once per 64 swaps with the device idle meanwhile
-  SearchCtrl* dst = &c->snap->ctrl;
-  HIPCHK(c, hipMemcpyAsync(dst, from ? from : c->ctrl, sizeof *h, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  *h = *dst;
+// The control block (and a block move's picks and gaps) to pinned memory by one launch, which is what a copy is, too: the search waits for it
+// once per 64 swaps or per move, with the device idle meanwhile.
+__global__ __launch_bounds__(128) void report_kernel(const SearchCtrl* __restrict__ ctrl, const int32_t* __restrict__ pick, const float* __restrict__ gap,
+                                                     osscar_ctx::Snap* __restrict__ out) {
+  const int t = threadIdx.x;
+  if (t == 0) out->ctrl = *ctrl;
+  if (pick) { out->pick[t] = pick[t]; if (t < 2) out->gap[t] = gap[t]; }
+}
+static osscar_status read_ctrl(osscar_ctx* c, SearchCtrl* h, const SearchCtrl* from = nullptr, bool picks = false) {
+  hipLaunchKernelGGL(report_kernel, dim3(1), dim3(128), 0, c->stream, from ? from : c->ctrl, picks ? c->g_pick : nullptr, c->g_gap, c->snap);
+  HIPCHK(c, hipGetLastError());
+  HIPCHK(c, wait(c));
+  *h = c->snap->ctrl;
   return OSSCAR_OK;
 }
 
@@ -1085,7 +1119,7 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
   h.obj = c->dense_is_exact ? 0.0 : obj;   // the dense layer reproduces its own output exactly; a target output it does not
   h.g_out = -1; h.g_in = -1; h.tau = 0; h.tau_inc = 0; h.pause = 0;
   h.spare = spare_start((flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 1);
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
+  HIPCHK(c, set_ctrl(c, h));
   TabDims d = dims(c);
   TabPtrs t = ptrs(c);
   t.trace_out = c->g_removed; t.trace_in = nullptr; t.trace_gap = nullptr; t.trace_obj = nullptr;
@@ -1182,16 +1216,16 @@ osscar_status osscar_init_greedy(osscar_ctx* c, int32_t t_hat, int32_t refresh_e
   if (st != OSSCAR_OK) return st;
   if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_init_greedy: a pivot block lost definiteness after %d removals", h.iters);
   if (h.iters != expected) return fail(c, OSSCAR_ESTATE, "internal: osscar_init_greedy applied %d of %d removals", h.iters, expected);
-  st = read_kept(c);
-  if (st != OSSCAR_OK) return st;
-  st = upload_rows(c);
-  if (st != OSSCAR_OK) return st;
   h.done = 0; h.iters = 0; h.accepted = 0;
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
-  if (removed_host && p > k) HIPCHK(c, hipMemcpyAsync(removed_host, c->g_removed, (size_t)(p - k) * 4, hipMemcpyDeviceToHost, s));
-  if (gaps_host && iter > 0) HIPCHK(c, hipMemcpyAsync(gaps_host, c->g_gap, (size_t)iter * 4, hipMemcpyDeviceToHost, s));
+  HIPCHK(c, set_ctrl(c, h));
+  c->obj = h.obj;
+  const size_t at_gap = (size_t)(reinterpret_cast<char*>(c->g_gap) - reinterpret_cast<char*>(c->g_removed));      // (they lie behind one another)
+  char* const pin = reinterpret_cast<char*>(c->pin_norms);
+  HIPCHK(c, hipMemcpyAsync(pin, c->g_removed, at_gap + (size_t)iter * 4, hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipEventRecord(c->ev_b, s));
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, wait(c));
+  if (removed_host && p > k) std::memcpy(removed_host, pin, (size_t)(p - k) * 4);
+  if (gaps_host && iter > 0) std::memcpy(gaps_host, pin + at_gap, (size_t)iter * 4);
   c->timers[2] = elapsed(c);
   if (obj_host) *obj_host = h.obj;
   c->phase = osscar_ctx::READY;
@@ -1207,16 +1241,13 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     return fail(c, OSSCAR_EINVAL, "osscar_local_search: max_swaps %d outside [0, desc.max_swaps = %d] or rel_tol < 0", max_swaps, c->desc.max_swaps);
   hipStream_t s = c->stream;
   SearchCtrl h{};
-  st = read_ctrl(c, &h);
-  if (st != OSSCAR_OK) return st;
-  const double obj0 = h.obj;
+  const double obj0 = h.obj = c->obj;
   h.done = (c->cr == 0) ? 1 : 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1;
   h.pause = 0; h.tau = 0; h.tau_inc = 0; h.misses = 0; h.stalled = 0;
   const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
   h.spare = spare_start(la_mode);
   for (auto& v : c->counters) v = 0;
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, set_ctrl(c, h));
   const int always = (flags & OSSCAR_SEARCH_ALWAYS_ACCEPT) ? 1 : 0;
   TabDims d = dims(c);
   TabPtrs t = ptrs(c);
@@ -1307,7 +1338,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
         h.pause = 0; h.tau = 0; h.tau_inc = 0;
       }
       if (want_refresh) {
-        if (flush_open) { HIPCHK(c, hipStreamSynchronize(s)); collect(); }      // the refresh times itself with the same events
+        if (flush_open) { HIPCHK(c, wait(c)); collect(); }      // the refresh times itself with the same events
         hipEvent_t r0 = c->ev_s[0][0], r1 = c->ev_s[0][1];
         HIPCHK(c, hipEventRecord(r0, s));
         st = read_kept(c);
@@ -1319,7 +1350,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
         HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(run.t.ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
         HIPCHK(c, run.init());     // selection records and look-ahead products of the rebuilt state
         HIPCHK(c, hipEventRecord(r1, s));
-        HIPCHK(c, hipStreamSynchronize(s));
+        HIPCHK(c, wait(c));
         float ms = 0; hipEventElapsedTime(&ms, r0, r1); refresh_ms += ms;
         since_refresh_base = h.accepted;
         h.obj = obj;
@@ -1327,13 +1358,16 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     }
     if (h.tau + h.tau_inc > 0) { st = flush(); if (st != OSSCAR_OK) return st; }
     HIPCHK(c, run.settle());
-    if (flush_open) { HIPCHK(c, hipStreamSynchronize(s)); collect(); }
+    if (flush_open) { HIPCHK(c, wait(c)); collect(); }
     c->timers[6] = refresh_ms + flush_ms;
     c->counters[0] = flushes; c->counters[1] = pauses; c->counters[2] = h.misses; c->counters[3] = h.iters; c->counters[4] = run.all_runs;
   } else {
-  const int BATCH = 32;
+  // Searches of groups often end after a few moves, and a move enqueued past the end is four idle launches (10 us): batches of 4, 8, 16, 32, ...
+  // (32 from the start: a layer of 32 groups of 64 rows that makes six moves took 0.25 ms longer; a wait costs 20 us).
+  int batch = 4;
   while (launched < max_swaps && !h.done) {
-    int nb = std::min(BATCH, max_swaps - launched);
+    int nb = std::min(batch, max_swaps - launched);
+    batch = std::min(2 * batch, 32);
     if (refresh_every > 0) nb = std::min(nb, std::max(1, refresh_every - (h.accepted - since_refresh_base)));
     const bool sample = samples + 1 < EV_SAMPLES;
     for (int i = 0; i < nb; i++) {
@@ -1360,7 +1394,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       if (st != OSSCAR_OK) return st;
       HIPCHK(c, hipMemcpyAsync(reinterpret_cast<char*>(c->ctrl) + offsetof(SearchCtrl, obj), &obj, 8, hipMemcpyHostToDevice, s));
       HIPCHK(c, hipEventRecord(r1, s));
-      HIPCHK(c, hipStreamSynchronize(s));
+      HIPCHK(c, wait(c));
       float ms = 0; hipEventElapsedTime(&ms, r0, r1); refresh_ms += ms;
       since_refresh_base = h.accepted;
       h.obj = obj;
@@ -1369,19 +1403,34 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
   c->timers[6] = refresh_ms;
   }
   HIPCHK(c, hipEventRecord(c->ev_b, s));
+  // the traces beside the control block: the host knows how many iterations have run
+  const int known = h.iters;
+  const bool any = known > 0 && (t_out || t_in || t_gap || t_obj);
+  const bool pinned = any && c->pin_trace_bytes > 0;
+  if (pinned)
+    HIPCHK(c, hipMemcpyAsync(c->pin_trace, c->trace_out, (size_t)(reinterpret_cast<char*>(c->trace_obj + known) - reinterpret_cast<char*>(c->trace_out)),
+                             hipMemcpyDeviceToHost, s));
   st = read_ctrl(c, &h);
   if (st != OSSCAR_OK) return st;
+  if (h.iters != known) return fail(c, OSSCAR_ESTATE, "internal: osscar_local_search lost count of its iterations");
+  c->obj = h.obj;
   c->timers[3] = elapsed(c);
   c->timers[5] = samples ? upd_n_ms / samples : 0;
   c->timers[7] = samples ? upd_z_ms / samples : 0;
   if (res) { res->iters = h.iters; res->accepted = h.accepted; res->obj_initial = obj0; res->obj_final = h.obj; }
-  const int n = h.iters;
-  if (n > 0) {
+  const size_t n = (size_t)known;
+  if (any && !pinned) {
     if (t_out) HIPCHK(c, hipMemcpyAsync(t_out, c->trace_out, n * 4, hipMemcpyDeviceToHost, s));
     if (t_in) HIPCHK(c, hipMemcpyAsync(t_in, c->trace_in, n * 4, hipMemcpyDeviceToHost, s));
     if (t_gap) HIPCHK(c, hipMemcpyAsync(t_gap, c->trace_gap, n * 8, hipMemcpyDeviceToHost, s));
     if (t_obj) HIPCHK(c, hipMemcpyAsync(t_obj, c->trace_obj, n * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    HIPCHK(c, wait(c));
+  } else if (any) {
+    auto from = [&](const void* dev) { return c->pin_trace + (reinterpret_cast<const char*>(dev) - reinterpret_cast<const char*>(c->trace_out)); };
+    if (t_out) std::memcpy(t_out, from(c->trace_out), n * 4);
+    if (t_in) std::memcpy(t_in, from(c->trace_in), n * 4);
+    if (t_gap) std::memcpy(t_gap, from(c->trace_gap), n * 8);
+    if (t_obj) std::memcpy(t_obj, from(c->trace_obj), n * 8);
   }
   return OSSCAR_OK;
 }
@@ -1395,14 +1444,11 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
     return fail(c, OSSCAR_EINVAL, "osscar_block_search: max_iters %d < 0, block %d outside [1, 64] or rel_tol < 0", max_iters, block);
   hipStream_t s = c->stream;
   SearchCtrl h{};
-  st = read_ctrl(c, &h);
-  if (st != OSSCAR_OK) return st;
-  const double obj0 = h.obj;
+  const double obj0 = h.obj = c->obj;
   h.done = 0; h.iters = 0; h.accepted = 0; h.notpd = 0; h.rel_tol = rel_tol; h.g_out = h.g_in = -1; h.pause = 0; h.tau = 0; h.tau_inc = 0;
   const int la_mode = (flags & OSSCAR_SEARCH_NO_LOOKAHEAD) ? 2 : 0;
   h.spare = spare_start(la_mode);
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, s));
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, set_ctrl(c, h));
   const bool always = (flags & OSSCAR_SEARCH_ALWAYS_ACCEPT) != 0;
   const bool use_lazy = (c->q == 1) && !(flags & OSSCAR_SEARCH_EAGER);
   const int take = std::min<int>(block, std::min(c->k, c->p - c->k));
@@ -1434,7 +1480,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
         const int misses = h.misses;
         if (owed) HIPCHK(c, run.swap(1, last, list, true));
         HIPCHK(c, run.run(1, last, take - idx, RUN_PATIENCE, list));
-        osscar_status q = read_ctrl(c, &h, run.t.ctrl);
+        osscar_status q = read_ctrl(c, &h, run.t.ctrl, use_lazy);
         if (q != OSSCAR_OK) return q;
         run.tau_most = h.tau;
         if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_block_search: a pivot lost definiteness in move %d", blocks);
@@ -1457,7 +1503,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
       if (use_lazy) for (int r = 0; r < launches; r++) HIPCHK(c, run.swap(1, last, list));
       else for (int r = idx; r < take; r++) HIPCHK(c, launch_search_iteration(d, t, c->snap->pick[out(r)], c->snap->pick[inn(r)], 1, s));
       const int misses = h.misses;
-      osscar_status q = read_ctrl(c, &h, run.t.ctrl);
+      osscar_status q = read_ctrl(c, &h, run.t.ctrl, use_lazy);
       if (q != OSSCAR_OK) return q;
       run.tau_most = h.tau;
       if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_block_search: a pivot lost definiteness in move %d", blocks);
@@ -1478,9 +1524,7 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   while (take > 0 && blocks < max_iters) {
     if (use_lazy && pending + 2 * take > LAZY_TM) { HIPCHK(c, run.flush()); pending = 0; h.spare = run.L.spare0; }
     HIPCHK(c, launch_greedy_pick(d, run.t, take, c->g_pick, c->g_gap, s, 2));
-    HIPCHK(c, hipMemcpyAsync(c->snap->pick, c->g_pick, sizeof c->snap->pick, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(c->snap->gap, c->g_gap, sizeof c->snap->gap, hipMemcpyDeviceToHost, s));
-    if (!use_lazy) HIPCHK(c, hipStreamSynchronize(s));
+    if (!use_lazy && (st = read_ctrl(c, &h, run.t.ctrl, true)) != OSSCAR_OK) return st;      // (else with the move's control block)
     const double obj_before = h.obj;
     st = run_pairs(false);
     if (st != OSSCAR_OK) return st;
@@ -1508,7 +1552,8 @@ osscar_status osscar_block_search(osscar_ctx* c, int32_t max_iters, int32_t bloc
   if (use_lazy && pending > 0) HIPCHK(c, run.flush());
   HIPCHK(c, run.settle());
   HIPCHK(c, hipEventRecord(c->ev_b, s));
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, wait(c));
+  c->obj = h.obj;
   c->timers[3] = elapsed(c);
   if (res) { res->iters = blocks; res->accepted = accepted; res->obj_initial = obj0; res->obj_final = h.obj; }
   return OSSCAR_OK;
@@ -1526,14 +1571,14 @@ osscar_status osscar_apply_swap(osscar_ctx* c, int32_t g_out, int32_t g_in) {
   st = read_ctrl(c, &h);
   if (st != OSSCAR_OK) return st;
   h.done = 0; h.iters = 0; h.notpd = 0; h.pause = 0; h.tau = 0; h.tau_inc = 0;
-  HIPCHK(c, hipMemcpyAsync(c->ctrl, &h, sizeof h, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  HIPCHK(c, set_ctrl(c, h));
   TabPtrs t = ptrs(c);
   t.trace_out = nullptr;
   HIPCHK(c, launch_search_iteration(dims(c), t, g_out, g_in, 1, c->stream));
   st = read_ctrl(c, &h);
   if (st != OSSCAR_OK) return st;
   if (h.notpd) return fail(c, OSSCAR_ENOTPD, "osscar_apply_swap: pivot block not definite");
+  c->obj = h.obj;
   return OSSCAR_OK;
 }
 
@@ -1590,9 +1635,9 @@ osscar_status osscar_backsolve(osscar_ctx* c, void* What, int64_t ldw_hat, int32
       HIPCHK(c, launch_dot64(b.T3, b.T3, (int64_t)kr * m, c->scal + 9, c->partial, s));
       HIPCHK(c, launch_dot64(b.B, b.B, (int64_t)kr * m, c->scal + 10, c->partial + 1024, s));
       hipLaunchKernelGGL(add_inplace_kernel, dim3(grid_for((int64_t)kr * m)), dim3(256), 0, s, b.B, b.T3, (int64_t)kr * m);
-      double nn[2] = {0, 0};
-      HIPCHK(c, hipMemcpyAsync(nn, c->scal + 9, 16, hipMemcpyDeviceToHost, s));
-      HIPCHK(c, hipStreamSynchronize(s));
+      const double* nn = c->snap->num + 20;
+      HIPCHK(c, hipMemcpyAsync(c->snap->num + 20, c->scal + 9, 16, hipMemcpyDeviceToHost, s));
+      HIPCHK(c, wait(c));
       const double ratio = std::sqrt(nn[0] / std::max(nn[1], 1e-300));
       if (!(ratio < 1e-2)) break;             // the maintained inverse is not good enough: refactorise
       if (ratio < 1e-4) ok = true;            // what is left is ratio * |I - P H_KK| <= 1e-6: below the float32 storage of B
@@ -1604,13 +1649,12 @@ osscar_status osscar_backsolve(osscar_ctx* c, void* What, int64_t ldw_hat, int32
   }
   HIPCHK(c, launch_fill_rows_zero(What, ldw_hat, c->d1, c->m, out_dtype == OSSCAR_BF16, s));
   HIPCHK(c, launch_scatter_rows(b.B, c->m, c->rowsK, c->kr, c->m, What, ldw_hat, out_dtype == OSSCAR_BF16, s));
-  double obj = 0;
-  st = objective_from(c, b.GK, b.B, &obj);
+  st = objective_dot(c, b.GK, b.B);
   if (st != OSSCAR_OK) return st;
   HIPCHK(c, hipEventRecord(c->ev_b, s));
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, wait(c));
   c->timers[4] = elapsed(c);
-  if (obj_host) *obj_host = obj;
+  if (obj_host) *obj_host = c->c0 - c->snap->num[8];
   if (support) {
     int n = 0;
     for (int g = 0; g < c->p; g++) if (c->kept_host[g]) support[n++] = g;
@@ -1630,7 +1674,7 @@ osscar_status osscar_get_tensor(osscar_ctx* c, int which, void* dst, size_t dst_
     size_t b = (which == OSSCAR_T_H ? d1 * d1 : d1 * m) * 4;
     if (!need(b)) return fail(c, OSSCAR_EINVAL, "osscar_get_tensor: destination too small");
     HIPCHK(c, hipMemcpyAsync(dst, which == OSSCAR_T_H ? c->H : c->G, b, hipMemcpyDeviceToDevice, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    HIPCHK(c, wait(c));
     return OSSCAR_OK;
   }
   if (c->phase != osscar_ctx::READY) return fail(c, OSSCAR_ESTATE, "osscar_get_tensor: no search state yet");
@@ -1640,7 +1684,7 @@ osscar_status osscar_get_tensor(osscar_ctx* c, int which, void* dst, size_t dst_
     if (!need((size_t)c->p * 8)) return fail(c, OSSCAR_EINVAL, "osscar_get_tensor: destination too small");
     std::vector<double> sc(c->p);
     HIPCHK(c, hipMemcpyAsync(sc.data(), c->score, c->p * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
+    HIPCHK(c, wait(c));
     for (int g = 0; g < c->p; g++) {
       if (which == OSSCAR_T_REM && !c->kept_host[g]) sc[g] = INFINITY;
       if (which == OSSCAR_T_ADD && c->kept_host[g]) sc[g] = -INFINITY;
@@ -1679,7 +1723,7 @@ osscar_status osscar_get_tensor(osscar_ctx* c, int which, void* dst, size_t dst_
       return fail(c, OSSCAR_EINVAL, "osscar_get_tensor: unknown tensor id %d", which);
   }
   HIPCHK(c, hipGetLastError());
-  HIPCHK(c, hipStreamSynchronize(s));
+  HIPCHK(c, wait(c));
   return OSSCAR_OK;
 }
 
