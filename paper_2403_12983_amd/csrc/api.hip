@@ -1264,9 +1264,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     SwapRun run(c, d, t, la_mode);
     HIPCHK(c, run.init());
     int since_flush = 0, extra = la_mode == 2 ? FLUSH : 0;
-    // what the first interval will miss: 32 rows a side of every 1024 have their products
-    const int picked = 32 * ((c->p + 1023) / 1024);
-    int missed = picked < std::min({FLUSH, (int)max_swaps, std::max(c->k, c->p - c->k)}) ? RUN_MISSES + 1 : 0;      // in the last interval
+    int missed = 0;                                              // pivots of the last interval whose products were missing
     int missing = 0;                                             // in this one so far
     bool runs = c->runs_fit && la_mode == 0 && !(flags & OSSCAR_SEARCH_LAUNCH_PER_SWAP), owed = false;
     const uint32_t patience = (flags & OSSCAR_SEARCH_IMPATIENT) ? 0u : RUN_PATIENCE;

@@ -274,7 +274,7 @@ struct LazyPtrs {
   double* Minv2; SwapRec* rec; SwapRec* rec2; double* K; double* KT;
   // runs of swaps: their shared words and two copies of ZT ZT^T for the pending pivots, where a flush has its packed operands (ZcP .. Zpk)
   void* run_shared; double* LL; double* LL2;
-  double* lkey; int32_t* lidx;   // 2 x 64 x 32: per-block winners of the candidate selection
+  double* lkey; int32_t* lidx;   // up to 2 x 1024: per-block winners of the candidate selection
   // block removal (nested schedule): X = M^-1 N0[T, G], U = ZT Y^T (LAZY_TM x LAZY_BT each), D, Y Y^T (LAZY_BT^2), the picks; the
   // removal lists of every 64 rows (in the phases' scratch)
   double* bX; double* bU; double* bD; double* bYY; int32_t* bG;
@@ -284,7 +284,7 @@ struct LazyPtrs {
 // With no rows picked every pivot takes a spare slot: as many as can be pending (64 let the swaps flush after 32 instead of 64)
 constexpr int spare_start(int mode) { return mode == 2 ? LAZY_NS - LAZY_TM : 0; }
 // mode: which rows get their products with Z0 computed ahead: 0 = LAZY_NPICK_OUT cheapest removals + LAZY_NPICK_IN largest gains,
-// 1 = LAZY_NC cheapest removals (removal-only loops), at most 32 a side of every 1024 rows; 2 = none (every pivot then costs a pass over Z0)
+// 1 = LAZY_NC cheapest removals (removal-only loops), of every 1024 rows a side at most its share of 1024; 2 = none (every pivot then costs a pass over Z0)
 hipError_t launch_lazy_init(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode = 0);
 // Pairs on the device that swaps take in turn, out[r * step] and in[r * step] for r < n <= 64; in == nullptr: rows out[r * step] to remove
 struct SwapList { const int32_t* out = nullptr; const int32_t* in = nullptr; int n = 0, step = 1; };

@@ -74,22 +74,24 @@ __global__ __launch_bounds__(256) void lazy_reset_kernel(LazyPtrs L, SearchCtrl*
 // ------------------------------------------------------------------------------------------------
 // candidate rows and their products with Z0 (after every flush)
 // ------------------------------------------------------------------------------------------------
-// ascending bitonic sort of 1024 (key, index) pairs in LDS; equal keys: lower index first.  Exchanges at a distance below 64 stay
-// inside a wave, whose LDS operations are in order: only the ten wider ones need the workgroup's barrier.
-__device__ __forceinline__ void bitonic1024(double* key, int* idx, int tid) {
+// ascending bitonic sort of 1024 (key, index) pairs, a thread each; equal keys: lower index first.  Exchanges at a distance below 64 stay
+// inside a wave and go by shuffles, only the ten wider ones through shared memory (all through shared memory: 16 us; so: 6).
+__device__ __forceinline__ void bitonic1024(double& key, int& idx, double* lk, int* li, int tid) {
   for (int k = 2; k <= 1024; k <<= 1)
     for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j >= 64 && j == k >> 1) __syncthreads();
-      const int other = tid ^ j;
-      if (other > tid) {
-        const bool up = ((tid & k) == 0);
-        const double a = key[tid], b = key[other];
-        const int ia = idx[tid], ib = idx[other];
-        const bool a_after_b = (a > b) || (a == b && ia > ib);
-        if (a_after_b == up) { key[tid] = b; key[other] = a; idx[tid] = ib; idx[other] = ia; }
+      double b;
+      int ib;
+      if (j >= 64) {
+        __syncthreads();
+        lk[tid] = key; li[tid] = idx;
+        __syncthreads();
+        b = lk[tid ^ j]; ib = li[tid ^ j];
+      } else {
+        b = __shfl_xor(key, j, 64); ib = __shfl_xor(idx, j, 64);
       }
-      if (j >= 64) __syncthreads();
-      else { asm volatile("" ::: "memory"); __builtin_amdgcn_wave_barrier(); }
+      const bool after = (key > b) || (key == b && idx > ib);                     // this one comes after the other
+      const bool low = (tid & j) == 0, up = (tid & k) == 0;
+      if (after == (low == up) && !(key == b && idx == ib)) { key = b; idx = ib; }
     }
 }
 
@@ -97,38 +99,33 @@ __device__ __forceinline__ void bitonic1024(double* key, int* idx, int tid) {
 // among the others (1)
 __global__ __launch_bounds__(1024) void cand_local_kernel(LazyPtrs L, int p, const int32_t* __restrict__ kept,
                                                            const double* __restrict__ score, int per_block) {
-  __shared__ double key[1024];
-  __shared__ int idx[1024];
+  __shared__ double lk[1024];
+  __shared__ int li[1024];
   const int tid = threadIdx.x, h = blockIdx.x * 1024 + tid, nblk = gridDim.x, side = blockIdx.y;
   const bool valid = (h < p) && ((kept[h] != 0) == (side == 0));
-  key[tid] = valid ? (side == 0 ? score[h] : -score[h]) : INFINITY;
-  idx[tid] = valid ? h : 0x7fffffff;
-  __syncthreads();
-  bitonic1024(key, idx, tid);
+  double key = valid ? (side == 0 ? score[h] : -score[h]) : INFINITY;
+  int idx = valid ? h : 0x7fffffff;
+  bitonic1024(key, idx, lk, li, tid);
   if (tid < per_block) {
-    L.lkey[(side * nblk + blockIdx.x) * 32 + tid] = key[tid];
-    L.lidx[(side * nblk + blockIdx.x) * 32 + tid] = idx[tid];
+    L.lkey[(side * nblk + blockIdx.x) * per_block + tid] = key;
+    L.lidx[(side * nblk + blockIdx.x) * per_block + tid] = idx;
   }
 }
 
 // merge of the per-block winners, a workgroup per side: n_k kept rows into slots [0, n_k), n_c others into [n_k, n_k + n_c);
-// unused slots hold -1.  15 us here and 17 us in the local sorts; both sides one after the
-// other, with a barrier per exchange, 30 and 32.
+// unused slots hold -1.
 __global__ __launch_bounds__(1024) void cand_merge_kernel(LazyPtrs L, int nblk, int per_block, int n_k, int n_c) {
-  __shared__ double key[1024];
-  __shared__ int idx[1024];
+  __shared__ double lk[1024];
+  __shared__ int li[1024];
   const int tid = threadIdx.x, total = nblk * per_block, side = blockIdx.x;
   const int cnt = side == 0 ? n_k : n_c, base = side == 0 ? 0 : n_k;
-  if (tid < total) {
-    key[tid] = L.lkey[(side * nblk + tid / per_block) * 32 + tid % per_block];
-    idx[tid] = L.lidx[(side * nblk + tid / per_block) * 32 + tid % per_block];
-  } else { key[tid] = INFINITY; idx[tid] = 0x7fffffff; }
-  __syncthreads();
-  bitonic1024(key, idx, tid);
+  double key = tid < total ? L.lkey[side * total + tid] : INFINITY;
+  int idx = tid < total ? L.lidx[side * total + tid] : 0x7fffffff;
+  if (nblk > 1) bitonic1024(key, idx, lk, li, tid);      // (one block's are sorted)
   if (tid < cnt) {
-    const bool have = key[tid] < INFINITY;
-    L.cand[base + tid] = have ? idx[tid] : -1;
-    if (have) L.cslot[idx[tid]] = base + tid;
+    const bool have = key < INFINITY;
+    L.cand[base + tid] = have ? idx : -1;
+    if (have) L.cslot[idx] = base + tid;
   }
   if (side == 0) {
     for (int s = n_k + n_c + tid; s < LAZY_NC + LAZY_NS; s += 1024) L.cand[s] = -1;
@@ -315,11 +312,13 @@ static CandCounts cand_counts(int mode) {
 // the pick: reads the scores and the kept flags only (two sorts in one workgroup each: latency, no bandwidth)
 static hipError_t launch_candidate_pick(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, int mode) {
   const int nblk = (d.p + 1023) / 1024;               // <= 64 (d1 <= 65536)
-  const int per_block = std::min(32, 1024 / nblk);    // a side's winners are merged by one workgroup of 1024
+  // A side's winners are merged by one workgroup of 1024.  Of few blocks every one gives as many as are picked in all: with 32 of each
+  // a layer of 826 rows missed half of its pivots, and one of 2000 a seventh.
+  const CandCounts cc = cand_counts(mode);
+  const int per_block = std::min(std::max({cc.n_k, cc.n_c, 1}), 1024 / nblk);
   hipError_t e = hipMemsetAsync(L.cslot, 0xFF, (size_t)d.d1 * 4, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(cand_local_kernel, dim3(nblk, 2), dim3(1024), 0, s, L, d.p, t.kept, t.score, per_block);
-  const CandCounts cc = cand_counts(mode);
   hipLaunchKernelGGL(cand_merge_kernel, dim3(2), dim3(1024), 0, s, L, nblk, per_block, cc.n_k, cc.n_c);
   return hipGetLastError();
 }
