@@ -152,28 +152,31 @@ __global__ __launch_bounds__(256) void cand_gather_kernel(LazyPtrs L, const floa
 // ------------------------------------------------------------------------------------------------
 typedef float la_f16v __attribute__((ext_vector_type(16)));
 typedef __bf16 la_bf8 __attribute__((ext_vector_type(8)));
+typedef uint32_t la_u4 __attribute__((ext_vector_type(4)));      // (arrays of HIP's vector structs end in scratch memory)
+typedef float la_f4 __attribute__((ext_vector_type(4)));
 constexpr int LA_STG = 32;                   // columns of Z per stage (two 16-deep matrix-core steps)
 // A workgroup multiplies its rows of Z0 with one block of NC = 32 NT candidates (NT = 4, 5 or 6 tiles of 32 per wave);
 // packets per stage and block: 3 pieces x 4 groups of 8 columns x NC candidates.
 
-__device__ __forceinline__ uint32_t la_rne(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-// v[0..8) -> three packets of 8 bf16 each
+// v[0..8) -> three packets of 8 bf16 each, by v_cvt_pk_bf16_f32 (round to nearest; two numbers an instruction where the same in whole
+// numbers took eight)
 __device__ __forceinline__ void la_split3(const float* v, uint4& p1, uint4& p2, uint4& p3) {
-  uint32_t h1[8], h2[8], h3[8];
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  uint32_t h1[4], h2[4], h3[4];
+  auto cut = [](float& x, float& y) -> uint32_t {
+    const uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{x, y}), b2));
+    x -= __uint_as_float(u << 16); y -= __uint_as_float(u & 0xFFFF0000u);
+    return u;
+  };
 #pragma unroll
-  for (int j = 0; j < 8; j++) {
-    const uint32_t b1 = la_rne(v[j]);
-    const float r1 = v[j] - __uint_as_float(b1 << 16);
-    const uint32_t b2 = la_rne(r1);
-    const float r2 = r1 - __uint_as_float(b2 << 16);
-    h1[j] = b1; h2[j] = b2; h3[j] = la_rne(r2);
+  for (int j = 0; j < 4; j++) {
+    float x = v[2 * j], y = v[2 * j + 1];
+    h1[j] = cut(x, y); h2[j] = cut(x, y); h3[j] = cut(x, y);
   }
-  p1 = uint4{h1[0] | (h1[1] << 16), h1[2] | (h1[3] << 16), h1[4] | (h1[5] << 16), h1[6] | (h1[7] << 16)};
-  p2 = uint4{h2[0] | (h2[1] << 16), h2[2] | (h2[3] << 16), h2[4] | (h2[5] << 16), h2[6] | (h2[7] << 16)};
-  p3 = uint4{h3[0] | (h3[1] << 16), h3[2] | (h3[3] << 16), h3[4] | (h3[5] << 16), h3[6] | (h3[7] << 16)};
+  p1 = uint4{h1[0], h1[1], h1[2], h1[3]};
+  p2 = uint4{h2[0], h2[1], h2[2], h2[3]};
+  p3 = uint4{h3[0], h3[1], h3[2], h3[3]};
 }
 
 // ZcP[(sb * nstg + stage) * 12 nc + piece * 4 nc + kg * nc + s] = columns stage*32 + kg*8 .. +8 of candidate sb*nc + s, piece
@@ -297,6 +300,106 @@ __global__ __launch_bounds__(256, 2) void la_product_kernel(const uint4* __restr
   }
 }
 
+// The same for layers whose rows do not fill the chip in 128s: 64 rows per workgroup and eight waves, wave w: rows 32 (w & 1) .., the 16 columns
+// (w >> 1) & 1 of every stage, candidate tiles of half w >> 2.  The two halves of a stage meet in shared memory at the end, in this order.
+// Bound by the chain of a stage (shared memory, cutting,
+// eighteen products, two barriers), whose loads are requested three stages ahead.  8192 x 2048: 63 us (128 workgroups of 128 rows: 72);
+// 3000 x 1000, a whole flush: 0.15 ms (0.20).
+template <int NT>
+__global__ __launch_bounds__(512) void la_product_rows64_kernel(const uint4* __restrict__ ZcP, const float* __restrict__ Z0, int d1, int m,
+                                                                 int nstg, double* __restrict__ GbT) {
+  constexpr int NC = 32 * NT, PK = 12 * NC, NLD = (PK + 511) / 512, TT = (NT + 1) / 2;
+  __shared__ __attribute__((aligned(16))) uint4 lds[PK + 64 * LA_ZLD / 4];
+  static_assert(sizeof(lds) >= 4 * 16 * 64 * sizeof(double), "a round of the final sums");
+  la_u4* lzc = reinterpret_cast<la_u4*>(lds);
+  float* lz0 = reinterpret_cast<float*>(lds + PK);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sb = blockIdx.y;
+  const int rg = wave & 1, ks = (wave >> 1) & 1, ch = wave >> 2, t0 = ch * TT;
+  const int i0 = blockIdx.x * 64;
+  const int per = (nstg + (int)gridDim.z - 1) / (int)gridDim.z, st_begin = (int)blockIdx.z * per, st_end = min(nstg, st_begin + per);
+  if (st_begin >= st_end) return;
+  const uint4* src = ZcP + (int64_t)sb * nstg * PK + tid;
+  const int lr = tid >> 3, lk = (tid & 7) * 4, row = min(i0 + lr, d1 - 1);      // rows past the end: clamped, never stored
+  const float* zsrc = Z0 + (int64_t)row * m + lk;
+  la_f16v acc[TT], acc2[TT];
+#pragma unroll
+  for (int t = 0; t < TT; t++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) { acc[t][r] = 0.f; acc2[t][r] = 0.f; }
+  la_u4 zc[3][NLD];                                            // three stages requested ahead
+  la_f4 zt[3];
+  auto gload = [&](int stage_, la_u4 (&q)[NLD], la_f4& z) {
+    const int stage = min(stage_, st_end - 1);                 // (past the end: the last one again, not used)
+    const la_u4* p = reinterpret_cast<const la_u4*>(src) + (int64_t)stage * PK;
+#pragma unroll
+    for (int i = 0; i < NLD; i++) q[i] = p[tid + 512 * i < PK ? 512 * i : 0];
+    // (columns past the end: the row's first ones, replaced where they are stored: replaced here they would be waited for here)
+    z = *reinterpret_cast<const la_f4*>(zsrc + (stage * LA_STG + lk < m ? stage * LA_STG : -lk));
+  };
+  const float* myrow = lz0 + (rg * 32 + (lane & 31)) * LA_ZLD + (lane >> 5) * 8 + ks * 16;
+  int since = 0;
+  auto one = [&](int stage, la_u4 (&q)[NLD], la_f4& z) {
+    __syncthreads();                                           // the previous stage has been read by every wave
+#pragma unroll
+    for (int i = 0; i < NLD; i++)
+      if (tid + 512 * i < PK) lzc[tid + 512 * i] = q[i];
+    const bool in = stage * LA_STG + lk < m;                   // m % 4 == 0: a float4 is inside or outside as a whole
+    *reinterpret_cast<la_f4*>(lz0 + lr * LA_ZLD + lk) = la_f4{in ? z.x : 0.f, in ? z.y : 0.f, in ? z.z : 0.f, in ? z.w : 0.f};
+    __syncthreads();
+    gload(stage + 3, q, z);
+    const float4 v0 = *reinterpret_cast<const float4*>(myrow), v1 = *reinterpret_cast<const float4*>(myrow + 4);
+    const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+    uint4 b1, b2, b3;
+    la_split3(v, b1, b2, b3);
+    const la_bf8 f1 = *reinterpret_cast<const la_bf8*>(&b1), f2 = *reinterpret_cast<const la_bf8*>(&b2), f3 = *reinterpret_cast<const la_bf8*>(&b3);
+    const int off = (ks * 2 + (lane >> 5)) * NC + (lane & 31);
+    la_bf8 a1[TT], a2[TT], a3[TT];
+#pragma unroll
+    for (int t = 0; t < TT; t++) {                             // (of an odd number of tiles the last one twice: the second is not stored)
+      const int tt = min(t0 + t, NT - 1) * 32;
+      a1[t] = __builtin_bit_cast(la_bf8, lzc[off + tt]); a2[t] = __builtin_bit_cast(la_bf8, lzc[4 * NC + off + tt]); a3[t] = __builtin_bit_cast(la_bf8, lzc[8 * NC + off + tt]);
+    }
+    auto mul = [&](const la_bf8 (&a)[TT], const la_bf8& f) {
+#pragma unroll
+      for (int t = 0; t < TT; t++) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], f, acc[t], 0, 0, 0);
+    };
+    mul(a3, f1); mul(a2, f2); mul(a1, f3); mul(a2, f1); mul(a1, f2); mul(a1, f1);      // smallest terms first
+    if (++since == 1024 / LA_STG && stage + 1 < st_end) {      // (512 columns of each half of the stages)
+      since = 0;
+#pragma unroll
+      for (int t = 0; t < TT; t++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) { acc2[t][r] += acc[t][r]; acc[t][r] = 0.f; }
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < 3; i++) gload(st_begin + i, zc[i], zt[i]);
+  for (int stage = st_begin; stage < st_end; stage += 3) {
+    one(stage, zc[0], zt[0]);
+    if (stage + 1 < st_end) one(stage + 1, zc[1], zt[1]);
+    if (stage + 2 < st_end) one(stage + 2, zc[2], zt[2]);
+  }
+  // C layout of the 32 x 32 tile: register r = rr*4 + r3 holds row rr*8 + (lane/32)*4 + r3 (a candidate), column lane%32 (a row of Z0)
+  double* half = reinterpret_cast<double*>(lds) + (rg * 2 + ch) * 16 * 64 + lane;
+  const int i_lane = i0 + rg * 32 + (lane & 31);
+#pragma unroll
+  for (int t = 0; t < TT; t++) {
+    __syncthreads();
+    if (ks == 1)
+#pragma unroll
+      for (int r = 0; r < 16; r++) half[r * 64] = (double)acc[t][r] + (double)acc2[t][r];
+    __syncthreads();
+    if (ks == 0 && t0 + t < NT && i_lane < d1)
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int sl = (t0 + t) * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        double* dst = GbT + (int64_t)(sb * NC + sl) * d1 + i_lane;
+        const double v = ((double)acc[t][r] + (double)acc2[t][r]) + half[r * 64];
+        if (gridDim.z == 1) *dst = v; else unsafeAtomicAdd(dst, v);
+      }
+  }
+}
+
 // mode 0: LAZY_NPICK_OUT slots for kept rows, LAZY_NPICK_IN for the others; 1: LAZY_NC for kept rows (removal-only loops); 2: none
 struct CandCounts { int n_k, n_c; };
 static CandCounts cand_counts(int mode) {
@@ -335,16 +438,23 @@ static hipError_t launch_candidate_products(const TabDims& d, const TabPtrs& t, 
   if (d.m % 8 == 0 && nt > 0) {
     const int nstg = (d.m + LA_STG - 1) / LA_STG, nc = 32 * nt, nsb = ncand / nc;
     hipLaunchKernelGGL(la_pack_kernel, dim3(nstg, nsb), dim3(256), 0, s, L, t.Z, d.m, nstg, nc, reinterpret_cast<uint4*>(L.ZcP));
-    // one block of candidates: 224 workgroups for 28672 rows would leave compute units empty and each of them with one
-    // latency chain over all of m; the contraction is then cut in two
-    const int ksplit = (((d.d1 + 127) / 128) * nsb < 400 && nstg >= 64) ? 2 : 1;
+    // One block of candidates: 224 workgroups for 28672 rows would leave compute units empty and each of them with one latency chain over
+    // all of m; the contraction is then cut in two.  Below 200 workgroups of 128 rows: 64 rows each, cut in two where they are fewer than 256.
+    const int wgs = (d.d1 + 127) / 128 * nsb;
+    const bool small = wgs < 200;
+    const int wgs64 = (d.d1 + 63) / 64 * nsb;
+    const int ksplit = small ? (wgs64 < 256 && nstg >= 16 ? 2 : 1) : (wgs < 400 && nstg >= 64) ? 2 : 1;
     if (ksplit > 1) {
       const hipError_t ez = hipMemsetAsync(L.GbT, 0, (size_t)ncand * d.d1 * sizeof(double), s);
       if (ez != hipSuccess) return ez;
     }
-    const dim3 grid((d.d1 + 127) / 128, nsb, ksplit);
+    const dim3 grid(small ? (d.d1 + 63) / 64 : (d.d1 + 127) / 128, nsb, ksplit);
     const uint4* zcp = reinterpret_cast<const uint4*>(L.ZcP);
-    if (nt == 4) hipLaunchKernelGGL(la_product_kernel<4>, grid, dim3(256), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
+    if (small) {
+      if (nt == 4) hipLaunchKernelGGL(la_product_rows64_kernel<4>, grid, dim3(512), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
+      else if (nt == 5) hipLaunchKernelGGL(la_product_rows64_kernel<5>, grid, dim3(512), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
+      else hipLaunchKernelGGL(la_product_rows64_kernel<6>, grid, dim3(512), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
+    } else if (nt == 4) hipLaunchKernelGGL(la_product_kernel<4>, grid, dim3(256), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
     else if (nt == 5) hipLaunchKernelGGL(la_product_kernel<5>, grid, dim3(256), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
     else hipLaunchKernelGGL(la_product_kernel<6>, grid, dim3(256), 0, s, zcp, t.Z, d.d1, d.m, nstg, L.GbT);
     return hipGetLastError();
@@ -547,50 +657,62 @@ __global__ __launch_bounds__(256, 2) void rk_update_kernel(const uint4* __restri
 }
 
 // E = C0 M^-1 of the flush (d1 x 128 times 128 x 128, float32 operands, float64 sums on v_mfma_f64_16x16x4_f64, float32
-// result).  It stands at the head of the flush's longest chain, so what counts is its latency: the general matrix-product
-// kernel runs it as 224 workgroups of one 128 x 128 tile each (0.085 ms); here a workgroup takes 64 rows with all of M^-1
-// and its rows of C0 in shared memory (448 workgroups, no barrier inside the contraction).  M^-1 (rounded to float32 here, zero
-// from tau on) is symmetric bit for bit, so its rows serve as the columns the product needs.  Wave w: rows 16 w .. 16 w + 15, eight 16 x 16 tiles.
+// result).  It stands at the head of the flush's longer chain, so what counts is its latency: a workgroup takes 32 rows (256 workgroups
+// at 8192 rows) with all of M^-1 and its rows of C0 in shared memory, no barrier inside the contraction; every thread has its share of
+// both requested at once.  M^-1 (rounded to float32 here, zero from tau on) is symmetric bit for bit, so its rows serve as the
+// columns the product needs.  Wave w: rows 16 (w & 1) .. + 15, columns 32 (w >> 1) .. + 31.
+// 20 us at 8192 rows beside Z0's update (as 128 workgroups of 64 rows 26), 60 us at 28672 either way.
 typedef double te_d4 __attribute__((ext_vector_type(4)));
 constexpr int TE_LD = LAZY_TM + 4;       // row stride in shared memory (floats): a quarter wave's 16 rows x 4 k fall on 32 banks twice
-__global__ __launch_bounds__(256) void thin_e_kernel(LazyPtrs L, int d1, const SearchCtrl* __restrict__ ctrl) {
-  static_assert(LAZY_TM == 128, "eight column tiles, thirty-two steps of four");
-  extern __shared__ float te_lds[];      // [128 rows of M^-1 | 64 rows of C0][TE_LD]
+constexpr int TE_ROWS = 32;
+__global__ __launch_bounds__(512) void thin_e_kernel(LazyPtrs L, int d1, const SearchCtrl* __restrict__ ctrl) {
+  static_assert(LAZY_TM == 128, "four pairs of column tiles, thirty-two steps of four");
+  extern __shared__ float te_lds[];      // [128 rows of M^-1 | 32 rows of C0][TE_LD]
   float* Ms = te_lds;
   float* As = te_lds + LAZY_TM * TE_LD;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i0 = blockIdx.x * 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i0 = blockIdx.x * TE_ROWS;
   const float* C0R = L.C0R;
   const double* Mi = L.Minv;
   const int tau = tau_all(ctrl);
-  for (int idx = tid; idx < LAZY_TM * (LAZY_TM / 2); idx += 256) {
-    const int r = idx >> 6, c = (idx & 63) * 2;
-    const double2 v = *reinterpret_cast<const double2*>(Mi + r * LAZY_TM + c);
-    *reinterpret_cast<float2*>(Ms + r * TE_LD + c) = float2{r < tau && c < tau ? (float)v.x : 0.f, r < tau && c + 1 < tau ? (float)v.y : 0.f};
+  float4 c[2];
+#pragma unroll
+  for (int u = 0; u < 2; u++) {
+    const int idx = tid + 512 * u, r = min(i0 + (idx >> 5), d1 - 1);
+    c[u] = *reinterpret_cast<const float4*>(C0R + (int64_t)r * LAZY_TM + (idx & 31) * 4);
   }
-  for (int idx = tid; idx < 64 * (LAZY_TM / 4); idx += 256) {
-    const int r = idx >> 5, c4 = (idx & 31) * 4;
-    const float4 v = (i0 + r < d1) ? *reinterpret_cast<const float4*>(C0R + (int64_t)(i0 + r) * LAZY_TM + c4) : float4{0.f, 0.f, 0.f, 0.f};
-    *reinterpret_cast<float4*>(As + r * TE_LD + c4) = v;
+  double2 v[16];
+#pragma unroll
+  for (int u = 0; u < 16; u++) {
+    const int idx = tid + 512 * u;
+    v[u] = *reinterpret_cast<const double2*>(Mi + (idx >> 6) * LAZY_TM + (idx & 63) * 2);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; u++) {
+    const int idx = tid + 512 * u;
+    *reinterpret_cast<float4*>(As + (idx >> 5) * TE_LD + (idx & 31) * 4) = c[u];
+  }
+#pragma unroll
+  for (int u = 0; u < 16; u++) {
+    const int idx = tid + 512 * u, r = idx >> 6, k = (idx & 63) * 2;
+    *reinterpret_cast<float2*>(Ms + r * TE_LD + k) = float2{r < tau && k < tau ? (float)v[u].x : 0.f, r < tau && k + 1 < tau ? (float)v[u].y : 0.f};
   }
   __syncthreads();
-  te_d4 acc[8];
-#pragma unroll
-  for (int ct = 0; ct < 8; ct++) acc[ct] = te_d4{0.0, 0.0, 0.0, 0.0};
-  const float* arow = As + (wave * 16 + (lane & 15)) * TE_LD + (lane >> 4);
-  const float* mrow = Ms + (lane & 15) * TE_LD + (lane >> 4);
-#pragma unroll 4
+  te_d4 acc[2] = {te_d4{0.0, 0.0, 0.0, 0.0}, te_d4{0.0, 0.0, 0.0, 0.0}};
+  const float* arow = As + ((wave & 1) * 16 + (lane & 15)) * TE_LD + (lane >> 4);
+  const float* mrow = Ms + ((wave >> 1) * 32 + (lane & 15)) * TE_LD + (lane >> 4);
+#pragma unroll 8
   for (int k0 = 0; k0 < LAZY_TM; k0 += 4) {
     const double a = (double)arow[k0];
 #pragma unroll
-    for (int ct = 0; ct < 8; ct++) acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)mrow[ct * 16 * TE_LD + k0], acc[ct], 0, 0, 0);
+    for (int ct = 0; ct < 2; ct++) acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)mrow[ct * 16 * TE_LD + k0], acc[ct], 0, 0, 0);
   }
   // lane holds D[4 r + lane/16][lane%16] of each 16 x 16 tile
 #pragma unroll
   for (int r = 0; r < 4; r++) {
-    const int row = i0 + wave * 16 + 4 * r + (lane >> 4);
+    const int row = i0 + (wave & 1) * 16 + 4 * r + (lane >> 4);
     if (row < d1) {
 #pragma unroll
-      for (int ct = 0; ct < 8; ct++) L.E[(int64_t)row * LAZY_TM + ct * 16 + (lane & 15)] = (float)acc[ct][r];
+      for (int ct = 0; ct < 2; ct++) L.E[(int64_t)row * LAZY_TM + (wave >> 1) * 32 + ct * 16 + (lane & 15)] = (float)acc[ct][r];
     }
   }
 }
@@ -647,39 +769,46 @@ hipError_t launch_lazy_flush(const TabDims& d, const TabPtrs& t, const LazyPtrs&
     return e != hipSuccess ? e : hipStreamWaitEvent(sn, side->fork, 0);
   };
   if ((err = here_to_there()) != hipSuccess) return err;
+  // the three thin operands in matrix-core order (C0's pieces serve both updates)
+  const int dpad = (d.d1 + 127) / 128 * 128, mpad = (d.m + 127) / 128 * 128;
+  uint4* Epk = reinterpret_cast<uint4*>(L.Epk); uint4* Cpk = reinterpret_cast<uint4*>(L.Cpk); uint4* Zpk = reinterpret_cast<uint4*>(L.Zpk);
+  // Launches take the host as long as the small ones run, so each stream's first ones come before the other's later ones (with all of
+  // N0's up to its update in front of the first of Z0's a flush was 20 us longer)
+  hipLaunchKernelGGL(rk_pack_rows_kernel, dim3((16 * dpad + 255) / 256), dim3(256), 0, s, L.C0R, d.d1, dpad, Cpk);
   if (two) {
     // The candidates of the next cycle, from the scores as the swaps left them (the refresh below changes them in the last
     // digits only, and the choice of candidates decides what is computed ahead, not any result)
     if ((err = launch_candidate_pick(d, t, L, sn, mode)) != hipSuccess) return err;
     if ((err = hipEventRecord(side->join, sn)) != hipSuccess) return err;
+    if ((err = hipEventRecord(side->fork, s)) != hipSuccess) return err;      // the pieces of C0
   }
+  if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err;
+  hipLaunchKernelGGL(rk_pack_cols_kernel, dim3((16 * mpad + 255) / 256), dim3(256), 0, s, L.ZT32, d.m, mpad, Zpk);
+  // Z0 -= C0 ZT
+  // (with two streams the kernel also leaves the sums of squares of every row's 64-column stretches: the row norms of the
+  // score refresh then come from these 25 MB instead of another pass over Z0)
+  auto update_z = [&]() {
+    hipLaunchKernelGGL(rk_update_kernel, dim3((unsigned)L.n_tiles_rect), dim3(256), 0, s, Cpk, dpad, Zpk, mpad, t.Z, (int64_t)d.m, d.d1, d.m,
+                       L.tiles_rect, two ? L.rowsq : (double*)nullptr);
+    hipLaunchKernelGGL(lazy_fix_z_kernel, dim3(mb, LAZY_TM / FIX_SPB), dim3(256), 0, s, L, t.Z, d.m, t.ctrl);
+  };
+  if (two) update_z();
   {                                     // E = C0 M^-1 (entered in the log of matrix products like the general kernel's launches)
-    const size_t shmem = (size_t)(LAZY_TM + 64) * TE_LD * sizeof(float);
+    const size_t shmem = (size_t)(LAZY_TM + TE_ROWS) * TE_LD * sizeof(float);
     if ((err = hipFuncSetAttribute(reinterpret_cast<const void*>(thin_e_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem)) != hipSuccess)
       return err;
     int log_slot = -1;
     gemm_log_open(d.d1, LAZY_TM, LAZY_TM, 0, sn, &log_slot);
-    hipLaunchKernelGGL(thin_e_kernel, dim3((d.d1 + 63) / 64), dim3(256), shmem, sn, L, d.d1, t.ctrl);
+    hipLaunchKernelGGL(thin_e_kernel, dim3((d.d1 + TE_ROWS - 1) / TE_ROWS), dim3(512), shmem, sn, L, d.d1, t.ctrl);
     gemm_log_close(log_slot, sn);
   }
-  // the three thin operands in matrix-core order (C0's pieces serve both updates)
-  const int dpad = (d.d1 + 127) / 128 * 128, mpad = (d.m + 127) / 128 * 128;
-  uint4* Epk = reinterpret_cast<uint4*>(L.Epk); uint4* Cpk = reinterpret_cast<uint4*>(L.Cpk); uint4* Zpk = reinterpret_cast<uint4*>(L.Zpk);
   hipLaunchKernelGGL(rk_pack_rows_kernel, dim3((16 * dpad + 255) / 256), dim3(256), 0, sn, L.E, d.d1, dpad, Epk);
-  hipLaunchKernelGGL(rk_pack_rows_kernel, dim3((16 * dpad + 255) / 256), dim3(256), 0, s, L.C0R, d.d1, dpad, Cpk);
-  if ((err = here_to_there()) != hipSuccess) return err;
-  if ((err = launch_zt(d, t, L, s)) != hipSuccess) return err;
-  hipLaunchKernelGGL(rk_pack_cols_kernel, dim3((16 * mpad + 255) / 256), dim3(256), 0, s, L.ZT32, d.m, mpad, Zpk);
+  if (two && (err = hipStreamWaitEvent(sn, side->fork, 0)) != hipSuccess) return err;
   // N0 -= E C0^T on the lower block triangle (pivot rows and columns are rewritten below)
   hipLaunchKernelGGL(rk_update_kernel, dim3((unsigned)L.n_tiles_sym), dim3(256), 0, sn, Epk, dpad, Cpk, dpad, t.N, (int64_t)d.d1, d.d1, d.d1,
                      L.tiles_sym, (double*)nullptr);
   hipLaunchKernelGGL(lazy_fix_kernel, dim3(rb, LAZY_TM / FIX_SPB), dim3(256), 0, sn, L, t.N, d.d1, t.ctrl);
-  // Z0 -= C0 ZT
-  // (with two streams the kernel also leaves the sums of squares of every row's 64-column stretches: the row norms of the
-  // score refresh then come from these 25 MB instead of another pass over Z0)
-  hipLaunchKernelGGL(rk_update_kernel, dim3((unsigned)L.n_tiles_rect), dim3(256), 0, s, Cpk, dpad, Zpk, mpad, t.Z, (int64_t)d.m, d.d1, d.m,
-                     L.tiles_rect, two ? L.rowsq : (double*)nullptr);
-  hipLaunchKernelGGL(lazy_fix_z_kernel, dim3(mb, LAZY_TM / FIX_SPB), dim3(256), 0, s, L, t.Z, d.m, t.ctrl);
+  if (!two) update_z();
   if (!two) {
     hipLaunchKernelGGL(lazy_reset_kernel, dim3(1), dim3(256), 0, s, L, t.ctrl);
     if ((err = launch_refresh_scores(d, t, s)) != hipSuccess) return err;
