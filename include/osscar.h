@@ -303,7 +303,7 @@ int32_t osscar_debug_tile_schedule(int64_t d1, int32_t* out_host, int32_t capaci
  * H_dev, G_dev: dev outputs, dense (leading dimensions d1 and m); scalars_dev: dev, 2 float64 = {lambda, c0}.
  * Everything is enqueued on hip_stream (a hipStream_t, NULL = default stream); the call does not wait for it and
  * calls no hipMalloc, hipFree or other allocating routine.  What osscar_gram keeps in the caller's workspace meanwhile
- * (float64 accumulator, float32 W, partial tiles) lives in a device array of OSSCAR_STATIC_SCRATCH_BYTES that
+ * (float64 accumulator, partial tiles, scalars) lives in a device array of OSSCAR_STATIC_SCRATCH_BYTES that
  * every GPU the library runs on holds until the process ends.  Limits: d1, m <= OSSCAR_STATIC_MAX_DIM, any n >= 0;
  * larger sizes return OSSCAR_ENOMEM.  All calls on one GPU share that array: calls that overlap in time on one GPU
  * (different streams or host threads) race and must be serialised by the caller.  After a failure

@@ -882,9 +882,13 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
   }
   HIPCHK(c, hipEventRecord(c->ev_s[1][0], s));
   HIPCHK(c, launch_sum_copies(H64, c->h_copies, d1, d1, 1, s));
-  HIPCHK(c, launch_trace64(H64, d1, c->scal, s));
-  hipLaunchKernelGGL(lambda_kernel, dim3(1), dim3(1), 0, s, c->scal, lambda_abs, lambda_rel, d1);
-  HIPCHK(c, launch_finalize_H(H64, c->H, d1, c->scal + 1, s));
+  if (d1 <= RIDGE_DIM) {
+    HIPCHK(c, launch_finalize_ridge(H64, c->H, d1, lambda_abs, lambda_rel, c->scal + 1, s));
+  } else {
+    HIPCHK(c, launch_trace64(H64, d1, c->scal, s));
+    hipLaunchKernelGGL(lambda_kernel, dim3(1), dim3(1), 0, s, c->scal, lambda_abs, lambda_rel, d1);
+    HIPCHK(c, launch_finalize_H(H64, c->H, d1, c->scal + 1, s));
+  }
   HIPCHK(c, launch_convert_to_f32(W, c->desc.w_dtype == OSSCAR_BF16, d1, m, ldw, Wf, s));
   if (target) {
     // G = X^T Y + lambda W, c0 = ||Y||^2 + lambda ||W||^2

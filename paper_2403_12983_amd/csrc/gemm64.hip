@@ -234,9 +234,9 @@ static int gemm64_tiles(int M, int N, int lower) {
 }
 
 // Ranges of the contraction.  A stage of 32 k takes a workgroup that has its compute unit to itself about 1.9 us (the way of
-// its loads), two or three that share one 0.9 us each (the matrix cores), so the time of a launch follows from the
+// its loads), two or three that share one 3.1 us together, more 0.95 us each (the matrix cores), so the time of a launch follows from the
 // workgroups on the fullest unit and the stages of one; adding the ranges up costs a second launch and the write and read of
-// their tiles (32 KB each at about 3 TB/s).
+// their tiles (32 KB each at about 3 TB/s).  (4096 rows of 288 columns, 15 tiles, whole quadratic form: 17 ranges 41.3 us, 22 45.4, 32 43.6.)
 static int gemm64_splits(int tiles, int K, size_t ws_bytes) {
   const int stages = std::max(1, (K + KS - 1) / KS);
   const int cap = (int)std::min<size_t>((size_t)stages, ws_bytes / ((size_t)tiles * 4096 * 8));
@@ -245,7 +245,8 @@ static int gemm64_splits(int tiles, int K, size_t ws_bytes) {
   for (int sp = 1; sp <= std::max(1, std::min(cap, 64)); sp++) {
     const int per = (stages + sp - 1) / sp, used = (stages + per - 1) / per;
     if (used != sp) continue;
-    const double us = std::max(1.9, 0.9 * ((tiles * sp + 255) / 256)) * per + (sp > 1 ? 5.0 + 0.0218 * tiles * sp : 0.0);
+    const int on_unit = (tiles * sp + 255) / 256;
+    const double us = (on_unit == 1 ? 1.9 : std::max(3.1, 0.95 * on_unit)) * per + (sp > 1 ? 5.0 + 0.0218 * tiles * sp : 0.0);
     if (us < best_us * 0.97) { best_us = us; best = sp; }
   }
   return best;

@@ -858,13 +858,29 @@ hipError_t launch_convert_to_f32(const void* src, int is_bf16, int64_t rows, int
   return hipGetLastError();
 }
 
+__device__ __forceinline__ double block_sum(double v, double* sh) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 0) sh[w] = v;
+  __syncthreads();
+  double t = 0;
+  if (threadIdx.x == 0)
+    for (int i = 0; i < (int)(blockDim.x >> 6); i++) t += sh[i];
+  return t;   // valid in thread 0
+}
+
 // H[i][j] = float(H64[max(i,j)][min(i,j)] + (i == j ? lam : 0)).  One workgroup per 64 x 64 tile on or below the
 // diagonal: it reads the tile of H64 along its rows, writes it to H, and writes the mirrored tile from LDS, so that both
-// the reads and the writes run along rows.
+// the reads and the writes run along rows.  The tile's loads are in flight together (one at a time a single tile took 8 us).
+// RIDGE: lam = lambda_abs + lambda_rel trace / d1 first, by every workgroup for itself (d1 loads; the first leaves it in *ridge):
+// for small layers, whose time is launches; *clear = 0 for a launch behind it.
+template <bool RIDGE>
 __global__ __launch_bounds__(256) void finalize_H_kernel(const double* __restrict__ H64, float* __restrict__ H, int d1,
-                                                          const double* __restrict__ lam_dev) {
+                                                          const double* __restrict__ lam_dev, double lambda_abs, double lambda_rel, double* __restrict__ ridge,
+                                                          int* __restrict__ clear) {
   __shared__ float tile[64][65];
-  const double lam = lam_dev ? lam_dev[0] : 0.0;
+  __shared__ double sh[4], s_lam;
   // tile index -> (tr, tc), tc <= tr
   const int t = blockIdx.x;
   int tr = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
@@ -873,16 +889,32 @@ __global__ __launch_bounds__(256) void finalize_H_kernel(const double* __restric
   const int tc = t - tr * (tr + 1) / 2;
   const int r0 = tr * 64, c0 = tc * 64;
   const int lx = threadIdx.x & 63, ly = threadIdx.x >> 6;
+  double x[16];
+#pragma unroll
+  for (int k = 0; k < 16; k++) {
+    // on a diagonal tile the entries above the diagonal come from their mirror images
+    const int i = min(r0 + ly + 4 * k, d1 - 1), j = min(c0 + lx, d1 - 1), hi = max(i, j), lo = min(i, j);
+    x[k] = H64[(int64_t)hi * d1 + lo];
+  }
+  double lam;
+  if constexpr (RIDGE) {
+    double v = 0;
+    for (int i = threadIdx.x; i < d1; i += 256) v += H64[(int64_t)i * d1 + i];
+    v = block_sum(v, sh);
+    if (threadIdx.x == 0) {
+      s_lam = lambda_abs + lambda_rel * v / (double)d1;
+      if (t == 0) { *ridge = s_lam; if (clear) *clear = 0; }
+    }
+    __syncthreads();
+    lam = s_lam;
+  } else {
+    lam = lam_dev ? lam_dev[0] : 0.0;
+  }
+#pragma unroll
   for (int k = 0; k < 16; k++) {
     const int i = r0 + ly + 4 * k, j = c0 + lx;
-    float v = 0.f;
-    if (i < d1 && j < d1) {
-      // on a diagonal tile the entries above the diagonal come from their mirror images
-      double x = (i >= j) ? H64[(int64_t)i * d1 + j] : H64[(int64_t)j * d1 + i];
-      if (i == j) x += lam;
-      v = (float)x;
-      H[(int64_t)i * d1 + j] = v;
-    }
+    const float v = (float)(i == j ? x[k] + lam : x[k]);
+    if (i < d1 && j < d1) H[(int64_t)i * d1 + j] = v;
     tile[ly + 4 * k][lx] = v;
   }
   if (tr == tc) return;
@@ -895,20 +927,14 @@ __global__ __launch_bounds__(256) void finalize_H_kernel(const double* __restric
 
 hipError_t launch_finalize_H(const double* H64, float* H, int d1, const double* lam_dev, hipStream_t s) {
   const int64_t nt = (d1 + 63) / 64;
-  hipLaunchKernelGGL(finalize_H_kernel, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, H64, H, d1, lam_dev);
+  hipLaunchKernelGGL(finalize_H_kernel<false>, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, H64, H, d1, lam_dev, 0.0, 0.0, (double*)nullptr, (int*)nullptr);
   return hipGetLastError();
 }
-
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sh[w] = v;
-  __syncthreads();
-  double t = 0;
-  if (threadIdx.x == 0)
-    for (int i = 0; i < (int)(blockDim.x >> 6); i++) t += sh[i];
-  return t;   // valid in thread 0
+hipError_t launch_finalize_ridge(const double* H64, float* H, int d1, double lambda_abs, double lambda_rel, double* ridge, hipStream_t s, int* clear) {
+  const int64_t nt = (d1 + 63) / 64;
+  hipLaunchKernelGGL(finalize_H_kernel<true>, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, H64, H, d1, (const double*)nullptr, lambda_abs,
+                     lambda_rel, ridge, clear);
+  return hipGetLastError();
 }
 
 __global__ __launch_bounds__(1024) void trace64_kernel(const double* __restrict__ H64, int d1, double* out) {
