@@ -1081,7 +1081,7 @@ __global__ __launch_bounds__(PREP_T) void blk_prep_kernel(LazyPtrs L, const floa
       sW[a][lc] = (a < t && lc < t) ? z : 0.0;            // Z_G Z_G^T
     }
     bool flag = false;
-    inv16_steps<0>(y, lane, t, flag);
+    inv16(y, lane, t, flag);
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       const int a = 4 * r + lr;

@@ -126,7 +126,7 @@ __device__ __forceinline__ bool inv_sym(int w, InvLds<NB>& L, Get get, Put put) 
   }
   auto invert = [&](const swd4& a, int kb) {
     swd4 y = a;
-    inv16_steps<0>(y, lane, w - kb * 16, flag);
+    inv16(y, lane, w - kb * 16, flag);
 #pragma unroll
     for (int r = 0; r < 4; r++) L.D[kb & 1][4 * r + lr][lc] = y[r];
   };
@@ -568,8 +568,8 @@ __global__ __launch_bounds__(256) void narrow_negate_mirror_kernel(const double*
     }
   }
 }
-// C = the pivot columns t0 .. t0 + w of N for every row, and (the first workgroup) D = the inverse of the pivot block,
-// straight from N, so that the copy runs beside the inverse.
+// Cz = the pivot columns t0 .. t0 + w of N for every row but the pivot's own, which are zero there (an operand of the bulk update), and
+// (the first workgroup) D = the inverse of the pivot block, straight from N, so that the copy runs beside the inverse.
 constexpr int IB_T = 768;                              // 12 waves x 3 of the 36 lower tiles of a pivot block
 __global__ __launch_bounds__(IB_T) void panel_inverse64_kernel(const double* __restrict__ N, int64_t ld, int n, int t0, int w,
                                                                 double* __restrict__ C, double* __restrict__ D, int32_t* notpd) {
@@ -598,7 +598,8 @@ __global__ __launch_bounds__(IB_T) void panel_inverse64_kernel(const double* __r
   } else {
     for (int idx = tid; idx < PANEL_ROWS64 * w; idx += IB_T) {
       const int r = idx / w, c = idx % w;
-      T[r][c] = (i0 + r < n) ? nsym64(N, ld, i0 + r, t0 + c) : 0.0;
+      const bool piv = i0 + r >= t0 && i0 + r < t0 + w;
+      T[r][c] = (i0 + r < n && !piv) ? nsym64(N, ld, i0 + r, t0 + c) : 0.0;
     }
   }
   __syncthreads();
@@ -607,32 +608,53 @@ __global__ __launch_bounds__(IB_T) void panel_inverse64_kernel(const double* __r
     if (i0 + r < n) C[(int64_t)(i0 + r) * w + c] = T[r][c];
   }
 }
-// outz = C D and Cz = C, both with the pivot rows zeroed: the operands of the bulk update; the pivot-row fix reads outz
-// outside the pivot rows only.  8 rows per workgroup, thread (h, c) sums 4 rows of column c, k ascending.
-__global__ __launch_bounds__(256) void panel_times_small64_kernel(const double* __restrict__ C, const double* __restrict__ D, int n, int w,
-                                                                   int t0, double* __restrict__ outz, double* __restrict__ Cz) {
-  __shared__ double Csh[8][128];
-  const int r0 = blockIdx.x * 8, tid = threadIdx.x;
-  for (int idx = tid; idx < 8 * w; idx += 256) {
-    const int r = idx / w, k = idx % w;
-    Csh[r][k] = (r0 + r < n) ? C[(int64_t)(r0 + r) * w + k] : 0.0;
+// outz = Cz D, the other operand, whose pivot rows are zero too (the pivot-row fix reads it outside them).  16 rows per workgroup on the float64 matrix
+// cores, wave w: columns 32 w .. + 31; D is symmetric and comes from L2, eight steps of four requested ahead.  Bound by that latency (in scalars, with a
+// pass over C in front, 10.5 us for 1536 rows and 53 for 8192).
+__global__ __launch_bounds__(256) void panel_times_block64_kernel(const double* __restrict__ Cz, const double* __restrict__ D, int n, int w, double* __restrict__ outz) {
+  __shared__ double As[16][130];
+  const int r0 = blockIdx.x * 16, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane >> 4, lc = lane & 15;
+  double c[8];
+#pragma unroll
+  for (int u = 0; u < 8; u++) {
+    const int idx = tid + 256 * u, r = min(r0 + (idx >> 7), n - 1), k = min(idx & 127, w - 1);
+    c[u] = Cz[(int64_t)r * w + k];
+  }
+  const int col0 = min(wave * 32 + lc, w - 1), col1 = min(wave * 32 + 16 + lc, w - 1);
+  double d0[2][8], d1[2][8];
+  auto request = [&](int g, double (&p)[8], double (&q)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const int64_t k = min(g * 32 + 4 * u + lr, w - 1);      // (past the end: times zero)
+      p[u] = D[k * w + col0]; q[u] = D[k * w + col1];
+    }
+  };
+  request(0, d0[0], d1[0]);
+#pragma unroll
+  for (int u = 0; u < 8; u++) {
+    const int idx = tid + 256 * u;
+    As[idx >> 7][idx & 127] = (idx & 127) < w ? c[u] : 0.0;
   }
   __syncthreads();
-  const int c = tid & 127, h = tid >> 7;
-  if (c >= w) return;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k = 0; k < w; k++) {
-    const double dv = D[k * w + c];
+  swd4 acc[2] = {swd4{0.0, 0.0, 0.0, 0.0}, swd4{0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
-    for (int r = 0; r < 4; r++) acc[r] += Csh[h * 4 + r][k] * dv;
+  for (int g = 0; g < 4; g++) {
+    if (g < 3) request(g + 1, d0[(g + 1) & 1], d1[(g + 1) & 1]);
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+      const double a = As[lc][g * 32 + 4 * u + lr];
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, d0[g & 1][u], acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, d1[g & 1][u], acc[1], 0, 0, 0);
+    }
   }
 #pragma unroll
   for (int r = 0; r < 4; r++) {
-    const int i = r0 + h * 4 + r;
-    if (i >= n) continue;
-    const bool piv = i >= t0 && i < t0 + w;
-    outz[(int64_t)i * w + c] = piv ? 0.0 : acc[r];
-    Cz[(int64_t)i * w + c] = piv ? 0.0 : Csh[h * 4 + r][c];
+    const int i = r0 + 4 * r + lr;
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int col = wave * 32 + 16 * j + lc;
+      if (i < n && col < w) outz[(int64_t)i * w + col] = acc[j][r];
+    }
   }
 }
 // pivot rows after the sweep of rows t0 .. t0 + w, for the 32 rows i0 ..: N(t0 + c, l) = CD[l][c] outside the pivot, -D on it
@@ -879,7 +901,6 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
   const int64_t tot = (int64_t)n * n;
   int blocks = (int)((tot + 1023) / 1024); if (blocks > 131072) blocks = 131072;
   hipLaunchKernelGGL(widen_lower_kernel, dim3(blocks), dim3(256), 0, s, H, ldh, n, A64);
-  double* panel = panels;
   const size_t shmem = SW_LDS_BYTES;
   {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(sweep_update64_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
@@ -888,7 +909,9 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
   const int tiles = (n + 127) / 128, nr = (tiles + 7) / 8;
   const unsigned upd_grid = (unsigned)((nr * (nr + 1) / 2 + 7) / 8 * 8 * 64) * 2;      // two workgroups per tile
   const int rb = (n + PANEL_ROWS64 - 1) / PANEL_ROWS64;
-  const bool two = side && side->stream && tiles > 2;
+  // (up to ten tiles a side the whole update takes as long as the next panel's part of it: 1152 rows 0.66 ms in order, 0.69 on two streams;
+  // 2048 rows 1.43 and 1.25)
+  const bool two = side && side->stream && tiles > 10;
   hipError_t err;
   bool pending = false;              // a bulk update is running on the side stream
   for (int t0 = 0, k = 0; t0 < n; t0 += INV_NB, k++) {
@@ -896,8 +919,8 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
     // operand panels alternate: the bulk update of step k - 1 may still be reading the other pair
     double* panelDz = panels + (int64_t)(1 + 2 * (k & 1)) * n * INV_NB;
     double* panelCz = panelDz + (int64_t)n * INV_NB;
-    hipLaunchKernelGGL(panel_inverse64_kernel, dim3(rb + 1), dim3(IB_T), 0, s, A64, (int64_t)n, n, t0, w, panel, small, notpd_flag);
-    hipLaunchKernelGGL(panel_times_small64_kernel, dim3((n + 7) / 8), dim3(256), 0, s, panel, small, n, w, t0, panelDz, panelCz);
+    hipLaunchKernelGGL(panel_inverse64_kernel, dim3(rb + 1), dim3(IB_T), 0, s, A64, (int64_t)n, n, t0, w, panelCz, small, notpd_flag);
+    hipLaunchKernelGGL(panel_times_block64_kernel, dim3((n + 15) / 16), dim3(256), 0, s, panelCz, small, n, w, panelDz);
     if (!two) {
       hipLaunchKernelGGL(sweep_update64_kernel, dim3(upd_grid + rb), dim3(512), shmem, s, panelDz, panelCz, n, w, A64, 0, k, upd_grid, small);
       continue;
