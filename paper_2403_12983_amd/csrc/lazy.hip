@@ -16,9 +16,8 @@
 // will be pivots before the next flush is predictable (in the largest layers the LAZY_NPICK_OUT cheapest removals and
 // LAZY_NPICK_IN largest gains at flush time cover all but a few per thousand of them), so right after each flush one matrix
 // product Zc Z0^T computes those products for these candidate rows (GbT); a pivot outside the candidates costs one read-only pass
-// over Z0 for its column (kept in one of LAZY_NS spare slots), a launch of its own.  At most 32 candidates a side come from each
-// 1024 rows, so layers of up to 2048 rows have 32 or 64 a side and miss more often (826 rows, 199 swaps: 192 pivots of 398), and the
-// removal-only loops have their LAZY_NC from 7169 rows on.  Every
+// over Z0 for its column (kept in one of LAZY_NS spare slots), a launch of its own.  A layer of up to 11 blocks of 1024 rows takes all its
+// picks from one of them if that is where they are; of more blocks each gives 1024 / blocks a side at most.  Every
 // LAZY_TM/2 iterations the pending rank-tau correction is applied to N0 and Z0 by matrix products on the
 // matrix cores.  The sequence of swaps is exactly that of the eager search (Proposition 4.1, Cases 1-3).
 //

@@ -548,6 +548,15 @@ def test_swaps_in_one_launch(p, m, k, swaps):
             assert Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-5 * torch.linalg.norm(We)
 
 
+@pytest.mark.parametrize("p,m,k,swaps", [(63, 8, 30, 40), (64, 504, 32, 40), (65, 520, 32, 40), (129, 1032, 60, 70), (4097, 1000, 2000, 70),
+                                         (16320, 512, 8000, 66), (16321, 520, 8000, 66), (25472, 24, 12000, 66), (25473, 24, 12000, 66)])
+def test_products_computed_ahead_in_64_rows(p, m, k, swaps):
+    """The same at the edges of the products' 64-row workgroups, of their last stage of 32 columns, of the cut of the columns in two (from 512 on,
+    below 256 workgroups) and of the 199 workgroups of 128 rows beyond which these do them.  Bounds as there: three bf16 terms a factor
+    leave 2^-24 of a product, as the float32 storage does."""
+    test_swaps_in_one_launch(p, m, k, swaps)
+
+
 @pytest.mark.parametrize("p,m,k,swaps", [(31, 3, 15, 40), (32, 8, 16, 40), (600, 72, 300, 90), (8192, 40, 4000, 150), (8193, 8, 4100, 70),
                                          (16384, 40, 8000, 66), (16385, 16, 8001, 66), (32768, 8, 16384, 66), (32769, 8, 16384, 10)])
 def test_runs_of_swaps(p, m, k, swaps):
