@@ -812,7 +812,8 @@ static osscar_status gram_impl(osscar_ctx* c, const char* who, int target, const
     c->timers[0] = 0;
   }
   const PackedGram packed{&c->queue, d1, PackedAcc{H64, h_copies, &c->h_copies}, c->tiles_h, Xt, m, PackedAcc{G64, g_copies, &c->g_copies}, c->tiles_g,
-                          target ? Ys : nullptr, (int)(PACK_ROWS / 64), target ? nullptr : c->ev_g, EV_SAMPLES};
+                          target ? Ys : nullptr, (int)(PACK_ROWS / 64), target ? nullptr : c->ev_g, EV_SAMPLES,
+                          reinterpret_cast<double*>(c->scratch + cv.off), c->scratch_bytes - cv.off};
   if (n_c > 0) {
     if (finalize) HIPCHK(c, hipEventRecord(c->ev_a, s));      // (the last call's time is the one that is kept)
     const bool bf16 = c->desc.x_dtype == OSSCAR_BF16;

@@ -132,11 +132,11 @@ __global__ __launch_bounds__(256) void gram_pack_conv_kernel(const uint16_t* __r
 // H64 += acc + acc2 for a wave's RT x CT MFMA tiles at (row0, col0); symmetric: on and below the diagonal only.  C layout of the
 // 32 x 32 MFMA: register r = rr*4 + r3 holds row rr*8 + (lane/32)*4 + r3, column lane%32.  A workgroup is the only one that
 // touches its tile in a launch, so these are plain loads and stores, a batch of 4 CT loads ahead of the batch that is stored
-// (or, atomics, additions that the few workgroups of a small launch do not wait for):
+// (or, atomics, additions that the few workgroups of a small launch do not wait for; or, fresh, stores of a part's sums by themselves):
 // with atomics throughout 8192 columns, 2048 rows took 0.305 ms, 0.251 so, 0.19 without reading H64.
 template <int RT, int CT, typename A2>
 __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const A2 (&acc2)[RT][CT], double* __restrict__ H64, int ldo, int row0,
-                                         int col0, int rows_out, int cols_out, int symmetric, int lane, int atomics = 0) {
+                                         int col0, int rows_out, int cols_out, int symmetric, int lane, int atomics = 0, int fresh = 0) {
   // opaque: keeps the compiler from computing all the addresses and conditions ahead of the main loop
   int ldv = ldo;
   asm volatile("" : "+s"(ldv), "+v"(lane));
@@ -157,6 +157,15 @@ __device__ __forceinline__ void add_tile(const f16v (&acc)[RT][CT], const A2 (&a
           const int a = batch >> 2, r = (batch & 3) * 4 + r3, ro = a * 32 + (batch & 3) * 8 + r3;
           if (inside(ro, b)) unsafeAtomicAdd(hbase + (int64_t)ro * ldv + b * 32, (double)acc[a][b][r] + (double)acc2[a][b][r]);
         }
+    return;
+  }
+  if (fresh) {      // the whole tile: its buffer holds what lies outside the result, too
+#pragma unroll
+    for (int a = 0; a < RT; a++)
+#pragma unroll
+      for (int r = 0; r < 16; r++)
+#pragma unroll
+        for (int b = 0; b < CT; b++) hbase[(int64_t)(a * 32 + (r >> 2) * 8 + (r & 3)) * ldv + b * 32] = (double)acc[a][b][r] + (double)acc2[a][b][r];
     return;
   }
   auto load = [&](int batch) {
@@ -319,19 +328,26 @@ template <int CT>
 __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) void gram_wide_kernel(
     const uint4* __restrict__ Ap, int a_panels, const uint4* __restrict__ Bp, int b_panels, int pstages, int nstages, int rows_out,
     int cols_out, int ldo, double* __restrict__ H64, int64_t copy_stride, const int2* __restrict__ tile_list, int per, int window, int range,
-    uint64_t ends_lo, uint64_t ends_hi, int symmetric) {
+    uint64_t ends_lo, uint64_t ends_hi, int symmetric, int whole, int tail_parts, int tail_per, double* __restrict__ tail_out) {
   constexpr int TC = CT * 64, GW_ST = GW_A + CT * 256;
   typedef typename std::conditional<CT == 2, double, float>::type A2;
   typedef typename std::conditional<CT == 2, d16v, f16v>::type A2v;
   __shared__ uint4 lb0[GW_ST], lb1[GW_ST], lb2[GW_ST], lb3[GW_ST];
-  const int2 tile = tile_list[blockIdx.x];
+  // workgroups from `whole` on: a part of a tile each, whose sums go to a tile of tail_out
+  const int in_tail = CT == 2 && (int)blockIdx.x >= whole ? (int)blockIdx.x - whole : -1;
+  const int2 tile = tile_list[in_tail >= 0 ? whole + in_tail / tail_parts : (int)blockIdx.x];
   if (tile.x < 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  int py = (int)blockIdx.y;
+  H64 += (int64_t)py * copy_stride;
+  if (in_tail >= 0) {
+    py = in_tail % tail_parts; per = tail_per; range = 2 * tail_per; ldo = TC;
+    H64 = tail_out + (int64_t)in_tail * (GW_R * TC) - ((int64_t)tile.x * GW_R * TC + tile.y * TC);
+  }
   // stages of 32 tokens from here on (so are window and range); the part of the contraction that this workgroup takes
-  const int part = 2 * per * (int)blockIdx.y, nst = min(2 * nstages, part + 2 * per);
+  const int part = 2 * per * py, nst = min(2 * nstages, part + 2 * per);
   if (part >= nst) return;
-  H64 += (int64_t)blockIdx.y * copy_stride;
 #define OSSCAR_GW_LOAD(st_, buf_)                                                                               \
   {                                                                                                             \
     _Pragma("unroll") for (int i = 0; i < NL; i++)                                                              \
@@ -425,7 +441,8 @@ __global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         OSSCAR_GW_TAIL(st, lb0, lb1); OSSCAR_GW_TAIL(st + 1, lb1, lb2); OSSCAR_GW_TAIL(st + 2, lb2, lb3); OSSCAR_GW_TAIL(st + 3, lb3, lb0);
         if (st + 4 < end) OSSCAR_GW_FOLD(st);      // the last window goes to float64 by itself
       }
-      add_tile<2, CT>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * TC + wn * (TC / 2), rows_out, cols_out, symmetric, lane);
+      add_tile<2, CT>(acc, acc2, H64, ldo, tile.x * GW_R + wm * 64, tile.y * TC + wn * (TC / 2), rows_out, cols_out, symmetric, lane, 0,
+                      in_tail >= 0);
     }
   };
   if (wave < 4) run(std::integral_constant<int, 4>{}); else run(std::integral_constant<int, CT>{});
@@ -542,7 +559,7 @@ static hipError_t launch_packed(const uint4* Ap, const uint4* Bp, int pstages, i
   if (takes_wide(t, nstages, ntiles, window)) {
     hipLaunchKernelGGL(gram_wide_kernel<3>, dim3((unsigned)t.wide_entries), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
                        (cols_out + 127) / 128 * 2, pstages, nstages, rows_out, cols_out, cols_out, acc.out, elems, t.wide, nstages, 2 * window,
-                       2 * range, 0ull, 0ull, symmetric);
+                       2 * range, 0ull, 0ull, symmetric, 0, 1, 0, (double*)nullptr);
     return hipGetLastError();
   }
   const int per = (ranges + acc.copies - 1) / acc.copies * range, parts = (nstages + per - 1) / per;
@@ -562,14 +579,51 @@ static int queue_parts(int nstages, const PackedTiles& t, int copies) {
 static bool queue_fills(int nstages, const PackedTiles& t, int copies) {
   return t.tall && t.tall_entries > 0 && t.tall_entries * queue_parts(nstages, t, copies) >= GW_MIN_TILES;
 }
-static hipError_t launch_queued(const uint4* Ap, const uint4* Bp, int pstages, const PackQueue& q, int window, int rows_out, int cols_out,
-                                const PackedAcc& acc, const PackedTiles& t, int symmetric, hipStream_t s) {
+// Out += the parts of the tiles that were cut, in order: 16 rows of a tile per workgroup, a column of eight per thread, so that a row is read as a
+// whole.  Bound by reading the parts (64 MB at most).
+__global__ __launch_bounds__(256) void gram_tail_kernel(const double* __restrict__ parts_in, int parts, const int2* __restrict__ tiles, int rows_out, int cols_out,
+                                                         double* __restrict__ out, int symmetric) {
+  const int2 tile = tiles[blockIdx.x];
+  if (tile.x < 0) return;
+  const int c = threadIdx.x & 127, r0 = blockIdx.y * 16 + (threadIdx.x >> 7) * 8;
+  const int col = tile.y * 128 + c;
+  const double* in = parts_in + (int64_t)blockIdx.x * parts * (GW_R * 128) + r0 * 128 + c;
+  double v[8];
+#pragma unroll
+  for (int r = 0; r < 8; r++) {
+    const int row = tile.x * GW_R + r0 + r;
+    v[r] = row < rows_out && col < cols_out && (!symmetric || col <= row) ? out[(int64_t)row * cols_out + col] : 0.0;
+  }
+  for (int p = 0; p < parts; p++)
+#pragma unroll
+    for (int r = 0; r < 8; r++) v[r] += in[(int64_t)p * (GW_R * 128) + r * 128];
+#pragma unroll
+  for (int r = 0; r < 8; r++) {
+    const int row = tile.x * GW_R + r0 + r;
+    if (row < rows_out && col < cols_out && (!symmetric || col <= row)) out[(int64_t)row * cols_out + col] = v[r];
+  }
+}
+static hipError_t launch_queued(const PackedGram& g, const uint4* Ap, const uint4* Bp, int window, int rows_out, int cols_out, const PackedAcc& acc,
+                                const PackedTiles& t, int symmetric, hipStream_t s) {
+  const PackQueue& q = *g.q;
   const int64_t elems = (int64_t)rows_out * cols_out;
   const int most = queue_parts(q.stages, t, acc.copies), per = ((q.stages + most - 1) / most + 1) / 2 * 2, parts = (q.stages + per - 1) / per;
   clear_copies(acc, parts, elems, s);
-  hipLaunchKernelGGL(gram_wide_kernel<2>, dim3((unsigned)t.tall_entries, (unsigned)parts), dim3(512), 0, s, Ap, (rows_out + 127) / 128 * 2, Bp,
-                     (cols_out + 127) / 128 * 2, pstages, q.stages, rows_out, cols_out, cols_out, acc.out, elems, t.tall, per, 2 * window, 2 * per,
-                     q.ends[0], q.ends[1], symmetric);
+  // Tiles that do not fill a last round of the 256 compute units (one workgroup each) are cut along the rows, as many parts of at least
+  // GW_MIN_PART stages as fill one, and the parts' sums added up by a second launch.  16384 rows in calls of 2048, repacking included: 4096
+  // columns (272 tiles) 487 us whole, 361 so; 8192 (1056) 1330 and 1240; 9216 (1332, cut in four) 1690 and 1580.
+  const int left = (int)(t.tall_entries % 256), rounds = (int)(t.tall_entries / 256);
+  int cut = 1;
+  if (parts == 1 && rounds > 0 && left > 0)
+    cut = std::min({256 / left, q.stages / GW_MIN_PART, (int)std::min<size_t>(256, g.spare_bytes / ((size_t)left * GW_R * 128 * 8))});
+  int tail_per = q.stages;
+  if (cut > 1) { tail_per = ((q.stages + cut - 1) / cut + 1) / 2 * 2; cut = (q.stages + tail_per - 1) / tail_per; }
+  const int whole = cut > 1 ? rounds * 256 : (int)t.tall_entries;
+  hipLaunchKernelGGL(gram_wide_kernel<2>, dim3((unsigned)(cut > 1 ? whole + left * cut : whole), (unsigned)parts), dim3(512), 0, s, Ap,
+                     (rows_out + 127) / 128 * 2, Bp, (cols_out + 127) / 128 * 2, g.pack_stages, q.stages, rows_out, cols_out, cols_out, acc.out, elems, t.tall,
+                     per, 2 * window, 2 * per, q.ends[0], q.ends[1], symmetric, whole, std::max(cut, 1), tail_per, g.spare);
+  if (cut > 1)
+    hipLaunchKernelGGL(gram_tail_kernel, dim3((unsigned)left, GW_R / 16), dim3(256), 0, s, g.spare, cut, t.tall + whole, rows_out, cols_out, acc.out, symmetric);
   return hipGetLastError();
 }
 
@@ -594,7 +648,7 @@ hipError_t launch_gram_queue(const PackedGram& g, hipStream_t s) {
       const int64_t at = (int64_t)st * PK_SLOTS;
       const bool timed = symmetric && g.ev && q.ev_used < g.ev_pairs;
       if (timed) hipEventRecord(g.ev[2 * q.ev_used], s);
-      const hipError_t e = together ? launch_queued(Xp, Bp, g.pack_stages, q, window, g.d1, cols, acc, t, symmetric, s)
+      const hipError_t e = together ? launch_queued(g, Xp, Bp, window, g.d1, cols, acc, t, symmetric, s)
                                     : launch_packed(Xp + at, Bp + at, g.pack_stages, n, g.d1, cols, acc, t, ntiles, 16, symmetric, s);
       if (e != hipSuccess) return e;
       if (timed) { hipEventRecord(g.ev[2 * q.ev_used + 1], s); q.ev_used++; q.ev_rows += (together || q.calls == 1) ? q.rows : std::min<int64_t>(n * GBK, q.rows); }

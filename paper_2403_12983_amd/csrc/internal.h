@@ -111,6 +111,7 @@ struct PackedGram {
   int d1; PackedAcc H64; PackedTiles tiles; void* pack_x;
   int m; PackedAcc G64; PackedTiles tiles_y; void* pack_y;
   int pack_stages; hipEvent_t* ev; int ev_pairs;
+  double* spare; size_t spare_bytes;      // unused memory of the phase, for parts of the tiles that do not fill a round (may be none)
 };
 // Repacks rows into MFMA operand order and accumulates their products, at once or when the buffer is full; launch_gram_queue adds
 // what still waits.  conv (optional): Xc is a feature map (NCHW, bf16) and the rows are its patches.

@@ -633,6 +633,15 @@ def test_rows_of_several_calls_in_one_product(d1, m, chunks, target):
         assert torch.equal(G[2:], (Xd.T @ Y.double())[2:])
 
 
+@pytest.mark.parametrize("target", [False, True])
+@pytest.mark.parametrize("d1,m,chunks", [(4096, 1096, [2048] * 8 + [0]), (4104, 2000, [2048] * 8 + [1, -130, 66]), (5632, 1536, [4000, 4000, 5000]),
+                                         (2056, 3720, [1000, 3000, 4500, 66])])
+def test_tiles_that_do_not_fill_a_round(d1, m, chunks, target):
+    """The same where the result's 256 x 128 tiles (272, 289 with remainders on either side, 506, which stay whole, and 45 beside 270 of the target's)
+    leave a last round of the compute units nearly empty and are cut along the rows."""
+    test_rows_of_several_calls_in_one_product(d1, m, chunks, target)
+
+
 @pytest.mark.parametrize("costs", ["shuffled", "equal", "ascending"])
 @pytest.mark.parametrize("p,t_hat", [(40, 3), (70, 16), (1030, 10), (8192, 16), (8193, 7), (30100, 16), (30144, 16), (30145, 16)])
 def test_picks_of_block_removals(p, t_hat, costs):
