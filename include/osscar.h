@@ -173,14 +173,15 @@ osscar_status osscar_init_greedy(osscar_ctx* ctx, int32_t t_hat, int32_t refresh
  * more pass over Z per iteration and runs on the in-place path; trace_gap[2i+1] then refers to these scores.
  * Such swaps are made many to a launch where all workgroups fit the GPU at once; OSSCAR_SEARCH_LAUNCH_PER_SWAP makes
  * every swap a launch of its own (the same swaps).  A launch whose workgroups wait for one another longer than 2 ms, because
- * other work keeps some of them from starting, is given up without effect and the rest of the call goes a launch per swap;
- * OSSCAR_SEARCH_IMPATIENT (for tests) gives up at the first wait.
+ * other work keeps some of them from starting, is given up without effect, the launches enqueued behind it are idle, and the rest of the call
+ * goes a launch per swap.  For tests: OSSCAR_SEARCH_IMPATIENT gives up the first launch of many swaps, OSSCAR_SEARCH_IMPATIENT_LATER
+ * the first one that goes on behind fetched products with swaps pending, with another one enqueued behind it.
  * refresh_every > 0 recomputes V, R and B from P, H, G by GEMM after that many accepted swaps.
  * Optional host outputs of length max_swaps (entry i describes iteration i, including a final rejected
  * one): trace_out / trace_in = group leaving / entering; trace_gap[2i], trace_gap[2i+1] = relative gap
  * between best and second-best removal cost / addition gain; trace_obj[i] = obj after the iteration. */
 enum { OSSCAR_SEARCH_ALWAYS_ACCEPT = 1u, OSSCAR_SEARCH_EAGER = 2u, OSSCAR_SEARCH_NO_LOOKAHEAD = 4u, OSSCAR_SEARCH_EXACT_IN = 8u,
-       OSSCAR_SEARCH_LAUNCH_PER_SWAP = 16u, OSSCAR_SEARCH_IMPATIENT = 32u };
+       OSSCAR_SEARCH_LAUNCH_PER_SWAP = 16u, OSSCAR_SEARCH_IMPATIENT = 32u, OSSCAR_SEARCH_IMPATIENT_LATER = 64u };
 typedef struct {
   int32_t iters;     /* iterations run (accepted swaps + at most one rejected) */
   int32_t accepted;  /* swaps applied */
@@ -250,7 +251,7 @@ osscar_status osscar_get_timers(osscar_ctx* ctx, double* out_host);
  * [0] flushes (the pending low-rank correction applied to the stored state by matrix products), [1] how many of them the
  * kernels asked for by stopping early (a selected group was still pending, or the spare slots for products not computed
  * ahead ran out), [2] pivots whose products with Z had not been computed ahead (each costs one pass over Z), [3] iterations
- * run; [4] launches that could make several swaps; [5..7] reserved (zero).  out_host: 8 int64. */
+ * run; [4] launches that could make several swaps, [5] whether one of them was given up; [6..7] reserved (zero).  out_host: 8 int64. */
 osscar_status osscar_get_counters(osscar_ctx* ctx, int64_t* out_host);
 
 /* Diagnostic log of the library's general matrix-product launches (all contexts of the process; not thread-safe).

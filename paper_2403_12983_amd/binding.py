@@ -17,6 +17,7 @@ OSSCAR_SEARCH_NO_LOOKAHEAD = 4
 OSSCAR_SEARCH_EXACT_IN = 8
 OSSCAR_SEARCH_LAUNCH_PER_SWAP = 16
 OSSCAR_SEARCH_IMPATIENT = 32
+OSSCAR_SEARCH_IMPATIENT_LATER = 64
 T_H, T_G, T_P, T_B, T_V, T_R, T_REM, T_ADD, T_KEPT, T_CAND = range(10)
 _STATUS = {0: "OK", 1: "EINVAL", 2: "ENOMEM", 3: "ENOTPD", 4: "EHIP", 5: "ESTATE"}
 
@@ -296,7 +297,7 @@ class Solver:
     def osscar_get_counters(self):
         arr = (C.c_int64 * 8)()
         self._check(self.lib.osscar_get_counters(self.ctx, arr))
-        return dict(flushes=arr[0], pauses=arr[1], lookahead_misses=arr[2], iters=arr[3], runs=arr[4])
+        return dict(flushes=arr[0], pauses=arr[1], lookahead_misses=arr[2], iters=arr[3], runs=arr[4], runs_given_up=arr[5])
 
 
 def gemm_log(enable: bool):

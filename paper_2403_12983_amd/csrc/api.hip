@@ -1273,6 +1273,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     int missing = 0;                                             // in this one so far
     bool runs = c->runs_fit && la_mode == 0 && !(flags & OSSCAR_SEARCH_LAUNCH_PER_SWAP), owed = false;
     const uint32_t patience = (flags & OSSCAR_SEARCH_IMPATIENT) ? 0u : RUN_PATIENCE;
+    const bool impatient_later = (flags & OSSCAR_SEARCH_IMPATIENT_LATER) != 0;
     double flush_ms = 0; int flushes = 0, pauses = 0;
     bool flush_open = false;                 // a flush whose events have not been read yet
     auto collect = [&]() {                   // only after the stream has been waited for
@@ -1301,11 +1302,12 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
       bool sampled = sample;
       if (by_run) {
         // a run ends before a pivot whose products are missing; the launch behind it fetches them, and the next run goes on
-        const int more = many ? 0 : std::min(extra, 4);
+        const bool give_up = impatient_later && owed && h.tau > 0;      // (tests)
+        const int more = many ? 0 : std::max(std::min(extra, 4), give_up ? 1 : 0);
         sampled = sample && !owed && more == 0;
         if (owed) HIPCHK(c, run.swap(always, before + nb, SwapList(), true));
         if (sampled) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][0], s));
-        HIPCHK(c, run.run(always, before + nb, nb, patience));
+        HIPCHK(c, run.run(always, before + nb, nb, give_up ? 0u : patience));
         if (sampled) HIPCHK(c, hipEventRecord(c->ev_s[samples + 1][1], s));
         for (int i = 0; i < more && run.can_run(); i++) {
           HIPCHK(c, run.swap(always, before + nb, SwapList(), true));
@@ -1364,6 +1366,7 @@ osscar_status osscar_local_search(osscar_ctx* c, int32_t max_swaps, double rel_t
     if (flush_open) { HIPCHK(c, wait(c)); collect(); }
     c->timers[6] = refresh_ms + flush_ms;
     c->counters[0] = flushes; c->counters[1] = pauses; c->counters[2] = h.misses; c->counters[3] = h.iters; c->counters[4] = run.all_runs;
+    c->counters[5] = h.stalled;
   } else {
   // Searches of groups often end after a few moves, and a move enqueued past the end is four idle launches (10 us): batches of 4, 8, 16, 32, ...
   // (32 from the start: a layer of 32 groups of 64 rows that makes six moves took 0.25 ms longer; a wait costs 20 us).

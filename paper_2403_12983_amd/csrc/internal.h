@@ -180,7 +180,7 @@ struct SearchCtrl {          // lives in device memory
   double rel_tol;
   double delta;              // exact change of the current pair
   double gap_rem, gap_add;
-  int32_t stalled;           // a run of swaps (swaprun.hip) waited too long and left everything as it was
+  int32_t stalled;           // a run of swaps (swaprun.hip) waited too long and left everything as it was; runs behind it make no swap
   int32_t spare;             // one-launch swaps: spare slots of the look-ahead products in use (below zero: slots of picked rows are spare too)
   int32_t taken;             // groups: whether the pair of this iteration is taken, until the scores' launch records it
 };

@@ -14,8 +14,9 @@
 // A launch each pays for the records, M^-1 and the rows to come from memory each time, and for the launch.
 //
 // No workgroup waits for ever.  One that has waited `patience` gives up, and all of them then agree (arrived, verdict) whether the run
-// counts: what a run leaves is written after that, so a run that does not count leaves the state as it was, and the host makes its swaps
-// a launch each.  That happens where other work keeps some of the workgroups from starting.
+// counts: what a run leaves is written after that, so a run that does not count leaves the state as it was (what has two copies is copied:
+// control block, records, M^-1, L), the runs enqueued behind it make no swap, and the host makes them a launch each.  That happens where
+// other work keeps some of the workgroups from starting.
 // GIVEN: the pairs stand in a list, nothing has to be agreed on, and no workgroup waits for another.
 #include "internal.h"
 #include "lazy_device.h"
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
   // ---- the state as the last launch left it
   int tau = P->cin->tau, iters = P->cin->iters, done = P->cin->done, pause = P->cin->pause, notpd = P->cin->notpd, accepted = 0;
   const int spare = P->cin->spare, tau_start = tau;
-  if (done | pause) limit = iters;
+  if (done | pause | P->cin->stalled) limit = iters;      // (a launch before this one was given up: the host goes on)
   if (tid < TM) { const bool in = tid < tau; s_T[tid] = in ? P->Tidx[tid] : 0; s_slot[tid] = in ? P->tslot[tid] : 0; s_sign[tid] = in && P->Jsg[tid] > 0.f ? 1 : -1; }
   if (tid == 0) {
     s_flag = 0; s_rec = P->rec[wg]; s_obj[iters & 1] = P->cin->obj;
@@ -596,6 +597,9 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
 
   // ---- does the run count?
   __syncthreads();      // the last swap's rows
+  if constexpr (!GIVEN) {      // without patience (tests) the last workgroup gives up for certain, whether or not it had to wait
+    if (A.patience == 0 && swapped) { waited = true; stalled |= wg == nwg - 1; }
+  }
   bool counts = !stalled;
   if constexpr (!GIVEN) {
     if (waited) {      // the same in every workgroup
@@ -632,7 +636,7 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
       const int r = 4 * rq + i, c = 32 * v + 2 * l;
       if ((i * 4 + v) % nwg == wg) {
         if (r < tw && c < tw) *reinterpret_cast<d2*>(E->Minv2 + r * TM + c) = counts ? mv[i][v] : *reinterpret_cast<const d2*>(E->Minv + r * TM + c);
-        if (counts && r < tw && c < tw) *reinterpret_cast<d2*>(E->LL2 + r * TM + c) = lv[i][v];
+        if (r < tw && c < tw) *reinterpret_cast<d2*>(E->LL2 + r * TM + c) = counts ? lv[i][v] : *reinterpret_cast<const d2*>(E->LL + r * TM + c);
       }
     }
   if (!counts) return;

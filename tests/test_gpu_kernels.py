@@ -557,6 +557,18 @@ def test_products_computed_ahead_in_64_rows(p, m, k, swaps):
     test_swaps_in_one_launch(p, m, k, swaps)
 
 
+def _same_swaps(r, e, Wr, We, Sr, Se):
+    """The search r took the swaps of e, except behind a choice between two groups that score alike."""
+    n = min(r["iters"], e["iters"])
+    same = (r["trace_out"][:n] == e["trace_out"][:n]) & (r["trace_in"][:n] == e["trace_in"][:n])
+    n = n if same.all() else int(np.argmin(same))
+    assert n == e["iters"] == r["iters"] or e["trace_gap"][n].min() <= 1e-9
+    assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-9, atol=0)
+    assert np.allclose(r["trace_gap"][:n], e["trace_gap"][:n], rtol=1e-5, atol=1e-9)
+    if n == e["iters"]:
+        assert r["accepted"] == e["accepted"] and Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-6 * torch.linalg.norm(We)
+
+
 @pytest.mark.parametrize("p,m,k,swaps", [(31, 3, 15, 40), (32, 8, 16, 40), (600, 72, 300, 90), (8192, 40, 4000, 150), (8193, 8, 4100, 70),
                                          (16384, 40, 8000, 66), (16385, 16, 8001, 66), (32768, 8, 16384, 66), (32769, 8, 16384, 10)])
 def test_runs_of_swaps(p, m, k, swaps):
@@ -582,18 +594,36 @@ def test_runs_of_swaps(p, m, k, swaps):
     s.close()
     (e, ce, (We, Se, _)) = out[0]
     assert ce["runs"] == 0 and (out[1][1]["runs"] > 0) == (p <= 32768)
+    assert out[2][1]["runs"] == out[2][1]["runs_given_up"] == (p <= 32768)
     for r, c, (Wr, Sr, _) in out[1:]:
-        n = min(r["iters"], e["iters"])
-        same = (r["trace_out"][:n] == e["trace_out"][:n]) & (r["trace_in"][:n] == e["trace_in"][:n])
-        n = n if same.all() else int(np.argmin(same))
-        assert n == e["iters"] == r["iters"] or e["trace_gap"][n].min() <= 1e-9
-        assert np.allclose(r["trace_obj"][:n], e["trace_obj"][:n], rtol=1e-9, atol=0)
-        assert np.allclose(r["trace_gap"][:n], e["trace_gap"][:n], rtol=1e-5, atol=1e-9)
-        if n == e["iters"]:
-            assert r["accepted"] == e["accepted"] and Sr.tolist() == Se.tolist() and torch.linalg.norm(Wr - We) <= 1e-6 * torch.linalg.norm(We)
+        _same_swaps(r, e, Wr, We, Sr, Se)
     (a, (Wa, Sa, _)), (b, (Wb, Sb, _)) = moves
     assert a["moves"] == b["moves"] and a["accepted"] == b["accepted"] and Sa.tolist() == Sb.tolist()
     assert abs(a["obj_final"] - b["obj_final"]) <= 1e-9 * abs(a["obj_final"]) and torch.linalg.norm(Wa - Wb) <= 1e-6 * torch.linalg.norm(Wa)
+
+
+@pytest.mark.parametrize("p,m,k,swaps", [(600, 72, 300, 180), (2000, 400, 900, 250), (8193, 8, 4100, 250), (16385, 16, 8001, 200)])
+def test_run_given_up_with_swaps_pending(p, m, k, swaps):
+    """A run that goes on behind fetched products, with the swaps of the run before still pending, is given up, with another run already
+    enqueued behind it: the same swaps as with a launch each.  Neighbouring columns are correlated, so that some pivots' products have to be
+    fetched.  Bounds as above."""
+    pkg = _pkg()
+    g = torch.Generator(device=DEV).manual_seed(p)
+    X = torch.randn(2 * p + 64 if p < 1000 else 1024, p, generator=g, device=DEV) * torch.exp(0.5 * torch.randn(p, generator=g, device=DEV))
+    X = X + 0.3 * torch.roll(X, -1, dims=1)
+    W = torch.randn(p, m, generator=g, device=DEV) / p ** 0.5
+    s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
+    s.osscar_gram(X, True, W, 0.0, 5e-2)
+    out = []
+    for flags in (pkg.OSSCAR_SEARCH_LAUNCH_PER_SWAP, pkg.OSSCAR_SEARCH_IMPATIENT_LATER):
+        s.osscar_init_support()
+        r = s.osscar_local_search(swaps, 0.0, flags | pkg.OSSCAR_SEARCH_ALWAYS_ACCEPT)
+        out.append((r, s.osscar_get_counters(), s.osscar_backsolve()))
+    s.close()
+    (e, ce, (We, Se, _)), (r, c, (Wr, Sr, _)) = out
+    assert ce["runs_given_up"] == 0 and ce["lookahead_misses"] > 0
+    assert c["runs_given_up"] == 1 and c["runs"] >= 3
+    _same_swaps(r, e, Wr, We, Sr, Se)
 
 
 @pytest.mark.parametrize("target", [False, True])
