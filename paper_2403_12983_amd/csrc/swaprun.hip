@@ -122,7 +122,7 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
   constexpr bool C_LDS = R >= 2;                                  // C0 of several rows, and of four the products' last stretch,
   constexpr int GV = R == 4 ? 3 : 4;                              // are in shared memory: the registers do not hold them
   __shared__ double s_v[2][8], s_2nd[8];      // (the gaps are taken while other waves are at the next pick)
-  __shared__ int s_i[8], s_s[8], s_T[TM], s_slot[TM], s_flag;
+  __shared__ int s_i[8], s_s[8], s_T[TM], s_slot[TM], s_flag, s_late;
   __shared__ __attribute__((aligned(16))) double sb[2][TM], sk[2][TM], sx[2][TM], sp[2][TM], sa[4][TM];
   __shared__ double s_kk[3], s_row[4][RPW], s_new[2][RPW], s_half[2][2];
   __shared__ float s_n0[3], s_c[2][RPW];
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
   if (done | pause | P->cin->stalled) limit = iters;      // (a launch before this one was given up: the host goes on)
   if (tid < TM) { const bool in = tid < tau; s_T[tid] = in ? P->Tidx[tid] : 0; s_slot[tid] = in ? P->tslot[tid] : 0; s_sign[tid] = in && P->Jsg[tid] > 0.f ? 1 : -1; }
   if (tid == 0) {
-    s_flag = 0; s_rec = P->rec[wg]; s_obj[iters & 1] = P->cin->obj;
+    s_flag = 0; s_late = 0; s_rec = P->rec[wg]; s_obj[iters & 1] = P->cin->obj;
     s_run.delta = P->cin->delta; s_run.gap_rem = P->cin->gap_rem; s_run.gap_add = P->cin->gap_add;
   }
   d2 mv[4][4], lv[4][4];      // M^-1 and ZT ZT^T: rows 4 rq + i, columns 32 v + 2 l and the next
@@ -316,11 +316,16 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
       }
       if constexpr (!GIVEN) {
         if (wg == 0) {      // second-best values: every record's best unless it is the pick
-          if (exchanges > 0) {      // (sent behind the others' first words, which are here; should they not be, the gap is of what there is)
+          if (exchanges > 0) {      // (sent behind the others' first words, which are here; should they be late by `patience` the run does not count)
             const uint64_t* w = A.sh->word[exchanges & 1][side * WORDS + 3] + min(rt, nwg - 1);
-            uint64_t hi, lo;
-            int tries = 0;
-            do { hi = seen(w); lo = seen(w + RUN_WGS); } while (!__all((uint32_t)(hi >> 32) == (uint32_t)(run * 256 + exchanges) && (uint32_t)(lo >> 32) == (uint32_t)(run * 256 + exchanges)) && ++tries < 10000);
+            uint64_t hi, lo, t0 = 0;
+            while (true) {
+              hi = seen(w); lo = seen(w + RUN_WGS);
+              if (__all((uint32_t)(hi >> 32) == (uint32_t)(run * 256 + exchanges) && (uint32_t)(lo >> 32) == (uint32_t)(run * 256 + exchanges))) break;
+              const uint64_t now = __builtin_amdgcn_s_memrealtime();
+              if (t0 == 0) t0 = now;
+              if (now - t0 >= args_again()->patience) { s_late = 1; break; }
+            }
             v2 = rt < nwg ? __hiloint2double((int)(uint32_t)hi, (int)(uint32_t)lo) : INFINITY;
           }
           const double sec = wave_min(i1 >= 0 && i1 != (side ? pick_j : pick_g) ? v1 : v2);
@@ -597,7 +602,9 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
 
   // ---- does the run count?
   __syncthreads();      // the last swap's rows
-  if constexpr (!GIVEN) {      // without patience (tests) the last workgroup gives up for certain, whether or not it had to wait
+  if constexpr (!GIVEN) {
+    if (s_late) stalled = true;
+    // without patience (tests) the last workgroup gives up for certain, whether or not it had to wait
     if (A.patience == 0 && swapped) { waited = true; stalled |= wg == nwg - 1; }
   }
   bool counts = !stalled;
