@@ -103,6 +103,7 @@ __global__ __launch_bounds__(1024) void cand_local_kernel(LazyPtrs L, int p, con
   const int tid = threadIdx.x, h = blockIdx.x * 1024 + tid, nblk = gridDim.x, side = blockIdx.y;
   const bool valid = (h < p) && ((kept[h] != 0) == (side == 0));
   double key = valid ? (side == 0 ? score[h] : -score[h]) : INFINITY;
+  if (key != key) key = INFINITY;      // not picked (with a NaN the two lanes of an exchange would disagree, and one row would be there twice, another not at all)
   int idx = valid ? h : 0x7fffffff;
   bitonic1024(key, idx, lk, li, tid);
   if (tid < per_block) {

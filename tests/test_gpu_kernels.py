@@ -969,3 +969,24 @@ def test_flushes_without_products_computed_ahead():
     obj, steps, _ = s.osscar_init_greedy(7, 0, pkg.OSSCAR_SEARCH_NO_LOOKAHEAD)
     assert sum(steps, []) == worst
     s.close()
+
+
+@pytest.mark.parametrize("p", [128, 2000])
+def test_rows_without_a_score_do_not_disturb_the_picks(p):
+    """Outside groups whose score is NaN (a NaN in their row of G) are not picked ahead, and every other row is where it would be without
+    them: with H = I the swaps exchange the smallest kept |G_i| for the largest outside ones, in order, and no pivot's products are missing."""
+    pkg = _pkg()
+    m, swaps, k = 8, 30, p // 2
+    G = torch.randn(p, m, generator=torch.Generator().manual_seed(p))
+    G[k:] *= 2.0
+    G[k::8] = float("nan")
+    s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
+    s.osscar_set_quadratic(torch.eye(p).to(DEV), G.to(DEV), 1e6, np.ones(p))
+    s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, range(k))
+    r = s.osscar_local_search(swaps)
+    c = s.osscar_get_counters()
+    s.close()
+    score = (G.double() ** 2).sum(1)
+    assert r["trace_out"].tolist() == torch.argsort(score[:k])[:swaps].tolist()
+    assert r["trace_in"].tolist() == (k + torch.argsort(-score[k:].nan_to_num(0.0))[:swaps]).tolist()
+    assert r["accepted"] == swaps and c["lookahead_misses"] == 0
