@@ -32,7 +32,8 @@ template <typename T>
 __device__ __forceinline__ T at32(const T* p, uint32_t i) { return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + i * (uint32_t)sizeof(T)); }
 
 // Best and second best of a block of RPW rows, cheapest removal by wave 0, largest gain by wave 1; sc, kp (1 kept, 0 not, -1 no row)
-// and sl (slot, or PENDING) in shared memory.
+// and sl (slot, or PENDING) in shared memory.  A row whose score is NaN is none of them (which of the others were compared with it, and lost,
+// would depend on the lanes).
 template <int RPW>
 __device__ __forceinline__ void write_record(SwapRec* rec, const double* sc, const int* kp, const int* sl, int row0, int wave, int lane) {
   constexpr int E = (RPW + 63) / 64;
@@ -42,8 +43,8 @@ __device__ __forceinline__ void write_record(SwapRec* rec, const double* sc, con
 #pragma unroll
   for (int e = 0; e < E; e++) {
     const int k = lane + 64 * e;
-    const bool has = k < RPW && kp[k < RPW ? k : 0] == 1 - wave;
     const double s = sc[k < RPW ? k : 0];
+    const bool has = k < RPW && kp[k < RPW ? k : 0] == 1 - wave && s == s;
     own[e] = has ? (wave == 0 ? s : -s) : INFINITY;
     idx[e] = has ? row0 + k : -1;
     if (idx[e] >= 0 && (i < 0 || own[e] < v)) { v = own[e]; i = idx[e]; }

@@ -501,7 +501,7 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
       const bool live = lane < RPW;
 #pragma unroll
       for (int h = 0; h < 2; h++) {
-        const bool has = live && kp == 1 - h;
+        const bool has = live && kp == 1 - h && sc == sc;      // (no record of a NaN, as in write_record)
         const double v = h == 0 ? sc : -sc;
         const int at = first_best(v, has ? row : -1);
         const bool some = __any(has);

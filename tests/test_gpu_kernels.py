@@ -971,19 +971,20 @@ def test_flushes_without_products_computed_ahead():
     s.close()
 
 
-@pytest.mark.parametrize("p", [128, 2000])
-def test_rows_without_a_score_do_not_disturb_the_picks(p):
-    """Outside groups whose score is NaN (a NaN in their row of G) are not picked ahead, and every other row is where it would be without
+@pytest.mark.parametrize("flags", ["", "OSSCAR_SEARCH_LAUNCH_PER_SWAP"])
+@pytest.mark.parametrize("p,at", [(128, 0), (128, 5), (128, 6), (128, 7), (2000, 0), (2000, 7), (8256, 7), (16448, 3)])
+def test_rows_without_a_score_do_not_disturb_the_picks(p, at, flags):
+    """Outside groups whose score is NaN (a NaN in their row of G) are picked by nothing, and every other row is where it would be without
     them: with H = I the swaps exchange the smallest kept |G_i| for the largest outside ones, in order, and no pivot's products are missing."""
     pkg = _pkg()
     m, swaps, k = 8, 30, p // 2
     G = torch.randn(p, m, generator=torch.Generator().manual_seed(p))
     G[k:] *= 2.0
-    G[k::8] = float("nan")
+    G[k + at::8] = float("nan")
     s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
     s.osscar_set_quadratic(torch.eye(p).to(DEV), G.to(DEV), 1e6, np.ones(p))
     s.osscar_init_support(pkg.OSSCAR_INIT_GIVEN, range(k))
-    r = s.osscar_local_search(swaps)
+    r = s.osscar_local_search(swaps, 0.0, getattr(pkg, flags, 0))
     c = s.osscar_get_counters()
     s.close()
     score = (G.double() ** 2).sum(1)
