@@ -236,8 +236,9 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
     L.ZcP = cv.take<char>((int64_t)LAZY_NC * ((m + 31) / 32 * 32) * 6);
     L.Epk = cv.take<char>((int64_t)768 * ((d1 + 127) / 128 * 128)); L.Cpk = cv.take<char>((int64_t)768 * ((d1 + 127) / 128 * 128));
     L.Zpk = cv.take<char>((int64_t)768 * ((m + 127) / 128 * 128));
-    // runs of swaps: between two flushes in the memory of the flush's packed operands (ZcP to Zpk, 344064 bytes at least)
-    const size_t words = align_up((size_t)swap_run_shared_words() * 8);
+    // runs of swaps: between two flushes in the memory of the flush's packed operands (ZcP to Zpk), which at least holds them
+    constexpr size_t words = ((size_t)RUN_SHARED_WORDS * 8 + 255) / 256 * 256;
+    static_assert((size_t)LAZY_NC * 32 * 6 + 3 * 768 * 128 >= words + 2 * (size_t)LAZY_TM * LAZY_TM * 8, "m <= 32 and d1 <= 128, the smallest ZcP to Zpk");
     L.run_shared = L.ZcP; L.LL = reinterpret_cast<double*>(reinterpret_cast<char*>(L.ZcP) + words); L.LL2 = L.LL + TM * TM;
     L.cslot = cv.take<int32_t>(d1); L.cand = cv.take<int32_t>(LAZY_NC + LAZY_NS); L.tslot = cv.take<int32_t>(LAZY_TM);
     L.lkey = cv.take<double>(2 * 64 * 32); L.lidx = cv.take<int32_t>(2 * 64 * 32);

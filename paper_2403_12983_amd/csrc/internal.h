@@ -307,7 +307,8 @@ constexpr int RUN_MOST = 64;
 hipError_t launch_swap_run(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, SearchCtrl* next, int always_accept, int limit, int run, uint32_t patience,
                            hipStream_t s, const SwapList& l = SwapList());
 bool swap_run_fits(int64_t d1);
-int64_t swap_run_shared_words();
+constexpr int RUN_WGS = 256, RUN_WORDS = 5;                                                 // workgroups at most; words of a record's side
+constexpr int RUN_SHARED_WORDS = 2 * 2 * RUN_WORDS * RUN_WGS + RUN_MOST;                     // the shared words of 64 bits
 // Rows per workgroup: one workgroup per compute unit where the rows allow it (8192 = 256 x 32, 16384 = 256 x 64, 28672 = 224 x 128).
 // More than 256 workgroups would run one after the other, and the algebra of order |T| is the same for each of them.
 constexpr int swap_rows_per_wg(int d1) { return d1 <= 8192 ? 32 : d1 <= 16384 ? 64 : 128; }

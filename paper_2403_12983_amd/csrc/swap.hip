@@ -534,7 +534,7 @@ hipError_t launch_lazy_swap(const TabDims& d, const TabPtrs& t, const LazyPtrs& 
 }
 
 hipError_t launch_swap_records(const TabDims& d, const TabPtrs& t, const LazyPtrs& L, hipStream_t s, bool refresh) {
-  const int nwg = swap_record_count(d.d1), fr = refresh ? 1 : 0, words = (int)swap_run_shared_words();
+  const int nwg = swap_record_count(d.d1), fr = refresh ? 1 : 0, words = RUN_SHARED_WORDS;
   uint64_t* shared = reinterpret_cast<uint64_t*>(L.run_shared);
   switch (swap_rows_per_wg(d.d1)) {
     case 32: hipLaunchKernelGGL(swap_records_kernel<32>, dim3(nwg), dim3(128), 0, s, L, d.d1, t.kept, t.score, t.gram, t.dblk, t.ctrl, fr, shared, words); break;

@@ -27,13 +27,13 @@ namespace osscar {
 
 constexpr int RT = 512;                     // threads: 32 groups of 16 lanes, a group four rows of M^-1, a lane eight of their columns
 constexpr int KROW = LAZY_NC + LAZY_NS;     // row length of K
-constexpr int RUN_WGS = 256;                // workgroups of a run at most
-constexpr int WORDS = 5;                    // of a record's side: best value (2), row and slot, second best value (2)
+constexpr int WORDS = RUN_WORDS;            // of a record's side: best value (2), row and slot, second best value (2)
 // cycles from a swap's last barrier to a wave's first look at the next records: at first; less after a look that found them, more after one
 // that came too early (9.5 us a swap with looks at once, 6.9 so)
 constexpr int HOLD_START = 2000, HOLD_LESS = 16, HOLD_MORE = 256, HOLD_MOST = 16384;
 constexpr int PEND = 1 << 30;               // flag in a record's slot: the row is a pending pivot
 struct RunShared { uint64_t word[2][2 * WORDS][RUN_WGS]; int32_t arrived[RUN_MOST], verdict[RUN_MOST]; };
+static_assert(sizeof(RunShared) == RUN_SHARED_WORDS * 8, "as the workspace has room for");
 static_assert(LAZY_TM == 128, "four stretches of 32 columns");
 
 typedef double d2 __attribute__((ext_vector_type(2)));
@@ -661,8 +661,6 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
   }
 }
 #undef OSSCAR_RUN_THREAD
-
-int64_t swap_run_shared_words() { return (int64_t)(sizeof(RunShared) / 8); }
 
 #define OSSCAR_RUN_KERNEL(GIVEN)                                                                               \
   (rows == 32 ? (const void*)swap_run_kernel<32, GIVEN> : rows == 64 ? (const void*)swap_run_kernel<64, GIVEN> \
