@@ -251,7 +251,7 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
   if (ds.target_output) gram_phase += align_up((size_t)d1 * m * 8 * g_copies_of(ds, extras)) + align_up(target_stage_bytes(m));
   auto init_bytes = [&](size_t a, size_t b) {   // kept rows a, candidate rows b
     return 4 * align_up(a * a * 4) + 3 * align_up(a * b * 4) + align_up(b * b * 4) + 4 * align_up(a * m * 4) + align_up(b * m * 4) +
-           align_up(10 * a * INV_NB * 4) + split_bytes(a, b, m) + i8_bytes(a, b, m) + 4096;
+           align_up(8 * a * INV_NB * 4) + split_bytes(a, b, m) + i8_bytes(a, b, m) + 4096;
   };
   size_t init_phase = init_bytes(kr, cr);
   if (ds.from_dense) {   // the nested schedule visits every kept-row count from d1 down to kr
@@ -591,7 +591,7 @@ InvBufs carve_inv(osscar_ctx* c, Carve& cv) {
   b.HKK = cv.take<float>(kr * kr); b.P = cv.take<float>(kr * kr);
   b.T1 = cv.take<float>(2 * kr * kr); b.T2 = b.T1 + kr * kr;      // together: the kr x kr float64 work matrix of the sweep inverse
   b.GK = cv.take<float>(kr * m); b.B = cv.take<float>(kr * m); b.T3 = cv.take<float>(kr * m); b.T4 = cv.take<float>(kr * m);
-  b.panels = cv.take<float>(10 * kr * INV_NB);                     // five panels of float64
+  b.panels = cv.take<float>(8 * kr * INV_NB);                      // four panels of float64
   return b;
 }
 

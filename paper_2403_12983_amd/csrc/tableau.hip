@@ -890,7 +890,7 @@ __global__ __launch_bounds__(512, 2) void sweep_update64_kernel(const double* __
 }
 
 // P (n x n float32, full) = H^-1 for the SPD H (n x n float32, leading dimension ldh; only its lower triangle is read).
-// A64: n x n float64 work matrix; panels: 5 n INV_NB float64; small: INV_NB^2 float64; notpd_flag as for spd_inverse_inplace.
+// A64: n x n float64 work matrix; panels: 4 n INV_NB float64; small: INV_NB^2 float64; notpd_flag as for spd_inverse_inplace.
 // With a side stream the panel work of step k + 1 (extract, 128 x 128 inverse, panel x block: 0.2 ms during which one
 // workgroup, then a few, have the chip to themselves) runs beside the bulk update of step k: the tiles the next panel is made
 // of (tile row and column k + 1) are updated first by a launch of their own, the pivot rows of step k are fixed, and the
@@ -917,7 +917,7 @@ hipError_t spd_inverse_f64(const float* H, int64_t ldh, int n, float* P, double*
   for (int t0 = 0, k = 0; t0 < n; t0 += INV_NB, k++) {
     const int w = (n - t0 < INV_NB) ? n - t0 : INV_NB;
     // operand panels alternate: the bulk update of step k - 1 may still be reading the other pair
-    double* panelDz = panels + (int64_t)(1 + 2 * (k & 1)) * n * INV_NB;
+    double* panelDz = panels + (int64_t)(2 * (k & 1)) * n * INV_NB;
     double* panelCz = panelDz + (int64_t)n * INV_NB;
     hipLaunchKernelGGL(panel_inverse64_kernel, dim3(rb + 1), dim3(IB_T), 0, s, A64, (int64_t)n, n, t0, w, panelCz, small, notpd_flag);
     hipLaunchKernelGGL(panel_times_block64_kernel, dim3((n + 15) / 16), dim3(256), 0, s, panelCz, small, n, w, panelDz);
