@@ -1,5 +1,7 @@
 """Kernels against plain float64 references at the sizes where their tilings can go wrong: edges of tiles and stages,
 remainders, the smallest and largest of each branch's range."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -624,6 +626,45 @@ def test_run_given_up_with_swaps_pending(p, m, k, swaps):
     assert ce["runs_given_up"] == 0 and ce["lookahead_misses"] > 0
     assert c["runs_given_up"] == 1 and c["runs"] >= 3
     _same_swaps(r, e, Wr, We, Sr, Se)
+
+
+def test_two_searches_at_once():
+    """Two contexts on two streams and two threads, each with runs that want every compute unit: whether or not a run is given up for it, the
+    swaps are those of a launch each with the GPU to itself.  Bounds as above."""
+    pkg = _pkg()
+    p, m, k, swaps = 8192, 64, 4096, 300
+    solvers, alone, both = [], [], [[], []]
+    for seed in (1, 2):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            g = torch.Generator(device=DEV).manual_seed(seed)
+            X = torch.randn(1024, p, generator=g, device=DEV) * torch.exp(0.5 * torch.randn(p, generator=g, device=DEV))
+            W = torch.randn(p, m, generator=g, device=DEV) / p ** 0.5
+            s = pkg.Solver(p, m, p, 1, k, swaps, torch.float32, torch.float32, DEV)
+            s.osscar_gram(X, True, W, 0.0, 5e-2)
+        s.osscar_init_support()
+        alone.append((s.osscar_local_search(swaps, 0.0, pkg.OSSCAR_SEARCH_LAUNCH_PER_SWAP), s.osscar_backsolve()))
+        solvers.append(s)
+    together = threading.Barrier(2, timeout=60)
+
+    def work(i):
+        for _ in range(4):
+            solvers[i].osscar_init_support()
+            together.wait()
+            r = solvers[i].osscar_local_search(swaps)
+            both[i].append((r, solvers[i].osscar_get_counters(), solvers[i].osscar_backsolve()))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for s in solvers:
+        s.close()
+    for (e, (We, Se, _)), calls in zip(alone, both):
+        assert len(calls) == 4
+        for r, c, (Wr, Sr, _) in calls:
+            assert c["runs"] > 0
+            _same_swaps(r, e, Wr, We, Sr, Se)
 
 
 @pytest.mark.parametrize("target", [False, True])
