@@ -301,7 +301,7 @@ int32_t osscar_debug_tile_schedule(int64_t d1, int32_t* out_host, int32_t capaci
  *   H = X^T X + lambda I (float32, d1 x d1, both triangles), lambda = lambda_abs + lambda_rel * mean(diag(X^T X)),
  *   G = H W (float32, d1 x m), c0 = Tr(W^T G); products accumulated in float64.
  * X_dev: dev, row-major n x d1 (leading dimension ldx), dtype x_dtype; W_dev: dev, d1 x m (ldw), dtype w_dtype;
- * H_dev, G_dev: dev outputs, dense (leading dimensions d1 and m); scalars_dev: dev, 2 float64 = {lambda, c0}.
+ * H_dev, G_dev: dev outputs, dense (leading dimensions d1 and m), G_dev may lie where W_dev does; scalars_dev: dev, 2 float64 = {lambda, c0}.
  * Everything is enqueued on hip_stream (a hipStream_t, NULL = default stream); the call does not wait for it and
  * calls no hipMalloc, hipFree or other allocating routine.  What osscar_gram keeps in the caller's workspace meanwhile
  * (float64 accumulator, partial tiles, scalars) lives in a device array of OSSCAR_STATIC_SCRATCH_BYTES that

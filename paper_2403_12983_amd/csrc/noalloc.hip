@@ -99,7 +99,8 @@ extern "C" osscar_status osscar_gram_static(const void* X_dev, int64_t n, int64_
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   double* H64 = reinterpret_cast<double*>(base);
   // the partial tiles of cut contractions take what the accumulator leaves in front of the scalars
-  const size_t h_bytes = ((size_t)d1 * d1 * 8 + 255) / 256 * 256, part_bytes = ST_H64 + ST_PART - h_bytes;
+  const size_t h_bytes = ((size_t)d1 * d1 * 8 + 255) / 256 * 256;
+  size_t part_bytes = ST_H64 + ST_PART - h_bytes;
   double* part = reinterpret_cast<double*>(base + h_bytes);
   double* scal = reinterpret_cast<double*>(base + ST_H64 + ST_PART);      // 64 scalars, then 2048 partial sums
   double* partial = scal + 64;
@@ -120,7 +121,16 @@ extern "C" osscar_status osscar_gram_static(const void* X_dev, int64_t n, int64_
   // The call's time is the chain of its launches (nine of them took 52 us for 4096 rows of 288 columns, six take 41): the ridge is formed where H is,
   // W is read as it comes, and one launch forms c0 = Tr(W^T G) and the two results.
   if (e == hipSuccess) e = launch_finalize_ridge(H64, H_dev, D, lambda_abs, lambda_rel, scal + 1, s, done);
-  const bool wbf = w_dtype == OSSCAR_BF16;
+  bool wbf = w_dtype == OSSCAR_BF16;
+  {      // W where G goes: a float32 copy of it, in front of the partial tiles
+    const char *w = reinterpret_cast<const char*>(W_dev), *g = reinterpret_cast<const char*>(G_dev);
+    if (w < g + (size_t)d1 * m * 4 && g < w + ((size_t)(d1 - 1) * ldw + m) * (wbf ? 2 : 4)) {
+      const size_t copy_bytes = ((size_t)d1 * m * 4 + 255) / 256 * 256;
+      if (e == hipSuccess) e = launch_convert_to_f32(W_dev, wbf, d1, m, ldw, reinterpret_cast<float*>(part), s);
+      W_dev = part; ldw = m; wbf = false;
+      part = reinterpret_cast<double*>(base + h_bytes + copy_bytes); part_bytes -= copy_bytes;
+    }
+  }
   if (e == hipSuccess) {
     Gemm64 g{};      // G = H W (H is symmetric: its rows serve as the columns that the product contracts)
     g.M = D; g.N = M; g.K = D; g.A = H_dev; g.lda = D; g.a_kind = OPK_K_F32; g.B = W_dev; g.ldb = ldw; g.b_kind = wbf ? OPK_K_BF16 : OPK_K_F32;

@@ -50,6 +50,28 @@ def test_small_tile_float64_products(dtype, n, d1, m, pad):
     assert abs(sc[1].item() - np.sum(Wd * Gr)) <= 1e-7 * np.sum(np.abs(Wd * Gr))
 
 
+@pytest.mark.parametrize("d1,m", [(64, 64), (288, 64), (191, 130), (1024, 1024)])
+def test_static_gram_with_the_weights_where_g_goes(d1, m):
+    """G may take the place of W: the same result as with a buffer of its own, up to the float64 sums' order (other ranges of the contraction:
+    G the same to float32's rounding, 6e-8 of an entry, c0 through it)."""
+    g = torch.Generator(device=DEV).manual_seed(d1)
+    X = torch.randn(512, d1, generator=g, device=DEV)
+    for dtype in (torch.float32, torch.bfloat16):
+        out = []
+        for in_place in (False, True):
+            g.manual_seed(m)
+            G = torch.empty(d1, m, device=DEV)
+            W = G.view(-1).view(dtype)[:d1 * m].view(d1, m) if in_place else torch.empty(d1, m, dtype=dtype, device=DEV)
+            W.copy_(torch.randn(d1, m, generator=g, device=DEV))
+            H, sc = torch.empty(d1, d1, device=DEV), torch.empty(2, dtype=torch.float64, device=DEV)
+            _pkg().osscar_gram_static(X, W, H, G, sc, 1e-3, 1e-2)
+            torch.cuda.synchronize()
+            out.append((H, G, sc))
+        (H0, G0, s0), (H1, G1, s1) = out
+        assert torch.equal(H0, H1) and torch.allclose(G1, G0, rtol=1.2e-7, atol=1e-9 * G0.abs().max().item())
+        assert s1[0] == s0[0] and abs(s1[1] - s0[1]) <= 1e-7 * abs(s0[1])
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_patch_rows_in_several_pieces(dtype):
     """float32 maps (and bf16 maps whose patch width is no multiple of eight) write their patches out as rows, as many as the
