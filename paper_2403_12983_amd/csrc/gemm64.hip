@@ -233,10 +233,13 @@ static int gemm64_tiles(int M, int N, int lower) {
   return lower ? tm * (tm + 1) / 2 : tm * tn;
 }
 
-// Ranges of the contraction.  A stage of 32 k takes a workgroup that has its compute unit to itself about 1.9 us (the way of
-// its loads), two or three that share one 3.1 us together, more 0.95 us each (the matrix cores), so the time of a launch follows from the
-// workgroups on the fullest unit and the stages of one; adding the ranges up costs a second launch and the write and read of
-// their tiles (32 KB each at about 3 TB/s).  (4096 rows of 288 columns, 15 tiles, whole quadratic form: 17 ranges 41.3 us, 22 45.4, 32 43.6.)
+// Ranges of the contraction.  A stage of 32 k takes a workgroup that has its compute unit to itself about 1.7 us (the way of
+// its loads) and every further one on the unit 0.9 - 1.05 us more (the matrix cores; two 2.65, three 3.6, four 4.7), so the time of a
+// launch follows from the workgroups on the fullest unit and the stages of one; adding the ranges up costs a second launch and the
+// write and read of their tiles (32 KB each).  Numbers of ranges timed one by one for 175 products (1 to 1128 tiles, K from 144 to 65536, all
+// operand kinds): this rule is 0.8 % from the best on average.  With two and three workgroups on a unit at the same cost it was 3.5 %, and
+// up to 23 % (1024 to 65536 rows of 440 to 640 columns, whose ranges then put three on a unit: 512 columns, 16384 rows 132 us in 16 ranges,
+// 115 in 14); with no cost for the second one 3.1 %, up to 22 % (288 columns, 4096 rows 29.9 us in 22 ranges, 26.2 in 16).
 static int gemm64_splits(int tiles, int K, size_t ws_bytes) {
   const int stages = std::max(1, (K + KS - 1) / KS);
   const int cap = (int)std::min<size_t>((size_t)stages, ws_bytes / ((size_t)tiles * 4096 * 8));
@@ -246,8 +249,8 @@ static int gemm64_splits(int tiles, int K, size_t ws_bytes) {
     const int per = (stages + sp - 1) / sp, used = (stages + per - 1) / per;
     if (used != sp) continue;
     const int on_unit = (tiles * sp + 255) / 256;
-    const double us = (on_unit == 1 ? 1.9 : std::max(3.1, 0.95 * on_unit)) * per + (sp > 1 ? 5.0 + 0.0218 * tiles * sp : 0.0);
-    if (us < best_us * 0.97) { best_us = us; best = sp; }
+    const double us = (1.75 + 0.9 * (on_unit - 1)) * per + (sp > 1 ? 3.0 + 0.018 * tiles * sp : 0.0);
+    if (us < best_us * 0.98) { best_us = us; best = sp; }
   }
   return best;
 }
