@@ -152,11 +152,11 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
   const float* const N0 = A.N0;
   const int d1 = P->d1, nwg = P->nwg, run = P->run;
   OSSCAR_RUN_THREAD;
-  int limit = P->limit;
+  int limit = P->cin->stalled ? 0 : P->limit;      // (a launch before this one was given up: the host goes on)
   // ---- the state as the last launch left it
   int tau = P->cin->tau, iters = P->cin->iters, done = P->cin->done, pause = P->cin->pause, notpd = P->cin->notpd, accepted = 0;
   const int spare = P->cin->spare, tau_start = tau;
-  if (done | pause | P->cin->stalled) limit = iters;      // (a launch before this one was given up: the host goes on)
+  if (done | pause) limit = iters;
   if (tid < TM) { const bool in = tid < tau; s_T[tid] = in ? P->Tidx[tid] : 0; s_slot[tid] = in ? P->tslot[tid] : 0; s_sign[tid] = in && P->Jsg[tid] > 0.f ? 1 : -1; }
   if (tid == 0) {
     s_flag = 0; s_late = 0; s_rec = P->rec[wg]; s_obj[iters & 1] = P->cin->obj;
@@ -633,7 +633,15 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
   if (!counts) {      // the state as it was
     if (wg == 0 && tid == 0) { SearchCtrl c = *E->cin; c.stalled = 1; *E->cout = c; }
     if (tid == 0) E->rec2[wg] = E->rec[wg];
-    tau = tau_start;
+    const int tw = min(TM, (tau_start + 31) & ~31);
+    for (int u = wg; u < 16; u += nwg) {      // (a loop of its own: beside the results it sent 40 of their registers to memory)
+      const int r = 4 * rq + u / 4, c = 32 * (u % 4) + 2 * l;
+      if (r < tw && c < tw) {
+        *reinterpret_cast<d2*>(E->Minv2 + r * TM + c) = *reinterpret_cast<const d2*>(E->Minv + r * TM + c);
+        *reinterpret_cast<d2*>(E->LL2 + r * TM + c) = *reinterpret_cast<const d2*>(E->LL + r * TM + c);
+      }
+    }
+    return;
   }
   const int tw = min(TM, (tau + 31) & ~31);
 #pragma unroll
@@ -641,12 +649,10 @@ __global__ __launch_bounds__(RT) void swap_run_kernel(const RunArgs A) {
 #pragma unroll
     for (int v = 0; v < 4; v++) {
       const int r = 4 * rq + i, c = 32 * v + 2 * l;
-      if ((i * 4 + v) % nwg == wg) {
-        if (r < tw && c < tw) *reinterpret_cast<d2*>(E->Minv2 + r * TM + c) = counts ? mv[i][v] : *reinterpret_cast<const d2*>(E->Minv + r * TM + c);
-        if (r < tw && c < tw) *reinterpret_cast<d2*>(E->LL2 + r * TM + c) = counts ? lv[i][v] : *reinterpret_cast<const d2*>(E->LL + r * TM + c);
+      if ((i * 4 + v) % nwg == wg && r < tw && c < tw) {
+        *reinterpret_cast<d2*>(E->Minv2 + r * TM + c) = mv[i][v]; *reinterpret_cast<d2*>(E->LL2 + r * TM + c) = lv[i][v];
       }
     }
-  if (!counts) return;
   if (tid == 0) E->rec2[wg] = s_rec;
   if (swapped && has_row) { E->rho[row] = s_rho[lrow]; E->diag[row] = s_diag[lrow]; E->score[row] = s_score[lrow]; E->kept[row] = s_kept[lrow]; E->pos[row] = s_pos[lrow]; }
   if (wg == 0) {
