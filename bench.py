@@ -24,7 +24,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 # HBM-side bytes per launch on cfg5 from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a 1 GiB copy
 # (profiles/gemm_f64acc_cfg5_pmc.md: mean over the launches of one layer; profiles/gram_wide_cfg5_pmc.md: one chunk)
-GEMM64_TRAFFIC_CFG5 = 2.99e7
+GEMM64_TRAFFIC_CFG5 = 3.05e7
 GRAM_TRAFFIC_CFG5 = 41.6e9
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
@@ -332,7 +332,7 @@ def main():
                                 "bound": "mfma", "achieved": gram_flops / phases["gram"] / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
                                 "frac": gram_flops / phases["gram"] / 1e12 / 2500.0,
                                 "note": "algorithmic SYRK flops n*d1*(d1+1); the kernel issues 2x that on diagonal tiles only"},
-        "search_iteration": ({"note": "per swap: one launch (selection and pivot algebra in every workgroup, from the Gram matrix of the candidate rows; "
+        "search_iteration": ({"note": "many swaps per launch (selection and pivot algebra in every workgroup, from the Gram matrix of the candidate rows; "
                                       "acceptance test; update of norms/diagonal/scores from the products computed ahead); every 64 swaps a flush by matrix "
                                       "products plus one look-ahead product Zc Z^T.  An eager in-place up/downdate of P, B, V, R would "
                                       "move bytes_per_swap_eager per swap",

@@ -246,7 +246,8 @@ Layout carve_all(const osscar_desc& ds, void* base, osscar_ctx* c, bool extras) 
     L.bD = cv.take<double>(LAZY_BT * LAZY_BT); L.bYY = cv.take<double>(LAZY_BT * LAZY_BT);
     L.bG = cv.take<int32_t>(LAZY_BT);
   }
-  // scratch: the larger of the Gram phase and the init / refresh / backsolve phase
+  // scratch: the larger of the Gram phase and the init / refresh / backsolve phase.  The Gram phase: accumulators, staged rows and d1 m floats
+  // for the parts of tiles that are cut along the rows (gram.hip: launch_queued takes all that is left)
   size_t gram_phase = align_up((size_t)d1 * d1 * 8 * h_copies_of(ds, extras)) + align_up((size_t)d1 * m * 4) + align_up(gram_stage_bytes(d1));
   if (ds.target_output) gram_phase += align_up((size_t)d1 * m * 8 * g_copies_of(ds, extras)) + align_up(target_stage_bytes(m));
   auto init_bytes = [&](size_t a, size_t b) {   // kept rows a, candidate rows b

@@ -7,10 +7,11 @@
 // memory past the XCDs' L2 caches: words of 32 bits beside the number of the exchange, so that a word tells by itself whether it has
 // arrived, in two buffers that change place (a workgroup writes exchange e + 2 after it has read all of e + 1, which nobody sends before
 // reading all of e).
-// Bound by latency: the exchange (between 256 workgroups 1.4 us if the first look comes when the words are there, 3 - 5 us if it comes too
-// early: the looks then stand in the words' way; so every wave waits as long as its looks have lately had to), one round trip for the
-// pivots' rows and products (0.9 us), the solve (0.8 us, 1.7 with 128 pending pivots), the rows' update (1.1 us), four barriers.  A swap,
-// launches and prologues included: 6.7 us at 8192 x 512 and 3001 x 1003 (a launch each: 11.5), 9.1 at 16384 x 256 (15), 11.3 at 28672 x 512 (20).
+// Bound by latency.  By cycle counts of the wave that sends the record (profiles/swap_kernels_pmc.md), at 8192 x 2048 (28672 x 512): from one record
+// sent to the next pair picked 1.9 us (3.6), the pivots' rows and products 1.8 (2.4), the solve 1.4 (1.6), the rows' sums 1.25 (2.1), their
+// norms and scores and the record 1.45 (2.1), barriers included; waves wait for 0.6 of their cycles.  A look at the records that comes too early
+// costs more than it gains (the looks stand in the words' way), so every wave waits as long as its looks have lately had to.  A swap, launches
+// and prologues included: 6.8 us at 8192 x 512, 8.7 at 16384 x 256, 10.9 - 11.3 at 28672 x 512 (a launch each: 11.5, 15, 20).
 // A launch each pays for the records, M^-1 and the rows to come from memory each time, and for the launch.
 //
 // No workgroup waits for ever.  One that has waited `patience` gives up, and all of them then agree (arrived, verdict) whether the run
